@@ -242,6 +242,13 @@ int collect_experience(gmi_t gmi, gmi_buffer_t buf, int32_t t, const float* obs,
 int rollout_collect(gmi_t gmi, gmi_model_t model, gmi_env_t env, gmi_buffer_t buf, float* obs,
                     uint64_t seed, uint32_t step0, uint32_t env_offset, float* last_value);
 
+/* The same stage for F32 models (rollout_collect refuses them): same arithmetic and Philox counters as agent_act,
+ * env_step and collect_experience called step by step (sums in a fixed order of their own), one launch.
+ * GMI_ERR_UNSUPPORTED and nothing has run: the model is not F32, its 16-env tile does not fit the on-chip memory, or the
+ * instance runs one launch per layer (gmi_set_fusion). */
+int rollout_collect_f32(gmi_t gmi, gmi_model_t model, gmi_env_t env, gmi_buffer_t buf, float* obs,
+                        uint64_t seed, uint32_t step0, uint32_t env_offset, float* last_value);
+
 /* Generalized advantage estimation over the horizon, then returns, then optional normalisation:
  *   delta_t = r_t + gamma v_{t+1} (1-d_t) - v_t (v_T = last_value),  A_t = delta_t + gamma lambda (1-d_t) A_{t+1}
  *   ret = A + v;  normalize != 0: A <- (A - mean) / (std + 1e-8) over all T*N entries.

@@ -25,7 +25,7 @@ EXPORTS = [
     "agent_act", "agent_value", "gmi_fp8_bind", "gmi_fp8_refresh", "gmi_fp8_destroy", "agent_act_fp8", "gmi_buffer_bind", "gmi_buffer_destroy", "collect_experience",
     "gae_compute", "gae_compute_static", "ppo_update", "ppo_evaluate", "ppo_gradient", "adam_update", "gmi_noise_fill",
     "gmi_permutation", "gmi_profile_enable", "gmi_profile_classes", "gmi_profile_class_name", "gmi_profile_read",
-    "gmi_measure_peak", "gmi_bench_linear", "gmi_bench_gae_variant", "gmi_set_fusion", "rollout_collect", "gmi_profile_work", "gmi_explore", "ppo_update_group", "gmi_select_reduction",
+    "gmi_measure_peak", "gmi_bench_linear", "gmi_bench_gae_variant", "gmi_set_fusion", "rollout_collect", "rollout_collect_f32", "gmi_profile_work", "gmi_explore", "ppo_update_group", "gmi_select_reduction",
     "gmi_har_leaders", "gmi_reduction_time", "gmi_channels_create", "gmi_channels_destroy", "gmi_channels_push",
     "gmi_channels_pop", "gmi_channels_drop", "gmi_channels_count", "gmi_route_least_loaded",
 ]
@@ -104,6 +104,7 @@ def load_library(path: str = LIB_PATH) -> C.CDLL:
         "gmi_buffer_destroy": (C.c_int, [vp]),
         "collect_experience": (C.c_int, [vp, vp, i32, vp, vp, vp, vp, vp, vp]),
         "rollout_collect": (C.c_int, [vp, vp, vp, vp, vp, u64, u32, u32, vp]),
+        "rollout_collect_f32": (C.c_int, [vp, vp, vp, vp, vp, u64, u32, u32, vp]),
         "gae_compute": (C.c_int, [vp, vp, vp, f32, f32, C.c_int]),
         "gae_compute_static": (C.c_int, [vp, i32, i32, i32, vp, vp, vp, vp, f32, f32, C.c_int, vp, vp]),
         "ppo_update": (C.c_int, [vp, vp, vp, C.POINTER(PPOHparams), vp]),
@@ -334,6 +335,11 @@ def collect_experience(gmi: int, buf: int, t: int, obs, act, logp, value, reward
 def rollout_collect(gmi: int, model: int, env: int, buf: int, obs, seed: int, step0: int, env_offset: int,
                     last_value) -> None:
     _check(_lib.rollout_collect(gmi, model, env, buf, _ptr(obs), seed, step0, env_offset, _ptr(last_value)))
+
+
+def rollout_collect_f32(gmi: int, model: int, env: int, buf: int, obs, seed: int, step0: int, env_offset: int,
+                        last_value) -> None:
+    _check(_lib.rollout_collect_f32(gmi, model, env, buf, _ptr(obs), seed, step0, env_offset, _ptr(last_value)))
 
 
 def gae_compute(gmi: int, buf: int, last_value, gamma: float, lam: float, normalize: bool) -> None:

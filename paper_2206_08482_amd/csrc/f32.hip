@@ -1,0 +1,836 @@
+// Full-precision (fp32) networks, a row tile per workgroup: the agent's action decision, the experience collection of a
+// whole horizon, and a minibatch's forward pass, loss, backward pass and weight gradients -- one launch each (Section 3
+// of the paper, "DRL Agent" and "DRL Trainer").
+//
+// Products run on the fp32 matrix instruction (16x16x4: exact fp32 operands and sums, twice the vector unit's rate
+// without packed arithmetic).  A workgroup of 8 waves keeps its rows' activations in LDS, [row][feature] with
+// 16 m + 4 floats per row: a lane takes 4 consecutive features as one 16-byte read, and the four products of a 16-wide
+// k chunk use element j of every lane, i.e. k = 16 c + 4 g + j for lane group g (any order of k will do as long as both
+// operands share it); the rows' stride, an odd multiple of 4 floats, spreads the 8 lanes of a read phase over all banks.
+// Weights come straight from the parameter vector (row-major [out, in] at any alignment: a 16-byte load needs 4-byte
+// alignment only), four chunks ahead, or, where they fit beside the activations, from a zero-padded LDS copy made once
+// at the start (WL), so that a layer waits for LDS instead of for L2.
+//
+// Bound: small models by one launch and a chain of dependent LDS / L2 round trips per layer; large batches by the fp32
+// matrix instruction (157 TFLOP/s).  The one-thread-per-output kernels (mlp.hip) remain for gmi_set_fusion(.., 0) and for
+// models whose 16-row tile does not fit LDS; against them, measured: see the table in the design notes.
+#include <algorithm>
+
+#include "rollout.h"
+
+namespace {
+
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
+struct __attribute__((packed, aligned(4))) Float4U { float x, y, z, w; };      // 16-byte load at 4-byte alignment
+
+constexpr int kNT = 512, kNW = kNT / 64;
+constexpr size_t kLdsMax = 160 * 1024;
+constexpr int kMaxLayers = GMI_MAX_HIDDEN + 1;
+
+__host__ __device__ __forceinline__ constexpr int pad16(int x) { return (x + 15) & ~15; }
+__host__ __device__ __forceinline__ constexpr int rstride(int width) { return pad16(width) + 4; }      // floats of an LDS row
+
+struct F32Layer {
+  const float* w;      // [out, in]
+  const float* b;      // [out]
+  int in, out;
+  int w_off, b_off;    // floats from the start of the parameter vector
+};
+struct F32Net {
+  F32Layer l[kMaxLayers];
+};
+
+// Lanes of a wave that share one row of `width` floats: a power of two, at most 64.
+__device__ __forceinline__ int lanes_per_row(int width) {
+  int n = 16;
+  while (n < 64 && n < width) n <<= 1;
+  return n;
+}
+
+// Zero-padded LDS copies of a net's weights (if WL) and biases, layer after layer.
+template <bool WL>
+__device__ __forceinline__ void stage_net(const F32Net& N, int nl, float* s_w, float* s_b, int wave, int nw, int lane) {
+  for (int l = 0; l < nl; ++l) {
+    const F32Layer L = N.l[l];
+    const int op = pad16(L.out), ld = rstride(L.in);
+    for (int f = wave * 64 + lane; f < op; f += nw * 64) s_b[f] = f < L.out ? L.b[f] : 0.f;
+    s_b += op;
+    if constexpr (WL) {
+      const int lpr = lanes_per_row(ld), rpw = 64 / lpr, c0 = lane & (lpr - 1);
+#pragma unroll 4
+      for (int f = wave * rpw + lane / lpr; f < op; f += nw * rpw) {
+        const float* src = L.w + (int64_t)(f < L.out ? f : L.out - 1) * L.in;
+        for (int c = c0; c < ld; c += lpr) {
+          const float v = src[c < L.in ? c : L.in - 1];
+          s_w[f * ld + c] = (f < L.out && c < L.in) ? v : 0.f;
+        }
+      }
+      s_w += op * ld;
+    }
+  }
+}
+
+// acc[i] += sum over nchunk 16-wide k chunks of A (load(c): this lane's 4 values of chunk c) and of the NR row tiles at
+// xp, xp + xts (this lane's row and lane group: xp points at k = 4 g).  Four chunks of A are in flight.
+template <int NR, class LoadA>
+__device__ __forceinline__ void products(floatx4 (&acc)[NR], int nchunk, LoadA load, const float* xp, int xts) {
+  if (nchunk <= 0) return;
+  float4 a[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) a[u] = load(min(u, nchunk - 1));
+  auto step = [&](const float4& w, int c) {
+    float4 x[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) x[i] = *reinterpret_cast<const float4*>(xp + i * xts + 16 * c);
+#pragma unroll
+    for (int i = 0; i < NR; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.x, x[i].x, acc[i], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < NR; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.y, x[i].y, acc[i], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < NR; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.z, x[i].z, acc[i], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < NR; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.w, x[i].w, acc[i], 0, 0, 0);
+  };
+  int c = 0;
+  for (; c + 4 <= nchunk; c += 4) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float4 w = a[u];
+      a[u] = load(min(c + 4 + u, nchunk - 1));
+      step(w, c + u);
+    }
+  }
+  if (c < nchunk) step(a[0], c);
+  if (c + 1 < nchunk) step(a[1], c + 1);
+  if (c + 2 < nchunk) step(a[2], c + 2);
+}
+
+__device__ __forceinline__ float elu32(float z) { return z > 0.f ? z : expm1f(z); }
+__device__ __forceinline__ float elu_grad32(float h) { return h > 0.f ? 1.0f : h + 1.0f; }
+
+enum { kHidden = 0, kHead = 1, kGrad = 2 };
+
+// One tile of a layer for NR row tiles: 16 features from f0 of rows from row tile rt0.
+//   kHidden / kHead: y[r][f] = ELU(x W^T + b) / x W^T + b        kGrad: y[r][i] = (x W)[r][i] ELU'(h[r][i])
+// s_w: the layer's LDS copy (WL).  Padding features of y come out as zero.
+template <bool WL, int NR, int KIND>
+__device__ __forceinline__ void tile_product(const F32Layer& L, const float* s_w, const float* s_bias, const float* s_x,
+                                             int sx, const float* s_h, float* s_y, int sy, int f0, int rt0, int lane) {
+  const int j = lane & 15, g = lane >> 4;
+  const int ld = rstride(L.in);
+  floatx4 acc[NR];
+#pragma unroll
+  for (int i = 0; i < NR; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const float* xp = s_x + (rt0 * 16 + j) * sx + 4 * g;
+  const int F = KIND == kGrad ? L.in : L.out;            // features of y
+  const int f = f0 + j;                                   // operand A's feature of this lane
+  if constexpr (KIND != kGrad) {
+    if constexpr (WL) {
+      const float* wp = s_w + f * ld + 4 * g;
+      products<NR>(acc, pad16(L.in) >> 4, [&](int c) { return *reinterpret_cast<const float4*>(wp + 16 * c); }, xp, 16 * sx);
+    } else {
+      const float* wp = L.w + (int64_t)(f < F ? f : F - 1) * L.in;
+      const int nfull = L.in >> 4;
+      products<NR>(acc, nfull, [&](int c) {
+        const Float4U v = *reinterpret_cast<const Float4U*>(wp + 16 * c + 4 * g);
+        return make_float4(v.x, v.y, v.z, v.w);
+      }, xp, 16 * sx);
+      if (L.in & 15) {                                    // the ragged chunk: x is zero beyond `in`
+        products<NR>(acc, 1, [&](int) {
+          const int k = 16 * nfull + 4 * g;
+          return make_float4(wp[min(k, L.in - 1)], wp[min(k + 1, L.in - 1)], wp[min(k + 2, L.in - 1)], wp[min(k + 3, L.in - 1)]);
+        }, xp + 16 * nfull, 16 * sx);
+      }
+    }
+  } else {                                                // A = W^T: lane's feature = input i, k = output o
+    if constexpr (WL) {
+      const float* wp = s_w + f;
+      products<NR>(acc, pad16(L.out) >> 4, [&](int c) {
+        const float* p = wp + (16 * c + 4 * g) * ld;
+        return make_float4(p[0], p[ld], p[2 * ld], p[3 * ld]);
+      }, xp, 16 * sx);
+    } else {
+      const float* wp = L.w + (f < F ? f : F - 1);
+      products<NR>(acc, pad16(L.out) >> 4, [&](int c) {   // x is zero beyond `out`
+        const int o = 16 * c + 4 * g, m = L.out - 1;
+        return make_float4(wp[(int64_t)min(o, m) * L.in], wp[(int64_t)min(o + 1, m) * L.in], wp[(int64_t)min(o + 2, m) * L.in],
+                           wp[(int64_t)min(o + 3, m) * L.in]);
+      }, xp, 16 * sx);
+    }
+  }
+  // this lane's results: features f0 + 4 g + 0..3 of row j of each row tile
+  const int fr = f0 + 4 * g;
+  float4 bv = make_float4(0.f, 0.f, 0.f, 0.f);
+  if constexpr (KIND != kGrad) bv = *reinterpret_cast<const float4*>(s_bias + fr);
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    const int r = (rt0 + i) * 16 + j;
+    float o[4] = {acc[i][0] + bv.x, acc[i][1] + bv.y, acc[i][2] + bv.z, acc[i][3] + bv.w};
+    if constexpr (KIND == kHidden) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) o[v] = elu32(o[v]);
+    } else if constexpr (KIND == kGrad) {
+      const float4 h = *reinterpret_cast<const float4*>(s_h + r * sy + fr);
+      o[0] *= elu_grad32(h.x); o[1] *= elu_grad32(h.y); o[2] *= elu_grad32(h.z); o[3] *= elu_grad32(h.w);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) o[v] = fr + v < F ? o[v] : 0.f;
+    *reinterpret_cast<float4*>(s_y + r * sy + fr) = make_float4(o[0], o[1], o[2], o[3]);
+  }
+}
+
+// Tile items of a layer: feature tiles x groups of row tiles (pairs where there are enough tiles for every wave: a
+// weight operand then serves two products).
+__device__ __forceinline__ int pair_rows(int n_ft, int RT, int nw) { return RT >= 2 && n_ft * (RT / 2) >= nw ? 2 : 1; }
+
+template <bool WL, int KIND>
+__device__ __forceinline__ void layer(const F32Layer& L, const float* s_w, const float* s_bias, const float* s_x, int sx,
+                                      const float* s_h, float* s_y, int sy, int RT, int wave, int nw, int lane) {
+  const int n_ft = pad16(KIND == kGrad ? L.in : L.out) >> 4;
+  const int pr = pair_rows(n_ft, RT, nw);
+  for (int item = wave; item < n_ft * (RT / pr); item += nw) {
+    const int ft = item % n_ft, rg = item / n_ft;
+    if (pr == 2) tile_product<WL, 2, KIND>(L, s_w, s_bias, s_x, sx, s_h, s_y, sy, ft * 16, rg * 2, lane);
+    else tile_product<WL, 1, KIND>(L, s_w, s_bias, s_x, sx, s_h, s_y, sy, ft * 16, rg, lane);
+  }
+}
+
+// All layers of a net on the tile in s_x0; hidden activations ping-pong between s_a and s_b (stride sh); the head goes to
+// s_out (stride so).  `run`: whether these waves take part (every thread reaches every barrier).
+template <bool WL>
+__device__ __forceinline__ void net_forward(const F32Net& N, int nl, const float* s_w, const float* s_bias, const float* s_x0,
+                                            int sx0, float* s_a, float* s_b, int sh, float* s_out, int so, int RT, bool run,
+                                            int wave, int nw, int lane) {
+  const float* x = s_x0;
+  int sx = sx0;
+  float* y = s_a;
+  for (int l = 0; l < nl; ++l) {
+    const F32Layer L = N.l[l];
+    if (run) {
+      if (l < nl - 1) layer<WL, kHidden>(L, s_w, s_bias, x, sx, nullptr, y, sh, RT, wave, nw, lane);
+      else layer<WL, kHead>(L, s_w, s_bias, x, sx, nullptr, s_out, so, RT, wave, nw, lane);
+    }
+    __syncthreads();
+    if constexpr (WL) s_w += pad16(L.out) * rstride(L.in);
+    s_bias += pad16(L.out);
+    x = y;
+    sx = sh;
+    y = y == s_a ? s_b : s_a;
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Action decision: grid (row tiles, nets).
+struct AgentF32Args {
+  F32Net net[2];
+  const float* log_std;
+  const float* obs;
+  int nl, n, obs_dim, act_dim, R, net0, sh, w_floats, b_floats;
+  uint32_t k0, k1, step, env_offset;
+  float* act; float* logp; float* value; float* mu_out;
+};
+
+template <bool WL>
+__global__ __launch_bounds__(kNT) void agent_f32_kernel(AgentF32Args a) {
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  const int net = blockIdx.y + a.net0;
+  const F32Net& N = a.net[net];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int R = a.R, O = a.obs_dim, A = a.act_dim, sx0 = rstride(O), so = rstride(A), nba = (A + 3) >> 2;
+  float* s_w = smem;
+  float* s_bias = s_w + (WL ? a.w_floats : 0);
+  float* s_x0 = s_bias + a.b_floats;
+  float* s_a = s_x0 + R * sx0;
+  float* s_b = s_a + R * a.sh;
+  float* s_out = s_b + R * a.sh;
+  float* s_lp = s_out + R * so;
+  const int r0 = blockIdx.x * R;
+  {
+    const int lpr = lanes_per_row(sx0), rpw = 64 / lpr, c0 = lane & (lpr - 1);
+#pragma unroll 4
+    for (int r = wave * rpw + lane / lpr; r < R; r += kNW * rpw) {
+      const float* src = a.obs + (int64_t)min(r0 + r, a.n - 1) * O;
+      for (int c = c0; c < sx0; c += lpr) {
+        const float v = src[c < O ? c : O - 1];
+        s_x0[r * sx0 + c] = c < O ? v : 0.f;
+      }
+    }
+  }
+  stage_net<WL>(N, a.nl, s_w, s_bias, wave, kNW, lane);
+  __syncthreads();
+  net_forward<WL>(N, a.nl, s_w, s_bias, s_x0, sx0, s_a, s_b, a.sh, s_out, so, R / 16, true, wave, kNW, lane);
+  if (net == 1) {
+    for (int r = tid; r < R; r += kNT)
+      if (r0 + r < a.n) a.value[r0 + r] = s_out[r * so];
+    return;
+  }
+  // act = mu + exp(log_std) * eps; log-prob partial per block of 4 action elements
+  for (int item = tid; item < R * nba; item += kNT) {
+    const int r = item / nba, b = item - r * nba;
+    const int e = r0 + r;
+    float lp = 0.f;
+    if (e < a.n) {
+      float z[4];
+      gmi::normal_block(a.env_offset + (uint32_t)e, a.step, gmi::kStreamAction, (uint32_t)b, a.k0, a.k1, z);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int j = 4 * b + i;
+        if (j < A) {
+          const float ls = a.log_std[j];
+          const float m = s_out[r * so + j];
+          a.act[(int64_t)e * A + j] = fmaf(expf(ls), z[i], m);
+          if (a.mu_out) a.mu_out[(int64_t)e * A + j] = m;
+          lp += -0.5f * z[i] * z[i] - ls - 0.918938533204672742f;
+        }
+      }
+    }
+    s_lp[r * nba + b] = lp;
+  }
+  __syncthreads();
+  for (int r = tid; r < R; r += kNT) {
+    if (r0 + r >= a.n) continue;
+    float lp = 0.f;
+    for (int b = 0; b < nba; ++b) lp += s_lp[r * nba + b];
+    a.logp[r0 + r] = lp;
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Minibatch: grid (row-tile groups, nets).  A workgroup takes the row tiles blockIdx.x, + gridDim.x, ...; its weight
+// gradients go to row blockIdx.x of the partials (written for its first tile, accumulated in place for later ones) and
+// its statistics to row blockIdx.x of the statistics partials.
+struct TrainF32Args {
+  F32Net net[2];
+  const float* log_std;
+  const int32_t* idx;
+  const float *b_obs, *b_act, *b_logp, *b_adv, *b_ret;
+  int n_envs, ld_envs, obs_dim, act_dim, nl, rows, R, n_tiles, sdz, w_floats, b_floats;
+  int w_net[2];                // floats of each net's LDS weight copy (w_floats: the larger)
+  int h_off[kMaxLayers];       // floats from the start of the activation area
+  int h_floats;
+  float clip, c_v;
+  float* part; int64_t part_stride;
+  float* stat_part;
+};
+
+template <bool WL>
+__global__ __launch_bounds__(kNT) void train_f32_kernel(TrainF32Args a) {
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  const int net = blockIdx.y;
+  const F32Net& N = a.net[net];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int R = a.R, RT = R / 16, O = a.obs_dim, A = a.act_dim, sx0 = rstride(O), so = rstride(A), nl = a.nl;
+  float* s_w = smem;
+  float* s_bias = s_w + (WL ? a.w_floats : 0);
+  float* s_h = s_bias + a.b_floats;
+  float* s_dz0 = s_h + a.h_floats;
+  float* s_dz1 = s_dz0 + R * a.sdz;
+  float* s_out = s_dz1 + R * a.sdz;               // head outputs, then per-sample log_std gradient terms
+  float* s_act = s_out + R * so;                  // [R][A]
+  float* s_scal = s_act + ((R * A + 3) & ~3);     // [3][R] old log-prob, advantage, return
+  float* s_ls = s_scal + 3 * R;                   // [A] log_std, [A] exp(-log_std)
+  float* s_sum = s_ls + 2 * A;                    // [4] statistics, [A] log_std gradient, over all tiles
+  const float inv_m = 1.0f / (float)a.rows;
+  float* part = a.part + (int64_t)blockIdx.x * a.part_stride;
+
+  stage_net<WL>(N, nl, s_w, s_bias, wave, kNW, lane);
+  for (int j = tid; j < A; j += kNT) {
+    const float ls = a.log_std[j];
+    s_ls[j] = ls;
+    s_ls[A + j] = expf(-ls);
+  }
+  for (int j = tid; j < 4 + A; j += kNT) s_sum[j] = 0.f;
+
+  for (int tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
+    const int r0 = tile * R;
+    {   // gather: observation rows (zero padded; rows past the batch repeat its last sample, their gradient is zero)
+      const int lpr = lanes_per_row(sx0), rpw = 64 / lpr, c0 = lane & (lpr - 1);
+#pragma unroll 2
+      for (int r = wave * rpw + lane / lpr; r < R; r += kNW * rpw) {
+        const int s = a.idx[min(r0 + r, a.rows - 1)];
+        const int64_t slot = (int64_t)(s / a.n_envs) * a.ld_envs + (s % a.n_envs);
+        const float* src = a.b_obs + slot * O;
+        for (int c = c0; c < sx0; c += lpr) {
+          const float v = src[c < O ? c : O - 1];
+          s_h[r * sx0 + c] = c < O ? v : 0.f;
+        }
+        if (net == 0) {
+          for (int c = c0; c < A; c += lpr) s_act[r * A + c] = a.b_act[slot * A + c];
+          if (c0 == 0) { s_scal[r] = a.b_logp[slot]; s_scal[R + r] = a.b_adv[slot]; }
+        } else if (c0 == 0) {
+          s_scal[2 * R + r] = a.b_ret[slot];
+        }
+      }
+    }
+    __syncthreads();
+    {   // forward
+      const float* w = s_w;
+      const float* bias = s_bias;
+      for (int l = 0; l < nl; ++l) {
+        const F32Layer L = N.l[l];
+        const float* x = s_h + a.h_off[l];
+        if (l < nl - 1)
+          layer<WL, kHidden>(L, w, bias, x, rstride(L.in), nullptr, s_h + a.h_off[l + 1], rstride(L.out), RT, wave, kNW, lane);
+        else
+          layer<WL, kHead>(L, w, bias, x, rstride(L.in), nullptr, s_out, so, RT, wave, kNW, lane);
+        __syncthreads();
+        if constexpr (WL) w += pad16(L.out) * rstride(L.in);
+        bias += pad16(L.out);
+      }
+    }
+    // loss: one thread per sample (the first wave); the head's gradient rows into s_dz0, stride rstride(head width)
+    const int sd = rstride(N.l[nl - 1].out), wd = pad16(N.l[nl - 1].out);
+    if (wave == 0) {
+      const int r = lane;
+      const bool ok = r < R && r0 + r < a.rows;
+      float st[4] = {0.f, 0.f, 0.f, 0.f};           // policy term, value term, kl, clipped
+      if (r < R) {
+        if (net == 0) {
+          float lp = 0.f;
+          for (int j = 0; j < A; ++j) {
+            const float z = (s_act[r * A + j] - s_out[r * so + j]) * s_ls[A + j];
+            lp += -0.5f * z * z - s_ls[j] - 0.918938533204672742f;
+          }
+          float g_lp = 0.f;
+          if (ok) {
+            const float lo = s_scal[r], ad = s_scal[R + r];
+            const float ratio = expf(lp - lo);
+            const float u1 = ratio * ad;
+            const float u2 = fminf(fmaxf(ratio, 1.0f - a.clip), 1.0f + a.clip) * ad;
+            st[0] = -fminf(u1, u2);
+            st[2] = lo - lp;
+            st[3] = fabsf(ratio - 1.0f) > a.clip ? 1.f : 0.f;
+            g_lp = (u1 <= u2) ? -(ad * ratio) * inv_m : 0.f;
+          }
+          for (int j = 0; j < A; ++j) {
+            const float z = (s_act[r * A + j] - s_out[r * so + j]) * s_ls[A + j];
+            s_dz0[r * sd + j] = g_lp * z * s_ls[A + j];
+            s_out[r * so + j] = g_lp * (z * z - 1.0f);
+          }
+          for (int j = A; j < wd; ++j) s_dz0[r * sd + j] = 0.f;
+        } else {
+          float dv = 0.f;
+          if (ok) {
+            dv = s_out[r * so] - s_scal[2 * R + r];
+            st[1] = dv * dv;
+          }
+          s_dz0[r * sd] = 2.0f * a.c_v * dv * inv_m;
+          for (int j = 1; j < wd; ++j) s_dz0[r * sd + j] = 0.f;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float v = st[q];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+        if (lane == 0) s_sum[q] += v;
+      }
+    }
+    __syncthreads();
+    if (net == 0)
+      for (int j = tid; j < A; j += kNT) {
+        float v = 0.f;
+        for (int r = 0; r < R; ++r) v += s_out[r * so + j];
+        s_sum[4 + j] += v;
+      }
+    // backward, head to first layer: the input gradient of layer l and, by the waves left over, its weight gradient
+    const float* dz = s_dz0;
+    float* dn = s_dz1;
+    const float* w = s_w + (WL ? a.w_net[net] : 0);
+    const bool first = tile == (int)blockIdx.x;
+    for (int l = nl - 1; l >= 0; --l) {
+      const F32Layer L = N.l[l];
+      const int sz = rstride(L.out), shl = rstride(L.in);
+      const float* h = s_h + a.h_off[l];
+      if constexpr (WL) w -= pad16(L.out) * rstride(L.in);
+      const int n_it = pad16(L.in) >> 4, n_ot = pad16(L.out) >> 4;
+      const int pr = pair_rows(n_it, RT, kNW);
+      const int n_grad = l > 0 ? n_it * (RT / pr) : 0, n_items = n_grad + n_it * n_ot;
+      const int j = lane & 15, g = lane >> 4;
+      for (int item = wave; item < n_items; item += kNW) {
+        if (item < n_grad) {
+          const int ft = item % n_it, rg = item / n_it;
+          if (pr == 2) tile_product<WL, 2, kGrad>(L, w, nullptr, dz, sz, h, dn, shl, ft * 16, rg * 2, lane);
+          else tile_product<WL, 1, kGrad>(L, w, nullptr, dz, sz, h, dn, shl, ft * 16, rg, lane);
+        } else {
+          // dW[o][i] = sum_r dz[r][o] h[r][i]: operands straight from the rows (lane = feature, lane group = row)
+          const int it = (item - n_grad) % n_it, ot = (item - n_grad) / n_it;
+          const float* zp = dz + g * sz + ot * 16 + j;
+          const float* hp = h + g * shl + it * 16 + j;
+          const int i = it * 16 + j, o = ot * 16 + 4 * g;
+          float* dst = part + L.w_off + (int64_t)o * L.in + i;
+          float* db = part + L.b_off + o;
+          floatx4 acc = {0.f, 0.f, 0.f, 0.f}, accb = {0.f, 0.f, 0.f, 0.f};
+          if (!first) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              if (o + v < L.out && i < L.in) acc[v] = dst[(int64_t)v * L.in];
+              if (it == 0 && o + v < L.out) accb[v] = db[v];
+            }
+          }
+#pragma unroll 4
+          for (int r = 0; r < R; r += 4) {
+            const float x = zp[r * sz], y = hp[r * shl];
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, acc, 0, 0, 0);
+            if (it == 0) accb = __builtin_amdgcn_mfma_f32_16x16x4f32(x, 1.0f, accb, 0, 0, 0);
+          }
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            if (o + v < L.out && i < L.in) dst[(int64_t)v * L.in] = acc[v];
+            if (it == 0 && j == 0 && o + v < L.out) db[v] = accb[v];
+          }
+        }
+      }
+      __syncthreads();
+      float* t = const_cast<float*>(dz);
+      dz = dn;
+      dn = t;
+    }
+  }
+  // this workgroup's statistics (the slots of the other net belong to the other net's workgroup)
+  float* out = a.stat_part + (int64_t)blockIdx.x * (gmi::kStatStride + A);
+  if (net == 0) {
+    if (tid == 0) { out[0] = s_sum[0]; out[3] = s_sum[2]; out[4] = s_sum[3]; }
+    if (tid == 1) {
+      float ent = 0.f;
+      if (blockIdx.x == 0)
+        for (int j = 0; j < A; ++j) ent += s_ls[j] + 1.418938533204672742f;
+      out[2] = ent;
+      out[5] = out[6] = out[7] = 0.f;
+    }
+    for (int j = tid; j < A; j += kNT) out[gmi::kStatStride + j] = s_sum[4 + j];
+  } else if (tid == 0) {
+    out[1] = s_sum[1];
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Experience collection of a whole horizon (see rollout_fused_kernel, fused.hip, whose phases this kernel has with fp32
+// networks): waves 0-3 run the policy net, waves 4-7 the value net.
+struct RolloutF32Args : RolloutEnv {
+  F32Net net[2];
+  int nl, sh, w_floats[2], b_floats[2], mt_lds;
+};
+
+template <bool WL>
+__global__ __launch_bounds__(kNT) void rollout_f32_kernel(RolloutF32Args a) {
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int half = __builtin_amdgcn_readfirstlane(tid >> 8), wave4 = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);
+  const int R = a.rows_per_wg, O = a.obs_dim, A = a.act_dim, OA = O + A, o4 = a.o4, nbo = o4 >> 2, nba = (A + 3) >> 2;
+  const int npr = nba + nbo + 1, sx0 = rstride(O), so = rstride(A);
+  float* s_w = smem;
+  float* s_bias = s_w + (WL ? a.w_floats[0] + a.w_floats[1] : 0);
+  float* s_x0 = s_bias + a.b_floats[0] + a.b_floats[1];
+  float* s_hid = s_x0 + R * sx0;                                   // [2 nets][2][R][sh]
+  float* s_mu = s_hid + 4 * R * a.sh;                              // [R][so]
+  float* s_val = s_mu + R * so;                                    // [R][rstride(1)]
+  float* s_next = s_val + R * rstride(1);                          // [R][o4]
+  float4* s_noise2 = reinterpret_cast<float4*>(s_next + R * o4);   // [2][R][npr]
+  float* s_in = reinterpret_cast<float*>(s_noise2 + 2 * R * npr);  // [R][O + A] state | action
+  float* s_lp = s_in + ((R * OA + 3) & ~3);                        // [R][nba]
+  float* s_part = s_lp + R * nba;                                  // [R][nbo]
+  int* s_done = reinterpret_cast<int*>(s_part + R * nbo);          // [R]
+  float* s_mt = reinterpret_cast<float*>(s_done + R);              // [O + A][o4] when mt_lds
+  const F32Net& N = a.net[half];
+  const float* s_wn = s_w + (half ? a.w_floats[0] : 0);
+  const float* s_bn = s_bias + (half ? a.b_floats[0] : 0);
+  float* s_a = s_hid + half * 2 * R * a.sh;
+  float* s_b = s_a + R * a.sh;
+
+  {
+    float* w = s_w + (half && WL ? a.w_floats[0] : 0);
+    float* b = s_bias + (half ? a.b_floats[0] : 0);
+    stage_net<WL>(N, a.nl, w, b, wave4, 4, lane);
+  }
+  if (a.mt_lds)
+    for (int i = tid; i < OA * nbo; i += kNT) reinterpret_cast<float4*>(s_mt)[i] = reinterpret_cast<const float4*>(a.m_t)[i];
+  const float4* mt_lds_ptr = reinterpret_cast<const float4*>(s_mt);
+  const float4* mt_glb_ptr = reinterpret_cast<const float4*>(a.m_t);
+
+  for (int tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
+    const int r0 = tile * R;
+    for (int i = tid; i < R * O; i += kNT) {
+      const int r = i / O, k = i - r * O;
+      s_in[r * OA + k] = (r0 + r < a.n) ? a.obs_state[(int64_t)(r0 + r) * O + k] : 0.f;
+    }
+    const int dtid = tid - (kNT - 64);        // the last wave carries the episode counters
+    uint32_t ep = 0;
+    if (dtid >= 0 && dtid < R && r0 + dtid < a.n) ep = a.episode_step[r0 + dtid];
+    draw_items(a, s_noise2, a.step0, R, r0, npr, nba, nbo, tid, kNT);
+    __syncthreads();
+    for (int i = tid; i < R * sx0; i += kNT) {
+      const int r = i / sx0, k = i - r * sx0;
+      s_x0[i] = k < O ? s_in[r * OA + k] : 0.f;
+    }
+    __syncthreads();
+    for (int t = 0; t <= a.T; ++t) {
+      net_forward<WL>(N, a.nl, s_wn, s_bn, s_x0, sx0, s_a, s_b, a.sh, half ? s_val : s_mu, half ? rstride(1) : so, R / 16,
+                      half == 1 || t < a.T, wave4, 4, lane);
+      if (t == a.T) {
+        if (tid < R && r0 + tid < a.n) a.last_value[r0 + tid] = s_val[tid * rstride(1)];
+        break;
+      }
+      const float4* s_noise = s_noise2 + (t & 1) * R * npr;
+      const uint32_t step = a.step0 + (uint32_t)t;
+      const int64_t slot0 = (int64_t)t * a.ld_envs + r0;
+      for (int item = tid; item < R * nba * 4; item += kNT) {
+        const int blk = item >> 2, i = item & 3;
+        const int r = blk / nba, b = blk - r * nba;
+        const int j = 4 * b + i;
+        float term = 0.f;
+        if (j < A) {
+          float act = 0.f;
+          if (r0 + r < a.n) {
+            const float z = reinterpret_cast<const float*>(s_noise + r * npr + b)[i];
+            const float ls = a.log_std[j];
+            act = fmaf(expf(ls), z, s_mu[r * so + j]);
+            a.b_act[(slot0 + r) * A + j] = act;
+            term = -0.5f * z * z - ls - 0.918938533204672742f;
+          }
+          s_in[r * OA + O + j] = act;
+        }
+        float lp = term;
+        lp += __shfl_down(term, 1, 64);
+        lp += __shfl_down(term, 2, 64);
+        lp += __shfl_down(term, 3, 64);
+        if (i == 0) s_lp[blk] = lp;
+      }
+      // the step's observations, last threads first (the first ones have the action items)
+      for (int i = kNT - 1 - tid; i < R * O; i += kNT) {
+        const int r = i / O, k = i - r * O;
+        if (r0 + r < a.n) a.b_obs[(slot0 + r) * O + k] = s_in[r * OA + k];
+      }
+      if (dtid >= 0 && dtid < R) {
+        int d = 0;
+        if (r0 + dtid < a.n) {
+          if (a.done_period > 0) d = ((ep + 1u) % a.done_period) == 0u;
+          else d = __float_as_uint(s_noise[dtid * npr + nba + nbo].x) < a.done_threshold;
+          ep = d ? 0u : ep + 1u;
+          a.b_done[slot0 + dtid] = (uint8_t)d;
+          a.b_val[slot0 + dtid] = s_val[dtid * rstride(1)];
+        }
+        s_done[dtid] = d;
+      }
+      __syncthreads();
+      if (tid < R && r0 + tid < a.n) {
+        float lp = 0.f;
+        for (int b = 0; b < nba; ++b) lp += s_lp[tid * nba + b];
+        a.b_logp[slot0 + tid] = lp;
+      }
+      // the next step's draws, last threads first (the simulator's items go to the first ones)
+      if (t + 1 < a.T)
+        draw_items(a, s_noise2 + ((t + 1) & 1) * R * npr, step + 1u, R, r0, npr, nba, nbo, kNT - 1 - tid, kNT);
+      const bool four = (R / 4) * nbo >= 192;
+      if (a.mt_lds) {
+        if (four) sim_items<4>(a, R, r0, step, s_in, mt_lds_ptr, s_part, s_next, s_done, s_noise, npr, nba);
+        else sim_items<1>(a, R, r0, step, s_in, mt_lds_ptr, s_part, s_next, s_done, s_noise, npr, nba);
+      } else {
+        if (four) sim_items<4>(a, R, r0, step, s_in, mt_glb_ptr, s_part, s_next, s_done, s_noise, npr, nba);
+        else sim_items<1>(a, R, r0, step, s_in, mt_glb_ptr, s_part, s_next, s_done, s_noise, npr, nba);
+      }
+      __syncthreads();
+      if (dtid >= 0 && dtid < R && r0 + dtid < a.n) {
+        float sum = 0.f;
+        for (int b = 0; b < nbo; ++b) sum += s_part[dtid * nbo + b];
+        a.b_rew[slot0 + dtid] = -a.reward_scale * sum;
+      }
+      for (int i = tid; i < R * O; i += kNT) {
+        const int r = i / O, k = i - r * O;
+        const float v = r0 + r < a.n ? s_next[r * o4 + k] : 0.f;
+        s_in[r * OA + k] = v;
+        s_x0[r * sx0 + k] = v;
+      }
+      __syncthreads();
+    }
+    for (int i = tid; i < R * O; i += kNT) {
+      const int r = i / O, k = i - r * O;
+      if (r0 + r < a.n) a.obs_state[(int64_t)(r0 + r) * O + k] = s_in[r * OA + k];
+    }
+    if (dtid >= 0 && dtid < R && r0 + dtid < a.n) a.episode_step[r0 + dtid] = ep;
+    __syncthreads();
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+void fill_net(const gmi_model* m, int net, F32Net* N, int* w_floats, int* b_floats) {
+  *w_floats = *b_floats = 0;
+  for (int l = 0; l < m->L.n_layers; ++l) {
+    const LayerInfo& li = m->L.net[net][l];
+    N->l[l] = F32Layer{m->params + li.w_off, m->params + li.b_off, li.in, li.out, (int)li.w_off, (int)li.b_off};
+    *w_floats += pad16(li.out) * rstride(li.in);
+    *b_floats += pad16(li.out);
+  }
+}
+int max_hidden(const ModelLayout& L) {
+  int w = 0;
+  for (int l = 0; l < L.n_hidden; ++l) w = std::max(w, L.net[0][l].out);
+  return w;
+}
+template <class K>
+int allow_lds(K kernel, bool* done) {
+  if (!*done) {
+    GMI_HIP(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
+    *done = true;
+  }
+  return GMI_OK;
+}
+
+size_t train_lds(const ModelLayout& L, int R, int w_floats, int b_floats) {
+  size_t n = (size_t)w_floats + b_floats;
+  int sdz = 0;
+  for (int l = 0; l < L.n_layers; ++l) {
+    n += (size_t)R * rstride(L.net[0][l].in);
+    sdz = std::max(sdz, rstride(L.net[0][l].out));
+  }
+  const int A = L.act_dim;
+  n += (size_t)R * (2 * sdz + rstride(A)) + ((R * A + 3) & ~3) + 3 * R + 2 * A + 4 + A;
+  return 4 * n;
+}
+
+}  // namespace
+
+namespace gmi {
+
+// Rows of gradient partials that the fp32 trainer kernel may fill: at most 128 (one workgroup per net and compute unit),
+// and no more than about 64 MB of them.
+int f32_part_rows(const ModelLayout& L) {
+  const int64_t n = ((int64_t)64 << 20) / (4 * L.n_params);
+  return (int)std::min<int64_t>(128, std::max<int64_t>(n, 1));
+}
+
+int launch_agent_f32(gmi_instance* g, gmi_model* m, const float* obs, int n, uint64_t seed, uint32_t step,
+                     uint32_t env_offset, float* act, float* logp, float* value, float* mu_out, bool do_policy) {
+  const ModelLayout& L = m->L;
+  if (L.dtype != GMI_DTYPE_F32) return GMI_ERR_UNSUPPORTED;
+  AgentF32Args a;
+  int wf[2], bf[2];
+  for (int net = 0; net < 2; ++net) fill_net(m, net, &a.net[net], &wf[net], &bf[net]);
+  a.nl = L.n_layers; a.n = n; a.obs_dim = L.obs_dim; a.act_dim = L.act_dim;
+  a.sh = rstride(max_hidden(L));
+  a.w_floats = std::max(wf[0], wf[1]);
+  a.b_floats = std::max(bf[0], bf[1]);
+  auto lds = [&](int R, bool wl) {
+    return 4 * ((size_t)(wl ? a.w_floats : 0) + a.b_floats +
+                (size_t)R * (rstride(L.obs_dim) + 2 * a.sh + rstride(L.act_dim) + (L.act_dim + 3) / 4));
+  };
+  // the tallest tile that still gives every compute unit a workgroup of each net
+  int R = 64;
+  while (R > 16 && (lds(R, false) > kLdsMax || (n + R - 1) / R < g->cu_count / 2)) R >>= 1;
+  if (lds(R, false) > kLdsMax) return GMI_ERR_UNSUPPORTED;
+  // the LDS copy of the weights where two workgroups still share a compute unit
+  const bool wl = lds(R, true) <= kLdsMax / 2;
+  a.R = R;
+  a.net0 = do_policy ? 0 : 1;
+  a.log_std = m->params + L.logstd_off;
+  a.obs = obs;
+  a.k0 = (uint32_t)seed; a.k1 = (uint32_t)(seed >> 32); a.step = step; a.env_offset = env_offset;
+  a.act = act; a.logp = logp; a.value = value; a.mu_out = mu_out;
+  static bool attr[2] = {false, false};
+  const int rc = wl ? allow_lds(agent_f32_kernel<true>, &attr[1]) : allow_lds(agent_f32_kernel<false>, &attr[0]);
+  if (rc != GMI_OK) return rc;
+  ProfScope ps(g, kClsFusedAgent);
+  const dim3 grid((n + R - 1) / R, 2 - a.net0);
+  if (wl) ps.launch(agent_f32_kernel<true>, grid, dim3(kNT), lds(R, true), a);
+  else ps.launch(agent_f32_kernel<false>, grid, dim3(kNT), lds(R, false), a);
+  GMI_LAUNCH_CHECK();
+  return GMI_OK;
+}
+
+int launch_train_f32(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_hparams* hp, const int32_t* idx, int rows,
+                     int* n_parts) {
+  const ModelLayout& L = m->L;
+  if (L.dtype != GMI_DTYPE_F32 || L.n_params >= (1ll << 31)) return GMI_ERR_UNSUPPORTED;
+  TrainF32Args a;
+  int wf[2], bf[2];
+  for (int net = 0; net < 2; ++net) fill_net(m, net, &a.net[net], &wf[net], &bf[net]);
+  a.w_floats = std::max(wf[0], wf[1]);
+  a.w_net[0] = wf[0]; a.w_net[1] = wf[1];
+  a.b_floats = std::max(bf[0], bf[1]);
+  // the tallest tile that fits and still gives each of the device's compute units a workgroup (not the instance's: replicas
+  // of one model on several instances reduce partials of one common count)
+  int R = 64;
+  while (R > 16 && (train_lds(L, R, 0, a.b_floats) > kLdsMax || (rows + R - 1) / R < 128)) R >>= 1;
+  if (train_lds(L, R, 0, a.b_floats) > kLdsMax) return GMI_ERR_UNSUPPORTED;
+  const bool wl = train_lds(L, R, a.w_floats, a.b_floats) <= kLdsMax;
+  a.R = R;
+  a.nl = L.n_layers; a.rows = rows; a.obs_dim = L.obs_dim; a.act_dim = L.act_dim;
+  a.n_tiles = (rows + R - 1) / R;
+  a.sdz = 0;
+  int off = 0;
+  for (int l = 0; l < L.n_layers; ++l) {
+    a.h_off[l] = off;
+    off += R * rstride(L.net[0][l].in);
+    a.sdz = std::max(a.sdz, rstride(L.net[0][l].out));
+  }
+  a.h_floats = off;
+  a.log_std = m->params + L.logstd_off;
+  a.idx = idx;
+  a.b_obs = b->d.obs; a.b_act = b->d.act; a.b_logp = b->d.logp; a.b_adv = b->d.adv; a.b_ret = b->d.ret;
+  a.n_envs = b->d.n_envs; a.ld_envs = b->d.ld_envs;
+  a.clip = hp->clip; a.c_v = hp->c_v;
+  a.part = m->grad_part; a.part_stride = L.n_params;
+  a.stat_part = m->stat_part;
+  const int groups = std::min(a.n_tiles, m->part_rows);
+  static bool attr[2] = {false, false};
+  const int rc = wl ? allow_lds(train_f32_kernel<true>, &attr[1]) : allow_lds(train_f32_kernel<false>, &attr[0]);
+  if (rc != GMI_OK) return rc;
+  *n_parts = groups;
+  ProfScope ps(g, kClsChainTrain);
+  if (wl) ps.launch(train_f32_kernel<true>, dim3(groups, 2), dim3(kNT), train_lds(L, R, a.w_floats, a.b_floats), a);
+  else ps.launch(train_f32_kernel<false>, dim3(groups, 2), dim3(kNT), train_lds(L, R, 0, a.b_floats), a);
+  GMI_LAUNCH_CHECK();
+  return GMI_OK;
+}
+
+}  // namespace gmi
+
+extern "C" int rollout_collect_f32(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_buffer_t b, float* obs, uint64_t seed,
+                                   uint32_t step0, uint32_t env_offset, float* last_value) {
+  if (!valid(g)) GMI_FAIL(GMI_ERR_BAD_HANDLE, "rollout_collect_f32: bad instance");
+  if (!valid(m)) GMI_FAIL(GMI_ERR_BAD_HANDLE, "rollout_collect_f32: bad model");
+  if (!valid(env)) GMI_FAIL(GMI_ERR_BAD_HANDLE, "rollout_collect_f32: bad env");
+  if (!valid(b)) GMI_FAIL(GMI_ERR_BAD_HANDLE, "rollout_collect_f32: bad buffer");
+  const ModelLayout& L = m->L;
+  const int rc = check_rollout("rollout_collect_f32", m, env, b);
+  if (rc != GMI_OK) return rc;
+  if (b->d.n_envs == 0 || b->d.horizon == 0) return GMI_OK;
+  if (!obs || !last_value) GMI_FAIL(GMI_ERR_INVALID_ARG, "rollout_collect_f32: NULL pointer");
+  if (L.dtype != GMI_DTYPE_F32) GMI_FAIL(GMI_ERR_UNSUPPORTED, "rollout_collect_f32: F32 models only; use rollout_collect");
+  if (!g->fusion) GMI_FAIL(GMI_ERR_UNSUPPORTED, "rollout_collect_f32: the instance runs one launch per layer");
+  RolloutF32Args a;
+  fill_rollout_env(m, env, b, obs, seed, step0, env_offset, last_value, &a);
+  a.log_std = m->params + L.logstd_off;
+  for (int net = 0; net < 2; ++net) fill_net(m, net, &a.net[net], &a.w_floats[net], &a.b_floats[net]);
+  a.nl = L.n_layers;
+  a.sh = rstride(max_hidden(L));
+  const int O = L.obs_dim, A = L.act_dim, nba = (A + 3) / 4, nbo = a.o4 / 4, npr = nba + nbo + 1;
+  auto lds = [&](int R, bool wl, bool mt) {
+    return 4 * ((size_t)(wl ? a.w_floats[0] + a.w_floats[1] : 0) + a.b_floats[0] + a.b_floats[1] +
+                (size_t)R * (rstride(O) + 4 * a.sh + rstride(A) + rstride(1) + a.o4 + 8 * npr + nba + nbo + 1) +
+                ((R * (O + A) + 3) & ~3) + (mt ? (size_t)(O + A) * a.o4 : 0));
+  };
+  // 32 envs per workgroup once that still gives every compute unit one
+  const int R = (a.n + 31) / 32 >= g->cu_count && lds(32, false, false) <= kLdsMax ? 32 : 16;
+  if (lds(R, false, false) > kLdsMax)
+    GMI_FAIL(GMI_ERR_UNSUPPORTED, "rollout_collect_f32: a 16-env tile of this model needs %zu bytes of LDS (limit %zu); "
+             "use agent_act / env_step / collect_experience", lds(R, false, false), kLdsMax);
+  // what stays on chip for all steps: the networks' weights first (read by every layer), then the simulator's matrix
+  const bool wl = lds(R, true, false) <= kLdsMax;
+  a.mt_lds = lds(R, wl, true) <= kLdsMax ? 1 : 0;
+  const size_t bytes = lds(R, wl, a.mt_lds != 0);
+  a.rows_per_wg = R;
+  a.n_tiles = (a.n + R - 1) / R;
+  static bool attr[2] = {false, false};
+  const int rc2 = wl ? allow_lds(rollout_f32_kernel<true>, &attr[1]) : allow_lds(rollout_f32_kernel<false>, &attr[0]);
+  if (rc2 != GMI_OK) return rc2;
+  // no more workgroups than the instance's compute units hold at once (see rollout_collect)
+  int per_cu = (int)(kLdsMax / bytes);
+  if (per_cu > 2) per_cu = 2;
+  const int grid = std::min(a.n_tiles, std::max(per_cu, 1) * g->cu_count);
+  gmi::ProfScope ps(g, gmi::kClsFusedRollout);
+  if (wl) ps.launch(rollout_f32_kernel<true>, dim3(grid), dim3(kNT), bytes, a);
+  else ps.launch(rollout_f32_kernel<false>, dim3(grid), dim3(kNT), bytes, a);
+  GMI_LAUNCH_CHECK();
+  return GMI_OK;
+}

@@ -5,6 +5,7 @@
 // sampling epilogue.
 #include "internal.h"
 #include "rng.h"
+#include "rollout.h"
 
 namespace {
 
@@ -278,107 +279,16 @@ __global__ __launch_bounds__(256) void agent_fused_kernel(AgentArgs a) {
 // Gaussian sampling), records the experience slot, and advances the linear-Gaussian simulator; after the last
 // step it evaluates the bootstrap value of the final state.  Arithmetic and Philox counters are those of
 // agent_act / env_step / collect_experience called step by step.
-struct RolloutArgs {
+struct RolloutArgs : RolloutEnv {
   FusedNet net[2];
-  const float* log_std;
-  float* obs_state;                 // [n, O]: in = state before the first step, out = state after the last
-  const float* m_t;                 // [(O + A), o4] transposed env matrices
-  uint32_t* episode_step;           // [n]
-  int n, obs_dim, obs_pad, act_dim, max_h, o4, T, ld_envs;
-  int rows_per_wg;                  // envs owned by a workgroup: the tile height, or half of it
-  int n_tiles;                      // ceil(n / rows_per_wg); the grid may be smaller (workgroups loop)
-  float noise_std, reward_scale;
-  uint32_t done_period, done_threshold;
-  uint32_t ak0, ak1, a_env_offset;  // agent's Philox key and env offset
-  uint32_t ek0, ek1, e_env_offset;  // simulator's
-  uint32_t step0;
+  int obs_pad, max_h;
   int mt_lds;                       // m_t: 2 = LDS copy kept for the whole launch, 1 = LDS copy made at every
                                     // step in the (then idle) hidden-activation space, 0 = read from global
   int obs_vec;                      // 1 = observation rows are whole 16-byte pieces in the buffer and in the LDS tile
   int noise_ahead;                  // 1 = the waves without simulator items make step t+1's random draws while the
                                     // others run step t's simulator (two buffers at byte ahead_off of the LDS)
   int ahead_off;
-  float* b_obs; float* b_act; float* b_logp; float* b_val; float* b_rew; uint8_t* b_done;
-  float* last_value;
 };
-
-// Simulator step for the tile: items (group of EPT envs, block of 4 state elements).  mt points at the
-// transposed matrices (LDS copy or global), row stride nbo float4.
-template <int EPT>
-__device__ __forceinline__ void sim_items(const RolloutArgs& a, int R, int r0, uint32_t step, const float* s_in,
-                                          const float4* mt, float* s_part, float* s_next, const int* s_done,
-                                          const float4* s_noise, int npr, int nba) {
-  const int O = a.obs_dim, A = a.act_dim, OA = O + A, o4 = a.o4, nbo = o4 >> 2;
-  for (int item = threadIdx.x; item < (R / EPT) * nbo; item += blockDim.x) {
-    const int g = item / nbo, b = item - g * nbo;
-    const float* xin = s_in + (g * EPT) * OA;
-    const float4* mrow = mt + b;
-    float acc[EPT][4];
-#pragma unroll
-    for (int i = 0; i < EPT; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-    // eight matrix rows (and state elements) are fetched before the first of their products: left to the
-    // compiler under this kernel's register pressure, every k waited a full LDS round trip for its row
-    int k = 0;
-    for (; k + 8 <= OA; k += 8) {
-      float4 m[8];
-      float xv[EPT][8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) m[u] = mrow[(k + u) * nbo];
-#pragma unroll
-      for (int i = 0; i < EPT; ++i)
-#pragma unroll
-        for (int u = 0; u < 8; ++u) xv[i][u] = xin[i * OA + k + u];
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-#pragma unroll
-        for (int i = 0; i < EPT; ++i) {
-          acc[i][0] = fmaf(xv[i][u], m[u].x, acc[i][0]);
-          acc[i][1] = fmaf(xv[i][u], m[u].y, acc[i][1]);
-          acc[i][2] = fmaf(xv[i][u], m[u].z, acc[i][2]);
-          acc[i][3] = fmaf(xv[i][u], m[u].w, acc[i][3]);
-        }
-    }
-    for (; k < OA; ++k) {
-      const float4 m = mrow[k * nbo];
-#pragma unroll
-      for (int i = 0; i < EPT; ++i) {
-        const float x = xin[i * OA + k];
-        acc[i][0] = fmaf(x, m.x, acc[i][0]);
-        acc[i][1] = fmaf(x, m.y, acc[i][1]);
-        acc[i][2] = fmaf(x, m.z, acc[i][2]);
-        acc[i][3] = fmaf(x, m.w, acc[i][3]);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) {
-      const int r = g * EPT + i;
-      float ps = 0.f, pa = 0.f;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int o = 4 * b + j;
-        if (o < O) { const float x = xin[i * OA + o]; ps = fmaf(x, x, ps); }
-      }
-      for (int q = b; q < A; q += nbo) { const float x = xin[i * OA + O + q]; pa = fmaf(x, x, pa); }
-      s_part[r * nbo + b] = ps + 0.01f * pa;
-      const int e = r0 + r;
-      float z[4] = {0.f, 0.f, 0.f, 0.f};
-      float outv[4];
-      if (s_done[r]) {
-        if (e < a.n) gmi::normal_block(a.e_env_offset + (uint32_t)e, step, gmi::kStreamReset, (uint32_t)b, a.ek0, a.ek1, z);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) outv[j] = z[j];
-      } else {
-        const float4 zn = s_noise[r * npr + nba + b];       // drawn at the top of the step
-        z[0] = zn.x; z[1] = zn.y; z[2] = zn.z; z[3] = zn.w;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) outv[j] = fmaf(a.noise_std, z[j], acc[i][j]);
-      }
-      *reinterpret_cast<float4*>(&s_next[r * o4 + 4 * b]) = make_float4(outv[0], outv[1], outv[2], outv[3]);
-    }
-  }
-}
 
 // ------------------------------------------------------------------------------------------------
 // Weight-stationary form of the layers, for model shapes whose share of the weights fits a wave's registers:
@@ -705,25 +615,6 @@ bool ws_matches(const ModelLayout& L) {
     for (int l = 0; l < WS::NL; ++l)
       if (L.net[net][l].in_pad != WS::dim(l) || L.net[net][l].out_pad != WS::dim(l + 1)) return false;
   return true;
-}
-
-// Random blocks first, first + stride, ... of one step of a tile, one float4 per (env, block): nba action-noise
-// blocks, nbo env-noise blocks, then the done draw (raw word in .x).
-__device__ __forceinline__ void draw_items(const RolloutArgs& a, float4* dst, uint32_t stp, int Rv, int r0, int npr, int nba,
-                                           int nbo, int first, int stride) {
-  for (int item = first; item < Rv * npr; item += stride) {
-    const int r = item / npr, q = item - r * npr;
-    const uint32_t e = (uint32_t)(r0 + r < a.n ? r0 + r : a.n - 1);
-    const bool is_act = q < nba, is_env = q >= nba && q < nba + nbo;
-    const uint32_t strm = is_act ? gmi::kStreamAction : (is_env ? gmi::kStreamEnv : gmi::kStreamDone);
-    const uint32_t blk = is_act ? (uint32_t)q : (is_env ? (uint32_t)(q - nba) : 0u);
-    const gmi::Words4 w = gmi::philox4x32_10((is_act ? a.a_env_offset : a.e_env_offset) + e, stp, strm, blk,
-                                             is_act ? a.ak0 : a.ek0, is_act ? a.ak1 : a.ek1);
-    float z0, z1, z2, z3;
-    gmi::normal_pair(w.w[0], w.w[1], z0, z1);
-    gmi::normal_pair(w.w[2], w.w[3], z2, z3);
-    dst[item] = (is_act || is_env) ? make_float4(z0, z1, z2, z3) : make_float4(__uint_as_float(w.w[0]), 0.f, 0.f, 0.f);
-  }
 }
 
 // 512 threads: waves 0-3 run the policy net and waves 4-7 the value net at the same time (the two nets
@@ -1143,12 +1034,9 @@ extern "C" int rollout_collect(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_buffer
   if (!valid(env)) GMI_FAIL(GMI_ERR_BAD_HANDLE, "rollout_collect: bad env");
   if (!valid(b)) GMI_FAIL(GMI_ERR_BAD_HANDLE, "rollout_collect: bad buffer");
   const ModelLayout& L = m->L;
-  const gmi_env_desc& ed = env->d;
   const gmi_buffer_desc& bd = b->d;
-  if (ed.obs_dim != L.obs_dim || ed.act_dim != L.act_dim || bd.obs_dim != L.obs_dim || bd.act_dim != L.act_dim)
-    GMI_FAIL(GMI_ERR_BAD_SHAPE, "rollout_collect: model, env and buffer disagree on obs_dim / act_dim");
-  if (ed.n_envs != bd.n_envs)
-    GMI_FAIL(GMI_ERR_BAD_SHAPE, "rollout_collect: env has %d envs, buffer %d", ed.n_envs, bd.n_envs);
+  const int shape_rc = check_rollout("rollout_collect", m, env, b);
+  if (shape_rc != GMI_OK) return shape_rc;
   if (bd.n_envs == 0 || bd.horizon == 0) return GMI_OK;
   if (!obs || !last_value) GMI_FAIL(GMI_ERR_INVALID_ARG, "rollout_collect: NULL pointer");
   if (L.dtype != GMI_DTYPE_BF16)
@@ -1178,23 +1066,12 @@ extern "C" int rollout_collect(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_buffer
   fill_net(m, 0, &a.net[0]);
   fill_net(m, 1, &a.net[1]);
   a.log_std = reinterpret_cast<const float*>(m->shadow + L.sh_logstd);
-  a.obs_state = obs;
-  a.m_t = env->m_t;
-  a.episode_step = env->episode_step;
-  a.n = n; a.obs_dim = L.obs_dim; a.obs_pad = gmi::pad32(L.obs_dim); a.act_dim = L.act_dim;
+  fill_rollout_env(m, env, b, obs, seed, step0, env_offset, last_value, &a);
+  a.obs_pad = gmi::pad32(L.obs_dim);
   a.max_h = 32;
   for (int l = 0; l < L.n_hidden; ++l) a.max_h = L.net[0][l].out_pad > a.max_h ? L.net[0][l].out_pad : a.max_h;
-  a.o4 = (L.obs_dim + 3) & ~3;
-  a.T = bd.horizon; a.ld_envs = bd.ld_envs;
-  a.noise_std = ed.noise_std; a.reward_scale = ed.reward_scale;
-  a.done_period = ed.done_period; a.done_threshold = ed.done_threshold;
-  a.ak0 = (uint32_t)seed; a.ak1 = (uint32_t)(seed >> 32); a.a_env_offset = env_offset;
-  a.ek0 = (uint32_t)ed.seed; a.ek1 = (uint32_t)(ed.seed >> 32); a.e_env_offset = ed.env_offset;
-  a.step0 = step0;
   a.mt_lds = mt_mode;
   a.obs_vec = (L.obs_dim % 4 == 0 && (L.obs_dim + L.act_dim) % 4 == 0 && ((uintptr_t)bd.obs & 15) == 0) ? 1 : 0;
-  a.b_obs = bd.obs; a.b_act = bd.act; a.b_logp = bd.logp; a.b_val = bd.val; a.b_rew = bd.rew; a.b_done = bd.done;
-  a.last_value = last_value;
   size_t lds = rollout_lds_bytes(m, R, mt_lds);
   // fewer 32-env tiles than compute units: 16 envs per workgroup use twice as many of them
   const int rows_per_wg = (R == 32 && (n + 31) / 32 < g->cu_count && n > 16) ? 16 : R;

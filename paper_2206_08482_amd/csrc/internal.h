@@ -172,9 +172,10 @@ struct gmi_model {
   float* val;       // [max_rows]
   // minibatch gathers
   float *mb_act, *mb_logp, *mb_adv, *mb_ret;
-  // gradient partials [n_split_max, n_params] and stats partials
+  // gradient partials [part_rows, n_params] and stats partials
   float* grad_part;
-  int n_split_max;
+  int n_split_max;  // most row splits of a weight-gradient launch
+  int part_rows;    // rows of grad_part (at least n_split_max)
   float* stat_part; // [n_split_max, 8]
 };
 
@@ -277,6 +278,13 @@ int forward_nets(gmi_instance* g, gmi_model* m, int rows, bool policy, bool valu
 int launch_agent_fused(gmi_instance* g, gmi_model* m, const float* obs, int n, uint64_t seed, uint32_t step,
                        uint32_t env_offset, float* act, float* logp, float* value, float* mu_out, bool do_policy);
 
+// The fp32 one-launch kernels (f32.hip); GMI_ERR_UNSUPPORTED (no message) where a 16-row tile does not fit LDS.
+int launch_agent_f32(gmi_instance* g, gmi_model* m, const float* obs, int n, uint64_t seed, uint32_t step,
+                     uint32_t env_offset, float* act, float* logp, float* value, float* mu_out, bool do_policy);
+// Forward, loss, backward and weight gradients of a minibatch: *n_parts rows of m->grad_part and of m->stat_part.
+int launch_train_f32(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_hparams* hp, const int32_t* idx, int rows,
+                     int* n_parts);
+int f32_part_rows(const ModelLayout& L);
 
 // Shuffles of epochs epoch0 .. epoch0 + n_epochs - 1 into out[e][n], one launch.
 constexpr int kPermEpochs = 8;

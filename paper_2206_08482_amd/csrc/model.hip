@@ -1,5 +1,7 @@
 // Policy / value model: parameter layout, bf16 shadow, workspace, forward driver, and the agent role's
 // action decision (Section 3 of the paper, "DRL Agent"; model shapes as in its Table 6).
+#include <algorithm>
+
 #include "internal.h"
 #include "rng.h"
 
@@ -325,6 +327,8 @@ extern "C" int gmi_model_bind(gmi_t g, const gmi_model_desc* d, float* params, v
       for (int l = 0; l < L.n_layers; ++l)
         n_tiles += ((L.net[net][l].out_pad + 127) / 128) * ((L.net[net][l].in_pad + 127) / 128);
     m->n_split_max = gmi::wgrad_split_limit(n_tiles);
+    m->part_rows = m->n_split_max;
+    if (L.dtype == GMI_DTYPE_F32 && adam_m) m->part_rows = std::max(m->part_rows, gmi::f32_part_rows(L));
   }
 
   const int64_t rows = d->max_rows;
@@ -358,7 +362,7 @@ extern "C" int gmi_model_bind(gmi_t g, const gmi_model_desc* d, float* params, v
     m->mb_logp = (float*)take(rows * 4);
     m->mb_adv = (float*)take(rows * 4);
     m->mb_ret = (float*)take(rows * 4);
-    m->grad_part = (float*)take((int64_t)m->n_split_max * L.n_params * 4);
+    m->grad_part = (float*)take((int64_t)m->part_rows * L.n_params * 4);
     m->stat_part = (float*)take((int64_t)(gmi::kLossBlocksMax + 1) * (gmi::kStatStride + A) * 4);
     if (pass == 0) {
       m->ws_bytes = (size_t)off;
@@ -414,7 +418,9 @@ extern "C" int agent_act(gmi_t g, gmi_model_t m, const float* obs, int32_t n_row
   if (n_rows == 0) return GMI_OK;
   if (!obs || !act || !logp || !value) GMI_FAIL(GMI_ERR_INVALID_ARG, "agent_act: NULL pointer");
   if (g->fusion) {
-    rc = gmi::launch_agent_fused(g, m, obs, n_rows, seed, step, env_offset, act, logp, value, mu, true);
+    rc = gmi::launch_agent_f32(g, m, obs, n_rows, seed, step, env_offset, act, logp, value, mu, true);
+    if (rc == GMI_ERR_UNSUPPORTED)
+      rc = gmi::launch_agent_fused(g, m, obs, n_rows, seed, step, env_offset, act, logp, value, mu, true);
     if (rc != GMI_ERR_UNSUPPORTED) return rc;
   }
   rc = g->fusion ? gmi::launch_forward_chain(g, m, obs, n_rows, m->mu, value) : GMI_ERR_UNSUPPORTED;
@@ -437,7 +443,8 @@ extern "C" int agent_value(gmi_t g, gmi_model_t m, const float* obs, int32_t n_r
   if (n_rows == 0) return GMI_OK;
   if (!obs || !value) GMI_FAIL(GMI_ERR_INVALID_ARG, "agent_value: NULL pointer");
   if (g->fusion) {
-    rc = gmi::launch_agent_fused(g, m, obs, n_rows, 0, 0, 0, nullptr, nullptr, value, nullptr, false);
+    rc = gmi::launch_agent_f32(g, m, obs, n_rows, 0, 0, 0, nullptr, nullptr, value, nullptr, false);
+    if (rc == GMI_ERR_UNSUPPORTED) rc = gmi::launch_agent_fused(g, m, obs, n_rows, 0, 0, 0, nullptr, nullptr, value, nullptr, false);
     if (rc != GMI_ERR_UNSUPPORTED) return rc;
   }
   rc = g->fusion ? gmi::launch_forward_chain(g, m, obs, n_rows, nullptr, value) : GMI_ERR_UNSUPPORTED;

@@ -442,6 +442,12 @@ int minibatch_pass(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_h
   const bool bf = L.dtype == GMI_DTYPE_BF16;
   int rc = GMI_ERR_UNSUPPORTED;
   bool blocks = false;
+  if (g->fusion >= 1 && want_grad && !bf) {
+    // fp32: everything up to the gradient partials in one launch
+    rc = gmi::launch_train_f32(g, m, b, hp, idx, rows, n_split_out);
+    if (rc == GMI_OK) { *n_loss_blocks_out = *n_split_out; return GMI_OK; }
+    if (rc != GMI_ERR_UNSUPPORTED) return rc;
+  }
   if (rc == GMI_ERR_UNSUPPORTED && g->fusion >= 1 && want_grad && bf) {
     // register-chained kernel (gather + forward + loss + input gradients in one launch) where this shape has one
     rc = gmi::launch_train_chain(g, m, b, hp, idx, rows, n_loss_blocks_out, obs16_ready, &blocks);

@@ -13,7 +13,7 @@ from . import (DTYPE_BF16, DTYPE_F32, agent_act, agent_value, buffer_desc, colle
                env_step, gae_compute, gmi_buffer_bind, gmi_buffer_destroy, gmi_create, gmi_destroy,
                gmi_env_bind, gmi_env_destroy, gmi_model_bind, gmi_model_destroy, gmi_model_refresh_shadow,
                gmi_model_shadow_bytes, gmi_stream, gmi_sync, gmi_wait_stream, model_desc, ppo_hparams, ppo_update,
-               rollout_collect, GmiError, ERR_UNSUPPORTED, ppo_update_group)
+               rollout_collect, rollout_collect_f32, GmiError, ERR_UNSUPPORTED, ppo_update_group)
 
 
 def dtype_code(name: str) -> int:
@@ -105,6 +105,7 @@ class PPOSession:
         self.done = torch.zeros(n_envs, dtype=torch.uint8, device=dev)
         self.last_value = torch.zeros(n_envs, **f)
         self.fused_rollout = fused_rollout and dtype == "bf16"
+        self.fused_rollout_f32 = fused_rollout and dtype == "f32"
         gmi_wait_stream(self.gmi)      # the fills above (torch's stream) come before anything queued on the instance
 
     # -- stage (i): experience collection
@@ -119,6 +120,15 @@ class PPOSession:
                 if e.code != ERR_UNSUPPORTED:
                     raise
                 self.fused_rollout = False      # this model does not fit the one-launch kernel
+        if self.fused_rollout_f32:
+            try:
+                rollout_collect_f32(g, self.model, self.env, self.buffer, self.obs[self.cur], self.seed,
+                                    iteration * self.T, self.env_offset, self.last_value)
+                return
+            except GmiError as e:
+                if e.code != ERR_UNSUPPORTED:
+                    raise
+                self.fused_rollout_f32 = False
         for t in range(self.T):
             step = iteration * self.T + t
             obs, nxt = self.obs[self.cur], self.obs[1 - self.cur]
