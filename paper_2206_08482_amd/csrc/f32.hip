@@ -35,39 +35,78 @@ struct F32Layer {
   const float* b;      // [out]
   int in, out;
   int w_off, b_off;    // floats from the start of the parameter vector
+  uint32_t in_magic;
 };
 struct F32Net {
   F32Layer l[kMaxLayers];
 };
 
-// Lanes of a wave that share one row of `width` floats: a power of two, at most 64.
-__device__ __forceinline__ int lanes_per_row(int width) {
-  int n = 16;
-  while (n < 64 && n < width) n <<= 1;
-  return n;
-}
+// n / d for n * d < 2^32 through one multiply: m = magic(d).
+__host__ __device__ __forceinline__ uint32_t magic(uint32_t d) { return d == 1 ? 0u : 0xFFFFFFFFu / d + 1u; }
+__device__ __forceinline__ int div_magic(int n, uint32_t m) { return m ? (int)__umulhi((uint32_t)n, m) : n; }
 
-// Zero-padded LDS copies of a net's weights (if WL) and biases, layer after layer.
+// Zero-padded LDS copies of a net's weights (if WL) and biases, layer after layer: s_w and s_b have been cleared.  The
+// net's parameters are one contiguous piece of the parameter vector; a thread takes every nt-th of them, kStage loads
+// in flight (row by row, each row's load waited for the one before it: 16 us for two layers of 64).
+constexpr int kStage = 16;
 template <bool WL>
-__device__ __forceinline__ void stage_net(const F32Net& N, int nl, float* s_w, float* s_b, int wave, int nw, int lane) {
-  for (int l = 0; l < nl; ++l) {
-    const F32Layer L = N.l[l];
-    const int op = pad16(L.out), ld = rstride(L.in);
-    for (int f = wave * 64 + lane; f < op; f += nw * 64) s_b[f] = f < L.out ? L.b[f] : 0.f;
-    s_b += op;
-    if constexpr (WL) {
-      const int lpr = lanes_per_row(ld), rpw = 64 / lpr, c0 = lane & (lpr - 1);
-#pragma unroll 4
-      for (int f = wave * rpw + lane / lpr; f < op; f += nw * rpw) {
-        const float* src = L.w + (int64_t)(f < L.out ? f : L.out - 1) * L.in;
-        for (int c = c0; c < ld; c += lpr) {
-          const float v = src[c < L.in ? c : L.in - 1];
-          s_w[f * ld + c] = (f < L.out && c < L.in) ? v : 0.f;
+__device__ __forceinline__ void stage_net(const F32Net& N, int nl, float* s_w, float* s_b, int tid, int nt) {
+  const float* base = N.l[0].w;
+  const int off0 = N.l[0].w_off;
+  if constexpr (WL) {
+    const int total = N.l[nl - 1].b_off + N.l[nl - 1].out - off0;
+    for (int e0 = tid; e0 < total; e0 += kStage * nt) {
+      float v[kStage];
+#pragma unroll
+      for (int u = 0; u < kStage; ++u) v[u] = base[min(e0 + u * nt, total - 1)];
+#pragma unroll
+      for (int u = 0; u < kStage; ++u) {
+        const int e = e0 + u * nt;
+        if (e >= total) break;
+        int l = 0, wo = 0, bo = 0;
+        while (l + 1 < nl && e >= N.l[l + 1].w_off - off0) {
+          wo += pad16(N.l[l].out) * rstride(N.l[l].in);
+          bo += pad16(N.l[l].out);
+          ++l;
+        }
+        const int q = e - (N.l[l].w_off - off0), nw = N.l[l].in * N.l[l].out;
+        if (q < nw) {
+          const int f = div_magic(q, N.l[l].in_magic);
+          s_w[wo + f * rstride(N.l[l].in) + q - f * N.l[l].in] = v[u];
+        } else {
+          s_b[bo + q - nw] = v[u];
         }
       }
-      s_w += op * ld;
+    }
+  } else {
+    for (int l = 0; l < nl; ++l) {
+      for (int f = tid; f < N.l[l].out; f += nt) s_b[f] = N.l[l].b[f];
+      s_b += pad16(N.l[l].out);
     }
   }
+}
+__device__ __forceinline__ void clear_lds(float* p, int n, int tid, int nt) {      // n a multiple of 4, p 16-byte aligned
+  for (int i = tid; i < n / 4; i += nt) reinterpret_cast<float4*>(p)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+}
+// Rows of `width` floats, row(r) -> their address, into LDS rows of stride rstride(width), zero padded; 8 loads in flight.
+template <class Row>
+__device__ __forceinline__ void stage_rows(int R, int width, uint32_t wmagic, Row row, float* dst, int tid) {
+  const int ld = rstride(width), n = R * width;
+  for (int e0 = tid; e0 < n; e0 += 8 * kNT) {
+    float v[8];
+    int d[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int e = min(e0 + u * kNT, n - 1), r = div_magic(e, wmagic), c = e - r * width;
+      v[u] = row(r)[c];
+      d[u] = r * ld + c;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) dst[d[u]] = v[u];      // past the end: the last element again
+  }
+  const int padn = ld - width;
+  for (int r = tid; r < R; r += kNT)
+    for (int c = 0; c < padn; ++c) dst[r * ld + width + c] = 0.f;
 }
 
 // acc[i] += sum over nchunk 16-wide k chunks of A (load(c): this lane's 4 values of chunk c) and of the NR row tiles at
@@ -226,6 +265,7 @@ struct AgentF32Args {
   const float* log_std;
   const float* obs;
   int nl, n, obs_dim, act_dim, R, net0, sh, w_floats, b_floats;
+  uint32_t o_magic;
   uint32_t k0, k1, step, env_offset;
   float* act; float* logp; float* value; float* mu_out;
 };
@@ -245,18 +285,10 @@ __global__ __launch_bounds__(kNT) void agent_f32_kernel(AgentF32Args a) {
   float* s_out = s_b + R * a.sh;
   float* s_lp = s_out + R * so;
   const int r0 = blockIdx.x * R;
-  {
-    const int lpr = lanes_per_row(sx0), rpw = 64 / lpr, c0 = lane & (lpr - 1);
-#pragma unroll 4
-    for (int r = wave * rpw + lane / lpr; r < R; r += kNW * rpw) {
-      const float* src = a.obs + (int64_t)min(r0 + r, a.n - 1) * O;
-      for (int c = c0; c < sx0; c += lpr) {
-        const float v = src[c < O ? c : O - 1];
-        s_x0[r * sx0 + c] = c < O ? v : 0.f;
-      }
-    }
-  }
-  stage_net<WL>(N, a.nl, s_w, s_bias, wave, kNW, lane);
+  clear_lds(smem, (WL ? a.w_floats : 0) + a.b_floats, tid, kNT);
+  stage_rows(R, O, a.o_magic, [&](int r) { return a.obs + (int64_t)min(r0 + r, a.n - 1) * O; }, s_x0, tid);
+  __syncthreads();
+  stage_net<WL>(N, a.nl, s_w, s_bias, tid, kNT);
   __syncthreads();
   net_forward<WL>(N, a.nl, s_w, s_bias, s_x0, sx0, s_a, s_b, a.sh, s_out, so, R / 16, true, wave, kNW, lane);
   if (net == 1) {
@@ -308,6 +340,7 @@ struct TrainF32Args {
   int w_net[2];                // floats of each net's LDS weight copy (w_floats: the larger)
   int h_off[kMaxLayers];       // floats from the start of the activation area
   int h_floats;
+  uint32_t o_magic, a_magic;
   float clip, c_v;
   float* part; int64_t part_stride;
   float* stat_part;
@@ -319,7 +352,7 @@ __global__ __launch_bounds__(kNT) void train_f32_kernel(TrainF32Args a) {
   const int net = blockIdx.y;
   const F32Net& N = a.net[net];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int R = a.R, RT = R / 16, O = a.obs_dim, A = a.act_dim, sx0 = rstride(O), so = rstride(A), nl = a.nl;
+  const int R = a.R, RT = R / 16, O = a.obs_dim, A = a.act_dim, so = rstride(A), nl = a.nl;
   float* s_w = smem;
   float* s_bias = s_w + (WL ? a.w_floats : 0);
   float* s_h = s_bias + a.b_floats;
@@ -328,12 +361,13 @@ __global__ __launch_bounds__(kNT) void train_f32_kernel(TrainF32Args a) {
   float* s_out = s_dz1 + R * a.sdz;               // head outputs, then per-sample log_std gradient terms
   float* s_act = s_out + R * so;                  // [R][A]
   float* s_scal = s_act + ((R * A + 3) & ~3);     // [3][R] old log-prob, advantage, return
-  float* s_ls = s_scal + 3 * R;                   // [A] log_std, [A] exp(-log_std)
+  int64_t* s_slot = reinterpret_cast<int64_t*>(s_scal + 3 * R);      // [R]
+  float* s_ls = s_scal + 5 * R;                   // [A] log_std, [A] exp(-log_std)
   float* s_sum = s_ls + 2 * A;                    // [4] statistics, [A] log_std gradient, over all tiles
   const float inv_m = 1.0f / (float)a.rows;
   float* part = a.part + (int64_t)blockIdx.x * a.part_stride;
 
-  stage_net<WL>(N, nl, s_w, s_bias, wave, kNW, lane);
+  clear_lds(smem, (WL ? a.w_floats : 0) + a.b_floats, tid, kNT);
   for (int j = tid; j < A; j += kNT) {
     const float ls = a.log_std[j];
     s_ls[j] = ls;
@@ -343,25 +377,25 @@ __global__ __launch_bounds__(kNT) void train_f32_kernel(TrainF32Args a) {
 
   for (int tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
     const int r0 = tile * R;
-    {   // gather: observation rows (zero padded; rows past the batch repeat its last sample, their gradient is zero)
-      const int lpr = lanes_per_row(sx0), rpw = 64 / lpr, c0 = lane & (lpr - 1);
-#pragma unroll 2
-      for (int r = wave * rpw + lane / lpr; r < R; r += kNW * rpw) {
-        const int s = a.idx[min(r0 + r, a.rows - 1)];
-        const int64_t slot = (int64_t)(s / a.n_envs) * a.ld_envs + (s % a.n_envs);
-        const float* src = a.b_obs + slot * O;
-        for (int c = c0; c < sx0; c += lpr) {
-          const float v = src[c < O ? c : O - 1];
-          s_h[r * sx0 + c] = c < O ? v : 0.f;
-        }
-        if (net == 0) {
-          for (int c = c0; c < A; c += lpr) s_act[r * A + c] = a.b_act[slot * A + c];
-          if (c0 == 0) { s_scal[r] = a.b_logp[slot]; s_scal[R + r] = a.b_adv[slot]; }
-        } else if (c0 == 0) {
-          s_scal[2 * R + r] = a.b_ret[slot];
-        }
-      }
+    const bool first = tile == (int)blockIdx.x;
+    // the rows' experience slots (rows past the batch repeat its last sample, their gradient is zero)
+    if (tid < R) {
+      const int s = a.idx[min(r0 + tid, a.rows - 1)];
+      s_slot[tid] = (int64_t)(s / a.n_envs) * a.ld_envs + (s % a.n_envs);
     }
+    __syncthreads();
+    if (tid < R) {
+      const int64_t slot = s_slot[tid];
+      if (net == 0) { s_scal[tid] = a.b_logp[slot]; s_scal[R + tid] = a.b_adv[slot]; }
+      else s_scal[2 * R + tid] = a.b_ret[slot];
+    }
+    stage_rows(R, O, a.o_magic, [&](int r) { return a.b_obs + s_slot[r] * O; }, s_h, tid);
+    if (net == 0)
+      for (int e = tid; e < R * A; e += kNT) {
+        const int r = div_magic(e, a.a_magic);
+        s_act[e] = a.b_act[s_slot[r] * A + e - r * A];
+      }
+    if (first) stage_net<WL>(N, nl, s_w, s_bias, tid, kNT);
     __syncthreads();
     {   // forward
       const float* w = s_w;
@@ -387,6 +421,7 @@ __global__ __launch_bounds__(kNT) void train_f32_kernel(TrainF32Args a) {
       if (r < R) {
         if (net == 0) {
           float lp = 0.f;
+#pragma unroll 4
           for (int j = 0; j < A; ++j) {
             const float z = (s_act[r * A + j] - s_out[r * so + j]) * s_ls[A + j];
             lp += -0.5f * z * z - s_ls[j] - 0.918938533204672742f;
@@ -402,6 +437,7 @@ __global__ __launch_bounds__(kNT) void train_f32_kernel(TrainF32Args a) {
             st[3] = fabsf(ratio - 1.0f) > a.clip ? 1.f : 0.f;
             g_lp = (u1 <= u2) ? -(ad * ratio) * inv_m : 0.f;
           }
+#pragma unroll 4
           for (int j = 0; j < A; ++j) {
             const float z = (s_act[r * A + j] - s_out[r * so + j]) * s_ls[A + j];
             s_dz0[r * sd + j] = g_lp * z * s_ls[A + j];
@@ -430,6 +466,7 @@ __global__ __launch_bounds__(kNT) void train_f32_kernel(TrainF32Args a) {
     if (net == 0)
       for (int j = tid; j < A; j += kNT) {
         float v = 0.f;
+#pragma unroll 8
         for (int r = 0; r < R; ++r) v += s_out[r * so + j];
         s_sum[4 + j] += v;
       }
@@ -437,7 +474,6 @@ __global__ __launch_bounds__(kNT) void train_f32_kernel(TrainF32Args a) {
     const float* dz = s_dz0;
     float* dn = s_dz1;
     const float* w = s_w + (WL ? a.w_net[net] : 0);
-    const bool first = tile == (int)blockIdx.x;
     for (int l = nl - 1; l >= 0; --l) {
       const F32Layer L = N.l[l];
       const int sz = rstride(L.out), shl = rstride(L.in);
@@ -531,18 +567,18 @@ __global__ __launch_bounds__(kNT) void rollout_f32_kernel(RolloutF32Args a) {
   float* s_lp = s_in + ((R * OA + 3) & ~3);                        // [R][nba]
   float* s_part = s_lp + R * nba;                                  // [R][nbo]
   int* s_done = reinterpret_cast<int*>(s_part + R * nbo);          // [R]
-  float* s_mt = reinterpret_cast<float*>(s_done + R);              // [O + A][o4] when mt_lds
+  float* s_ls = reinterpret_cast<float*>(s_done + R);              // [A] log_std, [A] exp(log_std)
+  float* s_mt = s_ls + ((2 * A + 3) & ~3);                         // [O + A][o4] when mt_lds
   const F32Net& N = a.net[half];
   const float* s_wn = s_w + (half ? a.w_floats[0] : 0);
   const float* s_bn = s_bias + (half ? a.b_floats[0] : 0);
   float* s_a = s_hid + half * 2 * R * a.sh;
   float* s_b = s_a + R * a.sh;
 
-  {
-    float* w = s_w + (half && WL ? a.w_floats[0] : 0);
-    float* b = s_bias + (half ? a.b_floats[0] : 0);
-    stage_net<WL>(N, a.nl, w, b, wave4, 4, lane);
-  }
+  clear_lds(smem, (WL ? a.w_floats[0] + a.w_floats[1] : 0) + a.b_floats[0] + a.b_floats[1], tid, kNT);
+  for (int j = tid; j < A; j += kNT) { s_ls[j] = a.log_std[j]; s_ls[A + j] = expf(a.log_std[j]); }
+  __syncthreads();
+  stage_net<WL>(N, a.nl, s_w + (half && WL ? a.w_floats[0] : 0), s_bias + (half ? a.b_floats[0] : 0), tid & 255, 256);
   if (a.mt_lds)
     for (int i = tid; i < OA * nbo; i += kNT) reinterpret_cast<float4*>(s_mt)[i] = reinterpret_cast<const float4*>(a.m_t)[i];
   const float4* mt_lds_ptr = reinterpret_cast<const float4*>(s_mt);
@@ -583,8 +619,8 @@ __global__ __launch_bounds__(kNT) void rollout_f32_kernel(RolloutF32Args a) {
           float act = 0.f;
           if (r0 + r < a.n) {
             const float z = reinterpret_cast<const float*>(s_noise + r * npr + b)[i];
-            const float ls = a.log_std[j];
-            act = fmaf(expf(ls), z, s_mu[r * so + j]);
+            const float ls = s_ls[j];
+            act = fmaf(s_ls[A + j], z, s_mu[r * so + j]);
             a.b_act[(slot0 + r) * A + j] = act;
             term = -0.5f * z * z - ls - 0.918938533204672742f;
           }
@@ -657,7 +693,8 @@ void fill_net(const gmi_model* m, int net, F32Net* N, int* w_floats, int* b_floa
   *w_floats = *b_floats = 0;
   for (int l = 0; l < m->L.n_layers; ++l) {
     const LayerInfo& li = m->L.net[net][l];
-    N->l[l] = F32Layer{m->params + li.w_off, m->params + li.b_off, li.in, li.out, (int)li.w_off, (int)li.b_off};
+    N->l[l] = F32Layer{m->params + li.w_off, m->params + li.b_off, li.in, li.out, (int)li.w_off, (int)li.b_off,
+                       magic(li.in)};
     *w_floats += pad16(li.out) * rstride(li.in);
     *b_floats += pad16(li.out);
   }
@@ -684,7 +721,7 @@ size_t train_lds(const ModelLayout& L, int R, int w_floats, int b_floats) {
     sdz = std::max(sdz, rstride(L.net[0][l].out));
   }
   const int A = L.act_dim;
-  n += (size_t)R * (2 * sdz + rstride(A)) + ((R * A + 3) & ~3) + 3 * R + 2 * A + 4 + A;
+  n += (size_t)R * (2 * sdz + rstride(A)) + ((R * A + 3) & ~3) + 5 * R + 2 * A + 4 + A;
   return 4 * n;
 }
 
@@ -707,6 +744,7 @@ int launch_agent_f32(gmi_instance* g, gmi_model* m, const float* obs, int n, uin
   int wf[2], bf[2];
   for (int net = 0; net < 2; ++net) fill_net(m, net, &a.net[net], &wf[net], &bf[net]);
   a.nl = L.n_layers; a.n = n; a.obs_dim = L.obs_dim; a.act_dim = L.act_dim;
+  a.o_magic = magic(L.obs_dim);
   a.sh = rstride(max_hidden(L));
   a.w_floats = std::max(wf[0], wf[1]);
   a.b_floats = std::max(bf[0], bf[1]);
@@ -764,6 +802,7 @@ int launch_train_f32(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo
     a.sdz = std::max(a.sdz, rstride(L.net[0][l].out));
   }
   a.h_floats = off;
+  a.o_magic = magic(L.obs_dim); a.a_magic = magic(L.act_dim);
   a.log_std = m->params + L.logstd_off;
   a.idx = idx;
   a.b_obs = b->d.obs; a.b_act = b->d.act; a.b_logp = b->d.logp; a.b_adv = b->d.adv; a.b_ret = b->d.ret;
@@ -808,7 +847,7 @@ extern "C" int rollout_collect_f32(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_bu
   auto lds = [&](int R, bool wl, bool mt) {
     return 4 * ((size_t)(wl ? a.w_floats[0] + a.w_floats[1] : 0) + a.b_floats[0] + a.b_floats[1] +
                 (size_t)R * (rstride(O) + 4 * a.sh + rstride(A) + rstride(1) + a.o4 + 8 * npr + nba + nbo + 1) +
-                ((R * (O + A) + 3) & ~3) + (mt ? (size_t)(O + A) * a.o4 : 0));
+                ((R * (O + A) + 3) & ~3) + ((2 * A + 3) & ~3) + (mt ? (size_t)(O + A) * a.o4 : 0));
   };
   // 32 envs per workgroup once that still gives every compute unit one
   const int R = (a.n + 31) / 32 >= g->cu_count && lds(32, false, false) <= kLdsMax ? 32 : 16;
