@@ -101,6 +101,8 @@ bool compiled_x16(const ModelLayout& L) { return (compiled_probe(L) & 256) != 0;
 namespace gmi {
 using namespace gmi_chain;
 
+bool chain_compiled(const ModelLayout& L) { return L.sh_chain_bytes != 0 && compiled_gmax(L) != 0; }
+
 // Bytes of one net's chain stream (0 if the two nets' padded widths differ, which only a policy head wider
 // than 32 outputs can cause: such models have no chain stream).
 int64_t chain_stream_bytes(const ModelLayout& L) {
@@ -170,7 +172,7 @@ int prepare_obs16(gmi_instance* g, gmi_model* m, gmi_buffer* b, bool* ready) {
   const ModelLayout& L = m->L;
   *ready = false;
   if (!b->obs16 || g->fusion < 1 || L.dtype != GMI_DTYPE_BF16 || L.sh_chain_bytes == 0 || L.act_dim > 32 ||
-      !compiled_x16(L))
+      use_resident(L) || !compiled_x16(L))
     return GMI_OK;
   const int64_t B = (int64_t)b->d.horizon * b->d.n_envs;
   const int rc = launch_gather_to(g, m, b->d.obs, b->d.n_envs, b->d.ld_envs, nullptr, (int)B, nullptr, b->obs16);

@@ -131,6 +131,7 @@ struct LayerInfo {
   int in_pad, out_pad;   // padded to multiples of 32
   int64_t w_off, b_off;  // offsets into the flat fp32 parameter vector
   int64_t sh_wf;              // bf16 W in matrix-core fragment order (see wfrag_index)
+  int64_t sh_wtf;             // bf16 W^T in the same order (rows = input features)
   int64_t sh_w, sh_wt, sh_b;  // byte offsets into the shadow (bf16 W [out_pad,in_pad], bf16 W^T
                               // [in_pad,out_pad], fp32 bias [out_pad])
   bool head;
@@ -285,6 +286,14 @@ int launch_agent_f32(gmi_instance* g, gmi_model* m, const float* obs, int n, uin
 int launch_train_f32(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_hparams* hp, const int32_t* idx, int rows,
                      int* n_parts);
 int f32_part_rows(const ModelLayout& L);
+// The resident trainer kernel (resident.hip): forward, loss and backward of a minibatch.  *n_parts > 0: the weight
+// gradients too, as that many rows of m->grad_part; 0: activations and gradients left row-major in m->h, m->dz.
+int launch_train_resident(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_hparams* hp, const int32_t* idx, int rows,
+                          int* n_parts, int* n_stat_rows);
+bool resident_supported(const ModelLayout& L);
+int resident_part_rows(const ModelLayout& L);
+bool use_resident(const ModelLayout& L);
+bool chain_compiled(const ModelLayout& L);       // a register-chained or row-tile trainer kernel has this shape
 
 // Shuffles of epochs epoch0 .. epoch0 + n_epochs - 1 into out[e][n], one launch.
 constexpr int kPermEpochs = 8;
@@ -377,7 +386,7 @@ __host__ __device__ static inline int64_t wfrag_index(int o, int i, int in_pad) 
 struct ShadowLayer {
   int64_t w_off, b_off;
   int in, out, in_pad, out_pad;
-  int64_t sh_w, sh_wt, sh_b, sh_wf;
+  int64_t sh_w, sh_wt, sh_b, sh_wf, sh_wtf;      // sh_wtf < 0: nobody reads that copy
 };
 struct ShadowTable {
   int n;
@@ -388,12 +397,14 @@ struct ShadowTable {
 };
 static inline ShadowTable make_shadow_table(const ModelLayout& L) {
   ShadowTable t;
+  const bool resident = resident_supported(L);
   t.n = 0;
   for (int net = 0; net < 2; ++net)
     for (const LayerInfo& li : L.net[net]) {
       ShadowLayer& s = t.l[t.n++];
       s.w_off = li.w_off; s.b_off = li.b_off; s.in = li.in; s.out = li.out;
       s.in_pad = li.in_pad; s.out_pad = li.out_pad; s.sh_w = li.sh_w; s.sh_wt = li.sh_wt; s.sh_b = li.sh_b; s.sh_wf = li.sh_wf;
+      s.sh_wtf = resident ? li.sh_wtf : -1;
     }
   t.logstd_off = L.logstd_off;
   t.sh_logstd = L.sh_logstd;

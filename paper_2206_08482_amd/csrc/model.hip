@@ -37,6 +37,7 @@ int build_layout(const gmi_model_desc* d, ModelLayout* L) {
       li.sh_w = sh;  sh += gmi::align_up((int64_t)li.out_pad * li.in_pad * 2, 256);
       li.sh_wt = sh; sh += gmi::align_up((int64_t)li.out_pad * li.in_pad * 2, 256);
       li.sh_wf = sh; sh += gmi::align_up((int64_t)li.out_pad * li.in_pad * 2, 256);
+      li.sh_wtf = sh; sh += gmi::align_up((int64_t)li.out_pad * li.in_pad * 2, 256);
       wbytes += (int64_t)li.out_pad * li.in_pad * 2;
       li.sh_b = sh;  sh += gmi::align_up((int64_t)li.out_pad * 4, 256);
       if (li.out_pad > maxw) maxw = li.out_pad;
@@ -104,6 +105,7 @@ __global__ void refresh_shadow_kernel(gmi::ShadowTable tab, const float* __restr
     reinterpret_cast<uint16_t*>(shadow + L.sh_w)[(int64_t)o * L.in_pad + i] = b;
     reinterpret_cast<uint16_t*>(shadow + L.sh_wt)[(int64_t)i * L.out_pad + o] = b;
     reinterpret_cast<uint16_t*>(shadow + L.sh_wf)[gmi::wfrag_index(o, i, L.in_pad)] = b;
+    if (L.sh_wtf >= 0) reinterpret_cast<uint16_t*>(shadow + L.sh_wtf)[gmi::wfrag_index(i, o, L.out_pad)] = b;
   }
 }
 
@@ -328,6 +330,7 @@ extern "C" int gmi_model_bind(gmi_t g, const gmi_model_desc* d, float* params, v
         n_tiles += ((L.net[net][l].out_pad + 127) / 128) * ((L.net[net][l].in_pad + 127) / 128);
     m->n_split_max = gmi::wgrad_split_limit(n_tiles);
     m->part_rows = m->n_split_max;
+    if (L.dtype == GMI_DTYPE_BF16 && adam_m) m->part_rows = std::max(m->part_rows, gmi::resident_part_rows(L));
     if (L.dtype == GMI_DTYPE_F32 && adam_m) m->part_rows = std::max(m->part_rows, gmi::f32_part_rows(L));
   }
 

@@ -116,6 +116,13 @@ __device__ __forceinline__ float adam_one(float g, float* __restrict__ params, f
   return w;
 }
 
+// The same expressions on values held in registers: m, v and w are updated.
+__device__ __forceinline__ void adam_step(float g, float& m, float& v, float& w, const AdamScalars& hs) {
+  m = hs.b1 * m + (1.0f - hs.b1) * g;
+  v = hs.b2 * v + (1.0f - hs.b2) * g * g;
+  w = w - hs.lr * (m / hs.c1) / (sqrtf(v / hs.c2) + hs.eps);
+}
+
 // Gradient partials of the trainer instances whose replicas are reduced into one update (one entry for an
 // ordinary single-instance update): per instance [n_split, part_stride] weight partials and the loss
 // kernel's [n_loss_blocks, kStatStride + A] statistics partials.
@@ -126,128 +133,132 @@ struct PartSet {
   const float* stat[kMaxGroup];
 };
 
-// One thread per weight / bias: reduce the gradient partials, Adam, and (BF16) refresh the bias and the
-// [out_pad, in_pad] weight shadow (the transposed shadow is rebuilt by shadow_transpose_kernel).
-// grad(p) = (1/n) sum_i sum_s part_i[s * part_stride + p]: the in-memory mean over the n replicas
-// (Section 4.1's gradient reduction for instances that share one address space), fixed summation order.
-// The last workgroup instead finalises the minibatch statistics and owns log_std, whose gradient is the sum
-// of the loss kernel's per-workgroup partials minus the entropy coefficient; it reduces the
-// [n_loss_blocks, kStatStride + A] partials cooperatively (a serial walk by one thread per column costs
-// one memory round trip per loss workgroup).
-__global__ __launch_bounds__(256) void adam_kernel(gmi::ShadowTable tab, int write_shadow, float* __restrict__ params,
-                                                   float* __restrict__ am, float* __restrict__ av,
-                                                   PartSet ps, int n_split, int64_t part_stride,
-                                                   int n_loss_blocks, int A,
-                                                   float c_e, float inv_rows, AdamScalars hs, char* __restrict__ shadow,
-                                                   float* __restrict__ stats_out, float* __restrict__ grad_out,
-                                                   int do_update) {
-  if (blockIdx.x == gridDim.x - 1) {
-    __shared__ float s_col[256];
-    const int C = gmi::kStatStride + A;              // columns of a statistics row
-    const int tid = threadIdx.x;
-    // up to 256 columns per pass; narrow rows are walked by 256 / C row groups in parallel
-    const int width = C < 256 ? C : 256;
-    const int groups = 256 / width;
-    const bool have_stat = ps.stat[0] != nullptr;
-    const float inv_n = 1.0f / (float)ps.n;
-    for (int cbase = 0; cbase < C; cbase += 256) {
-      const int col = cbase + tid % width, grp = tid / width;
-      float s = 0.f;
-      if (have_stat && grp < groups && col < C)
-        for (int i = 0; i < ps.n; ++i) {
-          // rows grp, grp + groups, ...: eight loads in flight, fixed order of additions
-          const float* q = ps.stat[i] + col;
-          int b = grp;
-          for (; b + 7 * groups < n_loss_blocks; b += 8 * groups) {
-            float t[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) t[u] = q[(int64_t)(b + u * groups) * C];
-            s += ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
-          }
-          for (; b < n_loss_blocks; b += groups) s += q[(int64_t)b * C];
-        }
-      s_col[tid] = s;
-      __syncthreads();
-      const int c = cbase + tid;
-      if (tid < width && c < C) {
-        float t = 0.f;
-        for (int q = 0; q < groups; ++q) t += s_col[q * width + tid];
-        t *= inv_n;                                   // mean over the replicas (exact for one)
-        if (have_stat && stats_out && c < 5) stats_out[c] = c == 2 ? t : t * inv_rows;
-        if (c >= gmi::kStatStride) {
-          const int j = c - gmi::kStatStride;
-          const int64_t p = tab.logstd_off + j;
-          // without loss partials (a caller-supplied gradient) log_std takes the split sums like any weight
-          float g = 0.f;
-          if (have_stat) g = t - c_e;
-          else for (int q = 0; q < n_split; ++q) g += ps.part[0][(int64_t)q * part_stride + p];
-          if (grad_out) grad_out[p] = g;
-          if (do_update) {
-            const float w = adam_one(g, params, am, av, p, hs);
-            if (write_shadow) reinterpret_cast<float*>(shadow + tab.sh_logstd)[j] = w;
-          }
-        }
-      }
-      __syncthreads();
-    }
-    return;
-  }
-  const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (p >= tab.logstd_off) return;
-  // the moments and the parameter are fetched ahead of the partials (their latency would otherwise follow the sum's)
-  float m0 = 0.f, v0 = 0.f, w0 = 0.f;
-  if (do_update) { m0 = am[p]; v0 = av[p]; w0 = params[p]; }
+// Sum over the replicas and splits of the partials at p, splits grp, grp + G, grp + 2 G, ...: fixed order of additions,
+// 16 (then 4) loads in flight.
+template <int G>
+__device__ __forceinline__ float sum_partials(const PartSet& ps, int64_t p, int n_split, int64_t part_stride, int grp) {
   float g = 0.f;
   for (int i = 0; i < ps.n; ++i) {
     const float* q = ps.part[i] + p;
-    int sidx = 0;
-    // fixed order of additions, 16 (then 8) loads in flight
-    for (; sidx + 16 <= n_split; sidx += 16) {
+    int s = grp;
+    for (; s + 15 * G < n_split; s += 16 * G) {
       float t[16];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) t[u] = q[(int64_t)(sidx + u) * part_stride];
+      for (int u = 0; u < 16; ++u) t[u] = q[(int64_t)(s + u * G) * part_stride];
 #pragma unroll
       for (int u = 0; u < 16; ++u) g += t[u];
     }
-    for (; sidx + 8 <= n_split; sidx += 8) {
-      float t[8];
+    for (; s + 3 * G < n_split; s += 4 * G) {
+      float t[4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) t[u] = q[(int64_t)(sidx + u) * part_stride];
+      for (int u = 0; u < 4; ++u) t[u] = q[(int64_t)(s + u * G) * part_stride];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) g += t[u];
+      for (int u = 0; u < 4; ++u) g += t[u];
     }
-    for (; sidx < n_split; ++sidx) g += q[(int64_t)sidx * part_stride];
+    for (; s < n_split; s += G) g += q[(int64_t)s * part_stride];
   }
-  g *= 1.0f / (float)ps.n;
-  if (grad_out) grad_out[p] = g;
-  if (!do_update) return;
-  // same expressions as adam_one
-  const float mn = hs.b1 * m0 + (1.0f - hs.b1) * g;
-  const float vn = hs.b2 * v0 + (1.0f - hs.b2) * g * g;
-  am[p] = mn;
-  av[p] = vn;
-  const float w = w0 - hs.lr * (mn / hs.c1) / (sqrtf(vn / hs.c2) + hs.eps);
-  params[p] = w;
-  if (!write_shadow) return;
-  int li = 0;
-  while (li + 1 < tab.n && p >= tab.l[li + 1].w_off) ++li;
-  const gmi::ShadowLayer& L = tab.l[li];
-  if (p >= L.b_off) {
-    reinterpret_cast<float*>(shadow + L.sh_b)[p - L.b_off] = w;
-  } else {
-    const int64_t q = p - L.w_off;
-    const int o = (int)(q / L.in), i = (int)(q % L.in);
-    reinterpret_cast<uint16_t*>(shadow + L.sh_w)[(int64_t)o * L.in_pad + i] = f_to_bf16_u(w);
+  return g;
+}
+
+// Finalises the minibatch statistics and owns log_std, whose gradient is the sum of the loss partials minus the entropy
+// coefficient: one workgroup of NT threads reduces the [n_loss_blocks, kStatStride + A] partials cooperatively (a serial
+// walk by one thread per column costs one memory round trip per loss workgroup).
+template <int NT>
+__device__ __forceinline__ void finish_stats(const gmi::ShadowTable& tab, float* __restrict__ params, float* __restrict__ am,
+                                             float* __restrict__ av, const PartSet& ps, int n_split, int64_t part_stride,
+                                             int n_loss_blocks, int A, float c_e, float inv_rows, const AdamScalars& hs,
+                                             float* __restrict__ log_std_shadow, float* __restrict__ stats_out,
+                                             float* __restrict__ grad_out, int do_update, float* s_col) {
+  const int C = gmi::kStatStride + A;              // columns of a statistics row
+  const int tid = threadIdx.x;
+  // up to NT columns per pass; narrow rows are walked by NT / C row groups in parallel
+  const int width = C < NT ? C : NT;
+  const int groups = NT / width;
+  const bool have_stat = ps.stat[0] != nullptr;
+  const float inv_n = 1.0f / (float)ps.n;
+  for (int cbase = 0; cbase < C; cbase += NT) {
+    const int col = cbase + tid % width, grp = tid / width;
+    float s = 0.f;
+    if (have_stat && grp < groups && col < C)
+      for (int i = 0; i < ps.n; ++i) {
+        // rows grp, grp + groups, ...: eight loads in flight, fixed order of additions
+        const float* q = ps.stat[i] + col;
+        int b = grp;
+        for (; b + 7 * groups < n_loss_blocks; b += 8 * groups) {
+          float t[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) t[u] = q[(int64_t)(b + u * groups) * C];
+          s += ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+        }
+        for (; b < n_loss_blocks; b += groups) s += q[(int64_t)b * C];
+      }
+    s_col[tid] = s;
+    __syncthreads();
+    const int c = cbase + tid;
+    if (tid < width && c < C) {
+      float t = 0.f;
+      for (int q = 0; q < groups; ++q) t += s_col[q * width + tid];
+      t *= inv_n;                                   // mean over the replicas (exact for one)
+      if (have_stat && stats_out && c < 5) stats_out[c] = c == 2 ? t : t * inv_rows;
+      if (c >= gmi::kStatStride) {
+        const int j = c - gmi::kStatStride;
+        const int64_t p = tab.logstd_off + j;
+        // without loss partials (a caller-supplied gradient) log_std takes the split sums like any weight
+        float g = 0.f;
+        if (have_stat) g = t - c_e;
+        else for (int q = 0; q < n_split; ++q) g += ps.part[0][(int64_t)q * part_stride + p];
+        if (grad_out) grad_out[p] = g;
+        if (do_update) {
+          const float w = adam_one(g, params, am, av, p, hs);
+          if (log_std_shadow) log_std_shadow[j] = w;
+        }
+      }
+    }
+    __syncthreads();
   }
 }
 
-// Rebuilds the transposed weight shadows [in_pad, out_pad] and the fragment-major ones from the
-// [out_pad, in_pad] ones through 64x64 LDS tiles, so that all sides move whole 16-byte pieces (one 2-byte
-// store per weight into the transposed copy touched a different memory line for every thread of a wave).
-struct TransposeTiles {
-  int n;
-  int start[gmi::kMaxWgradProblems + 1];
-};
+// fp32 models, caller-supplied gradients, and gradients that are only read (ppo_gradient): a workgroup of 64 G waves'
+// worth of threads owns 256 consecutive parameters, G threads per parameter each summing every G-th partial row.
+// grad(p) = (1/n) sum_i sum_s part_i[s * part_stride + p]: the in-memory mean over the n replicas (Section 4.1's gradient
+// reduction for instances that share one address space), fixed summation order.  The last workgroup finalises the
+// statistics and log_std.
+template <int G>
+__global__ __launch_bounds__(256 * G) void adam_kernel(gmi::ShadowTable tab, float* __restrict__ params,
+                                                       float* __restrict__ am, float* __restrict__ av, PartSet ps,
+                                                       int n_split, int64_t part_stride, int n_loss_blocks, int A, float c_e,
+                                                       float inv_rows, AdamScalars hs, float* __restrict__ stats_out,
+                                                       float* __restrict__ grad_out, int do_update) {
+  __shared__ float s_sum[256 * G];
+  if (blockIdx.x == gridDim.x - 1) {
+    finish_stats<256 * G>(tab, params, am, av, ps, n_split, part_stride, n_loss_blocks, A, c_e, inv_rows, hs, nullptr,
+                          stats_out, grad_out, do_update, s_sum);
+    return;
+  }
+  const int t = threadIdx.x & 255, grp = threadIdx.x >> 8;
+  const int64_t p = (int64_t)blockIdx.x * 256 + t;
+  const bool ok = p < tab.logstd_off;
+  // the moments and the parameter are fetched ahead of the partials (their latency would otherwise follow the sum's)
+  float m0 = 0.f, v0 = 0.f, w0 = 0.f;
+  if (do_update && ok && grp == 0) { m0 = am[p]; v0 = av[p]; w0 = params[p]; }
+  float g = ok ? sum_partials<G>(ps, p, n_split, part_stride, grp) : 0.f;
+  if constexpr (G > 1) {
+    s_sum[threadIdx.x] = g;
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int q = 1; q < G; ++q) g += s_sum[q * 256 + t];
+  }
+  if (!ok) return;
+  g *= 1.0f / (float)ps.n;
+  if (grad_out) grad_out[p] = g;
+  if (!do_update) return;
+  adam_step(g, m0, v0, w0, hs);
+  am[p] = m0;
+  av[p] = v0;
+  params[p] = w0;
+}
+
 // Index of block (feature tile ft, k step ks) inside a chain-stream segment of nft tiles and nks k steps whose
 // tiles are grouped gm, .., gm, (2), (1): groups one after the other, a group's blocks k step major.
 __device__ __forceinline__ int chain_block_index(int nft, int nks, int gm, int ft, int ks) {
@@ -269,85 +280,116 @@ __device__ __forceinline__ int chain_block_index(int nft, int nks, int gm, int f
   return base + ks * gs + t;
 }
 
-__global__ __launch_bounds__(256) void shadow_transpose_kernel(gmi::ShadowTable tab, TransposeTiles tt, gmi::ChainEmit ce,
-                                                               char* __restrict__ shadow) {
-  __shared__ __attribute__((aligned(16))) uint16_t s_t[64][72];
+// BF16 update: Adam and every bf16 copy of the weights in one pass (a second kernel that rebuilt the transposed copies
+// from the first one's output cost 5-6 us per minibatch, most of it launch and round trips).  A workgroup owns an 8
+// (outputs) x 32 (inputs) tile of one layer's W -- 128-byte rows of the partials, and just what the copies' 16-byte
+// pieces need: 8 consecutive inputs of an output (row-major and fragment-major W), 8 consecutive outputs of an input
+// (W^T, its fragment-major copy), the chain streams' permuted k orders -- and, in the first input tile, the 8 biases.
+// G threads per parameter, each summing every G-th partial row: 4 where the model has few tiles or the partials are many
+// rows, so that the sums do not become one long chain of loads in a few workgroups.
+struct AdamTiles {
+  int n;
+  int start[gmi::kMaxWgradProblems + 1];
+};
+template <int G>
+__global__ __launch_bounds__(256 * G) void adam_shadow_kernel(gmi::ShadowTable tab, AdamTiles tt, gmi::ChainEmit ce,
+                                                              float* __restrict__ params, float* __restrict__ am,
+                                                              float* __restrict__ av, PartSet ps, int n_split,
+                                                              int64_t part_stride, int n_loss_blocks, int A, float c_e,
+                                                              float inv_rows, AdamScalars hs, char* __restrict__ shadow,
+                                                              float* __restrict__ stats_out) {
+  __shared__ float s_sum[264 * G];
+  __shared__ __attribute__((aligned(16))) uint16_t s_t[8][40];
+  const int n_tiles = gridDim.x - 1;
+  if ((int)blockIdx.x == n_tiles) {
+    finish_stats<256 * G>(tab, params, am, av, ps, n_split, part_stride, n_loss_blocks, A, c_e, inv_rows, hs,
+                          reinterpret_cast<float*>(shadow + tab.sh_logstd), stats_out, nullptr, 1, s_sum);
+    return;
+  }
+  // neighbouring tiles, which share the memory lines of unaligned rows, on the same die (ids go round-robin over 8)
+  const int per = n_tiles >> 3, whole = per << 3;
+  const int tile = (int)blockIdx.x < whole ? (blockIdx.x & 7) * per + (blockIdx.x >> 3) : blockIdx.x;
   int li = 0;
-  while (li + 1 < tt.n && (int)blockIdx.x >= tt.start[li + 1]) ++li;
+  while (li + 1 < tt.n && tile >= tt.start[li + 1]) ++li;
   const gmi::ShadowLayer& L = tab.l[li];
-  const int local = blockIdx.x - tt.start[li];
-  const int n_ti = (L.in_pad + 63) / 64;
-  const int o0 = (local / n_ti) * 64, i0 = (local % n_ti) * 64;
-  const uint16_t* __restrict__ w = reinterpret_cast<const uint16_t*>(shadow + L.sh_w);
-  uint16_t* __restrict__ wt = reinterpret_cast<uint16_t*>(shadow + L.sh_wt);
-  uint16_t* __restrict__ wf = reinterpret_cast<uint16_t*>(shadow + L.sh_wf);
-  const int tid = threadIdx.x, c8 = (tid & 7) * 8, r = tid >> 3;
+  const int local = tile - tt.start[li], n_ti = (L.in + 31) >> 5;
+  const int o0 = (local / n_ti) * 8, i0 = (local % n_ti) * 32;
+  const int t = threadIdx.x & 255, grp = threadIdx.x >> 8;
+  const int o = o0 + (t >> 5), i = i0 + (t & 31);
+  const bool ok = o < L.out && i < L.in;
+  const bool okb = i0 == 0 && t < 8 && o0 + t < L.out;
+  const int64_t p = ok ? L.w_off + (int64_t)o * L.in + i : L.w_off, pb = okb ? L.b_off + o0 + t : L.b_off;
+  float m0 = 0.f, v0 = 0.f, w0 = 0.f, mb = 0.f, vb = 0.f, wb = 0.f;
+  if (grp == 0) {
+    m0 = am[p]; v0 = av[p]; w0 = params[p];
+    if (okb) { mb = am[pb]; vb = av[pb]; wb = params[pb]; }
+  }
+  float g = sum_partials<G>(ps, p, n_split, part_stride, grp);
+  float gb = okb ? sum_partials<G>(ps, pb, n_split, part_stride, grp) : 0.f;
+  if constexpr (G > 1) {
+    s_sum[grp * 264 + t] = g;
+    if (t < 8) s_sum[grp * 264 + 256 + t] = gb;
+    __syncthreads();
+    if (grp == 0) {
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int o = o0 + r + 32 * k, i = i0 + c8;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (o < L.out_pad && i < L.in_pad) v = *reinterpret_cast<const uint4*>(w + (int64_t)o * L.in_pad + i);
-    *reinterpret_cast<uint4*>(&s_t[r + 32 * k][c8]) = v;
+      for (int q = 1; q < G; ++q) {
+        g += s_sum[q * 264 + t];
+        if (t < 8) gb += s_sum[q * 264 + 256 + t];
+      }
+    }
+  }
+  if (grp == 0) {
+    const float inv_n = 1.0f / (float)ps.n;
+    adam_step(g * inv_n, m0, v0, w0, hs);
+    if (ok) { am[p] = m0; av[p] = v0; params[p] = w0; }
+    s_t[t >> 5][t & 31] = ok ? f_to_bf16_u(w0) : 0;
+    if (okb) {
+      adam_step(gb * inv_n, mb, vb, wb, hs);
+      am[pb] = mb; av[pb] = vb; params[pb] = wb;
+      reinterpret_cast<float*>(shadow + L.sh_b)[o0 + t] = wb;
+    }
   }
   __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int i = i0 + r + 32 * k, o = o0 + c8;
-    if (i < L.in_pad && o < L.out_pad) {
-      uint16_t e[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) e[j] = s_t[c8 + j][r + 32 * k];
+  if (threadIdx.x >= 256) return;
+  auto column = [&](int c) {      // the 8 outputs of input c
+    uint4 v;
+    v.x = s_t[0][c] | ((uint32_t)s_t[1][c] << 16); v.y = s_t[2][c] | ((uint32_t)s_t[3][c] << 16);
+    v.z = s_t[4][c] | ((uint32_t)s_t[5][c] << 16); v.w = s_t[6][c] | ((uint32_t)s_t[7][c] << 16);
+    return v;
+  };
+  const int e = t & 31;
+  if (t < 32) {                    // W, row-major
+    const int r = e >> 2, c = (e & 3) * 8;
+    *reinterpret_cast<uint4*>(shadow + L.sh_w + 2 * ((int64_t)(o0 + r) * L.in_pad + i0 + c)) = *reinterpret_cast<const uint4*>(&s_t[r][c]);
+  } else if (t < 64) {             // W, fragment-major
+    const int r = e & 7, c = (e >> 3) * 8;
+    *reinterpret_cast<uint4*>(shadow + L.sh_wf + 2 * gmi::wfrag_index(o0 + r, i0 + c, L.in_pad)) = *reinterpret_cast<const uint4*>(&s_t[r][c]);
+  } else if (t < 96) {             // W^T, row-major
+    *reinterpret_cast<uint4*>(shadow + L.sh_wt + 2 * ((int64_t)(i0 + e) * L.out_pad + o0)) = column(e);
+  } else if (t < 128) {            // W^T, fragment-major
+    if (L.sh_wtf >= 0) *reinterpret_cast<uint4*>(shadow + L.sh_wtf + 2 * gmi::wfrag_index(i0 + e, o0, L.out_pad)) = column(e);
+  } else if (ce.gmax > 0) {
+    // the chain streams of the one-launch trainer kernels: lane (s, h) of a block holds, for its row, the k indices
+    // 16 ks + 8 (j / 4) + 4 h + j % 4, j = 0..7 (natural order 8 h + j in the first forward layer)
+    char* cs = shadow + ce.out[li / ce.n_layers];
+    const gmi::ChainEmitLayer& E = ce.l[li];
+    if (t < 160) {                 // forward segment: rows = output features, k = input features
+      const int r = e & 7, ks = e >> 4, h = (e >> 3) & 1, il = 16 * ks;
       uint4 v;
-      v.x = e[0] | ((uint32_t)e[1] << 16); v.y = e[2] | ((uint32_t)e[3] << 16);
-      v.z = e[4] | ((uint32_t)e[5] << 16); v.w = e[6] | ((uint32_t)e[7] << 16);
-      *reinterpret_cast<uint4*>(wt + (int64_t)i * L.out_pad + o) = v;
-    }
-  }
-  // the tile holds 2 feature tiles x 4 k steps = 8 fragment blocks of 64 lanes x 16 bytes
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int idx = tid + 256 * k, blk = idx >> 6, lane = idx & 63;
-    const int ol = (blk >> 2) * 32 + (lane & 31), il = (blk & 3) * 16 + (lane >> 5) * 8;
-    if (o0 + ol < L.out_pad && i0 + il < L.in_pad)
-      *reinterpret_cast<uint4*>(wf + gmi::wfrag_index(o0 + ol, i0 + il, L.in_pad)) =
-          *reinterpret_cast<const uint4*>(&s_t[ol][il]);
-  }
-  // the same 8 + 8 blocks in the order and with the k permutation of the chained trainer kernel's streams:
-  // lane (s, h) of a block holds, for its row, the k indices 16 ks + 8 (j / 4) + 4 h + j % 4, j = 0..7 (natural
-  // order 8 h + j in the first forward layer)
-  if (ce.gmax == 0) return;
-  uint4* __restrict__ cs = reinterpret_cast<uint4*>(shadow + ce.out[li / ce.n_layers]);
-  const gmi::ChainEmitLayer& E = ce.l[li];
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int idx = tid + 256 * k, blk = idx >> 6, lane = idx & 63, h = lane >> 5;
-    {   // forward segment: rows = output features, k = input features
-      const int ol = (blk >> 2) * 32 + (lane & 31), il = (blk & 3) * 16;
-      if (o0 + ol < L.out_pad && i0 + il < L.in_pad) {
-        uint4 v;
-        if (E.natural) {
-          v = *reinterpret_cast<const uint4*>(&s_t[ol][il + 8 * h]);
-        } else {
-          const uint2 a = *reinterpret_cast<const uint2*>(&s_t[ol][il + 4 * h]);
-          const uint2 b = *reinterpret_cast<const uint2*>(&s_t[ol][il + 8 + 4 * h]);
-          v = make_uint4(a.x, a.y, b.x, b.y);
-        }
-        const int dst = E.fwd_blk + chain_block_index(L.out_pad >> 5, L.in_pad >> 4, ce.gmax, (o0 + ol) >> 5, (i0 + il) >> 4);
-        cs[(int64_t)dst * 64 + lane] = v;
+      if (E.natural) {
+        v = *reinterpret_cast<const uint4*>(&s_t[r][il + 8 * h]);
+      } else {
+        const uint2 a = *reinterpret_cast<const uint2*>(&s_t[r][il + 4 * h]);
+        const uint2 b = *reinterpret_cast<const uint2*>(&s_t[r][il + 8 + 4 * h]);
+        v = make_uint4(a.x, a.y, b.x, b.y);
       }
-    }
-    if (E.bwd_blk >= 0) {   // input-gradient segment: rows = input features, k = output features
-      const int il = (blk >> 2) * 32 + (lane & 31), ol = (blk & 3) * 16;
-      if (i0 + il < L.in_pad && o0 + ol < L.out_pad) {
-        uint16_t e[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) e[j] = s_t[ol + 8 * (j >> 2) + 4 * h + (j & 3)][il];
-        uint4 v;
-        v.x = e[0] | ((uint32_t)e[1] << 16); v.y = e[2] | ((uint32_t)e[3] << 16);
-        v.z = e[4] | ((uint32_t)e[5] << 16); v.w = e[6] | ((uint32_t)e[7] << 16);
-        const int dst = E.bwd_blk + chain_block_index(L.in_pad >> 5, L.out_pad >> 4, ce.gmax, (i0 + il) >> 5, (o0 + ol) >> 4);
-        cs[(int64_t)dst * 64 + lane] = v;
-      }
+      const int dst = E.fwd_blk + chain_block_index(L.out_pad >> 5, L.in_pad >> 4, ce.gmax, (o0 + r) >> 5, (i0 + il) >> 4);
+      *reinterpret_cast<uint4*>(cs + ((int64_t)dst * 64 + ((o0 + r) & 31) + 32 * h) * 16) = v;
+    } else if (t >= 192 && E.bwd_blk >= 0) {      // input-gradient segment: rows = input features, k = output features
+      const int h = (t >> 5) & 1, q = 4 * h;      // this tile's 8 outputs are half (o0 / 8) % 2 of a k step
+      const uint2 v = make_uint2(s_t[q][e] | ((uint32_t)s_t[q + 1][e] << 16), s_t[q + 2][e] | ((uint32_t)s_t[q + 3][e] << 16));
+      const int dst = E.bwd_blk + chain_block_index(L.in_pad >> 5, L.out_pad >> 4, ce.gmax, i0 >> 5, o0 >> 4);
+      *reinterpret_cast<uint2*>(cs + ((int64_t)dst * 64 + e + 32 * h) * 16 + 8 * ((o0 >> 3) & 1)) = v;
     }
   }
 }
@@ -448,6 +490,11 @@ int minibatch_pass(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_h
     if (rc == GMI_OK) { *n_loss_blocks_out = *n_split_out; return GMI_OK; }
     if (rc != GMI_ERR_UNSUPPORTED) return rc;
   }
+  if (g->fusion >= 1 && want_grad && bf && gmi::use_resident(L)) {
+    // the tile's activations resident in LDS; small nets' weight gradients in the same launch
+    rc = gmi::launch_train_resident(g, m, b, hp, idx, rows, n_split_out, n_loss_blocks_out);
+    if (rc == GMI_OK && *n_split_out > 0) return GMI_OK;
+  }
   if (rc == GMI_ERR_UNSUPPORTED && g->fusion >= 1 && want_grad && bf) {
     // register-chained kernel (gather + forward + loss + input gradients in one launch) where this shape has one
     rc = gmi::launch_train_chain(g, m, b, hp, idx, rows, n_loss_blocks_out, obs16_ready, &blocks);
@@ -486,35 +533,41 @@ int launch_adam(gmi_instance* g, gmi_model* const* ms, int n, int n_split, int n
   gmi_model* m = ms[0];
   const gmi::ShadowTable tab = gmi::make_shadow_table(m->L);
   gmi::ProfScope ps(g, gmi::kClsAdam);
-  // one workgroup per 256 weights / biases plus one for the statistics and log_std
-  const unsigned grid = (unsigned)((m->L.logstd_off + 255) / 256) + 1;
   PartSet set;
   set.n = n;
   for (int i = 0; i < kMaxGroup; ++i) {
     set.part[i] = i < n ? ms[i]->grad_part : nullptr;
     set.stat[i] = i < n ? ms[i]->stat_part : nullptr;
   }
-  const bool bf = m->L.dtype == GMI_DTYPE_BF16;
-  ps.launch(adam_kernel, dim3(grid), dim3(256), 0, tab, bf ? 1 : 0, m->params, m->adam_m, m->adam_v, set, n_split,
-            m->L.n_params, n_loss_blocks, m->L.act_dim, hp->c_e, 1.0f / (float)rows, adam_scalars(hp, k), m->shadow,
-            stats_out, grad_out, do_update ? 1 : 0);
-  GMI_LAUNCH_CHECK();
-  if (bf && do_update) {
-    TransposeTiles tt;
+  // four threads per parameter where one per parameter would leave the device short of loads in flight (fewer than
+  // about 1024 workgroups of 256) or make each thread walk a long column
+  const bool split4 = n_split >= 4 && (n_split >= 64 || m->L.logstd_off < 256 * 1024);
+  if (m->L.dtype == GMI_DTYPE_BF16 && do_update && !grad_out) {
+    AdamTiles tt;
     tt.n = tab.n;
     int total = 0;
     for (int i = 0; i < tab.n; ++i) {
       tt.start[i] = total;
-      total += ((tab.l[i].out_pad + 63) / 64) * ((tab.l[i].in_pad + 63) / 64);
+      total += ((tab.l[i].out + 7) / 8) * ((tab.l[i].in + 31) / 32);
     }
     tt.start[tab.n] = total;
-    gmi::ProfScope ps2(g, gmi::kClsShadowTranspose);
     gmi::ChainEmit ce;
     gmi::fill_chain_emit(m->L, &ce);
-    ps2.launch(shadow_transpose_kernel, dim3(total), dim3(256), 0, tab, tt, ce, m->shadow);
+    auto go = [&](auto kernel, int threads) {
+      ps.launch(kernel, dim3(total + 1), dim3(threads), 0, tab, tt, ce, m->params, m->adam_m, m->adam_v, set, n_split,
+                m->L.n_params, n_loss_blocks, m->L.act_dim, hp->c_e, 1.0f / (float)rows, adam_scalars(hp, k), m->shadow, stats_out);
+    };
+    if (split4) go(adam_shadow_kernel<4>, 1024); else go(adam_shadow_kernel<1>, 256);
     GMI_LAUNCH_CHECK();
     return GMI_OK;
   }
+  const unsigned grid = (unsigned)((m->L.logstd_off + 255) / 256) + 1;
+  auto go = [&](auto kernel, int threads) {
+    ps.launch(kernel, dim3(grid), dim3(threads), 0, tab, m->params, m->adam_m, m->adam_v, set, n_split, m->L.n_params,
+              n_loss_blocks, m->L.act_dim, hp->c_e, 1.0f / (float)rows, adam_scalars(hp, k), stats_out, grad_out, do_update ? 1 : 0);
+  };
+  if (split4) go(adam_kernel<4>, 1024); else go(adam_kernel<1>, 256);
+  GMI_LAUNCH_CHECK();
   return GMI_OK;
 }
 
@@ -701,8 +754,8 @@ extern "C" int adam_update(gmi_t g, float* params, float* adam_m, float* adam_v,
   set.n = 1;
   for (int i = 0; i < kMaxGroup; ++i) set.part[i] = set.stat[i] = nullptr;
   set.part[0] = grad;
-  ps.launch(adam_kernel, dim3((unsigned)((n + 255) / 256) + 1), dim3(256), 0, tab, 0, params, adam_m, adam_v, set, 1, n,
-            0, 0, 0.f, 1.f, adam_scalars(hp, step), nullptr, nullptr, nullptr, 1);
+  ps.launch(adam_kernel<1>, dim3((unsigned)((n + 255) / 256) + 1), dim3(256), 0, tab, params, adam_m, adam_v, set, 1, n,
+            0, 0, 0.f, 1.f, adam_scalars(hp, step), nullptr, nullptr, 1);
   GMI_LAUNCH_CHECK();
   return GMI_OK;
 }

@@ -1,0 +1,79 @@
+"""The one-launch kernels that take any layer widths -- the resident trainer kernel (bf16) and the fp32 kernels --
+against the per-layer kernels of the same instance (gmi_set_fusion 0), at the sizes where their tiling can go wrong:
+rows around the tile heights, widths around the 32- and 64-wide blocks, one to four hidden layers."""
+import numpy as np
+import pytest
+import torch
+
+from workloads import synthetic as syn
+from gpu_util import rel_l2, rel_max
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def g():
+    import paper_2206_08482_amd as m
+    return m
+
+
+@pytest.fixture(scope="module")
+def inst(g):
+    h = g.gmi_create()
+    yield h
+    g.gmi_destroy(h)
+
+
+def _setup(g, inst, obs, act, hidden, dtype, T, N, rows, seed=3):
+    from paper_2206_08482_amd.runner import RolloutBuffers
+    dev = torch.device("cuda:0")
+    theta = torch.tensor(syn.make_model_params(obs, act, hidden, seed, policy_head_scale=0.5), device=dev)
+    desc = g.model_desc(obs, act, list(hidden), g.dtype_code(dtype), rows)
+    nb = g.gmi_model_shadow_bytes(desc)
+    shadow = torch.zeros(nb, dtype=torch.uint8, device=dev) if nb else None
+    m, v = torch.zeros_like(theta), torch.zeros_like(theta)
+    rb = RolloutBuffers(T, N, obs, act, dev)
+    b = syn.make_rollout_batch(T, N, obs, act, seed=seed)
+    for k in ("obs", "act", "logp", "val", "rew", "done"):
+        getattr(rb, k).copy_(torch.tensor(b[k]))
+    rb.adv.copy_(torch.tensor(b["val"])); rb.ret.copy_(torch.tensor(b["rew"]))
+    torch.cuda.synchronize()
+    model = g.gmi_model_bind(inst, desc, theta, shadow, m, v)
+    g.gmi_model_refresh_shadow(inst, model)
+    buf = g.gmi_buffer_bind(inst, rb.desc(0, N))
+    return model, buf, (theta, shadow, m, v, rb)
+
+
+def _gradients(g, inst, model, buf, n_par, T, N, rows, fused):
+    g.gmi_set_fusion(inst, fused)
+    idx = torch.tensor(np.random.default_rng(1).permutation(T * N)[:rows].astype(np.int32), device="cuda:0")
+    hp = g.ppo_hparams(clip=0.2, c_v=0.5, c_e=0.01, minibatch=rows)
+    grad, stats = torch.zeros(n_par, device="cuda:0"), torch.zeros(5, device="cuda:0")
+    torch.cuda.synchronize()
+    g.ppo_gradient(inst, model, buf, hp, idx, rows, grad, stats)
+    g.gmi_sync(inst)
+    g.gmi_set_fusion(inst, 1)
+    return grad.cpu().numpy(), stats.cpu().numpy()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("obs,act,hidden", [
+    (45, 12, (128, 128)), (60, 8, (256, 128, 64)), (3, 1, (32,)), (64, 32, (33, 65)), (5, 23, (100, 48, 32)),
+    (130, 22, (256, 32)), (44, 18, (300, 200, 200)), (70, 11, (400, 128, 128, 64)), (251, 16, (100, 100)),
+    (197, 14, (512, 200, 100)), (16, 4, (48,))])
+@pytest.mark.parametrize("rows", [1, 31, 33, 130, 4097, 16500])
+def test_gradient_equals_the_per_layer_kernels(g, inst, obs, act, hidden, dtype, rows):
+    T, N = (1, rows) if rows < 100 else (2, (rows + 1) // 2)
+    model, buf, keep = _setup(g, inst, obs, act, hidden, dtype, T, N, rows)
+    n = keep[0].numel()
+    a, sa = _gradients(g, inst, model, buf, n, T, N, rows, 1)
+    b, sb = _gradients(g, inst, model, buf, n, T, N, rows, 0)
+    assert np.isfinite(a).all()
+    tol = 1e-5 if dtype == "f32" else 5e-3          # bf16: same roundings, other order of the fp32 sums
+    if rows < 100 and dtype == "bf16":
+        tol = 2e-2                                   # few rows: one activation that rounds the other way is not averaged
+    assert rel_l2(a, b) <= tol, rel_l2(a, b)
+    assert rel_max(a, b) <= 4 * tol, rel_max(a, b)
+    assert np.allclose(sa, sb, rtol=tol, atol=tol)
+    g.gmi_buffer_destroy(buf)
+    g.gmi_model_destroy(model)
