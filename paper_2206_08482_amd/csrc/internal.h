@@ -130,6 +130,7 @@ struct LayerInfo {
   int in, out;           // logical sizes
   int in_pad, out_pad;   // padded to multiples of 32
   int64_t w_off, b_off;  // offsets into the flat fp32 parameter vector
+  int64_t part_w, part_b;     // offsets (floats) into a row of gradient partials, see ModelLayout::part_floats
   int64_t sh_wf;              // bf16 W in matrix-core fragment order (see wfrag_index)
   int64_t sh_wtf;             // bf16 W^T in the same order (rows = input features)
   int64_t sh_w, sh_wt, sh_b;  // byte offsets into the shadow (bf16 W [out_pad,in_pad], bf16 W^T
@@ -144,6 +145,13 @@ struct ModelLayout {
   int64_t logstd_off;                         // into flat params
   int64_t sh_logstd;                          // byte offset into shadow (fp32 [act_dim])
   int64_t n_params;
+  // floats of one row of gradient partials.  F32: the flat parameter vector.  BF16: what the matrix instruction leaves in
+  // its lanes, so that kernels write and Adam reads whole 1 KiB pieces: per layer, 32 x 32 tile (ot, it) of W
+  // [out_pad, in_pad] by tile, quad q of it = 256 floats at part_w + ((ot in_pad / 32 + it) 4 + q) 256, element
+  // 4 (32 h + i) + e = (output 32 ot + 8 q + 4 h + e, input 32 it + i); then the layer's out_pad bias sums at part_b.
+  // (4-byte stores of row-major rows took 16 cycles each: 16 k cycles per workgroup for a 57 k-weight net.)
+  // Quads without a real output are neither written nor read.
+  int64_t part_floats;
   int64_t shadow_bytes;
   int64_t weight_bytes;                       // bf16 bytes of one copy of all weights (padded), both nets
   int64_t sh_chain[2];                        // byte offsets of the two nets' chain streams (chain.hip)
@@ -173,7 +181,7 @@ struct gmi_model {
   float* val;       // [max_rows]
   // minibatch gathers
   float *mb_act, *mb_logp, *mb_adv, *mb_ret;
-  // gradient partials [part_rows, n_params] and stats partials
+  // gradient partials [part_rows, L.part_floats] and stats partials
   float* grad_part;
   int n_split_max;  // most row splits of a weight-gradient launch
   int part_rows;    // rows of grad_part (at least n_split_max)
@@ -233,7 +241,8 @@ int launch_linear(gmi_instance* g, int dtype, int epi, int rows, const LinearBat
 
 // dW[o, i] = sum_r dz[r, o] * x[r, i],  db[o] = sum_r dz[r, o], reduced over row splits:
 // split sp covers rows [sp*chunk, min(rows, (sp+1)*chunk)) and writes
-// part[sp * part_stride + w_off + o*in + i] and part[sp * part_stride + b_off + o].
+// part[sp * part_stride + w_off + o*in + i] and part[sp * part_stride + b_off + o] (fp32), or the tiled form described at
+// ModelLayout::part_floats with w_off = part_w, b_off = part_b (bf16).
 struct WgradProblem {
   const void* dz; int lddz;
   const void* x; int ldx;
@@ -292,7 +301,7 @@ int launch_train_resident(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gm
                           int* n_parts, int* n_stat_rows);
 bool resident_supported(const ModelLayout& L);
 int resident_part_rows(const ModelLayout& L);
-bool use_resident(const ModelLayout& L);
+bool use_resident(const ModelLayout& L, int rows);
 bool chain_compiled(const ModelLayout& L);       // a register-chained or row-tile trainer kernel has this shape
 
 // Shuffles of epochs epoch0 .. epoch0 + n_epochs - 1 into out[e][n], one launch.
@@ -350,7 +359,7 @@ int launch_train_chain(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_p
                        int* n_stat_rows, bool obs16_ready, bool* blocks);
 // Before the minibatches of an update: converts all observations of the buffer into b->obs16 if the chained kernel
 // will run and cannot read the fp32 rows itself.  *ready = whether it did.
-int prepare_obs16(gmi_instance* g, gmi_model* m, gmi_buffer* b, bool* ready);
+int prepare_obs16(gmi_instance* g, gmi_model* m, gmi_buffer* b, int rows, bool* ready);
 
 }  // namespace gmi
 
@@ -384,7 +393,7 @@ __host__ __device__ static inline int64_t wfrag_index(int o, int i, int in_pad) 
 
 // Where each parameter lives in the flat vector and in the bf16 shadow (kernel argument).
 struct ShadowLayer {
-  int64_t w_off, b_off;
+  int64_t w_off, b_off, part_w, part_b;
   int in, out, in_pad, out_pad;
   int64_t sh_w, sh_wt, sh_b, sh_wf, sh_wtf;      // sh_wtf < 0: nobody reads that copy
 };
@@ -402,7 +411,7 @@ static inline ShadowTable make_shadow_table(const ModelLayout& L) {
   for (int net = 0; net < 2; ++net)
     for (const LayerInfo& li : L.net[net]) {
       ShadowLayer& s = t.l[t.n++];
-      s.w_off = li.w_off; s.b_off = li.b_off; s.in = li.in; s.out = li.out;
+      s.w_off = li.w_off; s.b_off = li.b_off; s.part_w = li.part_w; s.part_b = li.part_b; s.in = li.in; s.out = li.out;
       s.in_pad = li.in_pad; s.out_pad = li.out_pad; s.sh_w = li.sh_w; s.sh_wt = li.sh_wt; s.sh_b = li.sh_b; s.sh_wf = li.sh_wf;
       s.sh_wtf = resident ? li.sh_wtf : -1;
     }

@@ -549,19 +549,25 @@ __device__ __forceinline__ void wgrad_tile(const gmi::WgradProblem& P, int local
     }
   }
 
+  // tiled partials (ModelLayout::part_floats): a quad of results of a 32 x 32 tile is one 16-byte store per lane
   float* dst = part + (int64_t)sp * part_stride;
+  const int n_it = P.in_pad >> 5;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
+    const int ot = (o0 >> 5) + wo * 2 + i;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int o = o0 + (wo * 2 + i) * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-      if (o >= P.out) continue;
+    for (int q = 0; q < 4; ++q) {
+      if (32 * ot + 8 * q >= P.out) continue;
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        const int ii = i0 + (wi * 2 + j) * 32 + (lane & 31);
-        if (ii < P.in) dst[P.w_off + (int64_t)o * P.in + ii] = acc[i][j][v];
+        const int it = (i0 >> 5) + wi * 2 + j;
+        if (it < n_it)
+          *reinterpret_cast<float4*>(dst + P.w_off + (((int64_t)ot * n_it + it) * 4 + q) * 256 + lane * 4) =
+              make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
       }
-      if (do_bias && (lane & 31) == 0) dst[P.b_off + o] = accb[i][v];
+      if (do_bias && (lane & 31) == 0)
+        *reinterpret_cast<float4*>(dst + P.b_off + 32 * ot + 8 * q + 4 * (lane >> 5)) =
+            make_float4(accb[i][4 * q], accb[i][4 * q + 1], accb[i][4 * q + 2], accb[i][4 * q + 3]);
     }
   }
 }

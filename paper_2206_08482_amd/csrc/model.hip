@@ -20,7 +20,7 @@ int build_layout(const gmi_model_desc* d, ModelLayout* L) {
   L->n_hidden = d->n_hidden;
   L->n_layers = d->n_hidden + 1;
   L->dtype = d->dtype;
-  int64_t off = 0, sh = 0, wbytes = 0;
+  int64_t off = 0, sh = 0, wbytes = 0, pf = 0;
   int maxw = gmi::pad32(d->obs_dim);
   for (int net = 0; net < 2; ++net) {
     L->net[net].clear();
@@ -41,6 +41,12 @@ int build_layout(const gmi_model_desc* d, ModelLayout* L) {
       wbytes += (int64_t)li.out_pad * li.in_pad * 2;
       li.sh_b = sh;  sh += gmi::align_up((int64_t)li.out_pad * 4, 256);
       if (li.out_pad > maxw) maxw = li.out_pad;
+      if (d->dtype == GMI_DTYPE_BF16) {
+        li.part_w = pf; pf += (int64_t)li.out_pad * li.in_pad;
+        li.part_b = pf; pf += li.out_pad;
+      } else {
+        li.part_w = li.w_off; li.part_b = li.b_off;
+      }
       L->net[net].push_back(li);
       prev = li.out;
     }
@@ -50,6 +56,7 @@ int build_layout(const gmi_model_desc* d, ModelLayout* L) {
   L->sh_logstd = sh;
   sh += gmi::align_up((int64_t)d->act_dim * 4, 256);
   L->n_params = off;
+  L->part_floats = d->dtype == GMI_DTYPE_BF16 ? (pf + 255) & ~(int64_t)255 : off;
   L->weight_bytes = wbytes;
   L->max_width_pad = maxw;
   // the register-chained trainer kernel's weight streams (one per net), after everything else
@@ -365,7 +372,7 @@ extern "C" int gmi_model_bind(gmi_t g, const gmi_model_desc* d, float* params, v
     m->mb_logp = (float*)take(rows * 4);
     m->mb_adv = (float*)take(rows * 4);
     m->mb_ret = (float*)take(rows * 4);
-    m->grad_part = (float*)take((int64_t)m->part_rows * L.n_params * 4);
+    m->grad_part = (float*)take((int64_t)m->part_rows * L.part_floats * 4);
     m->stat_part = (float*)take((int64_t)(gmi::kLossBlocksMax + 1) * (gmi::kStatStride + A) * 4);
     if (pass == 0) {
       m->ws_bytes = (size_t)off;

@@ -44,7 +44,7 @@ struct ResLayer {
   int K, F;                // padded widths
   int in, out;             // logical widths
   int x_off, b_off;        // LDS: the layer's input rows (elements), its biases (floats)
-  int w_par, b_par;        // offsets into the parameter vector
+  int w_par, b_par;        // offsets into a row of gradient partials (ModelLayout::part_floats)
 };
 struct ResNet {
   ResLayer l[kMaxLayers];
@@ -490,25 +490,23 @@ __global__ __launch_bounds__(kNT) void train_resident_kernel(ResArgs a) {
       const int l = (int)(gd[n] >> 24);
       if (l < nl) {
         const ResLayer& L = N.l[l];
-        const int o0 = 32 * ((gd[n] >> 12) & 0xFFF), i0 = 32 * (gd[n] & 0xFFF);
-        float* dw = part + L.w_par;
+        const int ob = (gd[n] >> 12) & 0xFFF, ib = gd[n] & 0xFFF, n_it = L.K >> 5;
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int o = o0 + 32 * i + 8 * (v >> 2) + 4 * h + (v & 3);
-            if (o >= L.out) continue;
+          for (int q = 0; q < 4; ++q) {
+            if (32 * (ob + i) + 8 * q >= L.out) continue;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-              const int ii = i0 + 32 * j + s;
-              if (ii < L.in) dw[(int64_t)o * L.in + ii] = gw[n][i][j][v];
-            }
+            for (int j = 0; j < 2; ++j)
+              if (ib + j < n_it)
+                *reinterpret_cast<float4*>(part + L.w_par + ((((ob + i) * n_it + ib + j) * 4 + q) << 8) + lane * 4) =
+                    make_float4(gw[n][i][j][4 * q], gw[n][i][j][4 * q + 1], gw[n][i][j][4 * q + 2], gw[n][i][j][4 * q + 3]);
           }
-        if (i0 == 0) {
+        if (ib == 0) {
 #pragma unroll
           for (int i = 0; i < 2; ++i) {
             const float b = gb[n][i] + __shfl_xor(gb[n][i], 32, 64);
-            if (h == 0 && o0 + 32 * i + s < L.out) part[L.b_par + o0 + 32 * i + s] = b;
+            if (h == 0 && 32 * (ob + i) + s < L.F) part[L.b_par + 32 * (ob + i) + s] = b;
           }
         }
       }
@@ -577,7 +575,7 @@ bool plan_lds(const ModelLayout& L, int RT, Plan* p) {
 // Shape conditions alone: one 32-wide head per net, equal padded widths, a 32-row tile in LDS.
 bool shape_ok(const ModelLayout& L) {
   if (L.dtype != GMI_DTYPE_BF16 || L.act_dim > 32) return false;
-  if (L.n_params >= (1ll << 31)) return false;
+  if (L.part_floats >= (1ll << 31)) return false;
   Plan p;
   return plan_lds(L, 1, &p);
 }
@@ -600,11 +598,12 @@ int launch(gmi_instance* g, const ResArgs& a, int grid, size_t lds) {
 namespace gmi {
 
 bool resident_supported(const ModelLayout& L) { return shape_ok(L); }
-bool use_resident(const ModelLayout& L) {
-  static const char* e = getenv("GMI_RES");
+// Where a register-chained or row-tile kernel is compiled for the shape, this kernel is the faster one up to `rows`:
+// per minibatch with Adam, 60:256:128:64:8: 43.8 against 56.2 us at 2048 rows, 63.3 / 66.5 at 16384, 91.9 / 89.9 at 32768;
+// 108:400:200:100:21 (gradients not in registers): 50.5 / 64.5 at 2048, 69.0 / 75.2 at 8192, 117 / 98 at 16384.
+bool use_resident(const ModelLayout& L, int rows) {
   if (!shape_ok(L)) return false;
-  if (e) return atoi(e) != 0;
-  return resident_part_rows(L) > 0 || !chain_compiled(L);
+  return !chain_compiled(L) || rows <= (resident_part_rows(L) > 0 ? 16384 : 8192);
 }
 
 // Rows of gradient partials the kernel may fill with this model.
@@ -649,7 +648,7 @@ int launch_train_resident(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gm
       r.dz_out = (uint16_t*)m->dz[net][l];
       r.K = li.in_pad; r.F = li.out_pad; r.in = li.in; r.out = li.out;
       r.x_off = p.x_off[l]; r.b_off = p.b_off[l];
-      r.w_par = (int)li.w_off; r.b_par = (int)li.b_off;
+      r.w_par = (int)li.part_w; r.b_par = (int)li.part_b;
     }
     // the layers with the most blocks first, so that their blocks spread over all waves
     std::vector<std::pair<int, int>> order;
@@ -670,7 +669,7 @@ int launch_train_resident(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gm
   a.idx = idx;
   a.b_obs = b->d.obs; a.b_act = b->d.act; a.b_logp = b->d.logp; a.b_adv = b->d.adv; a.b_ret = b->d.ret;
   a.clip = hp->clip; a.c_v = hp->c_v;
-  a.part = m->grad_part; a.part_stride = L.n_params;
+  a.part = m->grad_part; a.part_stride = L.part_floats;
   a.stat_part = m->stat_part;
   int grid;
   if (NS > 0) {

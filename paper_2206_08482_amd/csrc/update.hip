@@ -218,7 +218,7 @@ __device__ __forceinline__ void finish_stats(const gmi::ShadowTable& tab, float*
   }
 }
 
-// fp32 models, caller-supplied gradients, and gradients that are only read (ppo_gradient): a workgroup of 64 G waves'
+// fp32 models and caller-supplied gradients (partials in flat parameter order): a workgroup of 64 G waves'
 // worth of threads owns 256 consecutive parameters, G threads per parameter each summing every G-th partial row.
 // grad(p) = (1/n) sum_i sum_s part_i[s * part_stride + p]: the in-memory mean over the n replicas (Section 4.1's gradient
 // reduction for instances that share one address space), fixed summation order.  The last workgroup finalises the
@@ -280,77 +280,103 @@ __device__ __forceinline__ int chain_block_index(int nft, int nks, int gm, int f
   return base + ks * gs + t;
 }
 
-// BF16 update: Adam and every bf16 copy of the weights in one pass (a second kernel that rebuilt the transposed copies
-// from the first one's output cost 5-6 us per minibatch, most of it launch and round trips).  A workgroup owns an 8
-// (outputs) x 32 (inputs) tile of one layer's W -- 128-byte rows of the partials, and just what the copies' 16-byte
-// pieces need: 8 consecutive inputs of an output (row-major and fragment-major W), 8 consecutive outputs of an input
-// (W^T, its fragment-major copy), the chain streams' permuted k orders -- and, in the first input tile, the 8 biases.
-// G threads per parameter, each summing every G-th partial row: 4 where the model has few tiles or the partials are many
-// rows, so that the sums do not become one long chain of loads in a few workgroups.
+// BF16 models: the sum of the partials, Adam and every bf16 copy of the weights in one pass (a second kernel that rebuilt
+// the transposed copies from the first one's output cost 5-6 us per minibatch, most of it launch and round trips).  A
+// workgroup owns one quad of one 32 x 32 tile of the partials (ModelLayout::part_floats) = 8 outputs x 32 inputs, i.e. 1 KiB
+// of every partial row, and just what the copies' 16-byte pieces need: 8 consecutive inputs of an output (row-major and
+// fragment-major W), 8 consecutive outputs of an input (W^T, its fragment-major copy), the chain streams' permuted k
+// orders; in the first input tile also the 8 biases.  Wave w sums the partial rows w, w + 4, ...  grad_out: the gradient
+// into the flat parameter order instead, updating nothing.
 struct AdamTiles {
   int n;
   int start[gmi::kMaxWgradProblems + 1];
 };
-template <int G>
-__global__ __launch_bounds__(256 * G) void adam_shadow_kernel(gmi::ShadowTable tab, AdamTiles tt, gmi::ChainEmit ce,
-                                                              float* __restrict__ params, float* __restrict__ am,
-                                                              float* __restrict__ av, PartSet ps, int n_split,
-                                                              int64_t part_stride, int n_loss_blocks, int A, float c_e,
-                                                              float inv_rows, AdamScalars hs, char* __restrict__ shadow,
-                                                              float* __restrict__ stats_out) {
-  __shared__ float s_sum[264 * G];
+__global__ __launch_bounds__(256) void adam_shadow_kernel(gmi::ShadowTable tab, AdamTiles tt, gmi::ChainEmit ce,
+                                                          float* __restrict__ params, float* __restrict__ am,
+                                                          float* __restrict__ av, PartSet ps, int n_split,
+                                                          int64_t part_stride, int n_loss_blocks, int A, float c_e,
+                                                          float inv_rows, AdamScalars hs, char* __restrict__ shadow,
+                                                          float* __restrict__ stats_out, float* __restrict__ grad_out,
+                                                          int do_update) {
+  __shared__ __attribute__((aligned(16))) float s_sum[4][256];
+  __shared__ float s_bsum[4][8];
   __shared__ __attribute__((aligned(16))) uint16_t s_t[8][40];
   const int n_tiles = gridDim.x - 1;
   if ((int)blockIdx.x == n_tiles) {
-    finish_stats<256 * G>(tab, params, am, av, ps, n_split, part_stride, n_loss_blocks, A, c_e, inv_rows, hs,
-                          reinterpret_cast<float*>(shadow + tab.sh_logstd), stats_out, nullptr, 1, s_sum);
+    finish_stats<256>(tab, params, am, av, ps, n_split, part_stride, n_loss_blocks, A, c_e, inv_rows, hs,
+                      do_update ? reinterpret_cast<float*>(shadow + tab.sh_logstd) : nullptr, stats_out, grad_out, do_update, &s_sum[0][0]);
     return;
   }
-  // neighbouring tiles, which share the memory lines of unaligned rows, on the same die (ids go round-robin over 8)
+  // neighbouring tiles, which share memory lines of the parameters and moments, on the same die (ids go round-robin over 8)
   const int per = n_tiles >> 3, whole = per << 3;
   const int tile = (int)blockIdx.x < whole ? (blockIdx.x & 7) * per + (blockIdx.x >> 3) : blockIdx.x;
-  int li = 0;
-  while (li + 1 < tt.n && tile >= tt.start[li + 1]) ++li;
+  int li = 0;      // the layer whose tiles hold this one (entries past the last layer hold no tile: all loads at once)
+#pragma unroll
+  for (int k = 1; k < gmi::kMaxWgradProblems; ++k) li += tile >= tt.start[k] ? 1 : 0;
   const gmi::ShadowLayer& L = tab.l[li];
   const int local = tile - tt.start[li], n_ti = (L.in + 31) >> 5;
-  const int o0 = (local / n_ti) * 8, i0 = (local % n_ti) * 32;
-  const int t = threadIdx.x & 255, grp = threadIdx.x >> 8;
+  const int o0 = (local / n_ti) * 8, it = local % n_ti, i0 = it * 32;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int o = o0 + (t >> 5), i = i0 + (t & 31);
   const bool ok = o < L.out && i < L.in;
   const bool okb = i0 == 0 && t < 8 && o0 + t < L.out;
   const int64_t p = ok ? L.w_off + (int64_t)o * L.in + i : L.w_off, pb = okb ? L.b_off + o0 + t : L.b_off;
   float m0 = 0.f, v0 = 0.f, w0 = 0.f, mb = 0.f, vb = 0.f, wb = 0.f;
-  if (grp == 0) {
+  if (do_update) {
     m0 = am[p]; v0 = av[p]; w0 = params[p];
     if (okb) { mb = am[pb]; vb = av[pb]; wb = params[pb]; }
   }
-  float g = sum_partials<G>(ps, p, n_split, part_stride, grp);
-  float gb = okb ? sum_partials<G>(ps, pb, n_split, part_stride, grp) : 0.f;
-  if constexpr (G > 1) {
-    s_sum[grp * 264 + t] = g;
-    if (t < 8) s_sum[grp * 264 + 256 + t] = gb;
-    __syncthreads();
-    if (grp == 0) {
+  const int64_t src = L.part_w + (((int64_t)(o0 >> 5) * (L.in_pad >> 5) + it) * 4 + ((o0 >> 3) & 3)) * 256 +
+                      4 * (i0 + (lane & 31) < L.in ? lane : lane & 32);      // padding inputs read a neighbour
+  const int64_t srcb = L.part_b + o0 + (lane & 7);
+  float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
+  float gb = 0.f;
+  for (int k = 0; k < ps.n; ++k) {
+    const float* q = ps.part[k] + src;
+    const float* qb = ps.part[k] + srcb;
+    auto add = [&](int s, auto n) {      // rows s, s + 4, ...: all loads before the first addition, fixed order
+      constexpr int U = decltype(n)::value;
+      float4 x[U];
+      float y[U];
 #pragma unroll
-      for (int q = 1; q < G; ++q) {
-        g += s_sum[q * 264 + t];
-        if (t < 8) gb += s_sum[q * 264 + 256 + t];
+      for (int u = 0; u < U; ++u) x[u] = *reinterpret_cast<const float4*>(q + (int64_t)min(s + 4 * u, n_split - 1) * part_stride);
+      if (i0 == 0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) y[u] = qb[(int64_t)min(s + 4 * u, n_split - 1) * part_stride];
       }
-    }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (s + 4 * u < n_split) {
+          g.x += x[u].x; g.y += x[u].y; g.z += x[u].z; g.w += x[u].w;
+          if (i0 == 0) gb += y[u];
+        }
+    };
+    int s = wave;
+    for (; s + 16 < n_split; s += 32) add(s, std::integral_constant<int, 8>{});
+    if (s < n_split) add(s, std::integral_constant<int, 4>{});
   }
-  if (grp == 0) {
-    const float inv_n = 1.0f / (float)ps.n;
-    adam_step(g * inv_n, m0, v0, w0, hs);
-    if (ok) { am[p] = m0; av[p] = v0; params[p] = w0; }
-    s_t[t >> 5][t & 31] = ok ? f_to_bf16_u(w0) : 0;
-    if (okb) {
-      adam_step(gb * inv_n, mb, vb, wb, hs);
-      am[pb] = mb; av[pb] = vb; params[pb] = wb;
-      reinterpret_cast<float*>(shadow + L.sh_b)[o0 + t] = wb;
-    }
+  *reinterpret_cast<float4*>(&s_sum[wave][lane * 4]) = g;
+  if (lane < 8) s_bsum[wave][lane] = gb;
+  __syncthreads();
+  const float inv_n = 1.0f / (float)ps.n;
+  // element of (o, i): 4 (32 h + i) + e with o - o0 = 4 h + e
+  const int el = 4 * (32 * (t >> 7) + (t & 31)) + ((t >> 5) & 3);
+  const float gs = (((s_sum[0][el] + s_sum[1][el]) + s_sum[2][el]) + s_sum[3][el]) * inv_n;
+  const float gbs = t < 8 ? (((s_bsum[0][t] + s_bsum[1][t]) + s_bsum[2][t]) + s_bsum[3][t]) * inv_n : 0.f;
+  if (grad_out) {
+    if (ok) grad_out[p] = gs;
+    if (okb) grad_out[pb] = gbs;
+  }
+  if (!do_update) return;
+  adam_step(gs, m0, v0, w0, hs);
+  if (ok) { am[p] = m0; av[p] = v0; params[p] = w0; }
+  s_t[t >> 5][t & 31] = ok ? f_to_bf16_u(w0) : 0;
+  if (okb) {
+    adam_step(gbs, mb, vb, wb, hs);
+    am[pb] = mb; av[pb] = vb; params[pb] = wb;
+    reinterpret_cast<float*>(shadow + L.sh_b)[o0 + t] = wb;
   }
   __syncthreads();
-  if (threadIdx.x >= 256) return;
   auto column = [&](int c) {      // the 8 outputs of input c
     uint4 v;
     v.x = s_t[0][c] | ((uint32_t)s_t[1][c] << 16); v.y = s_t[2][c] | ((uint32_t)s_t[3][c] << 16);
@@ -490,7 +516,7 @@ int minibatch_pass(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_h
     if (rc == GMI_OK) { *n_loss_blocks_out = *n_split_out; return GMI_OK; }
     if (rc != GMI_ERR_UNSUPPORTED) return rc;
   }
-  if (g->fusion >= 1 && want_grad && bf && gmi::use_resident(L)) {
+  if (g->fusion >= 1 && want_grad && bf && gmi::use_resident(L, rows)) {
     // the tile's activations resident in LDS; small nets' weight gradients in the same launch
     rc = gmi::launch_train_resident(g, m, b, hp, idx, rows, n_split_out, n_loss_blocks_out);
     if (rc == GMI_OK && *n_split_out > 0) return GMI_OK;
@@ -517,13 +543,13 @@ int minibatch_pass(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_h
       p.dz = m->dz[net][l]; p.lddz = li.out_pad;
       p.x = m->h[net][l]; p.ldx = li.in_pad;
       p.out = li.out; p.in = li.in; p.out_pad = li.out_pad; p.in_pad = li.in_pad;
-      p.w_off = li.w_off; p.b_off = li.b_off;
+      p.w_off = li.part_w; p.b_off = li.part_b;
       // the row-tile kernel leaves every activation and every gradient in its block layout
       if (blocks && l == 0) p.x = m->x0b;
       p.x_blocks = blocks ? (l == 0 ? 2 : 1) : 0;
       p.dz_blocks = blocks ? 1 : 0;
     }
-  return gmi::launch_wgrad(g, L.dtype, rows, n_split, chunk, wb, m->grad_part, L.n_params);
+  return gmi::launch_wgrad(g, L.dtype, rows, n_split, chunk, wb, m->grad_part, L.part_floats);
 }
 
 // Reduces the partials of the n bindings ms[0..n) (replicas of one model: same parameter arrays, own
@@ -539,31 +565,29 @@ int launch_adam(gmi_instance* g, gmi_model* const* ms, int n, int n_split, int n
     set.part[i] = i < n ? ms[i]->grad_part : nullptr;
     set.stat[i] = i < n ? ms[i]->stat_part : nullptr;
   }
-  // four threads per parameter where one per parameter would leave the device short of loads in flight (fewer than
-  // about 1024 workgroups of 256) or make each thread walk a long column
-  const bool split4 = n_split >= 4 && (n_split >= 64 || m->L.logstd_off < 256 * 1024);
-  if (m->L.dtype == GMI_DTYPE_BF16 && do_update && !grad_out) {
+  if (m->L.dtype == GMI_DTYPE_BF16) {
     AdamTiles tt;
     tt.n = tab.n;
     int total = 0;
     for (int i = 0; i < tab.n; ++i) {
       tt.start[i] = total;
-      total += ((tab.l[i].out + 7) / 8) * ((tab.l[i].in + 31) / 32);
+      if (do_update || grad_out) total += ((tab.l[i].out + 7) / 8) * ((tab.l[i].in + 31) / 32);
     }
-    tt.start[tab.n] = total;
+    for (int i = tab.n; i <= gmi::kMaxWgradProblems; ++i) tt.start[i] = INT32_MAX;
     gmi::ChainEmit ce;
     gmi::fill_chain_emit(m->L, &ce);
-    auto go = [&](auto kernel, int threads) {
-      ps.launch(kernel, dim3(total + 1), dim3(threads), 0, tab, tt, ce, m->params, m->adam_m, m->adam_v, set, n_split,
-                m->L.n_params, n_loss_blocks, m->L.act_dim, hp->c_e, 1.0f / (float)rows, adam_scalars(hp, k), m->shadow, stats_out);
-    };
-    if (split4) go(adam_shadow_kernel<4>, 1024); else go(adam_shadow_kernel<1>, 256);
+    ps.launch(adam_shadow_kernel, dim3(total + 1), dim3(256), 0, tab, tt, ce, m->params, m->adam_m, m->adam_v, set, n_split,
+              m->L.part_floats, n_loss_blocks, m->L.act_dim, hp->c_e, 1.0f / (float)rows, adam_scalars(hp, k), m->shadow,
+              stats_out, grad_out, do_update ? 1 : 0);
     GMI_LAUNCH_CHECK();
     return GMI_OK;
   }
+  // four threads per parameter where one per parameter would leave the device short of loads in flight (fewer than
+  // about 1024 workgroups of 256) or make each thread walk a long column
+  const bool split4 = n_split >= 4 && (n_split >= 64 || m->L.logstd_off < 256 * 1024);
   const unsigned grid = (unsigned)((m->L.logstd_off + 255) / 256) + 1;
   auto go = [&](auto kernel, int threads) {
-    ps.launch(kernel, dim3(grid), dim3(threads), 0, tab, m->params, m->adam_m, m->adam_v, set, n_split, m->L.n_params,
+    ps.launch(kernel, dim3(grid), dim3(threads), 0, tab, m->params, m->adam_m, m->adam_v, set, n_split, m->L.part_floats,
               n_loss_blocks, m->L.act_dim, hp->c_e, 1.0f / (float)rows, adam_scalars(hp, k), stats_out, grad_out, do_update ? 1 : 0);
   };
   if (split4) go(adam_kernel<4>, 1024); else go(adam_kernel<1>, 256);
@@ -592,7 +616,7 @@ extern "C" int ppo_update(gmi_t g, gmi_model_t m, gmi_buffer_t b, const gmi_ppo_
   const int nmb = (int)(B / hp->minibatch);
   uint32_t k = hp->adam_step0;
   bool obs16 = false;
-  rc = gmi::prepare_obs16(g, m, b, &obs16);
+  rc = gmi::prepare_obs16(g, m, b, hp->minibatch, &obs16);
   if (rc != GMI_OK) return rc;
   for (int e = 0; e < hp->epochs; ++e) {
     // the shuffles of up to kPermEpochs epochs in one launch (each launch of this small kernel is mostly latency)
@@ -658,7 +682,7 @@ extern "C" int ppo_update_group(const gmi_t* gs, const gmi_model_t* ms, const gm
   // theirs alone, but the shared parameters were last written on stream 0): nothing to order before the loop.
   bool obs16[kMaxGroup];
   for (int i = 0; i < n; ++i) {
-    rc = gmi::prepare_obs16(gs[i], ms[i], bs[i], &obs16[i]);
+    rc = gmi::prepare_obs16(gs[i], ms[i], bs[i], hp->minibatch, &obs16[i]);
     if (rc != GMI_OK) return rc;
   }
   for (int e = 0; e < hp->epochs; ++e) {
