@@ -258,7 +258,7 @@ constexpr int kMaxWgradProblems = 2 * (GMI_MAX_HIDDEN + 1);
 struct WgradBatch {
   int n;
   WgradProblem p[kMaxWgradProblems];
-  int blk_start[kMaxWgradProblems + 1];
+  int tiles[kMaxWgradProblems], net_tiles[2];      // bf16, filled by launch_wgrad: output tiles per problem and per net
 };
 int launch_wgrad(gmi_instance* g, int dtype, int rows, int n_split, int chunk, WgradBatch& batch,
                  float* part, int64_t part_stride);
@@ -364,16 +364,13 @@ int prepare_obs16(gmi_instance* g, gmi_model* m, gmi_buffer* b, int rows, bool* 
 }  // namespace gmi
 
 namespace gmi {
-constexpr int kSplitMin = 16;        // row splits of the weight-gradient reduction: lower and
-constexpr int kSplitMax = 32;        // upper bound of the per-model choice below
-
-// Row splits for a weight-gradient launch over n_tiles 128x128 output tiles.  Two workgroups fit a
-// compute unit, so up to 512 are resident at once; few-tile models get more splits to approach that.
-// The count stays a multiple of 8: workgroups go round-robin over the 8 XCDs, so with split = index % count
-// every tile of one split (which reads the same rows) lands on the same XCD and shares its L2.  Counts
-// that are not a multiple of 8 measured 1.4-2x slower.
+// Row splits for a weight-gradient launch over n_tiles 256 x 256 output tiles of both nets: as many as keep it in one round
+// of one workgroup per compute unit, in multiples of 4 (a split's two nets are the units that are dealt to the 8 dies),
+// at least 8 and at most 32 (each is a partial gradient that Adam reads).
+constexpr int kSplitMin = 8, kSplitMax = 32;
+static inline int wgrad_tiles(int out_pad, int in_pad) { return ((out_pad + 255) / 256) * ((in_pad + 255) / 256); }
 static inline int wgrad_split_limit(int n_tiles) {
-  int s = (512 / (n_tiles > 0 ? n_tiles : 1)) / 8 * 8;
+  int s = (256 / (n_tiles > 0 ? n_tiles : 1)) / 4 * 4;
   if (s < kSplitMin) s = kSplitMin;
   if (s > kSplitMax) s = kSplitMax;
   return s;

@@ -3,8 +3,9 @@
 // BF16 path: v_mfma_f32_32x32x16_bf16 (bf16 operands, fp32 accumulate).  A wavefront of 64 lanes
 // feeds the matrix core with 8 consecutive contraction elements per lane for both operands, so both
 // operands are staged in LDS with the contraction index contiguous; the weight-gradient product
-// contracts over samples, whose index is strided in memory, and transposes 8x8 blocks in registers
-// while staging.  F32 path: plain FMA loops (used for small fp32 configurations only).
+// contracts over samples, whose index is strided in memory, and reads its operands through the transposing LDS read.  F32 path: plain FMA loops (used for small fp32 configurations only).
+#include <algorithm>
+
 #include "internal.h"
 
 namespace {
@@ -362,226 +363,301 @@ __global__ __launch_bounds__(128 * WRN) void linear_bf16_big_kernel(gmi::LinearB
 }
 
 // ------------------------------------------------------------------------------------------------
-// Weight gradient: D[o, i] = sum_r dz[r, o] x[r, i].  Tile 128 (o) x 128 (i), 2 x 2 waves of 2 x 2
-// matrix-core tiles; the contraction runs over the rows of one split, 64 rows per stage.  Each thread
-// stages one 8 (rows) x 8 (features) block per step and transposes it in registers so that LDS holds
-// [feature][row] with rows contiguous.
-__device__ __forceinline__ void transpose8x8(const uint4 in[8], uint4 out[8]) {
-  // in[j] = 8 bf16 of row j (features 0..7); out[i] = 8 bf16 of feature i (rows 0..7).
-  // One byte-permute per output dword: low halves (even feature) or high halves (odd feature) of the
-  // same dword of two consecutive rows.
-  const uint32_t* s = reinterpret_cast<const uint32_t*>(in);
-  uint32_t* d = reinterpret_cast<uint32_t*>(out);
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      const uint32_t a = s[(2 * p) * 4 + (i >> 1)];       // row 2p,   features (i&~1), (i|1)
-      const uint32_t b = s[(2 * p + 1) * 4 + (i >> 1)];   // row 2p+1
-      // v_perm_b32(S0 = b, S1 = a): selector bytes index {S1: 0..3, S0: 4..7}
-      d[i * 4 + p] = __builtin_amdgcn_perm(b, a, (i & 1) ? 0x07060302u : 0x05040100u);
-    }
-  }
+// Weight gradient: D[o, i] = sum_r dz[r, o] x[r, i].  Tile 256 (o) x 256 (i), 8 waves of 4 x 2 matrix-core tiles; the
+// contraction runs over the rows of one split, 32 rows per stage.  Both operands go from memory straight into LDS (16
+// bytes per lane, no registers in between) as they lie there, through a ring of four stages: three (96 KiB) are in flight
+// while one is multiplied.  The contraction index is the strided one; the transposing LDS read (per 16 lanes: 4 rows x 16
+// features) delivers operands.  Bias gradients are row sums of the first operand (two-element dot products with ones).
+//
+// Bound: HBM / L2 traffic.  A tile reads 1 KiB per row; with 128 x 128 tiles (through registers, transposed there) the
+// same features were fetched by twice as many workgroups, whose second and third rounds found them evicted: 690 MB per
+// 32768-row minibatch of 211:512:512:256:128:20 for 403 MB of operands.  All workgroups now run in one round with at most
+// one per compute unit, and half as many splits are enough (their partials are another 6 MB each, written here and read
+// by Adam).  Measured on that minibatch: 145 us before, see the table of the design notes for now.
+constexpr int kWgradT = 256;                            // features per operand and tile
+constexpr int kWgradRows = 32;                          // rows per stage
+constexpr int kWgradOperand = kWgradT * kWgradRows * 2; // bytes
+constexpr int kWgradStage = 2 * kWgradOperand;
+constexpr int kWgradRing = 5;
+constexpr int kWgradLds = kWgradRing * kWgradStage;
+__device__ const uint4 g_zero_piece = {0, 0, 0, 0};     // what rows past the end load
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+
+// 16 bytes per lane from base + off to LDS bytes [lds, lds + 1024) in lane order.  Inline assembly: the compiler would
+// wait for every such load in flight before any LDS read.
+__device__ __forceinline__ void load_to_lds(const void* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+}
+__device__ __forceinline__ void load_to_lds(const void* src, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory");
 }
 
-// LAYOUT: 0 both operands row-major, 1 both in the block layout.  A compile-time constant: a run-time branch around
-// the staging loads makes the compiler wait for every load in flight where it should wait for the older of two
-// stages (measured: 1.8x the kernel's time).
-constexpr int kWgradT = 128;
-constexpr int kWgradBuf = 2 * kWgradT * kLds;                        // one LDS stage: [o][row] then [i][row]
+// LAYOUT: 0 both operands row-major, 1 both in the block layout of the row-tile trainer kernel.
 template <int LAYOUT>
-__device__ __forceinline__ void wgrad_tile(const gmi::WgradProblem& P, int local, int rows, int n_split, int chunk,
-                                           float* __restrict__ part, int64_t part_stride, uint16_t* s_stage) {
-  constexpr int T = kWgradT;
-  constexpr int kBuf = kWgradBuf;
-  const int sp = local % n_split;
-  const int tile = local / n_split;
-  const int n_ti = (P.in_pad + T - 1) / T;
-  const int o0 = (tile / n_ti) * T, i0 = (tile % n_ti) * T;
+__global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, int rows, int n_split, int chunk,
+                                                         float* __restrict__ part, int64_t part_stride) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  // workgroup -> (unit, tile of the unit's net), unit = (split, net): a unit's tiles read the same rows, so they belong
+  // on one die (ids go round-robin over the 8 dies and the unit count is a multiple of 8)
+  const int n_units = n_split * 2, unit = blockIdx.x % n_units, net = unit & 1, sp = unit >> 1;
+  int tile = blockIdx.x / n_units;
+  int pi = net * (batch.n >> 1);
+  if (tile >= batch.net_tiles[net]) return;
+  while (tile >= batch.tiles[pi]) tile -= batch.tiles[pi++];
+  const gmi::WgradProblem& P = batch.p[pi];
+  const int n_ti = (P.in_pad + kWgradT - 1) / kWgradT;
+  const int o0 = (tile / n_ti) * kWgradT, i0 = (tile % n_ti) * kWgradT;
   const int row_begin = sp * chunk;
   const int row_end = min(rows, row_begin + chunk);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wo = wave >> 1, wi = wave & 1;
-  const bool is_b = tid >= 128;
-  const int t2 = tid & 127;
-  const int ld = is_b ? P.ldx : P.lddz;
-  const int fmax = is_b ? P.in_pad : P.out_pad;
-  const int f0 = is_b ? i0 : o0;                      // first feature of the operand's 128-wide slice
-  constexpr bool blocks = LAYOUT == 1;
-  const bool natural = blocks && (is_b ? P.x_blocks : P.dz_blocks) == 2;      // k order inside a block's 16-wide step
-  const uint16_t* __restrict__ opnd = is_b ? (const uint16_t*)P.x : (const uint16_t*)P.dz;
-  // A thread stages 8 rows x 8 features per step: the rows rblk + 8 jj + 32 rt (jj = 0..3, rt = 0, 1) of the stage's
-  // 64 -- which 8 rows share a 16-byte piece of LDS does not matter to a sum over rows, as long as both operands
-  // agree.  Row-major operand: 16 feature blocks x 8 row blocks, the thread's features are feat .. feat + 7 and it
-  // reads 16 bytes of each of its rows.  Block layout (internal.h): 8 feature steps x 2 halves x 8 row blocks; the
-  // thread's features are 16 ks + 4 h + {0..3} and 16 ks + 8 + 4 h + {0..3}, row j is slot rblk + 8 (j % 4) of row
-  // tile j / 4 of the stage.
-  int fblk, rblk, feat;
-  int ksl = 0, hb = 0;
-  if (blocks) {
-    rblk = t2 & 7; hb = (t2 >> 3) & 1; ksl = t2 >> 4;  // 8 consecutive lanes read 128 consecutive bytes of a block
-    fblk = 2 * ksl;
-    feat = f0 + 16 * ksl;
+  // ---- loading: waves 0-3 the dz features, waves 4-7 the x features, four 1 KiB pieces per wave and stage
+  const bool is_x = wave >= 4;
+  const int fmax = is_x ? P.in_pad : P.out_pad, f0 = is_x ? i0 : o0;
+  const char* opnd = is_x ? (const char*)P.x : (const char*)P.dz;
+  const int ld = is_x ? P.ldx : P.lddz;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+  const uint32_t lds_w = lds0 + (is_x ? kWgradOperand : 0) + (wave & 3) * 4096;
+  // row-major: piece j = rows 2 j, 2 j + 1; lane = (row, 16-byte slot c), slot c holds the features of chunk
+  // c ^ 4 (row % 4), so that the four rows and two feature halves of half a wave's transposing read lie in different banks
+  const int rl = lane >> 5;
+  // blocks: piece j = feature step j of the tile's 16; lane slot L holds (row s, half h) with L = 8 (s / 4) + 4 h + s % 4,
+  // in odd steps L ^ 8 (for the same reason)
+  const int bs = (lane >> 3) * 4 + (lane & 3), bh = (lane >> 2) & 1;      // odd steps: row bs ^ 4
+  const int nks_op = fmax >> 4;
+  // loads of this wave per stage: features past the operand are not loaded (what the LDS holds there feeds results that
+  // are never stored)
+  const int n_ld = LAYOUT == 1 ? min(max(nks_op - (f0 >> 4) - (wave & 3) * 4, 0), 4) : 4;
+  const int j0 = (wave & 3) * 4;
+  // per-lane byte offsets of pieces with even and odd k (everything else of an address is wave-uniform), and whether the
+  // lane's features exist
+  uint32_t voff[2];
+  bool f_ok[2];
+#pragma unroll
+  for (int par = 0; par < 2; ++par) {
+    if constexpr (LAYOUT == 1) {
+      voff[par] = ((bs ^ (4 * par)) + 32 * bh) * 16;
+      f_ok[par] = true;
+    } else {
+      const int f = f0 + 8 * ((lane & 31) ^ (((2 * par + rl) & 3) << 2));
+      voff[par] = (uint32_t)(rl * ld + f) * 2;
+      f_ok[par] = f < fmax;
+    }
+  }
+  auto issue = [&](int stage) {
+    const int r0 = row_begin + stage * kWgradRows;
+    const uint32_t dst = lds_w + (stage % kWgradRing) * kWgradStage;
+    if constexpr (LAYOUT == 1) {
+      const char* base = opnd + ((((int64_t)(r0 >> 7) * nks_op + (f0 >> 4) + j0) * 4 + ((r0 >> 5) & 3)) << 10);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (k < n_ld) load_to_lds(base + k * 4096, voff[k & 1], dst + k * 1024);
+    } else if (r0 + kWgradRows <= row_end) {
+      const char* base = opnd + (int64_t)(r0 + 2 * j0) * ld * 2;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (f_ok[k & 1]) load_to_lds(base + (int64_t)k * ld * 4, voff[k & 1], dst + k * 1024);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int row = r0 + 2 * (j0 + k);
+        const void* src = row + rl < row_end ? (const void*)(opnd + (int64_t)row * ld * 2 + voff[k & 1]) : &g_zero_piece;
+        if (f_ok[k & 1]) load_to_lds(src, dst + k * 1024);
+      }
+    }
+  };
+  // at most the loads of the newest `stages` stages outstanding
+  auto landed = [&](int stages) {
+    switch (stages * n_ld) {
+      case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
+      case 1: asm volatile("s_waitcnt vmcnt(1)" ::: "memory"); break;
+      case 2: asm volatile("s_waitcnt vmcnt(2)" ::: "memory"); break;
+      case 3: asm volatile("s_waitcnt vmcnt(3)" ::: "memory"); break;
+      case 4: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
+      case 6: asm volatile("s_waitcnt vmcnt(6)" ::: "memory"); break;
+      case 8: asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); break;
+      case 9: asm volatile("s_waitcnt vmcnt(9)" ::: "memory"); break;
+      default: asm volatile("s_waitcnt vmcnt(12)" ::: "memory"); break;
+    }
+  };
+
+  // ---- reading: lane group q = lane / 16 takes features 16 (q % 2) .. + 15 and rows 8 (q / 2) .. + 7 of a 32-feature,
+  // 16-row operand; a lane addresses row i / 4 (of 4) and features 4 (i % 4) .. + 3, i = lane % 16
+  const int i16 = lane & 15, fh = (lane >> 4) & 1, rh = lane >> 5;
+  // Waves share the tile's 32 x 32 tiles as a 2 x 4 grid (4 x 2 where there are at most two input tiles), so that a narrow
+  // matrix still gives every wave its part: wave (wo, wi) has the output tiles ot0 .. ot0 + nz - 1 and the input tiles
+  // xt0 .. xt0 + nx - 1.
+  const int n_ot = min((P.out_pad - o0) >> 5, 8), n_xt = min((P.in_pad - i0) >> 5, 8);
+  const int go = n_xt <= 2 ? 4 : 2, gi = 8 / go, wo = wave / gi, wi = wave % gi;
+  const int zmax = (n_ot + go - 1) / go, xmax = (n_xt + gi - 1) / gi;
+  const int ot0 = wo * zmax, xt0 = wi * xmax;
+  const int nz = max(0, min(zmax, n_ot - ot0)), nx = max(0, min(xmax, n_xt - xt0));
+  // LDS addresses of the first 4 rows of z tile i and x tile j; *4: of the next 4.  In block layout a tile is 2 KiB after the
+  // one before it (an immediate of the read); row-major the swizzle reaches into the tile index.
+  constexpr int kRowStep16 = LAYOUT == 1 ? 512 : 8192;      // bytes between rows r and r + 16
+  constexpr int kBases = LAYOUT == 1 ? 1 : 4;
+  const unsigned char *za[kBases], *za4[kBases], *xa[kBases > 1 ? 2 : 1], *xa4[kBases > 1 ? 2 : 1];
+  if constexpr (LAYOUT == 1) {
+    const int c = i16 & 3, r = i16 >> 2;
+    const bool nat = P.x_blocks == 2;
+    const int hz = c & 1, lz = c >> 1, hx = nat ? c >> 1 : c & 1, lx = nat ? c & 1 : c >> 1;
+    const int row4 = 2 * rh + fh, row44 = 2 * rh + 1 - fh;      // 4-row groups 2 rh and 2 rh + 1, swapped in odd steps
+    const unsigned char* p = smem + (2 * ot0 + fh) * 1024 + (hz * 4 + r) * 16 + 8 * lz;
+    const unsigned char* q = smem + kWgradOperand + (2 * xt0 + fh) * 1024 + (hx * 4 + r) * 16 + 8 * lx;
+    za[0] = p + row4 * 128; za4[0] = p + row44 * 128;
+    xa[0] = q + row4 * 128; xa4[0] = q + row44 * 128;
   } else {
-    fblk = t2 & 15; rblk = t2 >> 4;
-    feat = f0 + fblk * 8;
-  }
-  const bool feat_ok = feat < fmax;
-  // loads are unconditional (clamped addresses, masked to zero afterwards) so that two stages stay in
-  // flight and the compiler waits only for the older one
-  const uint16_t* __restrict__ src = opnd + (feat_ok ? feat : 0);
-  // LDS holds [feature][row]; the 16-byte slot of row block rblk inside a feature's line is XOR-swizzled
-  // with the feature block index: the 16 lanes that write the same row block of 16 different feature
-  // blocks are 8 LDS lines apart, which without the swizzle is the same bank group for all of them
-  // (measured: 16-way conflicts made every stage cost ~4000 cycles whatever the tile's work).
-  // Feature i of the thread's 8 sits at local feature fl(i); its slot is swizzled with fl(i) / 8.
-  const int obase = is_b ? T * kLds : 0;
-  int sdst_i[8];
+    const int r = i16 >> 2;
+    const unsigned char* p = smem + (8 * rh + r) * 512 + 8 * (i16 & 1);
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int fl = blocks ? 16 * ksl + (natural ? 8 * hb + i : (i < 4 ? 4 * hb + i : 8 + 4 * hb + (i - 4))) : fblk * 8 + i;
-    sdst_i[i] = obase + fl * kLds + ((rblk ^ ((fl >> 3) & 7)) * 8);
-  }
-  const int nks_op = fmax >> 4;                        // feature steps of a block-layout operand
-
-  floatx16 acc[2][2];
-  floatx16 accb[2];
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    acc[0][0][v] = acc[0][1][v] = acc[1][0][v] = acc[1][1][v] = 0.f;
-    accb[0][v] = accb[1][v] = 0.f;
-  }
-  const bool do_bias = (i0 == 0) && (wi == 0);
-  bf16x8 ones;
-#pragma unroll
-  for (int v = 0; v < 8; ++v) ones[v] = (__bf16)1.0f;
-
-  uint4 st0[8], st1[8];
-  // row pointers of the thread's 8 rows for the stage being loaded next; advanced by 64 rows per stage.
-  // Stages wholly inside [row_begin, row_end) need neither clamping nor masking.
-  const int64_t ld64 = ld;
-  const int rows_alloc = (rows + 127) & ~127;          // block-layout arrays hold whole 128-row tiles
-  auto load_stage = [&](uint4* st, int rbase) {
-    if (blocks) {
-      // stage = rows rbase .. rbase + 63 = row tiles 2 (rbase / 64 % 2) + {0, 1} of workgroup tile rbase / 128
-      const int rb = rbase < rows_alloc ? rbase : rows_alloc - 64;      // stages past the end re-read the last one (masked)
-      const int tr = rb >> 7, rt = ((rb >> 6) & 1) * 2;
-      const int ksg = (feat_ok ? feat : 0) >> 4;
-      const uint4* p = reinterpret_cast<const uint4*>(opnd) + (((int64_t)tr * nks_op + ksg) * 4 + rt) * 64 + 32 * hb + rblk;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) st[j] = p[(j >> 2) * 64 + 8 * (j & 3)];
-    } else if (rbase + kBK <= row_end) {
-      const uint16_t* p = src + (int64_t)(rbase + rblk) * ld64;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) st[j] = *reinterpret_cast<const uint4*>(p + (32 * (j >> 2) + 8 * (j & 3)) * ld64);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        st[j] = *reinterpret_cast<const uint4*>(src + (int64_t)min(rbase + rblk + 32 * (j >> 2) + 8 * (j & 3), rows - 1) * ld64);
+    for (int i = 0; i < kBases; ++i) {
+      za[i] = p + ((4 * ((ot0 + i) & 7) + 2 * fh + ((i16 & 3) >> 1)) ^ (r << 2)) * 16;
+      za4[i] = za[i] + 2048;
     }
-  };
-  // rows past the split (and feature blocks past the operand) are zeroed here, when the data is consumed,
-  // not at load time: touching a loaded register right after the load would stall on it
-  auto store_stage = [&](const uint4* st, int buf, int rbase) {
-    uint4 m[8], tr[8];
-    if (rbase + kBK <= row_end && feat_ok) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) m[j] = st[j];
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const uint32_t k = (rbase + rblk + 32 * (j >> 2) + 8 * (j & 3) < row_end && feat_ok) ? 0xFFFFFFFFu : 0u;
-        m[j] = make_uint4(st[j].x & k, st[j].y & k, st[j].z & k, st[j].w & k);
-      }
+    for (int j = 0; j < 2; ++j) {
+      if (j >= (kBases > 1 ? 2 : 1)) break;
+      xa[j] = p + kWgradOperand + ((4 * ((xt0 + j) & 7) + 2 * fh + ((i16 & 3) >> 1)) ^ (r << 2)) * 16;
+      xa4[j] = xa[j] + 2048;
     }
-    transpose8x8(m, tr);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) *reinterpret_cast<uint4*>(&s_stage[buf * kBuf + sdst_i[i]]) = tr[i];
-  };
-  auto compute = [&](int buf) {
-    const uint16_t* s_a = s_stage + buf * kBuf;
-    const uint16_t* s_b = s_a + T * kLds;
-#pragma unroll
-    for (int kk = 0; kk < kBK / 16; ++kk) {
-      bf16x8 a[2], b[2];
-      const int kc = kk * 2 + (lane >> 5);          // 16-byte slot (8 rows) of this lane's fragment
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int fr = (wo * 2 + i) * 32 + (lane & 31);
-        a[i] = *reinterpret_cast<const bf16x8*>(&s_a[fr * kLds + ((kc ^ ((fr >> 3) & 7)) * 8)]);
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int fr = (wi * 2 + j) * 32 + (lane & 31);
-        b[j] = *reinterpret_cast<const bf16x8*>(&s_b[fr * kLds + ((kc ^ ((fr >> 3) & 7)) * 8)]);
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-      if (do_bias) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-          accb[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], ones, accb[i], 0, 0, 0);
-      }
-    }
+  }
+  auto operand = [&](const unsigned char* p, const unsigned char* p4) {
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(p));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(p4));
+    const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
   };
 
-  // stage s (64 rows) lives in LDS buffer s & 1; rows past the split load as zeros, so a trailing odd
-  // stage adds nothing and the loop body needs no conditions
-  const int nst = row_begin < row_end ? (row_end - row_begin + kBK - 1) / kBK : 0;
+  floatx16 acc[4][2];
+  float sum[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    sum[i] = 0.f;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  }
+  const bool do_bias = i0 == 0 && wi == 0;
+  typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+  const bf2 one = {(__bf16)1.0f, (__bf16)1.0f};
+
+  struct Operands { bf16x8 z[4], x[2]; };
+  constexpr int kAhead = kWgradRing - 1;
+  const int nst = row_begin < row_end ? (row_end - row_begin + kWgradRows - 1) / kWgradRows : 0;
+  // The stage loop of a wave with NZ x NX tiles.  The barrier of iteration s: every wave's pieces of the stages up to s + 1
+  // are in LDS, and every wave has read stage s - 1, whose place the newest stage takes.  Operands are read one 16-row step
+  // ahead of their products, across the stage boundary: the waves leave the barrier together, and reads before products
+  // would leave the matrix cores idle meanwhile.
+  auto run = [&](auto nzc, auto nxc, auto biasc) {
+    constexpr int NZ = decltype(nzc)::value, NX = decltype(nxc)::value;
+    constexpr bool BIAS = decltype(biasc)::value;
+    auto read = [&](int off, int k) {
+      Operands q;
+      const int o = off + k * kRowStep16;
+#pragma unroll
+      for (int i = 0; i < NZ; ++i) {
+        if constexpr (LAYOUT == 1) q.z[i] = operand(za[0] + o + i * 2048, za4[0] + o + i * 2048);
+        else q.z[i] = operand(za[i] + o, za4[i] + o);
+      }
+#pragma unroll
+      for (int j = 0; j < NX; ++j) {
+        if constexpr (LAYOUT == 1) q.x[j] = operand(xa[0] + o + j * 2048, xa4[0] + o + j * 2048);
+        else q.x[j] = operand(xa[j] + o, xa4[j] + o);
+      }
+      return q;
+    };
+    auto multiply = [&](const Operands& q) {
+#pragma unroll
+      for (int i = 0; i < NZ; ++i)
+#pragma unroll
+        for (int j = 0; j < NX; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q.z[i], q.x[j], acc[i][j], 0, 0, 0);
+      if constexpr (BIAS) {
+#pragma unroll
+        for (int i = 0; i < NZ; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const bf2 v = {q.z[i][2 * e], q.z[i][2 * e + 1]};
+            sum[i] = __builtin_amdgcn_fdot2_f32_bf16(v, one, sum[i], false);
+          }
+      }
+    };
+    // the reads of the next step between the products of this one: a wave issues in order, and a product keeps the matrix
+    // core busy for 32 cycles
+    auto interleave = [&]() {
+      constexpr int kProducts = NZ * NX > 0 ? NZ * NX : 1;
+      constexpr int kReads = (2 * (NZ + NX) + kProducts - 1) / kProducts;
+#pragma unroll
+      for (int m = 0; m < kProducts; ++m) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);               // a product
+        __builtin_amdgcn_sched_group_barrier(0x2, 2 * kReads, 0);      // vector instructions (addresses)
+        __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);        // LDS reads
+      }
+    };
+    Operands cur;
+    int off = 0;      // LDS offset of stage s
+    if constexpr (NZ > 0) cur = read(0, 0);
+    for (int s = 0; s < nst; ++s) {
+      landed(max(0, min(kAhead - 2, nst - 2 - s)));
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      if (s + kAhead < nst) issue(s + kAhead);
+      const int off1 = off == (kWgradRing - 1) * kWgradStage ? 0 : off + kWgradStage;
+      if constexpr (NZ > 0) {
+        const Operands nxt = read(off, 1);
+        multiply(cur);
+        interleave();
+        __builtin_amdgcn_sched_barrier(0);
+        cur = read(s + 1 < nst ? off1 : off, 0);
+        multiply(nxt);
+        interleave();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      off = off1;
+    }
+  };
   if (nst > 0) {
-    load_stage(st0, row_begin);
-    load_stage(st1, row_begin + kBK);
-    store_stage(st0, 0, row_begin);
-    load_stage(st0, row_begin + 2 * kBK);
-    for (int s2 = 0; s2 < nst; s2 += 2) {
-      __syncthreads();
-      store_stage(st1, 1, row_begin + (s2 + 1) * kBK);
-      load_stage(st1, row_begin + (s2 + 3) * kBK);
-      compute(0);
-      __syncthreads();
-      store_stage(st0, 0, row_begin + (s2 + 2) * kBK);
-      load_stage(st0, row_begin + (s2 + 4) * kBK);
-      compute(1);
-    }
+    for (int s = 0; s < min(kAhead, nst); ++s) issue(s);
+    landed(min(kAhead, nst) - 1);
+    asm volatile("s_barrier" ::: "memory");
+    auto pick = [&](auto bias) {
+#define GMI_WGRAD_RUN(Z, X) run(std::integral_constant<int, Z>{}, std::integral_constant<int, X>{}, bias)
+      if (nz == 0 || nx == 0) GMI_WGRAD_RUN(0, 0);
+      else if (nx == 1) {
+        if (nz == 1) GMI_WGRAD_RUN(1, 1); else if (nz == 2) GMI_WGRAD_RUN(2, 1); else if (nz == 3) GMI_WGRAD_RUN(3, 1); else GMI_WGRAD_RUN(4, 1);
+      } else {
+        if (nz == 1) GMI_WGRAD_RUN(1, 2); else if (nz == 2) GMI_WGRAD_RUN(2, 2); else if (nz == 3) GMI_WGRAD_RUN(3, 2); else GMI_WGRAD_RUN(4, 2);
+      }
+#undef GMI_WGRAD_RUN
+    };
+    if (do_bias) pick(std::true_type{}); else pick(std::false_type{});
   }
 
   // tiled partials (ModelLayout::part_floats): a quad of results of a 32 x 32 tile is one 16-byte store per lane
   float* dst = part + (int64_t)sp * part_stride;
   const int n_it = P.in_pad >> 5;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int ot = (o0 >> 5) + wo * 2 + i;
+  for (int i = 0; i < 4; ++i) {
+    if (i >= nz) break;
+    const int ot = (o0 >> 5) + ot0 + i;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       if (32 * ot + 8 * q >= P.out) continue;
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        const int it = (i0 >> 5) + wi * 2 + j;
-        if (it < n_it)
+        const int it = (i0 >> 5) + xt0 + j;
+        if (j < nx)
           *reinterpret_cast<float4*>(dst + P.w_off + (((int64_t)ot * n_it + it) * 4 + q) * 256 + lane * 4) =
               make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
       }
-      if (do_bias && (lane & 31) == 0)
-        *reinterpret_cast<float4*>(dst + P.b_off + 32 * ot + 8 * q + 4 * (lane >> 5)) =
-            make_float4(accb[i][4 * q], accb[i][4 * q + 1], accb[i][4 * q + 2], accb[i][4 * q + 3]);
+    }
+    if (do_bias) {
+      const float b = sum[i] + __shfl_xor(sum[i], 32, 64);      // the other half of the rows
+      if (lane < 32) dst[P.b_off + 32 * ot + lane] = b;
     }
   }
-}
-
-__global__ __launch_bounds__(256) void wgrad_bf16_kernel(gmi::WgradBatch batch, int rows, int n_split,
-                                                         int chunk, float* __restrict__ part,
-                                                         int64_t part_stride) {
-  __shared__ __attribute__((aligned(16))) uint16_t s_stage[2 * kWgradBuf];
-  int pi = 0;
-  while (pi + 1 < batch.n && (int)blockIdx.x >= batch.blk_start[pi + 1]) ++pi;
-  const gmi::WgradProblem& P = batch.p[pi];
-  const int local = blockIdx.x - batch.blk_start[pi];
-  if (P.dz_blocks) wgrad_tile<1>(P, local, rows, n_split, chunk, part, part_stride, s_stage);
-  else wgrad_tile<0>(P, local, rows, n_split, chunk, part, part_stride, s_stage);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -755,13 +831,23 @@ int launch_wgrad(gmi_instance* g, int dtype, int rows, int n_split, int chunk, W
     GMI_LAUNCH_CHECK();
     return GMI_OK;
   }
-  int total = 0;
+  // problems 0 .. n / 2 - 1 are the policy net's layers, the rest the value net's (one net alone: all of them, net 1 empty)
+  const int half = b.n >> 1;
+  b.net_tiles[0] = b.net_tiles[1] = 0;
   for (int i = 0; i < b.n; ++i) {
-    b.blk_start[i] = total;
-    total += ((b.p[i].out_pad + 127) / 128) * ((b.p[i].in_pad + 127) / 128) * n_split;
+    b.tiles[i] = wgrad_tiles(b.p[i].out_pad, b.p[i].in_pad);
+    b.net_tiles[i < half ? 0 : 1] += b.tiles[i];
   }
-  b.blk_start[b.n] = total;
-  ps.launch(wgrad_bf16_kernel, dim3(total), dim3(256), 0, b, rows, n_split, chunk, part, part_stride);
+  const int total = 2 * n_split * std::max(b.net_tiles[0], b.net_tiles[1]);
+  static bool attr[2] = {false, false};
+  const int layout = b.p[0].dz_blocks ? 1 : 0;
+  const void* kernel = layout ? (const void*)wgrad_bf16_kernel<1> : (const void*)wgrad_bf16_kernel<0>;
+  if (!attr[layout]) {
+    GMI_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kWgradLds));
+    attr[layout] = true;
+  }
+  if (layout) ps.launch(wgrad_bf16_kernel<1>, dim3(total), dim3(512), kWgradLds, b, rows, n_split, chunk, part, part_stride);
+  else ps.launch(wgrad_bf16_kernel<0>, dim3(total), dim3(512), kWgradLds, b, rows, n_split, chunk, part, part_stride);
   GMI_LAUNCH_CHECK();
   return GMI_OK;
 }

@@ -334,7 +334,7 @@ extern "C" int gmi_model_bind(gmi_t g, const gmi_model_desc* d, float* params, v
     int n_tiles = 0;
     for (int net = 0; net < 2; ++net)
       for (int l = 0; l < L.n_layers; ++l)
-        n_tiles += ((L.net[net][l].out_pad + 127) / 128) * ((L.net[net][l].in_pad + 127) / 128);
+        n_tiles += gmi::wgrad_tiles(L.net[net][l].out_pad, L.net[net][l].in_pad);
     m->n_split_max = gmi::wgrad_split_limit(n_tiles);
     m->part_rows = m->n_split_max;
     if (L.dtype == GMI_DTYPE_BF16 && adam_m) m->part_rows = std::max(m->part_rows, gmi::resident_part_rows(L));

@@ -145,7 +145,7 @@ extern "C" int gmi_bench_linear(gmi_t g, int kind, int rows, int K, int F, int n
     r.dz = y; r.lddz = F; r.x = x; r.ldx = K; r.out = F; r.in = K; r.out_pad = F; r.in_pad = K; r.dz_blocks = r.x_blocks = 0;
     r.w_off = (int64_t)z * ((int64_t)K * F + F); r.b_off = r.w_off + (int64_t)K * F;
   }
-  const int n_split = gmi::wgrad_split_limit(n_nets * ((F + 127) / 128) * ((K + 127) / 128));
+  const int n_split = gmi::wgrad_split_limit(n_nets * gmi::wgrad_tiles(F, K));
   if (kind == 3) part = (float*)take((size_t)n_split * P * 4);
   if (off > scratch_bytes) GMI_FAIL(GMI_ERR_BAD_SHAPE, "gmi_bench_linear: scratch too small (%zu needed)", off);
   const int chunk = ((rows + n_split - 1) / n_split + 63) / 64 * 64;
