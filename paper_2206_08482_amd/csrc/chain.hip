@@ -240,6 +240,19 @@ int launch_train_chain(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_p
   return GMI_OK;
 }
 
+bool has_tile_forward(const ModelLayout& L) {
+  if (L.dtype != GMI_DTYPE_BF16 || L.sh_chain_bytes == 0 || L.act_dim > 32) return false;
+  const ChainArgs a = {};
+  int probe = 0, rc = GMI_ERR_UNSUPPORTED;
+  for (int p = 0; p < kTileFwdParts && rc == GMI_ERR_UNSUPPORTED; ++p) rc = kTileFwdFns[p](nullptr, L, a, 0, &probe, 0.0, 0.0);
+  return rc == GMI_OK;
+}
+
+// agent_act with the one-launch agent kernel / with gather, this kernel and the sampling kernel, us: 211:512:512:256:128:20
+// 18 / 42 for 1 row, 34 / 56 for 8192, 52 / 63 for 12000, 68 / 65 for 16384; 211:512:512:512:256:20 22 / 52, 45 / 69,
+// 67 / 72, 90 / 77.
+bool use_tile_forward(const gmi_model* m, int rows) { return rows >= 12288 && has_tile_forward(m->L); }
+
 bool forward_chain_reads_x0(const gmi_model* m, const float* obs) {
   return !(m->L.obs_dim % 4 == 0 && ((uintptr_t)obs & 15) == 0);
 }
@@ -249,12 +262,9 @@ bool forward_chain_reads_x0(const gmi_model* m, const float* obs) {
 int launch_forward_chain(gmi_instance* g, gmi_model* m, const float* obs, int n_rows, float* mu, float* val,
                          bool x0_valid) {
   const ModelLayout& L = m->L;
-  if (L.dtype != GMI_DTYPE_BF16 || L.sh_chain_bytes == 0 || L.act_dim > 32) return GMI_ERR_UNSUPPORTED;
-  if (n_rows < 1 || n_rows > m->max_rows) return GMI_ERR_UNSUPPORTED;
+  if (n_rows < 1 || n_rows > m->max_rows || !use_tile_forward(m, n_rows)) return GMI_ERR_UNSUPPORTED;
+  int rc;
   ChainArgs a = {};
-  int probe = 0, rc = GMI_ERR_UNSUPPORTED;
-  for (int p = 0; p < kTileFwdParts && rc == GMI_ERR_UNSUPPORTED; ++p) rc = kTileFwdFns[p](nullptr, L, a, 0, &probe, 0.0, 0.0);
-  if (rc != GMI_OK) return rc;      // no forward-only kernel compiled for this shape
   for (int net = 0; net < 2; ++net) {
     a.wstream[net] = m->shadow + L.sh_chain[net];
     for (int l = 0; l < L.n_layers; ++l) a.bias[net][l] = reinterpret_cast<const float*>(m->shadow + L.net[net][l].sh_b);

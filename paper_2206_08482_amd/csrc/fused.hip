@@ -1,8 +1,6 @@
-// Row-tile fused MLP kernels: a workgroup owns a tile of R samples (envs), keeps the activations of the
+// One-launch collection kernel: a workgroup owns a tile of R samples (envs), keeps the activations of the
 // tile in LDS (bf16) from layer to layer, and streams each layer's bf16 weights from L2 straight into the
-// matrix cores' weight operand.  One launch replaces the per-layer launches of the agent's action decision
-// (Section 3 of the paper, "DRL Agent"): observation conversion, every layer of both nets, and the Gaussian
-// sampling epilogue.
+// matrix cores' weight operand.
 #include "internal.h"
 #include "rng.h"
 #include "rollout.h"
@@ -172,103 +170,6 @@ __device__ __forceinline__ void fused_layer(const uint16_t* __restrict__ W, cons
 __device__ __forceinline__ void stage_biases(const FusedNet& N, float* dst, int tid0, int nthreads) {
   for (int l = 0; l < N.n_layers; ++l)
     for (int f = tid0; f < N.out_pad[l]; f += nthreads) dst[N.bias_off[l] + f] = N.bias[l][f];
-}
-
-// Runs all layers of one net on the tile whose input sits in s_x0; hidden activations ping-pong between
-// s_a and s_b; the head's fp32 outputs go to s_head[r * head_stride + j].
-template <int RT>
-__device__ __forceinline__ void fused_net_forward(const FusedNet& N, const float* s_bias, const uint16_t* s_x0,
-                                                  int stride_x0, uint16_t* s_a, uint16_t* s_b, int stride_h,
-                                                  float* s_head, int head_stride) {
-  const uint16_t* in = s_x0;
-  int stride_in = stride_x0;
-  uint16_t* out = s_a;
-  for (int l = 0; l < N.n_layers - 1; ++l) {
-    fused_layer<RT, kFEpiElu>(N.w[l], s_bias + N.bias_off[l], N.in_pad[l], N.out_pad[l], in, stride_in, out, stride_h,
-                              nullptr, 0, 0);
-    __syncthreads();
-    in = out;
-    stride_in = stride_h;
-    out = (out == s_a) ? s_b : s_a;
-  }
-  const int l = N.n_layers - 1;
-  fused_layer<RT, kFEpiHead>(N.w[l], s_bias + N.bias_off[l], N.in_pad[l], N.out_pad[l], in, stride_in, nullptr, 0,
-                             s_head, head_stride, N.out_store);
-  __syncthreads();
-}
-
-struct AgentArgs {
-  FusedNet net[2];
-  const float* log_std;
-  const float* obs;
-  int n, obs_dim, obs_pad, act_dim, max_h;
-  int do_policy;
-  uint32_t k0, k1, step, env_offset;
-  float* act; float* logp; float* value; float* mu_out;
-};
-
-template <int RT>
-__global__ __launch_bounds__(256) void agent_fused_kernel(AgentArgs a) {
-  constexpr int R = RT * 32;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  const int stride_x0 = a.obs_pad + 8, stride_h = a.max_h + 8;
-  uint16_t* s_x0 = reinterpret_cast<uint16_t*>(smem_raw);
-  uint16_t* s_a = s_x0 + R * stride_x0;
-  uint16_t* s_b = s_a + R * stride_h;
-  float* s_mu = reinterpret_cast<float*>(s_b + R * stride_h);       // [R][act_dim]
-  float* s_val = s_mu + R * a.act_dim;                              // [R]
-  float* s_lp = s_val + R;                                          // [R][nb] log-prob partials
-  float* s_bias = s_lp + R * ((a.act_dim + 3) >> 2);                // biases of the policy net, then the value net
-  const int tid = threadIdx.x;
-  const int r0 = blockIdx.x * R;
-
-  if (a.do_policy) stage_biases(a.net[0], s_bias, tid, 256);
-  stage_biases(a.net[1], s_bias + a.net[0].bias_total, tid, 256);
-  // observations -> bf16 tile (zero padded columns, zero rows past the end)
-  for (int idx = tid; idx < R * a.obs_pad; idx += 256) {
-    const int r = idx / a.obs_pad, k = idx - r * a.obs_pad;
-    float v = 0.f;
-    if (r0 + r < a.n && k < a.obs_dim) v = a.obs[(int64_t)(r0 + r) * a.obs_dim + k];
-    s_x0[r * stride_x0 + k] = (uint16_t)(pack_bf16(v, 0.f) & 0xFFFFu);
-  }
-  __syncthreads();
-  if (a.do_policy) fused_net_forward<RT>(a.net[0], s_bias, s_x0, stride_x0, s_a, s_b, stride_h, s_mu, a.act_dim);
-  fused_net_forward<RT>(a.net[1], s_bias + a.net[0].bias_total, s_x0, stride_x0, s_a, s_b, stride_h, s_val, 1);
-
-  for (int r = tid; r < R; r += 256)
-    if (r0 + r < a.n) a.value[r0 + r] = s_val[r];
-  if (!a.do_policy) return;
-
-  // act = mu + exp(log_std) * eps; log-prob partial per block of 4 action elements
-  const int A = a.act_dim, nb = (A + 3) >> 2;
-  for (int item = tid; item < R * nb; item += 256) {
-    const int r = item / nb, b = item - r * nb;
-    const int e = r0 + r;
-    float lp = 0.f;
-    if (e < a.n) {
-      float z[4];
-      gmi::normal_block(a.env_offset + (uint32_t)e, a.step, gmi::kStreamAction, (uint32_t)b, a.k0, a.k1, z);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int j = 4 * b + i;
-        if (j < A) {
-          const float ls = a.log_std[j];
-          const float m = s_mu[r * A + j];
-          a.act[(int64_t)e * A + j] = fmaf(expf(ls), z[i], m);
-          if (a.mu_out) a.mu_out[(int64_t)e * A + j] = m;
-          lp += -0.5f * z[i] * z[i] - ls - 0.918938533204672742f;
-        }
-      }
-    }
-    s_lp[r * nb + b] = lp;
-  }
-  __syncthreads();
-  for (int r = tid; r < R; r += 256) {
-    if (r0 + r >= a.n) continue;
-    float lp = 0.f;
-    for (int b = 0; b < nb; ++b) lp += s_lp[r * nb + b];
-    a.logp[r0 + r] = lp;
-  }
 }
 
 
@@ -923,15 +824,6 @@ void fill_net(const gmi_model* m, int net, FusedNet* N) {
   N->out_store = L.net[net][L.n_layers - 1].out;
 }
 
-size_t agent_lds_bytes(const gmi_model* m, int R) {
-  const ModelLayout& L = m->L;
-  int max_h = 32;
-  for (int l = 0; l < L.n_hidden; ++l) max_h = L.net[0][l].out_pad > max_h ? L.net[0][l].out_pad : max_h;
-  const int nb = (L.act_dim + 3) / 4;
-  return (size_t)R * (gmi::pad32(L.obs_dim) + 8) * 2 + 2 * (size_t)R * (max_h + 8) * 2 +
-         ((size_t)R * (L.act_dim + 1 + nb) + bias_floats(m, 0) + bias_floats(m, 1)) * 4;
-}
-
 // Bytes of one step's random draws for a tile of R envs (one float4 per block).
 size_t rollout_noise_bytes(const gmi_model* m, int R) {
   const int O = m->L.obs_dim, A = m->L.act_dim, o4 = (O + 3) & ~3;
@@ -970,62 +862,6 @@ size_t rollout_lds_bytes(const gmi_model* m, int R, bool mt_lds) {
 }
 
 }  // namespace
-
-namespace gmi {
-
-// Returns GMI_OK if the fused kernel was launched, GMI_ERR_UNSUPPORTED (without setting an error
-// message the caller must report) if the model does not fit the fused kernel and the per-layer path
-// has to be used instead.
-int launch_agent_fused(gmi_instance* g, gmi_model* m, const float* obs, int n, uint64_t seed, uint32_t step,
-                       uint32_t env_offset, float* act, float* logp, float* value, float* mu_out, bool do_policy) {
-  if (m->L.dtype != GMI_DTYPE_BF16) return GMI_ERR_UNSUPPORTED;
-  // every row tile streams all weights from L2 once: beyond ~1 MB of bf16 weights the per-layer
-  // large-tile kernels are faster (measured on a
-  // [512,512,256,128] model: 180 us fused against ~140 us per-layer for 16384 rows)
-  if (m->L.weight_bytes > (1 << 20)) return GMI_ERR_UNSUPPORTED;
-  constexpr size_t kLdsMax = 160 * 1024;
-  int R = 64;
-  if (agent_lds_bytes(m, R) > kLdsMax) R = 32;
-  if (agent_lds_bytes(m, R) > kLdsMax) return GMI_ERR_UNSUPPORTED;
-  // small batches: 32-row tiles give twice the workgroups
-  if (R == 64 && (n + 63) / 64 < g->cu_count / 2) R = 32;
-  AgentArgs a;
-  fill_net(m, 0, &a.net[0]);
-  fill_net(m, 1, &a.net[1]);
-  a.log_std = reinterpret_cast<const float*>(m->shadow + m->L.sh_logstd);
-  a.obs = obs;
-  a.n = n;
-  a.obs_dim = m->L.obs_dim;
-  a.obs_pad = pad32(m->L.obs_dim);
-  a.act_dim = m->L.act_dim;
-  a.max_h = 32;
-  for (int l = 0; l < m->L.n_hidden; ++l) a.max_h = m->L.net[0][l].out_pad > a.max_h ? m->L.net[0][l].out_pad : a.max_h;
-  a.do_policy = do_policy ? 1 : 0;
-  a.k0 = (uint32_t)seed; a.k1 = (uint32_t)(seed >> 32); a.step = step; a.env_offset = env_offset;
-  a.act = act; a.logp = logp; a.value = value; a.mu_out = mu_out;
-  const size_t lds = agent_lds_bytes(m, R);
-  ProfScope ps(g, kClsFusedAgent);
-  if (R == 64) {
-    static bool attr64 = false;
-    if (!attr64) {
-      GMI_HIP(hipFuncSetAttribute((const void*)agent_fused_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
-      attr64 = true;
-    }
-    ps.launch(agent_fused_kernel<2>, dim3((n + 63) / 64), dim3(256), lds, a);
-  } else {
-    static bool attr32 = false;
-    if (!attr32) {
-      GMI_HIP(hipFuncSetAttribute((const void*)agent_fused_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
-      attr32 = true;
-    }
-    ps.launch(agent_fused_kernel<1>, dim3((n + 31) / 32), dim3(256), lds, a);
-  }
-  GMI_LAUNCH_CHECK();
-  return GMI_OK;
-}
-
-}  // namespace gmi
-
 
 extern "C" int rollout_collect(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_buffer_t b, float* obs, uint64_t seed,
                                uint32_t step0, uint32_t env_offset, float* last_value) {

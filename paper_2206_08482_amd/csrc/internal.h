@@ -285,8 +285,8 @@ int launch_gather_to(gmi_instance* g, gmi_model* m, const float* obs, int n_envs
 int forward_nets(gmi_instance* g, gmi_model* m, int rows, bool policy, bool value, float* mu_dst,
                  float* val_dst);
 
-int launch_agent_fused(gmi_instance* g, gmi_model* m, const float* obs, int n, uint64_t seed, uint32_t step,
-                       uint32_t env_offset, float* act, float* logp, float* value, float* mu_out, bool do_policy);
+int launch_agent(gmi_instance* g, gmi_model* m, const float* obs, int n, uint64_t seed, uint32_t step,
+                 uint32_t env_offset, float* act, float* logp, float* value, float* mu_out, bool do_policy);
 
 // The fp32 one-launch kernels (f32.hip); GMI_ERR_UNSUPPORTED (no message) where a 16-row tile does not fit LDS.
 int launch_agent_f32(gmi_instance* g, gmi_model* m, const float* obs, int n, uint64_t seed, uint32_t step,
@@ -325,9 +325,12 @@ struct ChainEmit {
 };
 void fill_chain_emit(const ModelLayout& L, ChainEmit* ce);
 // Forward pass of n_rows observation rows through the forward-only row-tile kernel: policy means into mu (NULL: value
-// net only) and values into val.  GMI_ERR_UNSUPPORTED (no message) if no such kernel is compiled for the shape.
+// net only) and values into val.  GMI_ERR_UNSUPPORTED (no message) where use_tile_forward says no.
 int launch_forward_chain(gmi_instance* g, gmi_model* m, const float* obs, int n_rows, float* mu, float* val,
                          bool x0_valid = false);
+// Whether such a kernel is compiled for the shape / is the faster one for that many rows (else launch_agent).
+bool has_tile_forward(const ModelLayout& L);
+bool use_tile_forward(const gmi_model* m, int rows);
 // Whether that kernel would read the bf16 rows m->x0 (made by the gather kernel) instead of obs itself.
 bool forward_chain_reads_x0(const gmi_model* m, const float* obs);
 // The collection stage for the models too large for the one-launch rollout kernel: per step the forward-only kernel

@@ -212,12 +212,15 @@ int rollout_stepwise(gmi_instance* g, gmi_model* m, gmi_env* env, gmi_buffer* b,
   if (T < 2 || n > m->max_rows || !g->fusion) return GMI_ERR_UNSUPPORTED;
   const int64_t ld = bd.ld_envs;
   const int o_pad = gmi::pad32(O);
+  if (!has_tile_forward(L)) return GMI_ERR_UNSUPPORTED;
+  const bool tile = use_tile_forward(m, n);      // as agent_act decides
   for (int t = 0; t < T; ++t) {
     const float* cur = t == 0 ? obs : bd.obs + (int64_t)t * ld * O;
     float* nxt = t == T - 1 ? obs : bd.obs + (int64_t)(t + 1) * ld * O;
     // policy means into the model's workspace, values straight into slot t
-    int rc = launch_forward_chain(g, m, cur, n, m->mu, bd.val + t * ld, t > 0 && forward_chain_reads_x0(m, cur));
-    if (rc != GMI_OK) return rc;      // before anything has run if this model has no forward-only kernel (t == 0)
+    int rc = tile ? launch_forward_chain(g, m, cur, n, m->mu, bd.val + t * ld, t > 0 && forward_chain_reads_x0(m, cur))
+                  : launch_agent(g, m, cur, n, 0, 0, 0, nullptr, nullptr, bd.val + t * ld, m->mu, true);
+    if (rc != GMI_OK) return rc;
     StepFuse fu;
     fu.mu = m->mu;
     fu.log_std = reinterpret_cast<const float*>(m->shadow + L.sh_logstd);
@@ -225,12 +228,13 @@ int rollout_stepwise(gmi_instance* g, gmi_model* m, gmi_env* env, gmi_buffer* b,
     fu.b_obs = t == 0 ? bd.obs : nullptr;
     fu.b_act = bd.act + (int64_t)t * ld * A;
     fu.b_logp = bd.logp + t * ld;
-    fu.x16_next = forward_chain_reads_x0(m, nxt) ? reinterpret_cast<uint16_t*>(m->x0) : nullptr;
+    fu.x16_next = tile && forward_chain_reads_x0(m, nxt) ? reinterpret_cast<uint16_t*>(m->x0) : nullptr;
     fu.o_pad = o_pad;
     rc = launch_env_step(g, env, cur, nullptr, step0 + (uint32_t)t, nxt, bd.rew + t * ld, bd.done + t * ld, &fu);
     if (rc != GMI_OK) return rc;
   }
-  return launch_forward_chain(g, m, obs, n, nullptr, last_value, forward_chain_reads_x0(m, obs));
+  return tile ? launch_forward_chain(g, m, obs, n, nullptr, last_value, forward_chain_reads_x0(m, obs))
+              : launch_agent(g, m, obs, n, 0, 0, 0, nullptr, nullptr, last_value, nullptr, false);
 }
 
 int launch_gather(gmi_instance* g, gmi_model* m, const float* obs, int n_envs, int ld_envs,
@@ -430,7 +434,7 @@ extern "C" int agent_act(gmi_t g, gmi_model_t m, const float* obs, int32_t n_row
   if (g->fusion) {
     rc = gmi::launch_agent_f32(g, m, obs, n_rows, seed, step, env_offset, act, logp, value, mu, true);
     if (rc == GMI_ERR_UNSUPPORTED)
-      rc = gmi::launch_agent_fused(g, m, obs, n_rows, seed, step, env_offset, act, logp, value, mu, true);
+      rc = gmi::launch_agent(g, m, obs, n_rows, seed, step, env_offset, act, logp, value, mu, true);
     if (rc != GMI_ERR_UNSUPPORTED) return rc;
   }
   rc = g->fusion ? gmi::launch_forward_chain(g, m, obs, n_rows, m->mu, value) : GMI_ERR_UNSUPPORTED;
@@ -454,7 +458,7 @@ extern "C" int agent_value(gmi_t g, gmi_model_t m, const float* obs, int32_t n_r
   if (!obs || !value) GMI_FAIL(GMI_ERR_INVALID_ARG, "agent_value: NULL pointer");
   if (g->fusion) {
     rc = gmi::launch_agent_f32(g, m, obs, n_rows, 0, 0, 0, nullptr, nullptr, value, nullptr, false);
-    if (rc == GMI_ERR_UNSUPPORTED) rc = gmi::launch_agent_fused(g, m, obs, n_rows, 0, 0, 0, nullptr, nullptr, value, nullptr, false);
+    if (rc == GMI_ERR_UNSUPPORTED) rc = gmi::launch_agent(g, m, obs, n_rows, 0, 0, 0, nullptr, nullptr, value, nullptr, false);
     if (rc != GMI_ERR_UNSUPPORTED) return rc;
   }
   rc = g->fusion ? gmi::launch_forward_chain(g, m, obs, n_rows, nullptr, value) : GMI_ERR_UNSUPPORTED;

@@ -77,3 +77,44 @@ def test_gradient_equals_the_per_layer_kernels(g, inst, obs, act, hidden, dtype,
     assert np.allclose(sa, sb, rtol=tol, atol=tol)
     g.gmi_buffer_destroy(buf)
     g.gmi_model_destroy(model)
+
+
+@pytest.mark.parametrize("obs,act,hidden,n,shift", [
+    (1, 1, [32], 1, 0),                       # one column, one action, one row
+    (45, 12, [128, 128], 31, 0),              # rows of an odd length: 16-byte pieces span two rows
+    (45, 12, [128, 128], 65, 1),              # ... of an array that is not 16-byte aligned
+    (60, 8, [256, 128, 64], 33, 1),
+    (60, 8, [256, 128, 64], 8193, 0),         # more 32-row tiles than fit at once: 64-row tiles
+    (108, 21, [400, 200, 100], 8200, 0),      # the same where two 64-row tiles do not fit: 32-row tiles in turn
+    (200, 33, [512, 512, 300], 130, 0),       # a head of two feature tiles; weights beyond 1 MB
+    (200, 20, [512, 512, 300], 65600, 0),     # ... and 64-row tiles one per compute unit
+    (211, 20, [512, 512, 256, 128], 12287, 0),      # the last size below the row-tile forward kernel
+    (30, 5, [64] * 8, 100, 0),                # the most layers
+])
+def test_agent_kernel_matches_the_per_layer_path(g, inst, obs, act, hidden, n, shift):
+    """Both paths round the same activations to bf16 after sums in another order: an activation may land on the other
+    neighbour (2^-8 of it), far less than 1e-2 of an output's norm; noise and log-density do not depend on them."""
+    dev = torch.device("cuda:0")
+    theta = torch.tensor(syn.make_model_params(obs, act, hidden, 5, policy_head_scale=0.5), device=dev)
+    desc = g.model_desc(obs, act, list(hidden), g.dtype_code("bf16"), n)
+    shadow = torch.zeros(g.gmi_model_shadow_bytes(desc), dtype=torch.uint8, device=dev)
+    x = torch.randn(n * obs + shift, generator=torch.Generator().manual_seed(n)).to(dev)[shift:]
+    torch.cuda.synchronize()
+    model = g.gmi_model_bind(inst, desc, theta, shadow)
+    g.gmi_model_refresh_shadow(inst, model)
+    out = {}
+    for fused in (1, 0):
+        g.gmi_set_fusion(inst, fused)
+        o = [torch.full(s, float("nan"), device=dev) for s in ((n, act), (n,), (n,), (n, act), (n,))]
+        torch.cuda.synchronize()
+        g.agent_act(inst, model, x, n, 42, 9, 100, *o[:4])
+        g.agent_value(inst, model, x, n, o[4])
+        g.gmi_sync(inst)
+        out[fused] = [t.cpu().numpy() for t in o]
+    g.gmi_set_fusion(inst, 1)
+    g.gmi_model_destroy(model)
+    for k in (0, 2, 3, 4):
+        assert np.isfinite(out[1][k]).all()
+        assert rel_l2(out[1][k], out[0][k]) <= 1e-2, k
+    assert rel_l2(out[1][1], out[0][1]) <= 1e-6
+    assert np.array_equal(out[1][2], out[1][4])      # agent_value is the same network pass
