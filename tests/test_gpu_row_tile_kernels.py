@@ -85,6 +85,7 @@ def test_gradient_equals_the_per_layer_kernels(g, inst, obs, act, hidden, dtype,
     (45, 12, [128, 128], 65, 1),              # ... of an array that is not 16-byte aligned
     (60, 8, [256, 128, 64], 33, 1),
     (60, 8, [256, 128, 64], 8193, 0),         # more 32-row tiles than fit at once: 64-row tiles
+    (45, 12, [128, 128], 32801, 1),           # enough rows for 128-row tiles
     (108, 21, [400, 200, 100], 8200, 0),      # the same where two 64-row tiles do not fit: 32-row tiles in turn
     (200, 33, [512, 512, 300], 130, 0),       # a head of two feature tiles; weights beyond 1 MB
     (200, 20, [512, 512, 300], 65600, 0),     # ... and 64-row tiles one per compute unit
@@ -118,3 +119,35 @@ def test_agent_kernel_matches_the_per_layer_path(g, inst, obs, act, hidden, n, s
         assert rel_l2(out[1][k], out[0][k]) <= 1e-2, k
     assert rel_l2(out[1][1], out[0][1]) <= 1e-6
     assert np.array_equal(out[1][2], out[1][4])      # agent_value is the same network pass
+
+
+@pytest.mark.parametrize("obs,act,hidden,n", [
+    (211, 20, [512, 512, 256, 128], 32769),   # 128 rows with all registers
+    (60, 8, [256, 128, 64], 32801),           # two 128-row tiles per compute unit
+    (107, 21, [400, 200, 100], 8225),         # two 64-row tiles; rows of an odd length
+    (45, 300, [100], 65),                     # a head of ten feature tiles
+    (45, 510, [512, 512], 33),                # draws and densities do not fit beside the tile: a launch of their own
+])
+def test_fp8_agent_rows_do_not_depend_on_the_tile(g, inst, obs, act, hidden, n):
+    """A row's results are the same whatever the workgroup's rows: a large batch against its rows in batches of 32, bit for
+    bit (the small batches are compared with the oracle elsewhere)."""
+    dev = torch.device("cuda:0")
+    theta = torch.tensor(syn.make_model_params(obs, act, hidden, 5, policy_head_scale=0.5), device=dev)
+    w = g.gmi_fp8_bind(inst, g.model_desc(obs, act, list(hidden), g.dtype_code("bf16"), n))
+    x = torch.randn(n, obs, generator=torch.Generator().manual_seed(n)).to(dev)
+    torch.cuda.synchronize()
+    g.gmi_fp8_refresh(inst, w, theta)
+    new = lambda k: [torch.full(s, float("nan"), device=dev) for s in ((k, act), (k,), (k,), (k, act))]
+    big = new(n)
+    torch.cuda.synchronize()
+    g.agent_act_fp8(inst, w, x, n, 42, 9, 100, *big)
+    for r0 in (0, 32 * (n // 64), 32 * ((n - 1) // 32)):
+        k = min(32, n - r0)
+        o, xs = new(k), x[r0:r0 + k].clone()
+        torch.cuda.synchronize()
+        g.agent_act_fp8(inst, w, xs, k, 42, 9, 100 + r0, *o)
+        g.gmi_sync(inst)
+        for a, b in zip(big, o):
+            assert torch.isfinite(b).all()
+            assert torch.equal(a[r0:r0 + k], b)
+    g.gmi_fp8_destroy(w)
