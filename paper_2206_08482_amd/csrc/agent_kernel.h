@@ -46,6 +46,12 @@ struct AgentArgs {
   uint32_t o_magic, pad_magic, k0, k1, step, env_offset;
   const float *log_std, *obs;
   float *act, *logp, *value, *mu_out;      // act NULL: means and values only
+  // Values of several steps at once (net0 = 1): blockIdx.z = t < T reads obs + t obs_step and writes value + t val_step,
+  // t = T reads obs_last and writes value_last.
+  int T;
+  int64_t obs_step, val_step;
+  const float* obs_last;
+  float* value_last;
 };
 
 // 32x32x16 products of bf16.
@@ -130,15 +136,108 @@ __device__ __forceinline__ void k_loop(floatx16 (&acc)[NRT], Ring<P, D>& wq, con
       for (int v = 0; v < P::align; ++v) step(ks + u + v, u + v);
 }
 
+// Row tiles of an item of a product with nft feature tiles: as many (at most MT) as still leave every wave an item.
+template <int RT, int MT>
+__device__ __forceinline__ int item_tiles(int nft) {
+  if (MT >= 4 && nft * (RT / 4) >= kNW) return 4;
+  return MT >= 2 && nft * (RT / 2) >= kNW ? 2 : 1;
+}
+
+// Requests the first weight blocks of an item of layer L.
+template <class P, int RT, int D, int MT>
+__device__ __forceinline__ void request(Ring<P, D>& wq, const AgentLayer& L, int item, int lane) {
+  const int nft = L.F >> 5, nks = L.K * P::size / (32 * P::pieces);
+  const int ft = min(item / (RT / item_tiles<RT, MT>(nft)), nft - 1);
+  const uint4* wp = L.w + (int64_t)ft * nks * 64 * P::pieces + lane;
+#pragma unroll
+  for (int u = 0; u < D; ++u)
+#pragma unroll
+    for (int p = 0; p < P::pieces; ++p) wq[u][p] = wp[(min(u, nks - 1) * P::pieces + p) * 64];
+}
+
+// All layers of a net on the workgroup's 32 RT rows.  Layer 0 reads the rows at x0; odd layers read ya, even ones yb (which
+// may be x0); a row of a layer's input takes K * P::size + 16 bytes.  The head's results go to s_head [row][ho].  wq holds
+// the first blocks of layer 0 for item `wave`; AGAIN: so it does afterwards, for the next pass.  Ends with a barrier.
+template <class P, int RT, int D, int MT, bool AGAIN>
+__device__ __forceinline__ void net_layers(const AgentLayer* N, int nl, Ring<P, D>& wq, const unsigned char* x0, unsigned char* ya,
+                                           unsigned char* yb, const float* s_bias, float* s_head, int ho, int wave, int lane) {
+  constexpr int B = 32 * P::pieces;
+  const int s = lane & 31, h = lane >> 5;
+  const float* bias = s_bias + 4 * h;
+  for (int l = 0; l < nl; ++l) {
+    const AgentLayer& L = N[l];
+    const AgentLayer& Ln = N[l + 1 < nl ? l + 1 : 0];
+    const int nft = L.F >> 5, nks = L.K * P::size / B, sx = L.K * P::size + 16, sy = L.F * P::size + 16;
+    const unsigned char* x = l == 0 ? x0 : l & 1 ? ya : yb;
+    unsigned char* y = l & 1 ? yb : ya;
+    const bool head = l == nl - 1;
+    const bool more = AGAIN || !head;
+    float scale = 1.f;
+    if constexpr (P::scaled) scale = *L.scale;
+    auto items = [&](auto nrt) {
+      constexpr int NRT = decltype(nrt)::value;
+      constexpr int nrg = RT / NRT;
+      const int n_items = nft * nrg;
+      for (int item = wave; item < n_items; item += kNW) {
+        const int ft = item / nrg, rg = item % nrg;
+        float4 b4[4];
+        if constexpr (!P::bias_lds)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) b4[q] = *reinterpret_cast<const float4*>(L.bias + 32 * ft + 8 * q + 4 * h);
+        floatx16 acc[NRT];
+#pragma unroll
+        for (int i = 0; i < NRT; ++i)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
+        k_loop<P, D, NRT>(acc, wq, L.w + (int64_t)ft * nks * 64 * P::pieces + lane, nks, x + (rg * NRT * 32 + s) * sx + B / 2 * h, 32 * sx);
+        if (item + kNW < n_items) request<P, RT, D, MT>(wq, L, item + kNW, lane);
+        else if (more) request<P, RT, D, MT>(wq, Ln, wave, lane);
+        // lane (s, h) holds, per quad q, the features 32 ft + 8 q + 4 h + 0..3 of row s
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int f = 32 * ft + 8 * q + 4 * h;
+          float4 b;
+          if constexpr (P::bias_lds) b = *reinterpret_cast<const float4*>(bias + 32 * ft + 8 * q);
+          else b = b4[q];
+#pragma unroll
+          for (int i = 0; i < NRT; ++i) {
+            const int r = (rg * NRT + i) * 32 + s;
+            float v[4] = {acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]};
+            if constexpr (P::scaled) {
+              v[0] = fmaf(v[0], scale, b.x); v[1] = fmaf(v[1], scale, b.y); v[2] = fmaf(v[2], scale, b.z); v[3] = fmaf(v[3], scale, b.w);
+            } else {
+              v[0] += b.x; v[1] += b.y; v[2] += b.z; v[3] += b.w;
+            }
+            if (!head) {
+              P::store4(y + r * sy + f * P::size, elu_f(v[0]), elu_f(v[1]), elu_f(v[2]), elu_f(v[3]));
+            } else {
+              float* d = s_head + r * ho + f;
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                if (f + e < ho) d[e] = v[e];
+            }
+          }
+        }
+      }
+      if (wave >= n_items && more) request<P, RT, D, MT>(wq, Ln, wave, lane);
+    };
+    const int nrt = item_tiles<RT, MT>(nft);
+    if (nrt == 1) items(std::integral_constant<int, 1>{});
+    if constexpr (MT >= 2) if (nrt == 2) items(std::integral_constant<int, 2>{});
+    if constexpr (MT >= 4) if (nrt == 4) items(std::integral_constant<int, 4>{});
+    bias += L.F;
+    __syncthreads();
+  }
+}
+
 // D: weight blocks in flight per wave; MT: most row tiles of an item; WPS: waves per SIMD (registers).
 template <class P, int RT, int D, int MT, int WPS>
 __global__ __launch_bounds__(kNT, WPS) void agent_kernel(AgentArgs a) {
-  constexpr int R = 32 * RT, B = 32 * P::pieces;
+  constexpr int R = 32 * RT;
   extern __shared__ __attribute__((aligned(16))) unsigned char s_x[];
   const int net = a.net0 + blockIdx.y;
   const AgentLayer* N = a.l[net];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int s = lane & 31, h = lane >> 5;
   const int nl = a.nl, O = a.O, K0 = N[0].K, S0 = K0 * P::size + 16;
   const int ho = net == 0 ? a.A : 1, nb = a.act ? (a.A + 3) >> 2 : 0;          // head outputs; blocks of 4 actions
   float4* s_noise = reinterpret_cast<float4*>(s_x + a.f_off);                  // [R][nb]
@@ -146,22 +245,7 @@ __global__ __launch_bounds__(kNT, WPS) void agent_kernel(AgentArgs a) {
   float* s_head = s_bias + a.bias_floats;                                      // [R][ho]
   const int r0 = blockIdx.x * R, rows = min(R, a.n - r0);
 
-  // row tiles of an item of a product with nft feature tiles
-  auto item_tiles = [&](int nft) {
-    if (MT >= 4 && nft * (RT / 4) >= kNW) return 4;
-    return MT >= 2 && nft * (RT / 2) >= kNW ? 2 : 1;
-  };
   Ring<P, D> wq;
-  auto request = [&](const AgentLayer& L, int item) {
-    const int nft = L.F >> 5, nks = L.K * P::size / B;
-    const int ft = min(item / (RT / item_tiles(nft)), nft - 1);
-    const uint4* wp = L.w + (int64_t)ft * nks * 64 * P::pieces + lane;
-#pragma unroll
-    for (int u = 0; u < D; ++u)
-#pragma unroll
-      for (int p = 0; p < P::pieces; ++p) wq[u][p] = wp[(min(u, nks - 1) * P::pieces + p) * 64];
-  };
-
   // biases in LDS: requested here, stored after the observations
   float bv[P::bias_lds ? 4 : 1];
   if constexpr (P::bias_lds)
@@ -169,7 +253,8 @@ __global__ __launch_bounds__(kNT, WPS) void agent_kernel(AgentArgs a) {
     for (int u = 0; u < 4; ++u) bv[u] = N[0].bias[min(tid + u * kNT, a.bias_floats - 1)];
   // the tile's observations are rows * O consecutive floats; 16-byte pieces of them may span two rows
   {
-    const float* src = a.obs + (int64_t)r0 * O;
+    const int t = blockIdx.z;
+    const float* src = (t < a.T ? a.obs + t * a.obs_step : a.obs_last) + (int64_t)r0 * O;
     const int cnt = rows * O, n4 = a.vec_obs ? cnt >> 2 : 0;
     for (int e0 = tid; e0 < n4; e0 += 4 * kNT) {
       float4 v[4];
@@ -203,7 +288,7 @@ __global__ __launch_bounds__(kNT, WPS) void agent_kernel(AgentArgs a) {
     }
     for (int e = rows * (S0 >> 4) + tid; e < R * (S0 >> 4); e += kNT) reinterpret_cast<uint4*>(s_x)[e] = make_uint4(0u, 0u, 0u, 0u);
   }
-  request(N[0], wave);
+  request<P, RT, D, MT>(wq, N[0], wave, lane);
   if constexpr (P::bias_lds) {
 #pragma unroll
     for (int u = 0; u < 4; ++u)
@@ -219,72 +304,12 @@ __global__ __launch_bounds__(kNT, WPS) void agent_kernel(AgentArgs a) {
     }
   __syncthreads();
 
-  const float* bias = s_bias + 4 * h;
-  for (int l = 0; l < nl; ++l) {
-    const AgentLayer& L = N[l];
-    const AgentLayer& Ln = N[min(l + 1, nl - 1)];
-    const int nft = L.F >> 5, nks = L.K * P::size / B, sx = L.K * P::size + 16, sy = L.F * P::size + 16;
-    const unsigned char* x = s_x + (l & 1 ? a.y_off : 0);
-    unsigned char* y = s_x + (l & 1 ? 0 : a.y_off);
-    const bool head = l == nl - 1;
-    float scale = 1.f;
-    if constexpr (P::scaled) scale = *L.scale;
-    auto items = [&](auto nrt) {
-      constexpr int NRT = decltype(nrt)::value;
-      constexpr int nrg = RT / NRT;
-      const int n_items = nft * nrg;
-      for (int item = wave; item < n_items; item += kNW) {
-        const int ft = item / nrg, rg = item % nrg;
-        float4 b4[4];
-        if constexpr (!P::bias_lds)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) b4[q] = *reinterpret_cast<const float4*>(L.bias + 32 * ft + 8 * q + 4 * h);
-        floatx16 acc[NRT];
-#pragma unroll
-        for (int i = 0; i < NRT; ++i)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
-        k_loop<P, D, NRT>(acc, wq, L.w + (int64_t)ft * nks * 64 * P::pieces + lane, nks, x + (rg * NRT * 32 + s) * sx + B / 2 * h, 32 * sx);
-        if (item + kNW < n_items) request(L, item + kNW); else request(Ln, wave);
-        // lane (s, h) holds, per quad q, the features 32 ft + 8 q + 4 h + 0..3 of row s
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int f = 32 * ft + 8 * q + 4 * h;
-          float4 b;
-          if constexpr (P::bias_lds) b = *reinterpret_cast<const float4*>(bias + 32 * ft + 8 * q);
-          else b = b4[q];
-#pragma unroll
-          for (int i = 0; i < NRT; ++i) {
-            const int r = (rg * NRT + i) * 32 + s;
-            float v[4] = {acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]};
-            if constexpr (P::scaled) {
-              v[0] = fmaf(v[0], scale, b.x); v[1] = fmaf(v[1], scale, b.y); v[2] = fmaf(v[2], scale, b.z); v[3] = fmaf(v[3], scale, b.w);
-            } else {
-              v[0] += b.x; v[1] += b.y; v[2] += b.z; v[3] += b.w;
-            }
-            if (!head) {
-              P::store4(y + r * sy + f * P::size, elu_f(v[0]), elu_f(v[1]), elu_f(v[2]), elu_f(v[3]));
-            } else {
-              float* d = s_head + r * ho + f;
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (f + e < ho) d[e] = v[e];
-            }
-          }
-        }
-      }
-      if (wave >= n_items) request(Ln, wave);
-    };
-    const int nrt = item_tiles(nft);
-    if (nrt == 1) items(std::integral_constant<int, 1>{});
-    if constexpr (MT >= 2) if (nrt == 2) items(std::integral_constant<int, 2>{});
-    if constexpr (MT >= 4) if (nrt == 4) items(std::integral_constant<int, 4>{});
-    bias += L.F;
-    __syncthreads();
-  }
+  net_layers<P, RT, D, MT, false>(N, nl, wq, s_x, s_x + a.y_off, s_x, s_bias, s_head, ho, wave, lane);
 
   if (net == 1) {
-    for (int r = tid; r < rows; r += kNT) a.value[r0 + r] = s_head[r];
+    const int t = blockIdx.z;
+    float* dst = t < a.T ? a.value + t * a.val_step : a.value_last;
+    for (int r = tid; r < rows; r += kNT) dst[r0 + r] = s_head[r];
     return;
   }
   if (!a.act) {      // the means alone
@@ -342,7 +367,7 @@ int launch(gmi_instance* g, AgentArgs& a, int nets, bool sample) {
     attr = true;
   }
   gmi::ProfScope ps(g, gmi::kClsFusedAgent);
-  ps.launch(agent_kernel<P, RT, D, MT, WPS>, dim3((a.n + 32 * RT - 1) / (32 * RT), nets), dim3(kNT), lds, a);
+  ps.launch(agent_kernel<P, RT, D, MT, WPS>, dim3((a.n + 32 * RT - 1) / (32 * RT), nets, a.T + (a.value_last ? 1 : 0)), dim3(kNT), lds, a);
   GMI_LAUNCH_CHECK();
   return GMI_OK;
 }

@@ -1,7 +1,7 @@
 // One-launch collection kernel: a workgroup owns a tile of R samples (envs), keeps the activations of the
 // tile in LDS (bf16) from layer to layer, and streams each layer's bf16 weights from L2 straight into the
 // matrix cores' weight operand.
-#include "internal.h"
+#include "agent_kernel.h"
 #include "rng.h"
 #include "rollout.h"
 
@@ -38,133 +38,7 @@ struct FusedNet {
   int out_store;                             // logical outputs of the head
 };
 
-enum { kFEpiElu = 0, kFEpiHead = 1, kFEpiEluGrad = 2 };
-
-// One layer for the workgroup's tile: s_out[r, f] = epi(sum_k s_in[r, k] W[f, k] + bias[f]).
-// Feature tiles of 32 are dealt to the 4 waves; a wave walks its (tile, 64-wide k chunk) pairs in one
-// flat loop through a ring of 4 register buffers, so the weight fragments of the next three pairs are in
-// flight while one is multiplied: an L2 round trip (~1 us measured here) costs far more than a chunk's
-// products, and with only one pair ahead every chunk waited for it.  The bias comes from LDS (s_bias).
-// FRAG: W is the fragment-major copy (wfrag_index) instead of row-major [out_pad, in_pad].
-template <int RT, int EPI, bool FRAG = true>
-__device__ __forceinline__ void fused_layer(const uint16_t* __restrict__ W, const float* s_bias,
-                                            int in_pad, int out_pad, const uint16_t* s_in, int stride_in,
-                                            uint16_t* s_out, int stride_out, float* s_head, int head_stride,
-                                            int out_store, const uint16_t* s_h = nullptr, int stride_hh = 0,
-                                            int wave_id = -1) {
-  // wave_id: this wave's index among the 4 that share the layer (default: a 256-thread workgroup's own);
-  // made wave-uniform for the compiler: tile loops and operand addresses then run on the scalar unit
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = wave_id >= 0 ? wave_id : __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n_ft = out_pad >> 5;
-  const int n_my = (n_ft - wave + 3) >> 2;                 // tiles wave, wave+4, ...
-  const int nchunk = (in_pad + 63) >> 6;
-  const int nq = n_my > 0 ? n_my * nchunk : 0;
-  const int khalf = (lane >> 5) * 8;
-  floatx16 acc[RT];
-  bf16x8 A0[4], A1[4], A2[4], A3[4];
-
-  auto load_chunk = [&](bf16x8* A, int q) {
-    if (q >= nq) return;
-    const int tile = q / nchunk, ch = q - tile * nchunk;
-    if (FRAG) {
-      // k steps past the ragged end repeat the last one (never multiplied)
-      const int nks = in_pad >> 4;
-      const uint16_t* p = W + ((int64_t)(wave + 4 * tile) * nks) * 512 + lane * 8;
-#pragma unroll
-      for (int s = 0; s < 4; ++s) A[s] = *reinterpret_cast<const bf16x8*>(p + (int64_t)min(ch * 4 + s, nks - 1) * 512);
-    } else {
-      const int frow = (wave + 4 * tile) * 32 + (lane & 31);
-      const uint16_t* p = W + (int64_t)frow * in_pad;
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int k = min(ch * 64 + s * 16 + khalf, in_pad - 8);
-        A[s] = *reinterpret_cast<const bf16x8*>(p + k);
-      }
-    }
-  };
-  auto compute_chunk = [&](const bf16x8* A, int q) {
-    if (q >= nq) return;
-    const int tile = q / nchunk, ch = q - tile * nchunk;
-    if (ch == 0) {
-#pragma unroll
-      for (int j = 0; j < RT; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
-    }
-    // widths are multiples of 32: a chunk holds 4 k-steps of 16, or 2 at the ragged end.  All activation
-    // fragments of the chunk are read from LDS before the first product, so the reads overlap each other.
-    const uint16_t* xrow = s_in + (lane & 31) * stride_in + ch * 64 + khalf;
-    if (ch * 64 + 64 <= in_pad) {
-      bf16x8 b[RT][4];
-#pragma unroll
-      for (int j = 0; j < RT; ++j)
-#pragma unroll
-        for (int s = 0; s < 4; ++s) b[j][s] = *reinterpret_cast<const bf16x8*>(xrow + j * 32 * stride_in + s * 16);
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int j = 0; j < RT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[s], b[j][s], acc[j], 0, 0, 0);
-    } else {
-      bf16x8 b[RT][2];
-#pragma unroll
-      for (int j = 0; j < RT; ++j)
-#pragma unroll
-        for (int s = 0; s < 2; ++s) b[j][s] = *reinterpret_cast<const bf16x8*>(xrow + j * 32 * stride_in + s * 16);
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int j = 0; j < RT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[s], b[j][s], acc[j], 0, 0, 0);
-    }
-    if (ch == nchunk - 1) {
-      const int fb = (wave + 4 * tile) * 32;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int f = fb + g * 8 + (lane >> 5) * 4;
-        float4 bv = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (EPI != kFEpiEluGrad) bv = *reinterpret_cast<const float4*>(s_bias + f);
-#pragma unroll
-        for (int j = 0; j < RT; ++j) {
-          const int r = j * 32 + (lane & 31);
-          float o0 = acc[j][g * 4 + 0] + bv.x, o1 = acc[j][g * 4 + 1] + bv.y;
-          float o2 = acc[j][g * 4 + 2] + bv.z, o3 = acc[j][g * 4 + 3] + bv.w;
-          if (EPI == kFEpiEluGrad) {
-            // times ELU'(z) expressed through the stored output h = ELU(z): 1 if h > 0 else h + 1
-            const uint2 hv = *reinterpret_cast<const uint2*>(&s_h[r * stride_hh + f]);
-            const float h0 = bf16_to_f((uint16_t)(hv.x & 0xFFFF)), h1 = bf16_to_f((uint16_t)(hv.x >> 16));
-            const float h2 = bf16_to_f((uint16_t)(hv.y & 0xFFFF)), h3 = bf16_to_f((uint16_t)(hv.y >> 16));
-            o0 *= elu_grad_f(h0); o1 *= elu_grad_f(h1);
-            o2 *= elu_grad_f(h2); o3 *= elu_grad_f(h3);
-            *reinterpret_cast<uint2*>(&s_out[r * stride_out + f]) = make_uint2(pack_bf16(o0, o1), pack_bf16(o2, o3));
-          } else if (EPI == kFEpiElu) {
-            *reinterpret_cast<uint2*>(&s_out[r * stride_out + f]) =
-                make_uint2(pack_bf16(elu_f(o0), elu_f(o1)), pack_bf16(elu_f(o2), elu_f(o3)));
-          } else {
-            float* d = s_head + r * head_stride + f;
-            if (f + 0 < out_store) d[0] = o0;
-            if (f + 1 < out_store) d[1] = o1;
-            if (f + 2 < out_store) d[2] = o2;
-            if (f + 3 < out_store) d[3] = o3;
-          }
-        }
-      }
-    }
-  };
-
-  load_chunk(A0, 0);
-  load_chunk(A1, 1);
-  load_chunk(A2, 2);
-  for (int q = 0; q < nq; q += 4) {
-    load_chunk(A3, q + 3);
-    compute_chunk(A0, q);
-    load_chunk(A0, q + 4);
-    compute_chunk(A1, q + 1);
-    load_chunk(A1, q + 5);
-    compute_chunk(A2, q + 2);
-    load_chunk(A2, q + 6);
-    compute_chunk(A3, q + 3);
-  }
-}
+enum { kFEpiElu = 0, kFEpiHead = 1 };
 
 // Copies the biases of all layers of a net into LDS (dst[bias_off[l] + f]); the caller synchronises.
 __device__ __forceinline__ void stage_biases(const FusedNet& N, float* dst, int tid0, int nthreads) {
@@ -182,6 +56,7 @@ __device__ __forceinline__ void stage_biases(const FusedNet& N, float* dst, int 
 // agent_act / env_step / collect_experience called step by step.
 struct RolloutArgs : RolloutEnv {
   FusedNet net[2];
+  gmi_agent::AgentLayer policy[gmi_agent::kMaxLayers];      // the streaming form's view of the policy net
   int obs_pad, max_h;
   int mt_lds;                       // m_t: 2 = LDS copy kept for the whole launch, 1 = LDS copy made at every
                                     // step in the (then idle) hidden-activation space, 0 = read from global
@@ -195,7 +70,7 @@ struct RolloutArgs : RolloutEnv {
 // Weight-stationary form of the layers, for model shapes whose share of the weights fits a wave's registers:
 // the one-launch rollout runs the same layers T + 1 times, so each wave fetches the operand blocks of ITS
 // feature tiles once, at kernel start, and keeps them in registers for all steps (streamed from L2 they cost
-// ~2000 cycles of latency per layer and step).  Same products in the same order as fused_layer: results are
+// ~2000 cycles of latency per layer and step).  Same products in the same order as the streaming form: results are
 // bit-identical.  DIMS = padded widths d[0..NL] (input, hidden..., head).
 template <class WS> struct WsFrags { static constexpr int value = WS::n_frags(); };
 template <> struct WsFrags<void> { static constexpr int value = 1; };
@@ -327,89 +202,6 @@ __device__ __forceinline__ int wfrag16_off(int f, int k0, int nks16) {
   return ((((f >> 5) * nks16 + (k0 >> 4)) * 64) + (f & 31) + 32 * ((k0 >> 3) & 1)) * 8;
 }
 
-// The streaming layer (fused_layer) for a 16-env tile: the same 32-feature tiles, 64-wide k chunks and ring of 4
-// register buffers, but every chunk's weights fetched as the operands of 16x16x32 products (two 16-feature halves x
-// two k steps of 32, from the same fragment-major copy) -- half the instruction passes and half the epilogue
-// arithmetic; k runs in the same order, so the sums are those of fused_layer bit for bit.
-template <int EPI>
-__device__ __forceinline__ void fused_layer16(const uint16_t* __restrict__ W, const float* s_bias, int in_pad, int out_pad,
-                                              const uint16_t* s_in, int stride_in, uint16_t* s_out, int stride_out,
-                                              float* s_head, int head_stride, int out_store, int wave) {
-  const int lane = threadIdx.x & 63, q = lane >> 4, n = lane & 15;
-  const int n_ft = out_pad >> 5;
-  const int n_my = (n_ft - wave + 3) >> 2;                 // tiles wave, wave+4, ...
-  const int nchunk = (in_pad + 63) >> 6;
-  const int nq = n_my > 0 ? n_my * nchunk : 0;
-  const int nks16 = in_pad >> 4;
-  floatx4 acc[2];
-  bf16x8 A0[4], A1[4], A2[4], A3[4];
-
-  auto load_chunk = [&](bf16x8* A, int qq) {
-    if (qq >= nq) return;
-    const int tile = qq / nchunk, ch = qq - tile * nchunk;
-#pragma unroll
-    for (int fh = 0; fh < 2; ++fh)
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        // a k step past the ragged end repeats the last one (never multiplied)
-        const int k0 = min(ch * 64 + ks * 32, in_pad - 32);
-        A[fh * 2 + ks] = *reinterpret_cast<const bf16x8*>(W + wfrag16_off((wave + 4 * tile) * 32 + fh * 16 + n, k0 + q * 8, nks16));
-      }
-  };
-  auto compute_chunk = [&](const bf16x8* A, int qq) {
-    if (qq >= nq) return;
-    const int tile = qq / nchunk, ch = qq - tile * nchunk;
-    if (ch == 0) {
-      acc[0] = floatx4{0.f, 0.f, 0.f, 0.f};
-      acc[1] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
-    const uint16_t* xrow = s_in + n * stride_in + ch * 64 + q * 8;
-    const bf16x8 b0 = *reinterpret_cast<const bf16x8*>(xrow);
-    if (ch * 64 + 64 <= in_pad) {
-      const bf16x8 b1 = *reinterpret_cast<const bf16x8*>(xrow + 32);
-      acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[0], b0, acc[0], 0, 0, 0);
-      acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[2], b0, acc[1], 0, 0, 0);
-      acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[1], b1, acc[0], 0, 0, 0);
-      acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[3], b1, acc[1], 0, 0, 0);
-    } else {                                              // widths are multiples of 32: one k step at the ragged end
-      acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[0], b0, acc[0], 0, 0, 0);
-      acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[2], b0, acc[1], 0, 0, 0);
-    }
-    if (ch == nchunk - 1) {
-#pragma unroll
-      for (int fh = 0; fh < 2; ++fh) {
-        const int f = (wave + 4 * tile) * 32 + fh * 16 + 4 * q;
-        const float4 bv = *reinterpret_cast<const float4*>(s_bias + f);
-        const float o0 = acc[fh][0] + bv.x, o1 = acc[fh][1] + bv.y, o2 = acc[fh][2] + bv.z, o3 = acc[fh][3] + bv.w;
-        if (EPI == kFEpiElu) {
-          *reinterpret_cast<uint2*>(&s_out[n * stride_out + f]) =
-              make_uint2(pack_bf16(elu_f(o0), elu_f(o1)), pack_bf16(elu_f(o2), elu_f(o3)));
-        } else {
-          float* d = s_head + n * head_stride + f;
-          if (f + 0 < out_store) d[0] = o0;
-          if (f + 1 < out_store) d[1] = o1;
-          if (f + 2 < out_store) d[2] = o2;
-          if (f + 3 < out_store) d[3] = o3;
-        }
-      }
-    }
-  };
-
-  load_chunk(A0, 0);
-  load_chunk(A1, 1);
-  load_chunk(A2, 2);
-  for (int qq = 0; qq < nq; qq += 4) {
-    load_chunk(A3, qq + 3);
-    compute_chunk(A0, qq);
-    load_chunk(A0, qq + 4);
-    compute_chunk(A1, qq + 1);
-    load_chunk(A1, qq + 5);
-    compute_chunk(A2, qq + 2);
-    load_chunk(A2, qq + 6);
-    compute_chunk(A3, qq + 3);
-  }
-}
-
 template <class WS, int L>
 __device__ __forceinline__ void ws_load16(bf16x8* wreg, const FusedNet& N, int wave, int lane) {
   if constexpr (L < WS::NL && L < WS::lds_from) {
@@ -518,11 +310,14 @@ bool ws_matches(const ModelLayout& L) {
   return true;
 }
 
-// 512 threads: waves 0-3 run the policy net and waves 4-7 the value net at the same time (the two nets
-// have the same hidden widths, so their layers finish together and share the barriers); every other phase
-// uses all 8 waves.
-// WS: a WsShape whose widths the model has (weights held in registers for the whole launch), or void (weights
-// streamed from L2 at every step).
+// 512 threads.
+// WS: a WsShape whose widths the model has (weights held in registers for the whole launch): waves 0-3 run the policy net
+// and waves 4-7 the value net at the same time (the two nets have the same hidden widths, so their layers finish together
+// and share the barriers); every other phase uses all 8 waves.
+// void: the policy net alone, on all 8 waves, its weights streamed from L2 at every step with the layer walk of the agent
+// kernel (agent_kernel.h): the next item's blocks, across layers and steps, are on their way before the present one is
+// left.  A compute unit draws weights at about 50 B/ns, which bounds the step of a wide net, so the value net -- which the
+// simulator does not wait for -- is left to one launch over all slots afterwards (launch_values).
 // R16: the 16-env form of the weight-stationary nets (rows_per_wg == 16).
 template <int RT, class WS = void, bool R16 = false>
 __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
@@ -534,7 +329,9 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
   // hidden activations (bf16, ping-pong, one pair per net) share their space with the next-state tile
   // (after the nets: next-state tile, then this step's random draws, then the staged simulator matrix)
   const int npr = nba + nbo + 1;                     // random blocks per env and step: action, env noise, done
-  const size_t hid_bytes = 4 * (size_t)R * stride_h * 2, next_bytes = ((size_t)R * o4 * 4 + 15) & ~(size_t)15;
+  constexpr bool kStationary = !std::is_void<WS>::value;
+  constexpr int kNets = kStationary ? 2 : 1;
+  const size_t hid_bytes = 2 * kNets * (size_t)R * stride_h * 2, next_bytes = ((size_t)R * o4 * 4 + 15) & ~(size_t)15;
   const size_t noise_bytes = (size_t)R * npr * 16;
   const size_t region = ((hid_bytes > next_bytes + noise_bytes ? hid_bytes : next_bytes + noise_bytes) + 15) & ~(size_t)15;
   float* s_in = reinterpret_cast<float*>(smem_raw);                                  // [R][O + A] state | action
@@ -551,7 +348,7 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
   // this step's random draws, one float4 per (env, block): nba action-noise blocks, nbo env-noise blocks, then
   // the done draw (raw word in .x); in the hidden-activation space, which is idle once the heads are done
   float4* s_noise_inplace = reinterpret_cast<float4*>(s_reg + next_bytes);
-  float* s_mt = s_bias + ((a.net[0].bias_total + a.net[1].bias_total + 3) & ~3);     // [O + A][o4] when mt_lds == 2
+  float* s_mt = s_bias + (kStationary ? (a.net[0].bias_total + a.net[1].bias_total + 3) & ~3 : 0);     // [O + A][o4] when mt_lds == 2
   // weight-stationary form: operand blocks of the LDS-resident layers, policy net then value net
   uint16_t* s_wl = reinterpret_cast<uint16_t*>(s_mt + (a.mt_lds == 2 ? OA * o4 : 0));
   float4* s_ahead = reinterpret_cast<float4*>(smem_raw + a.ahead_off);                // [2][Rv][npr] when noise_ahead
@@ -568,8 +365,10 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
   const int act_waves_end = (Rv * nba * 4 + 63) & ~63;
   const int obs_tid0 = act_waves_end <= NT / 2 ? act_waves_end : 0;
   for (int idx = tid; idx < (R - Rv) * stride_x0; idx += NT) s_x0[Rv * stride_x0 + idx] = 0;
-  stage_biases(a.net[0], s_bias, tid, NT);
-  stage_biases(a.net[1], s_bias + a.net[0].bias_total, tid, NT);
+  if constexpr (kStationary) {
+    stage_biases(a.net[0], s_bias, tid, NT);
+    stage_biases(a.net[1], s_bias + a.net[0].bias_total, tid, NT);
+  }
   if (a.mt_lds == 2)
     for (int idx = tid; idx < OA * nbo; idx += NT)
       reinterpret_cast<float4*>(s_mt)[idx] = reinterpret_cast<const float4*>(a.m_t)[idx];
@@ -585,7 +384,6 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
   float* s_head = half ? s_val : s_mu;
   const int head_stride = half ? 1 : A;
   const float* s_nb = s_bias + (half ? a.net[0].bias_total : 0);
-  constexpr bool kStationary = !std::is_void<WS>::value;
   // this wave's weight operands, fetched once (a dummy single entry in the streaming form)
   bf16x8 wreg[WsFrags<WS>::value];
   const uint16_t* s_w = s_wl;
@@ -596,6 +394,12 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
     ws_stage<WS, 0>(s_wl + WS::lds_elems(), a.net[1], tid, NT);
     s_w = s_wl + (half ? WS::lds_elems() : 0);
   }
+
+  // streaming form: the first weight blocks of this wave's first item are always on their way
+  constexpr int kAhead = RT == 1 ? 8 : 4;
+  gmi_agent::Ring<gmi_agent::Bf16, kAhead> wq;
+  const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if constexpr (!kStationary) gmi_agent::request<gmi_agent::Bf16, RT, kAhead, RT>(wq, a.policy[0], wave8, tid & 63);
 
   // The grid never exceeds what the instance's compute units hold at once: a workgroup takes the tiles
   // blockIdx.x, blockIdx.x + gridDim.x, ... one after the other, each through all T steps.  (Workgroups
@@ -631,33 +435,10 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
       else
         ws_net<WS, 0, RT>(wreg, s_w, N, s_nb, s_x0, stride_x0, s_a, s_b, stride_h, s_head, head_stride, run, wave4, tid & 63);
     } else {
-      const uint16_t* in = s_x0;
-      int stride_in = stride_x0;
-      uint16_t* out = s_a;
-      for (int l = 0; l < N.n_layers - 1; ++l) {
-        if (run) {
-          if constexpr (R16)
-            fused_layer16<kFEpiElu>(N.w[l], s_nb + N.bias_off[l], N.in_pad[l], N.out_pad[l], in, stride_in, out, stride_h,
-                                    nullptr, 0, 0, wave4);
-          else
-            fused_layer<RT, kFEpiElu>(N.w[l], s_nb + N.bias_off[l], N.in_pad[l], N.out_pad[l], in, stride_in, out, stride_h,
-                                      nullptr, 0, 0, nullptr, 0, wave4);
-        }
-        __syncthreads();
-        in = out;
-        stride_in = stride_h;
-        out = (out == s_a) ? s_b : s_a;
-      }
-      const int l = N.n_layers - 1;
-      if (run) {
-        if constexpr (R16)
-          fused_layer16<kFEpiHead>(N.w[l], s_nb + N.bias_off[l], N.in_pad[l], N.out_pad[l], in, stride_in, nullptr, 0,
-                                   s_head, head_stride, N.out_store, wave4);
-        else
-          fused_layer<RT, kFEpiHead>(N.w[l], s_nb + N.bias_off[l], N.in_pad[l], N.out_pad[l], in, stride_in, nullptr, 0,
-                                     s_head, head_stride, N.out_store, nullptr, 0, wave4);
-      }
-      __syncthreads();
+      if (t == a.T) break;
+      gmi_agent::net_layers<gmi_agent::Bf16, RT, kAhead, RT, true>(
+          a.policy, a.net[0].n_layers, wq, reinterpret_cast<const unsigned char*>(s_x0), reinterpret_cast<unsigned char*>(s_hid),
+          reinterpret_cast<unsigned char*>(s_hid + R * stride_h), nullptr, s_mu, A, wave8, tid & 63);
     }
     if (t == a.T) {
       if (tid < Rv && r0 + tid < a.n) a.last_value[r0 + tid] = s_val[tid];
@@ -726,7 +507,7 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
         }
         ep = d ? 0u : ep + 1u;
         a.b_done[slot0 + dtid] = (uint8_t)d;
-        a.b_val[slot0 + dtid] = s_val[dtid];
+        if constexpr (kStationary) a.b_val[slot0 + dtid] = s_val[dtid];
       }
       s_done[dtid] = d;
     }
@@ -832,12 +613,12 @@ size_t rollout_noise_bytes(const gmi_model* m, int R) {
 
 // Bytes of the hidden-activation space left over beside the next-state tile and the random draws while the
 // simulator runs.
-size_t rollout_stage_room(const gmi_model* m, int R) {
+size_t rollout_stage_room(const gmi_model* m, int R, int nets) {
   const ModelLayout& L = m->L;
   int max_h = 32;
   for (int l = 0; l < L.n_hidden; ++l) max_h = L.net[0][l].out_pad > max_h ? L.net[0][l].out_pad : max_h;
   const int o4 = (L.obs_dim + 3) & ~3;
-  const size_t hid = 4 * (size_t)R * (max_h + 8) * 2, used = (((size_t)R * o4 * 4 + 15) & ~(size_t)15) + rollout_noise_bytes(m, R);
+  const size_t hid = 2 * nets * (size_t)R * (max_h + 8) * 2, used = (((size_t)R * o4 * 4 + 15) & ~(size_t)15) + rollout_noise_bytes(m, R);
   return hid > used ? hid - used : 0;
 }
 
@@ -848,16 +629,16 @@ size_t rollout_ws_lds_bytes(const ModelLayout& L) {
   return 0;
 }
 
-size_t rollout_lds_bytes(const gmi_model* m, int R, bool mt_lds) {
+size_t rollout_lds_bytes(const gmi_model* m, int R, bool mt_lds, int nets) {
   const ModelLayout& L = m->L;
   int max_h = 32;
   for (int l = 0; l < L.n_hidden; ++l) max_h = L.net[0][l].out_pad > max_h ? L.net[0][l].out_pad : max_h;
   const int O = L.obs_dim, A = L.act_dim, o4 = (O + 3) & ~3;
-  const size_t hid = 4 * (size_t)R * (max_h + 8) * 2, used = (((size_t)R * o4 * 4 + 15) & ~(size_t)15) + rollout_noise_bytes(m, R);
+  const size_t hid = 2 * nets * (size_t)R * (max_h + 8) * 2, used = (((size_t)R * o4 * 4 + 15) & ~(size_t)15) + rollout_noise_bytes(m, R);
   const size_t region = ((hid > used ? hid : used) + 15) & ~(size_t)15;
   return (size_t)((R * (O + A) + 3) & ~3) * 4 + (size_t)R * (gmi::pad32(O) + 8) * 2 + region +
          (size_t)(R * (A + 1 + (A + 3) / 4 + o4 / 4) + ((R + 3) & ~3)) * 4 +
-         ((bias_floats(m, 0) + bias_floats(m, 1) + 3) & ~(size_t)3) * 4 +
+         (nets == 2 ? ((bias_floats(m, 0) + bias_floats(m, 1) + 3) & ~(size_t)3) * 4 : 0) +
          (mt_lds ? (size_t)(O + A) * o4 * 4 : 0) + rollout_ws_lds_bytes(L);
 }
 
@@ -890,17 +671,20 @@ extern "C" int rollout_collect(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_buffer
              "weights, limit %d); use agent_act / env_step / collect_experience", (long long)L.weight_bytes, 1 << 20);
   constexpr size_t kLdsMax = 160 * 1024;
   const int n = bd.n_envs;
+  const int nets = ws_matches<WsAnt>(L) || ws_matches<WsSmallObs>(L) ? 2 : 1;      // the streaming form runs the policy alone
   int R = 64;
-  if (rollout_lds_bytes(m, R, false) > kLdsMax || (n + 63) / 64 < g->cu_count) R = 32;
-  if (rollout_lds_bytes(m, R, false) > kLdsMax)
+  if (rollout_lds_bytes(m, R, false, 2) > kLdsMax || (n + 63) / 64 < g->cu_count) R = 32;
+  if (rollout_lds_bytes(m, R, false, 2) > kLdsMax)
     GMI_FAIL(GMI_ERR_UNSUPPORTED, "rollout_collect: a 32-env tile of this model needs %zu bytes of LDS (limit %zu); "
-             "use agent_act / env_step / collect_experience", rollout_lds_bytes(m, R, false), kLdsMax);
+             "use agent_act / env_step / collect_experience", rollout_lds_bytes(m, R, false, 2), kLdsMax);
   const size_t mt_bytes = (size_t)(L.obs_dim + L.act_dim) * ((L.obs_dim + 3) & ~3) * 4;
-  const bool mt_lds = rollout_lds_bytes(m, R, true) <= kLdsMax;
-  const int mt_mode = mt_lds ? 2 : (rollout_stage_room(m, R) >= mt_bytes ? 1 : 0);
+  const bool mt_lds = rollout_lds_bytes(m, R, true, nets) <= kLdsMax;
+  const int mt_mode = mt_lds ? 2 : (rollout_stage_room(m, R, nets) >= mt_bytes ? 1 : 0);
   RolloutArgs a;
   fill_net(m, 0, &a.net[0]);
   fill_net(m, 1, &a.net[1]);
+  for (int l = 0; l < L.n_layers; ++l)
+    a.policy[l] = {reinterpret_cast<const uint4*>(a.net[0].w[l]), a.net[0].bias[l], nullptr, L.net[0][l].in_pad, L.net[0][l].out_pad};
   a.log_std = reinterpret_cast<const float*>(m->shadow + L.sh_logstd);
   fill_rollout_env(m, env, b, obs, seed, step0, env_offset, last_value, &a);
   a.obs_pad = gmi::pad32(L.obs_dim);
@@ -908,7 +692,7 @@ extern "C" int rollout_collect(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_buffer
   for (int l = 0; l < L.n_hidden; ++l) a.max_h = L.net[0][l].out_pad > a.max_h ? L.net[0][l].out_pad : a.max_h;
   a.mt_lds = mt_mode;
   a.obs_vec = (L.obs_dim % 4 == 0 && (L.obs_dim + L.act_dim) % 4 == 0 && ((uintptr_t)bd.obs & 15) == 0) ? 1 : 0;
-  size_t lds = rollout_lds_bytes(m, R, mt_lds);
+  size_t lds = rollout_lds_bytes(m, R, mt_lds, nets);
   // fewer 32-env tiles than compute units: 16 envs per workgroup use twice as many of them
   const int rows_per_wg = (R == 32 && (n + 31) / 32 < g->cu_count && n > 16) ? 16 : R;
   a.rows_per_wg = rows_per_wg;
@@ -933,8 +717,7 @@ extern "C" int rollout_collect(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_buffer
   // 16 envs per workgroup: the weight-stationary nets on 16-row products
   if (rows_per_wg == 16 && variant == 2) { kfn = rollout_fused_kernel<1, WsAnt, true>; variant = 6; }
   else if (rows_per_wg == 16 && variant == 4) { kfn = rollout_fused_kernel<1, WsSmallObs, true>; variant = 7; }
-  else if (rows_per_wg == 16 && variant == 0) { kfn = rollout_fused_kernel<1, void, true>; variant = 8; }
-  static bool attr_set[9] = {false, false, false, false, false, false, false, false, false};
+  static bool attr_set[8] = {false, false, false, false, false, false, false, false};
   if (!attr_set[variant]) {
     GMI_HIP(hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
     attr_set[variant] = true;
@@ -946,8 +729,11 @@ extern "C" int rollout_collect(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_buffer
   if (per_cu < 1) per_cu = 1;
   const int64_t resident = (int64_t)per_cu * g->cu_count;
   const int grid = (int)(a.n_tiles < resident ? a.n_tiles : resident);
-  gmi::ProfScope ps(g, gmi::kClsFusedRollout);
-  ps.launch(kfn, dim3(grid), dim3(512), lds, a);
-  GMI_LAUNCH_CHECK();
-  return GMI_OK;
+  {
+    gmi::ProfScope ps(g, gmi::kClsFusedRollout);
+    ps.launch(kfn, dim3(grid), dim3(512), lds, a);
+    GMI_LAUNCH_CHECK();
+  }
+  // the simulator needs no values: the streaming form leaves them to one pass over all slots and the final states
+  return nets == 2 ? GMI_OK : gmi::launch_values(g, m, bd.obs, bd.horizon, n, bd.ld_envs, bd.val, obs, last_value);
 }

@@ -287,6 +287,9 @@ int forward_nets(gmi_instance* g, gmi_model* m, int rows, bool policy, bool valu
 
 int launch_agent(gmi_instance* g, gmi_model* m, const float* obs, int n, uint64_t seed, uint32_t step,
                  uint32_t env_offset, float* act, float* logp, float* value, float* mu_out, bool do_policy);
+// Values of T slots of n rows each (ld rows apart) and of one more array of n rows, in one launch (bf16 models).
+int launch_values(gmi_instance* g, gmi_model* m, const float* obs, int T, int n, int64_t ld, float* value, const float* obs_last,
+                  float* value_last);
 
 // The fp32 one-launch kernels (f32.hip); GMI_ERR_UNSUPPORTED (no message) where a 16-row tile does not fit LDS.
 int launch_agent_f32(gmi_instance* g, gmi_model* m, const float* obs, int n, uint64_t seed, uint32_t step,
