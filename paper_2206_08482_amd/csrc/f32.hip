@@ -657,14 +657,8 @@ __global__ __launch_bounds__(kNT) void rollout_f32_kernel(RolloutF32Args a) {
       // the next step's draws, last threads first (the simulator's items go to the first ones)
       if (t + 1 < a.T)
         draw_items(a, s_noise2 + ((t + 1) & 1) * R * npr, step + 1u, R, r0, npr, nba, nbo, kNT - 1 - tid, kNT);
-      const bool four = (R / 4) * nbo >= 192;
-      if (a.mt_lds) {
-        if (four) sim_items<4>(a, R, r0, step, s_in, mt_lds_ptr, s_part, s_next, s_done, s_noise, npr, nba);
-        else sim_items<1>(a, R, r0, step, s_in, mt_lds_ptr, s_part, s_next, s_done, s_noise, npr, nba);
-      } else {
-        if (four) sim_items<4>(a, R, r0, step, s_in, mt_glb_ptr, s_part, s_next, s_done, s_noise, npr, nba);
-        else sim_items<1>(a, R, r0, step, s_in, mt_glb_ptr, s_part, s_next, s_done, s_noise, npr, nba);
-      }
+      if (a.mt_lds) sim_step<false>(R, nbo, a, r0, step, s_in, O + A, mt_lds_ptr, s_part, s_next, s_done, s_noise, npr, nba);
+      else sim_step<false>(R, nbo, a, r0, step, s_in, O + A, mt_glb_ptr, s_part, s_next, s_done, s_noise, npr, nba);
       __syncthreads();
       if (dtid >= 0 && dtid < R && r0 + dtid < a.n) {
         float sum = 0.f;

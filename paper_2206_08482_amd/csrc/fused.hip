@@ -324,7 +324,7 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
   constexpr int R = RT * 32;
   constexpr int NT = 512;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  const int O = a.obs_dim, A = a.act_dim, OA = O + A, o4 = a.o4, nbo = o4 >> 2, nba = (A + 3) >> 2;
+  const int O = a.obs_dim, A = a.act_dim, OA = O + A, OS = (OA + 3) & ~3, o4 = a.o4, nbo = o4 >> 2, nba = (A + 3) >> 2;
   const int stride_x0 = a.obs_pad + 8, stride_h = a.max_h + 8;
   // hidden activations (bf16, ping-pong, one pair per net) share their space with the next-state tile
   // (after the nets: next-state tile, then this step's random draws, then the staged simulator matrix)
@@ -334,8 +334,8 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
   const size_t hid_bytes = 2 * kNets * (size_t)R * stride_h * 2, next_bytes = ((size_t)R * o4 * 4 + 15) & ~(size_t)15;
   const size_t noise_bytes = (size_t)R * npr * 16;
   const size_t region = ((hid_bytes > next_bytes + noise_bytes ? hid_bytes : next_bytes + noise_bytes) + 15) & ~(size_t)15;
-  float* s_in = reinterpret_cast<float*>(smem_raw);                                  // [R][O + A] state | action
-  uint16_t* s_x0 = reinterpret_cast<uint16_t*>(s_in + ((R * OA + 3) & ~3));          // [R][obs_pad + 8]
+  float* s_in = reinterpret_cast<float*>(smem_raw);                                  // [R][OS] state | action
+  uint16_t* s_x0 = reinterpret_cast<uint16_t*>(s_in + R * OS);          // [R][obs_pad + 8]
   unsigned char* s_reg = reinterpret_cast<unsigned char*>(s_x0 + R * stride_x0);
   uint16_t* s_hid = reinterpret_cast<uint16_t*>(s_reg);                              // [2 nets][2][R][stride_h]
   float* s_next = reinterpret_cast<float*>(s_reg);                                   // [R][o4]
@@ -358,8 +358,8 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
   // Rv <= R envs are owned by this workgroup (a half-filled tile doubles the workgroups of a small batch);
   // rows Rv..R-1 of the tile go through the matrix products but are never read or stored
   const int Rv = a.rows_per_wg;
-  // first thread of the first wave without a simulator item (rollout_sim_threads on the host)
-  const int ahead_tid0 = ((((Rv / 4) * nbo >= 192 ? (Rv / 4) * nbo : Rv * nbo) + 63) & ~63);
+  // first thread of the first wave without a simulator item
+  const int ahead_tid0 = sim_threads(Rv, nbo);
   // the observation stores go to the waves without action items when those are at least half of the workgroup
   // (in the simulator phase the idle waves have no time to spare: measured, the next step's draws fill it)
   const int act_waves_end = (Rv * nba * 4 + 63) & ~63;
@@ -408,7 +408,7 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
   const int r0 = tile * Rv;
   for (int idx = tid; idx < Rv * O; idx += NT) {
     const int r = idx / O, k = idx - r * O;
-    s_in[r * OA + k] = (r0 + r < a.n) ? a.obs_state[(int64_t)(r0 + r) * O + k] : 0.f;
+    s_in[r * OS + k] = (r0 + r < a.n) ? a.obs_state[(int64_t)(r0 + r) * O + k] : 0.f;
   }
   // thread NT - 64 + r (r < Rv; the last wave, which has no action items and gets an observation-store item last of
   // all: on the fifth wave the done flags came after an observation store and that wave ended the sampling phase
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
   // the nets' bf16 copy of the state, zero padded; every later step refreshes it together with the state itself
   for (int idx = tid; idx < Rv * a.obs_pad; idx += NT) {
     const int r = idx / a.obs_pad, k = idx - r * a.obs_pad;
-    const float v = k < O ? s_in[r * OA + k] : 0.f;
+    const float v = k < O ? s_in[r * OS + k] : 0.f;
     s_x0[r * stride_x0 + k] = (uint16_t)(pack_bf16(v, 0.f) & 0xFFFFu);
   }
   __syncthreads();
@@ -472,7 +472,7 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
           a.b_act[(slot0 + r) * A + j] = act;
           term = -0.5f * z * z - ls - 0.918938533204672742f;
         }
-        s_in[r * OA + O + j] = act;
+        s_in[r * OS + O + j] = act;
       }
       float lp = term;
       lp += __shfl_down(term, 1, 64);
@@ -486,13 +486,13 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
         const int o4n = O >> 2;
         for (int idx = tid - obs_tid0; idx < Rv * o4n; idx += NT - obs_tid0) {
           const int r = idx / o4n, c = idx - r * o4n;
-          const float4 v = *reinterpret_cast<const float4*>(s_in + r * OA + 4 * c);
+          const float4 v = *reinterpret_cast<const float4*>(s_in + r * OS + 4 * c);
           if (r0 + r < a.n) *reinterpret_cast<float4*>(a.b_obs + (slot0 + r) * O + 4 * c) = v;
         }
       } else {
         for (int idx = tid - obs_tid0; idx < Rv * O; idx += NT - obs_tid0) {
           const int r = idx / O, k = idx - r * O;
-          if (r0 + r < a.n) a.b_obs[(slot0 + r) * O + k] = s_in[r * OA + k];
+          if (r0 + r < a.n) a.b_obs[(slot0 + r) * O + k] = s_in[r * OS + k];
         }
       }
     }
@@ -526,13 +526,8 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
     // the next step's draws, by the waves that have no simulator item
     if (a.noise_ahead && t + 1 < a.T && tid >= ahead_tid0)
       draw_items(a, s_ahead + (size_t)((t + 1) & 1) * Rv * npr, step + 1u, Rv, r0, npr, nba, nbo, tid - ahead_tid0, NT - ahead_tid0);
-    if (a.mt_lds != 0) {
-      if ((Rv / 4) * nbo >= 192) sim_items<4>(a, Rv, r0, step, s_in, mt_lds_ptr, s_part, s_next, s_done, s_noise, npr, nba);
-      else sim_items<1>(a, Rv, r0, step, s_in, mt_lds_ptr, s_part, s_next, s_done, s_noise, npr, nba);
-    } else {
-      if ((Rv / 4) * nbo >= 192) sim_items<4>(a, Rv, r0, step, s_in, mt_glb_ptr, s_part, s_next, s_done, s_noise, npr, nba);
-      else sim_items<1>(a, Rv, r0, step, s_in, mt_glb_ptr, s_part, s_next, s_done, s_noise, npr, nba);
-    }
+    if (a.mt_lds != 0) sim_step<true>(Rv, nbo, a, r0, step, s_in, OS, mt_lds_ptr, s_part, s_next, s_done, s_noise, npr, nba);
+    else sim_step<true>(Rv, nbo, a, r0, step, s_in, OS, mt_glb_ptr, s_part, s_next, s_done, s_noise, npr, nba);
     __syncthreads();
     // the reward on the last wave (the state update below starts with the first threads)
     const int rt = tid - (NT - 64);
@@ -553,20 +548,20 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
     }
     // the new state, in fp32 for the simulator and the stores and in bf16 for the next step's nets (one pass and
     // one barrier instead of two)
-    if (a.obs_vec) {            // four elements per thread (O, O + A and the padded width are multiples of 4)
+    if (a.obs_vec) {            // four elements per thread (O, the row stride and the padded width are multiples of 4)
       const int p4 = a.obs_pad >> 2;
       for (int idx = tid; idx < Rv * p4; idx += NT) {
         const int r = idx / p4, k = 4 * (idx - r * p4);
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (k < O && r0 + r < a.n) v = *reinterpret_cast<const float4*>(s_next + r * o4 + k);
-        if (k < O) *reinterpret_cast<float4*>(s_in + r * OA + k) = v;
+        if (k < O) *reinterpret_cast<float4*>(s_in + r * OS + k) = v;
         *reinterpret_cast<uint2*>(s_x0 + r * stride_x0 + k) = make_uint2(pack_bf16(v.x, v.y), pack_bf16(v.z, v.w));
       }
     } else {
       for (int idx = tid; idx < Rv * a.obs_pad; idx += NT) {
         const int r = idx / a.obs_pad, k = idx - r * a.obs_pad;
         const float v = (k < O && r0 + r < a.n) ? s_next[r * o4 + k] : 0.f;
-        if (k < O) s_in[r * OA + k] = v;
+        if (k < O) s_in[r * OS + k] = v;
         s_x0[r * stride_x0 + k] = (uint16_t)(pack_bf16(v, 0.f) & 0xFFFFu);
       }
     }
@@ -575,7 +570,7 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
   // the loop ends right after the bootstrap value; s_in still holds the final state
   for (int idx = tid; idx < Rv * O; idx += NT) {
     const int r = idx / O, k = idx - r * O;
-    if (r0 + r < a.n) a.obs_state[(int64_t)(r0 + r) * O + k] = s_in[r * OA + k];
+    if (r0 + r < a.n) a.obs_state[(int64_t)(r0 + r) * O + k] = s_in[r * OS + k];
   }
   if (dtid >= 0 && dtid < Rv && r0 + dtid < a.n) a.episode_step[r0 + dtid] = ep;
   __syncthreads();                                   // the next tile overwrites the state rows
@@ -636,7 +631,7 @@ size_t rollout_lds_bytes(const gmi_model* m, int R, bool mt_lds, int nets) {
   const int O = L.obs_dim, A = L.act_dim, o4 = (O + 3) & ~3;
   const size_t hid = 2 * nets * (size_t)R * (max_h + 8) * 2, used = (((size_t)R * o4 * 4 + 15) & ~(size_t)15) + rollout_noise_bytes(m, R);
   const size_t region = ((hid > used ? hid : used) + 15) & ~(size_t)15;
-  return (size_t)((R * (O + A) + 3) & ~3) * 4 + (size_t)R * (gmi::pad32(O) + 8) * 2 + region +
+  return (size_t)R * ((O + A + 3) & ~3) * 4 + (size_t)R * (gmi::pad32(O) + 8) * 2 + region +
          (size_t)(R * (A + 1 + (A + 3) / 4 + o4 / 4) + ((R + 3) & ~3)) * 4 +
          (nets == 2 ? ((bias_floats(m, 0) + bias_floats(m, 1) + 3) & ~(size_t)3) * 4 : 0) +
          (mt_lds ? (size_t)(O + A) * o4 * 4 : 0) + rollout_ws_lds_bytes(L);
@@ -691,19 +686,18 @@ extern "C" int rollout_collect(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_buffer
   a.max_h = 32;
   for (int l = 0; l < L.n_hidden; ++l) a.max_h = L.net[0][l].out_pad > a.max_h ? L.net[0][l].out_pad : a.max_h;
   a.mt_lds = mt_mode;
-  a.obs_vec = (L.obs_dim % 4 == 0 && (L.obs_dim + L.act_dim) % 4 == 0 && ((uintptr_t)bd.obs & 15) == 0) ? 1 : 0;
+  a.obs_vec = (L.obs_dim % 4 == 0 && ((uintptr_t)bd.obs & 15) == 0) ? 1 : 0;
   size_t lds = rollout_lds_bytes(m, R, mt_lds, nets);
   // fewer 32-env tiles than compute units: 16 envs per workgroup use twice as many of them
   const int rows_per_wg = (R == 32 && (n + 31) / 32 < g->cu_count && n > 16) ? 16 : R;
   a.rows_per_wg = rows_per_wg;
-  // Draws one step ahead: when the simulator's items leave enough whole waves idle to make a step's draws in two
+  // Draws one step ahead: when the simulator's items leave enough whole waves idle to make a step's draws in three
   // rounds at most, and two buffers of them still fit
   {
     const int nbo = a.o4 / 4, nba = (L.act_dim + 3) / 4, npr = nba + nbo + 1;
-    const int sim_items = (rows_per_wg / 4) * nbo >= 192 ? (rows_per_wg / 4) * nbo : rows_per_wg * nbo;
-    const int idle = 512 - ((sim_items + 63) & ~63);
+    const int idle = 512 - sim_threads(rows_per_wg, nbo);
     const size_t off = (lds + 15) & ~(size_t)15, need = off + 2 * (size_t)rows_per_wg * npr * 16;
-    a.noise_ahead = (idle > 0 && idle * 2 >= rows_per_wg * npr && need <= kLdsMax) ? 1 : 0;
+    a.noise_ahead = (idle > 0 && idle * 3 >= rows_per_wg * npr && need <= kLdsMax) ? 1 : 0;
     a.ahead_off = (int)off;
     if (a.noise_ahead) lds = need;
   }

@@ -24,16 +24,23 @@ struct RolloutEnv {
   float* last_value;
 };
 
+// Envs per simulator item, and the threads that get an item.  An item reads 16 bytes of the matrix and 4 bytes per env for
+// its 4 EPT products of a k, so the LDS bounds many items of one env: 16 envs of 108 + 21 elements (432 items) take 18.0 us
+// a step with one, 15.7 with two and the next draws beside them.  Up to one wave per SIMD the chain of a wave's own reads
+// is the bound and items of one env are the faster ones (16 envs of 60 + 8: 7.4 against 8.5 us a step).
+__host__ __device__ __forceinline__ int sim_ept(int R, int nbo) { return (R / 4) * nbo >= 192 ? 4 : R * nbo > 256 ? 2 : 1; }
+__host__ __device__ __forceinline__ int sim_threads(int R, int nbo) { return ((R / sim_ept(R, nbo)) * nbo + 63) & ~63; }
+
 // Simulator step for the tile: items (group of EPT envs, block of 4 state elements).  mt points at the
-// transposed matrices (LDS copy or global), row stride nbo float4.
-template <int EPT>
-__device__ __forceinline__ void sim_items(const RolloutEnv& a, int R, int r0, uint32_t step, const float* s_in,
+// transposed matrices (LDS copy or global), row stride nbo float4; ld: floats between the rows of s_in, VEC: a multiple of 4.
+template <int EPT, bool VEC>
+__device__ __forceinline__ void sim_items(const RolloutEnv& a, int R, int r0, uint32_t step, const float* s_in, int ld,
                                           const float4* mt, float* s_part, float* s_next, const int* s_done,
                                           const float4* s_noise, int npr, int nba) {
   const int O = a.obs_dim, A = a.act_dim, OA = O + A, o4 = a.o4, nbo = o4 >> 2;
   for (int item = threadIdx.x; item < (R / EPT) * nbo; item += blockDim.x) {
     const int g = item / nbo, b = item - g * nbo;
-    const float* xin = s_in + (g * EPT) * OA;
+    const float* xin = s_in + (g * EPT) * ld;
     const float4* mrow = mt + b;
     float acc[EPT][4];
 #pragma unroll
@@ -48,10 +55,20 @@ __device__ __forceinline__ void sim_items(const RolloutEnv& a, int R, int r0, ui
       float xv[EPT][8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) m[u] = mrow[(k + u) * nbo];
+      if constexpr (VEC) {
 #pragma unroll
-      for (int i = 0; i < EPT; ++i)
+        for (int i = 0; i < EPT; ++i)
 #pragma unroll
-        for (int u = 0; u < 8; ++u) xv[i][u] = xin[i * OA + k + u];
+          for (int u = 0; u < 8; u += 4) {
+            const float4 v = *reinterpret_cast<const float4*>(xin + i * ld + k + u);
+            xv[i][u] = v.x; xv[i][u + 1] = v.y; xv[i][u + 2] = v.z; xv[i][u + 3] = v.w;
+          }
+      } else {
+#pragma unroll
+        for (int i = 0; i < EPT; ++i)
+#pragma unroll
+          for (int u = 0; u < 8; ++u) xv[i][u] = xin[i * ld + k + u];
+      }
 #pragma unroll
       for (int u = 0; u < 8; ++u)
 #pragma unroll
@@ -66,7 +83,7 @@ __device__ __forceinline__ void sim_items(const RolloutEnv& a, int R, int r0, ui
       const float4 m = mrow[k * nbo];
 #pragma unroll
       for (int i = 0; i < EPT; ++i) {
-        const float x = xin[i * OA + k];
+        const float x = xin[i * ld + k];
         acc[i][0] = fmaf(x, m.x, acc[i][0]);
         acc[i][1] = fmaf(x, m.y, acc[i][1]);
         acc[i][2] = fmaf(x, m.z, acc[i][2]);
@@ -80,9 +97,9 @@ __device__ __forceinline__ void sim_items(const RolloutEnv& a, int R, int r0, ui
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int o = 4 * b + j;
-        if (o < O) { const float x = xin[i * OA + o]; ps = fmaf(x, x, ps); }
+        if (o < O) { const float x = xin[i * ld + o]; ps = fmaf(x, x, ps); }
       }
-      for (int q = b; q < A; q += nbo) { const float x = xin[i * OA + O + q]; pa = fmaf(x, x, pa); }
+      for (int q = b; q < A; q += nbo) { const float x = xin[i * ld + O + q]; pa = fmaf(x, x, pa); }
       s_part[r * nbo + b] = ps + 0.01f * pa;
       const int e = r0 + r;
       float z[4] = {0.f, 0.f, 0.f, 0.f};
@@ -100,6 +117,14 @@ __device__ __forceinline__ void sim_items(const RolloutEnv& a, int R, int r0, ui
       *reinterpret_cast<float4*>(&s_next[r * o4 + 4 * b]) = make_float4(outv[0], outv[1], outv[2], outv[3]);
     }
   }
+}
+
+template <bool VEC, typename... Args>
+__device__ __forceinline__ void sim_step(int R, int nbo, const RolloutEnv& a, Args... args) {
+  const int ept = sim_ept(R, nbo);
+  if (ept == 4) sim_items<4, VEC>(a, R, args...);
+  else if (ept == 2) sim_items<2, VEC>(a, R, args...);
+  else sim_items<1, VEC>(a, R, args...);
 }
 
 // Random blocks first, first + stride, ... of one step of a tile, one float4 per (env, block): nba action-noise
