@@ -1,7 +1,7 @@
 // The agent's action decision in one launch (Section 3 of the paper, "DRL Agent"), bf16 and fp8 (E4M3): observation
 // conversion, every layer of one net, and the Gaussian sampling epilogue.
 //
-// A workgroup of 8 waves owns R = 32 RT rows of ONE net (grid: row tiles x nets).  The two nets meet nowhere: action and
+// A workgroup of 8 (16) waves owns R = 32 RT rows of ONE net (grid: row tiles x nets).  The two nets meet nowhere: action and
 // log-density need the policy net, the value needs the value net.  Activations are row-major [row][feature] in LDS (rows
 // 16 bytes longer than their features: an odd number of 16-byte pieces, so that operand reads of consecutive rows hit
 // different banks); layer l reads buffer l % 2 and writes the other one.  Products are computed transposed (weights first
@@ -24,7 +24,6 @@
 namespace gmi_agent {
 using namespace gmi_chain;
 
-constexpr int kNT = 512, kNW = 8;
 constexpr int kMaxLayers = GMI_MAX_HIDDEN + 1;
 constexpr size_t kLdsMax = 160 * 1024;
 typedef int intx8 __attribute__((ext_vector_type(8)));
@@ -137,17 +136,16 @@ __device__ __forceinline__ void k_loop(floatx16 (&acc)[NRT], Ring<P, D>& wq, con
 }
 
 // Row tiles of an item of a product with nft feature tiles: as many (at most MT) as still leave every wave an item.
-template <int RT, int MT>
+template <int RT, int MT, int NW>
 __device__ __forceinline__ int item_tiles(int nft) {
-  if (MT >= 4 && nft * (RT / 4) >= kNW) return 4;
-  return MT >= 2 && nft * (RT / 2) >= kNW ? 2 : 1;
+  return MT >= 2 && nft * (RT / 2) >= NW ? 2 : 1;
 }
 
 // Requests the first weight blocks of an item of layer L.
-template <class P, int RT, int D, int MT>
+template <class P, int RT, int D, int MT, int NW>
 __device__ __forceinline__ void request(Ring<P, D>& wq, const AgentLayer& L, int item, int lane) {
   const int nft = L.F >> 5, nks = L.K * P::size / (32 * P::pieces);
-  const int ft = min(item / (RT / item_tiles<RT, MT>(nft)), nft - 1);
+  const int ft = min(item / (RT / item_tiles<RT, MT, NW>(nft)), nft - 1);
   const uint4* wp = L.w + (int64_t)ft * nks * 64 * P::pieces + lane;
 #pragma unroll
   for (int u = 0; u < D; ++u)
@@ -158,7 +156,7 @@ __device__ __forceinline__ void request(Ring<P, D>& wq, const AgentLayer& L, int
 // All layers of a net on the workgroup's 32 RT rows.  Layer 0 reads the rows at x0; odd layers read ya, even ones yb (which
 // may be x0); a row of a layer's input takes K * P::size + 16 bytes.  The head's results go to s_head [row][ho].  wq holds
 // the first blocks of layer 0 for item `wave`; AGAIN: so it does afterwards, for the next pass.  Ends with a barrier.
-template <class P, int RT, int D, int MT, bool AGAIN>
+template <class P, int RT, int D, int MT, int NW, bool AGAIN>
 __device__ __forceinline__ void net_layers(const AgentLayer* N, int nl, Ring<P, D>& wq, const unsigned char* x0, unsigned char* ya,
                                            unsigned char* yb, const float* s_bias, float* s_head, int ho, int wave, int lane) {
   constexpr int B = 32 * P::pieces;
@@ -178,7 +176,7 @@ __device__ __forceinline__ void net_layers(const AgentLayer* N, int nl, Ring<P, 
       constexpr int NRT = decltype(nrt)::value;
       constexpr int nrg = RT / NRT;
       const int n_items = nft * nrg;
-      for (int item = wave; item < n_items; item += kNW) {
+      for (int item = wave; item < n_items; item += NW) {
         const int ft = item / nrg, rg = item % nrg;
         float4 b4[4];
         if constexpr (!P::bias_lds)
@@ -190,8 +188,8 @@ __device__ __forceinline__ void net_layers(const AgentLayer* N, int nl, Ring<P, 
 #pragma unroll
           for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
         k_loop<P, D, NRT>(acc, wq, L.w + (int64_t)ft * nks * 64 * P::pieces + lane, nks, x + (rg * NRT * 32 + s) * sx + B / 2 * h, 32 * sx);
-        if (item + kNW < n_items) request<P, RT, D, MT>(wq, L, item + kNW, lane);
-        else if (more) request<P, RT, D, MT>(wq, Ln, wave, lane);
+        if (item + NW < n_items) request<P, RT, D, MT, NW>(wq, L, item + NW, lane);
+        else if (more) request<P, RT, D, MT, NW>(wq, Ln, wave, lane);
         // lane (s, h) holds, per quad q, the features 32 ft + 8 q + 4 h + 0..3 of row s
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -219,21 +217,20 @@ __device__ __forceinline__ void net_layers(const AgentLayer* N, int nl, Ring<P, 
           }
         }
       }
-      if (wave >= n_items && more) request<P, RT, D, MT>(wq, Ln, wave, lane);
+      if (wave >= n_items && more) request<P, RT, D, MT, NW>(wq, Ln, wave, lane);
     };
-    const int nrt = item_tiles<RT, MT>(nft);
+    const int nrt = item_tiles<RT, MT, NW>(nft);
     if (nrt == 1) items(std::integral_constant<int, 1>{});
     if constexpr (MT >= 2) if (nrt == 2) items(std::integral_constant<int, 2>{});
-    if constexpr (MT >= 4) if (nrt == 4) items(std::integral_constant<int, 4>{});
     bias += L.F;
     __syncthreads();
   }
 }
 
-// D: weight blocks in flight per wave; MT: most row tiles of an item; WPS: waves per SIMD (registers).
-template <class P, int RT, int D, int MT, int WPS>
-__global__ __launch_bounds__(kNT, WPS) void agent_kernel(AgentArgs a) {
-  constexpr int R = 32 * RT;
+// D: weight blocks in flight per wave; MT: most row tiles of an item; WPS: waves per SIMD (registers); NW: waves.
+template <class P, int RT, int D, int MT, int WPS, int NW>
+__global__ __launch_bounds__(64 * NW, WPS) void agent_kernel(AgentArgs a) {
+  constexpr int R = 32 * RT, kNT = 64 * NW;
   extern __shared__ __attribute__((aligned(16))) unsigned char s_x[];
   const int net = a.net0 + blockIdx.y;
   const AgentLayer* N = a.l[net];
@@ -288,7 +285,7 @@ __global__ __launch_bounds__(kNT, WPS) void agent_kernel(AgentArgs a) {
     }
     for (int e = rows * (S0 >> 4) + tid; e < R * (S0 >> 4); e += kNT) reinterpret_cast<uint4*>(s_x)[e] = make_uint4(0u, 0u, 0u, 0u);
   }
-  request<P, RT, D, MT>(wq, N[0], wave, lane);
+  request<P, RT, D, MT, NW>(wq, N[0], wave, lane);
   if constexpr (P::bias_lds) {
 #pragma unroll
     for (int u = 0; u < 4; ++u)
@@ -304,7 +301,7 @@ __global__ __launch_bounds__(kNT, WPS) void agent_kernel(AgentArgs a) {
     }
   __syncthreads();
 
-  net_layers<P, RT, D, MT, false>(N, nl, wq, s_x, s_x + a.y_off, s_x, s_bias, s_head, ho, wave, lane);
+  net_layers<P, RT, D, MT, NW, false>(N, nl, wq, s_x, s_x + a.y_off, s_x, s_bias, s_head, ho, wave, lane);
 
   if (net == 1) {
     const int t = blockIdx.z;
@@ -358,16 +355,16 @@ size_t agent_lds(AgentArgs& a, int rt, bool sample) {
   return (size_t)a.f_off + (size_t)32 * rt * ((sample ? (a.A + 3) / 4 * 16 : 0) + a.A * 4) + (size_t)a.bias_floats * 4;
 }
 
-template <class P, int RT, int D, int MT, int WPS>
+template <class P, int RT, int D, int MT, int WPS, int NW = 8>
 int launch(gmi_instance* g, AgentArgs& a, int nets, bool sample) {
   const size_t lds = agent_lds<P>(a, RT, sample);
   static bool attr = false;
   if (!attr) {
-    GMI_HIP(hipFuncSetAttribute((const void*)agent_kernel<P, RT, D, MT, WPS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
+    GMI_HIP(hipFuncSetAttribute((const void*)agent_kernel<P, RT, D, MT, WPS, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
     attr = true;
   }
   gmi::ProfScope ps(g, gmi::kClsFusedAgent);
-  ps.launch(agent_kernel<P, RT, D, MT, WPS>, dim3((a.n + 32 * RT - 1) / (32 * RT), nets, a.T + (a.value_last ? 1 : 0)), dim3(kNT), lds, a);
+  ps.launch(agent_kernel<P, RT, D, MT, WPS, NW>, dim3((a.n + 32 * RT - 1) / (32 * RT), nets, a.T + (a.value_last ? 1 : 0)), dim3(64 * NW), lds, a);
   GMI_LAUNCH_CHECK();
   return GMI_OK;
 }

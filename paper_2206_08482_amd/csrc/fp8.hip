@@ -231,14 +231,15 @@ extern "C" int agent_act_fp8(gmi_t g, gmi_fp8_t w, const float* obs, int32_t n_r
   //   128 where two such tiles fit a compute unit and there are enough of them: 32768 rows of 60:256:128:64:8 31 / 24 / 19
   //   (16384 rows: 18 / 14 / 14), 262144: 220 / 156 / 112;
   //   64 where two of those fit: 65536 rows of 108:400:200:100:21 87 / 72 / 81;
-  //   128 with all of the registers where one tile fills a compute unit: 65536 rows of 211:512:512:256:128:20 154 / 167 / 141.
+  //   128 on 16 waves where one tile fills a compute unit: 65536 rows of 211:512:512:256:128:20 154 / 167 / 134 (on 8 waves
+  //   with twice the registers 141), 16384 rows 44 / 48 / 37.
   const int64_t slots = 2 * (int64_t)g->cu_count;
   auto groups = [&](int rt) { return (int64_t)((n_rows + 32 * rt - 1) / (32 * rt)) * 2; };
   auto per_cu = [&](int rt) { return (int)(kLdsMax / agent_lds<Fp8>(a, rt, sample)); };
   int rc;
   if (groups(1) > slots && per_cu(4) >= 2 && groups(4) >= slots) rc = launch<Fp8, 4, 2, 2, 4>(g, a, 2, sample);
   else if (groups(1) > slots && per_cu(2) >= 2) rc = launch<Fp8, 2, 2, 2, 4>(g, a, 2, sample);
-  else if (per_cu(4) >= 1 && 2 * groups(4) > slots) rc = launch<Fp8, 4, 4, 4, 2>(g, a, 2, sample);
+  else if (per_cu(4) >= 1 && 2 * groups(4) >= slots) rc = launch<Fp8, 4, 2, 2, 4, 16>(g, a, 2, sample);
   else rc = launch<Fp8, 1, 4, 1, 4>(g, a, 2, sample);
   if (rc != GMI_OK || sample) return rc;
   return gmi::launch_sample(g, mu_ws, a.log_std, n_rows, L.act_dim, seed, step, env_offset, act, logp, mu);

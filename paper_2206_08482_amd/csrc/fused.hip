@@ -399,7 +399,7 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
   constexpr int kAhead = RT == 1 ? 8 : 4;
   gmi_agent::Ring<gmi_agent::Bf16, kAhead> wq;
   const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if constexpr (!kStationary) gmi_agent::request<gmi_agent::Bf16, RT, kAhead, RT>(wq, a.policy[0], wave8, tid & 63);
+  if constexpr (!kStationary) gmi_agent::request<gmi_agent::Bf16, RT, kAhead, RT, 8>(wq, a.policy[0], wave8, tid & 63);
 
   // The grid never exceeds what the instance's compute units hold at once: a workgroup takes the tiles
   // blockIdx.x, blockIdx.x + gridDim.x, ... one after the other, each through all T steps.  (Workgroups
@@ -436,7 +436,7 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
         ws_net<WS, 0, RT>(wreg, s_w, N, s_nb, s_x0, stride_x0, s_a, s_b, stride_h, s_head, head_stride, run, wave4, tid & 63);
     } else {
       if (t == a.T) break;
-      gmi_agent::net_layers<gmi_agent::Bf16, RT, kAhead, RT, true>(
+      gmi_agent::net_layers<gmi_agent::Bf16, RT, kAhead, RT, 8, true>(
           a.policy, a.net[0].n_layers, wq, reinterpret_cast<const unsigned char*>(s_x0), reinterpret_cast<unsigned char*>(s_hid),
           reinterpret_cast<unsigned char*>(s_hid + R * stride_h), nullptr, s_mu, A, wave8, tid & 63);
     }

@@ -122,7 +122,7 @@ def test_agent_kernel_matches_the_per_layer_path(g, inst, obs, act, hidden, n, s
 
 
 @pytest.mark.parametrize("obs,act,hidden,n", [
-    (211, 20, [512, 512, 256, 128], 32769),   # 128 rows with all registers
+    (211, 20, [512, 512, 256, 128], 32769),   # 128 rows on 16 waves
     (60, 8, [256, 128, 64], 32801),           # two 128-row tiles per compute unit
     (107, 21, [400, 200, 100], 8225),         # two 64-row tiles; rows of an odd length
     (45, 300, [100], 65),                     # a head of ten feature tiles
