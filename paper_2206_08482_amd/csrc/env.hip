@@ -27,20 +27,54 @@ __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {      // roun
   return (a >> 16) | (b & 0xFFFF0000u);
 }
 
+// State (ACT: and action) of the envs env0 .. env0 + EB - 1 into LDS rows OS floats apart (zeros past the
+// last env), eight loads at a time; the state also into copy [N, O] if given.
+template <bool ACT>
+__device__ __forceinline__ void stage_inputs(const float* __restrict__ obs, const float* __restrict__ act, float* __restrict__ copy,
+                                             int env0, int EB, int N, int O, int A, float* dst, int OS, int tid) {
+  const int W = ACT ? O + A : O, n = EB * W;
+  const int dk = 256 % W, de = 256 / W;
+  int e = tid / W, k = tid - e * W;
+  for (int i0 = tid; i0 < n; i0 += 8 * 256) {
+    float v[8];
+    int es = e, ks = k;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int64_t env = min(env0 + e, N - 1);
+      if constexpr (ACT) v[u] = *(k < O ? obs + env * O + k : act + env * A + (k - O));
+      else v[u] = obs[env * O + k];
+      e += de; k += dk;
+      if (k >= W) { k -= W; ++e; }
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (es < EB) {
+        const bool ok = env0 + es < N;
+        dst[es * OS + ks] = ok ? v[u] : 0.f;
+        if (copy && ok) copy[(int64_t)(env0 + es) * O + ks] = v[u];
+      }
+      es += de; ks += dk;
+      if (ks >= W) { ks -= W; ++es; }
+    }
+  }
+}
+
 // One workgroup owns EB = G*EPT envs.  Thread (g, b): output block b (4 consecutive next-state
-// elements) of envs g*EPT .. g*EPT+EPT-1.  Inputs of the workgroup's envs are staged in LDS once.
+// elements) of envs g*EPT .. g*EPT+EPT-1.  Inputs of the workgroup's envs are staged in LDS once, rows OS floats apart.
+// The phases before the product are round trips to memory: loads of a phase are issued together, and every element has a
+// thread (one element after the other, the staging of 16 envs of 211 + 20 and their actions cost 33 round trips).
 template <int EPT, bool FUSED>
 __global__ __launch_bounds__(256) void env_step_kernel(
     const float* __restrict__ obs, const float* __restrict__ act, const float* __restrict__ m_t,
     uint32_t* __restrict__ episode_step, float* __restrict__ next_obs, float* __restrict__ reward,
-    uint8_t* __restrict__ done, int N, int O, int A, int o4, int nb, int G, float noise_std,
+    uint8_t* __restrict__ done, int N, int O, int A, int OS, int o4, int nb, int G, float noise_std,
     float reward_scale, uint32_t done_period, uint32_t done_threshold, uint32_t k0, uint32_t k1,
     uint32_t env_offset, uint32_t step, int vec_store, gmi::StepFuse fu) {
   extern __shared__ float smem[];
   const int OA = O + A;
   const int EB = G * EPT;
-  float* s_in = smem;                          // [EB][OA]
-  float* s_part = s_in + EB * OA;              // [EB][nb]
+  float* s_in = smem;                          // [EB][OS] state | action
+  float* s_part = s_in + EB * OS;              // [EB][nb]
   int* s_done = (int*)(s_part + EB * nb);      // [EB]
   const int env0 = blockIdx.x * EB;
   const int tid = threadIdx.x;
@@ -48,16 +82,7 @@ __global__ __launch_bounds__(256) void env_step_kernel(
   if constexpr (FUSED) {
     float* s_z = (float*)(s_done + EB);        // [EB][4 * nba] standard-normal draws of the step's actions
     const int nba = (A + 3) / 4;
-    for (int idx = tid; idx < EB * O; idx += 256) {
-      const int e = idx / O, k = idx % O;
-      const int env = env0 + e;
-      float v = 0.f;
-      if (env < N) {
-        v = obs[(int64_t)env * O + k];
-        if (fu.b_obs) fu.b_obs[(int64_t)env * O + k] = v;
-      }
-      s_in[e * OA + k] = v;
-    }
+    stage_inputs<false>(obs, nullptr, fu.b_obs, env0, EB, N, O, A, s_in, OS, tid);
     for (int p = tid; p < EB * nba; p += 256) {
       const int e = p / nba, b = p % nba;
       const int env = env0 + e;
@@ -67,31 +92,28 @@ __global__ __launch_bounds__(256) void env_step_kernel(
       for (int i = 0; i < 4; ++i) s_z[(e * nba + b) * 4 + i] = z[i];
     }
     __syncthreads();
-    for (int e = tid; e < EB; e += 256) {      // one thread per env: the log-density is summed in action order
+    for (int p = tid; p < EB * A; p += 256) {
+      const int e = p / A, j = p - e * A;
       const int env = env0 + e;
-      float lp = 0.f;
-      for (int j = 0; j < A; ++j) {
-        float a_j = 0.f;
-        if (env < N) {
-          const float zj = s_z[e * nba * 4 + j];
-          const float ls = fu.log_std[j];
-          const float m = fu.mu[(int64_t)env * A + j];
-          a_j = fmaf(expf(ls), zj, m);
-          fu.b_act[(int64_t)env * A + j] = a_j;
-          lp += -0.5f * zj * zj - ls - 0.918938533204672742f;
-        }
-        s_in[e * OA + O + j] = a_j;
+      float* zp = s_z + e * nba * 4 + j;
+      float a_j = 0.f;
+      if (env < N) {
+        const float zj = *zp, ls = fu.log_std[j];
+        a_j = fmaf(expf(ls), zj, fu.mu[(int64_t)env * A + j]);
+        fu.b_act[(int64_t)env * A + j] = a_j;
+        *zp = -0.5f * zj * zj - ls - 0.918938533204672742f;
       }
-      if (env < N) fu.b_logp[env] = lp;
+      s_in[e * OS + O + j] = a_j;
+    }
+    __syncthreads();
+    for (int e = tid; e < EB; e += 256) {      // the log-density is summed in action order
+      if (env0 + e >= N) continue;
+      float lp = 0.f;
+      for (int j = 0; j < A; ++j) lp += s_z[e * nba * 4 + j];
+      fu.b_logp[env0 + e] = lp;
     }
   } else {
-    for (int idx = tid; idx < EB * OA; idx += 256) {
-      const int e = idx / OA, k = idx % OA;
-      const int env = env0 + e;
-      float v = 0.f;
-      if (env < N) v = k < O ? obs[(int64_t)env * O + k] : act[(int64_t)env * A + (k - O)];
-      s_in[idx] = v;
-    }
+    stage_inputs<true>(obs, act, nullptr, env0, EB, N, O, A, s_in, OS, tid);
   }
   // done flags (integer decisions): periodic counter or Bernoulli by an integer threshold
   for (int el = tid; el < EB; el += 256) {
@@ -121,19 +143,60 @@ __global__ __launch_bounds__(256) void env_step_kernel(
     for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
 
   if (active) {
-    const float* xin = s_in + (g * EPT) * OA;
+    const float* xin = s_in + (g * EPT) * OS;
     const float4* mrow = reinterpret_cast<const float4*>(m_t) + b;
     const int stride4 = o4 / 4;
-#pragma unroll 4
-    for (int k = 0; k < OA; ++k) {
-      const float4 m = mrow[(int64_t)k * stride4];
+    // four matrix rows are fetched while the four before them are multiplied
+    float4 m[2][4];
+    auto fetch = [&](int buf, int k) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) m[buf][u] = mrow[(int64_t)min(k + u, OA - 1) * stride4];
+    };
+    auto multiply = [&](int buf, int k) {
+      float x[EPT][4];
+      if ((OS & 3) == 0) {
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+          const float4 v = *reinterpret_cast<const float4*>(xin + i * OS + k);
+          x[i][0] = v.x; x[i][1] = v.y; x[i][2] = v.z; x[i][3] = v.w;
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < EPT; ++i)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) x[i][u] = xin[i * OS + k + u];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+          acc[i][0] = fmaf(x[i][u], m[buf][u].x, acc[i][0]);
+          acc[i][1] = fmaf(x[i][u], m[buf][u].y, acc[i][1]);
+          acc[i][2] = fmaf(x[i][u], m[buf][u].z, acc[i][2]);
+          acc[i][3] = fmaf(x[i][u], m[buf][u].w, acc[i][3]);
+        }
+    };
+    fetch(0, 0);
+    int k = 0;
+    for (; k + 8 <= OA; k += 8) {
+      fetch(1, k + 4);
+      multiply(0, k);
+      fetch(0, k + 8);
+      multiply(1, k + 4);
+    }
+    if (k + 4 <= OA) {
+      multiply(0, k);
+      k += 4;
+    }
+    for (; k < OA; ++k) {
+      const float4 mk = mrow[(int64_t)k * stride4];
 #pragma unroll
       for (int i = 0; i < EPT; ++i) {
-        const float x = xin[i * OA + k];
-        acc[i][0] = fmaf(x, m.x, acc[i][0]);
-        acc[i][1] = fmaf(x, m.y, acc[i][1]);
-        acc[i][2] = fmaf(x, m.z, acc[i][2]);
-        acc[i][3] = fmaf(x, m.w, acc[i][3]);
+        const float x = xin[i * OS + k];
+        acc[i][0] = fmaf(x, mk.x, acc[i][0]);
+        acc[i][1] = fmaf(x, mk.y, acc[i][1]);
+        acc[i][2] = fmaf(x, mk.z, acc[i][2]);
+        acc[i][3] = fmaf(x, mk.w, acc[i][3]);
       }
     }
     // partial squared norms for the reward: this thread's 4 state elements, and its share of the action
@@ -143,9 +206,9 @@ __global__ __launch_bounds__(256) void env_step_kernel(
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int o = 4 * b + j;
-        if (o < O) { const float x = xin[i * OA + o]; ps = fmaf(x, x, ps); }
+        if (o < O) { const float x = xin[i * OS + o]; ps = fmaf(x, x, ps); }
       }
-      for (int a = b; a < A; a += nb) { const float x = xin[i * OA + O + a]; pa = fmaf(x, x, pa); }
+      for (int a = b; a < A; a += nb) { const float x = xin[i * OS + O + a]; pa = fmaf(x, x, pa); }
       s_part[(g * EPT + i) * nb + b] = ps + 0.01f * pa;
     }
   }
@@ -247,14 +310,17 @@ int launch_env_step(gmi_instance* g, gmi_env* env, const float* obs, const float
   while (ept > 1 && lds_bytes(ept) > 64 * 1024) ept >>= 1;
   if (lds_bytes(ept) > 64 * 1024) GMI_FAIL(GMI_ERR_UNSUPPORTED, "env_step: obs_dim + act_dim too large for the staging buffer");
   const int EB = G * ept;
+  int OS = (O + A + 3) & ~3;      // rows of 16-byte pieces where the padding fits
+  if (lds_bytes(ept) + (size_t)EB * (OS - O - A) * sizeof(float) > 64 * 1024) OS = O + A;
+  const size_t lds = lds_bytes(ept) + (size_t)EB * (OS - O - A) * sizeof(float);
   const unsigned grid = (unsigned)((N + EB - 1) / EB);
   const int vec_store = ((O & 3) == 0) && (((uintptr_t)next_obs & 15) == 0);
   const uint32_t k0 = (uint32_t)d.seed, k1 = (uint32_t)(d.seed >> 32);
   const StepFuse fu = fuse ? *fuse : StepFuse{};
   gmi::ProfScope ps(g, gmi::kClsEnvStep);
 #define GMI_ENV_LAUNCH(E, F)                                                                       \
-  ps.launch(env_step_kernel<E, F>, dim3(grid), dim3(256), lds_bytes(E),                                    \
-      obs, act, env->m_t, env->episode_step, next_obs, reward, done, N, O, A, o4, nb, G,          \
+  ps.launch(env_step_kernel<E, F>, dim3(grid), dim3(256), lds,                                    \
+      obs, act, env->m_t, env->episode_step, next_obs, reward, done, N, O, A, OS, o4, nb, G,          \
       d.noise_std, d.reward_scale, d.done_period, d.done_threshold, k0, k1, d.env_offset, step, vec_store, fu)
   if (fuse) {
     if (ept == 4) GMI_ENV_LAUNCH(4, true); else if (ept == 2) GMI_ENV_LAUNCH(2, true); else GMI_ENV_LAUNCH(1, true);
