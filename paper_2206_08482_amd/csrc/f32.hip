@@ -13,7 +13,8 @@
 //
 // Bound: small models by one launch and a chain of dependent LDS / L2 round trips per layer; large batches by the fp32
 // matrix instruction (157 TFLOP/s).  The one-thread-per-output kernels (mlp.hip) remain for gmi_set_fusion(.., 0) and for
-// models whose 16-row tile does not fit LDS; against them, measured: see the table in the design notes.
+// models whose 16-row tile does not fit LDS; against them agent_act of
+// 60:256:128:64:8 with 2048 rows takes 19 us instead of 468, an iteration of 17:64:64:6 with 512 envs 0.77 ms instead of 3.95.
 #include <algorithm>
 
 #include "rollout.h"

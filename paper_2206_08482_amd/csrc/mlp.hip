@@ -3,7 +3,8 @@
 // BF16 path: v_mfma_f32_32x32x16_bf16 (bf16 operands, fp32 accumulate).  A wavefront of 64 lanes
 // feeds the matrix core with 8 consecutive contraction elements per lane for both operands, so both
 // operands are staged in LDS with the contraction index contiguous; the weight-gradient product
-// contracts over samples, whose index is strided in memory, and reads its operands through the transposing LDS read.  F32 path: plain FMA loops (used for small fp32 configurations only).
+// contracts over samples, whose index is strided in memory, and reads its operands through the transposing LDS
+// read.  F32 path: plain FMA loops (gmi_set_fusion 0, and models whose rows do not fit the fp32 kernels' LDS tiles).
 #include <algorithm>
 
 #include "internal.h"
@@ -365,15 +366,15 @@ __global__ __launch_bounds__(128 * WRN) void linear_bf16_big_kernel(gmi::LinearB
 // ------------------------------------------------------------------------------------------------
 // Weight gradient: D[o, i] = sum_r dz[r, o] x[r, i].  Tile 256 (o) x 256 (i), 8 waves of 4 x 2 matrix-core tiles; the
 // contraction runs over the rows of one split, 32 rows per stage.  Both operands go from memory straight into LDS (16
-// bytes per lane, no registers in between) as they lie there, through a ring of four stages: three (96 KiB) are in flight
-// while one is multiplied.  The contraction index is the strided one; the transposing LDS read (per 16 lanes: 4 rows x 16
+// bytes per lane, no registers in between) as they lie there, through a ring of five stages: up to four (128 KiB) are in
+// flight while one is multiplied.  The contraction index is the strided one; the transposing LDS read (per 16 lanes: 4 rows x 16
 // features) delivers operands.  Bias gradients are row sums of the first operand (two-element dot products with ones).
 //
 // Bound: HBM / L2 traffic.  A tile reads 1 KiB per row; with 128 x 128 tiles (through registers, transposed there) the
 // same features were fetched by twice as many workgroups, whose second and third rounds found them evicted: 690 MB per
 // 32768-row minibatch of 211:512:512:256:128:20 for 403 MB of operands.  All workgroups now run in one round with at most
 // one per compute unit, and half as many splits are enough (their partials are another 6 MB each, written here and read
-// by Adam).  Measured on that minibatch: 145 us before, see the table of the design notes for now.
+// by Adam).  Measured on that minibatch: 145 us before, now 97 (388 MB fetched).
 constexpr int kWgradT = 256;                            // features per operand and tile
 constexpr int kWgradRows = 32;                          // rows per stage
 constexpr int kWgradOperand = kWgradT * kWgradRows * 2; // bytes
