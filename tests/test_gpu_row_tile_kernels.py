@@ -91,6 +91,8 @@ def test_gradient_equals_the_per_layer_kernels(g, inst, obs, act, hidden, dtype,
     (200, 20, [512, 512, 300], 65600, 0),     # ... and 64-row tiles one per compute unit
     (211, 20, [512, 512, 256, 128], 12287, 0),      # the last size below the row-tile forward kernel
     (30, 5, [64] * 8, 100, 0),                # the most layers
+    (211, 20, [512, 512, 256, 128], 12293, 0),      # row-tile forward kernel: rows gathered 16 at a time, ragged last ones
+    (211, 20, [512, 512, 256, 128], 12293, 1),      # ... row by row (not 16-byte aligned)
 ])
 def test_agent_kernel_matches_the_per_layer_path(g, inst, obs, act, hidden, n, shift):
     """Both paths round the same activations to bf16 after sums in another order: an activation may land on the other
