@@ -63,8 +63,8 @@ namespace gmi {
 //           4 linear_bf16_kernel<1,4,1,2,*> (128x64)
 //   role    0 forward hidden layer (bias + ELU)   1 forward head   2 input gradient (ELU')
 // (kClsGae covers gae_kernel and normalize_kernel, kClsLinearF32 the three fp32 epilogues, kClsFusedAgent the
-// one-launch agent forward of a model: agent_fused_kernel, or the forward-only row-tile kernel for the shapes that
-// have one -- a model uses one or the other.)
+// one-launch agent forward of a model: agent_kernel, or the forward-only row-tile kernel where use_tile_forward
+// says so.)
 enum KernelClass {
   kClsGather = 0, kClsWgrad, kClsLoss, kClsAdam, kClsShadowTranspose, kClsEnvStep, kClsSample,
   kClsCollect, kClsGae, kClsPermutation, kClsFusedAgent, kClsFusedRollout,

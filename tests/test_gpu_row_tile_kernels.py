@@ -153,3 +153,35 @@ def test_fp8_agent_rows_do_not_depend_on_the_tile(g, inst, obs, act, hidden, n):
             assert torch.isfinite(b).all()
             assert torch.equal(a[r0:r0 + k], b)
     g.gmi_fp8_destroy(w)
+
+
+@pytest.mark.parametrize("obs,act,hidden,n,T", [
+    (5, 1, [32], 1, 2),                       # one env, rows of an odd length
+    (45, 12, [128, 128], 33, 3),              # a ragged second tile; slots that are not 16-byte aligned
+    (107, 21, [400, 200, 100], 600, 3),       # 16 envs per workgroup, two envs per simulator item
+    (45, 12, [100], 16400, 2),                # 64 envs per workgroup
+])
+def test_streamed_collection_equals_the_step_by_step_calls(g, obs, act, hidden, n, T):
+    """Models whose weights the one-launch collection streams (the policy net in the launch, the values afterwards): every
+    array bit for bit that of agent_act / env_step / collect_experience, over two iterations in a row."""
+    from paper_2206_08482_amd.runner import PPOSession
+    rng = np.random.default_rng(9)
+    theta = syn.make_model_params(obs, act, hidden, 5, policy_head_scale=0.5)
+    a_mat = (0.9 * np.eye(obs) + 0.01 * rng.standard_normal((obs, obs))).astype(np.float32)
+    b_mat = (0.1 * rng.standard_normal((obs, act))).astype(np.float32)
+    state0 = rng.standard_normal((n, obs)).astype(np.float32)
+    ses = [PPOSession(n_envs=n, obs_dim=obs, act_dim=act, hidden=hidden, horizon=T, dtype="bf16", theta=theta, a_mat=a_mat,
+                      b_mat=b_mat, state0=state0, noise_std=0.01, reward_scale=1.0, done_period=0, done_threshold=(1 << 32) // 5,
+                      seed=11, minibatch=n, fused_rollout=f) for f in (True, False)]
+    for it in range(2):
+        for s in ses:
+            s.rollout(it)
+            s.sync()
+        assert ses[0].fused_rollout
+        ga, gb = (s.buf.to_numpy() for s in ses)
+        for k in ("obs", "act", "logp", "val", "rew", "done"):
+            assert np.array_equal(ga[k], gb[k]), (it, k)
+        assert np.array_equal(ses[0].state().cpu().numpy(), ses[1].state().cpu().numpy())
+        assert np.array_equal(ses[0].last_value.cpu().numpy(), ses[1].last_value.cpu().numpy())
+    for s in ses:
+        s.close()
