@@ -1,6 +1,7 @@
 // Trainer role (Section 3 of the paper, "DRL Trainer"; stage (ii) of Section 5.1): clipped-surrogate
 // loss, exact backward through both MLPs, Adam on the fp32 master parameters, shadow refresh.
 #include <math.h>
+#include <algorithm>
 
 #include "internal.h"
 
@@ -125,21 +126,27 @@ __device__ __forceinline__ void adam_step(float g, float& m, float& v, float& w,
 
 // Gradient partials of the trainer instances whose replicas are reduced into one update (one entry for an
 // ordinary single-instance update): per instance [n_split, part_stride] weight partials and the loss
-// kernel's [n_loss_blocks, kStatStride + A] statistics partials.
+// kernel's [n_stat, kStatStride + A] statistics partials.  The counts are the replica's own: they follow from the path
+// its instance takes (gmi_set_fusion).
 constexpr int kMaxGroup = 16;
+struct Partials {
+  const float *part, *stat;      // stat NULL: a caller-supplied gradient
+  int n_split, n_stat;
+};
 struct PartSet {
   int n;
-  const float* part[kMaxGroup];
-  const float* stat[kMaxGroup];
+  Partials r[kMaxGroup];
 };
 
 // Sum over the replicas and splits of the partials at p, splits grp, grp + G, grp + 2 G, ...: fixed order of additions,
 // 16 (then 4) loads in flight.
 template <int G>
-__device__ __forceinline__ float sum_partials(const PartSet& ps, int64_t p, int n_split, int64_t part_stride, int grp) {
+__device__ __forceinline__ float sum_partials(const PartSet& ps, int64_t p, int64_t part_stride, int grp) {
   float g = 0.f;
-  for (int i = 0; i < ps.n; ++i) {
-    const float* q = ps.part[i] + p;
+  Partials r = ps.r[0];      // the first entry comes with the other arguments, ahead of the loop
+  for (int i = 1;; ++i) {
+    const float* q = r.part + p;
+    const int n_split = r.n_split;
     int s = grp;
     for (; s + 15 * G < n_split; s += 16 * G) {
       float t[16];
@@ -156,17 +163,19 @@ __device__ __forceinline__ float sum_partials(const PartSet& ps, int64_t p, int 
       for (int u = 0; u < 4; ++u) g += t[u];
     }
     for (; s < n_split; s += G) g += q[(int64_t)s * part_stride];
+    if (i >= ps.n) break;
+    r = ps.r[i];
   }
   return g;
 }
 
 // Finalises the minibatch statistics and owns log_std, whose gradient is the sum of the loss partials minus the entropy
-// coefficient: one workgroup of NT threads reduces the [n_loss_blocks, kStatStride + A] partials cooperatively (a serial
+// coefficient: one workgroup of NT threads reduces the [n_stat, kStatStride + A] partials cooperatively (a serial
 // walk by one thread per column costs one memory round trip per loss workgroup).
 template <int NT>
 __device__ __forceinline__ void finish_stats(const gmi::ShadowTable& tab, float* __restrict__ params, float* __restrict__ am,
-                                             float* __restrict__ av, const PartSet& ps, int n_split, int64_t part_stride,
-                                             int n_loss_blocks, int A, float c_e, float inv_rows, const AdamScalars& hs,
+                                             float* __restrict__ av, const PartSet& ps, int64_t part_stride,
+                                             int A, float c_e, float inv_rows, const AdamScalars& hs,
                                              float* __restrict__ log_std_shadow, float* __restrict__ stats_out,
                                              float* __restrict__ grad_out, int do_update, float* s_col) {
   const int C = gmi::kStatStride + A;              // columns of a statistics row
@@ -174,7 +183,7 @@ __device__ __forceinline__ void finish_stats(const gmi::ShadowTable& tab, float*
   // up to NT columns per pass; narrow rows are walked by NT / C row groups in parallel
   const int width = C < NT ? C : NT;
   const int groups = NT / width;
-  const bool have_stat = ps.stat[0] != nullptr;
+  const bool have_stat = ps.r[0].stat != nullptr;
   const float inv_n = 1.0f / (float)ps.n;
   for (int cbase = 0; cbase < C; cbase += NT) {
     const int col = cbase + tid % width, grp = tid / width;
@@ -182,15 +191,16 @@ __device__ __forceinline__ void finish_stats(const gmi::ShadowTable& tab, float*
     if (have_stat && grp < groups && col < C)
       for (int i = 0; i < ps.n; ++i) {
         // rows grp, grp + groups, ...: eight loads in flight, fixed order of additions
-        const float* q = ps.stat[i] + col;
+        const float* q = ps.r[i].stat + col;
+        const int n_stat = ps.r[i].n_stat;
         int b = grp;
-        for (; b + 7 * groups < n_loss_blocks; b += 8 * groups) {
+        for (; b + 7 * groups < n_stat; b += 8 * groups) {
           float t[8];
 #pragma unroll
           for (int u = 0; u < 8; ++u) t[u] = q[(int64_t)(b + u * groups) * C];
           s += ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
         }
-        for (; b < n_loss_blocks; b += groups) s += q[(int64_t)b * C];
+        for (; b < n_stat; b += groups) s += q[(int64_t)b * C];
       }
     s_col[tid] = s;
     __syncthreads();
@@ -206,7 +216,7 @@ __device__ __forceinline__ void finish_stats(const gmi::ShadowTable& tab, float*
         // without loss partials (a caller-supplied gradient) log_std takes the split sums like any weight
         float g = 0.f;
         if (have_stat) g = t - c_e;
-        else for (int q = 0; q < n_split; ++q) g += ps.part[0][(int64_t)q * part_stride + p];
+        else for (int q = 0; q < ps.r[0].n_split; ++q) g += ps.r[0].part[(int64_t)q * part_stride + p];
         if (grad_out) grad_out[p] = g;
         if (do_update) {
           const float w = adam_one(g, params, am, av, p, hs);
@@ -226,12 +236,12 @@ __device__ __forceinline__ void finish_stats(const gmi::ShadowTable& tab, float*
 template <int G>
 __global__ __launch_bounds__(256 * G) void adam_kernel(gmi::ShadowTable tab, float* __restrict__ params,
                                                        float* __restrict__ am, float* __restrict__ av, PartSet ps,
-                                                       int n_split, int64_t part_stride, int n_loss_blocks, int A, float c_e,
-                                                       float inv_rows, AdamScalars hs, float* __restrict__ stats_out,
-                                                       float* __restrict__ grad_out, int do_update) {
+                                                       int64_t part_stride, int A, float c_e, float inv_rows, AdamScalars hs,
+                                                       float* __restrict__ stats_out, float* __restrict__ grad_out,
+                                                       int do_update) {
   __shared__ float s_sum[256 * G];
   if (blockIdx.x == gridDim.x - 1) {
-    finish_stats<256 * G>(tab, params, am, av, ps, n_split, part_stride, n_loss_blocks, A, c_e, inv_rows, hs, nullptr,
+    finish_stats<256 * G>(tab, params, am, av, ps, part_stride, A, c_e, inv_rows, hs, nullptr,
                           stats_out, grad_out, do_update, s_sum);
     return;
   }
@@ -241,7 +251,7 @@ __global__ __launch_bounds__(256 * G) void adam_kernel(gmi::ShadowTable tab, flo
   // the moments and the parameter are fetched ahead of the partials (their latency would otherwise follow the sum's)
   float m0 = 0.f, v0 = 0.f, w0 = 0.f;
   if (do_update && ok && grp == 0) { m0 = am[p]; v0 = av[p]; w0 = params[p]; }
-  float g = ok ? sum_partials<G>(ps, p, n_split, part_stride, grp) : 0.f;
+  float g = ok ? sum_partials<G>(ps, p, part_stride, grp) : 0.f;
   if constexpr (G > 1) {
     s_sum[threadIdx.x] = g;
     __syncthreads();
@@ -293,9 +303,8 @@ struct AdamTiles {
 };
 __global__ __launch_bounds__(256) void adam_shadow_kernel(gmi::ShadowTable tab, AdamTiles tt, gmi::ChainEmit ce,
                                                           float* __restrict__ params, float* __restrict__ am,
-                                                          float* __restrict__ av, PartSet ps, int n_split,
-                                                          int64_t part_stride, int n_loss_blocks, int A, float c_e,
-                                                          float inv_rows, AdamScalars hs, char* __restrict__ shadow,
+                                                          float* __restrict__ av, PartSet ps, int64_t part_stride,
+                                                          int A, float c_e, float inv_rows, AdamScalars hs, char* __restrict__ shadow,
                                                           float* __restrict__ stats_out, float* __restrict__ grad_out,
                                                           int do_update) {
   __shared__ __attribute__((aligned(16))) float s_sum[4][256];
@@ -303,7 +312,7 @@ __global__ __launch_bounds__(256) void adam_shadow_kernel(gmi::ShadowTable tab, 
   __shared__ __attribute__((aligned(16))) uint16_t s_t[8][40];
   const int n_tiles = gridDim.x - 1;
   if ((int)blockIdx.x == n_tiles) {
-    finish_stats<256>(tab, params, am, av, ps, n_split, part_stride, n_loss_blocks, A, c_e, inv_rows, hs,
+    finish_stats<256>(tab, params, am, av, ps, part_stride, A, c_e, inv_rows, hs,
                       do_update ? reinterpret_cast<float*>(shadow + tab.sh_logstd) : nullptr, stats_out, grad_out, do_update, &s_sum[0][0]);
     return;
   }
@@ -331,9 +340,11 @@ __global__ __launch_bounds__(256) void adam_shadow_kernel(gmi::ShadowTable tab, 
   const int64_t srcb = L.part_b + o0 + (lane & 7);
   float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
   float gb = 0.f;
-  for (int k = 0; k < ps.n; ++k) {
-    const float* q = ps.part[k] + src;
-    const float* qb = ps.part[k] + srcb;
+  Partials r = ps.r[0];      // the first entry comes with the other arguments, ahead of the loop
+  for (int k = 1;; ++k) {
+    const float* q = r.part + src;
+    const float* qb = r.part + srcb;
+    const int n_split = r.n_split;
     auto add = [&](int s, auto n) {      // rows s, s + 4, ...: all loads before the first addition, fixed order
       constexpr int U = decltype(n)::value;
       float4 x[U];
@@ -354,6 +365,8 @@ __global__ __launch_bounds__(256) void adam_shadow_kernel(gmi::ShadowTable tab, 
     int s = wave;
     for (; s + 16 < n_split; s += 32) add(s, std::integral_constant<int, 8>{});
     if (s < n_split) add(s, std::integral_constant<int, 4>{});
+    if (k >= ps.n) break;
+    r = ps.r[k];
   }
   *reinterpret_cast<float4*>(&s_sum[wave][lane * 4]) = g;
   if (lane < 8) s_bsum[wave][lane] = gb;
@@ -553,17 +566,18 @@ int minibatch_pass(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_h
 }
 
 // Reduces the partials of the n bindings ms[0..n) (replicas of one model: same parameter arrays, own
-// workspaces) and applies one Adam step through ms[0]; launched on instance g.
-int launch_adam(gmi_instance* g, gmi_model* const* ms, int n, int n_split, int n_loss_blocks,
+// workspaces; n_split[i] and n_stat[i] rows of them) and applies one Adam step through ms[0]; launched on instance g.
+int launch_adam(gmi_instance* g, gmi_model* const* ms, int n, const int* n_split, const int* n_stat,
                 const gmi_ppo_hparams* hp, int rows, uint32_t k, float* stats_out, float* grad_out, bool do_update) {
   gmi_model* m = ms[0];
   const gmi::ShadowTable tab = gmi::make_shadow_table(m->L);
   gmi::ProfScope ps(g, gmi::kClsAdam);
-  PartSet set;
+  PartSet set = {};
   set.n = n;
-  for (int i = 0; i < kMaxGroup; ++i) {
-    set.part[i] = i < n ? ms[i]->grad_part : nullptr;
-    set.stat[i] = i < n ? ms[i]->stat_part : nullptr;
+  int most = 0;
+  for (int i = 0; i < n; ++i) {
+    set.r[i] = Partials{ms[i]->grad_part, ms[i]->stat_part, n_split[i], n_stat[i]};
+    most = std::max(most, n_split[i]);
   }
   if (m->L.dtype == GMI_DTYPE_BF16) {
     AdamTiles tt;
@@ -576,19 +590,19 @@ int launch_adam(gmi_instance* g, gmi_model* const* ms, int n, int n_split, int n
     for (int i = tab.n; i <= gmi::kMaxWgradProblems; ++i) tt.start[i] = INT32_MAX;
     gmi::ChainEmit ce;
     gmi::fill_chain_emit(m->L, &ce);
-    ps.launch(adam_shadow_kernel, dim3(total + 1), dim3(256), 0, tab, tt, ce, m->params, m->adam_m, m->adam_v, set, n_split,
-              m->L.part_floats, n_loss_blocks, m->L.act_dim, hp->c_e, 1.0f / (float)rows, adam_scalars(hp, k), m->shadow,
+    ps.launch(adam_shadow_kernel, dim3(total + 1), dim3(256), 0, tab, tt, ce, m->params, m->adam_m, m->adam_v, set,
+              m->L.part_floats, m->L.act_dim, hp->c_e, 1.0f / (float)rows, adam_scalars(hp, k), m->shadow,
               stats_out, grad_out, do_update ? 1 : 0);
     GMI_LAUNCH_CHECK();
     return GMI_OK;
   }
   // four threads per parameter where one per parameter would leave the device short of loads in flight (fewer than
   // about 1024 workgroups of 256) or make each thread walk a long column
-  const bool split4 = n_split >= 4 && (n_split >= 64 || m->L.logstd_off < 256 * 1024);
+  const bool split4 = most >= 4 && (most >= 64 || m->L.logstd_off < 256 * 1024);
   const unsigned grid = (unsigned)((m->L.logstd_off + 255) / 256) + 1;
   auto go = [&](auto kernel, int threads) {
-    ps.launch(kernel, dim3(grid), dim3(threads), 0, tab, m->params, m->adam_m, m->adam_v, set, n_split, m->L.part_floats,
-              n_loss_blocks, m->L.act_dim, hp->c_e, 1.0f / (float)rows, adam_scalars(hp, k), stats_out, grad_out, do_update ? 1 : 0);
+    ps.launch(kernel, dim3(grid), dim3(threads), 0, tab, m->params, m->adam_m, m->adam_v, set, m->L.part_floats,
+              m->L.act_dim, hp->c_e, 1.0f / (float)rows, adam_scalars(hp, k), stats_out, grad_out, do_update ? 1 : 0);
   };
   if (split4) go(adam_kernel<4>, 1024); else go(adam_kernel<1>, 256);
   GMI_LAUNCH_CHECK();
@@ -631,7 +645,7 @@ extern "C" int ppo_update(gmi_t g, gmi_model_t m, gmi_buffer_t b, const gmi_ppo_
       rc = minibatch_pass(g, m, b, hp, perm + (int64_t)j * hp->minibatch, hp->minibatch, true, &n_split, &nlb, obs16);
       if (rc != GMI_OK) return rc;
       ++k;
-      rc = launch_adam(g, &m, 1, n_split, nlb, hp, hp->minibatch, k,
+      rc = launch_adam(g, &m, 1, &n_split, &nlb, hp, hp->minibatch, k,
                        stats_out ? stats_out + 5 * ((int64_t)e * nmb + j) : nullptr, nullptr, true);
       if (rc != GMI_OK) return rc;
     }
@@ -695,13 +709,11 @@ extern "C" int ppo_update_group(const gmi_t* gs, const gmi_model_t* ms, const gm
     }
     const int64_t perm_off = (int64_t)(e % gmi::kPermEpochs) * B;
     for (int j = 0; j < nmb; ++j) {
-      int n_split = 1, nlb = 1;
+      int n_split[kMaxGroup], nlb[kMaxGroup];
       for (int i = 0; i < n; ++i) {
-        int ns_i = 1, nlb_i = 1;
         rc = minibatch_pass(gs[i], ms[i], bs[i], hp, bs[i]->perm + perm_off + (int64_t)j * hp->minibatch, hp->minibatch, true,
-                            &ns_i, &nlb_i, obs16[i]);
+                            &n_split[i], &nlb[i], obs16[i]);
         if (rc != GMI_OK) return rc;
-        if (i == 0) { n_split = ns_i; nlb = nlb_i; }
         // replica i's partials are complete: let instance 0 see them
         if (i > 0) {
           GMI_HIP(hipEventRecord(gs[i]->event, gs[i]->stream));
@@ -744,7 +756,7 @@ extern "C" int ppo_evaluate(gmi_t g, gmi_model_t m, gmi_buffer_t b, const gmi_pp
   int n_split = 0, nlb = 1;
   rc = minibatch_pass(g, m, b, hp, idx, n, false, &n_split, &nlb);
   if (rc != GMI_OK) return rc;
-  return launch_adam(g, &m, 1, 0, nlb, hp, n, 1, stats_out, nullptr, false);
+  return launch_adam(g, &m, 1, &n_split, &nlb, hp, n, 1, stats_out, nullptr, false);
 }
 
 extern "C" int ppo_gradient(gmi_t g, gmi_model_t m, gmi_buffer_t b, const gmi_ppo_hparams* hp, const int32_t* idx,
@@ -755,7 +767,7 @@ extern "C" int ppo_gradient(gmi_t g, gmi_model_t m, gmi_buffer_t b, const gmi_pp
   int n_split = 1, nlb = 1;
   rc = minibatch_pass(g, m, b, hp, idx, n, true, &n_split, &nlb);
   if (rc != GMI_OK) return rc;
-  return launch_adam(g, &m, 1, n_split, nlb, hp, n, 1, stats_out, grad_out, false);
+  return launch_adam(g, &m, 1, &n_split, &nlb, hp, n, 1, stats_out, grad_out, false);
 }
 
 extern "C" int adam_update(gmi_t g, float* params, float* adam_m, float* adam_v, const float* grad, int64_t n,
@@ -774,12 +786,11 @@ extern "C" int adam_update(gmi_t g, float* params, float* adam_m, float* adam_v,
   tab.act_dim = 0;
   tab.n_params = n;
   gmi::ProfScope ps(g, gmi::kClsAdam);
-  PartSet set;
+  PartSet set = {};
   set.n = 1;
-  for (int i = 0; i < kMaxGroup; ++i) set.part[i] = set.stat[i] = nullptr;
-  set.part[0] = grad;
-  ps.launch(adam_kernel<1>, dim3((unsigned)((n + 255) / 256) + 1), dim3(256), 0, tab, params, adam_m, adam_v, set, 1, n,
-            0, 0, 0.f, 1.f, adam_scalars(hp, step), nullptr, nullptr, 1);
+  set.r[0] = Partials{grad, nullptr, 1, 0};
+  ps.launch(adam_kernel<1>, dim3((unsigned)((n + 255) / 256) + 1), dim3(256), 0, tab, params, adam_m, adam_v, set, n,
+            0, 0.f, 1.f, adam_scalars(hp, step), nullptr, nullptr, 1);
   GMI_LAUNCH_CHECK();
   return GMI_OK;
 }

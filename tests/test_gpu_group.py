@@ -196,3 +196,40 @@ def test_group_error_paths(g):
     other.close()
     for s in reversed(ses):
         s.close()
+
+
+@pytest.mark.parametrize("fusion", [(0, 1), (1, 0)])
+@pytest.mark.parametrize("obs,act,hidden,dtype,n_envs,horizon", [
+    (17, 6, (64, 64), "f32", 512, 8),             # one-launch minibatch: 128 partial rows; per-layer: 32
+    (45, 12, (128, 128), "bf16", 1000, 4),        # gradients in registers: 125 partial rows; per-layer: 32
+    (60, 8, (256, 128, 64), "bf16", 4200, 4),     # a compiled kernel: the same counts either way
+    (108, 21, (400, 200, 100), "bf16", 300, 2)])  # activations to memory: the same splits, 19 statistics rows against 3
+def test_group_of_instances_with_different_fusion_settings(g, obs, act, hidden, dtype, n_envs, horizon, fusion):
+    """gmi_set_fusion is a switch per instance, and the two settings leave different numbers of partial gradients and
+    statistics rows: every replica's rows have to enter the mean.  One minibatch of a whole buffer per replica; after
+    the first Adam step m = (1 - beta1) g, so adam_m is compared as the gradient (a replica that loses rows moves it by
+    tens of per cent)."""
+    cfg = syn.get_config("C1", obs_dim=obs, act_dim=act, hidden=hidden, n_envs=n_envs, horizon=horizon, dtype=dtype,
+                         done_period=0, done_prob_inv=1000, epochs=1, minibatch=n_envs * horizon)
+    shape, theta, env, _, hp = oracle_pieces(cfg)
+    states = [syn.make_initial_state(n_envs, obs, cfg.seed + 20 + i) for i in range(2)]
+    bufs = _oracle_collect(cfg, shape, theta, env, states, n_envs, horizon)
+    z = np.zeros_like(theta)
+    _, r_m, _, _, r_stats = oppo.ppo_update_group(theta, z, z, 0, shape, bufs, hp, env.seed, 0)
+    ses = _sessions(g, cfg, 2, n_envs, horizon, cfg.minibatch, dtype, theta, env, states)
+    for s, b, f in zip(ses, bufs, fusion):
+        g.gmi_set_fusion(s.gmi, f)
+        for k in ("obs", "act", "logp", "val", "rew", "done", "adv", "ret"):
+            getattr(s.buf, k).copy_(torch.tensor(b[k], device="cuda"))
+    stats = torch.zeros(1, 5, device="cuda")
+    torch.cuda.synchronize()
+    type(ses[0]).update_group(ses, 0, epochs=1, minibatch=cfg.minibatch, stats=stats, **_hp_kwargs(cfg))
+    for s in ses:
+        s.sync()
+    tol = 1e-4 if dtype == "f32" else TOL16
+    assert rel_l2(ses[0].adam_m.cpu().numpy(), r_m) <= tol, rel_l2(ses[0].adam_m.cpu().numpy(), r_m)
+    ls = ses[0].adam_m.cpu().numpy()[-act:]
+    assert rel_l2(ls, r_m[-act:]) <= 10 * tol, rel_l2(ls, r_m[-act:])      # log_std: from the statistics rows
+    assert np.abs(stats.cpu().numpy()[0, :2] - r_stats[0, :2]).max() <= tol * max(1.0, np.abs(r_stats).max())
+    for s in reversed(ses):
+        s.close()
