@@ -391,7 +391,7 @@ __global__ __launch_bounds__(kNT) void train_resident_kernel(ResArgs a) {
             float g_lp = 0.f;
             if (ok) {
               const float lo = s_scal[r], ad = s_scal[R + r];
-              const float ratio = __expf(lp - lo);
+              const float ratio = expf(lp - lo);
               const float u1 = ratio * ad;
               const float u2 = fminf(fmaxf(ratio, 1.0f - a.clip), 1.0f + a.clip) * ad;
               g_lp = (u1 <= u2) ? -(ad * ratio) * inv_m : 0.f;

@@ -185,3 +185,39 @@ def test_streamed_collection_equals_the_step_by_step_calls(g, obs, act, hidden, 
         assert np.array_equal(ses[0].last_value.cpu().numpy(), ses[1].last_value.cpu().numpy())
     for s in ses:
         s.close()
+
+
+@pytest.mark.parametrize("dtype,fused", [("bf16", 1), ("bf16", 0), ("f32", 1), ("f32", 0)])
+def test_probability_ratio_is_the_accurate_exponential(g, inst, dtype, fused):
+    """The ratio of a model without a compiled trainer kernel is expf of the log-density difference, also far from 1.  All
+    policy weights are zero and the action is the mean, so the log-density is -log(2 pi) / 2 exactly; one sample per call,
+    and an advantage whose sign keeps the unclipped term: the policy loss is the ratio itself.  Bound: the difference is
+    one fp32 subtraction on both sides, expf is within 1 ulp (1.2e-7), so 4e-7; a 2^x of an fp32 product x log2 e is off by
+    up to |x| 2^-24 (1.4e-6 was measured at 37.7)."""
+    obs, act, hidden, N = 5, 1, (32,), 12
+    model, buf, keep = _setup(g, inst, obs, act, hidden, dtype, 1, N, N)
+    theta, shadow, m, v, rb = keep
+    theta.zero_()
+    x = np.array([0.0, 0.3, -0.7, 2.5, -3.3, 7.9, -9.1, 13.7, 21.3, -25.9, 37.7, 43.1], np.float32)
+    lp = np.float32(-0.918938533204672742)
+    logp = (lp - x).astype(np.float32)
+    rb.act.zero_()
+    rb.logp.copy_(torch.tensor(logp)[None])
+    rb.adv.copy_(torch.tensor(np.where(x > 0, -1, 1).astype(np.float32))[None])
+    torch.cuda.synchronize()
+    g.gmi_model_refresh_shadow(inst, model)
+    g.gmi_set_fusion(inst, fused)
+    hp = g.ppo_hparams(clip=0.2, c_v=0.5, c_e=0.0, minibatch=1)
+    grad = torch.zeros(theta.numel(), device="cuda:0")
+    stats = torch.zeros(N, 5, device="cuda:0")
+    idx = torch.arange(N, dtype=torch.int32, device="cuda:0")
+    torch.cuda.synchronize()
+    for i in range(N):
+        g.ppo_gradient(inst, model, buf, hp, idx[i:], 1, grad, stats[i])
+    g.gmi_sync(inst)
+    g.gmi_set_fusion(inst, 1)
+    got = np.abs(stats[:, 0].cpu().numpy().astype(np.float64))
+    want = np.exp((lp - logp).astype(np.float32).astype(np.float64))
+    assert np.abs(got / want - 1).max() <= 4e-7, np.abs(got / want - 1)
+    g.gmi_buffer_destroy(buf)
+    g.gmi_model_destroy(model)
