@@ -358,11 +358,9 @@ size_t agent_lds(AgentArgs& a, int rt, bool sample) {
 template <class P, int RT, int D, int MT, int WPS, int NW = 8>
 int launch(gmi_instance* g, AgentArgs& a, int nets, bool sample) {
   const size_t lds = agent_lds<P>(a, RT, sample);
-  static bool attr = false;
-  if (!attr) {
-    GMI_HIP(hipFuncSetAttribute((const void*)agent_kernel<P, RT, D, MT, WPS, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
-    attr = true;
-  }
+  static gmi::DeviceSet allowed;
+  const int rc = gmi::allow_lds((const void*)agent_kernel<P, RT, D, MT, WPS, NW>, kLdsMax, g->device, &allowed);
+  if (rc != GMI_OK) return rc;
   gmi::ProfScope ps(g, gmi::kClsFusedAgent);
   ps.launch(agent_kernel<P, RT, D, MT, WPS, NW>, dim3((a.n + 32 * RT - 1) / (32 * RT), nets, a.T + (a.value_last ? 1 : 0)), dim3(64 * NW), lds, a);
   GMI_LAUNCH_CHECK();

@@ -752,15 +752,13 @@ bool shape_matches(const ModelLayout& L) {
 
 template <class S>
 int launch_shape(gmi_instance* g, const ChainArgs& a, int rows, int* tiles_out, double flops, double bytes) {
-  static bool attr = false;
+  static gmi::DeviceSet allowed;
   const size_t lds = S::lds_bytes();
   const int tiles = (rows + 32 * S::NW - 1) / (32 * S::NW);
   *tiles_out = tiles;
   if (tiles > gmi::kLossBlocksMax) return GMI_ERR_UNSUPPORTED;      // one statistics row per tile
-  if (!attr) {
-    GMI_HIP(hipFuncSetAttribute((const void*)train_chain_kernel<S>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    attr = true;
-  }
+  const int rc = gmi::allow_lds((const void*)train_chain_kernel<S>, lds, g->device, &allowed);
+  if (rc != GMI_OK) return rc;
   gmi::ProfScope ps(g, gmi::kClsChainTrain);
   ps.work(flops, bytes);
   ps.launch(train_chain_kernel<S>, dim3(tiles, 2), dim3(S::NT), lds, a);

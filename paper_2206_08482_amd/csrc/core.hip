@@ -15,6 +15,20 @@ void set_error(const char* fmt, ...) {
 }
 }  // namespace gmi
 
+namespace gmi {
+int allow_lds(const void* kernel, size_t bytes, int device, DeviceSet* done) {
+  if (done->has(device)) return GMI_OK;
+  int cur = -1;
+  GMI_HIP(hipGetDevice(&cur));
+  if (cur != device) GMI_HIP(hipSetDevice(device));
+  const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (cur != device) (void)hipSetDevice(cur);
+  GMI_HIP(e);
+  done->add(device);
+  return GMI_OK;
+}
+}  // namespace gmi
+
 extern "C" const char* gmi_last_error(void) { return gmi::g_err; }
 
 namespace gmi {

@@ -699,15 +699,6 @@ int max_hidden(const ModelLayout& L) {
   for (int l = 0; l < L.n_hidden; ++l) w = std::max(w, L.net[0][l].out);
   return w;
 }
-template <class K>
-int allow_lds(K kernel, bool* done) {
-  if (!*done) {
-    GMI_HIP(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
-    *done = true;
-  }
-  return GMI_OK;
-}
-
 size_t train_lds(const ModelLayout& L, int R, int w_floats, int b_floats) {
   size_t n = (size_t)w_floats + b_floats;
   int sdz = 0;
@@ -759,8 +750,8 @@ int launch_agent_f32(gmi_instance* g, gmi_model* m, const float* obs, int n, uin
   a.obs = obs;
   a.k0 = (uint32_t)seed; a.k1 = (uint32_t)(seed >> 32); a.step = step; a.env_offset = env_offset;
   a.act = act; a.logp = logp; a.value = value; a.mu_out = mu_out;
-  static bool attr[2] = {false, false};
-  const int rc = wl ? allow_lds(agent_f32_kernel<true>, &attr[1]) : allow_lds(agent_f32_kernel<false>, &attr[0]);
+  static DeviceSet allowed[2];
+  const int rc = allow_lds(wl ? (const void*)agent_f32_kernel<true> : (const void*)agent_f32_kernel<false>, kLdsMax, g->device, &allowed[wl]);
   if (rc != GMI_OK) return rc;
   ProfScope ps(g, kClsFusedAgent);
   const dim3 grid((n + R - 1) / R, 2 - a.net0);
@@ -806,8 +797,8 @@ int launch_train_f32(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo
   a.part = m->grad_part; a.part_stride = L.n_params;
   a.stat_part = m->stat_part;
   const int groups = std::min(a.n_tiles, m->part_rows);
-  static bool attr[2] = {false, false};
-  const int rc = wl ? allow_lds(train_f32_kernel<true>, &attr[1]) : allow_lds(train_f32_kernel<false>, &attr[0]);
+  static DeviceSet allowed[2];
+  const int rc = allow_lds(wl ? (const void*)train_f32_kernel<true> : (const void*)train_f32_kernel<false>, kLdsMax, g->device, &allowed[wl]);
   if (rc != GMI_OK) return rc;
   *n_parts = groups;
   ProfScope ps(g, kClsChainTrain);
@@ -855,8 +846,8 @@ extern "C" int rollout_collect_f32(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_bu
   const size_t bytes = lds(R, wl, a.mt_lds != 0);
   a.rows_per_wg = R;
   a.n_tiles = (a.n + R - 1) / R;
-  static bool attr[2] = {false, false};
-  const int rc2 = wl ? allow_lds(rollout_f32_kernel<true>, &attr[1]) : allow_lds(rollout_f32_kernel<false>, &attr[0]);
+  static gmi::DeviceSet allowed[2];
+  const int rc2 = gmi::allow_lds(wl ? (const void*)rollout_f32_kernel<true> : (const void*)rollout_f32_kernel<false>, kLdsMax, g->device, &allowed[wl]);
   if (rc2 != GMI_OK) return rc2;
   // no more workgroups than the instance's compute units hold at once (see rollout_collect)
   int per_cu = (int)(kLdsMax / bytes);

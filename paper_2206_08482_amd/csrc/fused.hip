@@ -711,11 +711,9 @@ extern "C" int rollout_collect(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_buffer
   // 16 envs per workgroup: the weight-stationary nets on 16-row products
   if (rows_per_wg == 16 && variant == 2) { kfn = rollout_fused_kernel<1, WsAnt, true>; variant = 6; }
   else if (rows_per_wg == 16 && variant == 4) { kfn = rollout_fused_kernel<1, WsSmallObs, true>; variant = 7; }
-  static bool attr_set[8] = {false, false, false, false, false, false, false, false};
-  if (!attr_set[variant]) {
-    GMI_HIP(hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
-    attr_set[variant] = true;
-  }
+  static gmi::DeviceSet allowed[8];
+  const int lds_rc = gmi::allow_lds((const void*)kfn, kLdsMax, g->device, &allowed[variant]);
+  if (lds_rc != GMI_OK) return lds_rc;
   // no more workgroups than the instance's compute units hold at once; the rest of the tiles are taken
   // by the same workgroups in turn
   int per_cu = 0;

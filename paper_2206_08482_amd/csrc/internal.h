@@ -5,6 +5,7 @@
 #include <hip/hip_bf16.h>
 #include <stdint.h>
 #include <stdio.h>
+#include <atomic>
 #include <string>
 #include <tuple>
 #include <type_traits>
@@ -48,6 +49,18 @@ constexpr uint32_t kMagicInstance = 0x474d4931;  // "GMI1"
 constexpr uint32_t kMagicModel = 0x474d494d;
 constexpr uint32_t kMagicEnv = 0x474d4945;
 constexpr uint32_t kMagicBuffer = 0x474d4942;
+
+// Devices on which something has been done once (several threads may ask).
+struct DeviceSet {
+  std::atomic<uint64_t> bits{0};
+  bool has(int device) const { return device >= 0 && device < 64 && ((bits.load(std::memory_order_acquire) >> device) & 1u); }
+  void add(int device) {
+    if (device >= 0 && device < 64) bits.fetch_or(1ull << device, std::memory_order_release);      // others: done every time
+  }
+};
+// Lets a kernel take `bytes` of dynamic LDS on `device`.  The limit is an attribute of the kernel on one device and a process
+// may hold instances on several, so `done` -- one per kernel -- records the devices that have it.
+int allow_lds(const void* kernel, size_t bytes, int device, DeviceSet* done);
 
 static inline int pad32(int x) { return (x + 31) & ~31; }
 static inline int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }

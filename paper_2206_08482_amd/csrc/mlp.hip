@@ -840,13 +840,11 @@ int launch_wgrad(gmi_instance* g, int dtype, int rows, int n_split, int chunk, W
     b.net_tiles[i < half ? 0 : 1] += b.tiles[i];
   }
   const int total = 2 * n_split * std::max(b.net_tiles[0], b.net_tiles[1]);
-  static bool attr[2] = {false, false};
+  static DeviceSet allowed[2];
   const int layout = b.p[0].dz_blocks ? 1 : 0;
   const void* kernel = layout ? (const void*)wgrad_bf16_kernel<1> : (const void*)wgrad_bf16_kernel<0>;
-  if (!attr[layout]) {
-    GMI_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kWgradLds));
-    attr[layout] = true;
-  }
+  const int rc = allow_lds(kernel, kWgradLds, g->device, &allowed[layout]);
+  if (rc != GMI_OK) return rc;
   if (layout) ps.launch(wgrad_bf16_kernel<1>, dim3(total), dim3(512), kWgradLds, b, rows, n_split, chunk, part, part_stride);
   else ps.launch(wgrad_bf16_kernel<0>, dim3(total), dim3(512), kWgradLds, b, rows, n_split, chunk, part, part_stride);
   GMI_LAUNCH_CHECK();

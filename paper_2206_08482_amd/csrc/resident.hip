@@ -582,11 +582,9 @@ bool shape_ok(const ModelLayout& L) {
 
 template <int RT, int NS>
 int launch(gmi_instance* g, const ResArgs& a, int grid, size_t lds) {
-  static bool attr = false;
-  if (!attr) {
-    GMI_HIP(hipFuncSetAttribute((const void*)train_resident_kernel<RT, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
-    attr = true;
-  }
+  static gmi::DeviceSet allowed;
+  const int rc = gmi::allow_lds((const void*)train_resident_kernel<RT, NS>, kLdsMax, g->device, &allowed);
+  if (rc != GMI_OK) return rc;
   gmi::ProfScope ps(g, gmi::kClsChainTrain);
   ps.launch(train_resident_kernel<RT, NS>, dim3(grid, 2), dim3(kNT), lds, a);
   GMI_LAUNCH_CHECK();

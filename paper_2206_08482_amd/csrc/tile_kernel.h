@@ -619,16 +619,14 @@ bool shape_matches(const ModelLayout& L) {
 
 template <class S>
 int launch_shape(gmi_instance* g, const ChainArgs& a, int rows, int* tiles_out, double flops, double bytes) {
-  static bool attr = false;
+  static gmi::DeviceSet allowed;
   const size_t lds = S::lds_bytes();
   const int tiles = (rows + kRows - 1) / kRows;
   *tiles_out = tiles;
   if (!S::fwd && tiles > gmi::kLossBlocksMax) return GMI_ERR_UNSUPPORTED;      // one statistics row per tile
   if (a.x0_ready == 0 && (a.obs_dim % 4 != 0 || a.obs_dim < 4)) return GMI_ERR_UNSUPPORTED;
-  if (!attr) {
-    GMI_HIP(hipFuncSetAttribute((const void*)train_tile_kernel<S>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    attr = true;
-  }
+  const int rc = gmi::allow_lds((const void*)train_tile_kernel<S>, lds, g->device, &allowed);
+  if (rc != GMI_OK) return rc;
   gmi::ProfScope ps(g, S::fwd ? gmi::kClsFusedAgent : gmi::kClsChainTrain);
   ps.work(flops, bytes);
   ps.launch(train_tile_kernel<S>, dim3(tiles, S::fwd ? 2 - a.net0 : 2), dim3(kWaves * 64), lds, a);

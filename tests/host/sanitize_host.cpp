@@ -4,9 +4,11 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <thread>
 #include <vector>
 
 #include "../../include/gmidrl.h"
+#include "../../paper_2206_08482_amd/csrc/internal.h"
 
 static int fails = 0;
 #define CHECK(c) do { if (!(c)) { std::printf("FAILED %s:%d: %s\n", __FILE__, __LINE__, #c); ++fails; } } while (0)
@@ -65,6 +67,20 @@ int main() {
     CHECK(gmi_destroy(nullptr) == GMI_ERR_BAD_HANDLE);
     CHECK(gmi_channels_drop(nullptr, 1) == GMI_ERR_BAD_HANDLE);
     CHECK(gmi_stream(nullptr) == nullptr);
+  }
+  {
+    // what a kernel has been allowed on one device says nothing about another; devices may be added by several threads
+    gmi::DeviceSet done;
+    CHECK(!done.has(0) && !done.has(-1) && !done.has(64));
+    done.add(3);
+    CHECK(done.has(3) && !done.has(0) && !done.has(2) && !done.has(4) && !done.has(35));
+    done.add(-1);
+    done.add(64);
+    CHECK(!done.has(-1) && !done.has(64) && !done.has(0));
+    std::vector<std::thread> ts;
+    for (int i = 0; i < 8; ++i) ts.emplace_back([&done, i]() { for (int d = i; d < 64; d += 8) done.add(d); });
+    for (std::thread& t : ts) t.join();
+    for (int d = 0; d < 64; ++d) CHECK(done.has(d));
   }
   std::printf(fails ? "host checks: %d failed\n" : "host checks passed\n", fails);
   return fails ? 1 : 0;

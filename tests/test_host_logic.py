@@ -37,3 +37,11 @@ def test_cu_masks_reject_counts_that_are_not_whole_rows():
         cu_masks(256, [60, 60], "contiguous")                  # not a multiple of 8: some die would get fewer CUs
     with pytest.raises(ValueError):
         cu_masks(256, [128, 136], "contiguous")                # more than the device has
+
+
+def test_kernel_attributes_are_set_per_device():
+    """The dynamic-LDS limit of a kernel belongs to one device; a process may hold instances on several.  Every launcher
+    goes through allow_lds, which keeps a set of devices per kernel."""
+    csrc = os.path.join(ROOT, "paper_2206_08482_amd", "csrc")
+    with_call = [f for f in sorted(os.listdir(csrc)) if "hipFuncSetAttribute" in open(os.path.join(csrc, f)).read()]
+    assert with_call == ["core.hip"]
