@@ -388,13 +388,17 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
 
 // 16 bytes per lane from base + off to LDS bytes [lds, lds + 1024) in lane order.  Inline assembly: the compiler would
-// wait for every such load in flight before any LDS read.
+// wait for every such load in flight before any LDS read.  m0 (the LDS address) is a register that the compiler never
+// allocates, and says so of a clobber; it does write m0 for instructions of its own, and has to know of this write.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_to_lds(const void* base, uint32_t off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "m0", "memory");
 }
 __device__ __forceinline__ void load_to_lds(const void* src, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "m0", "memory");
 }
+#pragma clang diagnostic pop
 
 // LAYOUT: 0 both operands row-major, 1 both in the block layout of the row-tile trainer kernel.
 template <int LAYOUT>

@@ -1,5 +1,6 @@
 """Host-side logic that needs no GPU: the one-GPU contract of bench.py and the CU-mask builder."""
 import os
+import re
 import subprocess
 import sys
 
@@ -45,3 +46,15 @@ def test_kernel_attributes_are_set_per_device():
     csrc = os.path.join(ROOT, "paper_2206_08482_amd", "csrc")
     with_call = [f for f in sorted(os.listdir(csrc)) if "hipFuncSetAttribute" in open(os.path.join(csrc, f)).read()]
     assert with_call == ["core.hip"]
+
+
+def test_inline_assembly_names_the_registers_it_writes():
+    """Instructions that take an LDS address from m0 are preceded by a write of m0: the compiler has to be told."""
+    csrc = os.path.join(ROOT, "paper_2206_08482_amd", "csrc")
+    found = 0
+    for f in sorted(os.listdir(csrc)):
+        for stmt in re.findall(r"asm volatile\((.*?)\);", open(os.path.join(csrc, f)).read(), re.S):
+            if re.search(r"\bs_\w+ m0\b", stmt):
+                found += 1
+                assert re.search(r':[^:]*"m0"[^:]*$', stmt), (f, stmt)
+    assert found == 2
