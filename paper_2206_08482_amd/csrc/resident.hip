@@ -580,6 +580,26 @@ bool shape_ok(const ModelLayout& L) {
   return plan_lds(L, 1, &p);
 }
 
+// Sets of dW blocks that a wave keeps in registers (0: too many, gradients go to memory).
+int grad_sets(const ModelLayout& L) {
+  const int blocks = std::max(n_blocks(L, 0), n_blocks(L, 1));
+  return blocks <= kNW ? 1 : (blocks <= 2 * kNW ? 2 : 0);
+}
+
+// The row tiles per workgroup for `rows` rows: the fewest with which kMaxGroupsA workgroups per net hold them all, else as
+// many as fit LDS (and the compiled variants).
+int pick_tiles(const ModelLayout& L, int64_t rows, Plan* p) {
+  int RT = 0;
+  for (int rt = 1; rt <= (grad_sets(L) > 0 ? 4 : 2); rt <<= 1) {
+    Plan q;
+    if (!plan_lds(L, rt, &q)) break;
+    *p = q;
+    RT = rt;
+    if (rows <= 32 * (int64_t)rt * kMaxGroupsA) break;
+  }
+  return RT;
+}
+
 template <int RT, int NS>
 int launch(gmi_instance* g, const ResArgs& a, int grid, size_t lds) {
   static gmi::DeviceSet allowed;
@@ -596,36 +616,31 @@ int launch(gmi_instance* g, const ResArgs& a, int grid, size_t lds) {
 namespace gmi {
 
 bool resident_supported(const ModelLayout& L) { return shape_ok(L); }
-// Where a register-chained or row-tile kernel is compiled for the shape, this kernel is the faster one up to `rows`:
-// per minibatch with Adam, 60:256:128:64:8: 43.8 against 56.2 us at 2048 rows, 63.3 / 66.5 at 16384, 91.9 / 89.9 at 32768;
-// 108:400:200:100:21 (gradients not in registers): 50.5 / 64.5 at 2048, 69.0 / 75.2 at 8192, 117 / 98 at 16384.
+// Where a register-chained or row-tile kernel is compiled for the shape, this kernel is the faster one while every tile has a
+// workgroup of its own (one per net and two compute units; 128-row tiles with the gradients in registers, else 64 or, where
+// only those fit LDS, 32).  Per minibatch with Adam, us, this kernel / the compiled one:
+//   60:256:128:64:8 (128 rows): 34.7 / 45.5 at 1000 rows, 48.5 / 50.8 at 8192, 56.6 / 57.1 at 16384, 91.9 / 89.9 at 32768;
+//   108:400:200:100:21 (64): 49.8 / 64.1 at 1000, 55.4 / 68.5 at 4096, 68.6 / 74.6 at 8192, 117 / 98 at 16384;
+//   211:512:512:256:128:20 (32): 81.9 / 98.1 at 1000, 91.7 / 107.4 at 4096, 137 / 113 at 6000, 145 / 119 at 8192;
+//   211:512:512:512:256:20 (32): 101 / 124 at 1000, 114 / 135 at 4096, 184 / 153 at 8192.
 bool use_resident(const ModelLayout& L, int rows) {
   if (!shape_ok(L)) return false;
-  return !chain_compiled(L) || rows <= (resident_part_rows(L) > 0 ? 16384 : 8192);
+  Plan p;
+  return !chain_compiled(L) || rows <= 32 * (int64_t)pick_tiles(L, INT32_MAX, &p) * kMaxGroupsA;
 }
 
 // Rows of gradient partials the kernel may fill with this model.
 int resident_part_rows(const ModelLayout& L) {
-  return shape_ok(L) && std::max(n_blocks(L, 0), n_blocks(L, 1)) <= 16 ? kMaxGroupsA : 0;
+  return shape_ok(L) && grad_sets(L) > 0 ? kMaxGroupsA : 0;
 }
 
 int launch_train_resident(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_hparams* hp, const int32_t* idx, int rows,
                           int* n_parts, int* n_stat_rows) {
   const ModelLayout& L = m->L;
   if (!shape_ok(L) || rows < 1 || rows > m->max_rows) return GMI_ERR_UNSUPPORTED;
-  const int blocks = std::max(n_blocks(L, 0), n_blocks(L, 1));
-  const int NS = blocks <= 8 ? 1 : (blocks <= 16 ? 2 : 0);
+  const int NS = grad_sets(L);
   Plan p;
-  int RT = 0;
-  for (int rt = 1; rt <= (NS > 0 ? 4 : 2); rt <<= 1) {
-    Plan q;
-    if (!plan_lds(L, rt, &q)) break;
-    p = q;
-    RT = rt;
-    // gradients in registers: the shortest tile with which one workgroup per net and two compute units is enough (a
-    // partial gradient each); else the shortest that does not leave the device a second, nearly empty round
-    if ((rows + 32 * rt - 1) / (32 * rt) <= kMaxGroupsA) break;
-  }
+  const int RT = pick_tiles(L, rows, &p);
   ResArgs a;
   a.nl = L.n_layers; a.rows = rows; a.obs_dim = L.obs_dim; a.act_dim = L.act_dim;
   a.n_envs = b->d.n_envs; a.ld_envs = b->d.ld_envs;

@@ -105,6 +105,43 @@ def test_gradient_matches_the_bf16_error_model(g, inst, name, T, N, rows, path):
     g.gmi_set_fusion(inst, 1)
 
 
+def _stated_work(g, inst, cls_name, call):
+    """Launches of a kernel class during call(), and the flops that their launchers state."""
+    names = [g.gmi_profile_class_name(c) for c in range(g.gmi_profile_classes())]
+    c = names.index(cls_name)
+    g.gmi_profile_enable(inst, 1 << c)
+    try:
+        out = call()
+        return out, g.gmi_profile_read(inst, c)[1], g.gmi_profile_work(inst, c)[0]
+    finally:
+        g.gmi_profile_enable(inst, 0)
+
+
+@pytest.mark.parametrize("name,T,N,rows", [
+    ("C2", 3, 5600, 16397), ("BB", 2, 8300, 16413), ("FC", 3, 5500, 16389), ("AY", 2, 8200, 16386),      # 16384: the last
+    ("C3", 2, 4200, 8205), ("HM", 3, 2800, 8321),      # 8192
+    ("C4", 2, 2100, 4099), ("SH", 3, 1400, 4133), ("C4", 2, 4300, 8191)])      # 4096 rows of the resident kernel
+def test_gradient_of_the_compiled_trainer_kernels_at_ragged_rows(g, inst, name, T, N, rows):
+    """The register-chained and the row-tile trainer kernels just beyond the rows up to which the resident kernel serves
+    their shapes (use_resident).  Only their launchers state work for the class, so this also checks which kernel ran."""
+    (shape, (got_g, got_s), args), launches, flops = _stated_work(
+        g, inst, "chain_train", lambda: _gradient_case(g, inst, name, T, N, rows))
+    assert launches == 1 and flops > 0
+    m_stats, m_grad = bm.ppo_loss_and_grad(*args)
+    assert rel_l2(got_g, m_grad) <= TOL_MODEL, rel_l2(got_g, m_grad)
+    assert rel_max(got_g, m_grad) <= TOL_MODEL_MAX, rel_max(got_g, m_grad)
+    _per_tensor(shape, got_g, m_grad, 2 * TOL_MODEL)
+    assert np.allclose(got_s[:2], m_stats[:2], rtol=TOL_MODEL, atol=1e-5)
+
+
+@pytest.mark.parametrize("name,rows", [("C2", 16384), ("C3", 8192), ("C4", 4096), ("SH", 4096)])
+def test_the_resident_kernel_serves_the_last_rows_it_is_faster_at(g, inst, name, rows):
+    (_, (got_g, _), _), launches, flops = _stated_work(
+        g, inst, "chain_train", lambda: _gradient_case(g, inst, name, 2, rows // 2, rows))
+    assert launches == 1 and flops == 0
+    assert np.isfinite(got_g).all()
+
+
 def test_gradient_of_a_benchmark_sized_minibatch_c4(g, inst):
     """32768 rows of the largest workload's model, the launch configuration the benchmark times (512 workgroups
     of the trainer kernel, every row split of the weight-gradient kernel), against the fp32 oracle and the
