@@ -27,6 +27,13 @@ int allow_lds(const void* kernel, size_t bytes, int device, DeviceSet* done) {
   done->add(device);
   return GMI_OK;
 }
+
+int resident_groups(gmi_instance* g, const void* kernel, int threads, size_t lds, int64_t* groups) {
+  int per_cu = 0;
+  GMI_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds));
+  *groups = (int64_t)(per_cu < 1 ? 1 : per_cu) * g->cu_count;
+  return GMI_OK;
+}
 }  // namespace gmi
 
 extern "C" const char* gmi_last_error(void) { return gmi::g_err; }

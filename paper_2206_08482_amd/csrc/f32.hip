@@ -849,10 +849,11 @@ extern "C" int rollout_collect_f32(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_bu
   static gmi::DeviceSet allowed[2];
   const int rc2 = gmi::allow_lds(wl ? (const void*)rollout_f32_kernel<true> : (const void*)rollout_f32_kernel<false>, kLdsMax, g->device, &allowed[wl]);
   if (rc2 != GMI_OK) return rc2;
-  // no more workgroups than the instance's compute units hold at once (see rollout_collect)
-  int per_cu = (int)(kLdsMax / bytes);
-  if (per_cu > 2) per_cu = 2;
-  const int grid = std::min(a.n_tiles, std::max(per_cu, 1) * g->cu_count);
+  // no more workgroups than the instance's compute units hold at once (see rollout_collect): one each, by registers (164)
+  int64_t resident = 1;
+  const int rc3 = gmi::resident_groups(g, wl ? (const void*)rollout_f32_kernel<true> : (const void*)rollout_f32_kernel<false>, kNT, bytes, &resident);
+  if (rc3 != GMI_OK) return rc3;
+  const int grid = (int)std::min<int64_t>(a.n_tiles, resident);
   gmi::ProfScope ps(g, gmi::kClsFusedRollout);
   if (wl) ps.launch(rollout_f32_kernel<true>, dim3(grid), dim3(kNT), bytes, a);
   else ps.launch(rollout_f32_kernel<false>, dim3(grid), dim3(kNT), bytes, a);

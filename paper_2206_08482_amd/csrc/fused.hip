@@ -716,10 +716,9 @@ extern "C" int rollout_collect(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_buffer
   if (lds_rc != GMI_OK) return lds_rc;
   // no more workgroups than the instance's compute units hold at once; the rest of the tiles are taken
   // by the same workgroups in turn
-  int per_cu = 0;
-  GMI_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kfn, 512, lds));
-  if (per_cu < 1) per_cu = 1;
-  const int64_t resident = (int64_t)per_cu * g->cu_count;
+  int64_t resident = 1;
+  const int occ_rc = gmi::resident_groups(g, (const void*)kfn, 512, lds, &resident);
+  if (occ_rc != GMI_OK) return occ_rc;
   const int grid = (int)(a.n_tiles < resident ? a.n_tiles : resident);
   {
     gmi::ProfScope ps(g, gmi::kClsFusedRollout);

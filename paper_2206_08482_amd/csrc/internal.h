@@ -218,6 +218,12 @@ struct gmi_buffer {
                     // the start of an update; only for observation rows that 16-byte loads cannot read (else NULL)
 };
 
+namespace gmi {
+// Workgroups of a kernel that the instance's compute units hold at once (*groups >= 1).  A launch of more keeps the
+// dispatcher busy and kernels of other streams wait behind it, so kernels that walk their tiles launch no more than this.
+int resident_groups(gmi_instance* g, const void* kernel, int threads, size_t lds, int64_t* groups);
+}  // namespace gmi
+
 static inline bool valid(gmi_t g) { return g && g->magic == gmi::kMagicInstance; }
 static inline bool valid(gmi_model_t m) { return m && m->magic == gmi::kMagicModel; }
 static inline bool valid(gmi_env_t e) { return e && e->magic == gmi::kMagicEnv; }

@@ -221,3 +221,77 @@ def test_probability_ratio_is_the_accurate_exponential(g, inst, dtype, fused):
     assert np.abs(got / want - 1).max() <= 4e-7, np.abs(got / want - 1)
     g.gmi_buffer_destroy(buf)
     g.gmi_model_destroy(model)
+
+
+def _collecting_sessions(obs, act, hidden, dtype, n, T, cus, seed=9):
+    """The same session with the one-launch collection and with the step-by-step calls, on `cus` compute units (None: all)."""
+    from paper_2206_08482_amd.instances import cu_masks
+    from paper_2206_08482_amd.runner import PPOSession
+    rng = np.random.default_rng(seed)
+    theta = syn.make_model_params(obs, act, hidden, 5, policy_head_scale=0.5)
+    a_mat = (0.9 * np.eye(obs) + 0.01 * rng.standard_normal((obs, obs))).astype(np.float32)
+    b_mat = (0.1 * rng.standard_normal((obs, act))).astype(np.float32)
+    state0 = rng.standard_normal((n, obs)).astype(np.float32)
+    mask = cu_masks(256, [cus])[0] if cus else None
+    return [PPOSession(n_envs=n, obs_dim=obs, act_dim=act, hidden=hidden, horizon=T, dtype=dtype, theta=theta, a_mat=a_mat,
+                       b_mat=b_mat, state0=state0, noise_std=0.01, reward_scale=1.0, done_period=0, cu_mask=mask,
+                       done_threshold=(1 << 32) // 5, seed=11, minibatch=n, fused_rollout=f) for f in (True, False)]
+
+
+@pytest.mark.parametrize("obs,act,hidden,n,T,cus", [
+    (1, 1, [32], 1, 2, None),                  # one env
+    (17, 6, [64, 64], 33, 3, None),            # weights in LDS, a ragged third tile of 16
+    (45, 12, [128, 128], 100, 3, None),        # weights that do not fit LDS
+    (17, 6, [64, 64], 8211, 2, None),          # 32 envs per workgroup, 257 tiles: one workgroup takes two
+    (45, 12, [128, 128], 8211, 2, None),
+    (17, 6, [64, 64], 300, 3, 8),              # ten tiles of 32 on eight compute units
+    (45, 12, [128, 128], 300, 3, 8),
+    (200, 20, [256, 256], 200, 2, 8),          # 32 envs do not fit: thirteen tiles of 16 on eight
+])
+def test_fp32_collection_equals_the_step_by_step_calls(g, obs, act, hidden, n, T, cus):
+    """Both are fp32 arithmetic with sums in orders of their own: 1e-5 as everywhere on this path; done flags exactly."""
+    ses = _collecting_sessions(obs, act, hidden, "f32", n, T, cus)
+    for it in range(2):
+        for s in ses:
+            s.rollout(it)
+            s.sync()
+        assert ses[0].fused_rollout_f32 and not ses[1].fused_rollout_f32
+        ga, gb = (s.buf.to_numpy() for s in ses)
+        assert np.array_equal(ga["done"], gb["done"])
+        for k in ("obs", "act", "logp", "val", "rew"):
+            assert rel_l2(ga[k], gb[k]) <= 1e-5, (it, k, rel_l2(ga[k], gb[k]))
+        assert rel_l2(ses[0].state().cpu().numpy(), ses[1].state().cpu().numpy()) <= 1e-5
+        assert rel_l2(ses[0].last_value.cpu().numpy(), ses[1].last_value.cpu().numpy()) <= 1e-5
+        assert torch.equal(ses[0].episode_step, ses[1].episode_step)
+    for s in reversed(ses):
+        s.close()
+
+
+@pytest.mark.parametrize("obs,act,hidden,n,shift", [
+    (8, 2, [32, 32], 4093, 0), (8, 2, [32, 32], 8195, 1),                 # 32 and 64 rows, weights in LDS
+    (60, 8, [256, 128, 64], 4099, 1), (60, 8, [256, 128, 64], 8193, 0),   # ... and streamed
+    (45, 12, [128, 128], 1, 0), (45, 33, [128, 100], 17, 0),              # 16 rows; a head of three feature tiles
+    (108, 21, [256, 128], 8200, 0), (200, 20, [512, 512], 8200, 0),       # 64 rows do not fit; 32 do not either
+])
+def test_fp32_agent_matches_the_per_layer_path(g, inst, obs, act, hidden, n, shift):
+    dev = torch.device("cuda:0")
+    theta = torch.tensor(syn.make_model_params(obs, act, hidden, 5, policy_head_scale=0.5), device=dev)
+    x = torch.randn(n * obs + shift, generator=torch.Generator().manual_seed(n)).to(dev)[shift:]
+    torch.cuda.synchronize()
+    model = g.gmi_model_bind(inst, g.model_desc(obs, act, list(hidden), g.dtype_code("f32"), n), theta, None)
+    out = {}
+    for fused in (1, 0):
+        g.gmi_set_fusion(inst, fused)
+        o = [torch.full(s, float("nan"), device=dev) for s in ((n, act), (n,), (n,), (n, act), (n,))]
+        torch.cuda.synchronize()
+        g.agent_act(inst, model, x, n, 42, 9, 100, *o[:4])
+        g.agent_value(inst, model, x, n, o[4])
+        g.gmi_sync(inst)
+        out[fused] = [t.cpu().numpy() for t in o]
+    g.gmi_set_fusion(inst, 1)
+    g.gmi_model_destroy(model)
+    for k in range(5):
+        assert np.isfinite(out[1][k]).all()
+        assert rel_l2(out[1][k], out[0][k]) <= 1e-5, (k, rel_l2(out[1][k], out[0][k]))
+        row = np.abs(out[1][k] - out[0][k]).reshape(n, -1).max(axis=1)      # every row on its own
+        assert row.max() <= 1e-4 * np.abs(out[0][k]).max(), (k, int(row.argmax()))
