@@ -8,8 +8,8 @@
 // k chunk use element j of every lane, i.e. k = 16 c + 4 g + j for lane group g (any order of k will do as long as both
 // operands share it); the rows' stride, an odd multiple of 4 floats, spreads the 8 lanes of a read phase over all banks.
 // Weights come straight from the parameter vector (row-major [out, in] at any alignment: a 16-byte load needs 4-byte
-// alignment only), four chunks ahead, or, where they fit beside the activations, from a zero-padded LDS copy made once
-// at the start (WL), so that a layer waits for LDS instead of for L2.
+// alignment only), four chunks ahead, or, where a workgroup passes over them several times, from a zero-padded LDS copy made
+// once at the start (WL), so that a layer waits for LDS instead of for L2.
 //
 // Bound: small models by one launch and a chain of dependent LDS / L2 round trips per layer; large batches by the fp32
 // matrix instruction (157 TFLOP/s).  The one-thread-per-output kernels (mlp.hip) remain for gmi_set_fusion(.., 0) and for
@@ -26,6 +26,8 @@ struct __attribute__((packed, aligned(4))) Float4U { float x, y, z, w; };      /
 
 constexpr int kNT = 512, kNW = kNT / 64;
 constexpr size_t kLdsMax = 160 * 1024;
+constexpr int kGroups = 128;                       // trainer workgroups per net: one per two compute units
+constexpr size_t kSmallWeights = 16 * 1024;
 constexpr int kMaxLayers = GMI_MAX_HIDDEN + 1;
 
 __host__ __device__ __forceinline__ constexpr int pad16(int x) { return (x + 15) & ~15; }
@@ -262,36 +264,34 @@ __device__ __forceinline__ void net_forward(const F32Net& N, int nl, const float
 // ------------------------------------------------------------------------------------------------
 // Action decision: grid (row tiles, nets).
 struct AgentF32Args {
+  const float* obs;
+  int nl, n, obs_dim, act_dim, R, net0, sh, b_floats;
+  uint32_t o_magic;
   F32Net net[2];
   const float* log_std;
-  const float* obs;
-  int nl, n, obs_dim, act_dim, R, net0, sh, w_floats, b_floats;
-  uint32_t o_magic;
   uint32_t k0, k1, step, env_offset;
   float* act; float* logp; float* value; float* mu_out;
 };
 
-template <bool WL>
 __global__ __launch_bounds__(kNT) void agent_f32_kernel(AgentF32Args a) {
   extern __shared__ __attribute__((aligned(16))) float smem[];
   const int net = blockIdx.y + a.net0;
   const F32Net& N = a.net[net];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int R = a.R, O = a.obs_dim, A = a.act_dim, sx0 = rstride(O), so = rstride(A), nba = (A + 3) >> 2;
-  float* s_w = smem;
-  float* s_bias = s_w + (WL ? a.w_floats : 0);
+  float* s_bias = smem;
   float* s_x0 = s_bias + a.b_floats;
   float* s_a = s_x0 + R * sx0;
   float* s_b = s_a + R * a.sh;
   float* s_out = s_b + R * a.sh;
   float* s_lp = s_out + R * so;
   const int r0 = blockIdx.x * R;
-  clear_lds(smem, (WL ? a.w_floats : 0) + a.b_floats, tid, kNT);
+  clear_lds(smem, a.b_floats, tid, kNT);
   stage_rows(R, O, a.o_magic, [&](int r) { return a.obs + (int64_t)min(r0 + r, a.n - 1) * O; }, s_x0, tid);
   __syncthreads();
-  stage_net<WL>(N, a.nl, s_w, s_bias, tid, kNT);
+  stage_net<false>(N, a.nl, smem, s_bias, tid, kNT);
   __syncthreads();
-  net_forward<WL>(N, a.nl, s_w, s_bias, s_x0, sx0, s_a, s_b, a.sh, s_out, so, R / 16, true, wave, kNW, lane);
+  net_forward<false>(N, a.nl, smem, s_bias, s_x0, sx0, s_a, s_b, a.sh, s_out, so, R / 16, true, wave, kNW, lane);
   if (net == 1) {
     for (int r = tid; r < R; r += kNT)
       if (r0 + r < a.n) a.value[r0 + r] = s_out[r * so];
@@ -699,6 +699,7 @@ int max_hidden(const ModelLayout& L) {
   for (int l = 0; l < L.n_hidden; ++l) w = std::max(w, L.net[0][l].out);
   return w;
 }
+
 size_t train_lds(const ModelLayout& L, int R, int w_floats, int b_floats) {
   size_t n = (size_t)w_floats + b_floats;
   int sdz = 0;
@@ -715,11 +716,11 @@ size_t train_lds(const ModelLayout& L, int R, int w_floats, int b_floats) {
 
 namespace gmi {
 
-// Rows of gradient partials that the fp32 trainer kernel may fill: at most 128 (one workgroup per net and compute unit),
-// and no more than about 64 MB of them.
+// Rows of gradient partials that the fp32 trainer kernel may fill: at most one per workgroup of a net, and no more than
+// about 64 MB of them.
 int f32_part_rows(const ModelLayout& L) {
   const int64_t n = ((int64_t)64 << 20) / (4 * L.n_params);
-  return (int)std::min<int64_t>(128, std::max<int64_t>(n, 1));
+  return (int)std::min<int64_t>(kGroups, std::max<int64_t>(n, 1));
 }
 
 int launch_agent_f32(gmi_instance* g, gmi_model* m, const float* obs, int n, uint64_t seed, uint32_t step,
@@ -732,31 +733,30 @@ int launch_agent_f32(gmi_instance* g, gmi_model* m, const float* obs, int n, uin
   a.nl = L.n_layers; a.n = n; a.obs_dim = L.obs_dim; a.act_dim = L.act_dim;
   a.o_magic = magic(L.obs_dim);
   a.sh = rstride(max_hidden(L));
-  a.w_floats = std::max(wf[0], wf[1]);
   a.b_floats = std::max(bf[0], bf[1]);
-  auto lds = [&](int R, bool wl) {
-    return 4 * ((size_t)(wl ? a.w_floats : 0) + a.b_floats +
-                (size_t)R * (rstride(L.obs_dim) + 2 * a.sh + rstride(L.act_dim) + (L.act_dim + 3) / 4));
+  auto lds = [&](int R) {
+    return 4 * (a.b_floats + (size_t)R * (rstride(L.obs_dim) + 2 * a.sh + rstride(L.act_dim) + (L.act_dim + 3) / 4));
   };
-  // the tallest tile that still gives every compute unit a workgroup of each net
+  // the tallest tile that still gives every compute unit a workgroup; 64 rows only where two such tiles share one (45:128:128:12,
+  // where one does not leave room for the next: 107 us with 32 rows, 143 with 64 for 65536 rows, 17.6 / 20.7 for 8192).
+  // us for 16 / 32 / 64 rows: 17:64:64:6 9.1 / 10.4 / 11.5 for 2048, 17.3 / 12.1 / 11.5 for 8192, 97 / 76 / 46 for 65536;
+  // 60:256:128:64:8 19.5 / 23.4 / 35 for 2048, 28 / 24 / 35 for 4096, 51 / 34 / 35 for 8192.
+  // The weights stream from L2: an LDS copy of them per workgroup took 12.4 us instead of 9.1 (2048 rows of 17:64:64:6), 63
+  // instead of 46 (65536).
   int R = 64;
-  while (R > 16 && (lds(R, false) > kLdsMax || (n + R - 1) / R < g->cu_count / 2)) R >>= 1;
-  if (lds(R, false) > kLdsMax) return GMI_ERR_UNSUPPORTED;
-  // the LDS copy of the weights where two workgroups still share a compute unit
-  const bool wl = lds(R, true) <= kLdsMax / 2;
+  while (R > 16 && (lds(R) > (R == 64 ? kLdsMax / 2 : kLdsMax) || (n + R - 1) / R < g->cu_count / 2)) R >>= 1;
+  if (lds(R) > kLdsMax) return GMI_ERR_UNSUPPORTED;
   a.R = R;
   a.net0 = do_policy ? 0 : 1;
   a.log_std = m->params + L.logstd_off;
   a.obs = obs;
   a.k0 = (uint32_t)seed; a.k1 = (uint32_t)(seed >> 32); a.step = step; a.env_offset = env_offset;
   a.act = act; a.logp = logp; a.value = value; a.mu_out = mu_out;
-  static DeviceSet allowed[2];
-  const int rc = allow_lds(wl ? (const void*)agent_f32_kernel<true> : (const void*)agent_f32_kernel<false>, kLdsMax, g->device, &allowed[wl]);
+  static DeviceSet allowed;
+  const int rc = allow_lds((const void*)agent_f32_kernel, kLdsMax, g->device, &allowed);
   if (rc != GMI_OK) return rc;
   ProfScope ps(g, kClsFusedAgent);
-  const dim3 grid((n + R - 1) / R, 2 - a.net0);
-  if (wl) ps.launch(agent_f32_kernel<true>, grid, dim3(kNT), lds(R, true), a);
-  else ps.launch(agent_f32_kernel<false>, grid, dim3(kNT), lds(R, false), a);
+  ps.launch(agent_f32_kernel, dim3((n + R - 1) / R, 2 - a.net0), dim3(kNT), lds(R), a);
   GMI_LAUNCH_CHECK();
   return GMI_OK;
 }
@@ -771,12 +771,17 @@ int launch_train_f32(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo
   a.w_floats = std::max(wf[0], wf[1]);
   a.w_net[0] = wf[0]; a.w_net[1] = wf[1];
   a.b_floats = std::max(bf[0], bf[1]);
-  // the tallest tile that fits and still gives each of the device's compute units a workgroup (not the instance's: replicas
-  // of one model on several instances reduce partials of one common count)
-  int R = 64;
-  while (R > 16 && (train_lds(L, R, 0, a.b_floats) > kLdsMax || (rows + R - 1) / R < 128)) R >>= 1;
+  // the shortest tile with which a workgroup per net and two compute units of the device holds all rows, else the tallest that
+  // fits.  us per minibatch with Adam for 16 / 32 / 64 rows: 17:64:64:6 27.7 / 29.8 / 34 for 2048 rows, 45 / 32 / 35 for 3000,
+  // 61 / 53 / 37 for 6000, 144 / 93 / 62 for 16384; 45:128:128:12 49 / 50 / 64 for 2048, 81 / 54 / 67 for 3000
+  int R = 16;
   if (train_lds(L, R, 0, a.b_floats) > kLdsMax) return GMI_ERR_UNSUPPORTED;
-  const bool wl = train_lds(L, R, a.w_floats, a.b_floats) <= kLdsMax;
+  while (R < 64 && (rows + R - 1) / R > kGroups && train_lds(L, 2 * R, 0, a.b_floats) <= kLdsMax) R *= 2;
+  // an LDS copy of the weights where it serves several tiles (17:64:64:6, 32768 rows: 109 us against 112) or is small enough to
+  // be there before the gather is (8:32:32:2, 9 KB: 20.6 / 21.2 for 256 rows; 20:48:48:4, 20 KB: 24.6 / 23.7 for 1000;
+  // 45:128:128:12, 96 KB: 63 / 49 for 2048)
+  const bool wl = train_lds(L, R, a.w_floats, a.b_floats) <= kLdsMax &&
+                  ((rows + R - 1) / R > kGroups || 4 * (size_t)a.w_floats <= kSmallWeights);
   a.R = R;
   a.nl = L.n_layers; a.rows = rows; a.obs_dim = L.obs_dim; a.act_dim = L.act_dim;
   a.n_tiles = (rows + R - 1) / R;
@@ -835,12 +840,15 @@ extern "C" int rollout_collect_f32(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_bu
                 (size_t)R * (rstride(O) + 4 * a.sh + rstride(A) + rstride(1) + a.o4 + 8 * npr + nba + nbo + 1) +
                 ((R * (O + A) + 3) & ~3) + ((2 * A + 3) & ~3) + (mt ? (size_t)(O + A) * a.o4 : 0));
   };
-  // 32 envs per workgroup once that still gives every compute unit one
-  const int R = (a.n + 31) / 32 >= g->cu_count && lds(32, false, false) <= kLdsMax ? 32 : 16;
+  // 32 envs per workgroup once tiles of 16 are more than the compute units, which hold one workgroup each.  us for 16 steps,
+  // 16 / 32 envs: 17:64:64:6 133 / 159 for 4096 envs, 245 / 159 for 5000; 45:128:128:12 289 / 362, 569 / 360; 60:128:64:8 243 /
+  // 301, 475 / 305
+  const int R = (a.n + 15) / 16 > g->cu_count && lds(32, false, false) <= kLdsMax ? 32 : 16;
   if (lds(R, false, false) > kLdsMax)
     GMI_FAIL(GMI_ERR_UNSUPPORTED, "rollout_collect_f32: a 16-env tile of this model needs %zu bytes of LDS (limit %zu); "
              "use agent_act / env_step / collect_experience", lds(R, false, false), kLdsMax);
-  // what stays on chip for all steps: the networks' weights first (read by every layer), then the simulator's matrix
+  // what stays on chip for all steps: the networks' weights first (read by every layer; 17:64:64:6, 16 steps: 129 us with them,
+  // 153 without), then the simulator's matrix
   const bool wl = lds(R, true, false) <= kLdsMax;
   a.mt_lds = lds(R, wl, true) <= kLdsMax ? 1 : 0;
   const size_t bytes = lds(R, wl, a.mt_lds != 0);

@@ -242,6 +242,7 @@ def _collecting_sessions(obs, act, hidden, dtype, n, T, cus, seed=9):
     (1, 1, [32], 1, 2, None),                  # one env
     (17, 6, [64, 64], 33, 3, None),            # weights in LDS, a ragged third tile of 16
     (45, 12, [128, 128], 100, 3, None),        # weights that do not fit LDS
+    (17, 6, [64, 64], 4113, 2, None),          # the first tiles of 32 envs
     (17, 6, [64, 64], 8211, 2, None),          # 32 envs per workgroup, 257 tiles: one workgroup takes two
     (45, 12, [128, 128], 8211, 2, None),
     (17, 6, [64, 64], 300, 3, 8),              # ten tiles of 32 on eight compute units
