@@ -17,11 +17,10 @@ void fill_model(const gmi_model* m, const float* obs, int n, float* value, Agent
   a->log_std = reinterpret_cast<const float*>(m->shadow + L.sh_logstd);
   a->obs = obs; a->value = value;
   a->vec_obs = ((uintptr_t)obs & 15) == 0 ? 1 : 0;
-  a->T = 1;
 }
 
-int launch_rows(gmi_instance* g, AgentArgs& a, int nets, bool sample, int64_t weight_bytes) {
-  const int wgs = nets * (a.T + (a.value_last ? 1 : 0));      // workgroups per row tile
+// units: nets or, for values_kernel, slots per row tile.
+int launch_rows(gmi_instance* g, AgentArgs& a, int64_t units, bool sample, int64_t weight_bytes) {
   // Rows per workgroup, us for 32 / 64 / 128 rows:
   //   32 while all workgroups are resident at once (two per compute unit): 5000 rows of 108:400:200:100:21 16 / 18;
   //   128 where two such tiles fit a compute unit and there are enough of them: 32768 rows of 45:128:128:12 31 / 20 / 15
@@ -31,13 +30,15 @@ int launch_rows(gmi_instance* g, AgentArgs& a, int nets, bool sample, int64_t we
   //   counts (65536 rows of 200:512:512:300:20: 258 / 228, 20000: 85 / 88);
   //   else 32 (20000 rows of 108:400:200:100:21: 40 / 47).
   const int64_t slots = 2 * (int64_t)g->cu_count;
-  auto groups = [&](int rt) { return (int64_t)((a.n + 32 * rt - 1) / (32 * rt)) * wgs; };
+  auto groups = [&](int rt) { return (int64_t)((a.n + 32 * rt - 1) / (32 * rt)) * units; };
   auto per_cu = [&](int rt) { return (int)(kLdsMax / agent_lds<Bf16>(a, rt, sample)); };
   if (per_cu(1) < 1) return GMI_ERR_UNSUPPORTED;
-  if (groups(1) > slots && per_cu(4) >= 2 && groups(4) >= slots) return launch<Bf16, 4, 4, 2, 4>(g, a, nets, sample);
+  const bool values = a.T > 0;
+  if (groups(1) > slots && per_cu(4) >= 2 && groups(4) >= slots)
+    return values ? launch_slots<Bf16, 4, 4, 2, 4>(g, a) : launch<Bf16, 4, 4, 2, 4>(g, a, (int)units, sample);
   if (groups(1) > slots && (per_cu(2) >= 2 || (per_cu(2) == 1 && weight_bytes > (1 << 20) && groups(1) >= 8 * slots)))
-    return launch<Bf16, 2, 4, 2, 4>(g, a, nets, sample);
-  return launch<Bf16, 1, 8, 1, 4>(g, a, nets, sample);
+    return values ? launch_slots<Bf16, 2, 4, 2, 4>(g, a) : launch<Bf16, 2, 4, 2, 4>(g, a, (int)units, sample);
+  return values ? launch_slots<Bf16, 1, 8, 1, 4>(g, a) : launch<Bf16, 1, 8, 1, 4>(g, a, (int)units, sample);
 }
 
 }  // namespace
@@ -62,19 +63,19 @@ int launch_agent(gmi_instance* g, gmi_model* m, const float* obs, int n, uint64_
 
 int launch_values(gmi_instance* g, gmi_model* m, const float* obs, int T, int n, int64_t ld, float* value, const float* obs_last,
                   float* value_last) {
-  constexpr int kSlots = 32768;      // slots of a launch (grid limit)
-  for (int t0 = 0; t0 < T; t0 += kSlots) {
+  const int per = std::max(1, (1 << 30) / ((n + 31) / 32) - 1);      // slots of a launch: its items are a 32-bit count
+  for (int t0 = 0; t0 < T; t0 += per) {
     AgentArgs a = {};
     a.obs_step = ld * m->L.obs_dim; a.val_step = ld;
     fill_model(m, obs + t0 * a.obs_step, n, value + t0 * a.val_step, &a);
     a.net0 = 1;
-    a.T = std::min(T - t0, kSlots);
+    a.T = std::min(T - t0, per);
     if (a.T > 1 && (a.obs_step & 3) != 0) a.vec_obs = 0;
     if (t0 + a.T == T) {
       a.obs_last = obs_last; a.value_last = value_last;
       if (((uintptr_t)obs_last & 15) != 0) a.vec_obs = 0;
     }
-    const int rc = launch_rows(g, a, 1, false, m->L.weight_bytes);
+    const int rc = launch_rows(g, a, a.T + (a.value_last ? 1 : 0), false, m->L.weight_bytes);
     if (rc != GMI_OK) return rc;
   }
   return GMI_OK;

@@ -45,9 +45,9 @@ struct AgentArgs {
   uint32_t o_magic, pad_magic, k0, k1, step, env_offset;
   const float *log_std, *obs;
   float *act, *logp, *value, *mu_out;      // act NULL: means and values only
-  // Values of several steps at once (net0 = 1): blockIdx.z = t < T reads obs + t obs_step and writes value + t val_step,
-  // t = T reads obs_last and writes value_last.
-  int T;
+  // values_kernel: slot t < T reads obs + t obs_step and writes value + t val_step, slot T reads obs_last and writes value_last;
+  // item = slot * tiles + row tile.
+  int T, tiles, items;
   int64_t obs_step, val_step;
   const float* obs_last;
   float* value_last;
@@ -227,6 +227,46 @@ __device__ __forceinline__ void net_layers(const AgentLayer* N, int nl, Ring<P, 
   }
 }
 
+// The workgroup's observation rows into LDS (rows of K0 elements).  They are rows * O consecutive floats at src; 16-byte pieces
+// of them may span two rows.
+template <class P, int RT, int NW>
+__device__ __forceinline__ void stage_obs(const AgentArgs& a, int K0, const float* src, int rows, unsigned char* s_x, int tid) {
+  constexpr int R = 32 * RT, kNT = 64 * NW;
+  const int O = a.O, S0 = K0 * P::size + 16;
+  const int cnt = rows * O, n4 = a.vec_obs ? cnt >> 2 : 0;
+  for (int e0 = tid; e0 < n4; e0 += 4 * kNT) {
+    float4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = reinterpret_cast<const float4*>(src)[min(e0 + u * kNT, n4 - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int e = 4 * min(e0 + u * kNT, n4 - 1);
+      int r = div_magic(e, a.o_magic), c = e - r * O;
+      if ((O & 3) == 0) {
+        P::store4(s_x + r * S0 + c * P::size, v[u].x, v[u].y, v[u].z, v[u].w);
+      } else {
+        const float q[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          P::store1(s_x + r * S0 + c * P::size, q[i]);
+          if (++c == O) { c = 0; ++r; }
+        }
+      }
+    }
+  }
+  for (int e = 4 * n4 + tid; e < cnt; e += kNT) {
+    const int r = div_magic(e, a.o_magic);
+    P::store1(s_x + r * S0 + (e - r * O) * P::size, src[e]);
+  }
+  // padding columns, and rows past the end (never stored: any finite value will do)
+  const int np = K0 - O;
+  for (int e = tid; e < np * R; e += kNT) {
+    const int r = div_magic(e, a.pad_magic);
+    P::store1(s_x + r * S0 + (O + e - r * np) * P::size, 0.f);
+  }
+  for (int e = rows * (S0 >> 4) + tid; e < R * (S0 >> 4); e += kNT) reinterpret_cast<uint4*>(s_x)[e] = make_uint4(0u, 0u, 0u, 0u);
+}
+
 // D: weight blocks in flight per wave; MT: most row tiles of an item; WPS: waves per SIMD (registers); NW: waves.
 template <class P, int RT, int D, int MT, int WPS, int NW>
 __global__ __launch_bounds__(64 * NW, WPS) void agent_kernel(AgentArgs a) {
@@ -235,7 +275,7 @@ __global__ __launch_bounds__(64 * NW, WPS) void agent_kernel(AgentArgs a) {
   const int net = a.net0 + blockIdx.y;
   const AgentLayer* N = a.l[net];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nl = a.nl, O = a.O, K0 = N[0].K, S0 = K0 * P::size + 16;
+  const int nl = a.nl, K0 = N[0].K;
   const int ho = net == 0 ? a.A : 1, nb = a.act ? (a.A + 3) >> 2 : 0;          // head outputs; blocks of 4 actions
   float4* s_noise = reinterpret_cast<float4*>(s_x + a.f_off);                  // [R][nb]
   float* s_bias = reinterpret_cast<float*>(s_noise + R * nb);                  // of all layers, one after the other
@@ -248,43 +288,7 @@ __global__ __launch_bounds__(64 * NW, WPS) void agent_kernel(AgentArgs a) {
   if constexpr (P::bias_lds)
 #pragma unroll
     for (int u = 0; u < 4; ++u) bv[u] = N[0].bias[min(tid + u * kNT, a.bias_floats - 1)];
-  // the tile's observations are rows * O consecutive floats; 16-byte pieces of them may span two rows
-  {
-    const int t = blockIdx.z;
-    const float* src = (t < a.T ? a.obs + t * a.obs_step : a.obs_last) + (int64_t)r0 * O;
-    const int cnt = rows * O, n4 = a.vec_obs ? cnt >> 2 : 0;
-    for (int e0 = tid; e0 < n4; e0 += 4 * kNT) {
-      float4 v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = reinterpret_cast<const float4*>(src)[min(e0 + u * kNT, n4 - 1)];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int e = 4 * min(e0 + u * kNT, n4 - 1);
-        int r = div_magic(e, a.o_magic), c = e - r * O;
-        if ((O & 3) == 0) {
-          P::store4(s_x + r * S0 + c * P::size, v[u].x, v[u].y, v[u].z, v[u].w);
-        } else {
-          const float q[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            P::store1(s_x + r * S0 + c * P::size, q[i]);
-            if (++c == O) { c = 0; ++r; }
-          }
-        }
-      }
-    }
-    for (int e = 4 * n4 + tid; e < cnt; e += kNT) {
-      const int r = div_magic(e, a.o_magic);
-      P::store1(s_x + r * S0 + (e - r * O) * P::size, src[e]);
-    }
-    // padding columns, and rows past the end (never stored: any finite value will do)
-    const int np = K0 - O;
-    for (int e = tid; e < np * R; e += kNT) {
-      const int r = div_magic(e, a.pad_magic);
-      P::store1(s_x + r * S0 + (O + e - r * np) * P::size, 0.f);
-    }
-    for (int e = rows * (S0 >> 4) + tid; e < R * (S0 >> 4); e += kNT) reinterpret_cast<uint4*>(s_x)[e] = make_uint4(0u, 0u, 0u, 0u);
-  }
+  stage_obs<P, RT, NW>(a, K0, a.obs + (int64_t)r0 * a.O, rows, s_x, tid);
   request<P, RT, D, MT, NW>(wq, N[0], wave, lane);
   if constexpr (P::bias_lds) {
 #pragma unroll
@@ -304,9 +308,7 @@ __global__ __launch_bounds__(64 * NW, WPS) void agent_kernel(AgentArgs a) {
   net_layers<P, RT, D, MT, NW, false>(N, nl, wq, s_x, s_x + a.y_off, s_x, s_bias, s_head, ho, wave, lane);
 
   if (net == 1) {
-    const int t = blockIdx.z;
-    float* dst = t < a.T ? a.value + t * a.val_step : a.value_last;
-    for (int r = tid; r < rows; r += kNT) dst[r0 + r] = s_head[r];
+    for (int r = tid; r < rows; r += kNT) a.value[r0 + r] = s_head[r];
     return;
   }
   if (!a.act) {      // the means alone
@@ -339,6 +341,30 @@ __global__ __launch_bounds__(64 * NW, WPS) void agent_kernel(AgentArgs a) {
   }
 }
 
+// Values of several steps at once, items one after the other: a collection's values would be thousands of workgroups (4096 envs
+// and 32 steps: 4224, on 64 compute units in the four-agent pipeline), and a launch that its compute units cannot hold keeps
+// kernels of other streams waiting.  The next item's first weights are on their way while the present one ends.
+template <class P, int RT, int D, int MT, int WPS>
+__global__ __launch_bounds__(512, WPS) void values_kernel(AgentArgs a) {
+  static_assert(!P::bias_lds, "no room for biases in this layout");
+  constexpr int R = 32 * RT, kNT = 512;
+  extern __shared__ __attribute__((aligned(16))) unsigned char s_x[];
+  const AgentLayer* N = a.l[1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  float* s_head = reinterpret_cast<float*>(s_x + a.f_off);
+  Ring<P, D> wq;
+  request<P, RT, D, MT, 8>(wq, N[0], wave, lane);
+  for (int item = blockIdx.x; item < a.items; item += gridDim.x) {
+    const int t = item / a.tiles, r0 = (item - t * a.tiles) * R, rows = min(R, a.n - r0);
+    stage_obs<P, RT, 8>(a, N[0].K, (t < a.T ? a.obs + t * a.obs_step : a.obs_last) + (int64_t)r0 * a.O, rows, s_x, tid);
+    __syncthreads();
+    // ends with a barrier: the rows may be replaced; s_head is written again behind the next pass's first barrier
+    net_layers<P, RT, D, MT, 8, true>(N, a.nl, wq, s_x, s_x + a.y_off, s_x, nullptr, s_head, 1, wave, lane);
+    float* dst = t < a.T ? a.value + t * a.val_step : a.value_last;
+    for (int r = tid; r < rows; r += kNT) dst[r0 + r] = s_head[r];
+  }
+}
+
 // Lays out the LDS of a tile of 32 rt rows and returns its bytes; sample: with the draws and log-density terms (else means only).
 template <class P>
 size_t agent_lds(AgentArgs& a, int rt, bool sample) {
@@ -362,7 +388,26 @@ int launch(gmi_instance* g, AgentArgs& a, int nets, bool sample) {
   const int rc = gmi::allow_lds((const void*)agent_kernel<P, RT, D, MT, WPS, NW>, kLdsMax, g->device, &allowed);
   if (rc != GMI_OK) return rc;
   gmi::ProfScope ps(g, gmi::kClsFusedAgent);
-  ps.launch(agent_kernel<P, RT, D, MT, WPS, NW>, dim3((a.n + 32 * RT - 1) / (32 * RT), nets, a.T + (a.value_last ? 1 : 0)), dim3(64 * NW), lds, a);
+  ps.launch(agent_kernel<P, RT, D, MT, WPS, NW>, dim3((a.n + 32 * RT - 1) / (32 * RT), nets), dim3(64 * NW), lds, a);
+  GMI_LAUNCH_CHECK();
+  return GMI_OK;
+}
+
+template <class P, int RT, int D, int MT, int WPS>
+int launch_slots(gmi_instance* g, AgentArgs& a) {
+  const size_t lds = agent_lds<P>(a, RT, false);
+  const void* kernel = (const void*)values_kernel<P, RT, D, MT, WPS>;
+  static gmi::DeviceSet allowed;
+  int rc = gmi::allow_lds(kernel, kLdsMax, g->device, &allowed);
+  if (rc != GMI_OK) return rc;
+  int64_t resident = 1;
+  rc = gmi::resident_groups(g, kernel, 512, lds, &resident);
+  if (rc != GMI_OK) return rc;
+  a.tiles = (a.n + 32 * RT - 1) / (32 * RT);
+  a.items = a.tiles * (a.T + (a.value_last ? 1 : 0));
+  const int64_t rounds = (a.items + resident - 1) / resident;
+  gmi::ProfScope ps(g, gmi::kClsFusedAgent);
+  ps.launch(values_kernel<P, RT, D, MT, WPS>, dim3((unsigned)((a.items + rounds - 1) / rounds)), dim3(512), lds, a);
   GMI_LAUNCH_CHECK();
   return GMI_OK;
 }

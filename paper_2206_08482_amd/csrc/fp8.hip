@@ -206,7 +206,7 @@ extern "C" int agent_act_fp8(gmi_t g, gmi_fp8_t w, const float* obs, int32_t n_r
   if (!obs || !act || !logp || !value) GMI_FAIL(GMI_ERR_INVALID_ARG, "agent_act_fp8: NULL pointer");
   if (g->device != w->device) GMI_FAIL(GMI_ERR_INVALID_ARG, "agent_act_fp8: instance and weights live on different devices");
   const ModelLayout& L = w->L;
-  AgentArgs a;
+  AgentArgs a = {};
   float* mu_ws = reinterpret_cast<float*>(w->base + w->mu_off);
   const float* scale = reinterpret_cast<const float*>(w->base + w->scale_off);
   for (int net = 0; net < 2; ++net)
@@ -219,7 +219,6 @@ extern "C" int agent_act_fp8(gmi_t g, gmi_fp8_t w, const float* obs, int32_t n_r
   a.n = n_rows; a.O = L.obs_dim; a.A = L.act_dim;
   a.vec_obs = ((uintptr_t)obs & 15) == 0 ? 1 : 0;
   a.lp_blocks = 0;
-  a.T = 1; a.obs_step = a.val_step = 0; a.obs_last = nullptr; a.value_last = nullptr;
   a.k0 = (uint32_t)seed; a.k1 = (uint32_t)(seed >> 32); a.step = step; a.env_offset = env_offset;
   a.log_std = reinterpret_cast<const float*>(w->base + w->logstd_off);
   a.obs = obs; a.act = act; a.logp = logp; a.value = value; a.mu_out = mu;

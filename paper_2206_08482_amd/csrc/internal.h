@@ -76,8 +76,8 @@ namespace gmi {
 //           4 linear_bf16_kernel<1,4,1,2,*> (128x64)
 //   role    0 forward hidden layer (bias + ELU)   1 forward head   2 input gradient (ELU')
 // (kClsGae covers gae_kernel and normalize_kernel, kClsLinearF32 the three fp32 epilogues, kClsFusedAgent the
-// one-launch agent forward of a model: agent_kernel, or the forward-only row-tile kernel where use_tile_forward
-// says so.)
+// one-launch agent forward of a model: agent_kernel, values_kernel for the values of a collection, or the forward-only
+// row-tile kernel where use_tile_forward says so.)
 enum KernelClass {
   kClsGather = 0, kClsWgrad, kClsLoss, kClsAdam, kClsShadowTranspose, kClsEnvStep, kClsSample,
   kClsCollect, kClsGae, kClsPermutation, kClsFusedAgent, kClsFusedRollout,

@@ -296,3 +296,25 @@ def test_fp32_agent_matches_the_per_layer_path(g, inst, obs, act, hidden, n, shi
         assert rel_l2(out[1][k], out[0][k]) <= 1e-5, (k, rel_l2(out[1][k], out[0][k]))
         row = np.abs(out[1][k] - out[0][k]).reshape(n, -1).max(axis=1)      # every row on its own
         assert row.max() <= 1e-4 * np.abs(out[0][k]).max(), (k, int(row.argmax()))
+
+
+@pytest.mark.parametrize("obs,act,hidden,n,T", [
+    (45, 12, [128, 128], 600, 3),              # values: 128 rows per workgroup, 20 items on eight compute units
+    (107, 21, [400, 200, 100], 600, 3),        # 32 rows, 76 items
+    (60, 8, [256, 256], 161, 1),               # the last value alone beside one step
+])
+def test_values_of_a_collection_on_few_compute_units(g, obs, act, hidden, n, T):
+    """The values of all slots come from workgroups that the instance's compute units hold, each taking several items:
+    bit for bit those of the step-by-step calls."""
+    ses = _collecting_sessions(obs, act, hidden, "bf16", n, T, 8)
+    for it in range(2):
+        for s in ses:
+            s.rollout(it)
+            s.sync()
+        assert ses[0].fused_rollout and not ses[1].fused_rollout
+        ga, gb = (s.buf.to_numpy() for s in ses)
+        for k in ("obs", "act", "logp", "val", "rew", "done"):
+            assert np.array_equal(ga[k], gb[k]), (it, k)
+        assert torch.equal(ses[0].last_value, ses[1].last_value)
+    for s in reversed(ses):
+        s.close()
