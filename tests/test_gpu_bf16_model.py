@@ -23,7 +23,8 @@ TOL_MODEL_MAX = 3e-3   # the same, largest element error over largest element (a
 TOL16 = 2e-2
 
 
-@pytest.mark.parametrize("name,n", [("C2", 4096), ("C3", 777), ("C4", 5000), ("SH", 700), ("C2", 33)])
+@pytest.mark.parametrize("name,n", [("C2", 4096), ("C3", 777), ("C4", 5000), ("SH", 700), ("C2", 33),
+                                    ("C4", 12289), ("SH", 12301)])      # the row-tile forward kernel
 @pytest.mark.parametrize("fused", [True, False])
 def test_agent_forward_matches_the_bf16_error_model(g, inst, name, n, fused):
     g.gmi_set_fusion(inst, 1 if fused else 0)

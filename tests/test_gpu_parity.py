@@ -242,7 +242,7 @@ def _theta_and_batch(cfg, T, N, seed=1):
     ("C2", 4, 512, 2048, "bf16", "bimodal"), ("C2", 3, 500, 1111, "bf16", "bimodal"),
     ("C3", 2, 1024, 2048, "bf16", "bimodal"), ("C4", 2, 700, 1400, "bf16", "bimodal"),
     ("C2", 4, 512, 2048, "bf16", "straddle"),
-    # large-tile kernels (rows >= 8192), ragged against their 256-row tiles
+    # the per-layer path's large-tile kernels (rows >= 8192), ragged against their 256-row tiles
     ("C4", 2, 4200, 8400, "bf16", "bimodal"), ("C3", 3, 3000, 8999, "bf16", "bimodal"),
     ("C2", 2, 8192, 16384, "bf16", "bimodal"),
     # the paper's Table 6 model shapes under their own layer orders
@@ -252,8 +252,9 @@ def _theta_and_batch(cfg, T, N, seed=1):
 @pytest.mark.parametrize("path", ["chain", "layers"])
 def test_gradient_and_stats_match_oracle(g, inst, name, T, N, rows, dtype, ratios, path):
     """path: which trainer kernels compute forward, loss and input gradients: "chain" the one-launch kernels (the
-    register-chained kernel or, for the 512-wide shapes, the row-tile kernel; the library's default for the model
-    shapes they are compiled for), "layers" the per-layer kernels.
+    library's default: the resident kernel, or beyond its rows -- use_resident -- the register-chained kernel or, for the
+    512-wide shapes, the row-tile kernel; of these cases C3's 8999 and C4's 8400 rows.  The others just beyond those rows:
+    test_gradient_of_the_compiled_trainer_kernels_at_ragged_rows), "layers" the per-layer kernels.
     ratios = "straddle": old/new probability ratios spread smoothly across the clip range, so some
     samples sit within rounding distance of a clip boundary.  Which side such a sample falls on is a
     yes/no decision taken in the arithmetic of the forward pass; in fp32 both sides agree, in bf16 a
@@ -262,7 +263,7 @@ def test_gradient_and_stats_match_oracle(g, inst, name, T, N, rows, dtype, ratio
     inside or well outside the clip range, so the decisions agree and the comparison measures the
     arithmetic of the products alone."""
     if path == "chain" and (dtype == "f32" or name == "C1"):
-        pytest.skip("the register-chained kernel covers the bf16 benchmark shapes")
+        pytest.skip("one launch of a model this small: compared with the per-layer path in test_gpu_row_tile_kernels.py")
     fused = path != "layers"
     g.gmi_set_fusion(inst, {"chain": 1, "layers": 0}[path])
     cfg = syn.get_config(name)
@@ -472,7 +473,8 @@ def test_rollout_collect_equals_the_step_by_step_calls(g, name, n_envs, horizon,
     (same kernels' arithmetic, same Philox counters): every array it leaves must be identical, over two
     iterations in a row (state, episode counters and step offsets carry over), ragged last tile included.
     (6000 envs: more 16-env tiles than compute units, so a workgroup takes several tiles in turn.  C4 and SH: models
-    beyond the one-launch kernel's size limit, collected with two launches per step.)"""
+    beyond the one-launch kernel's size limit, collected with two launches per step, the first of them the agent kernel at
+    these sizes; the row-tile forward kernel: test_two_launch_collection_through_the_row_tile_kernel.)"""
     import dataclasses
     cfg = syn.get_config(name)
     if prob_inv:

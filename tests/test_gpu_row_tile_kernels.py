@@ -93,6 +93,7 @@ def test_gradient_equals_the_per_layer_kernels(g, inst, obs, act, hidden, dtype,
     (30, 5, [64] * 8, 100, 0),                # the most layers
     (211, 20, [512, 512, 256, 128], 12293, 0),      # row-tile forward kernel: rows gathered 16 at a time, ragged last ones
     (211, 20, [512, 512, 256, 128], 12293, 1),      # ... row by row (not 16-byte aligned)
+    (211, 20, [512, 512, 512, 256], 12287, 0), (211, 20, [512, 512, 512, 256], 12307, 0),      # the same two kernels, widest shape
 ])
 def test_agent_kernel_matches_the_per_layer_path(g, inst, obs, act, hidden, n, shift):
     """Both paths round the same activations to bf16 after sums in another order: an activation may land on the other
@@ -316,5 +317,23 @@ def test_values_of_a_collection_on_few_compute_units(g, obs, act, hidden, n, T):
         for k in ("obs", "act", "logp", "val", "rew", "done"):
             assert np.array_equal(ga[k], gb[k]), (it, k)
         assert torch.equal(ses[0].last_value, ses[1].last_value)
+    for s in reversed(ses):
+        s.close()
+
+
+@pytest.mark.parametrize("hidden", [[512, 512, 256, 128], [512, 512, 512, 256]])
+def test_two_launch_collection_through_the_row_tile_kernel(g, hidden):
+    """From 12288 envs on the 512-wide models collect through the forward-only row-tile kernel, as agent_act does: bit for
+    bit the step-by-step calls, a ragged last tile included."""
+    ses = _collecting_sessions(211, 20, hidden, "bf16", 12341, 2, None)
+    for it in range(2):
+        for s in ses:
+            s.rollout(it)
+            s.sync()
+        assert ses[0].fused_rollout and not ses[1].fused_rollout
+        ga, gb = (s.buf.to_numpy() for s in ses)
+        for k in ("obs", "act", "logp", "val", "rew", "done"):
+            assert np.array_equal(ga[k], gb[k]), (it, k)
+        assert torch.equal(ses[0].state(), ses[1].state()) and torch.equal(ses[0].last_value, ses[1].last_value)
     for s in reversed(ses):
         s.close()
