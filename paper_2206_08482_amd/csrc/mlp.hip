@@ -371,10 +371,10 @@ __global__ __launch_bounds__(128 * WRN) void linear_bf16_big_kernel(gmi::LinearB
 // features) delivers operands.  Bias gradients are row sums of the first operand (two-element dot products with ones).
 //
 // Bound: HBM / L2 traffic.  A tile reads 1 KiB per row; with 128 x 128 tiles (through registers, transposed there) the
-// same features were fetched by twice as many workgroups, whose second and third rounds found them evicted: 690 MB per
+// same features were fetched by twice as many workgroups, whose second and third rounds found them evicted: 616 MB per
 // 32768-row minibatch of 211:512:512:256:128:20 for 403 MB of operands.  All workgroups now run in one round with at most
 // one per compute unit, and half as many splits are enough (their partials are another 6 MB each, written here and read
-// by Adam).  Measured on that minibatch: 145 us before, now 97 (388 MB fetched).
+// by Adam).  Measured on that minibatch: 145 us before, now 94 (467 MB fetched, 52 written).
 constexpr int kWgradT = 256;                            // features per operand and tile
 constexpr int kWgradRows = 32;                          // rows per stage
 constexpr int kWgradOperand = kWgradT * kWgradRows * 2; // bytes
@@ -836,7 +836,7 @@ int launch_wgrad(gmi_instance* g, int dtype, int rows, int n_split, int chunk, W
     GMI_LAUNCH_CHECK();
     return GMI_OK;
   }
-  // problems 0 .. n / 2 - 1 are the policy net's layers, the rest the value net's (one net alone: all of them, net 1 empty)
+  // problems 0 .. n / 2 - 1 are the policy net's layers, the rest the value net's (one problem alone: net 0 is empty)
   const int half = b.n >> 1;
   b.net_tiles[0] = b.net_tiles[1] = 0;
   for (int i = 0; i < b.n; ++i) {
