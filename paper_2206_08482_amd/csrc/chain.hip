@@ -168,11 +168,11 @@ void fill_chain_emit(const ModelLayout& L, ChainEmit* ce) {
 // Gather of the minibatch rows idx[0..rows) of buffer b + forward + loss + input gradients.
 // Leaves m->h, m->dz ready for the weight-gradient launch and one row of statistics / log_std partials per
 // tile in m->stat_part (*n_stat_rows rows, the layout of the loss kernel's per-workgroup rows).  GMI_ERR_UNSUPPORTED (no message) if no kernel is compiled for this shape.
-int prepare_obs16(gmi_instance* g, gmi_model* m, gmi_buffer* b, int rows, bool* ready) {
+int prepare_obs16(gmi_instance* g, gmi_model* m, gmi_buffer* b, int rows, int cus, bool* ready) {
   const ModelLayout& L = m->L;
   *ready = false;
   if (!b->obs16 || g->fusion < 1 || L.dtype != GMI_DTYPE_BF16 || L.sh_chain_bytes == 0 || L.act_dim > 32 ||
-      use_resident(L, rows) || !compiled_x16(L))
+      use_resident(L, rows, cus) || !compiled_x16(L))
     return GMI_OK;
   const int64_t B = (int64_t)b->d.horizon * b->d.n_envs;
   const int rc = launch_gather_to(g, m, b->d.obs, b->d.n_envs, b->d.ld_envs, nullptr, (int)B, nullptr, b->obs16);

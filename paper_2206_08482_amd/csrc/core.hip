@@ -157,6 +157,7 @@ extern "C" int gmi_create(const uint32_t* cu_mask, uint32_t n_words, int device,
   g->device = device;
   g->stream = stream;
   g->cu_count = cu_count;
+  g->device_cus = n_cu;
   g->prof_mask = 0;
   g->fusion = 1;
   hipError_t e = hipEventCreateWithFlags(&g->event, hipEventDisableTiming);

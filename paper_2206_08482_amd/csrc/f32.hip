@@ -26,7 +26,6 @@ struct __attribute__((packed, aligned(4))) Float4U { float x, y, z, w; };      /
 
 constexpr int kNT = 512, kNW = kNT / 64;
 constexpr size_t kLdsMax = 160 * 1024;
-constexpr int kGroups = 128;                       // trainer workgroups per net: one per two compute units
 constexpr size_t kSmallWeights = 16 * 1024;
 constexpr int kMaxLayers = GMI_MAX_HIDDEN + 1;
 
@@ -720,7 +719,7 @@ namespace gmi {
 // about 64 MB of them.
 int f32_part_rows(const ModelLayout& L) {
   const int64_t n = ((int64_t)64 << 20) / (4 * L.n_params);
-  return (int)std::min<int64_t>(kGroups, std::max<int64_t>(n, 1));
+  return (int)std::min<int64_t>(trainer_groups(INT32_MAX), std::max<int64_t>(n, 1));
 }
 
 int launch_agent_f32(gmi_instance* g, gmi_model* m, const float* obs, int n, uint64_t seed, uint32_t step,
@@ -762,7 +761,7 @@ int launch_agent_f32(gmi_instance* g, gmi_model* m, const float* obs, int n, uin
 }
 
 int launch_train_f32(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_hparams* hp, const int32_t* idx, int rows,
-                     int* n_parts) {
+                     int cus, int* n_parts) {
   const ModelLayout& L = m->L;
   if (L.dtype != GMI_DTYPE_F32 || L.n_params >= (1ll << 31)) return GMI_ERR_UNSUPPORTED;
   TrainF32Args a;
@@ -771,17 +770,18 @@ int launch_train_f32(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo
   a.w_floats = std::max(wf[0], wf[1]);
   a.w_net[0] = wf[0]; a.w_net[1] = wf[1];
   a.b_floats = std::max(bf[0], bf[1]);
-  // the shortest tile with which a workgroup per net and two compute units of the device holds all rows, else the tallest that
+  // the shortest tile with which a workgroup per net and two compute units holds all rows, else the tallest that
   // fits.  us per minibatch with Adam for 16 / 32 / 64 rows: 17:64:64:6 27.7 / 29.8 / 34 for 2048 rows, 45 / 32 / 35 for 3000,
   // 61 / 53 / 37 for 6000, 144 / 93 / 62 for 16384; 45:128:128:12 49 / 50 / 64 for 2048, 81 / 54 / 67 for 3000
+  const int most = trainer_groups(cus);
   int R = 16;
   if (train_lds(L, R, 0, a.b_floats) > kLdsMax) return GMI_ERR_UNSUPPORTED;
-  while (R < 64 && (rows + R - 1) / R > kGroups && train_lds(L, 2 * R, 0, a.b_floats) <= kLdsMax) R *= 2;
+  while (R < 64 && (rows + R - 1) / R > most && train_lds(L, 2 * R, 0, a.b_floats) <= kLdsMax) R *= 2;
   // an LDS copy of the weights where it serves several tiles (17:64:64:6, 32768 rows: 109 us against 112) or is small enough to
   // be there before the gather is (8:32:32:2, 9 KB: 20.6 / 21.2 for 256 rows; 20:48:48:4, 20 KB: 24.6 / 23.7 for 1000;
   // 45:128:128:12, 96 KB: 63 / 49 for 2048)
   const bool wl = train_lds(L, R, a.w_floats, a.b_floats) <= kLdsMax &&
-                  ((rows + R - 1) / R > kGroups || 4 * (size_t)a.w_floats <= kSmallWeights);
+                  ((rows + R - 1) / R > most || 4 * (size_t)a.w_floats <= kSmallWeights);
   a.R = R;
   a.nl = L.n_layers; a.rows = rows; a.obs_dim = L.obs_dim; a.act_dim = L.act_dim;
   a.n_tiles = (rows + R - 1) / R;
@@ -801,7 +801,7 @@ int launch_train_f32(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo
   a.clip = hp->clip; a.c_v = hp->c_v;
   a.part = m->grad_part; a.part_stride = L.n_params;
   a.stat_part = m->stat_part;
-  const int groups = std::min(a.n_tiles, m->part_rows);
+  const int groups = std::min(a.n_tiles, std::min(most, m->part_rows));
   static DeviceSet allowed[2];
   const int rc = allow_lds(wl ? (const void*)train_f32_kernel<true> : (const void*)train_f32_kernel<false>, kLdsMax, g->device, &allowed[wl]);
   if (rc != GMI_OK) return rc;

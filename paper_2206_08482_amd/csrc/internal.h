@@ -97,7 +97,8 @@ struct gmi_instance {
   hipStream_t stream;
   hipEvent_t event;      // used by gmi_transfer
   hipEvent_t wait_event; // used by gmi_wait_stream
-  int cu_count;
+  int cu_count;          // compute units of the instance's mask
+  int device_cus;        // of the device
   int fusion;            // 1: use the row-tile fused kernels where the model fits them (default)
   uint32_t prof_mask;    // bit c set: launches of kernel class c carry timing events
   gmi::ProfSlot prof[gmi::kClsCount];
@@ -314,16 +315,25 @@ int launch_values(gmi_instance* g, gmi_model* m, const float* obs, int T, int n,
 int launch_agent_f32(gmi_instance* g, gmi_model* m, const float* obs, int n, uint64_t seed, uint32_t step,
                      uint32_t env_offset, float* act, float* logp, float* value, float* mu_out, bool do_policy);
 // Forward, loss, backward and weight gradients of a minibatch: *n_parts rows of m->grad_part and of m->stat_part.
+// cus: the compute units that the launch may count on, here and below (trainer_cus).
 int launch_train_f32(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_hparams* hp, const int32_t* idx, int rows,
-                     int* n_parts);
+                     int cus, int* n_parts);
 int f32_part_rows(const ModelLayout& L);
 // The resident trainer kernel (resident.hip): forward, loss and backward of a minibatch.  *n_parts > 0: the weight
 // gradients too, as that many rows of m->grad_part; 0: activations and gradients left row-major in m->h, m->dz.
 int launch_train_resident(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_hparams* hp, const int32_t* idx, int rows,
-                          int* n_parts, int* n_stat_rows);
+                          int cus, int* n_parts, int* n_stat_rows);
 bool resident_supported(const ModelLayout& L);
 int resident_part_rows(const ModelLayout& L);
-bool use_resident(const ModelLayout& L, int rows);
+bool use_resident(const ModelLayout& L, int rows, int cus);
+// Compute units of instance g when n instances train at once: its own, but no more than its share of the device.
+static inline int trainer_cus(const gmi_instance* g, int n) {
+  const int share = g->device_cus / n;
+  return g->cu_count < share ? g->cu_count : (share > 0 ? share : 1);
+}
+// Trainer workgroups per net of the resident and fp32 kernels: one per two compute units.
+static inline int trainer_groups(int cus) { return cus >= 2 ? (cus < 256 ? cus / 2 : 128) : 1; }
+
 bool chain_compiled(const ModelLayout& L);       // a register-chained or row-tile trainer kernel has this shape
 
 // Shuffles of epochs epoch0 .. epoch0 + n_epochs - 1 into out[e][n], one launch.
@@ -384,7 +394,7 @@ int launch_train_chain(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_p
                        int* n_stat_rows, bool obs16_ready, bool* blocks);
 // Before the minibatches of an update: converts all observations of the buffer into b->obs16 if the chained kernel
 // will run and cannot read the fp32 rows itself.  *ready = whether it did.
-int prepare_obs16(gmi_instance* g, gmi_model* m, gmi_buffer* b, int rows, bool* ready);
+int prepare_obs16(gmi_instance* g, gmi_model* m, gmi_buffer* b, int rows, int cus, bool* ready);
 
 }  // namespace gmi
 

@@ -34,7 +34,6 @@ constexpr int kNT = 512, kNW = 8;
 constexpr int kMaxLayers = GMI_MAX_HIDDEN + 1;
 constexpr size_t kLdsMax = 160 * 1024;
 constexpr int kDzStride = 32 + 8;           // head gradient rows
-constexpr int kMaxGroupsA = 128;            // workgroups per net with gradients in registers: one per two compute units
 
 struct ResLayer {
   const uint4* wf;         // fragment-major W: operand blocks of the forward product
@@ -586,16 +585,16 @@ int grad_sets(const ModelLayout& L) {
   return blocks <= kNW ? 1 : (blocks <= 2 * kNW ? 2 : 0);
 }
 
-// The row tiles per workgroup for `rows` rows: the fewest with which kMaxGroupsA workgroups per net hold them all, else as
-// many as fit LDS (and the compiled variants).
-int pick_tiles(const ModelLayout& L, int64_t rows, Plan* p) {
+// The row tiles per workgroup for `rows` rows: the fewest with which `groups` workgroups per net hold them all, else as many as
+// fit LDS (and the compiled variants).
+int pick_tiles(const ModelLayout& L, int64_t rows, int groups, Plan* p) {
   int RT = 0;
   for (int rt = 1; rt <= (grad_sets(L) > 0 ? 4 : 2); rt <<= 1) {
     Plan q;
     if (!plan_lds(L, rt, &q)) break;
     *p = q;
     RT = rt;
-    if (rows <= 32 * (int64_t)rt * kMaxGroupsA) break;
+    if (rows <= 32 * (int64_t)rt * groups) break;
   }
   return RT;
 }
@@ -617,30 +616,34 @@ namespace gmi {
 
 bool resident_supported(const ModelLayout& L) { return shape_ok(L); }
 // Where a register-chained or row-tile kernel is compiled for the shape, this kernel is the faster one while every tile has a
-// workgroup of its own (one per net and two compute units; 128-row tiles with the gradients in registers, else 64 or, where
-// only those fit LDS, 32).  Per minibatch with Adam, us, this kernel / the compiled one:
+// workgroup of its own (one per net and two of the instance's compute units; 128-row tiles with the gradients in registers,
+// else 64 or, where only those fit LDS, 32).  Per minibatch with Adam, us, this kernel / the compiled one:
 //   60:256:128:64:8 (128 rows): 34.7 / 45.5 at 1000 rows, 48.5 / 50.8 at 8192, 56.6 / 57.1 at 16384, 91.9 / 89.9 at 32768;
-//   108:400:200:100:21 (64): 49.8 / 64.1 at 1000, 55.4 / 68.5 at 4096, 68.6 / 74.6 at 8192, 117 / 98 at 16384;
-//   211:512:512:256:128:20 (32): 81.9 / 98.1 at 1000, 91.7 / 107.4 at 4096, 137 / 113 at 6000, 145 / 119 at 8192;
+//     on 64 compute units 39 / 52 at 1024, 52 / 66 at 4096, 117 / 72 at 8192; on 128 46 / 53 at 4096, 53 / 56 at 8192;
+//   108:400:200:100:21 (64): 49.8 / 64.1 at 1000, 55.4 / 68.5 at 4096, 68.6 / 74.6 at 8192, 117 / 98 at 16384; on 64
+//     compute units 67 / 83 at 1024, 81 / 88 at 2048, 143 / 95 at 4096;
+//   211:512:512:256:128:20 (32): 81.9 / 98.1 at 1000, 91.7 / 107.4 at 4096, 137 / 113 at 6000, 145 / 119 at 8192; on 64
+//     compute units 134 / 151 at 1024, 184 / 159 at 2048;
 //   211:512:512:512:256:20 (32): 101 / 124 at 1000, 114 / 135 at 4096, 184 / 153 at 8192.
-bool use_resident(const ModelLayout& L, int rows) {
+bool use_resident(const ModelLayout& L, int rows, int cus) {
   if (!shape_ok(L)) return false;
   Plan p;
-  return !chain_compiled(L) || rows <= 32 * (int64_t)pick_tiles(L, INT32_MAX, &p) * kMaxGroupsA;
+  return !chain_compiled(L) || rows <= 32 * (int64_t)pick_tiles(L, INT32_MAX, 1, &p) * trainer_groups(cus);
 }
 
 // Rows of gradient partials the kernel may fill with this model.
 int resident_part_rows(const ModelLayout& L) {
-  return shape_ok(L) && grad_sets(L) > 0 ? kMaxGroupsA : 0;
+  return shape_ok(L) && grad_sets(L) > 0 ? trainer_groups(INT32_MAX) : 0;
 }
 
 int launch_train_resident(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_hparams* hp, const int32_t* idx, int rows,
-                          int* n_parts, int* n_stat_rows) {
+                          int cus, int* n_parts, int* n_stat_rows) {
   const ModelLayout& L = m->L;
   if (!shape_ok(L) || rows < 1 || rows > m->max_rows) return GMI_ERR_UNSUPPORTED;
   const int NS = grad_sets(L);
   Plan p;
-  const int RT = pick_tiles(L, rows, &p);
+  const int groups = trainer_groups(cus);
+  const int RT = pick_tiles(L, rows, groups, &p);
   ResArgs a;
   a.nl = L.n_layers; a.rows = rows; a.obs_dim = L.obs_dim; a.act_dim = L.act_dim;
   a.n_envs = b->d.n_envs; a.ld_envs = b->d.ld_envs;
@@ -686,7 +689,7 @@ int launch_train_resident(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gm
   a.stat_part = m->stat_part;
   int grid;
   if (NS > 0) {
-    const int rounds = (a.n_tiles + kMaxGroupsA - 1) / kMaxGroupsA;
+    const int rounds = (a.n_tiles + groups - 1) / groups;
     grid = (a.n_tiles + rounds - 1) / rounds;
     if (grid > m->part_rows) return GMI_ERR_UNSUPPORTED;
   } else {

@@ -127,7 +127,7 @@ __device__ __forceinline__ void adam_step(float g, float& m, float& v, float& w,
 // Gradient partials of the trainer instances whose replicas are reduced into one update (one entry for an
 // ordinary single-instance update): per instance [n_split, part_stride] weight partials and the loss
 // kernel's [n_stat, kStatStride + A] statistics partials.  The counts are the replica's own: they follow from the path
-// its instance takes (gmi_set_fusion).
+// its instance takes (gmi_set_fusion, compute units).
 constexpr int kMaxGroup = 16;
 struct Partials {
   const float *part, *stat;      // stat NULL: a caller-supplied gradient
@@ -516,22 +516,23 @@ int layers_pass(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_hpar
 }
 
 // Forward + loss (+ backward products) of the `rows` samples idx[0..rows) of the buffer.
-// Leaves gradient partials in m->grad_part / m->stat_part.  Returns the split count through n_split.
+// Leaves gradient partials in m->grad_part / m->stat_part; their numbers of rows follow from the path, and with that from
+// the instance's switch and compute units.
 int minibatch_pass(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_hparams* hp, const int32_t* idx,
-                   int rows, bool want_grad, int* n_split_out, int* n_loss_blocks_out, bool obs16_ready = false) {
+                   int rows, int cus, bool want_grad, int* n_split_out, int* n_loss_blocks_out, bool obs16_ready = false) {
   const ModelLayout& L = m->L;
   const bool bf = L.dtype == GMI_DTYPE_BF16;
   int rc = GMI_ERR_UNSUPPORTED;
   bool blocks = false;
   if (g->fusion >= 1 && want_grad && !bf) {
     // fp32: everything up to the gradient partials in one launch
-    rc = gmi::launch_train_f32(g, m, b, hp, idx, rows, n_split_out);
+    rc = gmi::launch_train_f32(g, m, b, hp, idx, rows, cus, n_split_out);
     if (rc == GMI_OK) { *n_loss_blocks_out = *n_split_out; return GMI_OK; }
     if (rc != GMI_ERR_UNSUPPORTED) return rc;
   }
-  if (g->fusion >= 1 && want_grad && bf && gmi::use_resident(L, rows)) {
+  if (g->fusion >= 1 && want_grad && bf && gmi::use_resident(L, rows, cus)) {
     // the tile's activations resident in LDS; small nets' weight gradients in the same launch
-    rc = gmi::launch_train_resident(g, m, b, hp, idx, rows, n_split_out, n_loss_blocks_out);
+    rc = gmi::launch_train_resident(g, m, b, hp, idx, rows, cus, n_split_out, n_loss_blocks_out);
     if (rc == GMI_OK && *n_split_out > 0) return GMI_OK;
   }
   if (rc == GMI_ERR_UNSUPPORTED && g->fusion >= 1 && want_grad && bf) {
@@ -630,7 +631,8 @@ extern "C" int ppo_update(gmi_t g, gmi_model_t m, gmi_buffer_t b, const gmi_ppo_
   const int nmb = (int)(B / hp->minibatch);
   uint32_t k = hp->adam_step0;
   bool obs16 = false;
-  rc = gmi::prepare_obs16(g, m, b, hp->minibatch, &obs16);
+  const int cus = gmi::trainer_cus(g, 1);
+  rc = gmi::prepare_obs16(g, m, b, hp->minibatch, cus, &obs16);
   if (rc != GMI_OK) return rc;
   for (int e = 0; e < hp->epochs; ++e) {
     // the shuffles of up to kPermEpochs epochs in one launch (each launch of this small kernel is mostly latency)
@@ -642,7 +644,8 @@ extern "C" int ppo_update(gmi_t g, gmi_model_t m, gmi_buffer_t b, const gmi_ppo_
     }
     for (int j = 0; j < nmb; ++j) {
       int n_split = 1, nlb = 1;
-      rc = minibatch_pass(g, m, b, hp, perm + (int64_t)j * hp->minibatch, hp->minibatch, true, &n_split, &nlb, obs16);
+      rc = minibatch_pass(g, m, b, hp, perm + (int64_t)j * hp->minibatch, hp->minibatch, cus, true, &n_split, &nlb,
+                          obs16);
       if (rc != GMI_OK) return rc;
       ++k;
       rc = launch_adam(g, &m, 1, &n_split, &nlb, hp, hp->minibatch, k,
@@ -696,7 +699,7 @@ extern "C" int ppo_update_group(const gmi_t* gs, const gmi_model_t* ms, const gm
   // theirs alone, but the shared parameters were last written on stream 0): nothing to order before the loop.
   bool obs16[kMaxGroup];
   for (int i = 0; i < n; ++i) {
-    rc = gmi::prepare_obs16(gs[i], ms[i], bs[i], hp->minibatch, &obs16[i]);
+    rc = gmi::prepare_obs16(gs[i], ms[i], bs[i], hp->minibatch, gmi::trainer_cus(gs[i], n), &obs16[i]);
     if (rc != GMI_OK) return rc;
   }
   for (int e = 0; e < hp->epochs; ++e) {
@@ -711,8 +714,8 @@ extern "C" int ppo_update_group(const gmi_t* gs, const gmi_model_t* ms, const gm
     for (int j = 0; j < nmb; ++j) {
       int n_split[kMaxGroup], nlb[kMaxGroup];
       for (int i = 0; i < n; ++i) {
-        rc = minibatch_pass(gs[i], ms[i], bs[i], hp, bs[i]->perm + perm_off + (int64_t)j * hp->minibatch, hp->minibatch, true,
-                            &n_split[i], &nlb[i], obs16[i]);
+        rc = minibatch_pass(gs[i], ms[i], bs[i], hp, bs[i]->perm + perm_off + (int64_t)j * hp->minibatch, hp->minibatch,
+                            gmi::trainer_cus(gs[i], n), true, &n_split[i], &nlb[i], obs16[i]);
         if (rc != GMI_OK) return rc;
         // replica i's partials are complete: let instance 0 see them
         if (i > 0) {
@@ -754,7 +757,7 @@ extern "C" int ppo_evaluate(gmi_t g, gmi_model_t m, gmi_buffer_t b, const gmi_pp
   if (rc != GMI_OK) return rc;
   if (!stats_out) GMI_FAIL(GMI_ERR_INVALID_ARG, "ppo_evaluate: stats_out is NULL");
   int n_split = 0, nlb = 1;
-  rc = minibatch_pass(g, m, b, hp, idx, n, false, &n_split, &nlb);
+  rc = minibatch_pass(g, m, b, hp, idx, n, gmi::trainer_cus(g, 1), false, &n_split, &nlb);
   if (rc != GMI_OK) return rc;
   return launch_adam(g, &m, 1, &n_split, &nlb, hp, n, 1, stats_out, nullptr, false);
 }
@@ -765,7 +768,7 @@ extern "C" int ppo_gradient(gmi_t g, gmi_model_t m, gmi_buffer_t b, const gmi_pp
   if (rc != GMI_OK) return rc;
   if (!grad_out) GMI_FAIL(GMI_ERR_INVALID_ARG, "ppo_gradient: grad_out is NULL");
   int n_split = 1, nlb = 1;
-  rc = minibatch_pass(g, m, b, hp, idx, n, true, &n_split, &nlb);
+  rc = minibatch_pass(g, m, b, hp, idx, n, gmi::trainer_cus(g, 1), true, &n_split, &nlb);
   if (rc != GMI_OK) return rc;
   return launch_adam(g, &m, 1, &n_split, &nlb, hp, n, 1, stats_out, grad_out, false);
 }

@@ -143,6 +143,22 @@ def test_the_resident_kernel_serves_the_last_rows_it_is_faster_at(g, inst, name,
     assert np.isfinite(got_g).all()
 
 
+@pytest.mark.parametrize("name,rows,cus,compiled", [("C2", 4096, 64, False), ("C2", 4099, 64, True), ("C3", 1024, 32, False),
+                                                    ("C3", 1029, 32, True), ("C4", 512, 32, False), ("C4", 515, 32, True)])
+def test_the_trainer_kernel_follows_the_compute_units_of_the_instance(g, name, rows, cus, compiled):
+    """The resident kernel serves a compiled shape while each of its tiles has a workgroup of its own: on 64 compute units
+    a quarter of the rows that the whole device takes."""
+    from paper_2206_08482_amd.instances import cu_masks
+    masked = g.gmi_create(cu_masks(256, [cus])[0])
+    (shape, (got_g, _), args), launches, flops = _stated_work(
+        g, masked, "chain_train", lambda: _gradient_case(g, masked, name, 2, (rows + 1) // 2, rows))
+    assert launches == 1 and (flops > 0) == compiled
+    _, m_grad = bm.ppo_loss_and_grad(*args)
+    assert rel_l2(got_g, m_grad) <= TOL_MODEL, rel_l2(got_g, m_grad)
+    _per_tensor(shape, got_g, m_grad, 2 * TOL_MODEL)
+    g.gmi_destroy(masked)
+
+
 def test_gradient_of_a_benchmark_sized_minibatch_c4(g, inst):
     """32768 rows of the largest workload's model, the launch configuration the benchmark times (512 workgroups
     of the trainer kernel, every row split of the weight-gradient kernel), against the fp32 oracle and the

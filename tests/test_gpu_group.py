@@ -198,15 +198,15 @@ def test_group_error_paths(g):
         s.close()
 
 
-@pytest.mark.parametrize("fusion", [(0, 1), (1, 0)])
+@pytest.mark.parametrize("fusion,cus", [((0, 1), None), ((1, 0), None), ((1, 1), (64, 128))])
 @pytest.mark.parametrize("obs,act,hidden,dtype,n_envs,horizon", [
     (17, 6, (64, 64), "f32", 512, 8),             # one-launch minibatch: 128 partial rows; per-layer: 32
     (45, 12, (128, 128), "bf16", 1000, 4),        # gradients in registers: 125 partial rows; per-layer: 32
     (60, 8, (256, 128, 64), "bf16", 4200, 4),     # a compiled kernel: the same counts either way
     (108, 21, (400, 200, 100), "bf16", 300, 2)])  # activations to memory: the same splits, 19 statistics rows against 3
-def test_group_of_instances_with_different_fusion_settings(g, obs, act, hidden, dtype, n_envs, horizon, fusion):
-    """gmi_set_fusion is a switch per instance, and the two settings leave different numbers of partial gradients and
-    statistics rows: every replica's rows have to enter the mean.  One minibatch of a whole buffer per replica; after
+def test_group_of_instances_that_leave_different_numbers_of_partials(g, obs, act, hidden, dtype, n_envs, horizon, fusion, cus):
+    """gmi_set_fusion is a switch per instance and so is the set of compute units; both decide how many partial gradients and
+    statistics rows a replica leaves: every replica's rows have to enter the mean.  One minibatch of a whole buffer per replica; after
     the first Adam step m = (1 - beta1) g, so adam_m is compared as the gradient (a replica that loses rows moves it by
     tens of per cent)."""
     cfg = syn.get_config("C1", obs_dim=obs, act_dim=act, hidden=hidden, n_envs=n_envs, horizon=horizon, dtype=dtype,
@@ -216,7 +216,9 @@ def test_group_of_instances_with_different_fusion_settings(g, obs, act, hidden, 
     bufs = _oracle_collect(cfg, shape, theta, env, states, n_envs, horizon)
     z = np.zeros_like(theta)
     _, r_m, _, _, r_stats = oppo.ppo_update_group(theta, z, z, 0, shape, bufs, hp, env.seed, 0)
-    ses = _sessions(g, cfg, 2, n_envs, horizon, cfg.minibatch, dtype, theta, env, states)
+    from paper_2206_08482_amd.instances import cu_masks
+    masks = cu_masks(256, cus) if cus else None
+    ses = _sessions(g, cfg, 2, n_envs, horizon, cfg.minibatch, dtype, theta, env, states, masks)
     for s, b, f in zip(ses, bufs, fusion):
         g.gmi_set_fusion(s.gmi, f)
         for k in ("obs", "act", "logp", "val", "rew", "done", "adv", "ret"):

@@ -79,6 +79,27 @@ def test_gradient_equals_the_per_layer_kernels(g, inst, obs, act, hidden, dtype,
     g.gmi_model_destroy(model)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("obs,act,hidden,rows", [(45, 12, (128, 128), 3001), (17, 6, (64, 64), 700), (8, 2, (32, 32), 130),
+                                                 (44, 18, (300, 200, 200), 1500)])
+def test_gradient_on_eight_compute_units_equals_the_per_layer_kernels(g, obs, act, hidden, rows, dtype):
+    """Four workgroups per net, each with several tiles."""
+    from paper_2206_08482_amd.instances import cu_masks
+    masked = g.gmi_create(cu_masks(256, [8])[0])
+    N = (rows + 1) // 2
+    model, buf, keep = _setup(g, masked, obs, act, hidden, dtype, 2, N, rows)
+    n = keep[0].numel()
+    a, sa = _gradients(g, masked, model, buf, n, 2, N, rows, 1)
+    b, sb = _gradients(g, masked, model, buf, n, 2, N, rows, 0)
+    tol = 1e-5 if dtype == "f32" else 5e-3          # as on the whole device, above
+    assert rel_l2(a, b) <= tol, rel_l2(a, b)
+    assert rel_max(a, b) <= 4 * tol, rel_max(a, b)
+    assert np.allclose(sa, sb, rtol=tol, atol=tol)
+    g.gmi_buffer_destroy(buf)
+    g.gmi_model_destroy(model)
+    g.gmi_destroy(masked)
+
+
 @pytest.mark.parametrize("obs,act,hidden,n,shift", [
     (1, 1, [32], 1, 0),                       # one column, one action, one row
     (45, 12, [128, 128], 31, 0),              # rows of an odd length: 16-byte pieces span two rows
