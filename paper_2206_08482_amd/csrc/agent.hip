@@ -51,7 +51,7 @@ int launch_agent(gmi_instance* g, gmi_model* m, const float* obs, int n, uint64_
                  float* act, float* logp, float* value, float* mu_out, bool do_policy) {
   const ModelLayout& L = m->L;
   if (L.dtype != GMI_DTYPE_BF16) return GMI_ERR_UNSUPPORTED;
-  if (use_tile_forward(m, n)) return GMI_ERR_UNSUPPORTED;
+  if (use_tile_forward(g, m, n)) return GMI_ERR_UNSUPPORTED;
   AgentArgs a = {};
   fill_model(m, obs, n, value, &a);
   a.net0 = do_policy ? 0 : 1;

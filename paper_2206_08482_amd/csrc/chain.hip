@@ -249,9 +249,12 @@ bool has_tile_forward(const ModelLayout& L) {
 }
 
 // agent_act with the one-launch agent kernel / with gather, this kernel and the sampling kernel, us: 211:512:512:256:128:20
-// 18 / 42 for 1 row, 34 / 56 for 8192, 52 / 63 for 12000, 68 / 65 for 16384; 211:512:512:512:256:20 22 / 52, 45 / 69,
-// 67 / 72, 90 / 77.
-bool use_tile_forward(const gmi_model* m, int rows) { return rows >= 12288 && has_tile_forward(m->L); }
+// 34 / 46 for 8192 rows, 49 / 50 for 11000, 51.5 / 49 for 12288, 66 / 54 for 16384, on 64 compute units 27 / 41 for 2048,
+// 39 / 43 for 3072, 51 / 43 for 4096, 96 / 78 for 8192, on 16 39 / 42 for 768, 50 / 43 for 1024; 211:512:512:512:256:20 47 / 57
+// for 8192 rows, 68 / 61 for 12288, on 64 compute units 51 / 53 for 3072, 66 / 54 for 4096, on 16 51 / 52 for 768, 66 / 53 for 1024.
+bool use_tile_forward(const gmi_instance* g, const gmi_model* m, int rows) {
+  return rows >= 48 * (int64_t)g->cu_count && has_tile_forward(m->L);
+}
 
 bool forward_chain_reads_x0(const gmi_model* m, const float* obs) {
   return !(m->L.obs_dim % 4 == 0 && ((uintptr_t)obs & 15) == 0);
@@ -262,7 +265,7 @@ bool forward_chain_reads_x0(const gmi_model* m, const float* obs) {
 int launch_forward_chain(gmi_instance* g, gmi_model* m, const float* obs, int n_rows, float* mu, float* val,
                          bool x0_valid) {
   const ModelLayout& L = m->L;
-  if (n_rows < 1 || n_rows > m->max_rows || !use_tile_forward(m, n_rows)) return GMI_ERR_UNSUPPORTED;
+  if (n_rows < 1 || n_rows > m->max_rows || !use_tile_forward(g, m, n_rows)) return GMI_ERR_UNSUPPORTED;
   int rc;
   ChainArgs a = {};
   for (int net = 0; net < 2; ++net) {

@@ -360,9 +360,9 @@ void fill_chain_emit(const ModelLayout& L, ChainEmit* ce);
 // net only) and values into val.  GMI_ERR_UNSUPPORTED (no message) where use_tile_forward says no.
 int launch_forward_chain(gmi_instance* g, gmi_model* m, const float* obs, int n_rows, float* mu, float* val,
                          bool x0_valid = false);
-// Whether such a kernel is compiled for the shape / is the faster one for that many rows (else launch_agent).
+// Whether such a kernel is compiled for the shape / is the faster one for that many rows on that instance (else launch_agent).
 bool has_tile_forward(const ModelLayout& L);
-bool use_tile_forward(const gmi_model* m, int rows);
+bool use_tile_forward(const gmi_instance* g, const gmi_model* m, int rows);
 // Whether that kernel would read the bf16 rows m->x0 (made by the gather kernel) instead of obs itself.
 bool forward_chain_reads_x0(const gmi_model* m, const float* obs);
 // The collection stage for the models too large for the one-launch rollout kernel: per step the forward-only kernel

@@ -259,7 +259,7 @@ int rollout_stepwise(gmi_instance* g, gmi_model* m, gmi_env* env, gmi_buffer* b,
   const int64_t ld = bd.ld_envs;
   const int o_pad = gmi::pad32(O);
   if (!has_tile_forward(L)) return GMI_ERR_UNSUPPORTED;
-  const bool tile = use_tile_forward(m, n);      // as agent_act decides
+  const bool tile = use_tile_forward(g, m, n);      // as agent_act decides
   for (int t = 0; t < T; ++t) {
     const float* cur = t == 0 ? obs : bd.obs + (int64_t)t * ld * O;
     float* nxt = t == T - 1 ? obs : bd.obs + (int64_t)(t + 1) * ld * O;

@@ -342,15 +342,21 @@ def test_values_of_a_collection_on_few_compute_units(g, obs, act, hidden, n, T):
         s.close()
 
 
+@pytest.mark.parametrize("n,cus,tile", [(12341, None, True), (12287, None, False), (777, 16, True), (767, 16, False)])
 @pytest.mark.parametrize("hidden", [[512, 512, 256, 128], [512, 512, 512, 256]])
-def test_two_launch_collection_through_the_row_tile_kernel(g, hidden):
-    """From 12288 envs on the 512-wide models collect through the forward-only row-tile kernel, as agent_act does: bit for
-    bit the step-by-step calls, a ragged last tile included."""
-    ses = _collecting_sessions(211, 20, hidden, "bf16", 12341, 2, None)
+def test_two_launch_collection_through_the_row_tile_kernel(g, hidden, n, cus, tile):
+    """From 48 envs per compute unit on (12288 on the whole device) the 512-wide models collect through the forward-only
+    row-tile kernel, as agent_act does: bit for bit the step-by-step calls, a ragged last tile included.  Of the class's
+    kernels only that one states its work."""
+    ses = _collecting_sessions(211, 20, hidden, "bf16", n, 2, cus)
+    cls = [g.gmi_profile_class_name(c) for c in range(g.gmi_profile_classes())].index("fused_agent")
     for it in range(2):
         for s in ses:
+            g.gmi_profile_enable(s.gmi, 1 << cls)
             s.rollout(it)
             s.sync()
+            assert (g.gmi_profile_work(s.gmi, cls)[0] > 0) == tile
+            g.gmi_profile_enable(s.gmi, 0)
         assert ses[0].fused_rollout and not ses[1].fused_rollout
         ga, gb = (s.buf.to_numpy() for s in ses)
         for k in ("obs", "act", "logp", "val", "rew", "done"):
