@@ -286,7 +286,7 @@ __device__ __forceinline__ void scr_to_global(const char* scr, int lane, uint16_
   for (int it = 0; it < 32 / RPI; ++it) {
     const int r = it * RPI + lane / LPR, ch = lane % LPR;
     const uint4 v = *reinterpret_cast<const uint4*>(scr + r * kScrStride + ch * 16);
-    *reinterpret_cast<uint4*>(dst + (int64_t)(row0 + r) * ld + col0 + ch * 8) = v;     // arrays hold whole tiles
+    gmi::store_through(dst + (int64_t)row0 * ld + col0, (uint32_t)(r * ld + ch * 8) * 2, v);     // arrays hold whole tiles
   }
 }
 template <int GS>
@@ -514,7 +514,7 @@ __device__ __forceinline__ void item_compute(Ctx<S>& c, const ChainArgs& a) {
     const int r = it * RPI + c.lane / LPR, ch = c.lane % LPR;
     uint16_t* dst = bwd ? a.dz[c.net][layer - 1] : a.h[c.net][layer + 1];
     constexpr int ld = bwd ? D.d[layer] : D.d[layer + 1];
-    *reinterpret_cast<uint4*>(dst + (int64_t)(c.row0 + r) * ld + 32 * pi.tile0 + ch * 8) = pre;    // arrays hold whole tiles
+    gmi::store_through(dst + (int64_t)c.row0 * ld + 32 * pi.tile0, (uint32_t)(r * ld + ch * 8) * 2, pre);    // arrays hold whole tiles
   }
 }
 // Item I with the read of item I + 1 issued ahead of it -- except the first store step's, which reads what the

@@ -654,8 +654,8 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
       for (int j = 0; j < 2; ++j) {
         const int it = (i0 >> 5) + xt0 + j;
         if (j < nx)
-          *reinterpret_cast<float4*>(dst + P.w_off + (((int64_t)ot * n_it + it) * 4 + q) * 256 + lane * 4) =
-              make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+          gmi::store_through(dst + P.w_off + (((int64_t)ot * n_it + it) * 4 + q) * 256, lane * 16,
+                             acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
       }
     }
     if (do_bias) {

@@ -172,7 +172,7 @@ __device__ __forceinline__ void rows_out(const uint16_t* src, int width, int R, 
 #pragma unroll 2
   for (int r = wave * rpw + rl; r < R; r += kNW * rpw)
     for (int c = c0; c < np; c += lpr)
-      *reinterpret_cast<uint4*>(dst + (int64_t)r * width + 8 * c) = *reinterpret_cast<const uint4*>(src + r * (width + 8) + 8 * c);
+      gmi::store_through(dst, (uint32_t)(r * width + 8 * c) * 2, *reinterpret_cast<const uint4*>(src + r * (width + 8) + 8 * c));
 }
 
 template <int RT, int NS>
@@ -498,8 +498,8 @@ __global__ __launch_bounds__(kNT) void train_resident_kernel(ResArgs a) {
 #pragma unroll
             for (int j = 0; j < 2; ++j)
               if (ib + j < n_it)
-                *reinterpret_cast<float4*>(part + L.w_par + ((((ob + i) * n_it + ib + j) * 4 + q) << 8) + lane * 4) =
-                    make_float4(gw[n][i][j][4 * q], gw[n][i][j][4 * q + 1], gw[n][i][j][4 * q + 2], gw[n][i][j][4 * q + 3]);
+                gmi::store_through(part + L.w_par + ((((ob + i) * n_it + ib + j) * 4 + q) << 8), lane * 16,
+                                   gw[n][i][j][4 * q], gw[n][i][j][4 * q + 1], gw[n][i][j][4 * q + 2], gw[n][i][j][4 * q + 3]);
           }
         if (ib == 0) {
 #pragma unroll

@@ -163,6 +163,9 @@ __device__ __forceinline__ void read_x(Ctx<S>& c) {
 // 32 rows x 16 bytes per load or store instruction; as blocks every access is 1 KiB contiguous.)
 __device__ __forceinline__ int64_t block_word(int tr, int nks, int ks, int rt) { return (((int64_t)tr * nks + ks) * 4 + rt) * 64; }
 
+// One block to memory for the weight-gradient kernel.
+__device__ __forceinline__ void store_block(uint4* blk, int lane, const uint4& v) { gmi::store_through(blk, lane * 16, v); }
+
 // Stored activations h[layer] of tile T = a * RT + b of this wave (input-gradient epilogue of segment SEG): the
 // lane's own slots of the blocks (2 ft, b) and (2 ft + 1, b), i.e. the values at the positions of its 16 results.
 template <class S, int SEG, int T>
@@ -204,7 +207,7 @@ __device__ __forceinline__ void aux_op(Ctx<S>& c, const ChainArgs& a) {
     if constexpr (I == G::RT) {
       c.sx[KS & 1] = c.X[(KS * 4 + c.wave) * 64 + c.lane];
     } else if constexpr (KS >= 1) {
-      (store_x_array<S, SEG>(c, a) + block_word(blockIdx.x, G::NKS, KS - 1, c.wave))[c.lane] = c.sx[(KS - 1) & 1];      // arrays hold whole tiles
+      store_block(store_x_array<S, SEG>(c, a) + block_word(blockIdx.x, G::NKS, KS - 1, c.wave), c.lane, c.sx[(KS - 1) & 1]);      // arrays hold whole tiles
     }
   }
 }
@@ -386,8 +389,8 @@ __device__ __forceinline__ void loss_epilogue(Ctx<S>& c, const ChainArgs& a, con
   c.X[(1 * 4 + c.wave) * 64 + c.lane] = make_uint4(w[4], w[5], w[6], w[7]);
   {
     uint4* arr = reinterpret_cast<uint4*>(a.dz[c.net][S::NL - 1]);
-    (arr + block_word(blockIdx.x, 2, 0, c.wave))[c.lane] = make_uint4(w[0], w[1], w[2], w[3]);      // arrays hold whole tiles
-    (arr + block_word(blockIdx.x, 2, 1, c.wave))[c.lane] = make_uint4(w[4], w[5], w[6], w[7]);
+    store_block(arr + block_word(blockIdx.x, 2, 0, c.wave), c.lane, make_uint4(w[0], w[1], w[2], w[3]));      // arrays hold whole tiles
+    store_block(arr + block_word(blockIdx.x, 2, 1, c.wave), c.lane, make_uint4(w[4], w[5], w[6], w[7]));
   }
   // workgroup sums -> this tile's row of the statistics partials
   __syncthreads();
@@ -469,7 +472,7 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
     if constexpr (G::XD > 1) read_x<S, SEG, 1>(c);
     k_steps<S, SEG, 0>(c, a, wseg);
     if constexpr (G::store_x)
-      (store_x_array<S, SEG>(c, a) + block_word(blockIdx.x, G::NKS, G::NKS - 1, c.wave))[c.lane] = c.sx[(G::NKS - 1) & 1];
+      store_block(store_x_array<S, SEG>(c, a) + block_word(blockIdx.x, G::NKS, G::NKS - 1, c.wave), c.lane, c.sx[(G::NKS - 1) & 1]);
     issue_first_weights<S, SEG + 1>(c);
     __syncthreads();                       // every wave is done with the layer's input
     // this lane's loss inputs: cold loads, issued where a long stretch of arithmetic follows and no younger load is
@@ -489,7 +492,7 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
       uint4* arr = reinterpret_cast<uint4*>(a.dz[c.net][G::layer - 1]);
 #pragma unroll 8
       for (int ks = 0; ks < G::F / 16; ++ks)
-        (arr + block_word(blockIdx.x, G::F / 16, ks, c.wave))[c.lane] = c.X[(ks * 4 + c.wave) * 64 + c.lane];      // arrays hold whole tiles
+        store_block(arr + block_word(blockIdx.x, G::F / 16, ks, c.wave), c.lane, c.X[(ks * 4 + c.wave) * 64 + c.lane]);      // arrays hold whole tiles
     }
     run_segment<S, SEG + 1>(c, a);
   }
