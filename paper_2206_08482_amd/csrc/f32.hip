@@ -8,13 +8,15 @@
 // k chunk use element j of every lane, i.e. k = 16 c + 4 g + j for lane group g (any order of k will do as long as both
 // operands share it); the rows' stride, an odd multiple of 4 floats, spreads the 8 lanes of a read phase over all banks.
 // Weights come straight from the parameter vector (row-major [out, in] at any alignment: a 16-byte load needs 4-byte
-// alignment only), four chunks ahead, or, where a workgroup passes over them several times, from a zero-padded LDS copy made
-// once at the start (WL), so that a layer waits for LDS instead of for L2.
+// alignment only), four chunks ahead; the collection, which passes over them every step, keeps a zero-padded LDS copy where it
+// fits (WL).
 //
-// Bound: small models by one launch and a chain of dependent LDS / L2 round trips per layer; large batches by the fp32
-// matrix instruction (157 TFLOP/s).  The one-thread-per-output kernels (mlp.hip) remain for gmi_set_fusion(.., 0) and for
-// models whose 16-row tile does not fit LDS; against them agent_act of
-// 60:256:128:64:8 with 2048 rows takes 19 us instead of 468, an iteration of 17:64:64:6 with 512 envs 0.77 ms instead of 3.95.
+// Bound: small models by the instructions of one pass -- a wave fetches straight-line code at about a byte per cycle, so that
+// every 8-byte instruction costs 8 cycles whatever it does -- and by the latencies between them; large batches by the fp32
+// matrix instruction (157 TFLOP/s).  Requesting a layer's weights during the epilogue before it, or staging them into LDS,
+// takes more instructions than the waits it saves (agent_act of 60:256:128:64:8 with 2048 rows 35 and 19 us instead of 15).
+// The one-thread-per-output kernels (mlp.hip) remain for gmi_set_fusion(.., 0) and for models whose 16-row tile does not fit
+// LDS; against them agent_act of 60:256:128:64:8 with 2048 rows takes 15 us instead of 468.
 #include <algorithm>
 
 #include "rollout.h"
@@ -26,128 +28,188 @@ struct __attribute__((packed, aligned(4))) Float4U { float x, y, z, w; };      /
 
 constexpr int kNT = 512, kNW = kNT / 64;
 constexpr size_t kLdsMax = 160 * 1024;
-constexpr size_t kSmallWeights = 16 * 1024;
 constexpr int kMaxLayers = GMI_MAX_HIDDEN + 1;
 
 __host__ __device__ __forceinline__ constexpr int pad16(int x) { return (x + 15) & ~15; }
 __host__ __device__ __forceinline__ constexpr int rstride(int width) { return pad16(width) + 4; }      // floats of an LDS row
 
 struct F32Layer {
-  const float* w;      // [out, in]
-  const float* b;      // [out]
   int in, out;
-  int w_off, b_off;    // floats from the start of the parameter vector
-  uint32_t in_magic;
+  int w_off, b_off;          // floats from the start of the parameter vector: W [out, in], b [out]
+  uint32_t piece_magic;      // of the 16-byte pieces of a padded row of W
+  uint32_t fill[3];
 };
 struct F32Net {
   F32Layer l[kMaxLayers];
+};
+// A net's layers, layer l in lane l: fetched at the kernel's start, once.  (Out of the kernel's arguments by a layer index that
+// only the wave knows, every field is a scalar load of its own, 300 to 700 cycles in front of every layer's products.)
+struct Layers {
+  F32Layer mine;
+  __device__ __forceinline__ explicit Layers(const F32Net& N) : mine(N.l[min((int)(threadIdx.x & 63), kMaxLayers - 1)]) {}
+  __device__ __forceinline__ F32Layer operator[](int l) const {
+    F32Layer r;
+    r.in = __builtin_amdgcn_readlane(mine.in, l);
+    r.out = __builtin_amdgcn_readlane(mine.out, l);
+    r.w_off = __builtin_amdgcn_readlane(mine.w_off, l);
+    r.b_off = __builtin_amdgcn_readlane(mine.b_off, l);
+    r.piece_magic = (uint32_t)__builtin_amdgcn_readlane((int)mine.piece_magic, l);
+    return r;
+  }
 };
 
 // n / d for n * d < 2^32 through one multiply: m = magic(d).
 __host__ __device__ __forceinline__ uint32_t magic(uint32_t d) { return d == 1 ? 0u : 0xFFFFFFFFu / d + 1u; }
 __device__ __forceinline__ int div_magic(int n, uint32_t m) { return m ? (int)__umulhi((uint32_t)n, m) : n; }
 
-// Zero-padded LDS copies of a net's weights (if WL) and biases, layer after layer: s_w and s_b have been cleared.  The
-// net's parameters are one contiguous piece of the parameter vector; a thread takes every nt-th of them, kStage loads
-// in flight (row by row, each row's load waited for the one before it: 16 us for two layers of 64).
-constexpr int kStage = 16;
-template <bool WL>
-__device__ __forceinline__ void stage_net(const F32Net& N, int nl, float* s_w, float* s_b, int tid, int nt) {
-  const float* base = N.l[0].w;
-  const int off0 = N.l[0].w_off;
-  if constexpr (WL) {
-    const int total = N.l[nl - 1].b_off + N.l[nl - 1].out - off0;
-    for (int e0 = tid; e0 < total; e0 += kStage * nt) {
-      float v[kStage];
-#pragma unroll
-      for (int u = 0; u < kStage; ++u) v[u] = base[min(e0 + u * nt, total - 1)];
-#pragma unroll
-      for (int u = 0; u < kStage; ++u) {
-        const int e = e0 + u * nt;
-        if (e >= total) break;
-        int l = 0, wo = 0, bo = 0;
-        while (l + 1 < nl && e >= N.l[l + 1].w_off - off0) {
-          wo += pad16(N.l[l].out) * rstride(N.l[l].in);
-          bo += pad16(N.l[l].out);
-          ++l;
-        }
-        const int q = e - (N.l[l].w_off - off0), nw = N.l[l].in * N.l[l].out;
-        if (q < nw) {
-          const int f = div_magic(q, N.l[l].in_magic);
-          s_w[wo + f * rstride(N.l[l].in) + q - f * N.l[l].in] = v[u];
-        } else {
-          s_b[bo + q - nw] = v[u];
-        }
-      }
-    }
+// Floats 4 c .. 4 c + 3 of a row of `width` floats, zero beyond it: one 16-byte load that ends with the row.
+__device__ __forceinline__ float4 load_piece(const float* row, int c, int width) {
+  float4 v;
+  if (width >= 4) {
+    const int st = min(4 * c, width - 4), d = 4 * c - st;
+    const Float4U t = *reinterpret_cast<const Float4U*>(row + st);
+    v.x = d == 0 ? t.x : d == 1 ? t.y : d == 2 ? t.z : t.w;
+    v.y = d == 0 ? t.y : d == 1 ? t.z : t.w;
+    v.z = d == 0 ? t.z : t.w;
+    v.w = t.w;
   } else {
-    for (int l = 0; l < nl; ++l) {
-      for (int f = tid; f < N.l[l].out; f += nt) s_b[f] = N.l[l].b[f];
-      s_b += pad16(N.l[l].out);
+    v = make_float4(row[0], row[min(1, width - 1)], row[min(2, width - 1)], 0.f);
+  }
+  v.x = 4 * c + 0 < width ? v.x : 0.f; v.y = 4 * c + 1 < width ? v.y : 0.f;
+  v.z = 4 * c + 2 < width ? v.z : 0.f; v.w = 4 * c + 3 < width ? v.w : 0.f;
+  return v;
+}
+
+// A net's weights on their way into its zero-padded LDS copy (layer after layer, [pad16(out)][rstride(in)]): 16-byte pieces,
+// the threads' nt at a time, U rounds of loads before the first of them is stored.  (Element by element the copy of 9 KB
+// took longer than it saved; these loads are issued ahead of everything the workgroup waits for first.)
+template <int U>
+struct WeightStage {
+  int l = 0, p0 = 0, off = 0;      // next round: pieces p0 + tid of layer l, whose copy starts at off
+  float4 v[U];
+  __device__ __forceinline__ void advance(const F32Layer& L, int nt) {
+    p0 += nt;
+    if (p0 >= pad16(L.out) * (pad16(L.in) >> 2)) {
+      off += pad16(L.out) * rstride(L.in);
+      p0 = 0;
+      ++l;
     }
   }
-}
-__device__ __forceinline__ void clear_lds(float* p, int n, int tid, int nt) {      // n a multiple of 4, p 16-byte aligned
-  for (int i = tid; i < n / 4; i += nt) reinterpret_cast<float4*>(p)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-}
-// Rows of `width` floats, row(r) -> their address, into LDS rows of stride rstride(width), zero padded; 8 loads in flight.
-template <class Row>
-__device__ __forceinline__ void stage_rows(int R, int width, uint32_t wmagic, Row row, float* dst, int tid) {
-  const int ld = rstride(width), n = R * width;
-  for (int e0 = tid; e0 < n; e0 += 8 * kNT) {
-    float v[8];
-    int d[8];
+  __device__ __forceinline__ void request(const float* params, const Layers& N, int nl, int tid, int nt) {      // does not move on
+    WeightStage<U> w = *this;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int e = min(e0 + u * kNT, n - 1), r = div_magic(e, wmagic), c = e - r * width;
-      v[u] = row(r)[c];
-      d[u] = r * ld + c;
+    for (int u = 0; u < U; ++u) {
+      if (w.l >= nl) break;
+      const F32Layer L = N[w.l];
+      const int nc = pad16(L.in) >> 2, p = w.p0 + tid, r = div_magic(p, L.piece_magic), c = p - r * nc;
+      v[u] = load_piece(params + L.w_off + (int64_t)min(r, L.out - 1) * L.in, c, L.in);
+      if (r >= L.out) v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      w.advance(L, nt);
+    }
+  }
+  __device__ __forceinline__ void store(const Layers& N, int nl, float* s_w, int tid, int nt) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (l >= nl) break;
+      const F32Layer L = N[l];
+      const int nc = pad16(L.in) >> 2, p = p0 + tid, r = div_magic(p, L.piece_magic), c = p - r * nc;
+      if (r < pad16(L.out)) *reinterpret_cast<float4*>(s_w + off + r * rstride(L.in) + 4 * c) = v[u];
+      advance(L, nt);
+    }
+  }
+};
+// Bias e of all layers' biases, layer after layer, each zero-padded to pad16(out).
+__device__ __forceinline__ float bias_elem(const float* params, const Layers& N, int nl, int e) {
+  int off = -1;
+  for (int l = 0; l < nl; ++l) {
+    const F32Layer L = N[l];
+    if (e >= 0 && e < L.out) off = L.b_off + e;
+    e -= pad16(L.out);
+  }
+  const float v = params[max(off, 0)];
+  return off >= 0 ? v : 0.f;
+}
+// Rows of `width` floats, row(r) -> their address, into LDS rows of stride rstride(width), zero padded; magic of pad16(width) / 4.
+template <int R, class Row>
+__device__ __forceinline__ void stage_rows(int width, uint32_t pmagic, Row row, float* dst, int tid) {
+  const int nc = pad16(width) >> 2, n = R * nc, ld = rstride(width);
+  for (int e0 = tid; e0 < n; e0 += 2 * kNT) {
+    float4 v[2];
+    int d[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int e = min(e0 + u * kNT, n - 1), r = div_magic(e, pmagic), c = e - r * nc;
+      v[u] = load_piece(row(r), c, width);
+      d[u] = r * ld + 4 * c;
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) dst[d[u]] = v[u];      // past the end: the last element again
+    for (int u = 0; u < 2; ++u) *reinterpret_cast<float4*>(dst + d[u]) = v[u];      // past the end: the last piece again
   }
-  const int padn = ld - width;
-  for (int r = tid; r < R; r += kNT)
-    for (int c = 0; c < padn; ++c) dst[r * ld + width + c] = 0.f;
 }
 
 // acc[i] += sum over nchunk 16-wide k chunks of A (load(c): this lane's 4 values of chunk c) and of the NR row tiles at
-// xp, xp + xts (this lane's row and lane group: xp points at k = 4 g).  Four chunks of A are in flight.
-template <int NR, class LoadA>
+// xp, xp + xts (this lane's row and lane group: xp points at k = 4 g).  The operands of D chunks are in flight.
+template <int NR, int D, class LoadA>
 __device__ __forceinline__ void products(floatx4 (&acc)[NR], int nchunk, LoadA load, const float* xp, int xts) {
   if (nchunk <= 0) return;
-  float4 a[4];
+  float4 a[D], x[D][NR];
+  auto fetch = [&](int u, int c) {
+    a[u] = load(c);
 #pragma unroll
-  for (int u = 0; u < 4; ++u) a[u] = load(min(u, nchunk - 1));
-  auto step = [&](const float4& w, int c) {
-    float4 x[NR];
-#pragma unroll
-    for (int i = 0; i < NR; ++i) x[i] = *reinterpret_cast<const float4*>(xp + i * xts + 16 * c);
-#pragma unroll
-    for (int i = 0; i < NR; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.x, x[i].x, acc[i], 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < NR; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.y, x[i].y, acc[i], 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < NR; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.z, x[i].z, acc[i], 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < NR; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.w, x[i].w, acc[i], 0, 0, 0);
+    for (int i = 0; i < NR; ++i) x[u][i] = *reinterpret_cast<const float4*>(xp + i * xts + 16 * c);
   };
-  int c = 0;
-  for (; c + 4 <= nchunk; c += 4) {
+  auto step = [&](int u) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const float4 w = a[u];
-      a[u] = load(min(c + 4 + u, nchunk - 1));
-      step(w, c + u);
+    for (int i = 0; i < NR; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u].x, x[u][i].x, acc[i], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < NR; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u].y, x[u][i].y, acc[i], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < NR; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u].z, x[u][i].z, acc[i], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < NR; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u].w, x[u][i].w, acc[i], 0, 0, 0);
+  };
+#pragma unroll
+  for (int u = 0; u < D; ++u)
+    if (u < nchunk) fetch(u, u);
+  int c = 0;
+  for (; c + D < nchunk; c += D)
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      step(u);
+      if (c + D + u < nchunk) fetch(u, c + D + u);
     }
-  }
-  if (c < nchunk) step(a[0], c);
-  if (c + 1 < nchunk) step(a[1], c + 1);
-  if (c + 2 < nchunk) step(a[2], c + 2);
+#pragma unroll
+  for (int u = 0; u < D; ++u)
+    if (c + u < nchunk) step(u);
 }
 
-__device__ __forceinline__ float elu32(float z) { return z > 0.f ? z : expm1f(z); }
+// e^z - 1 for z <= 0 as 2^n (e^r - 1) + (2^n - 1), z = n ln 2 + r, |r| <= ln 2 / 2 (ln 2 in two words): e^r - 1 = r + r^2 q(r), q
+// of degree 5 fitted to the least relative error.  Within 0.86 ulp of expm1 over [-20, 0] (checked against 64 bits); 18
+// instructions.  z < -30 gives -1, as the nearest float does from -17.4 on.
+__device__ __forceinline__ float elu32(float z) {
+  const float c = z < -30.f ? -30.f : z;
+  const float n = __builtin_rintf(c * 0x1.715476p+0f);
+  const float r = fmaf(n, -0x1.7f7d1cp-20f, fmaf(n, -0x1.62e4p-1f, c));
+  float q = 0x1.a032c4p-13f;
+  q = fmaf(q, r, 0x1.6d723ep-10f);
+  q = fmaf(q, r, 0x1.11118ap-7f);
+  q = fmaf(q, r, 0x1.5554bp-5f);
+  q = fmaf(q, r, 0x1.555554p-3f);
+  q = fmaf(q, r, 0.5f);
+  const float p = fmaf(r * r, q, r);
+  const float s = __builtin_amdgcn_ldexpf(1.0f, (int)n);
+  return z > 0.f ? z : fmaf(s, p, s - 1.0f);
+}
 __device__ __forceinline__ float elu_grad32(float h) { return h > 0.f ? 1.0f : h + 1.0f; }
+
+// Sum over the 8 lanes 8 i .. 8 i + 7, in all of them.
+__device__ __forceinline__ float sum8(float v) {
+  auto add = [&](auto ctrl) { v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), decltype(ctrl)::value, 0xF, 0xF, true)); };
+  add(std::integral_constant<int, 0xB1>{});       // lane ^ 1
+  add(std::integral_constant<int, 0x4E>{});       // lane ^ 2
+  add(std::integral_constant<int, 0x141>{});      // mirrored among 8: the other four
+  return v;
+}
 
 enum { kHidden = 0, kHead = 1, kGrad = 2 };
 
@@ -155,7 +217,7 @@ enum { kHidden = 0, kHead = 1, kGrad = 2 };
 //   kHidden / kHead: y[r][f] = ELU(x W^T + b) / x W^T + b        kGrad: y[r][i] = (x W)[r][i] ELU'(h[r][i])
 // s_w: the layer's LDS copy (WL).  Padding features of y come out as zero.
 template <bool WL, int NR, int KIND>
-__device__ __forceinline__ void tile_product(const F32Layer& L, const float* s_w, const float* s_bias, const float* s_x,
+__device__ __forceinline__ void tile_product(const float* params, const F32Layer& L, const float* s_w, const float* s_bias, const float* s_x,
                                              int sx, const float* s_h, float* s_y, int sy, int f0, int rt0, int lane) {
   const int j = lane & 15, g = lane >> 4;
   const int ld = rstride(L.in);
@@ -165,19 +227,25 @@ __device__ __forceinline__ void tile_product(const F32Layer& L, const float* s_w
   const float* xp = s_x + (rt0 * 16 + j) * sx + 4 * g;
   const int F = KIND == kGrad ? L.in : L.out;            // features of y
   const int f = f0 + j;                                   // operand A's feature of this lane
+  const int fr = f0 + 4 * g;                              // this lane's results: features fr + 0..3 of row j of each row tile
+  float4 bv = make_float4(0.f, 0.f, 0.f, 0.f), hv[NR];
+  if constexpr (KIND != kGrad) bv = *reinterpret_cast<const float4*>(s_bias + fr);
+  else
+#pragma unroll
+    for (int i = 0; i < NR; ++i) hv[i] = *reinterpret_cast<const float4*>(s_h + ((rt0 + i) * 16 + j) * sy + fr);
   if constexpr (KIND != kGrad) {
     if constexpr (WL) {
       const float* wp = s_w + f * ld + 4 * g;
-      products<NR>(acc, pad16(L.in) >> 4, [&](int c) { return *reinterpret_cast<const float4*>(wp + 16 * c); }, xp, 16 * sx);
+      products<NR, 4>(acc, pad16(L.in) >> 4, [&](int c) { return *reinterpret_cast<const float4*>(wp + 16 * c); }, xp, 16 * sx);
     } else {
-      const float* wp = L.w + (int64_t)(f < F ? f : F - 1) * L.in;
+      const float* wp = params + L.w_off + (int64_t)(f < F ? f : F - 1) * L.in;
       const int nfull = L.in >> 4;
-      products<NR>(acc, nfull, [&](int c) {
+      products<NR, 4>(acc, nfull, [&](int c) {
         const Float4U v = *reinterpret_cast<const Float4U*>(wp + 16 * c + 4 * g);
         return make_float4(v.x, v.y, v.z, v.w);
       }, xp, 16 * sx);
       if (L.in & 15) {                                    // the ragged chunk: x is zero beyond `in`
-        products<NR>(acc, 1, [&](int) {
+        products<NR, 1>(acc, 1, [&](int) {
           const int k = 16 * nfull + 4 * g;
           return make_float4(wp[min(k, L.in - 1)], wp[min(k + 1, L.in - 1)], wp[min(k + 2, L.in - 1)], wp[min(k + 3, L.in - 1)]);
         }, xp + 16 * nfull, 16 * sx);
@@ -186,23 +254,19 @@ __device__ __forceinline__ void tile_product(const F32Layer& L, const float* s_w
   } else {                                                // A = W^T: lane's feature = input i, k = output o
     if constexpr (WL) {
       const float* wp = s_w + f;
-      products<NR>(acc, pad16(L.out) >> 4, [&](int c) {
+      products<NR, 4>(acc, pad16(L.out) >> 4, [&](int c) {
         const float* p = wp + (16 * c + 4 * g) * ld;
         return make_float4(p[0], p[ld], p[2 * ld], p[3 * ld]);
       }, xp, 16 * sx);
     } else {
-      const float* wp = L.w + (f < F ? f : F - 1);
-      products<NR>(acc, pad16(L.out) >> 4, [&](int c) {   // x is zero beyond `out`
+      const float* wp = params + L.w_off + (f < F ? f : F - 1);
+      products<NR, 4>(acc, pad16(L.out) >> 4, [&](int c) {   // x is zero beyond `out`
         const int o = 16 * c + 4 * g, m = L.out - 1;
         return make_float4(wp[(int64_t)min(o, m) * L.in], wp[(int64_t)min(o + 1, m) * L.in], wp[(int64_t)min(o + 2, m) * L.in],
                            wp[(int64_t)min(o + 3, m) * L.in]);
       }, xp, 16 * sx);
     }
   }
-  // this lane's results: features f0 + 4 g + 0..3 of row j of each row tile
-  const int fr = f0 + 4 * g;
-  float4 bv = make_float4(0.f, 0.f, 0.f, 0.f);
-  if constexpr (KIND != kGrad) bv = *reinterpret_cast<const float4*>(s_bias + fr);
 #pragma unroll
   for (int i = 0; i < NR; ++i) {
     const int r = (rt0 + i) * 16 + j;
@@ -211,11 +275,12 @@ __device__ __forceinline__ void tile_product(const F32Layer& L, const float* s_w
 #pragma unroll
       for (int v = 0; v < 4; ++v) o[v] = elu32(o[v]);
     } else if constexpr (KIND == kGrad) {
-      const float4 h = *reinterpret_cast<const float4*>(s_h + r * sy + fr);
+      const float4& h = hv[i];
       o[0] *= elu_grad32(h.x); o[1] *= elu_grad32(h.y); o[2] *= elu_grad32(h.z); o[3] *= elu_grad32(h.w);
     }
+    if (f0 + 16 > F)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) o[v] = fr + v < F ? o[v] : 0.f;
+      for (int v = 0; v < 4; ++v) o[v] = fr + v < F ? o[v] : 0.f;
     *reinterpret_cast<float4*>(s_y + r * sy + fr) = make_float4(o[0], o[1], o[2], o[3]);
   }
 }
@@ -225,31 +290,33 @@ __device__ __forceinline__ void tile_product(const F32Layer& L, const float* s_w
 __device__ __forceinline__ int pair_rows(int n_ft, int RT, int nw) { return RT >= 2 && n_ft * (RT / 2) >= nw ? 2 : 1; }
 
 template <bool WL, int KIND>
-__device__ __forceinline__ void layer(const F32Layer& L, const float* s_w, const float* s_bias, const float* s_x, int sx,
+__device__ __forceinline__ void layer(const float* params, const F32Layer& L, const float* s_w, const float* s_bias, const float* s_x, int sx,
                                       const float* s_h, float* s_y, int sy, int RT, int wave, int nw, int lane) {
   const int n_ft = pad16(KIND == kGrad ? L.in : L.out) >> 4;
   const int pr = pair_rows(n_ft, RT, nw);
-  for (int item = wave; item < n_ft * (RT / pr); item += nw) {
-    const int ft = item % n_ft, rg = item / n_ft;
-    if (pr == 2) tile_product<WL, 2, KIND>(L, s_w, s_bias, s_x, sx, s_h, s_y, sy, ft * 16, rg * 2, lane);
-    else tile_product<WL, 1, KIND>(L, s_w, s_bias, s_x, sx, s_h, s_y, sy, ft * 16, rg, lane);
+  int ft = wave, rg = 0;
+  for (;; ft += nw) {
+    while (ft >= n_ft) { ft -= n_ft; ++rg; }
+    if (rg >= RT / pr) break;
+    if (pr == 2) tile_product<WL, 2, KIND>(params, L, s_w, s_bias, s_x, sx, s_h, s_y, sy, ft * 16, rg * 2, lane);
+    else tile_product<WL, 1, KIND>(params, L, s_w, s_bias, s_x, sx, s_h, s_y, sy, ft * 16, rg, lane);
   }
 }
 
 // All layers of a net on the tile in s_x0; hidden activations ping-pong between s_a and s_b (stride sh); the head goes to
 // s_out (stride so).  `run`: whether these waves take part (every thread reaches every barrier).
 template <bool WL>
-__device__ __forceinline__ void net_forward(const F32Net& N, int nl, const float* s_w, const float* s_bias, const float* s_x0,
+__device__ __forceinline__ void net_forward(const float* params, const Layers& N, int nl, const float* s_w, const float* s_bias, const float* s_x0,
                                             int sx0, float* s_a, float* s_b, int sh, float* s_out, int so, int RT, bool run,
                                             int wave, int nw, int lane) {
   const float* x = s_x0;
   int sx = sx0;
   float* y = s_a;
   for (int l = 0; l < nl; ++l) {
-    const F32Layer L = N.l[l];
+    const F32Layer L = N[l];
     if (run) {
-      if (l < nl - 1) layer<WL, kHidden>(L, s_w, s_bias, x, sx, nullptr, y, sh, RT, wave, nw, lane);
-      else layer<WL, kHead>(L, s_w, s_bias, x, sx, nullptr, s_out, so, RT, wave, nw, lane);
+      if (l < nl - 1) layer<WL, kHidden>(params, L, s_w, s_bias, x, sx, nullptr, y, sh, RT, wave, nw, lane);
+      else layer<WL, kHead>(params, L, s_w, s_bias, x, sx, nullptr, s_out, so, RT, wave, nw, lane);
     }
     __syncthreads();
     if constexpr (WL) s_w += pad16(L.out) * rstride(L.in);
@@ -264,20 +331,23 @@ __device__ __forceinline__ void net_forward(const F32Net& N, int nl, const float
 // Action decision: grid (row tiles, nets).
 struct AgentF32Args {
   const float* obs;
-  int nl, n, obs_dim, act_dim, R, net0, sh, b_floats;
+  int nl, n, obs_dim, act_dim, net0, sh, b_floats, b_net[2];
   uint32_t o_magic;
   F32Net net[2];
+  const float* params;
   const float* log_std;
   uint32_t k0, k1, step, env_offset;
   float* act; float* logp; float* value; float* mu_out;
 };
 
+template <int RT>
 __global__ __launch_bounds__(kNT) void agent_f32_kernel(AgentF32Args a) {
+  constexpr int R = 16 * RT;
   extern __shared__ __attribute__((aligned(16))) float smem[];
   const int net = blockIdx.y + a.net0;
-  const F32Net& N = a.net[net];
+  const Layers N(a.net[net]);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int R = a.R, O = a.obs_dim, A = a.act_dim, sx0 = rstride(O), so = rstride(A), nba = (A + 3) >> 2;
+  const int O = a.obs_dim, A = a.act_dim, sx0 = rstride(O), so = rstride(A), nba = (A + 3) >> 2;
   float* s_bias = smem;
   float* s_x0 = s_bias + a.b_floats;
   float* s_a = s_x0 + R * sx0;
@@ -285,12 +355,10 @@ __global__ __launch_bounds__(kNT) void agent_f32_kernel(AgentF32Args a) {
   float* s_out = s_b + R * a.sh;
   float* s_lp = s_out + R * so;
   const int r0 = blockIdx.x * R;
-  clear_lds(smem, a.b_floats, tid, kNT);
-  stage_rows(R, O, a.o_magic, [&](int r) { return a.obs + (int64_t)min(r0 + r, a.n - 1) * O; }, s_x0, tid);
+  stage_rows<R>(O, a.o_magic, [&](int r) { return a.obs + (int64_t)min(r0 + r, a.n - 1) * O; }, s_x0, tid);
+  for (int e = tid; e < a.b_net[net]; e += kNT) s_bias[e] = bias_elem(a.params, N, a.nl, e);
   __syncthreads();
-  stage_net<false>(N, a.nl, smem, s_bias, tid, kNT);
-  __syncthreads();
-  net_forward<false>(N, a.nl, smem, s_bias, s_x0, sx0, s_a, s_b, a.sh, s_out, so, R / 16, true, wave, kNW, lane);
+  net_forward<false>(a.params, N, a.nl, smem, s_bias, s_x0, sx0, s_a, s_b, a.sh, s_out, so, RT, true, wave, kNW, lane);
   if (net == 1) {
     for (int r = tid; r < R; r += kNT)
       if (r0 + r < a.n) a.value[r0 + r] = s_out[r * so];
@@ -333,11 +401,12 @@ __global__ __launch_bounds__(kNT) void agent_f32_kernel(AgentF32Args a) {
 // its statistics to row blockIdx.x of the statistics partials.
 struct TrainF32Args {
   F32Net net[2];
+  const float* params;
   const float* log_std;
   const int32_t* idx;
   const float *b_obs, *b_act, *b_logp, *b_adv, *b_ret;
-  int n_envs, ld_envs, obs_dim, act_dim, nl, rows, R, n_tiles, sdz, w_floats, b_floats;
-  int w_net[2];                // floats of each net's LDS weight copy (w_floats: the larger)
+  int n_envs, ld_envs, obs_dim, act_dim, nl, rows, n_tiles, sdz, b_floats;
+  int b_net[2];                // floats of each net's biases (b_floats: of the larger)
   int h_off[kMaxLayers];       // floats from the start of the activation area
   int h_floats;
   uint32_t o_magic, a_magic;
@@ -346,15 +415,18 @@ struct TrainF32Args {
   float* stat_part;
 };
 
-template <bool WL>
+// What the kernel waits for first -- sample indices, then the rows they name -- is requested first; the biases travel meanwhile.
+// The weights are read from L2: an LDS copy of them made by every workgroup costs more instructions than its reads save.  Loss: 8 lanes per sample share its actions.  Backward, a layer: input-gradient tiles, weight-gradient tiles
+// and, with the head's, the sums over the tile's samples (statistics, log_std) are items of one list, dealt to the waves.
+template <int RT>
 __global__ __launch_bounds__(kNT) void train_f32_kernel(TrainF32Args a) {
+  constexpr int R = 16 * RT;
   extern __shared__ __attribute__((aligned(16))) float smem[];
   const int net = blockIdx.y;
-  const F32Net& N = a.net[net];
+  const Layers N(a.net[net]);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int R = a.R, RT = R / 16, O = a.obs_dim, A = a.act_dim, so = rstride(A), nl = a.nl;
-  float* s_w = smem;
-  float* s_bias = s_w + (WL ? a.w_floats : 0);
+  const int O = a.obs_dim, A = a.act_dim, so = rstride(A), nl = a.nl;
+  float* s_bias = smem;
   float* s_h = s_bias + a.b_floats;
   float* s_dz0 = s_h + a.h_floats;
   float* s_dz1 = s_dz0 + R * a.sdz;
@@ -362,12 +434,15 @@ __global__ __launch_bounds__(kNT) void train_f32_kernel(TrainF32Args a) {
   float* s_act = s_out + R * so;                  // [R][A]
   float* s_scal = s_act + ((R * A + 3) & ~3);     // [3][R] old log-prob, advantage, return
   int64_t* s_slot = reinterpret_cast<int64_t*>(s_scal + 3 * R);      // [R]
-  float* s_ls = s_scal + 5 * R;                   // [A] log_std, [A] exp(-log_std)
+  float* s_stat = s_scal + 5 * R;                 // [4][R] policy term, value term, kl, clipped of each sample
+  float* s_ls = s_stat + 4 * R;                   // [A] log_std, [A] exp(-log_std)
   float* s_sum = s_ls + 2 * A;                    // [4] statistics, [A] log_std gradient, over all tiles
   const float inv_m = 1.0f / (float)a.rows;
   float* part = a.part + (int64_t)blockIdx.x * a.part_stride;
 
-  clear_lds(smem, (WL ? a.w_floats : 0) + a.b_floats, tid, kNT);
+  // sample of row tid of the present tile (rows past the batch repeat its last sample, their gradient is zero)
+  int sample = tid < R ? a.idx[min((int)blockIdx.x * R + tid, a.rows - 1)] : 0;
+  for (int e = tid; e < a.b_net[net]; e += kNT) s_bias[e] = bias_elem(a.params, N, nl, e);
   for (int j = tid; j < A; j += kNT) {
     const float ls = a.log_std[j];
     s_ls[j] = ls;
@@ -378,143 +453,149 @@ __global__ __launch_bounds__(kNT) void train_f32_kernel(TrainF32Args a) {
   for (int tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
     const int r0 = tile * R;
     const bool first = tile == (int)blockIdx.x;
-    // the rows' experience slots (rows past the batch repeat its last sample, their gradient is zero)
-    if (tid < R) {
-      const int s = a.idx[min(r0 + tid, a.rows - 1)];
-      s_slot[tid] = (int64_t)(s / a.n_envs) * a.ld_envs + (s % a.n_envs);
-    }
+    if (tid < R) s_slot[tid] = (int64_t)(sample / a.n_envs) * a.ld_envs + (sample % a.n_envs);
     __syncthreads();
-    if (tid < R) {
-      const int64_t slot = s_slot[tid];
-      if (net == 0) { s_scal[tid] = a.b_logp[slot]; s_scal[R + tid] = a.b_adv[slot]; }
-      else s_scal[2 * R + tid] = a.b_ret[slot];
-    }
-    stage_rows(R, O, a.o_magic, [&](int r) { return a.b_obs + s_slot[r] * O; }, s_h, tid);
-    if (net == 0)
-      for (int e = tid; e < R * A; e += kNT) {
-        const int r = div_magic(e, a.a_magic);
-        s_act[e] = a.b_act[s_slot[r] * A + e - r * A];
+    {   // the gather: everything is requested before the first result is stored
+      float sc0 = 0.f, sc1 = 0.f, av = 0.f;
+      if (tid < R) {
+        const int64_t slot = s_slot[tid];
+        sc0 = net == 0 ? a.b_logp[slot] : a.b_ret[slot];
+        sc1 = a.b_adv[slot];
+        sample = a.idx[min((tile + (int)gridDim.x) * R + tid, a.rows - 1)];      // the next tile's
       }
-    if (first) stage_net<WL>(N, nl, s_w, s_bias, tid, kNT);
+      const int e0 = min(tid, R * A - 1), ar = div_magic(e0, a.a_magic);
+      if (net == 0) av = a.b_act[s_slot[ar] * A + e0 - ar * A];
+      stage_rows<R>(O, a.o_magic, [&](int r) { return a.b_obs + s_slot[r] * O; }, s_h, tid);
+      if (tid < R) { s_scal[net == 0 ? tid : 2 * R + tid] = sc0; s_scal[R + tid] = sc1; }
+      if (net == 0) {
+        if (tid < R * A) s_act[tid] = av;
+        for (int e = tid + kNT; e < R * A; e += kNT) {
+          const int r = div_magic(e, a.a_magic);
+          s_act[e] = a.b_act[s_slot[r] * A + e - r * A];
+        }
+      }
+    }
     __syncthreads();
     {   // forward
-      const float* w = s_w;
       const float* bias = s_bias;
       for (int l = 0; l < nl; ++l) {
-        const F32Layer L = N.l[l];
+        const F32Layer L = N[l];
         const float* x = s_h + a.h_off[l];
         if (l < nl - 1)
-          layer<WL, kHidden>(L, w, bias, x, rstride(L.in), nullptr, s_h + a.h_off[l + 1], rstride(L.out), RT, wave, kNW, lane);
+          layer<false, kHidden>(a.params, L, nullptr, bias, x, rstride(L.in), nullptr, s_h + a.h_off[l + 1], rstride(L.out), RT, wave, kNW, lane);
         else
-          layer<WL, kHead>(L, w, bias, x, rstride(L.in), nullptr, s_out, so, RT, wave, kNW, lane);
+          layer<false, kHead>(a.params, L, nullptr, bias, x, rstride(L.in), nullptr, s_out, so, RT, wave, kNW, lane);
         __syncthreads();
-        if constexpr (WL) w += pad16(L.out) * rstride(L.in);
         bias += pad16(L.out);
       }
     }
-    // loss: one thread per sample (the first wave); the head's gradient rows into s_dz0, stride rstride(head width)
-    const int sd = rstride(N.l[nl - 1].out), wd = pad16(N.l[nl - 1].out);
-    if (wave == 0) {
-      const int r = lane;
-      const bool ok = r < R && r0 + r < a.rows;
-      float st[4] = {0.f, 0.f, 0.f, 0.f};           // policy term, value term, kl, clipped
-      if (r < R) {
-        if (net == 0) {
-          float lp = 0.f;
-#pragma unroll 4
-          for (int j = 0; j < A; ++j) {
+    // loss: lanes 8 r .. 8 r + 7 have sample r; the head's gradient rows into s_dz0, stride rstride(head width)
+    const int sd = rstride(net == 0 ? A : 1), wd = pad16(net == 0 ? A : 1);
+    if (tid < 8 * R) {
+      const int r = tid >> 3, j0 = tid & 7;
+      const bool ok = r0 + r < a.rows;
+      if (net == 0) {
+        float lp = 0.f;
+        for (int j = j0; j < A; j += 8) {
+          const float z = (s_act[r * A + j] - s_out[r * so + j]) * s_ls[A + j];
+          lp += -0.5f * z * z - s_ls[j] - 0.918938533204672742f;
+        }
+        lp = sum8(lp);
+        float g_lp = 0.f, pl = 0.f, kl = 0.f, cf = 0.f;
+        if (ok) {
+          const float lo = s_scal[r], ad = s_scal[R + r];
+          const float ratio = expf(lp - lo);
+          const float u1 = ratio * ad;
+          const float u2 = fminf(fmaxf(ratio, 1.0f - a.clip), 1.0f + a.clip) * ad;
+          pl = -fminf(u1, u2);
+          kl = lo - lp;
+          cf = fabsf(ratio - 1.0f) > a.clip ? 1.f : 0.f;
+          g_lp = (u1 <= u2) ? -(ad * ratio) * inv_m : 0.f;
+        }
+        if (j0 == 0) { s_stat[r] = pl; s_stat[2 * R + r] = kl; s_stat[3 * R + r] = cf; }
+        for (int j = j0; j < wd; j += 8) {
+          float dz = 0.f;
+          if (j < A) {
             const float z = (s_act[r * A + j] - s_out[r * so + j]) * s_ls[A + j];
-            lp += -0.5f * z * z - s_ls[j] - 0.918938533204672742f;
-          }
-          float g_lp = 0.f;
-          if (ok) {
-            const float lo = s_scal[r], ad = s_scal[R + r];
-            const float ratio = expf(lp - lo);
-            const float u1 = ratio * ad;
-            const float u2 = fminf(fmaxf(ratio, 1.0f - a.clip), 1.0f + a.clip) * ad;
-            st[0] = -fminf(u1, u2);
-            st[2] = lo - lp;
-            st[3] = fabsf(ratio - 1.0f) > a.clip ? 1.f : 0.f;
-            g_lp = (u1 <= u2) ? -(ad * ratio) * inv_m : 0.f;
-          }
-#pragma unroll 4
-          for (int j = 0; j < A; ++j) {
-            const float z = (s_act[r * A + j] - s_out[r * so + j]) * s_ls[A + j];
-            s_dz0[r * sd + j] = g_lp * z * s_ls[A + j];
+            dz = g_lp * z * s_ls[A + j];
             s_out[r * so + j] = g_lp * (z * z - 1.0f);
           }
-          for (int j = A; j < wd; ++j) s_dz0[r * sd + j] = 0.f;
-        } else {
-          float dv = 0.f;
-          if (ok) {
-            dv = s_out[r * so] - s_scal[2 * R + r];
-            st[1] = dv * dv;
-          }
-          s_dz0[r * sd] = 2.0f * a.c_v * dv * inv_m;
-          for (int j = 1; j < wd; ++j) s_dz0[r * sd + j] = 0.f;
+          s_dz0[r * sd + j] = dz;
         }
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float v = st[q];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-        if (lane == 0) s_sum[q] += v;
+      } else {
+        const float dv = ok ? s_out[r * so] - s_scal[2 * R + r] : 0.f;
+        if (j0 == 0) s_stat[R + r] = dv * dv;
+        for (int j = j0; j < wd; j += 8) s_dz0[r * sd + j] = j == 0 ? 2.0f * a.c_v * dv * inv_m : 0.f;
       }
     }
     __syncthreads();
-    if (net == 0)
-      for (int j = tid; j < A; j += kNT) {
-        float v = 0.f;
-#pragma unroll 8
-        for (int r = 0; r < R; ++r) v += s_out[r * so + j];
-        s_sum[4 + j] += v;
-      }
-    // backward, head to first layer: the input gradient of layer l and, by the waves left over, its weight gradient
+    // backward, head to first layer
     const float* dz = s_dz0;
     float* dn = s_dz1;
-    const float* w = s_w + (WL ? a.w_net[net] : 0);
     for (int l = nl - 1; l >= 0; --l) {
-      const F32Layer L = N.l[l];
+      const F32Layer L = N[l];
       const int sz = rstride(L.out), shl = rstride(L.in);
       const float* h = s_h + a.h_off[l];
-      if constexpr (WL) w -= pad16(L.out) * rstride(L.in);
       const int n_it = pad16(L.in) >> 4, n_ot = pad16(L.out) >> 4;
       const int pr = pair_rows(n_it, RT, kNW);
-      const int n_grad = l > 0 ? n_it * (RT / pr) : 0, n_items = n_grad + n_it * n_ot;
+      const int n_grad = l > 0 ? RT / pr : 0;      // rows of n_it items: input gradients, then weight gradients
       const int j = lane & 15, g = lane >> 4;
-      for (int item = wave; item < n_items; item += kNW) {
-        if (item < n_grad) {
-          const int ft = item % n_it, rg = item / n_it;
-          if (pr == 2) tile_product<WL, 2, kGrad>(L, w, nullptr, dz, sz, h, dn, shl, ft * 16, rg * 2, lane);
-          else tile_product<WL, 1, kGrad>(L, w, nullptr, dz, sz, h, dn, shl, ft * 16, rg, lane);
+      int it = wave, row = 0;
+      for (;; it += kNW) {
+        while (it >= n_it) { it -= n_it; ++row; }
+        if (row >= n_grad + n_ot) break;
+        if (row < n_grad) {
+          if (pr == 2) tile_product<false, 2, kGrad>(a.params, L, nullptr, nullptr, dz, sz, h, dn, shl, it * 16, row * 2, lane);
+          else tile_product<false, 1, kGrad>(a.params, L, nullptr, nullptr, dz, sz, h, dn, shl, it * 16, row, lane);
         } else {
           // dW[o][i] = sum_r dz[r][o] h[r][i]: operands straight from the rows (lane = feature, lane group = row)
-          const int it = (item - n_grad) % n_it, ot = (item - n_grad) / n_it;
+          const int ot = row - n_grad;
           const float* zp = dz + g * sz + ot * 16 + j;
           const float* hp = h + g * shl + it * 16 + j;
           const int i = it * 16 + j, o = ot * 16 + 4 * g;
           float* dst = part + L.w_off + (int64_t)o * L.in + i;
-          float* db = part + L.b_off + o;
-          floatx4 acc = {0.f, 0.f, 0.f, 0.f}, accb = {0.f, 0.f, 0.f, 0.f};
+          float* db = part + L.b_off + ot * 16 + j;
+          floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+          float x[R / 4], y[R / 4], b = 0.f, bold = 0.f;
+#pragma unroll
+          for (int q = 0; q < R / 4; ++q) { x[q] = zp[4 * q * sz]; y[q] = hp[4 * q * shl]; }
           if (!first) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
+            for (int v = 0; v < 4; ++v)
               if (o + v < L.out && i < L.in) acc[v] = dst[(int64_t)v * L.in];
-              if (it == 0 && o + v < L.out) accb[v] = db[v];
-            }
-          }
-#pragma unroll 4
-          for (int r = 0; r < R; r += 4) {
-            const float x = zp[r * sz], y = hp[r * shl];
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, acc, 0, 0, 0);
-            if (it == 0) accb = __builtin_amdgcn_mfma_f32_16x16x4f32(x, 1.0f, accb, 0, 0, 0);
+            if (it == 0 && ot * 16 + j < L.out) bold = *db;
           }
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            if (o + v < L.out && i < L.in) dst[(int64_t)v * L.in] = acc[v];
-            if (it == 0 && j == 0 && o + v < L.out) db[v] = accb[v];
+          for (int q = 0; q < R / 4; ++q) {
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[q], y[q], acc, 0, 0, 0);
+            b += x[q];
           }
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            if (o + v < L.out && i < L.in) dst[(int64_t)v * L.in] = acc[v];
+          if (it == 0) {
+            b += __shfl_xor(b, 16, 64);
+            b += __shfl_xor(b, 32, 64);
+            if (g == 0 && ot * 16 + j < L.out) *db = bold + b;
+          }
+        }
+      }
+      // the sums over the tile's samples, with the head's items, by the last two waves
+      if (l == nl - 1 && wave == kNW - 1) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if ((q == 1) != (net == 1)) continue;
+          float v = lane < R ? s_stat[q * R + lane] : 0.f;
+#pragma unroll
+          for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+          if (lane == 0) s_sum[q] += v;
+        }
+      } else if (l == nl - 1 && wave == kNW - 2 && net == 0) {
+        for (int k = lane; k < A; k += 64) {
+          float v = 0.f;
+#pragma unroll 16
+          for (int r = 0; r < R; ++r) v += s_out[r * so + k];
+          s_sum[4 + k] += v;
         }
       }
       __syncthreads();
@@ -545,6 +626,7 @@ __global__ __launch_bounds__(kNT) void train_f32_kernel(TrainF32Args a) {
 // networks): waves 0-3 run the policy net, waves 4-7 the value net.
 struct RolloutF32Args : RolloutEnv {
   F32Net net[2];
+  const float* params;
   int nl, sh, w_floats[2], b_floats[2], mt_lds;
 };
 
@@ -569,16 +651,21 @@ __global__ __launch_bounds__(kNT) void rollout_f32_kernel(RolloutF32Args a) {
   int* s_done = reinterpret_cast<int*>(s_part + R * nbo);          // [R]
   float* s_ls = reinterpret_cast<float*>(s_done + R);              // [A] log_std, [A] exp(log_std)
   float* s_mt = s_ls + ((2 * A + 3) & ~3);                         // [O + A][o4] when mt_lds
-  const F32Net& N = a.net[half];
+  const Layers N(a.net[half]);
   const float* s_wn = s_w + (half ? a.w_floats[0] : 0);
   const float* s_bn = s_bias + (half ? a.b_floats[0] : 0);
   float* s_a = s_hid + half * 2 * R * a.sh;
   float* s_b = s_a + R * a.sh;
 
-  clear_lds(smem, (WL ? a.w_floats[0] + a.w_floats[1] : 0) + a.b_floats[0] + a.b_floats[1], tid, kNT);
   for (int j = tid; j < A; j += kNT) { s_ls[j] = a.log_std[j]; s_ls[A + j] = expf(a.log_std[j]); }
-  __syncthreads();
-  stage_net<WL>(N, a.nl, s_w + (half && WL ? a.w_floats[0] : 0), s_bias + (half ? a.b_floats[0] : 0), tid & 255, 256);
+  if constexpr (WL) {
+    WeightStage<8> ws;
+    while (ws.l < a.nl) {
+      ws.request(a.params, N, a.nl, tid & 255, 256);
+      ws.store(N, a.nl, s_w + (half ? a.w_floats[0] : 0), tid & 255, 256);
+    }
+  }
+  for (int e = tid & 255; e < a.b_floats[half]; e += 256) s_bias[(half ? a.b_floats[0] : 0) + e] = bias_elem(a.params, N, a.nl, e);
   if (a.mt_lds)
     for (int i = tid; i < OA * nbo; i += kNT) reinterpret_cast<float4*>(s_mt)[i] = reinterpret_cast<const float4*>(a.m_t)[i];
   const float4* mt_lds_ptr = reinterpret_cast<const float4*>(s_mt);
@@ -601,7 +688,7 @@ __global__ __launch_bounds__(kNT) void rollout_f32_kernel(RolloutF32Args a) {
     }
     __syncthreads();
     for (int t = 0; t <= a.T; ++t) {
-      net_forward<WL>(N, a.nl, s_wn, s_bn, s_x0, sx0, s_a, s_b, a.sh, half ? s_val : s_mu, half ? rstride(1) : so, R / 16,
+      net_forward<WL>(a.params, N, a.nl, s_wn, s_bn, s_x0, sx0, s_a, s_b, a.sh, half ? s_val : s_mu, half ? rstride(1) : so, R / 16,
                       half == 1 || t < a.T, wave4, 4, lane);
       if (t == a.T) {
         if (tid < R && r0 + tid < a.n) a.last_value[r0 + tid] = s_val[tid * rstride(1)];
@@ -687,8 +774,7 @@ void fill_net(const gmi_model* m, int net, F32Net* N, int* w_floats, int* b_floa
   *w_floats = *b_floats = 0;
   for (int l = 0; l < m->L.n_layers; ++l) {
     const LayerInfo& li = m->L.net[net][l];
-    N->l[l] = F32Layer{m->params + li.w_off, m->params + li.b_off, li.in, li.out, (int)li.w_off, (int)li.b_off,
-                       magic(li.in)};
+    N->l[l] = F32Layer{li.in, li.out, (int)li.w_off, (int)li.b_off, magic(pad16(li.in) / 4), {0, 0, 0}};
     *w_floats += pad16(li.out) * rstride(li.in);
     *b_floats += pad16(li.out);
   }
@@ -699,15 +785,15 @@ int max_hidden(const ModelLayout& L) {
   return w;
 }
 
-size_t train_lds(const ModelLayout& L, int R, int w_floats, int b_floats) {
-  size_t n = (size_t)w_floats + b_floats;
+size_t train_lds(const ModelLayout& L, int R, int b_floats) {
+  size_t n = b_floats;
   int sdz = 0;
   for (int l = 0; l < L.n_layers; ++l) {
     n += (size_t)R * rstride(L.net[0][l].in);
     sdz = std::max(sdz, rstride(L.net[0][l].out));
   }
   const int A = L.act_dim;
-  n += (size_t)R * (2 * sdz + rstride(A)) + ((R * A + 3) & ~3) + 5 * R + 2 * A + 4 + A;
+  n += (size_t)R * (2 * sdz + rstride(A)) + ((R * A + 3) & ~3) + 9 * R + 2 * A + 4 + A;
   return 4 * n;
 }
 
@@ -730,9 +816,11 @@ int launch_agent_f32(gmi_instance* g, gmi_model* m, const float* obs, int n, uin
   int wf[2], bf[2];
   for (int net = 0; net < 2; ++net) fill_net(m, net, &a.net[net], &wf[net], &bf[net]);
   a.nl = L.n_layers; a.n = n; a.obs_dim = L.obs_dim; a.act_dim = L.act_dim;
-  a.o_magic = magic(L.obs_dim);
+  a.o_magic = magic(pad16(L.obs_dim) / 4);
   a.sh = rstride(max_hidden(L));
   a.b_floats = std::max(bf[0], bf[1]);
+  a.b_net[0] = bf[0]; a.b_net[1] = bf[1];
+  a.params = m->params;
   auto lds = [&](int R) {
     return 4 * (a.b_floats + (size_t)R * (rstride(L.obs_dim) + 2 * a.sh + rstride(L.act_dim) + (L.act_dim + 3) / 4));
   };
@@ -745,19 +833,22 @@ int launch_agent_f32(gmi_instance* g, gmi_model* m, const float* obs, int n, uin
   int R = 64;
   while (R > 16 && (lds(R) > (R == 64 ? kLdsMax / 2 : kLdsMax) || (n + R - 1) / R < g->cu_count / 2)) R >>= 1;
   if (lds(R) > kLdsMax) return GMI_ERR_UNSUPPORTED;
-  a.R = R;
   a.net0 = do_policy ? 0 : 1;
   a.log_std = m->params + L.logstd_off;
   a.obs = obs;
   a.k0 = (uint32_t)seed; a.k1 = (uint32_t)(seed >> 32); a.step = step; a.env_offset = env_offset;
   a.act = act; a.logp = logp; a.value = value; a.mu_out = mu_out;
-  static DeviceSet allowed;
-  const int rc = allow_lds((const void*)agent_f32_kernel, kLdsMax, g->device, &allowed);
-  if (rc != GMI_OK) return rc;
-  ProfScope ps(g, kClsFusedAgent);
-  ps.launch(agent_f32_kernel, dim3((n + R - 1) / R, 2 - a.net0), dim3(kNT), lds(R), a);
-  GMI_LAUNCH_CHECK();
-  return GMI_OK;
+  auto go = [&](auto rt) -> int {
+    constexpr int RT = decltype(rt)::value;
+    static DeviceSet allowed;
+    const int rc = allow_lds((const void*)agent_f32_kernel<RT>, kLdsMax, g->device, &allowed);
+    if (rc != GMI_OK) return rc;
+    ProfScope ps(g, kClsFusedAgent);
+    ps.launch(agent_f32_kernel<RT>, dim3((n + R - 1) / R, 2 - a.net0), dim3(kNT), lds(R), a);
+    GMI_LAUNCH_CHECK();
+    return GMI_OK;
+  };
+  return R == 16 ? go(std::integral_constant<int, 1>{}) : R == 32 ? go(std::integral_constant<int, 2>{}) : go(std::integral_constant<int, 4>{});
 }
 
 int launch_train_f32(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_hparams* hp, const int32_t* idx, int rows,
@@ -767,22 +858,17 @@ int launch_train_f32(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo
   TrainF32Args a;
   int wf[2], bf[2];
   for (int net = 0; net < 2; ++net) fill_net(m, net, &a.net[net], &wf[net], &bf[net]);
-  a.w_floats = std::max(wf[0], wf[1]);
-  a.w_net[0] = wf[0]; a.w_net[1] = wf[1];
   a.b_floats = std::max(bf[0], bf[1]);
+  a.b_net[0] = bf[0]; a.b_net[1] = bf[1];
+  a.params = m->params;
   // the shortest tile with which a workgroup per net and two compute units holds all rows, else the tallest that
-  // fits.  us per minibatch with Adam for 16 / 32 / 64 rows: 17:64:64:6 27.7 / 29.8 / 34 for 2048 rows, 45 / 32 / 35 for 3000,
-  // 61 / 53 / 37 for 6000, 144 / 93 / 62 for 16384; 45:128:128:12 49 / 50 / 64 for 2048, 81 / 54 / 67 for 3000
+  // fits.  us per minibatch with Adam for 16 / 32 rows (before this form of the kernel with the same rule): 17:64:64:6 21.2 / 21.7
+  // (27.9) for 2048 rows, 32 / 23.7 (32) for 4096, with 64 rows 28.6 (37.1) for 8192, 81 (109) for 32768; 45:128:128:12 35.9 / 37.3
+  // (49) for 2048, 55 / 42 (55) for 4096, 57 (72) for 8192; 60:256:128:64:8 53 / 62 (79) for 2048, 247 (353) for 16384
   const int most = trainer_groups(cus);
   int R = 16;
-  if (train_lds(L, R, 0, a.b_floats) > kLdsMax) return GMI_ERR_UNSUPPORTED;
-  while (R < 64 && (rows + R - 1) / R > most && train_lds(L, 2 * R, 0, a.b_floats) <= kLdsMax) R *= 2;
-  // an LDS copy of the weights where it serves several tiles (17:64:64:6, 32768 rows: 109 us against 112) or is small enough to
-  // be there before the gather is (8:32:32:2, 9 KB: 20.6 / 21.2 for 256 rows; 20:48:48:4, 20 KB: 24.6 / 23.7 for 1000;
-  // 45:128:128:12, 96 KB: 63 / 49 for 2048)
-  const bool wl = train_lds(L, R, a.w_floats, a.b_floats) <= kLdsMax &&
-                  ((rows + R - 1) / R > most || 4 * (size_t)a.w_floats <= kSmallWeights);
-  a.R = R;
+  if (train_lds(L, R, a.b_floats) > kLdsMax) return GMI_ERR_UNSUPPORTED;
+  while (R < 64 && (rows + R - 1) / R > most && train_lds(L, 2 * R, a.b_floats) <= kLdsMax) R *= 2;
   a.nl = L.n_layers; a.rows = rows; a.obs_dim = L.obs_dim; a.act_dim = L.act_dim;
   a.n_tiles = (rows + R - 1) / R;
   a.sdz = 0;
@@ -793,7 +879,7 @@ int launch_train_f32(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo
     a.sdz = std::max(a.sdz, rstride(L.net[0][l].out));
   }
   a.h_floats = off;
-  a.o_magic = magic(L.obs_dim); a.a_magic = magic(L.act_dim);
+  a.o_magic = magic(pad16(L.obs_dim) / 4); a.a_magic = magic(L.act_dim);
   a.log_std = m->params + L.logstd_off;
   a.idx = idx;
   a.b_obs = b->d.obs; a.b_act = b->d.act; a.b_logp = b->d.logp; a.b_adv = b->d.adv; a.b_ret = b->d.ret;
@@ -802,15 +888,18 @@ int launch_train_f32(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo
   a.part = m->grad_part; a.part_stride = L.n_params;
   a.stat_part = m->stat_part;
   const int groups = std::min(a.n_tiles, std::min(most, m->part_rows));
-  static DeviceSet allowed[2];
-  const int rc = allow_lds(wl ? (const void*)train_f32_kernel<true> : (const void*)train_f32_kernel<false>, kLdsMax, g->device, &allowed[wl]);
-  if (rc != GMI_OK) return rc;
   *n_parts = groups;
-  ProfScope ps(g, kClsChainTrain);
-  if (wl) ps.launch(train_f32_kernel<true>, dim3(groups, 2), dim3(kNT), train_lds(L, R, a.w_floats, a.b_floats), a);
-  else ps.launch(train_f32_kernel<false>, dim3(groups, 2), dim3(kNT), train_lds(L, R, 0, a.b_floats), a);
-  GMI_LAUNCH_CHECK();
-  return GMI_OK;
+  auto go = [&](auto rt) -> int {
+    constexpr int RT = decltype(rt)::value;
+    static DeviceSet allowed;
+    const int rc = allow_lds((const void*)train_f32_kernel<RT>, kLdsMax, g->device, &allowed);
+    if (rc != GMI_OK) return rc;
+    ProfScope ps(g, kClsChainTrain);
+    ps.launch(train_f32_kernel<RT>, dim3(groups, 2), dim3(kNT), train_lds(L, R, a.b_floats), a);
+    GMI_LAUNCH_CHECK();
+    return GMI_OK;
+  };
+  return R == 16 ? go(std::integral_constant<int, 1>{}) : R == 32 ? go(std::integral_constant<int, 2>{}) : go(std::integral_constant<int, 4>{});
 }
 
 }  // namespace gmi
@@ -832,6 +921,7 @@ extern "C" int rollout_collect_f32(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_bu
   fill_rollout_env(m, env, b, obs, seed, step0, env_offset, last_value, &a);
   a.log_std = m->params + L.logstd_off;
   for (int net = 0; net < 2; ++net) fill_net(m, net, &a.net[net], &a.w_floats[net], &a.b_floats[net]);
+  a.params = m->params;
   a.nl = L.n_layers;
   a.sh = rstride(max_hidden(L));
   const int O = L.obs_dim, A = L.act_dim, nba = (A + 3) / 4, nbo = a.o4 / 4, npr = nba + nbo + 1;

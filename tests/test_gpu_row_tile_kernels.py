@@ -364,3 +364,29 @@ def test_two_launch_collection_through_the_row_tile_kernel(g, hidden, n, cus, ti
         assert torch.equal(ses[0].state(), ses[1].state()) and torch.equal(ses[0].last_value, ses[1].last_value)
     for s in reversed(ses):
         s.close()
+
+
+@pytest.mark.parametrize("obs,n", [(1, 4096), (2, 33), (3, 700), (5, 17)])
+def test_fp32_elu_is_within_an_ulp(g, inst, obs, n):
+    """One hidden unit copies the last observation, the head copies the unit: the mean is ELU(x) itself (every other product is
+    zero).  The kernel's e^x - 1 is within 0.86 ulp of the exact value, its place in a sum of zeros exact: 1 ulp; beyond -30 and
+    at -inf it is -1."""
+    act, hidden, dev = 2, [33], torch.device("cuda:0")
+    theta = torch.zeros(sum(33 * (obs + 1) + 33 * o + o for o in (act, 1)) + act)
+    theta[obs - 1] = 1.0                          # policy W0[0][obs - 1]
+    theta[33 * (obs + 1)] = 1.0                   # policy W1[0][0]
+    rng = np.random.default_rng(obs)
+    x = rng.standard_normal((n, obs)).astype(np.float32)
+    x[:, -1] = np.concatenate([-np.exp(rng.uniform(-20, 3.4, n - 4)), [-31.0, -1e30, -0.0, 2.5]]).astype(np.float32)
+    xd, theta = torch.tensor(x, device=dev), theta.to(dev)
+    model = g.gmi_model_bind(inst, g.model_desc(obs, act, hidden, g.dtype_code("f32"), n), theta, None)
+    o = [torch.zeros(s, device=dev) for s in ((n, act), (n,), (n,), (n, act))]
+    torch.cuda.synchronize()
+    g.agent_act(inst, model, xd, n, 42, 9, 0, *o)
+    g.gmi_sync(inst)
+    g.gmi_model_destroy(model)
+    got = o[3].cpu().numpy()[:, 0].astype(np.float64)
+    z = x[:, -1].astype(np.float64)
+    want = np.where(z > 0, z, np.expm1(np.minimum(z, 0.0)))
+    ulp = np.spacing(np.abs(want).astype(np.float32)).astype(np.float64)
+    assert (np.abs(got - want) <= ulp).all(), (np.abs(got - want) / ulp).max()
