@@ -5,15 +5,16 @@
 
 namespace {
 
-// m_t[k, o] (row stride o4) = A[o, k] for k < O, B[o, k-O] for O <= k < O+A; zero padded columns.
+// m_t[k, o] (row stride o4) and m_r[o, k] (row stride ms) = A[o, k] for k < O, B[o, k-O] for O <= k < O+A; zero padded.
 __global__ void build_env_matrix(const float* __restrict__ a_mat, const float* __restrict__ b_mat, int O,
-                                 int A, int o4, float* __restrict__ m_t) {
+                                 int A, int o4, int ms, float* __restrict__ m_t, float* __restrict__ m_r) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (O + A) * o4) return;
+  if (idx >= ms * o4) return;
   const int k = idx / o4, o = idx % o4;
   float v = 0.f;
-  if (o < O) v = k < O ? a_mat[o * O + k] : b_mat[o * A + (k - O)];
-  m_t[idx] = v;
+  if (o < O && k < O + A) v = k < O ? a_mat[o * O + k] : b_mat[o * A + (k - O)];
+  if (k < O + A) m_t[idx] = v;
+  m_r[o * ms + k] = v;
 }
 
 // FUSED (gmi::StepFuse, internal.h): what the collection stage of a model too large for the one-launch rollout kernel
@@ -209,7 +210,7 @@ __global__ __launch_bounds__(256) void env_step_kernel(
         if (o < O) { const float x = xin[i * OS + o]; ps = fmaf(x, x, ps); }
       }
       for (int a = b; a < A; a += nb) { const float x = xin[i * OS + O + a]; pa = fmaf(x, x, pa); }
-      s_part[(g * EPT + i) * nb + b] = ps + 0.01f * pa;
+      s_part[(g * EPT + i) * nb + b] = gmi::reward_part(ps, pa);
     }
   }
   __syncthreads();
@@ -266,10 +267,12 @@ extern "C" int gmi_env_bind(gmi_t g, const gmi_env_desc* d, const float* a_mat, 
     GMI_FAIL(GMI_ERR_BAD_SHAPE, "gmi_env_bind: need n_envs >= 0, 1 <= obs_dim, act_dim <= 1024");
   const int O = d->obs_dim, A = d->act_dim;
   const int o4 = (O + 3) & ~3;
+  const int ms = gmi::env_row_stride(O, A);
   float* m_t = nullptr;
-  GMI_HIP(hipMalloc(&m_t, sizeof(float) * (size_t)(O + A) * o4));
-  const int total = (O + A) * o4;
-  build_env_matrix<<<(total + 255) / 256, 256, 0, g->stream>>>(a_mat, b_mat, O, A, o4, m_t);
+  GMI_HIP(hipMalloc(&m_t, sizeof(float) * (size_t)(O + A + ms) * o4));
+  float* m_r = m_t + (size_t)(O + A) * o4;      // o4 is a multiple of 4: 16-byte aligned
+  const int total = ms * o4;
+  build_env_matrix<<<(total + 255) / 256, 256, 0, g->stream>>>(a_mat, b_mat, O, A, o4, ms, m_t, m_r);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
   if (e != hipSuccess) {
@@ -280,6 +283,7 @@ extern "C" int gmi_env_bind(gmi_t g, const gmi_env_desc* d, const float* a_mat, 
   env->magic = gmi::kMagicEnv;
   env->d = *d;
   env->m_t = m_t;
+  env->m_r = m_r;
   env->episode_step = episode_step;
   *out = env;
   return GMI_OK;

@@ -304,11 +304,11 @@ __device__ __forceinline__ void layer(const float* params, const F32Layer& L, co
 }
 
 // All layers of a net on the tile in s_x0; hidden activations ping-pong between s_a and s_b (stride sh); the head goes to
-// s_out (stride so).  `run`: whether these waves take part (every thread reaches every barrier).
-template <bool WL>
+// s_out (stride so).  `run`: whether these waves take part (every thread reaches every barrier).  beside(): called with the head.
+template <bool WL, class Beside>
 __device__ __forceinline__ void net_forward(const float* params, const Layers& N, int nl, const float* s_w, const float* s_bias, const float* s_x0,
                                             int sx0, float* s_a, float* s_b, int sh, float* s_out, int so, int RT, bool run,
-                                            int wave, int nw, int lane) {
+                                            int wave, int nw, int lane, Beside beside) {
   const float* x = s_x0;
   int sx = sx0;
   float* y = s_a;
@@ -318,6 +318,7 @@ __device__ __forceinline__ void net_forward(const float* params, const Layers& N
       if (l < nl - 1) layer<WL, kHidden>(params, L, s_w, s_bias, x, sx, nullptr, y, sh, RT, wave, nw, lane);
       else layer<WL, kHead>(params, L, s_w, s_bias, x, sx, nullptr, s_out, so, RT, wave, nw, lane);
     }
+    if (l == nl - 1) beside();
     __syncthreads();
     if constexpr (WL) s_w += pad16(L.out) * rstride(L.in);
     s_bias += pad16(L.out);
@@ -358,7 +359,7 @@ __global__ __launch_bounds__(kNT) void agent_f32_kernel(AgentF32Args a) {
   stage_rows<R>(O, a.o_magic, [&](int r) { return a.obs + (int64_t)min(r0 + r, a.n - 1) * O; }, s_x0, tid);
   for (int e = tid; e < a.b_net[net]; e += kNT) s_bias[e] = bias_elem(a.params, N, a.nl, e);
   __syncthreads();
-  net_forward<false>(a.params, N, a.nl, smem, s_bias, s_x0, sx0, s_a, s_b, a.sh, s_out, so, RT, true, wave, kNW, lane);
+  net_forward<false>(a.params, N, a.nl, smem, s_bias, s_x0, sx0, s_a, s_b, a.sh, s_out, so, RT, true, wave, kNW, lane, []() {});
   if (net == 1) {
     for (int r = tid; r < R; r += kNT)
       if (r0 + r < a.n) a.value[r0 + r] = s_out[r * so];
@@ -627,30 +628,35 @@ __global__ __launch_bounds__(kNT) void train_f32_kernel(TrainF32Args a) {
 struct RolloutF32Args : RolloutEnv {
   F32Net net[2];
   const float* params;
-  int nl, sh, w_floats[2], b_floats[2], mt_lds;
+  int nl, sh, w_floats[2], b_floats[2], mr_lds;
+  int ahead;               // 1: a step's draws are made beside the step before it (two buffers), 0: ahead of it, in the idle hidden space
+  int hid_floats;          // of all hidden activations
 };
+
+__host__ __device__ __forceinline__ int in_stride(int O, int A) { return (O + A + 3) & ~3; }
 
 template <bool WL>
 __global__ __launch_bounds__(kNT) void rollout_f32_kernel(RolloutF32Args a) {
   extern __shared__ __attribute__((aligned(16))) float smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int half = __builtin_amdgcn_readfirstlane(tid >> 8), wave4 = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);
-  const int R = a.rows_per_wg, O = a.obs_dim, A = a.act_dim, OA = O + A, o4 = a.o4, nbo = o4 >> 2, nba = (A + 3) >> 2;
+  const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int R = a.rows_per_wg, O = a.obs_dim, A = a.act_dim, OS = in_stride(O, A), nbo = a.o4 >> 2, nba = (A + 3) >> 2;
   const int npr = nba + nbo + 1, sx0 = rstride(O), so = rstride(A);
   float* s_w = smem;
   float* s_bias = s_w + (WL ? a.w_floats[0] + a.w_floats[1] : 0);
   float* s_x0 = s_bias + a.b_floats[0] + a.b_floats[1];
   float* s_hid = s_x0 + R * sx0;                                   // [2 nets][2][R][sh]
-  float* s_mu = s_hid + 4 * R * a.sh;                              // [R][so]
+  float* s_mu = s_hid + a.hid_floats;                              // [R][so]
   float* s_val = s_mu + R * so;                                    // [R][rstride(1)]
-  float* s_next = s_val + R * rstride(1);                          // [R][o4]
-  float4* s_noise2 = reinterpret_cast<float4*>(s_next + R * o4);   // [2][R][npr]
-  float* s_in = reinterpret_cast<float*>(s_noise2 + 2 * R * npr);  // [R][O + A] state | action
-  float* s_lp = s_in + ((R * OA + 3) & ~3);                        // [R][nba]
+  float* s_in2 = s_val + R * rstride(1);                           // [2][R][OS] state | action, of this and the next step
+  float* s_end = s_in2 + 2 * R * OS;
+  float4* s_noise2 = reinterpret_cast<float4*>(a.ahead ? s_end : s_hid);      // [ahead + 1][R][npr]
+  float* s_lp = a.ahead ? s_end + 8 * R * npr : s_end;             // [R][nba]
   float* s_part = s_lp + R * nba;                                  // [R][nbo]
   int* s_done = reinterpret_cast<int*>(s_part + R * nbo);          // [R]
   float* s_ls = reinterpret_cast<float*>(s_done + R);              // [A] log_std, [A] exp(log_std)
-  float* s_mt = s_ls + ((2 * A + 3) & ~3);                         // [O + A][o4] when mt_lds
+  float* s_m = s_ls + ((2 * A + 3) & ~3);                          // [o4][ms] when mr_lds
   const Layers N(a.net[half]);
   const float* s_wn = s_w + (half ? a.w_floats[0] : 0);
   const float* s_bn = s_bias + (half ? a.b_floats[0] : 0);
@@ -666,105 +672,76 @@ __global__ __launch_bounds__(kNT) void rollout_f32_kernel(RolloutF32Args a) {
     }
   }
   for (int e = tid & 255; e < a.b_floats[half]; e += 256) s_bias[(half ? a.b_floats[0] : 0) + e] = bias_elem(a.params, N, a.nl, e);
-  if (a.mt_lds)
-    for (int i = tid; i < OA * nbo; i += kNT) reinterpret_cast<float4*>(s_mt)[i] = reinterpret_cast<const float4*>(a.m_t)[i];
-  const float4* mt_lds_ptr = reinterpret_cast<const float4*>(s_mt);
-  const float4* mt_glb_ptr = reinterpret_cast<const float4*>(a.m_t);
+  if (a.mr_lds)
+    for (int i = tid; i < a.o4 * (a.ms >> 2); i += kNT) reinterpret_cast<float4*>(s_m)[i] = reinterpret_cast<const float4*>(a.m_r)[i];
+  for (int i = tid; i < R * sx0; i += kNT) s_x0[i] = 0.f;
+  for (int i = tid; i < R * OS; i += kNT) s_in2[R * OS + i] = 0.f;
+  const SimLane sl = sim_lane(a, wave8, OS, lane);
+  __syncthreads();
 
   for (int tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
     const int r0 = tile * R;
-    for (int i = tid; i < R * O; i += kNT) {
-      const int r = i / O, k = i - r * O;
-      s_in[r * OA + k] = (r0 + r < a.n) ? a.obs_state[(int64_t)(r0 + r) * O + k] : 0.f;
-    }
-    const int dtid = tid - (kNT - 64);        // the last wave carries the episode counters
+    load_states(a, r0, s_in2, OS, tid);
+    const int et = tid - (kNT - 64);          // the last wave carries the episode counters, makes the done flags and writes the sums
+    const bool env_thread = et >= 0 && et < R, env_ok = env_thread && r0 + et < a.n;
     uint32_t ep = 0;
-    if (dtid >= 0 && dtid < R && r0 + dtid < a.n) ep = a.episode_step[r0 + dtid];
-    draw_items(a, s_noise2, a.step0, R, r0, npr, nba, nbo, tid, kNT);
+    if (env_ok) ep = a.episode_step[r0 + et];
+    if (a.ahead) draw_all(a, s_noise2, a.step0, r0, npr, nba, tid);
     __syncthreads();
-    for (int i = tid; i < R * sx0; i += kNT) {
-      const int r = i / sx0, k = i - r * sx0;
-      s_x0[i] = k < O ? s_in[r * OA + k] : 0.f;
+    {
+      const int r = tid >> a.row_shift, c = tid & ((1 << a.row_shift) - 1), nc = 1 << a.row_shift;
+      for (int k = c; k < O; k += nc) s_x0[r * sx0 + k] = s_in2[r * OS + k];
     }
     __syncthreads();
-    for (int t = 0; t <= a.T; ++t) {
+    int64_t slot0 = r0;
+    auto reward = [&]() {      // of the step before
+      if (env_ok) a.b_rew[slot0 - a.ld_envs + et] = -a.reward_scale * block_sum(s_part + et * nbo, nbo);
+    };
+    for (int t = 0; t <= a.T; ++t, slot0 += a.ld_envs) {
+      float* s_in = s_in2 + (t & 1) * R * OS;
+      float4* s_noise = s_noise2 + (a.ahead ? (t & 1) * R * npr : 0);
+      const uint32_t step = a.step0 + (uint32_t)t;
+      // beside the heads, whose tiles leave the last wave idle: the reward of the step before and, where the draws are there,
+      // this step's done flags
       net_forward<WL>(a.params, N, a.nl, s_wn, s_bn, s_x0, sx0, s_a, s_b, a.sh, half ? s_val : s_mu, half ? rstride(1) : so, R / 16,
-                      half == 1 || t < a.T, wave4, 4, lane);
+                      half == 1 || t < a.T, wave4, 4, lane, [&]() {
+                        if (!env_thread) return;
+                        if (t > 0) reward();
+                        if (a.ahead && t < a.T) finish_env(a, r0, slot0, et, s_noise, npr, ep, s_done);
+                                      });
       if (t == a.T) {
-        if (tid < R && r0 + tid < a.n) a.last_value[r0 + tid] = s_val[tid * rstride(1)];
+        if (env_ok) a.last_value[r0 + et] = s_val[et * rstride(1)];
         break;
       }
-      const float4* s_noise = s_noise2 + (t & 1) * R * npr;
-      const uint32_t step = a.step0 + (uint32_t)t;
-      const int64_t slot0 = (int64_t)t * a.ld_envs + r0;
-      for (int item = tid; item < R * nba * 4; item += kNT) {
-        const int blk = item >> 2, i = item & 3;
-        const int r = blk / nba, b = blk - r * nba;
-        const int j = 4 * b + i;
-        float term = 0.f;
-        if (j < A) {
-          float act = 0.f;
-          if (r0 + r < a.n) {
-            const float z = reinterpret_cast<const float*>(s_noise + r * npr + b)[i];
-            const float ls = s_ls[j];
-            act = fmaf(s_ls[A + j], z, s_mu[r * so + j]);
-            a.b_act[(slot0 + r) * A + j] = act;
-            term = -0.5f * z * z - ls - 0.918938533204672742f;
-          }
-          s_in[r * OA + O + j] = act;
-        }
-        float lp = term;
-        lp += __shfl_down(term, 1, 64);
-        lp += __shfl_down(term, 2, 64);
-        lp += __shfl_down(term, 3, 64);
-        if (i == 0) s_lp[blk] = lp;
+      if (!a.ahead) {
+        draw_all(a, s_noise, step, r0, npr, nba, tid);
+        __syncthreads();
+        if (env_thread) finish_env(a, r0, slot0, et, s_noise, npr, ep, s_done);
       }
-      // the step's observations, last threads first (the first ones have the action items)
-      for (int i = kNT - 1 - tid; i < R * O; i += kNT) {
-        const int r = i / O, k = i - r * O;
-        if (r0 + r < a.n) a.b_obs[(slot0 + r) * O + k] = s_in[r * OA + k];
-      }
-      if (dtid >= 0 && dtid < R) {
-        int d = 0;
-        if (r0 + dtid < a.n) {
-          if (a.done_period > 0) d = ((ep + 1u) % a.done_period) == 0u;
-          else d = __float_as_uint(s_noise[dtid * npr + nba + nbo].x) < a.done_threshold;
-          ep = d ? 0u : ep + 1u;
-          a.b_done[slot0 + dtid] = (uint8_t)d;
-          a.b_val[slot0 + dtid] = s_val[dtid * rstride(1)];
-        }
-        s_done[dtid] = d;
-      }
+      sample_and_store(a, r0, slot0, s_in, OS, s_mu, so, s_noise, npr, nba, s_ls, s_lp, tid);
       __syncthreads();
-      if (tid < R && r0 + tid < a.n) {
-        float lp = 0.f;
-        for (int b = 0; b < nba; ++b) lp += s_lp[tid * nba + b];
-        a.b_logp[slot0 + tid] = lp;
+      float* s_nxt = s_in2 + ((t + 1) & 1) * R * OS;
+      auto put = [&](int r, int o, const float (&v)[4]) {      // (what lies beyond the state belongs to the next step's actions)
+        *reinterpret_cast<float4*>(s_nxt + r * OS + o) = make_float4(v[0], v[1], v[2], v[3]);
+        *reinterpret_cast<float4*>(s_x0 + r * sx0 + o) =
+            make_float4(v[0], o + 1 < O ? v[1] : 0.f, o + 2 < O ? v[2] : 0.f, o + 3 < O ? v[3] : 0.f);
+      };
+      if (a.mr_lds) sim_items(a, r0, step, sl, s_in, OS, s_m, s_part, s_done, s_noise, npr, nba, wave8, lane, put);
+      else sim_items(a, r0, step, sl, s_in, OS, a.m_r, s_part, s_done, s_noise, npr, nba, wave8, lane, put);
+      if (env_ok) {
+        a.b_logp[slot0 + et] = block_sum(s_lp + et * nba, nba);
+        a.b_val[slot0 + et] = s_val[et * rstride(1)];
       }
-      // the next step's draws, last threads first (the simulator's items go to the first ones)
-      if (t + 1 < a.T)
-        draw_items(a, s_noise2 + ((t + 1) & 1) * R * npr, step + 1u, R, r0, npr, nba, nbo, kNT - 1 - tid, kNT);
-      if (a.mt_lds) sim_step<false>(R, nbo, a, r0, step, s_in, O + A, mt_lds_ptr, s_part, s_next, s_done, s_noise, npr, nba);
-      else sim_step<false>(R, nbo, a, r0, step, s_in, O + A, mt_glb_ptr, s_part, s_next, s_done, s_noise, npr, nba);
-      __syncthreads();
-      if (dtid >= 0 && dtid < R && r0 + dtid < a.n) {
-        float sum = 0.f;
-        for (int b = 0; b < nbo; ++b) sum += s_part[dtid * nbo + b];
-        a.b_rew[slot0 + dtid] = -a.reward_scale * sum;
-      }
-      for (int i = tid; i < R * O; i += kNT) {
-        const int r = i / O, k = i - r * O;
-        const float v = r0 + r < a.n ? s_next[r * o4 + k] : 0.f;
-        s_in[r * OA + k] = v;
-        s_x0[r * sx0 + k] = v;
-      }
+      if (a.ahead && t + 1 < a.T) draw_rest(a, s_noise2 + ((t + 1) & 1) * R * npr, step + 1u, r0, npr, nba, tid);
       __syncthreads();
     }
-    for (int i = tid; i < R * O; i += kNT) {
-      const int r = i / O, k = i - r * O;
-      if (r0 + r < a.n) a.obs_state[(int64_t)(r0 + r) * O + k] = s_in[r * OA + k];
+    {
+      const float* s_in = s_in2 + (a.T & 1) * R * OS;
+      const int r = tid >> a.row_shift, c = tid & ((1 << a.row_shift) - 1), nc = 1 << a.row_shift;
+      if (r0 + r < a.n)
+        for (int k = c; k < O; k += nc) a.obs_state[(int64_t)(r0 + r) * O + k] = s_in[r * OS + k];
     }
-    if (dtid >= 0 && dtid < R && r0 + dtid < a.n) a.episode_step[r0 + dtid] = ep;
+    if (env_ok) a.episode_step[r0 + et] = ep;
     __syncthreads();
   }
 }
@@ -925,25 +902,34 @@ extern "C" int rollout_collect_f32(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_bu
   a.nl = L.n_layers;
   a.sh = rstride(max_hidden(L));
   const int O = L.obs_dim, A = L.act_dim, nba = (A + 3) / 4, nbo = a.o4 / 4, npr = nba + nbo + 1;
-  auto lds = [&](int R, bool wl, bool mt) {
-    return 4 * ((size_t)(wl ? a.w_floats[0] + a.w_floats[1] : 0) + a.b_floats[0] + a.b_floats[1] +
-                (size_t)R * (rstride(O) + 4 * a.sh + rstride(A) + rstride(1) + a.o4 + 8 * npr + nba + nbo + 1) +
-                ((R * (O + A) + 3) & ~3) + ((2 * A + 3) & ~3) + (mt ? (size_t)(O + A) * a.o4 : 0));
+  auto hid_floats = [&](int R, bool ahead) { return 4 * R * std::max(a.sh, ahead ? 0 : npr); };
+  auto lds = [&](int R, bool wl, bool mr, bool ahead) {
+    return 4 * ((size_t)(wl ? a.w_floats[0] + a.w_floats[1] : 0) + a.b_floats[0] + a.b_floats[1] + hid_floats(R, ahead) +
+                (size_t)R * (rstride(O) + rstride(A) + rstride(1) + 2 * in_stride(O, A) + (ahead ? 8 * npr : 0) + nba + nbo + 1) +
+                ((2 * A + 3) & ~3) + (mr ? (size_t)a.o4 * a.ms : 0));
   };
   // 32 envs per workgroup once tiles of 16 are more than the compute units, which hold one workgroup each.  us for 16 steps,
-  // 16 / 32 envs: 17:64:64:6 133 / 159 for 4096 envs, 245 / 159 for 5000; 45:128:128:12 289 / 362, 569 / 360; 60:128:64:8 243 /
-  // 301, 475 / 305
-  const int R = (a.n + 15) / 16 > g->cu_count && lds(32, false, false) <= kLdsMax ? 32 : 16;
-  if (lds(R, false, false) > kLdsMax)
+  // 16 / 32 envs (the kernel's first form): 17:64:64:6 133 / 159 for 4096 envs, 245 / 159 for 5000; 45:128:128:12 289 / 362, 569 /
+  // 360; 60:128:64:8 243 / 301, 475 / 305
+  // Height and refusal go by the bytes of the kernel's first form (one state per env, two steps' draws): what was refused stays
+  // refused.  Without draws ahead the present form never takes more.
+  auto admission = [&](int R) {
+    return 4 * ((size_t)a.b_floats[0] + a.b_floats[1] +
+                (size_t)R * (rstride(O) + 4 * a.sh + rstride(A) + rstride(1) + a.o4 + 8 * npr + nba + nbo + 1) + ((R * (O + A) + 3) & ~3) +
+                ((2 * A + 3) & ~3));
+  };
+  const int R = (a.n + 15) / 16 > g->cu_count && admission(32) <= kLdsMax ? 32 : 16;
+  if (admission(R) > kLdsMax)
     GMI_FAIL(GMI_ERR_UNSUPPORTED, "rollout_collect_f32: a 16-env tile of this model needs %zu bytes of LDS (limit %zu); "
-             "use agent_act / env_step / collect_experience", lds(R, false, false), kLdsMax);
+             "use agent_act / env_step / collect_experience", admission(R), kLdsMax);
+  a.ahead = lds(R, false, false, true) <= kLdsMax ? 1 : 0;
+  a.hid_floats = hid_floats(R, a.ahead != 0);
   // what stays on chip for all steps: the networks' weights first (read by every layer; 17:64:64:6, 16 steps: 129 us with them,
   // 153 without), then the simulator's matrix
-  const bool wl = lds(R, true, false) <= kLdsMax;
-  a.mt_lds = lds(R, wl, true) <= kLdsMax ? 1 : 0;
-  const size_t bytes = lds(R, wl, a.mt_lds != 0);
-  a.rows_per_wg = R;
-  a.n_tiles = (a.n + R - 1) / R;
+  const bool wl = lds(R, true, false, a.ahead != 0) <= kLdsMax;
+  a.mr_lds = lds(R, wl, true, a.ahead != 0) <= kLdsMax ? 1 : 0;
+  const size_t bytes = lds(R, wl, a.mr_lds != 0, a.ahead != 0);
+  set_rows(&a, R);
   static gmi::DeviceSet allowed[2];
   const int rc2 = gmi::allow_lds(wl ? (const void*)rollout_f32_kernel<true> : (const void*)rollout_f32_kernel<false>, kLdsMax, g->device, &allowed[wl]);
   if (rc2 != GMI_OK) return rc2;

@@ -58,12 +58,11 @@ struct RolloutArgs : RolloutEnv {
   FusedNet net[2];
   gmi_agent::AgentLayer policy[gmi_agent::kMaxLayers];      // the streaming form's view of the policy net
   int obs_pad, max_h;
-  int mt_lds;                       // m_t: 2 = LDS copy kept for the whole launch, 1 = LDS copy made at every
+  int mr_lds;                       // m_r: 2 = LDS copy kept for the whole launch, 1 = LDS copy made at every
                                     // step in the (then idle) hidden-activation space, 0 = read from global
-  int obs_vec;                      // 1 = observation rows are whole 16-byte pieces in the buffer and in the LDS tile
-  int noise_ahead;                  // 1 = the waves without simulator items make step t+1's random draws while the
-                                    // others run step t's simulator (two buffers at byte ahead_off of the LDS)
-  int ahead_off;
+  int ahead;                        // 1 = step t + 1's random draws are made beside step t's simulator (two buffers)
+  // LDS bytes: next to the state rows at 0 ([2][rows_per_wg][OS] state | action, of this and the next step)
+  int x0_off, hid_off, mu_off, val_off, lp_off, part_off, done_off, ls_off, bias_off, m_off, w_off, draw_off;
 };
 
 // ------------------------------------------------------------------------------------------------
@@ -258,40 +257,42 @@ __device__ __forceinline__ void ws_layer16(const bf16x8* wreg, const uint16_t* s
   }
 }
 
-template <class WS, int L>
+template <class WS, int L, class Idle>
 __device__ __forceinline__ void ws_net16(const bf16x8* wreg, const uint16_t* s_w, const FusedNet& N, const float* s_nb,
                                          const uint16_t* in, int stride_in, uint16_t* s_a, uint16_t* s_b, int stride_h,
-                                         float* s_head, int head_stride, bool run, int wave, int lane) {
+                                         float* s_head, int head_stride, bool run, int wave, int lane, Idle idle) {
   if constexpr (L < WS::NL - 1) {
     uint16_t* out = (L & 1) ? s_b : s_a;
     if (run)
       ws_layer16<WS, L, kFEpiElu>(wreg, s_w, s_nb + N.bias_off[L], in, stride_in, out, stride_h, nullptr, 0, 0, wave, lane);
     __syncthreads();
-    ws_net16<WS, L + 1>(wreg, s_w, N, s_nb, out, stride_h, s_a, s_b, stride_h, s_head, head_stride, run, wave, lane);
+    ws_net16<WS, L + 1>(wreg, s_w, N, s_nb, out, stride_h, s_a, s_b, stride_h, s_head, head_stride, run, wave, lane, idle);
   } else {
     if (run)
       ws_layer16<WS, L, kFEpiHead>(wreg, s_w, s_nb + N.bias_off[L], in, stride_in, nullptr, 0, s_head, head_stride,
                                    N.out_store, wave, lane);
+    idle();
     __syncthreads();
   }
 }
 
 // All layers of one net from layer L on, hidden activations ping-ponging between s_a and s_b as in the
 // streaming form; every layer ends with a workgroup barrier.
-template <class WS, int L, int RT>
+template <class WS, int L, int RT, class Idle>
 __device__ __forceinline__ void ws_net(const bf16x8* wreg, const uint16_t* s_w, const FusedNet& N, const float* s_nb, const uint16_t* in,
                                        int stride_in, uint16_t* s_a, uint16_t* s_b, int stride_h, float* s_head,
-                                       int head_stride, bool run, int wave, int lane) {
+                                       int head_stride, bool run, int wave, int lane, Idle idle) {
   if constexpr (L < WS::NL - 1) {
     uint16_t* out = (L & 1) ? s_b : s_a;
     if (run)
       ws_layer<WS, L, RT, kFEpiElu>(wreg, s_w, s_nb + N.bias_off[L], in, stride_in, out, stride_h, nullptr, 0, 0, wave, lane);
     __syncthreads();
-    ws_net<WS, L + 1, RT>(wreg, s_w, N, s_nb, out, stride_h, s_a, s_b, stride_h, s_head, head_stride, run, wave, lane);
+    ws_net<WS, L + 1, RT>(wreg, s_w, N, s_nb, out, stride_h, s_a, s_b, stride_h, s_head, head_stride, run, wave, lane, idle);
   } else {
     if (run)
       ws_layer<WS, L, RT, kFEpiHead>(wreg, s_w, s_nb + N.bias_off[L], in, stride_in, nullptr, 0, s_head, head_stride,
                                      N.out_store, wave, lane);
+    idle();
     __syncthreads();
   }
 }
@@ -310,74 +311,149 @@ bool ws_matches(const ModelLayout& L) {
   return true;
 }
 
+// ---- The streaming form for 16 envs per workgroup: the policy net on 16x16x32 products, 16 features a tile, dealt to all 8 waves.
+// With 32x32x16 tiles half of the products and of the epilogue's instructions are padding rows and half of the waves have no tile
+// of a 128-wide layer: three layers of 45:128:128:12 took 8300 cycles.  wq holds the first weight blocks of layer 0 for this
+// wave, and again afterwards.
+// One place in the code requests weights, and no branch goes around it (clamped addresses instead): where the registers of loads
+// from two places meet, the compiler copies them, and a copy waits for the load (2500 cycles a layer instead of 1500).
+constexpr int kAhead16 = 8;
+typedef uint4 Ring16[kAhead16];
+struct Walk16 {
+  const char* w;      // weights of the wave's tile: wave-uniform
+  int nks;            // k steps
+};
+// Where the weights of tile `tile` (the last one if there are fewer) of a layer start; lane_off is the lane's place in a k step's
+// 2 KiB.
+__device__ __forceinline__ Walk16 walk16(const uint4* w, int K, int F, int tile) {
+  const int t = min(tile, (F >> 4) - 1);
+  return {reinterpret_cast<const char*>(w) + (int64_t)(t >> 1) * (K >> 4) * 1024 + 256 * (t & 1), K >> 5};
+}
+__device__ __forceinline__ void request16(Ring16& wq, const Walk16& k, uint32_t lane_off) {
+#pragma unroll
+  for (int u = 0; u < kAhead16; ++u) wq[u] = gmi::load_uniform(k.w, min(u, k.nks - 1) * 2048, lane_off);
+}
+// idle(): called once by wave 7, in the last layer, whose tiles are the fewest.
+template <class Idle>
+__device__ __forceinline__ void net_layers16(const gmi_agent::AgentLayer* N, int nl, Ring16& wq, const unsigned char* x0, unsigned char* ya,
+                                             unsigned char* yb, const float* s_bias, float* s_head, int ho, int wave, int lane, Idle idle) {
+  const int n = lane & 15, q = lane >> 4;      // lane (n, q): env n, k values 8 q .. + 7 of a k step, features 4 q .. + 3 of a tile
+  const uint32_t lane_off = ((q >> 1) * 64 + n + 32 * (q & 1)) * 16;
+  const uint4* w = N[0].w;
+  int K = N[0].K, F = N[0].F;
+  for (int l = 0; l < nl; ++l) {
+    const gmi_agent::AgentLayer& Ln = N[l + 1 < nl ? l + 1 : 0];
+    const uint4* wn = Ln.w;
+    const int Kn = Ln.K, Fn = Ln.F;
+    const int nt = F >> 4, sx = K * 2 + 16, sy = F * 2 + 16;
+    const unsigned char* x = (l == 0 ? x0 : l & 1 ? ya : yb) + n * sx + 16 * q;
+    unsigned char* y = (l & 1 ? yb : ya) + n * sy + 8 * q;
+    const bool head = l == nl - 1;
+    int tile = wave;
+    do {      // a wave without a tile multiplies the last one again and drops it
+      const Walk16 k = walk16(w, K, F, tile);
+      const float4 b = *reinterpret_cast<const float4*>(s_bias + 16 * min(tile, nt - 1) + 4 * q);
+      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+      auto read = [&](int ks) { return *reinterpret_cast<const bf16x8*>(x + 64 * ks); };
+      auto product = [&](int u, const bf16x8& xv) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wq[u]), xv, acc, 0, 0, 0);
+      };
+      int ks = 0;
+      for (; ks + kAhead16 < k.nks; ks += kAhead16)
+#pragma unroll
+        for (int u = 0; u < kAhead16; ++u) {
+          product(u, read(ks + u));
+          wq[u] = gmi::load_uniform(k.w, min(ks + kAhead16 + u, k.nks - 1) * 2048, lane_off);
+        }
+      auto tail4 = [&](auto first) {
+        constexpr int U = decltype(first)::value;
+        bf16x8 xr[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) xr[u] = read(min(ks + U + u, k.nks - 1));
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (ks + U + u < k.nks) product(U + u, xr[u]);
+      };
+      tail4(std::integral_constant<int, 0>{});
+      if (ks + 4 < k.nks) tail4(std::integral_constant<int, 4>{});
+      const bool more = tile + 8 < nt;
+      request16(wq, more ? walk16(w, K, F, tile + 8) : walk16(wn, Kn, Fn, wave), lane_off);
+      const float v0 = acc[0] + b.x, v1 = acc[1] + b.y, v2 = acc[2] + b.z, v3 = acc[3] + b.w;
+      if (tile >= nt) {
+      } else if (!head) {
+        *reinterpret_cast<uint2*>(y + 32 * tile) = make_uint2(pack_bf16(elu_f(v0), elu_f(v1)), pack_bf16(elu_f(v2), elu_f(v3)));
+      } else {
+        const int f = 16 * tile + 4 * q;
+        float* d = s_head + n * ho + f;
+        if (f + 0 < ho) d[0] = v0;
+        if (f + 1 < ho) d[1] = v1;
+        if (f + 2 < ho) d[2] = v2;
+        if (f + 3 < ho) d[3] = v3;
+      }
+      tile += 8;
+    } while (tile < nt);
+    if (head && wave == 7) idle();
+    __syncthreads();
+    s_bias += F;
+    w = wn; K = Kn; F = Fn;
+  }
+}
+
 // 512 threads.
 // WS: a WsShape whose widths the model has (weights held in registers for the whole launch): waves 0-3 run the policy net
 // and waves 4-7 the value net at the same time (the two nets have the same hidden widths, so their layers finish together
 // and share the barriers); every other phase uses all 8 waves.
 // void: the policy net alone, on all 8 waves, its weights streamed from L2 at every step with the layer walk of the agent
-// kernel (agent_kernel.h): the next item's blocks, across layers and steps, are on their way before the present one is
-// left.  A compute unit draws weights at about 50 B/ns, which bounds the step of a wide net, so the value net -- which the
-// simulator does not wait for -- is left to one launch over all slots afterwards (launch_values).
-// R16: the 16-env form of the weight-stationary nets (rows_per_wg == 16).
+// kernel (agent_kernel.h) or, 16 envs, the one above: the next item's blocks, across layers and steps, are on their way before
+// the present one is left.  A compute unit draws weights at about 50 B/ns, which bounds the step of a wide net, so the value net
+// -- which the simulator does not wait for -- is left to one launch over all slots afterwards (launch_values).
+// R16: the 16-env form of the nets (rows_per_wg == 16).
+// A step has three phases between barriers: the layers; sampling and stores; simulator, the next step's draws, sums.  The
+// simulator writes the next state where the next step reads it (two buffers), so nothing is copied in between.
+// Measured, us (the form with the simulator on the vector unit, 32-row products for 16 envs and a copy of the state): 4096 envs
+// of 108:400:200:100:21, 32 steps 350 (470); 4096 envs of 60:256:128:64:8, 16 steps 107 (120); 1000 envs of 45:128:128:12, 24
+// steps 126 (179).
 template <int RT, class WS = void, bool R16 = false>
 __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
-  constexpr int R = RT * 32;
+  constexpr int R = R16 ? 16 : RT * 32;              // rows of the products
   constexpr int NT = 512;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  const int O = a.obs_dim, A = a.act_dim, OA = O + A, OS = (OA + 3) & ~3, o4 = a.o4, nbo = o4 >> 2, nba = (A + 3) >> 2;
-  const int stride_x0 = a.obs_pad + 8, stride_h = a.max_h + 8;
-  // hidden activations (bf16, ping-pong, one pair per net) share their space with the next-state tile
-  // (after the nets: next-state tile, then this step's random draws, then the staged simulator matrix)
-  const int npr = nba + nbo + 1;                     // random blocks per env and step: action, env noise, done
   constexpr bool kStationary = !std::is_void<WS>::value;
-  constexpr int kNets = kStationary ? 2 : 1;
-  const size_t hid_bytes = 2 * kNets * (size_t)R * stride_h * 2, next_bytes = ((size_t)R * o4 * 4 + 15) & ~(size_t)15;
-  const size_t noise_bytes = (size_t)R * npr * 16;
-  const size_t region = ((hid_bytes > next_bytes + noise_bytes ? hid_bytes : next_bytes + noise_bytes) + 15) & ~(size_t)15;
-  float* s_in = reinterpret_cast<float*>(smem_raw);                                  // [R][OS] state | action
-  uint16_t* s_x0 = reinterpret_cast<uint16_t*>(s_in + R * OS);          // [R][obs_pad + 8]
-  unsigned char* s_reg = reinterpret_cast<unsigned char*>(s_x0 + R * stride_x0);
-  uint16_t* s_hid = reinterpret_cast<uint16_t*>(s_reg);                              // [2 nets][2][R][stride_h]
-  float* s_next = reinterpret_cast<float*>(s_reg);                                   // [R][o4]
-  float* s_mu = reinterpret_cast<float*>(s_reg + region);                            // [R][A]
-  float* s_val = s_mu + R * A;                                                       // [R]
-  float* s_lp = s_val + R;                                                           // [R][nba]
-  float* s_part = s_lp + R * nba;                                                    // [R][nbo]
-  int* s_done = reinterpret_cast<int*>(s_part + R * nbo);                            // [R]
-  float* s_bias = reinterpret_cast<float*>(s_done + ((R + 3) & ~3));                 // policy biases, value biases
-  // this step's random draws, one float4 per (env, block): nba action-noise blocks, nbo env-noise blocks, then
-  // the done draw (raw word in .x); in the hidden-activation space, which is idle once the heads are done
-  float4* s_noise_inplace = reinterpret_cast<float4*>(s_reg + next_bytes);
-  float* s_mt = s_bias + (kStationary ? (a.net[0].bias_total + a.net[1].bias_total + 3) & ~3 : 0);     // [O + A][o4] when mt_lds == 2
-  // weight-stationary form: operand blocks of the LDS-resident layers, policy net then value net
-  uint16_t* s_wl = reinterpret_cast<uint16_t*>(s_mt + (a.mt_lds == 2 ? OA * o4 : 0));
-  float4* s_ahead = reinterpret_cast<float4*>(smem_raw + a.ahead_off);                // [2][Rv][npr] when noise_ahead
-  const int tid = threadIdx.x;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  const int O = a.obs_dim, A = a.act_dim, OA = O + A, OS = (OA + 3) & ~3, nbo = a.o4 >> 2, nba = (A + 3) >> 2;
+  const int npr = nba + nbo + 1;                     // random blocks per env and step: action, env noise, done
+  const int stride_x0 = a.obs_pad + 8, stride_h = a.max_h + 8;
+  const int Rv = a.rows_per_wg;                      // envs owned by this workgroup: R
+  float* s_in2 = reinterpret_cast<float*>(smem_raw);                                 // [2][Rv][OS] state | action
+  uint16_t* s_x0 = reinterpret_cast<uint16_t*>(smem_raw + a.x0_off);                 // [R][obs_pad + 8]
+  uint16_t* s_hid = reinterpret_cast<uint16_t*>(smem_raw + a.hid_off);               // [nets][2][R][stride_h]
+  float* s_mu = reinterpret_cast<float*>(smem_raw + a.mu_off);                       // [R][A]
+  float* s_val = reinterpret_cast<float*>(smem_raw + a.val_off);                     // [R]
+  float* s_lp = reinterpret_cast<float*>(smem_raw + a.lp_off);                       // [Rv][nba]
+  float* s_part = reinterpret_cast<float*>(smem_raw + a.part_off);                   // [Rv][nbo]
+  int* s_done = reinterpret_cast<int*>(smem_raw + a.done_off);                       // [Rv]
+  float* s_ls = reinterpret_cast<float*>(smem_raw + a.ls_off);                       // [A] log_std, [A] exp(log_std)
+  float* s_bias = reinterpret_cast<float*>(smem_raw + a.bias_off);                   // policy biases, (stationary) value biases
+  float* s_m = reinterpret_cast<float*>(smem_raw + a.m_off);                         // [o4][ms] when mr_lds
+  uint16_t* s_wl = reinterpret_cast<uint16_t*>(smem_raw + a.w_off);                  // operand blocks of LDS-resident layers
+  float4* s_draws = reinterpret_cast<float4*>(smem_raw + a.draw_off);                // [ahead + 1][Rv][npr]
+  const int tid = threadIdx.x, lane = tid & 63;
   // wave-uniform values, so that the per-net kernel arguments are fetched by scalar loads
   const int half = __builtin_amdgcn_readfirstlane(tid >> 8), wave4 = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);
-  // Rv <= R envs are owned by this workgroup (a half-filled tile doubles the workgroups of a small batch);
-  // rows Rv..R-1 of the tile go through the matrix products but are never read or stored
-  const int Rv = a.rows_per_wg;
-  // first thread of the first wave without a simulator item
-  const int ahead_tid0 = sim_threads(Rv, nbo);
-  // the observation stores go to the waves without action items when those are at least half of the workgroup
-  // (in the simulator phase the idle waves have no time to spare: measured, the next step's draws fill it)
-  const int act_waves_end = (Rv * nba * 4 + 63) & ~63;
-  const int obs_tid0 = act_waves_end <= NT / 2 ? act_waves_end : 0;
-  for (int idx = tid; idx < (R - Rv) * stride_x0; idx += NT) s_x0[Rv * stride_x0 + idx] = 0;
+  const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int idx = tid; idx < R * (stride_x0 >> 3); idx += NT) reinterpret_cast<uint4*>(s_x0)[idx] = make_uint4(0u, 0u, 0u, 0u);
+  for (int idx = tid; idx < Rv * OS; idx += NT) s_in2[Rv * OS + idx] = 0.f;
+  for (int j = tid; j < A; j += NT) {
+    const float ls = a.log_std[j];
+    s_ls[j] = ls;
+    s_ls[A + j] = expf(ls);
+  }
   if constexpr (kStationary) {
     stage_biases(a.net[0], s_bias, tid, NT);
     stage_biases(a.net[1], s_bias + a.net[0].bias_total, tid, NT);
   }
-  if (a.mt_lds == 2)
-    for (int idx = tid; idx < OA * nbo; idx += NT)
-      reinterpret_cast<float4*>(s_mt)[idx] = reinterpret_cast<const float4*>(a.m_t)[idx];
-  float4* s_stage = reinterpret_cast<float4*>(s_reg + next_bytes + noise_bytes);
-  // the simulator matrix as an LDS pointer (resident copy or per-step staging) or as a global pointer: kept apart,
-  // because one pointer that may be either makes every access a flat load (measured: the 68-step matrix-vector
-  // loop of a 60-dimensional env took 8600 cycles through flat loads)
-  const float4* mt_lds_ptr = a.mt_lds == 2 ? reinterpret_cast<const float4*>(s_mt) : s_stage;
-  const float4* mt_glb_ptr = reinterpret_cast<const float4*>(a.m_t);
+  const int m4 = a.o4 * (a.ms >> 2);
+  if (a.mr_lds == 2)
+    for (int idx = tid; idx < m4; idx += NT) reinterpret_cast<float4*>(s_m)[idx] = reinterpret_cast<const float4*>(a.m_r)[idx];
   const FusedNet& N = a.net[half];
   uint16_t* s_a = s_hid + (size_t)half * 2 * R * stride_h;
   uint16_t* s_b = s_a + R * stride_h;
@@ -388,8 +464,8 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
   bf16x8 wreg[WsFrags<WS>::value];
   const uint16_t* s_w = s_wl;
   if constexpr (kStationary) {
-    if constexpr (R16) ws_load16<WS, 0>(wreg, N, wave4, tid & 63);
-    else ws_load<WS, 0>(wreg, N, wave4, tid & 63);
+    if constexpr (R16) ws_load16<WS, 0>(wreg, N, wave4, lane);
+    else ws_load<WS, 0>(wreg, N, wave4, lane);
     ws_stage<WS, 0>(s_wl, a.net[0], tid, NT);
     ws_stage<WS, 0>(s_wl + WS::lds_elems(), a.net[1], tid, NT);
     s_w = s_wl + (half ? WS::lds_elems() : 0);
@@ -398,182 +474,120 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
   // streaming form: the first weight blocks of this wave's first item are always on their way
   constexpr int kAhead = RT == 1 ? 8 : 4;
   gmi_agent::Ring<gmi_agent::Bf16, kAhead> wq;
-  const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if constexpr (!kStationary) gmi_agent::request<gmi_agent::Bf16, RT, kAhead, RT, 8>(wq, a.policy[0], wave8, tid & 63);
+  Ring16 wq16;
+  if constexpr (!kStationary) {
+    if constexpr (R16) {
+      for (int f = tid; f < a.net[0].bias_total; f += NT) {      // the policy's biases, layer after layer
+        int l = 0;
+        while (l + 1 < a.net[0].n_layers && f >= a.net[0].bias_off[l + 1]) ++l;
+        s_bias[f] = a.net[0].bias[l][f - a.net[0].bias_off[l]];
+      }
+      request16(wq16, walk16(a.policy[0].w, a.policy[0].K, a.policy[0].F, wave8),
+                (((lane >> 5) * 64) + (lane & 15) + 32 * ((lane >> 4) & 1)) * 16);
+    }
+    else gmi_agent::request<gmi_agent::Bf16, RT, kAhead, RT, 8>(wq, a.policy[0], wave8, lane);
+  }
 
+  const SimLane sl = sim_lane(a, wave8, OS, lane);
   // The grid never exceeds what the instance's compute units hold at once: a workgroup takes the tiles
   // blockIdx.x, blockIdx.x + gridDim.x, ... one after the other, each through all T steps.  (Workgroups
   // that wait for a free compute unit would keep the dispatcher from placing other instances' kernels.)
   for (int tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
-  const int r0 = tile * Rv;
-  for (int idx = tid; idx < Rv * O; idx += NT) {
-    const int r = idx / O, k = idx - r * O;
-    s_in[r * OS + k] = (r0 + r < a.n) ? a.obs_state[(int64_t)(r0 + r) * O + k] : 0.f;
-  }
-  // thread NT - 64 + r (r < Rv; the last wave, which has no action items and gets an observation-store item last of
-  // all: on the fifth wave the done flags came after an observation store and that wave ended the sampling phase
-  // 1000 cycles after the others) carries env r's episode counter and makes its done flag
-  const int dtid = tid - (NT - 64);
-  uint32_t ep = 0;
-  if (dtid >= 0 && dtid < Rv && r0 + dtid < a.n) ep = a.episode_step[r0 + dtid];
-  if (a.noise_ahead) draw_items(a, s_ahead, a.step0, Rv, r0, npr, nba, nbo, tid, NT);
-  __syncthreads();
-  // the nets' bf16 copy of the state, zero padded; every later step refreshes it together with the state itself
-  for (int idx = tid; idx < Rv * a.obs_pad; idx += NT) {
-    const int r = idx / a.obs_pad, k = idx - r * a.obs_pad;
-    const float v = k < O ? s_in[r * OS + k] : 0.f;
-    s_x0[r * stride_x0 + k] = (uint16_t)(pack_bf16(v, 0.f) & 0xFFFFu);
-  }
-  __syncthreads();
+    const int r0 = tile * Rv;
+    load_states(a, r0, s_in2, OS, tid);
+    // thread NT - 64 + e (e < Rv; the last wave, which has the fewest other items) carries env e's episode counter, makes its
+    // done flag and writes its sums
+    const int et = tid - (NT - 64);
+    const bool env_thread = et >= 0 && et < Rv, env_ok = env_thread && r0 + et < a.n;
+    uint32_t ep = 0;
+    if (env_ok) ep = a.episode_step[r0 + et];
+    if (a.ahead) draw_all(a, s_draws, a.step0, r0, npr, nba, tid);
+    __syncthreads();
+    // the nets' bf16 copy of the state; every later step's comes from the simulator
+    {
+      const int r = tid >> a.row_shift, c = tid & ((1 << a.row_shift) - 1), nc = 1 << a.row_shift;
+      for (int k = c; k < O; k += nc) s_x0[r * stride_x0 + k] = (uint16_t)(pack_bf16(s_in2[r * OS + k], 0.f) & 0xFFFFu);
+    }
+    __syncthreads();
 
-  for (int t = 0; t <= a.T; ++t) {
-    // both nets, layer by layer; after the last step only the value net (bootstrap value)
-    const bool run = half == 1 || t < a.T;
-    if constexpr (kStationary) {
-      if constexpr (R16)
-        ws_net16<WS, 0>(wreg, s_w, N, s_nb, s_x0, stride_x0, s_a, s_b, stride_h, s_head, head_stride, run, wave4, tid & 63);
-      else
-        ws_net<WS, 0, RT>(wreg, s_w, N, s_nb, s_x0, stride_x0, s_a, s_b, stride_h, s_head, head_stride, run, wave4, tid & 63);
-    } else {
-      if (t == a.T) break;
-      gmi_agent::net_layers<gmi_agent::Bf16, RT, kAhead, RT, 8, true>(
-          a.policy, a.net[0].n_layers, wq, reinterpret_cast<const unsigned char*>(s_x0), reinterpret_cast<unsigned char*>(s_hid),
-          reinterpret_cast<unsigned char*>(s_hid + R * stride_h), nullptr, s_mu, A, wave8, tid & 63);
-    }
-    if (t == a.T) {
-      if (tid < Rv && r0 + tid < a.n) a.last_value[r0 + tid] = s_val[tid];
-      break;
-    }
-
-    // All random draws of this step, one block per thread and the same instructions for every kind of block
-    // (left where they are used, they ran on the few threads of the sampling phase and inside the simulator's
-    // matrix product).  With noise_ahead they were made during the previous step's simulator phase.
-    float4* s_noise = a.noise_ahead ? s_ahead + (size_t)(t & 1) * Rv * npr : s_noise_inplace;
-    if (!a.noise_ahead) {
-      draw_items(a, s_noise, a.step0 + (uint32_t)t, Rv, r0, npr, nba, nbo, tid, NT);
-      __syncthreads();
-    }
-    const uint32_t step = a.step0 + (uint32_t)t;
-    const int64_t slot0 = (int64_t)t * a.ld_envs + r0;
-    // action = mu + exp(log_std) * eps, log-prob partials per block of 4 action elements: one thread per element;
-    // the four terms of a block are added in index order through lane exchanges (((t0 + t1) + t2) + t3, the order
-    // of a single accumulator), so that one thread per block no longer walks its four elements one after the other
-    for (int item = tid; item < Rv * nba * 4; item += NT) {
-      const int blk = item >> 2, i = item & 3;
-      const int r = blk / nba, b = blk - r * nba;
-      const int e = r0 + r, j = 4 * b + i;
-      float term = 0.f;
-      if (j < A) {
-        float act = 0.f;
-        if (e < a.n) {
-          const float z = reinterpret_cast<const float*>(s_noise + r * npr + b)[i];
-          const float ls = a.log_std[j];
-          act = fmaf(expf(ls), z, s_mu[r * A + j]);
-          a.b_act[(slot0 + r) * A + j] = act;
-          term = -0.5f * z * z - ls - 0.918938533204672742f;
-        }
-        s_in[r * OS + O + j] = act;
-      }
-      float lp = term;
-      lp += __shfl_down(term, 1, 64);
-      lp += __shfl_down(term, 2, 64);
-      lp += __shfl_down(term, 3, 64);
-      if (i == 0) s_lp[blk] = lp;
-    }
-    // this step's observations to the buffer, by the waves without action items
-    if (tid >= obs_tid0) {
-      if (a.obs_vec) {          // rows of whole 16-byte pieces on both sides: a quarter of the stores
-        const int o4n = O >> 2;
-        for (int idx = tid - obs_tid0; idx < Rv * o4n; idx += NT - obs_tid0) {
-          const int r = idx / o4n, c = idx - r * o4n;
-          const float4 v = *reinterpret_cast<const float4*>(s_in + r * OS + 4 * c);
-          if (r0 + r < a.n) *reinterpret_cast<float4*>(a.b_obs + (slot0 + r) * O + 4 * c) = v;
-        }
+    int64_t slot0 = r0;
+    auto reward = [&]() {      // of the step before
+      if (env_ok) a.b_rew[slot0 - a.ld_envs + et] = -a.reward_scale * block_sum(s_part + et * nbo, nbo);
+    };
+    for (int t = 0; t <= a.T; ++t, slot0 += a.ld_envs) {
+      float* s_in = s_in2 + (t & 1) * Rv * OS;
+      float4* s_noise = s_draws + (a.ahead ? (t & 1) * Rv * npr : 0);
+      const uint32_t step = a.step0 + (uint32_t)t;
+      // beside the heads, whose tiles leave the last wave idle: the reward of the step before and, where the draws are there,
+      // this step's done flags
+      auto beside = [&]() {
+        if (!env_thread) return;
+        if (t > 0) reward();
+        if (a.ahead && t < a.T) finish_env(a, r0, slot0, et, s_noise, npr, ep, s_done);
+      };
+      // both nets, layer by layer; after the last step only the value net (bootstrap value)
+      if constexpr (kStationary) {
+        const bool run = half == 1 || t < a.T;
+        if constexpr (R16)
+          ws_net16<WS, 0>(wreg, s_w, N, s_nb, s_x0, stride_x0, s_a, s_b, stride_h, s_head, head_stride, run, wave4, lane, beside);
+        else
+          ws_net<WS, 0, RT>(wreg, s_w, N, s_nb, s_x0, stride_x0, s_a, s_b, stride_h, s_head, head_stride, run, wave4, lane, beside);
       } else {
-        for (int idx = tid - obs_tid0; idx < Rv * O; idx += NT - obs_tid0) {
-          const int r = idx / O, k = idx - r * O;
-          if (r0 + r < a.n) a.b_obs[(slot0 + r) * O + k] = s_in[r * OS + k];
+        if (t == a.T) {
+          beside();
+          break;
         }
-      }
-    }
-    if (dtid >= 0 && dtid < Rv) {
-      const int e = r0 + dtid;
-      int d = 0;
-      if (e < a.n) {
-        if (a.done_period > 0) {
-          d = ((ep + 1u) % a.done_period) == 0u;
+        if constexpr (R16) {
+          net_layers16(a.policy, a.net[0].n_layers, wq16, reinterpret_cast<const unsigned char*>(s_x0), reinterpret_cast<unsigned char*>(s_hid),
+                       reinterpret_cast<unsigned char*>(s_hid + R * stride_h), s_bias, s_mu, A, wave8, lane, beside);
         } else {
-          d = __float_as_uint(s_noise[dtid * npr + nba + nbo].x) < a.done_threshold;
+          beside();
+          gmi_agent::net_layers<gmi_agent::Bf16, RT, kAhead, RT, 8, true>(
+              a.policy, a.net[0].n_layers, wq, reinterpret_cast<const unsigned char*>(s_x0), reinterpret_cast<unsigned char*>(s_hid),
+              reinterpret_cast<unsigned char*>(s_hid + R * stride_h), nullptr, s_mu, A, wave8, lane);
         }
-        ep = d ? 0u : ep + 1u;
-        a.b_done[slot0 + dtid] = (uint8_t)d;
-        if constexpr (kStationary) a.b_val[slot0 + dtid] = s_val[dtid];
       }
-      s_done[dtid] = d;
-    }
-    __syncthreads();
-    if (tid < Rv && r0 + tid < a.n) {
-      float lp = 0.f;
-      for (int b = 0; b < nba; ++b) lp += s_lp[tid * nba + b];
-      a.b_logp[slot0 + tid] = lp;
-    }
-    // simulator: next = A s + B act + noise_std * eps (or a fresh N(0,1) state after a done); as many envs
-    // per item as still leaves an item for every thread
-    if (a.mt_lds == 1) {
-      for (int idx = tid; idx < OA * nbo; idx += NT) s_stage[idx] = reinterpret_cast<const float4*>(a.m_t)[idx];
+      if (t == a.T) {
+        if constexpr (kStationary)
+          if (env_ok) a.last_value[r0 + et] = s_val[et];
+        break;
+      }
+      if (!a.ahead) {
+        draw_all(a, s_noise, step, r0, npr, nba, tid);
+        __syncthreads();
+        if (env_thread) finish_env(a, r0, slot0, et, s_noise, npr, ep, s_done);
+      }
+      sample_and_store(a, r0, slot0, s_in, OS, s_mu, A, s_noise, npr, nba, s_ls, s_lp, tid);
+      __syncthreads();
+      if (a.mr_lds == 1) {
+        for (int idx = tid; idx < m4; idx += NT) reinterpret_cast<float4*>(s_m)[idx] = reinterpret_cast<const float4*>(a.m_r)[idx];
+        __syncthreads();
+      }
+      float* s_nxt = s_in2 + ((t + 1) & 1) * Rv * OS;
+      auto put = [&](int r, int o, const float (&v)[4]) {      // (what lies beyond the state belongs to the next step's actions)
+        *reinterpret_cast<float4*>(s_nxt + r * OS + o) = make_float4(v[0], v[1], v[2], v[3]);
+        const float w1 = o + 1 < O ? v[1] : 0.f, w2 = o + 2 < O ? v[2] : 0.f, w3 = o + 3 < O ? v[3] : 0.f;
+        *reinterpret_cast<uint2*>(s_x0 + r * stride_x0 + o) = make_uint2(pack_bf16(v[0], w1), pack_bf16(w2, w3));
+      };
+      // an LDS pointer or a global pointer, kept apart: one that may be either makes every access a flat load
+      if (a.mr_lds != 0) sim_items(a, r0, step, sl, s_in, OS, s_m, s_part, s_done, s_noise, npr, nba, wave8, lane, put);
+      else sim_items(a, r0, step, sl, s_in, OS, a.m_r, s_part, s_done, s_noise, npr, nba, wave8, lane, put);
+      if (env_ok) {
+        a.b_logp[slot0 + et] = block_sum(s_lp + et * nba, nba);
+        if constexpr (kStationary) a.b_val[slot0 + et] = s_val[et];
+      }
+      if (a.ahead && t + 1 < a.T) draw_rest(a, s_draws + ((t + 1) & 1) * Rv * npr, step + 1u, r0, npr, nba, tid);
       __syncthreads();
     }
-    // the next step's draws, by the waves that have no simulator item
-    if (a.noise_ahead && t + 1 < a.T && tid >= ahead_tid0)
-      draw_items(a, s_ahead + (size_t)((t + 1) & 1) * Rv * npr, step + 1u, Rv, r0, npr, nba, nbo, tid - ahead_tid0, NT - ahead_tid0);
-    if (a.mt_lds != 0) sim_step<true>(Rv, nbo, a, r0, step, s_in, OS, mt_lds_ptr, s_part, s_next, s_done, s_noise, npr, nba);
-    else sim_step<true>(Rv, nbo, a, r0, step, s_in, OS, mt_glb_ptr, s_part, s_next, s_done, s_noise, npr, nba);
-    __syncthreads();
-    // the reward on the last wave (the state update below starts with the first threads)
-    const int rt = tid - (NT - 64);
-    if (rt >= 0 && rt < Rv && r0 + rt < a.n) {
-      // same order of additions as one by one, eight LDS reads in flight
-      const float* q = s_part + rt * nbo;
-      float sum = 0.f;
-      int j = 0;
-      for (; j + 8 <= nbo; j += 8) {
-        float t8[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) t8[u] = q[j + u];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) sum += t8[u];
-      }
-      for (; j < nbo; ++j) sum += q[j];
-      a.b_rew[slot0 + rt] = -a.reward_scale * sum;
+    // the final state
+    {
+      const float* s_in = s_in2 + (a.T & 1) * Rv * OS;
+      const int r = tid >> a.row_shift, c = tid & ((1 << a.row_shift) - 1), nc = 1 << a.row_shift;
+      if (r0 + r < a.n)
+        for (int k = c; k < O; k += nc) a.obs_state[(int64_t)(r0 + r) * O + k] = s_in[r * OS + k];
     }
-    // the new state, in fp32 for the simulator and the stores and in bf16 for the next step's nets (one pass and
-    // one barrier instead of two)
-    if (a.obs_vec) {            // four elements per thread (O, the row stride and the padded width are multiples of 4)
-      const int p4 = a.obs_pad >> 2;
-      for (int idx = tid; idx < Rv * p4; idx += NT) {
-        const int r = idx / p4, k = 4 * (idx - r * p4);
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (k < O && r0 + r < a.n) v = *reinterpret_cast<const float4*>(s_next + r * o4 + k);
-        if (k < O) *reinterpret_cast<float4*>(s_in + r * OS + k) = v;
-        *reinterpret_cast<uint2*>(s_x0 + r * stride_x0 + k) = make_uint2(pack_bf16(v.x, v.y), pack_bf16(v.z, v.w));
-      }
-    } else {
-      for (int idx = tid; idx < Rv * a.obs_pad; idx += NT) {
-        const int r = idx / a.obs_pad, k = idx - r * a.obs_pad;
-        const float v = (k < O && r0 + r < a.n) ? s_next[r * o4 + k] : 0.f;
-        if (k < O) s_in[r * OS + k] = v;
-        s_x0[r * stride_x0 + k] = (uint16_t)(pack_bf16(v, 0.f) & 0xFFFFu);
-      }
-    }
-    __syncthreads();
-  }
-  // the loop ends right after the bootstrap value; s_in still holds the final state
-  for (int idx = tid; idx < Rv * O; idx += NT) {
-    const int r = idx / O, k = idx - r * O;
-    if (r0 + r < a.n) a.obs_state[(int64_t)(r0 + r) * O + k] = s_in[r * OS + k];
-  }
-  if (dtid >= 0 && dtid < Rv && r0 + dtid < a.n) a.episode_step[r0 + dtid] = ep;
-  __syncthreads();                                   // the next tile overwrites the state rows
+    if (env_ok) a.episode_step[r0 + et] = ep;
+    __syncthreads();                                   // the next tile overwrites the state rows
   }
 }
 
@@ -600,23 +614,6 @@ void fill_net(const gmi_model* m, int net, FusedNet* N) {
   N->out_store = L.net[net][L.n_layers - 1].out;
 }
 
-// Bytes of one step's random draws for a tile of R envs (one float4 per block).
-size_t rollout_noise_bytes(const gmi_model* m, int R) {
-  const int O = m->L.obs_dim, A = m->L.act_dim, o4 = (O + 3) & ~3;
-  return (size_t)R * ((A + 3) / 4 + o4 / 4 + 1) * 16;
-}
-
-// Bytes of the hidden-activation space left over beside the next-state tile and the random draws while the
-// simulator runs.
-size_t rollout_stage_room(const gmi_model* m, int R, int nets) {
-  const ModelLayout& L = m->L;
-  int max_h = 32;
-  for (int l = 0; l < L.n_hidden; ++l) max_h = L.net[0][l].out_pad > max_h ? L.net[0][l].out_pad : max_h;
-  const int o4 = (L.obs_dim + 3) & ~3;
-  const size_t hid = 2 * nets * (size_t)R * (max_h + 8) * 2, used = (((size_t)R * o4 * 4 + 15) & ~(size_t)15) + rollout_noise_bytes(m, R);
-  return hid > used ? hid - used : 0;
-}
-
 // LDS of the operand blocks that the weight-stationary form keeps there (both nets); 0 for other shapes.
 size_t rollout_ws_lds_bytes(const ModelLayout& L) {
   if (ws_matches<WsAnt>(L)) return 2 * (size_t)WsAnt::lds_elems() * 2;
@@ -624,17 +621,52 @@ size_t rollout_ws_lds_bytes(const ModelLayout& L) {
   return 0;
 }
 
-size_t rollout_lds_bytes(const gmi_model* m, int R, bool mt_lds, int nets) {
+int max_hidden_pad(const ModelLayout& L) {
+  int w = 32;
+  for (int l = 0; l < L.n_hidden; ++l) w = std::max(w, L.net[0][l].out_pad);
+  return w;
+}
+
+// What the first form of the streaming kernel, which held both nets' activations, took for a tile of R envs: decides the tile
+// height and which models are refused.
+size_t admission_bytes(const gmi_model* m, int R) {
   const ModelLayout& L = m->L;
-  int max_h = 32;
-  for (int l = 0; l < L.n_hidden; ++l) max_h = L.net[0][l].out_pad > max_h ? L.net[0][l].out_pad : max_h;
-  const int O = L.obs_dim, A = L.act_dim, o4 = (O + 3) & ~3;
-  const size_t hid = 2 * nets * (size_t)R * (max_h + 8) * 2, used = (((size_t)R * o4 * 4 + 15) & ~(size_t)15) + rollout_noise_bytes(m, R);
+  const int max_h = max_hidden_pad(L), O = L.obs_dim, A = L.act_dim, o4 = (O + 3) & ~3;
+  const size_t hid = 4 * (size_t)R * (max_h + 8) * 2;
+  const size_t used = (((size_t)R * o4 * 4 + 15) & ~(size_t)15) + (size_t)R * ((A + 3) / 4 + o4 / 4 + 1) * 16;
   const size_t region = ((hid > used ? hid : used) + 15) & ~(size_t)15;
   return (size_t)R * ((O + A + 3) & ~3) * 4 + (size_t)R * (gmi::pad32(O) + 8) * 2 + region +
-         (size_t)(R * (A + 1 + (A + 3) / 4 + o4 / 4) + ((R + 3) & ~3)) * 4 +
-         (nets == 2 ? ((bias_floats(m, 0) + bias_floats(m, 1) + 3) & ~(size_t)3) * 4 : 0) +
-         (mt_lds ? (size_t)(O + A) * o4 * 4 : 0) + rollout_ws_lds_bytes(L);
+         (size_t)(R * (A + 1 + (A + 3) / 4 + o4 / 4) + ((R + 3) & ~3)) * 4 + ((bias_floats(m, 0) + bias_floats(m, 1) + 3) & ~(size_t)3) * 4 +
+         rollout_ws_lds_bytes(L);
+}
+
+// Lays out the LDS of a tile of Rv envs and returns its bytes.
+size_t rollout_lds(const gmi_model* m, int Rv, int nets, int mr_lds, int ahead, RolloutArgs* a) {
+  const ModelLayout& L = m->L;
+  const int O = L.obs_dim, A = L.act_dim, o4 = (O + 3) & ~3, nba = (A + 3) / 4, nbo = o4 / 4;
+  const size_t mr_bytes = (size_t)o4 * gmi::env_row_stride(O, A) * 4, draws = (size_t)Rv * (nba + nbo + 1) * 16;
+  const size_t hid = 2 * nets * (size_t)Rv * (max_hidden_pad(L) + 8) * 2;
+  size_t off = 2 * (size_t)Rv * ((O + A + 3) & ~3) * 4;
+  auto take = [&](int* field, size_t bytes) { *field = (int)off; off = (off + bytes + 15) & ~(size_t)15; };
+  take(&a->x0_off, (size_t)Rv * (gmi::pad32(O) + 8) * 2);
+  // the hidden activations' space is idle outside the nets: a step's draws, where they are not made ahead, and the simulator's
+  // matrix, where it is staged at every step, lie there too
+  take(&a->hid_off, std::max(hid, (ahead ? 0 : draws) + (mr_lds == 1 ? mr_bytes : 0)));
+  take(&a->mu_off, (size_t)Rv * A * 4);
+  take(&a->val_off, nets == 2 ? (size_t)Rv * 4 : 0);
+  take(&a->lp_off, (size_t)Rv * nba * 4);
+  take(&a->part_off, (size_t)Rv * nbo * 4);
+  take(&a->done_off, (size_t)Rv * 4);
+  take(&a->ls_off, 2 * (size_t)A * 4);
+  take(&a->bias_off, (bias_floats(m, 0) + (nets == 2 ? bias_floats(m, 1) : 0)) * 4);
+  take(&a->w_off, rollout_ws_lds_bytes(L));
+  take(&a->m_off, mr_lds == 2 ? mr_bytes : 0);
+  if (mr_lds == 1) a->m_off = a->hid_off + (int)(ahead ? 0 : draws);
+  take(&a->draw_off, ahead ? 2 * draws : 0);
+  if (!ahead) a->draw_off = a->hid_off;
+  a->mr_lds = mr_lds;
+  a->ahead = ahead;
+  return off;
 }
 
 }  // namespace
@@ -671,13 +703,10 @@ extern "C" int rollout_collect(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_buffer
   // refused stays refused, and heights change with envs for all models at one line.  (With the streaming form's own bytes
   // 60:256:256:8 would take 64 envs: 364 us instead of 417 for 16384 envs and 16 steps, but 637 instead of 588 for 20000.)
   int R = 64;
-  if (rollout_lds_bytes(m, R, false, 2) > kLdsMax || (n + 63) / 64 < g->cu_count) R = 32;
-  if (rollout_lds_bytes(m, R, false, 2) > kLdsMax)
+  if (admission_bytes(m, R) > kLdsMax || (n + 63) / 64 < g->cu_count) R = 32;
+  if (admission_bytes(m, R) > kLdsMax)
     GMI_FAIL(GMI_ERR_UNSUPPORTED, "rollout_collect: a 32-env tile of this model needs %zu bytes of LDS (limit %zu); "
-             "use agent_act / env_step / collect_experience", rollout_lds_bytes(m, R, false, 2), kLdsMax);
-  const size_t mt_bytes = (size_t)(L.obs_dim + L.act_dim) * ((L.obs_dim + 3) & ~3) * 4;
-  const bool mt_lds = rollout_lds_bytes(m, R, true, nets) <= kLdsMax;
-  const int mt_mode = mt_lds ? 2 : (rollout_stage_room(m, R, nets) >= mt_bytes ? 1 : 0);
+             "use agent_act / env_step / collect_experience", admission_bytes(m, R), kLdsMax);
   RolloutArgs a;
   fill_net(m, 0, &a.net[0]);
   fill_net(m, 1, &a.net[1]);
@@ -686,35 +715,37 @@ extern "C" int rollout_collect(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_buffer
   a.log_std = reinterpret_cast<const float*>(m->shadow + L.sh_logstd);
   fill_rollout_env(m, env, b, obs, seed, step0, env_offset, last_value, &a);
   a.obs_pad = gmi::pad32(L.obs_dim);
-  a.max_h = 32;
-  for (int l = 0; l < L.n_hidden; ++l) a.max_h = L.net[0][l].out_pad > a.max_h ? L.net[0][l].out_pad : a.max_h;
-  a.mt_lds = mt_mode;
-  a.obs_vec = (L.obs_dim % 4 == 0 && ((uintptr_t)bd.obs & 15) == 0) ? 1 : 0;
-  size_t lds = rollout_lds_bytes(m, R, mt_lds, nets);
-  // fewer 32-env tiles than compute units: 16 envs per workgroup use twice as many of them
-  const int rows_per_wg = (R == 32 && (n + 31) / 32 < g->cu_count && n > 16) ? 16 : R;
-  a.rows_per_wg = rows_per_wg;
-  // Draws one step ahead: when the simulator's items leave enough whole waves idle to make a step's draws in three
-  // rounds at most, and two buffers of them still fit
+  a.max_h = max_hidden_pad(L);
+  // fewer 32-env tiles than compute units: 16 envs per workgroup use twice as many of them.  So do the models whose two rows of
+  // state per env leave no room for more.
+  int rows_per_wg = (R == 32 && (n + 31) / 32 < g->cu_count) ? 16 : R;
+  while (rows_per_wg > 16 && rollout_lds(m, rows_per_wg, nets, 0, 0, &a) > kLdsMax) rows_per_wg >>= 1;
+  // what else the LDS holds: the simulator's matrix for the whole launch, draws one step ahead, else the matrix step by step
+  size_t lds = 0;
   {
-    const int nbo = a.o4 / 4, nba = (L.act_dim + 3) / 4, npr = nba + nbo + 1;
-    const int idle = 512 - sim_threads(rows_per_wg, nbo);
-    const size_t off = (lds + 15) & ~(size_t)15, need = off + 2 * (size_t)rows_per_wg * npr * 16;
-    a.noise_ahead = (idle > 0 && idle * 3 >= rows_per_wg * npr && need <= kLdsMax) ? 1 : 0;
-    a.ahead_off = (int)off;
-    if (a.noise_ahead) lds = need;
+    static const int order[][2] = {{2, 1}, {1, 1}, {2, 0}, {0, 1}, {1, 0}, {0, 0}};
+    const size_t hid = 2 * nets * (size_t)rows_per_wg * (a.max_h + 8) * 2;
+    for (const auto& o : order) {
+      lds = rollout_lds(m, rows_per_wg, nets, o[0], o[1], &a);
+      // staged at every step only into space that is there anyway
+      if (lds <= kLdsMax && (o[0] != 1 || (size_t)a.m_off + (size_t)a.o4 * a.ms * 4 <= (size_t)a.hid_off + hid)) break;
+    }
   }
-  a.n_tiles = (n + rows_per_wg - 1) / rows_per_wg;
+  if (lds > kLdsMax) GMI_FAIL(GMI_ERR_UNSUPPORTED, "rollout_collect: a 16-env tile of this model needs %zu bytes of LDS (limit %zu)", lds, kLdsMax);
+  set_rows(&a, rows_per_wg);
   // weight-stationary variant where this model's padded widths have one (both nets share them)
   typedef void (*rollout_fn)(RolloutArgs);
-  rollout_fn kfn = R == 64 ? rollout_fused_kernel<2> : rollout_fused_kernel<1>;
-  int variant = R == 64 ? 1 : 0;
-  if (ws_matches<WsAnt>(L)) { kfn = R == 64 ? rollout_fused_kernel<2, WsAnt> : rollout_fused_kernel<1, WsAnt>; variant += 2; }
-  else if (ws_matches<WsSmallObs>(L)) { kfn = R == 64 ? rollout_fused_kernel<2, WsSmallObs> : rollout_fused_kernel<1, WsSmallObs>; variant += 4; }
-  // 16 envs per workgroup: the weight-stationary nets on 16-row products
-  if (rows_per_wg == 16 && variant == 2) { kfn = rollout_fused_kernel<1, WsAnt, true>; variant = 6; }
-  else if (rows_per_wg == 16 && variant == 4) { kfn = rollout_fused_kernel<1, WsSmallObs, true>; variant = 7; }
-  static gmi::DeviceSet allowed[8];
+  rollout_fn kfn = rows_per_wg == 64 ? rollout_fused_kernel<2> : rollout_fused_kernel<1>;
+  int variant = rows_per_wg == 64 ? 1 : 0;
+  if (ws_matches<WsAnt>(L)) { kfn = rows_per_wg == 64 ? rollout_fused_kernel<2, WsAnt> : rollout_fused_kernel<1, WsAnt>; variant += 2; }
+  else if (ws_matches<WsSmallObs>(L)) { kfn = rows_per_wg == 64 ? rollout_fused_kernel<2, WsSmallObs> : rollout_fused_kernel<1, WsSmallObs>; variant += 4; }
+  // 16 envs per workgroup: the nets on 16-row products
+  if (rows_per_wg == 16) {
+    if (variant == 2) { kfn = rollout_fused_kernel<1, WsAnt, true>; variant = 6; }
+    else if (variant == 4) { kfn = rollout_fused_kernel<1, WsSmallObs, true>; variant = 7; }
+    else { kfn = rollout_fused_kernel<1, void, true>; variant = 8; }
+  }
+  static gmi::DeviceSet allowed[9];
   const int lds_rc = gmi::allow_lds((const void*)kfn, kLdsMax, g->device, &allowed[variant]);
   if (lds_rc != GMI_OK) return lds_rc;
   // no more workgroups than the instance's compute units hold at once; the rest of the tiles are taken

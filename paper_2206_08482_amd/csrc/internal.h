@@ -65,6 +65,14 @@ int allow_lds(const void* kernel, size_t bytes, int device, DeviceSet* done);
 static inline int pad32(int x) { return (x + 31) & ~31; }
 static inline int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
+// 16 bytes per lane from base + s_off + lane_off, base and s_off wave-uniform: the address takes no vector instruction and no
+// vector registers beside lane_off.
+__device__ __forceinline__ uint4 load_uniform(const void* base, int s_off, uint32_t lane_off) {
+  const auto v = __builtin_amdgcn_raw_buffer_load_b128(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0xFFFFFFFFu, 0x00020000),
+                                                       lane_off, s_off, 0);
+  return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
 // 16 bytes to base + off (base wave-uniform, off < 4 GiB) written through the second-level cache (sc0 sc1).  For what a kernel
 // leaves to the next one: written back otherwise, up to 4 MB per die stay dirty until the kernel's end, and the write-back that
 // ends a kernel runs at 2.5 TB/s with the compute units idle.  Measured, us per launch with ordinary stores / these:
@@ -220,7 +228,8 @@ struct gmi_model {
 struct gmi_env {
   uint32_t magic;
   gmi_env_desc d;
-  float* m_t;       // dev [(O + A), O]: rows 0..O-1 = A^T, rows O..O+A-1 = B^T
+  float* m_t;       // dev [(O + A), o4]: rows 0..O-1 = A^T, rows O..O+A-1 = B^T
+  float* m_r;       // dev [o4, env_row_stride]: rows of [A B], in the same allocation
   uint32_t* episode_step;
 };
 
@@ -235,6 +244,10 @@ struct gmi_buffer {
 };
 
 namespace gmi {
+// Floats between the rows of [A B]: an odd number of 16-byte pieces, so that 16-byte LDS reads of consecutive rows hit
+// different banks.
+__host__ __device__ static inline int env_row_stride(int obs_dim, int act_dim) { return (((obs_dim + act_dim + 3) >> 2) | 1) * 4; }
+
 // Workgroups of a kernel that the instance's compute units hold at once (*groups >= 1).  A launch of more keeps the
 // dispatcher busy and kernels of other streams wait behind it, so kernels that walk their tiles launch no more than this.
 int resident_groups(gmi_instance* g, const void* kernel, int threads, size_t lds, int64_t* groups);

@@ -115,4 +115,11 @@ __device__ __forceinline__ uint32_t feistel_perm(uint32_t i, uint32_t n, int bit
   return y;
 }
 
+// A block's part of a step's cost: the sum of squares of its state elements plus 0.01 times that of its actions, two roundings
+// wherever it is computed.
+__device__ __forceinline__ float reward_part(float ps, float pa) {
+#pragma clang fp contract(off)
+  return ps + 0.01f * pa;
+}
+
 }  // namespace gmi

@@ -390,3 +390,46 @@ def test_fp32_elu_is_within_an_ulp(g, inst, obs, n):
     want = np.where(z > 0, z, np.expm1(np.minimum(z, 0.0)))
     ulp = np.spacing(np.abs(want).astype(np.float32)).astype(np.float64)
     assert (np.abs(got - want) <= ulp).all(), (np.abs(got - want) / ulp).max()
+
+
+@pytest.mark.parametrize("obs,act,hidden,n,T", [
+    (1, 1, [32], 1, 3), (2, 1, [33, 65], 15, 4), (7, 3, [48], 16, 3),      # 16 envs; 1, 2 and 3 products left over of a group of four
+    (3, 21, [40], 17, 3),                      # more blocks of actions than of states
+    (45, 12, [128, 128], 100, 5), (130, 9, [300, 100], 33, 3),      # two weight rounds per layer, nine state tiles
+    (254, 24, [256], 40, 3),                   # the simulator's matrix read from memory
+    (90, 6, [512, 100], 17000, 2),             # 32 envs, the matrix staged at every step
+    (200, 30, [64], 16500, 2),                 # two states of 64 envs do not fit: 32
+    (120, 6, [64, 100], 17000, 2),             # 64 envs, a step's draws ahead of it
+    (300, 16, [32], 20000, 2),                 # 32 envs, the same
+])
+def test_collection_at_the_edges_of_its_layouts(g, obs, act, hidden, n, T):
+    """Same draws, same sums in the same order: bit for bit the step-by-step calls."""
+    ses = _collecting_sessions(obs, act, hidden, "bf16", n, T, None)
+    for it in range(2):
+        for s in ses:
+            s.rollout(it)
+            s.sync()
+        assert ses[0].fused_rollout and not ses[1].fused_rollout
+        ga, gb = (s.buf.to_numpy() for s in ses)
+        for k in ("obs", "act", "logp", "val", "rew", "done"):
+            assert np.array_equal(ga[k], gb[k]), (it, k)
+        assert torch.equal(ses[0].state(), ses[1].state()) and torch.equal(ses[0].last_value, ses[1].last_value)
+        assert torch.equal(ses[0].episode_step, ses[1].episode_step)
+    for s in reversed(ses):
+        s.close()
+
+
+@pytest.mark.parametrize("obs,act,hidden,n", [(408, 40, [32], 40), (380, 9, [32], 20), (3, 21, [40], 17)])
+def test_fp32_collection_at_the_edges_of_its_layout(g, obs, act, hidden, n):
+    """A step's draws ahead of it (408:32:40), the matrix from memory; 1e-5 as everywhere on this path."""
+    ses = _collecting_sessions(obs, act, hidden, "f32", n, 3, None)
+    for s in ses:
+        s.rollout(0)
+        s.sync()
+    assert ses[0].fused_rollout_f32 and not ses[1].fused_rollout_f32
+    ga, gb = (s.buf.to_numpy() for s in ses)
+    assert np.array_equal(ga["done"], gb["done"])
+    for k in ("obs", "act", "logp", "val", "rew"):
+        assert rel_l2(ga[k], gb[k]) <= 1e-5, (k, rel_l2(ga[k], gb[k]))
+    for s in reversed(ses):
+        s.close()
