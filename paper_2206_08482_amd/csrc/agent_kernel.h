@@ -42,7 +42,7 @@ struct AgentArgs {
   int bias_floats;         // of all layers, policy net (its head is the wider one)
   int vec_obs;             // the observations are 16-byte aligned
   int lp_blocks;           // log-density: 1 = blocks of 4 actions summed first, 0 = one action after the other
-  uint32_t o_magic, pad_magic, k0, k1, step, env_offset;
+  uint32_t o_magic, pad_magic, nb_magic, k0, k1, step, env_offset;
   const float *log_std, *obs;
   float *act, *logp, *value, *mu_out;      // act NULL: means and values only
   // values_kernel: slot t < T reads obs + t obs_step and writes value + t val_step, slot T reads obs_last and writes value_last;
@@ -102,9 +102,10 @@ __device__ __forceinline__ int div_magic(int n, uint32_t m) { return m ? (int)__
 template <class P, int D>
 using Ring = uint4[D][P::pieces];
 
-// acc[i] += W tile x row tiles at xp, xp + xts bytes; wq holds the first k steps' weight blocks of this lane.
+// acc[i] += W tile x row tiles at xp, xp + xts bytes; w: the tile's weight blocks (wave-uniform), of which wq holds the first k
+// steps' for this lane.
 template <class P, int D, int NRT>
-__device__ __forceinline__ void k_loop(floatx16 (&acc)[NRT], Ring<P, D>& wq, const uint4* wp, int nks, const unsigned char* xp, int xts) {
+__device__ __forceinline__ void k_loop(floatx16 (&acc)[NRT], Ring<P, D>& wq, const uint4* w, int nks, const unsigned char* xp, int xts, int lane) {
   constexpr int B = 32 * P::pieces;      // bytes of a row per k step
   uint4 x[2][NRT][P::pieces];
   auto read = [&](int b, int ks) {
@@ -124,9 +125,9 @@ __device__ __forceinline__ void k_loop(floatx16 (&acc)[NRT], Ring<P, D>& wq, con
 #pragma unroll
     for (int u = 0; u < D; ++u) {
       step(ks + u, u);
-      const uint4* q = wp + min(ks + u + D, nks - 1) * 64 * P::pieces;
 #pragma unroll
-      for (int p = 0; p < P::pieces; ++p) wq[u][p] = q[64 * p];
+      for (int p = 0; p < P::pieces; ++p)
+        wq[u][p] = gmi::load_uniform(w, (min(ks + u + D, nks - 1) * P::pieces + p) * 1024, lane * 16);
     }
 #pragma unroll
   for (int u = 0; u < D; u += P::align)
@@ -146,11 +147,11 @@ template <class P, int RT, int D, int MT, int NW>
 __device__ __forceinline__ void request(Ring<P, D>& wq, const AgentLayer& L, int item, int lane) {
   const int nft = L.F >> 5, nks = L.K * P::size / (32 * P::pieces);
   const int ft = min(item / (RT / item_tiles<RT, MT, NW>(nft)), nft - 1);
-  const uint4* wp = L.w + (int64_t)ft * nks * 64 * P::pieces + lane;
+  const uint4* w = L.w + (int64_t)ft * nks * 64 * P::pieces;
 #pragma unroll
   for (int u = 0; u < D; ++u)
 #pragma unroll
-    for (int p = 0; p < P::pieces; ++p) wq[u][p] = wp[(min(u, nks - 1) * P::pieces + p) * 64];
+    for (int p = 0; p < P::pieces; ++p) wq[u][p] = gmi::load_uniform(w, (min(u, nks - 1) * P::pieces + p) * 1024, lane * 16);
 }
 
 // All layers of a net on the workgroup's 32 RT rows.  Layer 0 reads the rows at x0; odd layers read ya, even ones yb (which
@@ -176,8 +177,12 @@ __device__ __forceinline__ void net_layers(const AgentLayer* N, int nl, Ring<P, 
       constexpr int NRT = decltype(nrt)::value;
       constexpr int nrg = RT / NRT;
       const int n_items = nft * nrg;
-      for (int item = wave; item < n_items; item += NW) {
-        const int ft = item / nrg, rg = item % nrg;
+      // One kind of item and one pass (MT == 1, !AGAIN): a wave without an item goes through the motions, so that one place in the code
+      // requests weights; where the registers of loads from two places meet, the compiler copies them, and a copy waits for the
+      // load ahead of the layer's barrier.
+      constexpr bool kGhost = MT == 1 && !AGAIN;
+      for (int item = wave; kGhost ? item == wave || item < n_items : item < n_items; item += NW) {
+        const int it = kGhost ? min(item, n_items - 1) : item, ft = it / nrg, rg = it % nrg;
         float4 b4[4];
         if constexpr (!P::bias_lds)
 #pragma unroll
@@ -187,9 +192,15 @@ __device__ __forceinline__ void net_layers(const AgentLayer* N, int nl, Ring<P, 
         for (int i = 0; i < NRT; ++i)
 #pragma unroll
           for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
-        k_loop<P, D, NRT>(acc, wq, L.w + (int64_t)ft * nks * 64 * P::pieces + lane, nks, x + (rg * NRT * 32 + s) * sx + B / 2 * h, 32 * sx);
-        if (item + NW < n_items) request<P, RT, D, MT, NW>(wq, L, item + NW, lane);
-        else if (more) request<P, RT, D, MT, NW>(wq, Ln, wave, lane);
+        if (!kGhost || item < n_items) k_loop<P, D, NRT>(acc, wq, L.w + (int64_t)ft * nks * 64 * P::pieces, nks, x + (rg * NRT * 32 + s) * sx + B / 2 * h, 32 * sx, lane);
+        if constexpr (kGhost) {
+          const bool again = item + NW < n_items;
+          request<P, RT, D, MT, NW>(wq, again ? L : Ln, again ? item + NW : wave, lane);
+          if (item >= n_items) break;
+        } else {
+          if (item + NW < n_items) request<P, RT, D, MT, NW>(wq, L, item + NW, lane);
+          else if (more) request<P, RT, D, MT, NW>(wq, Ln, wave, lane);
+        }
         // lane (s, h) holds, per quad q, the features 32 ft + 8 q + 4 h + 0..3 of row s
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -217,7 +228,7 @@ __device__ __forceinline__ void net_layers(const AgentLayer* N, int nl, Ring<P, 
           }
         }
       }
-      if (wave >= n_items && more) request<P, RT, D, MT, NW>(wq, Ln, wave, lane);
+      if (!kGhost && wave >= n_items && more) request<P, RT, D, MT, NW>(wq, Ln, wave, lane);
     };
     const int nrt = item_tiles<RT, MT, NW>(nft);
     if (nrt == 1) items(std::integral_constant<int, 1>{});
@@ -283,6 +294,13 @@ __global__ __launch_bounds__(64 * NW, WPS) void agent_kernel(AgentArgs a) {
   const int r0 = blockIdx.x * R, rows = min(R, a.n - r0);
 
   Ring<P, D> wq;
+  // this thread's first action element, its log_std requested ahead of everything
+  auto element = [&](int item) {
+    const int blk = item >> 2;
+    return 4 * (blk - div_magic(blk, a.nb_magic) * nb) + (item & 3);
+  };
+  float ls = 0.f;
+  if (net == 0 && nb > 0) ls = a.log_std[min(element(tid), a.A - 1)];
   // biases in LDS: requested here, stored after the observations
   float bv[P::bias_lds ? 4 : 1];
   if constexpr (P::bias_lds)
@@ -298,7 +316,7 @@ __global__ __launch_bounds__(64 * NW, WPS) void agent_kernel(AgentArgs a) {
   }
   if (net == 0)
     for (int item = tid; item < rows * nb; item += kNT) {
-      const int r = item / nb, b = item - r * nb;
+      const int r = div_magic(item, a.nb_magic), b = item - r * nb;
       float z[4];
       gmi::normal_block(a.env_offset + (uint32_t)(r0 + r), a.step, gmi::kStreamAction, (uint32_t)b, a.k0, a.k1, z);
       s_noise[item] = make_float4(z[0], z[1], z[2], z[3]);
@@ -317,14 +335,19 @@ __global__ __launch_bounds__(64 * NW, WPS) void agent_kernel(AgentArgs a) {
   }
   // act = mu + exp(log_std) * eps, one thread per element, which leaves its log-density term in place of its draw
   const int A = a.A;
+  float sigma = expf(ls);
   for (int item = tid; item < rows * nb * 4; item += kNT) {
-    const int blk = item >> 2, r = blk / nb, j = 4 * (blk - r * nb) + (item & 3);
+    const int r = div_magic(item >> 2, a.nb_magic), j = element(item);
+    if (item != tid && j < A) {
+      ls = a.log_std[j];
+      sigma = expf(ls);
+    }
     float* zp = reinterpret_cast<float*>(s_noise) + item;
     float term = 0.f;
     if (j < A) {
-      const float z = *zp, ls = a.log_std[j], m = s_head[r * A + j];
+      const float z = *zp, m = s_head[r * A + j];
       const int64_t o = (int64_t)(r0 + r) * A + j;
-      a.act[o] = fmaf(expf(ls), z, m);
+      a.act[o] = fmaf(sigma, z, m);
       if (a.mu_out) a.mu_out[o] = m;
       term = -0.5f * z * z - ls - 0.918938533204672742f;
     }
@@ -376,6 +399,7 @@ size_t agent_lds(AgentArgs& a, int rt, bool sample) {
   }
   a.o_magic = magic((uint32_t)a.O);
   a.pad_magic = magic((uint32_t)std::max(a.l[0][0].K - a.O, 1));
+  a.nb_magic = magic((uint32_t)((a.A + 3) / 4));
   a.y_off = 32 * rt * w[0];
   a.f_off = 32 * rt * (w[0] + w[1]);
   return (size_t)a.f_off + (size_t)32 * rt * ((sample ? (a.A + 3) / 4 * 16 : 0) + a.A * 4) + (size_t)a.bias_floats * 4;
