@@ -184,6 +184,8 @@ int launch_train_chain(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_p
                        int* n_stat_rows, bool obs16_ready, bool* blocks) {
   const ModelLayout& L = m->L;
   if (L.dtype != GMI_DTYPE_BF16 || L.sh_chain_bytes == 0 || L.act_dim > 32) return GMI_ERR_UNSUPPORTED;
+  // fetch_actions (chain_kernel.h) reads four actions at a time
+  if (((int64_t)(b->d.horizon - 1) * b->d.ld_envs + b->d.n_envs) * L.act_dim < 4) return GMI_ERR_UNSUPPORTED;
   ChainArgs a;
   for (int net = 0; net < 2; ++net) {
     a.wstream[net] = m->shadow + L.sh_chain[net];

@@ -235,6 +235,36 @@ struct ChainShape {
   }
 };
 
+// The actions of one sample for a lane of the head: features 8 q + 4 hh .. + 3 for q = 0 .. 3, by 16-byte loads (4-byte aligned).  Every
+// lane of a load touches a cache line of its own and those take a cycle each, so it is the number of loads that counts: 16
+// single ones took a workgroup of train_tile_kernel 9 thousand cycles.  A load that would pass the row's end is moved
+// back to end there and its values shifted into place where they are used (lane_actions); with fewer than 4 actions it begins
+// in an earlier row, `back` elements before this one, but not before the array's start (the launch sees to 4 elements in all).
+__device__ __forceinline__ int actions_back(int64_t slot, int A) {
+  return A >= 4 ? 0 : (slot * A < 4 - A ? (int)(slot * A) : 4 - A);
+}
+__device__ __forceinline__ void fetch_actions(const float* act, int64_t slot, int A, int hh, float (&out)[16]) {
+  typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+  const int top = A >= 4 ? A - 4 : 0;
+  const float* row = act + slot * A - actions_back(slot, A);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int f0 = 8 * q + 4 * hh;
+    const float4u t = *reinterpret_cast<const float4u*>(row + (f0 < top ? f0 : top));
+    out[4 * q] = t.x; out[4 * q + 1] = t.y; out[4 * q + 2] = t.z; out[4 * q + 3] = t.w;
+  }
+}
+__device__ __forceinline__ void lane_actions(const float (&in)[16], int A, int back, int q, int hh, float (&out)[4]) {
+  const int f0 = 8 * q + 4 * hh;
+  const int sh = A >= 4 ? f0 - (A - 4) : back;               // how far back the load began (4 and more: no feature of A)
+  const float x0 = in[4 * q], x1 = in[4 * q + 1], x2 = in[4 * q + 2], x3 = in[4 * q + 3];
+  const float y = sh == 1 ? x1 : (sh == 2 ? x2 : x3), z = sh == 1 ? x2 : x3;
+  out[0] = sh <= 0 ? x0 : y;
+  out[1] = sh <= 0 ? x1 : z;
+  out[2] = sh <= 0 ? x2 : x3;
+  out[3] = x3;
+}
+
 template <class S>
 struct Ctx {
   uint4 xa[S::maxks()], xb[S::maxks()];      // activation operands of the current layer: in / out (ping-pong by segment)
@@ -244,6 +274,7 @@ struct Ctx {
   uint4 ht[8];                           // stored activations of the group (input-gradient segments)
   uint4 ipre[2];                         // LDS operand of the epilogue item in work / of the next one
   int64_t slot;                          // this lane's sample in the experience buffer
+  int l_back;
   float l_act[16], l_lo, l_ad, l_rt;     // this lane's loss inputs (fetched at kernel start): actions of its 16
                                          // features, old log-prob, advantage, return
   const uint4* wsrc;                     // this net's stream
@@ -324,12 +355,8 @@ __device__ __forceinline__ float wave_sum64(float v) {
 template <class S>
 __device__ __forceinline__ void fetch_loss_inputs(Ctx<S>& c, const ChainArgs& a) {
   c.l_lo = a.b_logp[c.slot]; c.l_ad = a.b_adv[c.slot]; c.l_rt = a.b_ret[c.slot];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int f = 8 * (i >> 2) + 4 * c.hh + (i & 3);
-    const int fc = f < a.act_dim ? f : a.act_dim - 1;
-    c.l_act[i] = a.b_act[c.slot * a.act_dim + fc];
-  }
+  c.l_back = actions_back(c.slot, a.act_dim);
+  fetch_actions(a.b_act, c.slot, a.act_dim, c.hh, c.l_act);
 }
 
 template <class S>
@@ -354,12 +381,14 @@ __device__ __forceinline__ void loss_epilogue(Ctx<S>& c, const ChainArgs& a, con
       const float4 b4 = *reinterpret_cast<const float4*>(c.s_bias + HB + f0);
       const float lsv[4] = {ls4.x, ls4.y, ls4.z, ls4.w}, igv[4] = {ig4.x, ig4.y, ig4.z, ig4.w};
       const float bv[4] = {b4.x, b4.y, b4.z, b4.w};
+      float av[4];
+      lane_actions(c.l_act, A, c.l_back, q, c.hh, av);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int i = 4 * q + e;
         const float mu = acc[i] + bv[e];
         isg[i] = igv[e];
-        z[i] = (c.l_act[i] - mu) * igv[e];                    // 0 for f >= A
+        z[i] = (av[e] - mu) * igv[e];                         // 0 for f >= A
         lp += f0 + e < A ? -0.5f * z[i] * z[i] - lsv[e] - 0.918938533204672742f : 0.f;
       }
     }

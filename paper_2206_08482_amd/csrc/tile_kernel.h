@@ -2,13 +2,14 @@
 // forward pass, clipped-surrogate / value loss and the whole input-gradient chain of one minibatch (stage (ii)
 // of Section 5.1 of the paper, the "DRL Trainer" role of Section 3) in one launch per minibatch.
 //
-// A workgroup of 4 waves owns 128 samples and keeps their current activations in LDS, as the second operands of
+// A workgroup of 8 waves owns 128 samples and keeps their current activations in LDS, as the second operands of
 // the 32x32x16 matrix instruction: block (k step ks, row tile rt) = 1 KiB, lane L of it = the 8 contraction
 // values of sample 32 rt + L % 32 that operand lane L takes.  Every product is computed transposed,
-// H^T = W X^T, and a wave owns a slice of the layer's OUTPUT FEATURES for all 128 samples (F / 128 feature tiles x
-// 4 row tiles, at most 16 accumulator tiles = 256 registers): per k step it fetches its own weight blocks straight
+// H^T = W X^T, and a wave owns a slice of the layer's OUTPUT FEATURES for all 128 samples (F / 256 feature tiles x
+// 4 row tiles, at most 8 accumulator tiles = 128 registers; layers of 4 feature tiles: two waves share one, half the rows
+// each): per k step it fetches its own weight blocks straight
 // from the second-level cache into registers (no other wave of the workgroup needs them) and the 4 activation
-// blocks from LDS, i.e. 8 KiB of operands for 16 matrix instructions.  (With a wave per 32 samples and the weights
+// blocks from LDS, i.e. 6 KiB of operands for 8 matrix instructions.  (With a wave per 32 samples and the weights
 // in LDS every wave reads every weight block: 1 KiB of LDS traffic per matrix instruction, which is the LDS
 // bandwidth of a compute unit.)  The weights come from the chain stream of the register-chained kernel
 // (chain_kernel.h): its blocks are the first operands of exactly these products, its k order inside a 16-wide
@@ -19,6 +20,13 @@
 // the stored activation; conversion; the results into LDS in place of the layer's input; from there they go to memory
 // for the weight-gradient kernel) - barrier.  The next layer's first weight blocks are fetched before the epilogue.
 //
+// Two waves per SIMD, not one of 16 accumulator tiles: an epilogue is straight-line code that runs once, and one wave alone gets
+// its instructions at about a byte per cycle, half of what the vector unit takes; in the k loops one wave's fetches ride under the
+// other's products.  What bounds the walk now: the matrix unit in the k loops of 512 x 512 layers (17 of 19 thousand cycles), the
+// exponentials in the forward epilogues, and the activations and gradients on their way to memory and back (540 MB for 32768
+// samples: 110 us at the rate of a copy).  Forward + gradients of 32768 samples of 211:512:512:256:128:20, us: 220 with 4 waves,
+// 178 with 8.
+//
 // TileShapeFwd is the same walk cut after the heads (agent_act / agent_value of these models: Section 3, "DRL Agent"):
 // nothing is stored for the weight gradients and the heads' results go out as policy means and values.
 #pragma once
@@ -28,9 +36,10 @@ namespace gmi_tile {
 using namespace gmi_chain;
 
 constexpr int kRows = 128;        // samples per workgroup
-constexpr int kWaves = 4;
-constexpr int kRing = 16;         // weight blocks in flight per wave: 16 / (feature tiles per wave) k steps
-constexpr int kHPre = 3;          // tiles whose stored activations are fetched ahead in an input-gradient epilogue
+constexpr int kWaves = 8;
+constexpr int kLossWaves = kRows / 32;      // the loss and the heads are a row tile per wave: the first four
+constexpr int kRing = 8;          // weight blocks in flight per wave: 8 / (feature tiles per wave) k steps
+constexpr int kHPre = 4;          // tiles whose stored activations are fetched ahead in an input-gradient epilogue
 
 template <int... DIMS>
 struct TileShape {
@@ -55,14 +64,14 @@ struct TileShape {
     return n;
   }
   static constexpr size_t x_bytes() { return (size_t)maxks() * 4 * 1024; }
-  static constexpr size_t lds_bytes() { return x_bytes() + (size_t)bias_total() * 4 + (size_t)(kWaves * 40 + 64) * 4; }
+  static constexpr size_t lds_bytes() { return x_bytes() + (size_t)bias_total() * 4 + (size_t)(kLossWaves * 40 + 64) * 4; }
   static constexpr bool valid() {
     const ChainDims D = dims();
-    if (D.d[NL] != 32 || D.d[0] % 16 != 0) return false;
+    if (D.d[NL] != 32 || D.d[0] % 16 != 0 || maxks() > 32) return false;
     for (int l = 1; l < NL; ++l)
       if (D.d[l] % 128 != 0) return false;
     // the loss epilogue's per-wave transposition buffers live in the activation area behind the head layer's input
-    return x_bytes() >= 65536 + (size_t)kWaves * kScrBytes && D.d[NL - 1] / 16 * 4096 <= 65536;
+    return x_bytes() >= 65536 + (size_t)kLossWaves * kScrBytes && D.d[NL - 1] / 16 * 4096 <= 65536;
   }
 };
 
@@ -84,11 +93,14 @@ struct Seg {
   static constexpr bool bwd = SEG >= S::NL;
   static constexpr bool last = !S::fwd && SEG == S::nseg() - 1;
   static constexpr int layer = cd_layer(D, SEG);
-  static constexpr int FTW = head ? 1 : NFT / kWaves;     // feature tiles per wave
-  static constexpr int RT = head ? 1 : 4;                 // row tiles per wave (the head: one row tile per wave)
+  // Waves over features, then over rows: wave w has the feature tiles (w % NWF) FTW .. and the row tiles (w / NWF) RT ..  The
+  // head is a row tile per wave, by both halves of the workgroup (the second half's results are dropped).
+  static constexpr int NWF = head ? 1 : (NFT < kWaves ? NFT : kWaves);
+  static constexpr int FTW = head ? 1 : NFT / NWF;        // feature tiles per wave
+  static constexpr int RT = head ? 1 : 4 / (kWaves / NWF);      // row tiles per wave
   static constexpr int GS = NFT >= 4 ? 4 : NFT;           // tiles per group of the stream (chain_kernel.h)
   static constexpr int DEP = kRing / FTW < NKS ? kRing / FTW : NKS;      // k steps of weight blocks in flight
-  static constexpr int XD = FTW >= 4 ? 1 : 2;             // k steps the activation blocks are read ahead (a k step of
+  static constexpr int XD = FTW >= 2 ? 1 : 2;             // k steps the activation blocks are read ahead (a k step of
                                                           // fewer products is shorter than an LDS round trip)
   static constexpr int blk0 = S::seg_blk0(SEG);
   // The segment's input, which the previous segment's epilogue left in LDS, goes to memory block by block (for the
@@ -98,42 +110,64 @@ struct Seg {
   // segment (the gather stores its rows) nor the first input-gradient segment (the loss epilogue stores the head's).
   static constexpr int HK = NKS > 6 ? NKS - 6 : 0;        // k step at which an input-gradient segment starts to fetch ELU' inputs
   static constexpr bool store_x = !S::fwd && ((SEG >= 1 && SEG <= S::NL - 1) || SEG > S::NL);
-  static_assert(head || NFT % kWaves == 0, "feature tiles divide over the waves");
+  static_assert(head || (NFT % NWF == 0 && kWaves % NWF == 0 && kWaves / NWF <= 4), "feature and row tiles divide over the waves");
   static_assert(!head || NFT == 1, "the head is one 32-wide tile");
 };
 
 template <class S>
 struct Ctx {
-  floatx16 acc[4][4];
+  floatx16 acc[2][4];
   uint4 wq[kRing];                   // weight blocks of k steps g .. g + DEP - 1: block (ks, a) at (ks % DEP) * FTW + a
   uint4 xq[3][4];                    // activation blocks of k steps g .. g + XD (ring indexed by k step % 3)
-  uint4 sx[2];                       // blocks of the activation area on their way to memory (store_x)
+  uint4 sx;                          // block of the activation area on its way to memory (store_x)
   uint4 hq[kHPre + 1][2];            // stored activations of the tiles ahead (input-gradient epilogues)
   const uint4* wnet;                 // this net's stream
   uint4* X;                          // activation area
+  uint32_t lane16;                   // 16 lane
+  uint32_t xo[2];                    // this lane's byte offset in k steps 0 .. 15 and 16 .. 31 of the activation area
   const float* s_bias;
   float* s_red;
   char* scr;                         // this wave's transposition buffer (loss epilogue only)
   int64_t slot;                      // experience slot of this lane's sample of the head layer
+  int l_back;
   float l_act[16], l_lo, l_ad, l_rt;
   int tid, lane, wave, s, hh;
   int row0, net;                     // first row of the workgroup's tile
 };
 
-// First weight block of wave `wave` in segment SEG: its FTW tiles are consecutive tiles of one group of the stream.
+template <class G, class S>
+__device__ __forceinline__ int first_ft(const Ctx<S>& c) { return G::head ? 0 : (c.wave & (G::NWF - 1)) * G::FTW; }
+template <class G, class S>
+__device__ __forceinline__ int first_rt(const Ctx<S>& c) {
+  if constexpr (G::head) return c.wave & 3;
+  else if constexpr (G::NWF == kWaves) return 0;
+  else return c.wave / G::NWF * G::RT;
+}
+
+// First weight block (bytes from the stream's start) of wave `wave` in segment SEG: its FTW tiles are consecutive tiles of one group of the stream.
 template <class S, int SEG>
-__device__ __forceinline__ const uint4* seg_weights(const Ctx<S>& c) {
+__device__ __forceinline__ int seg_weights(const Ctx<S>& c) {
   using G = Seg<S, SEG>;
-  const int ft0 = G::head ? 0 : c.wave * G::FTW;
-  const int off = G::blk0 + (ft0 / 4) * 4 * G::NKS + (ft0 % 4);
-  return c.wnet + (int64_t)off * 64;
+  const int ft0 = first_ft<G>(c);
+  return (G::blk0 + (ft0 / 4) * 4 * G::NKS + (ft0 % 4)) * 1024;
+}
+// This lane's 16 bytes of block (ks, rt).  An LDS instruction's constant reaches 64 KiB: with one offset per half of the area every
+// block is a constant away.  (Left to itself the compiler forms an address per block of the upper half, keeps them from one segment
+// to the next and spills them: 47 registers, each reload in a k loop behind every fetch and store in flight.)
+template <class S>
+__device__ __forceinline__ uint4* x_block(const Ctx<S>& c, int ks, int rt) {
+  return reinterpret_cast<uint4*>(reinterpret_cast<char*>(c.X) + c.xo[ks / 16] + rt * 1024) + (ks % 16) * 256;
 }
 template <class S, int SEG, int KS>
-__device__ __forceinline__ void issue_weights(Ctx<S>& c, const uint4* wseg) {
+__device__ __forceinline__ uint4 weight_block(const Ctx<S>& c, int wseg, int ta) {
+  return gmi::load_uniform(c.wnet, wseg + (KS * Seg<S, SEG>::GS + ta) * 1024, c.lane16);
+}
+template <class S, int SEG, int KS>
+__device__ __forceinline__ void issue_weights(Ctx<S>& c, int wseg) {
   using G = Seg<S, SEG>;
   if constexpr (KS < G::NKS) {
 #pragma unroll
-    for (int a = 0; a < G::FTW; ++a) c.wq[(KS % G::DEP) * G::FTW + a] = (wseg + (KS * G::GS + a) * 64)[c.lane];
+    for (int a = 0; a < G::FTW; ++a) c.wq[(KS % G::DEP) * G::FTW + a] = weight_block<S, SEG, KS>(c, wseg, a);
   }
 }
 // The first DEP k steps of segment SEG (issued before the previous segment's epilogue).
@@ -152,7 +186,7 @@ __device__ __forceinline__ void read_x(Ctx<S>& c) {
   using G = Seg<S, SEG>;
   if constexpr (KS < G::NKS) {
 #pragma unroll
-    for (int b = 0; b < G::RT; ++b) c.xq[KS % 3][b] = c.X[(KS * 4 + (G::head ? c.wave : b)) * 64 + c.lane];
+    for (int b = 0; b < G::RT; ++b) c.xq[KS % 3][b] = *x_block(c, KS, first_rt<G>(c) + b);
   }
 }
 
@@ -164,7 +198,7 @@ __device__ __forceinline__ void read_x(Ctx<S>& c) {
 __device__ __forceinline__ int64_t block_word(int tr, int nks, int ks, int rt) { return (((int64_t)tr * nks + ks) * 4 + rt) * 64; }
 
 // One block to memory for the weight-gradient kernel.
-__device__ __forceinline__ void store_block(uint4* blk, int lane, const uint4& v) { gmi::store_through(blk, lane * 16, v); }
+__device__ __forceinline__ void store_block(uint4* blk, uint32_t lane16, const uint4& v) { gmi::store_through(blk, lane16, v); }
 
 // Stored activations h[layer] of tile T = a * RT + b of this wave (input-gradient epilogue of segment SEG): the
 // lane's own slots of the blocks (2 ft, b) and (2 ft + 1, b), i.e. the values at the positions of its 16 results.
@@ -174,10 +208,10 @@ __device__ __forceinline__ void fetch_h(Ctx<S>& c, const ChainArgs& a) {
   if constexpr (G::bwd && T < G::FTW * G::RT) {
     constexpr int ta = T / G::RT, tb = T % G::RT;
     constexpr int nks = G::D.d[G::layer] / 16;
-    const int ft = c.wave * G::FTW + ta;
-    const uint4* p = reinterpret_cast<const uint4*>(a.h[c.net][G::layer]) + block_word(blockIdx.x, nks, 2 * ft, tb) + c.lane;
-    c.hq[T % (kHPre + 1)][0] = p[0];
-    c.hq[T % (kHPre + 1)][1] = p[4 * 64];
+    const int ft = first_ft<G>(c) + ta;
+    const uint4* p = reinterpret_cast<const uint4*>(a.h[c.net][G::layer]) + block_word(blockIdx.x, nks, 2 * ft, first_rt<G>(c) + tb);
+    c.hq[T % (kHPre + 1)][0] = gmi::load_uniform(p, 0, c.lane16);
+    c.hq[T % (kHPre + 1)][1] = gmi::load_uniform(p, 4 * 1024, c.lane16);
   }
 }
 
@@ -191,7 +225,8 @@ __device__ __forceinline__ void fetch_h_first(Ctx<S>& c, const ChainArgs& a) {
 
 // The small operations that ride along with the products of k step KS, by index I: I < RT: the activation block of
 // row tile I for k step KS + XD; then, where the segment's input goes to memory (store_x), wave w's share of that
-// move: I = RT reads block (KS, w) of the activation area, I = RT + 1 stores the block read a k step earlier.
+// move, row tile w % 4 of every other k step: I = RT reads a block of the activation area at even k steps, I = RT + 1 stores it at
+// odd ones.
 template <class S, int SEG>
 __device__ __forceinline__ uint4* store_x_array(const Ctx<S>& c, const ChainArgs& a) {
   using G = Seg<S, SEG>;
@@ -202,12 +237,13 @@ __device__ __forceinline__ void aux_op(Ctx<S>& c, const ChainArgs& a) {
   using G = Seg<S, SEG>;
   if constexpr (I < G::RT) {
     if constexpr (KS + G::XD < G::NKS)
-      c.xq[(KS + G::XD) % 3][I] = c.X[((KS + G::XD) * 4 + (G::head ? c.wave : I)) * 64 + c.lane];
+      c.xq[(KS + G::XD) % 3][I] = *x_block(c, KS + G::XD, first_rt<G>(c) + I);
   } else if constexpr (G::store_x) {
+    static_assert(G::NKS % 2 == 0, "a wave moves a block every two k steps");
     if constexpr (I == G::RT) {
-      c.sx[KS & 1] = c.X[(KS * 4 + c.wave) * 64 + c.lane];
-    } else if constexpr (KS >= 1) {
-      store_block(store_x_array<S, SEG>(c, a) + block_word(blockIdx.x, G::NKS, KS - 1, c.wave), c.lane, c.sx[(KS - 1) & 1]);      // arrays hold whole tiles
+      if constexpr (KS % 2 == 0) c.sx = *x_block(c, KS, c.wave);      // waves 4 .. 7: row tiles 0 .. 3 of k step KS + 1
+    } else if constexpr (KS % 2 == 1) {
+      store_block(store_x_array<S, SEG>(c, a) + block_word(blockIdx.x, G::NKS, KS - 1, c.wave), c.lane16, c.sx);      // arrays hold whole tiles
     }
   }
 }
@@ -226,7 +262,7 @@ __device__ __forceinline__ void aux_slot(Ctx<S>& c, const ChainArgs& a) {
 // idle meanwhile (measured: ~100-170 of a k step's 256 / 512 cycles), one or two of them after every product do not.
 // The next weight block of feature tile a follows the last product that reads the present one.
 template <class S, int SEG, int KS, int M>
-__device__ __forceinline__ void k_products(Ctx<S>& c, const ChainArgs& a, const uint4* wseg) {
+__device__ __forceinline__ void k_products(Ctx<S>& c, const ChainArgs& a, int wseg) {
   using G = Seg<S, SEG>;
   if constexpr (M < G::FTW * G::RT) {
     constexpr int ta = M / G::RT, tb = M % G::RT;
@@ -235,7 +271,7 @@ __device__ __forceinline__ void k_products(Ctx<S>& c, const ChainArgs& a, const 
         c.acc[ta][tb], 0, 0, 0);
     if constexpr (tb == G::RT - 1) {
       if constexpr (KS + G::DEP < G::NKS)
-        c.wq[(KS % G::DEP) * G::FTW + ta] = (wseg + ((KS + G::DEP) * G::GS + ta) * 64)[c.lane];
+        c.wq[(KS % G::DEP) * G::FTW + ta] = weight_block<S, SEG, KS + G::DEP>(c, wseg, ta);
       if constexpr (G::RT == 1) {                                 // the head: one product per k step
         aux_op<S, SEG, KS, 0>(c, a);
         aux_op<S, SEG, KS, 1>(c, a);
@@ -250,7 +286,7 @@ __device__ __forceinline__ void k_products(Ctx<S>& c, const ChainArgs& a, const 
 }
 
 template <class S, int SEG, int KS>
-__device__ __forceinline__ void k_steps(Ctx<S>& c, const ChainArgs& a, const uint4* wseg) {
+__device__ __forceinline__ void k_steps(Ctx<S>& c, const ChainArgs& a, int wseg) {
   using G = Seg<S, SEG>;
   if constexpr (KS < G::NKS) {
     if constexpr (G::bwd && KS == G::HK) {          // the first tiles' stored activations, late enough not to hold up
@@ -267,7 +303,7 @@ __device__ __forceinline__ void tile_epilogue(Ctx<S>& c, const ChainArgs& a) {
   using G = Seg<S, SEG>;
   if constexpr (T < G::FTW * G::RT) {
     constexpr int ta = T / G::RT, tb = T % G::RT;
-    const int ft = c.wave * G::FTW + ta;
+    const int ft = first_ft<G>(c) + ta, rt = first_rt<G>(c) + tb;
     fetch_h<S, SEG, T + kHPre>(c, a);
     const floatx16& acc = c.acc[ta][tb];
     uint32_t w[8];
@@ -285,8 +321,9 @@ __device__ __forceinline__ void tile_epilogue(Ctx<S>& c, const ChainArgs& a) {
       w[2 * q] = pack_bf16(v0, v1);
       w[2 * q + 1] = pack_bf16(v2, v3);
     }
-    c.X[((2 * ft + 0) * 4 + tb) * 64 + c.lane] = make_uint4(w[0], w[1], w[2], w[3]);
-    c.X[((2 * ft + 1) * 4 + tb) * 64 + c.lane] = make_uint4(w[4], w[5], w[6], w[7]);
+    uint4* x = c.X + ((2 * ft) * 4 + rt) * 64 + c.lane;
+    x[0] = make_uint4(w[0], w[1], w[2], w[3]);
+    x[256] = make_uint4(w[4], w[5], w[6], w[7]);
     tile_epilogue<S, SEG, T + 1>(c, a);
   }
 }
@@ -296,12 +333,8 @@ __device__ __forceinline__ void tile_epilogue(Ctx<S>& c, const ChainArgs& a) {
 template <class S>
 __device__ __forceinline__ void fetch_loss_inputs(Ctx<S>& c, const ChainArgs& a) {
   c.l_lo = a.b_logp[c.slot]; c.l_ad = a.b_adv[c.slot]; c.l_rt = a.b_ret[c.slot];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int f = 8 * (i >> 2) + 4 * c.hh + (i & 3);
-    const int fc = f < a.act_dim ? f : a.act_dim - 1;
-    c.l_act[i] = a.b_act[c.slot * a.act_dim + fc];
-  }
+  c.l_back = actions_back(c.slot, a.act_dim);
+  fetch_actions(a.b_act, c.slot, a.act_dim, c.hh, c.l_act);
 }
 
 // Loss on the wave's 32 samples (row tile `wave` of the workgroup) from the head's accumulators: lane = sample s,
@@ -312,6 +345,7 @@ template <class S>
 __device__ __forceinline__ void loss_epilogue(Ctx<S>& c, const ChainArgs& a, const floatx16& acc) {
   constexpr int HB = S::bias_off(S::NL - 1);
   const int A = a.act_dim;
+  if (c.wave < kLossWaves) {
   const int wrow0 = c.row0 + 32 * c.wave;
   const int row = wrow0 + c.s;
   const bool ok = row < a.rows;
@@ -319,7 +353,7 @@ __device__ __forceinline__ void loss_epilogue(Ctx<S>& c, const ChainArgs& a, con
   float d[16];
   float* red = c.s_red + c.wave * 40;
   if (c.net == 0) {
-    const float* s_ls = c.s_red + kWaves * 40;      // [f] log_std, [32 + f] exp(-log_std) (0 for f >= A)
+    const float* s_ls = c.s_red + kLossWaves * 40;      // [f] log_std, [32 + f] exp(-log_std) (0 for f >= A)
     float z[16], isg[16];
     float lp = 0.f;
 #pragma unroll
@@ -330,12 +364,14 @@ __device__ __forceinline__ void loss_epilogue(Ctx<S>& c, const ChainArgs& a, con
       const float4 b4 = *reinterpret_cast<const float4*>(c.s_bias + HB + f0);
       const float lsv[4] = {ls4.x, ls4.y, ls4.z, ls4.w}, igv[4] = {ig4.x, ig4.y, ig4.z, ig4.w};
       const float bv[4] = {b4.x, b4.y, b4.z, b4.w};
+      float av[4];
+      lane_actions(c.l_act, A, c.l_back, q, c.hh, av);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int i = 4 * q + e;
         const float mu = acc[i] + bv[e];
         isg[i] = igv[e];
-        z[i] = (c.l_act[i] - mu) * igv[e];                    // 0 for f >= A
+        z[i] = (av[e] - mu) * igv[e];                         // 0 for f >= A
         lp += f0 + e < A ? -0.5f * z[i] * z[i] - lsv[e] - 0.918938533204672742f : 0.f;
       }
     }
@@ -389,8 +425,9 @@ __device__ __forceinline__ void loss_epilogue(Ctx<S>& c, const ChainArgs& a, con
   c.X[(1 * 4 + c.wave) * 64 + c.lane] = make_uint4(w[4], w[5], w[6], w[7]);
   {
     uint4* arr = reinterpret_cast<uint4*>(a.dz[c.net][S::NL - 1]);
-    store_block(arr + block_word(blockIdx.x, 2, 0, c.wave), c.lane, make_uint4(w[0], w[1], w[2], w[3]));      // arrays hold whole tiles
-    store_block(arr + block_word(blockIdx.x, 2, 1, c.wave), c.lane, make_uint4(w[4], w[5], w[6], w[7]));
+    store_block(arr + block_word(blockIdx.x, 2, 0, c.wave), c.lane16, make_uint4(w[0], w[1], w[2], w[3]));      // arrays hold whole tiles
+    store_block(arr + block_word(blockIdx.x, 2, 1, c.wave), c.lane16, make_uint4(w[4], w[5], w[6], w[7]));
+  }
   }
   // workgroup sums -> this tile's row of the statistics partials
   __syncthreads();
@@ -398,7 +435,7 @@ __device__ __forceinline__ void loss_epilogue(Ctx<S>& c, const ChainArgs& a, con
   if (c.net == 0) {
     if (c.tid < 3) {
       float v = 0.f;
-      for (int wv = 0; wv < kWaves; ++wv) v += c.s_red[wv * 40 + c.tid];
+      for (int wv = 0; wv < kLossWaves; ++wv) v += c.s_red[wv * 40 + c.tid];
       out[c.tid == 0 ? 0 : (c.tid == 1 ? 3 : 4)] = v;
     }
     if (c.tid == 3) {
@@ -411,12 +448,12 @@ __device__ __forceinline__ void loss_epilogue(Ctx<S>& c, const ChainArgs& a, con
     if (c.tid >= 64 && c.tid < 64 + A) {
       const int j = c.tid - 64;
       float v = 0.f;
-      for (int wv = 0; wv < kWaves; ++wv) v += c.s_red[wv * 40 + 8 + j];
+      for (int wv = 0; wv < kLossWaves; ++wv) v += c.s_red[wv * 40 + 8 + j];
       out[gmi::kStatStride + j] = v;
     }
   } else if (c.tid == 0) {
     float v = 0.f;
-    for (int wv = 0; wv < kWaves; ++wv) v += c.s_red[wv * 40];
+    for (int wv = 0; wv < kLossWaves; ++wv) v += c.s_red[wv * 40];
     out[1] = v;
   }
 }
@@ -427,7 +464,7 @@ template <class S>
 __device__ __forceinline__ void head_outputs(Ctx<S>& c, const ChainArgs& a, const floatx16& acc) {
   constexpr int HB = S::bias_off(S::NL - 1);
   const int row = c.row0 + 32 * c.wave + c.s;
-  if (row >= a.rows) return;
+  if (row >= a.rows || c.wave >= kLossWaves) return;
   if (c.net == 0) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -443,13 +480,13 @@ template <class S, int SEG>
 __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
   if constexpr (SEG < n_run<S>()) {
     using G = Seg<S, SEG>;
-    const uint4* wseg = seg_weights<S, SEG>(c);
+    const int wseg = seg_weights<S, SEG>(c);
     if constexpr (!G::bwd && !G::head) {
       // the accumulators start at the bias (register i of a lane = feature 8 (i / 4) + 4 hh + i % 4 of the tile)
       constexpr int boff = S::bias_off(G::layer);
 #pragma unroll
       for (int ta = 0; ta < G::FTW; ++ta) {
-        const float* bp = c.s_bias + boff + 32 * (c.wave * G::FTW + ta) + 4 * c.hh;
+        const float* bp = c.s_bias + boff + 32 * (first_ft<G>(c) + ta) + 4 * c.hh;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const float4 b4 = *reinterpret_cast<const float4*>(bp + 8 * q);
@@ -471,8 +508,6 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
     read_x<S, SEG, 0>(c);
     if constexpr (G::XD > 1) read_x<S, SEG, 1>(c);
     k_steps<S, SEG, 0>(c, a, wseg);
-    if constexpr (G::store_x)
-      store_block(store_x_array<S, SEG>(c, a) + block_word(blockIdx.x, G::NKS, G::NKS - 1, c.wave), c.lane, c.sx[(G::NKS - 1) & 1]);
     issue_first_weights<S, SEG + 1>(c);
     __syncthreads();                       // every wave is done with the layer's input
     // this lane's loss inputs: cold loads, issued where a long stretch of arithmetic follows and no younger load is
@@ -487,12 +522,13 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
     }
     __syncthreads();
     if constexpr (G::last) {
-      // nothing consumes the last results on chip: row tile `wave` of the activation area goes to dz[layer - 1]
-      // block by block, the way a k loop moves its input
+      // nothing consumes the last results on chip: the activation area goes to dz[layer - 1] block by block, the way a k
+      // loop moves its input
       uint4* arr = reinterpret_cast<uint4*>(a.dz[c.net][G::layer - 1]);
 #pragma unroll 8
-      for (int ks = 0; ks < G::F / 16; ++ks)
-        store_block(arr + block_word(blockIdx.x, G::F / 16, ks, c.wave), c.lane, c.X[(ks * 4 + c.wave) * 64 + c.lane]);      // arrays hold whole tiles
+      for (int k2 = 0; k2 < G::F / 16; k2 += 2) {
+        store_block(arr + block_word(blockIdx.x, G::F / 16, k2, c.wave), c.lane16, c.X[(k2 * 4 + c.wave) * 64 + c.lane]);      // arrays hold whole tiles
+      }
     }
     run_segment<S, SEG + 1>(c, a);
   }
@@ -512,35 +548,46 @@ __global__ __launch_bounds__(kWaves * 64) void train_tile_kernel(ChainArgs a) {
   c.net = S::fwd ? (int)blockIdx.y + a.net0 : (int)blockIdx.y;
   c.row0 = blockIdx.x * kRows;
   c.X = reinterpret_cast<uint4*>(smem_raw);
+  c.lane16 = c.lane * 16;
+  c.xo[0] = c.lane16;
+  c.xo[1] = c.lane16 + 65536;
+  asm volatile("" : "+v"(c.xo[1]));
   float* s_bias = reinterpret_cast<float*>(smem_raw + S::x_bytes());
   c.s_bias = s_bias;
   c.s_red = s_bias + S::bias_total();
-  c.scr = reinterpret_cast<char*>(smem_raw) + 65536 + c.wave * kScrBytes;
+  c.scr = reinterpret_cast<char*>(smem_raw) + 65536 + (c.wave & 3) * kScrBytes;
   c.wnet = reinterpret_cast<const uint4*>(a.wstream[c.net]);
 
-  issue_first_weights<S, 0>(c);
-  {
-    int off = 0;
+  // Everything a workgroup starts from is requested before anything is waited for, in the order in which it is needed: the memory
+  // counter is in order.  (Indices, biases and scales loaded and stored one after another behind the first weights: 17 thousand
+  // cycles up to the first product, of 170.)
+  constexpr int NG = kRows / 16 / kWaves;
+  const int rr = c.lane & 15, jj = c.lane >> 4;
+  int sm[NG], srow[NG], hrow = 0, hsm = 0;
+  const void* ixp = a.idx ? (const void*)a.idx : (const void*)a.log_std;      // no index: rows in order
+  const auto ix = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(ixp), 0, 0xFFFFFFFFu, 0x00020000);
 #pragma unroll
-    for (int l = 0; l < S::NL; ++l) {
-      for (int f = c.tid; f < D.d[l + 1]; f += kWaves * 64) s_bias[off + f] = a.bias[c.net][l][f];
-      off += D.d[l + 1];
-    }
-  }
-  for (int i = c.tid; i < kWaves * 40; i += kWaves * 64) c.s_red[i] = 0.f;
-  if (c.tid < 32) {                      // per-feature constants of the Gaussian log-prob (policy net)
-    const int fc = c.tid < a.act_dim ? c.tid : a.act_dim - 1;
-    const float ls = a.log_std[fc];
-    c.s_red[kWaves * 40 + c.tid] = ls;
-    c.s_red[kWaves * 40 + 32 + c.tid] = c.tid < a.act_dim ? expf(-ls) : 0.f;
+  for (int gi = 0; gi < NG; ++gi) {
+    const int row = c.row0 + 16 * (c.wave + kWaves * gi) + rr;
+    srow[gi] = row < a.rows ? row : a.rows - 1;
+    sm[gi] = __builtin_amdgcn_raw_buffer_load_b32(ix, a.idx ? srow[gi] * 4 : 0, 0, 0);
   }
   if constexpr (!S::fwd) {
-    // this lane's sample of the head layer (rows past the batch take the last sample; their results are dropped)
-    const int row = c.row0 + 32 * c.wave + c.s;
-    const int rc = row < a.rows ? row : a.rows - 1;
-    const int sm = a.idx ? a.idx[rc] : rc;
-    c.slot = (int64_t)(sm / a.n_envs) * a.ld_envs + (sm % a.n_envs);
+    // this lane's sample of the head layer (rows past the batch take the last sample, the waves without a part in the loss one
+    // sample for all lanes; their results are dropped)
+    const int row = c.row0 + (c.wave < kLossWaves ? 32 * c.wave + c.s : 0);
+    hrow = row < a.rows ? row : a.rows - 1;
+    hsm = __builtin_amdgcn_raw_buffer_load_b32(ix, a.idx ? hrow * 4 : 0, 0, 0);
   }
+  float bv[S::NL][S::maxks() * 16 / (kWaves * 64)];
+#pragma unroll
+  for (int l = 0; l < S::NL; ++l)
+#pragma unroll
+    for (int i = 0; i * kWaves * 64 < D.d[l + 1]; ++i) {
+      const int f = c.tid + i * kWaves * 64;
+      bv[l][i] = a.bias[c.net][l][f < D.d[l + 1] ? f : D.d[l + 1] - 1];
+    }
+  const float ls = a.log_std[c.tid < a.act_dim ? c.tid : a.act_dim - 1];
   {
     // The gather: the workgroup's 128 observation rows as the first layer's operand blocks in natural k order (lane
     // (s, h) of block (ks, rt) holds features 16 ks + 8 h .. + 7 of sample 32 rt + s), zero padded.  A lane takes
@@ -548,20 +595,14 @@ __global__ __launch_bounds__(kWaves * 64) void train_tile_kernel(ChainArgs a) {
     // consecutive bytes of a row.  The policy net's workgroups also leave the same blocks in x0b for the
     // weight-gradient kernel.  All loads unconditional (clamped addresses, selected values).
     constexpr int NP = D.d[0] / 8;                       // 16-byte pieces of a row
-    const int rr = c.lane & 15, jj = c.lane >> 4;
     const int O = a.obs_dim;
     constexpr int NI = (NP + 3) / 4;
-    int sm[2];
 #pragma unroll
-    for (int gi = 0; gi < 2; ++gi) {
-      const int row = c.row0 + 16 * (c.wave + kWaves * gi) + rr;
-      const int rc = row < a.rows ? row : a.rows - 1;
-      sm[gi] = a.idx ? a.idx[rc] : rc;
-    }
-    uint4 v[2][NI];
+    for (int gi = 0; gi < NG; ++gi) sm[gi] = a.idx ? sm[gi] : srow[gi];
+    uint4 v[NG][NI];
     if (a.x0_ready != 0) {                               // workgroup-uniform; no branch around a single load
 #pragma unroll
-      for (int gi = 0; gi < 2; ++gi) {
+      for (int gi = 0; gi < NG; ++gi) {
         const int row = c.row0 + 16 * (c.wave + kWaves * gi) + rr;
         const uint16_t* src = a.x0_ready == 1 ? a.x0 + (int64_t)row * D.d[0] : a.x16 + (int64_t)sm[gi] * D.d[0];
 #pragma unroll
@@ -572,7 +613,7 @@ __global__ __launch_bounds__(kWaves * 64) void train_tile_kernel(ChainArgs a) {
       }
     } else {
 #pragma unroll
-      for (int gi = 0; gi < 2; ++gi) {
+      for (int gi = 0; gi < NG; ++gi) {
         const int64_t slot = (int64_t)(sm[gi] / a.n_envs) * a.ld_envs + (sm[gi] % a.n_envs);
         const float* orow = a.b_obs + slot * O;
 #pragma unroll
@@ -591,9 +632,31 @@ __global__ __launch_bounds__(kWaves * 64) void train_tile_kernel(ChainArgs a) {
         }
       }
     }
+    issue_first_weights<S, 0>(c);
+    {
+      int off = 0;
+#pragma unroll
+      for (int l = 0; l < S::NL; ++l) {
+#pragma unroll
+        for (int i = 0; i * kWaves * 64 < D.d[l + 1]; ++i) {
+          const int f = c.tid + i * kWaves * 64;
+          if (f < D.d[l + 1]) s_bias[off + f] = bv[l][i];
+        }
+        off += D.d[l + 1];
+      }
+      if (c.tid < kLossWaves * 40) c.s_red[c.tid] = 0.f;
+      if (c.tid < 32) {                      // per-feature constants of the Gaussian log-prob (policy net)
+        c.s_red[kLossWaves * 40 + c.tid] = ls;
+        c.s_red[kLossWaves * 40 + 32 + c.tid] = c.tid < a.act_dim ? expf(-ls) : 0.f;
+      }
+      if constexpr (!S::fwd) {
+        hsm = a.idx ? hsm : hrow;
+        c.slot = (int64_t)(hsm / a.n_envs) * a.ld_envs + (hsm % a.n_envs);
+      }
+    }
     uint4* xb = reinterpret_cast<uint4*>(a.x0b) + block_word(blockIdx.x, D.d[0] / 16, 0, 0);
 #pragma unroll
-    for (int gi = 0; gi < 2; ++gi) {
+    for (int gi = 0; gi < NG; ++gi) {
       const int r = 16 * (c.wave + kWaves * gi) + rr;
 #pragma unroll
       for (int it = 0; it < NI; ++it) {
