@@ -251,9 +251,11 @@ bool has_tile_forward(const ModelLayout& L) {
 }
 
 // agent_act with the one-launch agent kernel / with gather, this kernel and the sampling kernel, us: 211:512:512:256:128:20
-// 34 / 46 for 8192 rows, 49 / 50 for 11000, 51.5 / 49 for 12288, 66 / 54 for 16384, on 64 compute units 27 / 41 for 2048,
-// 39 / 43 for 3072, 51 / 43 for 4096, 96 / 78 for 8192, on 16 39 / 42 for 768, 50 / 43 for 1024; 211:512:512:512:256:20 47 / 57
-// for 8192 rows, 68 / 61 for 12288, on 64 compute units 51 / 53 for 3072, 66 / 54 for 4096, on 16 51 / 52 for 768, 66 / 53 for 1024.
+// 34 / 40 for 8192 rows, 45 / 42 for 9216, 50 / 44 for 12288, on 64 compute units 27 / 37 for 2048, 39 / 38 for 2560 and 3072, on 16
+// 27 / 36 for 512, 39 / 37 for 640 and 768, 50 / 38 for 1024; 211:512:512:512:256:20 44 / 49 for 8192 rows, 58 / 51 for 9216, 63 / 54 for
+// 12288, on 64 compute units 34 / 46 for 2048, 50 / 47 for 2560 and 3072, on 16 35 / 45 for 512, 50 / 46 for 640 and 768.  They cross at 32 rows
+// per compute unit, where the agent kernel needs another round; the line stays at 48, where it was when they crossed there: the
+// two add in different orders, and between 32 and 48 a caller's results would change in the last bit for 3 to 9 us.
 bool use_tile_forward(const gmi_instance* g, const gmi_model* m, int rows) {
   return rows >= 48 * (int64_t)g->cu_count && has_tile_forward(m->L);
 }
