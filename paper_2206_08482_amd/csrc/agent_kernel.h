@@ -18,7 +18,7 @@
 #pragma once
 #include <algorithm>
 
-#include "chain_kernel.h"
+#include "chain_stream.h"
 #include "rng.h"
 
 namespace gmi_agent {

@@ -1,5 +1,5 @@
-// Host side of the register-chained trainer kernel (chain_kernel.h): the weight stream in the shadow, its packing
-// kernel and the launch.  The kernel itself is compiled once per model shape in chain_p<k>.hip.
+// Host side of the row-tile kernels (tile_kernel.h): the weight stream in the shadow, its packing kernel and the launches.  The
+// kernels themselves are compiled once per model shape, the trainers in tile_p<k>.hip, the forward-only ones in tile_f<k>.hip.
 #include <stdlib.h>
 
 #include "tile_kernel.h"
@@ -22,7 +22,6 @@ struct PackSeg {
 struct PackTable {
   int n;
   int total_blocks;
-  int gmax;               // tiles in the largest group (4 or 2)
   PackSeg s[2 * (GMI_MAX_HIDDEN + 1)];
 };
 
@@ -38,8 +37,9 @@ __global__ __launch_bounds__(256) void chain_pack_kernel(PackTable t0, PackTable
   const PackSeg& S = tab.s[si];
   const int nft = S.F >> 5, nks = S.K >> 4;
   int lb = blk - S.blk_start;
-  // locate the group: full groups of gmax tiles first, then (2), then (1)
-  const int gm = tab.gmax, full = nft / gm;
+  // locate the group: full groups of kGroupTiles tiles first, then (2), then (1)
+  constexpr int gm = kGroupTiles;
+  const int full = nft / gm;
   int tile0, gs;
   if (lb < full * gm * nks) {
     const int gi = lb / (gm * nks);
@@ -66,34 +66,26 @@ __global__ __launch_bounds__(256) void chain_pack_kernel(PackTable t0, PackTable
   reinterpret_cast<uint4*>(out)[(int64_t)blk * 64 + lane] = v;
 }
 
-ChainDims dims_of(const ModelLayout& L, int gmax = 4) {
+ChainDims dims_of(const ModelLayout& L) {
   ChainDims D;
   D.nl = L.n_layers;
-  D.gmax = gmax;
   for (int l = 0; l < L.n_layers; ++l) { D.d[l] = L.net[0][l].in_pad; D.d[l + 1] = L.net[0][l].out_pad; }
   return D;
 }
 
 typedef int (*part_fn)(gmi_instance*, const ModelLayout&, const ChainArgs&, int, int*, double, double);
-const part_fn kParts[gmi::kChainParts] = {gmi::launch_chain_part0, gmi::launch_chain_part1, gmi::launch_chain_part2,
-                                          gmi::launch_chain_part3};
-// The row-tile kernel's shapes (tile_kernel.h) come first: a model shape compiled for both takes that one.
-const part_fn kTileFns[gmi::kTileParts] = {gmi::launch_tile_part0, gmi::launch_tile_part1};
+const part_fn kTileFns[gmi::kTileParts] = {gmi::launch_tile_part0, gmi::launch_tile_part1, gmi::launch_tile_part2,
+                                           gmi::launch_tile_part3, gmi::launch_tile_part4, gmi::launch_tile_part5};
 const part_fn kTileFwdFns[gmi::kTileFwdParts] = {gmi::launch_tile_fwd_part0, gmi::launch_tile_fwd_part1};
 
-// What the trainer kernel compiled for this model's shape answers to the probe: its largest group, plus 256 if it
-// can gather its rows from the bf16 copy of all observations; 0 if there is none.
-int compiled_probe(const ModelLayout& L) {
+// True if a trainer kernel is compiled for this model's shape.
+bool compiled(const ModelLayout& L) {
   ChainArgs none = {};
   int v = 0;
   for (int p = 0; p < gmi::kTileParts; ++p)
-    if (kTileFns[p](nullptr, L, none, 0, &v, 0.0, 0.0) == GMI_OK) return v;
-  for (int p = 0; p < gmi::kChainParts; ++p)
-    if (kParts[p](nullptr, L, none, 0, &v, 0.0, 0.0) == GMI_OK) return v;
-  return 0;
+    if (kTileFns[p](nullptr, L, none, 0, &v, 0.0, 0.0) == GMI_OK) return true;
+  return false;
 }
-int compiled_gmax(const ModelLayout& L) { return compiled_probe(L) & 255; }
-bool compiled_x16(const ModelLayout& L) { return (compiled_probe(L) & 256) != 0; }
 
 }  // namespace
 
@@ -101,7 +93,7 @@ bool compiled_x16(const ModelLayout& L) { return (compiled_probe(L) & 256) != 0;
 namespace gmi {
 using namespace gmi_chain;
 
-bool chain_compiled(const ModelLayout& L) { return L.sh_chain_bytes != 0 && compiled_gmax(L) != 0; }
+bool chain_compiled(const ModelLayout& L) { return L.sh_chain_bytes != 0 && compiled(L); }
 
 // Bytes of one net's chain stream (0 if the two nets' padded widths differ, which only a policy head wider
 // than 32 outputs can cause: such models have no chain stream).
@@ -109,7 +101,7 @@ int64_t chain_stream_bytes(const ModelLayout& L) {
   if (L.dtype != GMI_DTYPE_BF16) return 0;
   for (int l = 0; l < L.n_layers; ++l)
     if (L.net[0][l].in_pad != L.net[1][l].in_pad || L.net[0][l].out_pad != L.net[1][l].out_pad) return 0;
-  return (int64_t)cd_nblocks(dims_of(L)) * 1024 + kSlotBytes;      // tail padding: chunks are fetched as full 16 KiB
+  return (int64_t)cd_nblocks(dims_of(L)) * 1024 + 16 * 1024;      // (the padding keeps the size that shadows always had)
 }
 
 // Rebuilds both nets' chain streams from the row-major shadows (W for the forward segments, W^T for the
@@ -117,13 +109,11 @@ int64_t chain_stream_bytes(const ModelLayout& L) {
 int launch_chain_pack(gmi_instance* g, gmi_model* m) {
   const ModelLayout& L = m->L;
   if (L.sh_chain_bytes == 0) return GMI_OK;
-  const int gmax = compiled_gmax(L);
-  if (gmax == 0) return GMI_OK;                        // no chained kernel for this shape: nobody reads the stream
-  const ChainDims D = dims_of(L, gmax);
+  if (!compiled(L)) return GMI_OK;                     // no kernel for this shape: nobody reads the stream
+  const ChainDims D = dims_of(L);
   PackTable t[2];
   for (int net = 0; net < 2; ++net) {
     t[net].n = cd_nseg(D);
-    t[net].gmax = gmax;
     int blk = 0;
     for (int s = 0; s < cd_nseg(D); ++s) {
       PackSeg& ps = t[net].s[s];
@@ -149,10 +139,9 @@ void fill_chain_emit(const ModelLayout& L, ChainEmit* ce) {
   ce->gmax = 0;
   ce->n_layers = L.n_layers;
   if (L.sh_chain_bytes == 0) return;
-  const int gmax = compiled_gmax(L);
-  if (gmax == 0) return;
-  const ChainDims D = dims_of(L, gmax);
-  ce->gmax = gmax;
+  if (!compiled(L)) return;
+  const ChainDims D = dims_of(L);
+  ce->gmax = kGroupTiles;
   for (int net = 0; net < 2; ++net) {
     ce->out[net] = L.sh_chain[net];
     for (int l = 0; l < L.n_layers; ++l) ce->l[net * L.n_layers + l] = ChainEmitLayer{0, -1, l == 0 ? 1 : 0};
@@ -172,7 +161,7 @@ int prepare_obs16(gmi_instance* g, gmi_model* m, gmi_buffer* b, int rows, int cu
   const ModelLayout& L = m->L;
   *ready = false;
   if (!b->obs16 || g->fusion < 1 || L.dtype != GMI_DTYPE_BF16 || L.sh_chain_bytes == 0 || L.act_dim > 32 ||
-      use_resident(L, rows, cus) || !compiled_x16(L))
+      use_resident(L, rows, cus) || !compiled(L))
     return GMI_OK;
   const int64_t B = (int64_t)b->d.horizon * b->d.n_envs;
   const int rc = launch_gather_to(g, m, b->d.obs, b->d.n_envs, b->d.ld_envs, nullptr, (int)B, nullptr, b->obs16);
@@ -181,10 +170,10 @@ int prepare_obs16(gmi_instance* g, gmi_model* m, gmi_buffer* b, int rows, int cu
 }
 
 int launch_train_chain(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_hparams* hp, const int32_t* idx, int rows,
-                       int* n_stat_rows, bool obs16_ready, bool* blocks) {
+                       int* n_stat_rows, bool obs16_ready) {
   const ModelLayout& L = m->L;
   if (L.dtype != GMI_DTYPE_BF16 || L.sh_chain_bytes == 0 || L.act_dim > 32) return GMI_ERR_UNSUPPORTED;
-  // fetch_actions (chain_kernel.h) reads four actions at a time
+  // fetch_actions (tile_kernel.h) reads four actions at a time
   if (((int64_t)(b->d.horizon - 1) * b->d.ld_envs + b->d.n_envs) * L.act_dim < 4) return GMI_ERR_UNSUPPORTED;
   ChainArgs a;
   for (int net = 0; net < 2; ++net) {
@@ -203,7 +192,7 @@ int launch_train_chain(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_p
   a.n_envs = b->d.n_envs; a.ld_envs = b->d.ld_envs; a.obs_dim = L.obs_dim;
   a.x0_ready = (L.obs_dim % 4 == 0 && ((uintptr_t)b->d.obs & 15) == 0) ? 0 : 1;
   a.x16 = b->obs16;
-  if (a.x0_ready == 1 && obs16_ready && b->obs16 && idx && compiled_x16(L)) a.x0_ready = 2;
+  if (a.x0_ready == 1 && obs16_ready && b->obs16 && idx) a.x0_ready = 2;
   a.rows = rows; a.act_dim = L.act_dim;
   a.clip = hp->clip; a.c_v = hp->c_v;
   a.stat_part = m->stat_part;
@@ -226,17 +215,13 @@ int launch_train_chain(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_p
     }
   }
   bytes += 4.0 * rows * (L.act_dim + 3);
-  if (compiled_gmax(L) == 0) return GMI_ERR_UNSUPPORTED;
-  if (a.x0_ready == 1) {  // unaligned observation rows: the gather kernel converts them (a lane-wise gather of 4-byte
-                          // pieces at the start of the chained kernel measured slower than the separate launch)
+  if (!compiled(L)) return GMI_ERR_UNSUPPORTED;
+  if (a.x0_ready == 1) {  // unaligned observation rows: the gather kernel converts them
     rc = launch_gather(g, m, b->d.obs, b->d.n_envs, b->d.ld_envs, idx, rows, nullptr);
     if (rc != GMI_OK) return rc;
   }
   rc = GMI_ERR_UNSUPPORTED;
-  *blocks = false;
   for (int p = 0; p < kTileParts && rc == GMI_ERR_UNSUPPORTED; ++p) rc = kTileFns[p](g, L, a, rows, &tiles, flops, bytes);
-  if (rc == GMI_OK) *blocks = true;
-  for (int p = 0; p < kChainParts && rc == GMI_ERR_UNSUPPORTED; ++p) rc = kParts[p](g, L, a, rows, &tiles, flops, bytes);
   if (rc != GMI_OK) return rc;
   *n_stat_rows = tiles;
   return GMI_OK;

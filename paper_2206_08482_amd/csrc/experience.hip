@@ -242,7 +242,7 @@ extern "C" int gmi_buffer_bind(gmi_t g, const gmi_buffer_desc* d, gmi_buffer_t* 
     if (e == hipSuccess && d->horizon > 0) {
       e = hipMalloc(&b->perm, sizeof(int32_t) * (size_t)gmi::kPermEpochs * d->horizon * d->n_envs);
       if (e != hipSuccess) (void)hipFree(b->part);
-      // observation rows that 16-byte loads cannot read: room for their bf16 copy (the trainer's chained kernel)
+      // observation rows that 16-byte loads cannot read: room for their bf16 copy (the row-tile trainer kernel)
       if (e == hipSuccess && (d->obs_dim % 4 != 0 || ((uintptr_t)d->obs & 15) != 0)) {
         e = hipMalloc(&b->obs16, sizeof(uint16_t) * (size_t)d->horizon * d->n_envs * gmi::pad32(d->obs_dim));
         if (e != hipSuccess) { (void)hipFree(b->part); (void)hipFree(b->perm); }

@@ -73,16 +73,16 @@ __device__ __forceinline__ uint4 load_uniform(const void* base, int s_off, uint3
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
-// 16 bytes to base + off (base wave-uniform, off < 4 GiB) written through the second-level cache (sc0 sc1).  For what a kernel
+// 16 bytes to base + off + s_off (base and s_off wave-uniform, offsets < 4 GiB) written through the second-level cache (sc0 sc1).  For what a kernel
 // leaves to the next one: written back otherwise, up to 4 MB per die stay dirty until the kernel's end, and the write-back that
 // ends a kernel runs at 2.5 TB/s with the compute units idle.  Measured, us per launch with ordinary stores / these:
-// train_resident_kernel of 45:128:128:12 with 6000 rows (17 MB of gradient partials) 25.8 / 23.7, train_chain_kernel of
-// 108:400:200:100:21 with 32768 rows 104.4 / 99.8, train_tile_kernel of 211:512:512:256:128:20 220 / 216.  Non-temporal stores
+// train_resident_kernel of 45:128:128:12 with 6000 rows (17 MB of gradient partials) 25.8 / 23.7, train_tile_kernel of
+// 211:512:512:256:128:20 with 32768 rows 220 / 216.  Non-temporal stores
 // bypass the memory-side cache as well: the kernel that reads them waits longer (Adam 7.2 / 8.4).
-__device__ __forceinline__ void store_through(void* base, uint32_t off, const uint4& v) {
+__device__ __forceinline__ void store_through(void* base, uint32_t off, const uint4& v, int s_off = 0) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   const u32x4 x = {v.x, v.y, v.z, v.w};
-  __builtin_amdgcn_raw_buffer_store_b128(x, __builtin_amdgcn_make_buffer_rsrc(base, 0, 0xFFFFFFFFu, 0x00020000), off, 0, 17);
+  __builtin_amdgcn_raw_buffer_store_b128(x, __builtin_amdgcn_make_buffer_rsrc(base, 0, 0xFFFFFFFFu, 0x00020000), off, s_off, 17);
 }
 __device__ __forceinline__ void store_through(void* base, uint32_t off, float x, float y, float z, float w) {
   store_through(base, off, make_uint4(__float_as_uint(x), __float_as_uint(y), __float_as_uint(z), __float_as_uint(w)));
@@ -362,13 +362,13 @@ static inline int trainer_cus(const gmi_instance* g, int n) {
 // Trainer workgroups per net of the resident and fp32 kernels: one per two compute units.
 static inline int trainer_groups(int cus) { return cus >= 2 ? (cus < 256 ? cus / 2 : 128) : 1; }
 
-bool chain_compiled(const ModelLayout& L);       // a register-chained or row-tile trainer kernel has this shape
+bool chain_compiled(const ModelLayout& L);       // a row-tile trainer kernel has this shape
 
 // Shuffles of epochs epoch0 .. epoch0 + n_epochs - 1 into out[e][n], one launch.
 constexpr int kPermEpochs = 8;
 int launch_permutation(gmi_instance* g, int n, uint64_t seed, uint32_t iteration, uint32_t epoch0, int n_epochs, int32_t* out);
 
-// Register-chained trainer kernel (chain.hip): its weight stream in the shadow and the launch.
+// Row-tile trainer kernel (chain.hip): its weight stream in the shadow and the launch.
 int64_t chain_stream_bytes(const ModelLayout& L);
 int launch_chain_pack(gmi_instance* g, gmi_model* m);
 // Where shadow_transpose_kernel puts the blocks of the chain streams (the layout launch_chain_pack writes): per
@@ -417,10 +417,9 @@ int launch_env_step(gmi_instance* g, gmi_env* env, const float* obs, const float
 int launch_sample(gmi_instance* g, const float* mu, const float* log_std, int n_rows, int act_dim, uint64_t seed,
                   uint32_t step, uint32_t env_offset, float* act, float* logp, float* mu_out);
 // obs16_ready: b->obs16 holds the bf16 copy of the buffer's present observations (prepare_obs16).
-// *blocks = whether the hidden activations and gradients were left in the row-tile kernel's block layout.
 int launch_train_chain(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_hparams* hp, const int32_t* idx, int rows,
-                       int* n_stat_rows, bool obs16_ready, bool* blocks);
-// Before the minibatches of an update: converts all observations of the buffer into b->obs16 if the chained kernel
+                       int* n_stat_rows, bool obs16_ready);
+// Before the minibatches of an update: converts all observations of the buffer into b->obs16 if the row-tile kernel
 // will run and cannot read the fp32 rows itself.  *ready = whether it did.
 int prepare_obs16(gmi_instance* g, gmi_model* m, gmi_buffer* b, int rows, int cus, bool* ready);
 
@@ -438,7 +437,8 @@ static inline int wgrad_split_limit(int n_tiles) {
   if (s > kSplitMax) s = kSplitMax;
   return s;
 }
-constexpr int kLossBlocksMax = 2048; // rows of per-workgroup loss statistics (one more row holds their sum)
+constexpr int kLossBlocksMax = 2048; // workgroups of the loss kernel
+constexpr int kStatRowsMax = 8192;   // rows of per-workgroup loss statistics (one more row holds their sum)
 constexpr int kStatStride = 8;       // per-workgroup statistics slots before the log_std partials
 
 // Fragment-major weight copy for the row-tile fused kernels: the weights of (32-feature tile ft, 16-wide

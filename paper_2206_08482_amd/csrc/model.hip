@@ -59,7 +59,7 @@ int build_layout(const gmi_model_desc* d, ModelLayout* L) {
   L->part_floats = d->dtype == GMI_DTYPE_BF16 ? (pf + 255) & ~(int64_t)255 : off;
   L->weight_bytes = wbytes;
   L->max_width_pad = maxw;
-  // the register-chained trainer kernel's weight streams (one per net), after everything else
+  // the row-tile trainer kernel's weight streams (one per net), after everything else
   L->sh_chain_bytes = gmi::chain_stream_bytes(*L);
   for (int net = 0; net < 2; ++net) {
     L->sh_chain[net] = sh;
@@ -409,7 +409,7 @@ extern "C" int gmi_model_bind(gmi_t g, const gmi_model_desc* d, float* params, v
       off += gmi::align_up(bytes, 256);
       return p;
     };
-    // activation arrays hold a whole number of 256-row tiles: the register-chained trainer kernel stores
+    // activation arrays hold a whole number of 256-row tiles: the row-tile trainer kernel stores
     // (and loads) the ragged last tile without bounds checks; rows past the batch are never used
     const int64_t arows = (rows + 255) / 256 * 256;
     m->x0 = take(arows * gmi::pad32(L.obs_dim) * es);
@@ -429,7 +429,7 @@ extern "C" int gmi_model_bind(gmi_t g, const gmi_model_desc* d, float* params, v
     m->mb_adv = (float*)take(rows * 4);
     m->mb_ret = (float*)take(rows * 4);
     m->grad_part = (float*)take((int64_t)m->part_rows * L.part_floats * 4);
-    m->stat_part = (float*)take((int64_t)(gmi::kLossBlocksMax + 1) * (gmi::kStatStride + A) * 4);
+    m->stat_part = (float*)take((int64_t)(gmi::kStatRowsMax + 1) * (gmi::kStatStride + A) * 4);
     if (pass == 0) {
       m->ws_bytes = (size_t)off;
       hipError_t e = hipMalloc(&m->ws_base, m->ws_bytes);

@@ -22,10 +22,16 @@
 // epilogues' vector arithmetic.
 #include <algorithm>
 
-#include "chain_kernel.h"
+#include "chain_stream.h"
 
 namespace {
 using namespace gmi_chain;
+
+__device__ __forceinline__ float wave_sum64(float v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
@@ -617,7 +623,7 @@ int launch(gmi_instance* g, const ResArgs& a, int grid, size_t lds) {
 namespace gmi {
 
 bool resident_supported(const ModelLayout& L) { return shape_ok(L); }
-// Where a register-chained or row-tile kernel is compiled for the shape, this kernel is the faster one while every tile has a
+// Where a row-tile kernel is compiled for the shape, this kernel is the faster one while every tile has a
 // workgroup of its own (one per net and two of the instance's compute units; 128-row tiles with the gradients in registers,
 // else 64 or, where only those fit LDS, 32).  Per minibatch with Adam, us, this kernel / the compiled one:
 //   60:256:128:64:8 (128 rows): 34.7 / 45.5 at 1000 rows, 48.5 / 50.8 at 8192, 56.6 / 57.1 at 16384, 91.9 / 89.9 at 32768;

@@ -1,18 +1,19 @@
-// Row-tile trainer kernel for the wide model shapes (every hidden width a multiple of 128): minibatch gather,
+// Row-tile trainer kernel for the model shapes compiled in tile_p<k>.hip (hidden widths padded to multiples of 32): minibatch gather,
 // forward pass, clipped-surrogate / value loss and the whole input-gradient chain of one minibatch (stage (ii)
 // of Section 5.1 of the paper, the "DRL Trainer" role of Section 3) in one launch per minibatch.
 //
-// A workgroup of 8 waves owns 128 samples and keeps their current activations in LDS, as the second operands of
+// A workgroup owns 64 samples (4 waves, two workgroups per compute unit) or 128 (8 waves) and keeps their current activations in
+// LDS, as the second operands of
 // the 32x32x16 matrix instruction: block (k step ks, row tile rt) = 1 KiB, lane L of it = the 8 contraction
 // values of sample 32 rt + L % 32 that operand lane L takes.  Every product is computed transposed,
-// H^T = W X^T, and a wave owns a slice of the layer's OUTPUT FEATURES for all 128 samples (F / 256 feature tiles x
-// 4 row tiles, at most 8 accumulator tiles = 128 registers; layers of 4 feature tiles: two waves share one, half the rows
-// each): per k step it fetches its own weight blocks straight
-// from the second-level cache into registers (no other wave of the workgroup needs them) and the 4 activation
+// H^T = W X^T, and a wave owns a slice of the layer's OUTPUT FEATURES for all samples (8 accumulator tiles = 128 registers at
+// most; where there are fewer feature tiles than waves, two or four waves share one and split its rows): per k step it fetches its own
+// weight blocks straight
+// from the second-level cache into registers (no other wave of the workgroup needs them) and the activation
 // blocks from LDS, i.e. 6 KiB of operands for 8 matrix instructions.  (With a wave per 32 samples and the weights
 // in LDS every wave reads every weight block: 1 KiB of LDS traffic per matrix instruction, which is the LDS
-// bandwidth of a compute unit.)  The weights come from the chain stream of the register-chained kernel
-// (chain_kernel.h): its blocks are the first operands of exactly these products, its k order inside a 16-wide
+// bandwidth of a compute unit.)  The weights come from the weight stream (chain_stream.h): its blocks are the first operands of
+// exactly these products, its k order inside a 16-wide
 // step is the order in which the matrix instruction leaves its results in a lane, so a lane's 8 results of a
 // k step are written back to LDS as one 16-byte piece at its own lane's slot.
 //
@@ -20,32 +21,34 @@
 // the stored activation; conversion; the results into LDS in place of the layer's input; from there they go to memory
 // for the weight-gradient kernel) - barrier.  The next layer's first weight blocks are fetched before the epilogue.
 //
-// Two waves per SIMD, not one of 16 accumulator tiles: an epilogue is straight-line code that runs once, and one wave alone gets
-// its instructions at about a byte per cycle, half of what the vector unit takes; in the k loops one wave's fetches ride under the
-// other's products.  What bounds the walk now: the matrix unit in the k loops of 512 x 512 layers (17 of 19 thousand cycles), the
-// exponentials in the forward epilogues, and the activations and gradients on their way to memory and back (540 MB for 32768
-// samples: 110 us at the rate of a copy).  Forward + gradients of 32768 samples of 211:512:512:256:128:20, us: 220 with 4 waves,
-// 178 with 8.
+// Two waves per SIMD: an epilogue is straight-line code that runs once, and a wave gets its instructions at about a byte per cycle,
+// half of what the vector unit takes, so one wave alone is bound by them.  In the k loops one wave's fetches ride under the
+// other's products, and two workgroups of 64 samples have their barriers, epilogues, loss and start at different times.  What bounds
+// the walk now: instructions in the epilogues, and the activations and gradients on their way to memory and back (307 MB for 32768
+// samples of 108:400:200:100:21, 540 MB of 211:512:512:256:128:20: 63 and 110 us at the rate of a copy; the matrix unit 19 and 53).
+// Forward + loss + gradients of 32768 samples, us: 211:512:512:256:128:20 220 with 4 waves of 128 samples, 178 with 8;
+// 108:400:200:100:21 107 with a wave's activations in registers and the weights through LDS, 86 with 8 waves of 128 samples, 79 with 4
+// of 64; 60:256:128:64:8 44, 46 and 39.
 //
 // TileShapeFwd is the same walk cut after the heads (agent_act / agent_value of these models: Section 3, "DRL Agent"):
 // nothing is stored for the weight gradients and the heads' results go out as policy means and values.
 #pragma once
-#include "chain_kernel.h"
+#include "chain_stream.h"
 
 namespace gmi_tile {
 using namespace gmi_chain;
 
-constexpr int kRows = 128;        // samples per workgroup
-constexpr int kWaves = 8;
-constexpr int kLossWaves = kRows / 32;      // the loss and the heads are a row tile per wave: the first four
-constexpr int kRing = 8;          // weight blocks in flight per wave: 8 / (feature tiles per wave) k steps
+constexpr int kScrBytes = 32 * 33 * 4;      // a loss wave's transposition buffer
 constexpr int kHPre = 4;          // tiles whose stored activations are fetched ahead in an input-gradient epilogue
 
-template <int... DIMS>
+// ROWS: samples per workgroup, 128 (8 waves) or 64 (4 waves).
+template <int ROWS, int... DIMS>
 struct TileShape {
+  static constexpr int rows = ROWS, nrt = ROWS / 32, waves = 2 * nrt, threads = 64 * waves;
+  static constexpr int acc_ft = 16 / waves, ring = 8;      // feature tiles of a wave; weight blocks in flight per wave
   static constexpr bool fwd = false;      // TileShapeFwd: the forward pass alone (inference)
   static constexpr int NL = (int)sizeof...(DIMS) - 1;
-  static constexpr ChainDims dims() { return ChainDims{NL, 4, {DIMS...}}; }
+  static constexpr ChainDims dims() { return ChainDims{NL, {DIMS...}}; }
   static constexpr int nseg() { return cd_nseg(dims()); }
   static constexpr int maxks() { return cd_maxdim(dims()) / 16; }
   static constexpr int bias_total() {
@@ -63,22 +66,23 @@ struct TileShape {
     for (int i = 0; i < s; ++i) n += cd_seg_blocks(dims(), i);
     return n;
   }
-  static constexpr size_t x_bytes() { return (size_t)maxks() * 4 * 1024; }
-  static constexpr size_t lds_bytes() { return x_bytes() + (size_t)bias_total() * 4 + (size_t)(kLossWaves * 40 + 64) * 4; }
+  // the loss epilogue's per-wave transposition buffers live in the activation area behind the head layer's input
+  static constexpr size_t scr_offset() { return (size_t)dims().d[NL - 1] / 16 * nrt * 1024; }
+  static constexpr size_t x_bytes() { return (size_t)maxks() * nrt * 1024; }
+  static constexpr size_t lds_bytes() { return x_bytes() + (size_t)bias_total() * 4 + (size_t)(nrt * 40 + 64) * 4; }
   static constexpr bool valid() {
     const ChainDims D = dims();
-    if (D.d[NL] != 32 || D.d[0] % 16 != 0 || maxks() > 32) return false;
-    for (int l = 1; l < NL; ++l)
-      if (D.d[l] % 128 != 0) return false;
-    // the loss epilogue's per-wave transposition buffers live in the activation area behind the head layer's input
-    return x_bytes() >= 65536 + (size_t)kLossWaves * kScrBytes && D.d[NL - 1] / 16 * 4096 <= 65536;
+    if (D.d[NL] != 32 || maxks() > 32) return false;
+    for (int l = 0; l < NL; ++l)
+      if (D.d[l] % 32 != 0) return false;
+    return (ROWS == 64 || ROWS == 128) && x_bytes() >= scr_offset() + (size_t)nrt * kScrBytes;
   }
 };
 
 // The same shape for inference: the walk ends after the heads, nothing is stored for the weight gradients, and the
 // heads' results go out as policy means and values (the products and their order are the trainer's forward pass).
-template <int... DIMS>
-struct TileShapeFwd : TileShape<DIMS...> {
+template <int ROWS, int... DIMS>
+struct TileShapeFwd : TileShape<ROWS, DIMS...> {
   static constexpr bool fwd = true;
 };
 // Segments the kernel runs for shape S.
@@ -93,13 +97,15 @@ struct Seg {
   static constexpr bool bwd = SEG >= S::NL;
   static constexpr bool last = !S::fwd && SEG == S::nseg() - 1;
   static constexpr int layer = cd_layer(D, SEG);
-  // Waves over features, then over rows: wave w has the feature tiles (w % NWF) FTW .. and the row tiles (w / NWF) RT ..  The
-  // head is a row tile per wave, by both halves of the workgroup (the second half's results are dropped).
-  static constexpr int NWF = head ? 1 : (NFT < kWaves ? NFT : kWaves);
-  static constexpr int FTW = head ? 1 : NFT / NWF;        // feature tiles per wave
-  static constexpr int RT = head ? 1 : 4 / (kWaves / NWF);      // row tiles per wave
-  static constexpr int GS = NFT >= 4 ? 4 : NFT;           // tiles per group of the stream (chain_kernel.h)
-  static constexpr int DEP = kRing / FTW < NKS ? kRing / FTW : NKS;      // k steps of weight blocks in flight
+  // Waves over features, then over rows: a wave has FTW feature tiles (tile_of) and the row tiles (w / NWF) RT ..  One feature tile
+  // (the head) is a row tile per wave, by both halves of the workgroup (what the second half computes again is dropped).
+  static constexpr int NWF = NFT == 1 ? 1 : (NFT == 2 ? 2 : (NFT <= 4 ? 4 : S::waves));
+  static constexpr int FTW = (NFT + NWF - 1) / NWF;       // feature tiles per wave
+  static constexpr int RT = NFT == 1 ? 1 : S::nrt * NWF / S::waves;      // row tiles per wave
+  static constexpr bool even = NFT == NWF * FTW;          // every wave has FTW tiles of its own
+  static constexpr int GS = NFT >= 4 ? 4 : NFT;           // tiles per group of the stream (chain_stream.h) ..
+  static constexpr bool one_gs = NFT % 4 == 0 || NFT <= 2;      // .. if all its groups are alike
+  static constexpr int DEP = S::ring / FTW < NKS ? S::ring / FTW : NKS;      // k steps of weight blocks in flight
   static constexpr int XD = FTW >= 2 ? 1 : 2;             // k steps the activation blocks are read ahead (a k step of
                                                           // fewer products is shorter than an LDS round trip)
   static constexpr int blk0 = S::seg_blk0(SEG);
@@ -110,21 +116,52 @@ struct Seg {
   // segment (the gather stores its rows) nor the first input-gradient segment (the loss epilogue stores the head's).
   static constexpr int HK = NKS > 6 ? NKS - 6 : 0;        // k step at which an input-gradient segment starts to fetch ELU' inputs
   static constexpr bool store_x = !S::fwd && ((SEG >= 1 && SEG <= S::NL - 1) || SEG > S::NL);
-  static_assert(head || (NFT % NWF == 0 && kWaves % NWF == 0 && kWaves / NWF <= 4), "feature and row tiles divide over the waves");
   static_assert(!head || NFT == 1, "the head is one 32-wide tile");
+  static_assert(FTW <= S::acc_ft, "accumulators of a wave");
 };
+
+// The actions of one sample for a lane of the head: features 8 q + 4 hh .. + 3 for q = 0 .. 3, by 16-byte loads (4-byte aligned).  Every
+// lane of a load touches a cache line of its own and those take a cycle each, so it is the number of loads that counts: 16
+// single ones took a workgroup of train_tile_kernel 9 thousand cycles.  A load that would pass the row's end is moved
+// back to end there and its values shifted into place where they are used (lane_actions); with fewer than 4 actions it begins
+// in an earlier row, `back` elements before this one, but not before the array's start (the launch sees to 4 elements in all).
+__device__ __forceinline__ int actions_back(int64_t slot, int A) {
+  return A >= 4 ? 0 : (slot * A < 4 - A ? (int)(slot * A) : 4 - A);
+}
+__device__ __forceinline__ void fetch_actions(const float* act, int64_t slot, int A, int hh, float (&out)[16]) {
+  typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+  const int top = A >= 4 ? A - 4 : 0;
+  const float* row = act + slot * A - actions_back(slot, A);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int f0 = 8 * q + 4 * hh;
+    const float4u t = *reinterpret_cast<const float4u*>(row + (f0 < top ? f0 : top));
+    out[4 * q] = t.x; out[4 * q + 1] = t.y; out[4 * q + 2] = t.z; out[4 * q + 3] = t.w;
+  }
+}
+__device__ __forceinline__ void lane_actions(const float (&in)[16], int A, int back, int q, int hh, float (&out)[4]) {
+  const int f0 = 8 * q + 4 * hh;
+  const int sh = A >= 4 ? f0 - (A - 4) : back;               // how far back the load began (4 and more: no feature of A)
+  const float x0 = in[4 * q], x1 = in[4 * q + 1], x2 = in[4 * q + 2], x3 = in[4 * q + 3];
+  const float y = sh == 1 ? x1 : (sh == 2 ? x2 : x3), z = sh == 1 ? x2 : x3;
+  out[0] = sh <= 0 ? x0 : y;
+  out[1] = sh <= 0 ? x1 : z;
+  out[2] = sh <= 0 ? x2 : x3;
+  out[3] = x3;
+}
 
 template <class S>
 struct Ctx {
-  floatx16 acc[2][4];
-  uint4 wq[kRing];                   // weight blocks of k steps g .. g + DEP - 1: block (ks, a) at (ks % DEP) * FTW + a
-  uint4 xq[3][4];                    // activation blocks of k steps g .. g + XD (ring indexed by k step % 3)
+  floatx16 acc[S::acc_ft][S::nrt];
+  uint4 wq[S::ring];                   // weight blocks of k steps g .. g + DEP - 1: block (ks, a) at (ks % DEP) * FTW + a
+  uint4 xq[3][S::nrt];                    // activation blocks of k steps g .. g + XD (ring indexed by k step % 3)
   uint4 sx;                          // block of the activation area on its way to memory (store_x)
   uint4 hq[kHPre + 1][2];            // stored activations of the tiles ahead (input-gradient epilogues)
   const uint4* wnet;                 // this net's stream
   uint4* X;                          // activation area
   uint32_t lane16;                   // 16 lane
-  uint32_t xo[2];                    // this lane's byte offset in k steps 0 .. 15 and 16 .. 31 of the activation area
+  float log2e;                       // of e, in a scalar register
+  uint32_t xo[2];                    // this lane's byte offset in the first 64 KiB of the activation area and behind them
   const float* s_bias;
   float* s_red;
   char* scr;                         // this wave's transposition buffer (loss epilogue only)
@@ -133,37 +170,61 @@ struct Ctx {
   float l_act[16], l_lo, l_ad, l_rt;
   int tid, lane, wave, s, hh;
   int row0, net;                     // first row of the workgroup's tile
+  int tr, rt0;                       // 128-row tile of the stored arrays that it lies in, and its first row tile there
 };
 
+// Feature tile `a` of this wave: consecutive tiles where they divide evenly, else every NWF-th one, and beyond the last the last one
+// again (its results are written twice, the same).
 template <class G, class S>
-__device__ __forceinline__ int first_ft(const Ctx<S>& c) { return G::head ? 0 : (c.wave & (G::NWF - 1)) * G::FTW; }
+__device__ __forceinline__ int tile_of(const Ctx<S>& c, int a) {
+  if constexpr (G::NFT == 1) return 0;
+  const int w = c.wave & (G::NWF - 1);
+  if constexpr (G::even) return w * G::FTW + a;
+  const int ft = a * G::NWF + w;
+  return ft < G::NFT ? ft : G::NFT - 1;
+}
 template <class G, class S>
 __device__ __forceinline__ int first_rt(const Ctx<S>& c) {
-  if constexpr (G::head) return c.wave & 3;
-  else if constexpr (G::NWF == kWaves) return 0;
+  if constexpr (G::NFT == 1) return c.wave & (S::nrt - 1);
+  else if constexpr (G::NWF == S::waves) return 0;
   else return c.wave / G::NWF * G::RT;
 }
 
-// First weight block (bytes from the stream's start) of wave `wave` in segment SEG: its FTW tiles are consecutive tiles of one group of the stream.
+// Where the weight blocks of a wave's feature tiles begin in the stream and how far apart its k steps are, in bytes.
+struct WeightPos { int base[4], step[4]; };
 template <class S, int SEG>
-__device__ __forceinline__ int seg_weights(const Ctx<S>& c) {
+__device__ __forceinline__ WeightPos seg_weights(const Ctx<S>& c) {
   using G = Seg<S, SEG>;
-  const int ft0 = first_ft<G>(c);
-  return (G::blk0 + (ft0 / 4) * 4 * G::NKS + (ft0 % 4)) * 1024;
+  WeightPos p;
+#pragma unroll
+  for (int a = 0; a < G::FTW; ++a) {
+    const int ft = tile_of<G>(c, a);
+    int t0 = ft & ~3, gs = G::GS;                 // first tile and size of the tile's group: 4, .., 4, (2), (1)
+    if constexpr (!G::one_gs) {
+      const int left = G::NFT - t0;
+      if (left < 4) {
+        gs = left == 1 || ft - t0 == 2 ? 1 : 2;
+        if (ft - t0 == 2) t0 = ft;
+      }
+    }
+    p.base[a] = (G::blk0 + t0 * G::NKS + ft - t0) * 1024;
+    p.step[a] = gs * 1024;
+  }
+  return p;
 }
 // This lane's 16 bytes of block (ks, rt).  An LDS instruction's constant reaches 64 KiB: with one offset per half of the area every
 // block is a constant away.  (Left to itself the compiler forms an address per block of the upper half, keeps them from one segment
 // to the next and spills them: 47 registers, each reload in a k loop behind every fetch and store in flight.)
 template <class S>
 __device__ __forceinline__ uint4* x_block(const Ctx<S>& c, int ks, int rt) {
-  return reinterpret_cast<uint4*>(reinterpret_cast<char*>(c.X) + c.xo[ks / 16] + rt * 1024) + (ks % 16) * 256;
+  return reinterpret_cast<uint4*>(reinterpret_cast<char*>(c.X) + c.xo[ks * S::nrt / 64] + rt * 1024) + (ks * S::nrt % 64) * 64;
 }
 template <class S, int SEG, int KS>
-__device__ __forceinline__ uint4 weight_block(const Ctx<S>& c, int wseg, int ta) {
-  return gmi::load_uniform(c.wnet, wseg + (KS * Seg<S, SEG>::GS + ta) * 1024, c.lane16);
+__device__ __forceinline__ uint4 weight_block(const Ctx<S>& c, const WeightPos& w, int ta) {
+  return gmi::load_uniform(c.wnet, w.base[ta] + KS * w.step[ta], c.lane16);
 }
 template <class S, int SEG, int KS>
-__device__ __forceinline__ void issue_weights(Ctx<S>& c, int wseg) {
+__device__ __forceinline__ void issue_weights(Ctx<S>& c, const WeightPos& wseg) {
   using G = Seg<S, SEG>;
   if constexpr (KS < G::NKS) {
 #pragma unroll
@@ -198,7 +259,7 @@ __device__ __forceinline__ void read_x(Ctx<S>& c) {
 __device__ __forceinline__ int64_t block_word(int tr, int nks, int ks, int rt) { return (((int64_t)tr * nks + ks) * 4 + rt) * 64; }
 
 // One block to memory for the weight-gradient kernel.
-__device__ __forceinline__ void store_block(uint4* blk, uint32_t lane16, const uint4& v) { gmi::store_through(blk, lane16, v); }
+__device__ __forceinline__ void store_block(uint4* blk, uint32_t lane16, const uint4& v, int off = 0) { gmi::store_through(blk, lane16, v, off); }
 
 // Stored activations h[layer] of tile T = a * RT + b of this wave (input-gradient epilogue of segment SEG): the
 // lane's own slots of the blocks (2 ft, b) and (2 ft + 1, b), i.e. the values at the positions of its 16 results.
@@ -208,8 +269,8 @@ __device__ __forceinline__ void fetch_h(Ctx<S>& c, const ChainArgs& a) {
   if constexpr (G::bwd && T < G::FTW * G::RT) {
     constexpr int ta = T / G::RT, tb = T % G::RT;
     constexpr int nks = G::D.d[G::layer] / 16;
-    const int ft = first_ft<G>(c) + ta;
-    const uint4* p = reinterpret_cast<const uint4*>(a.h[c.net][G::layer]) + block_word(blockIdx.x, nks, 2 * ft, first_rt<G>(c) + tb);
+    const int ft = tile_of<G>(c, ta);
+    const uint4* p = reinterpret_cast<const uint4*>(a.h[c.net][G::layer]) + block_word(c.tr, nks, 2 * ft, c.rt0 + first_rt<G>(c) + tb);
     c.hq[T % (kHPre + 1)][0] = gmi::load_uniform(p, 0, c.lane16);
     c.hq[T % (kHPre + 1)][1] = gmi::load_uniform(p, 4 * 1024, c.lane16);
   }
@@ -241,9 +302,10 @@ __device__ __forceinline__ void aux_op(Ctx<S>& c, const ChainArgs& a) {
   } else if constexpr (G::store_x) {
     static_assert(G::NKS % 2 == 0, "a wave moves a block every two k steps");
     if constexpr (I == G::RT) {
-      if constexpr (KS % 2 == 0) c.sx = *x_block(c, KS, c.wave);      // waves 4 .. 7: row tiles 0 .. 3 of k step KS + 1
+      if constexpr (KS % 2 == 0) c.sx = *x_block(c, KS, c.wave);      // the second half of the waves: k step KS + 1
     } else if constexpr (KS % 2 == 1) {
-      store_block(store_x_array<S, SEG>(c, a) + block_word(blockIdx.x, G::NKS, KS - 1, c.wave), c.lane16, c.sx);      // arrays hold whole tiles
+      store_block(store_x_array<S, SEG>(c, a) + block_word(c.tr, G::NKS, c.wave / S::nrt, c.rt0 + c.wave % S::nrt), c.lane16, c.sx,
+                  (KS - 1) * 4096);      // arrays hold whole tiles
     }
   }
 }
@@ -262,7 +324,7 @@ __device__ __forceinline__ void aux_slot(Ctx<S>& c, const ChainArgs& a) {
 // idle meanwhile (measured: ~100-170 of a k step's 256 / 512 cycles), one or two of them after every product do not.
 // The next weight block of feature tile a follows the last product that reads the present one.
 template <class S, int SEG, int KS, int M>
-__device__ __forceinline__ void k_products(Ctx<S>& c, const ChainArgs& a, int wseg) {
+__device__ __forceinline__ void k_products(Ctx<S>& c, const ChainArgs& a, const WeightPos& wseg) {
   using G = Seg<S, SEG>;
   if constexpr (M < G::FTW * G::RT) {
     constexpr int ta = M / G::RT, tb = M % G::RT;
@@ -286,7 +348,7 @@ __device__ __forceinline__ void k_products(Ctx<S>& c, const ChainArgs& a, int ws
 }
 
 template <class S, int SEG, int KS>
-__device__ __forceinline__ void k_steps(Ctx<S>& c, const ChainArgs& a, int wseg) {
+__device__ __forceinline__ void k_steps(Ctx<S>& c, const ChainArgs& a, const WeightPos& wseg) {
   using G = Seg<S, SEG>;
   if constexpr (KS < G::NKS) {
     if constexpr (G::bwd && KS == G::HK) {          // the first tiles' stored activations, late enough not to hold up
@@ -297,13 +359,23 @@ __device__ __forceinline__ void k_steps(Ctx<S>& c, const ChainArgs& a, int wseg)
   }
 }
 
+// elu_f (chain_stream.h) in 24 bytes of code instead of 32: an epilogue runs at the rate at which instructions come.  The factor from
+// a scalar register, and the maximum without the compiler's canonicalisation of z (an instruction; z is a matrix
+// product's result).  The maximum's operands depend on the product z * log2e, so z has left the matrix unit.
+__device__ __forceinline__ float tile_elu(float z, float log2e) {
+  const float e = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(z * log2e), 0.f, 1.f) - 1.0f;
+  float y;
+  asm("v_max_f32 %0, %1, %2" : "=v"(y) : "v"(z), "v"(e));
+  return y;
+}
+
 // Epilogue of tile T of a hidden forward layer or of an input-gradient layer.
 template <class S, int SEG, int T>
 __device__ __forceinline__ void tile_epilogue(Ctx<S>& c, const ChainArgs& a) {
   using G = Seg<S, SEG>;
   if constexpr (T < G::FTW * G::RT) {
     constexpr int ta = T / G::RT, tb = T % G::RT;
-    const int ft = first_ft<G>(c) + ta, rt = first_rt<G>(c) + tb;
+    const int ft = tile_of<G>(c, ta), rt = first_rt<G>(c) + tb;
     fetch_h<S, SEG, T + kHPre>(c, a);
     const floatx16& acc = c.acc[ta][tb];
     uint32_t w[8];
@@ -316,14 +388,15 @@ __device__ __forceinline__ void tile_epilogue(Ctx<S>& c, const ChainArgs& a) {
         v0 *= elu_grad_f(bf16_lo(h01)); v1 *= elu_grad_f(bf16_hi(h01));
         v2 *= elu_grad_f(bf16_lo(h23)); v3 *= elu_grad_f(bf16_hi(h23));
       } else {
-        v0 = elu_f(v0); v1 = elu_f(v1); v2 = elu_f(v2); v3 = elu_f(v3);      // the bias is in the sums already
+        v0 = tile_elu(v0, c.log2e); v1 = tile_elu(v1, c.log2e);
+        v2 = tile_elu(v2, c.log2e); v3 = tile_elu(v3, c.log2e);      // the bias is in the sums already
       }
       w[2 * q] = pack_bf16(v0, v1);
       w[2 * q + 1] = pack_bf16(v2, v3);
     }
-    uint4* x = c.X + ((2 * ft) * 4 + rt) * 64 + c.lane;
+    uint4* x = c.X + ((2 * ft) * S::nrt + rt) * 64 + c.lane;
     x[0] = make_uint4(w[0], w[1], w[2], w[3]);
-    x[256] = make_uint4(w[4], w[5], w[6], w[7]);
+    x[S::nrt * 64] = make_uint4(w[4], w[5], w[6], w[7]);
     tile_epilogue<S, SEG, T + 1>(c, a);
   }
 }
@@ -337,6 +410,18 @@ __device__ __forceinline__ void fetch_loss_inputs(Ctx<S>& c, const ChainArgs& a)
   fetch_actions(a.b_act, c.slot, a.act_dim, c.hh, c.l_act);
 }
 
+// Sum over the wave, in lane 63.
+__device__ __forceinline__ float sum_to_last(float v) {
+  auto add = [&](auto ctrl) { v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), decltype(ctrl)::value, 0xF, 0xF, true)); };
+  add(std::integral_constant<int, 0x111>{});      // the lanes of a row of 16, one, two, four and eight up
+  add(std::integral_constant<int, 0x112>{});
+  add(std::integral_constant<int, 0x114>{});
+  add(std::integral_constant<int, 0x118>{});
+  add(std::integral_constant<int, 0x142>{});      // a row's last lane to the next row
+  add(std::integral_constant<int, 0x143>{});      // lane 31 to the upper half
+  return v;
+}
+
 // Loss on the wave's 32 samples (row tile `wave` of the workgroup) from the head's accumulators: lane = sample s,
 // half hh; register i = feature 8 (i / 4) + 4 hh + i % 4.  Leaves the head gradient as the two k steps of the first
 // input-gradient product in the activation area and, as the same blocks, in dz[NL - 1], and the workgroup's
@@ -345,7 +430,7 @@ template <class S>
 __device__ __forceinline__ void loss_epilogue(Ctx<S>& c, const ChainArgs& a, const floatx16& acc) {
   constexpr int HB = S::bias_off(S::NL - 1);
   const int A = a.act_dim;
-  if (c.wave < kLossWaves) {
+  if (c.wave < S::nrt) {
   const int wrow0 = c.row0 + 32 * c.wave;
   const int row = wrow0 + c.s;
   const bool ok = row < a.rows;
@@ -353,11 +438,14 @@ __device__ __forceinline__ void loss_epilogue(Ctx<S>& c, const ChainArgs& a, con
   float d[16];
   float* red = c.s_red + c.wave * 40;
   if (c.net == 0) {
-    const float* s_ls = c.s_red + kLossWaves * 40;      // [f] log_std, [32 + f] exp(-log_std) (0 for f >= A)
+    const float* s_ls = c.s_red + S::nrt * 40;      // [f] log_std, [32 + f] exp(-log_std) (0 for f >= A)
     float z[16], isg[16];
     float lp = 0.f;
 #pragma unroll
+    for (int i = 0; i < 16; ++i) d[i] = 0.f;
+#pragma unroll
     for (int q = 0; q < 4; ++q) {
+      if (8 * q >= A) break;                         // no action among these eight features
       const int f0 = 8 * q + 4 * c.hh;
       const float4 ls4 = *reinterpret_cast<const float4*>(s_ls + f0);
       const float4 ig4 = *reinterpret_cast<const float4*>(s_ls + 32 + f0);
@@ -390,22 +478,25 @@ __device__ __forceinline__ void loss_epilogue(Ctx<S>& c, const ChainArgs& a, con
       }
     }
     // log_std gradient partials g_lp (z^2 - 1): transposed through the wave's buffer as [feature][sample] fp32,
-    // then lane f < 32 sums feature f's 32 samples in a fixed order
+    // then lane (f, half) sums 16 samples of feature f in a fixed order
     float* tp = reinterpret_cast<float*>(c.scr);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int f = 8 * (i >> 2) + 4 * c.hh + (i & 3);
-      d[i] = g_lp * z[i] * isg[i];
-      tp[f * 33 + c.s] = g_lp * (z[i] * z[i] - 1.0f);
-    }
-    if (c.lane < 32) {
-      float sum = 0.f;
+    for (int q = 0; q < 4; ++q) {
+      if (8 * q >= A) break;
 #pragma unroll
-      for (int k = 0; k < 32; ++k) sum += tp[c.lane * 33 + k];
-      red[8 + c.lane] = c.lane < A ? sum : 0.f;
+      for (int e = 0; e < 4; ++e) {
+        const int i = 4 * q + e, f = 8 * q + 4 * c.hh + e;
+        d[i] = g_lp * z[i] * isg[i];
+        tp[f * 33 + c.s] = g_lp * (z[i] * z[i] - 1.0f);
+      }
     }
-    s_pl = wave_sum64(s_pl); s_kl = wave_sum64(s_kl); s_cf = wave_sum64(s_cf);
-    if (c.lane == 0) { red[0] = s_pl; red[1] = s_kl; red[2] = s_cf; }
+    float sum = 0.f;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) sum += tp[c.s * 33 + 16 * c.hh + k];
+    sum += __shfl_xor(sum, 32, 64);
+    if (c.lane < A) red[8 + c.lane] = sum;
+    s_pl = sum_to_last(s_pl); s_kl = sum_to_last(s_kl); s_cf = sum_to_last(s_cf);
+    if (c.lane == 63) { red[0] = s_pl; red[1] = s_kl; red[2] = s_cf; }
   } else {
     float s_vl = 0.f;
 #pragma unroll
@@ -415,45 +506,49 @@ __device__ __forceinline__ void loss_epilogue(Ctx<S>& c, const ChainArgs& a, con
       s_vl = dv * dv;
       d[0] = 2.0f * a.c_v * dv * inv_m;
     }
-    s_vl = wave_sum64(s_vl);
-    if (c.lane == 0) red[0] = s_vl;
+    s_vl = sum_to_last(s_vl);
+    if (c.lane == 63) red[0] = s_vl;
   }
   uint32_t w[8];
 #pragma unroll
   for (int q = 0; q < 8; ++q) w[q] = pack_bf16(d[2 * q], d[2 * q + 1]);
-  c.X[(0 * 4 + c.wave) * 64 + c.lane] = make_uint4(w[0], w[1], w[2], w[3]);
-  c.X[(1 * 4 + c.wave) * 64 + c.lane] = make_uint4(w[4], w[5], w[6], w[7]);
+  c.X[(0 * S::nrt + c.wave) * 64 + c.lane] = make_uint4(w[0], w[1], w[2], w[3]);
+  c.X[(1 * S::nrt + c.wave) * 64 + c.lane] = make_uint4(w[4], w[5], w[6], w[7]);
   {
     uint4* arr = reinterpret_cast<uint4*>(a.dz[c.net][S::NL - 1]);
-    store_block(arr + block_word(blockIdx.x, 2, 0, c.wave), c.lane16, make_uint4(w[0], w[1], w[2], w[3]));      // arrays hold whole tiles
-    store_block(arr + block_word(blockIdx.x, 2, 1, c.wave), c.lane16, make_uint4(w[4], w[5], w[6], w[7]));
+    store_block(arr + block_word(c.tr, 2, 0, c.rt0 + c.wave), c.lane16, make_uint4(w[0], w[1], w[2], w[3]));      // arrays hold whole tiles
+    store_block(arr + block_word(c.tr, 2, 1, c.rt0 + c.wave), c.lane16, make_uint4(w[4], w[5], w[6], w[7]));
   }
   }
-  // workgroup sums -> this tile's row of the statistics partials
-  __syncthreads();
+}
+
+// The workgroup's sums -> its row of the statistics partials.
+template <class S>
+__device__ __forceinline__ void loss_sums(const Ctx<S>& c, const ChainArgs& a) {
+  const int A = a.act_dim;
   float* out = a.stat_part + (int64_t)blockIdx.x * (gmi::kStatStride + A);
   if (c.net == 0) {
     if (c.tid < 3) {
       float v = 0.f;
-      for (int wv = 0; wv < kLossWaves; ++wv) v += c.s_red[wv * 40 + c.tid];
+      for (int wv = 0; wv < S::nrt; ++wv) v += c.s_red[wv * 40 + c.tid];
       out[c.tid == 0 ? 0 : (c.tid == 1 ? 3 : 4)] = v;
     }
     if (c.tid == 3) {
       float ent = 0.f;
       if (blockIdx.x == 0)
-        for (int j = 0; j < A; ++j) ent += a.log_std[j] + 1.418938533204672742f;
+        for (int j = 0; j < A; ++j) ent += c.s_red[S::nrt * 40 + j] + 1.418938533204672742f;
       out[2] = ent;
       out[5] = out[6] = out[7] = 0.f;
     }
     if (c.tid >= 64 && c.tid < 64 + A) {
       const int j = c.tid - 64;
       float v = 0.f;
-      for (int wv = 0; wv < kLossWaves; ++wv) v += c.s_red[wv * 40 + 8 + j];
+      for (int wv = 0; wv < S::nrt; ++wv) v += c.s_red[wv * 40 + 8 + j];
       out[gmi::kStatStride + j] = v;
     }
   } else if (c.tid == 0) {
     float v = 0.f;
-    for (int wv = 0; wv < kLossWaves; ++wv) v += c.s_red[wv * 40];
+    for (int wv = 0; wv < S::nrt; ++wv) v += c.s_red[wv * 40];
     out[1] = v;
   }
 }
@@ -464,7 +559,7 @@ template <class S>
 __device__ __forceinline__ void head_outputs(Ctx<S>& c, const ChainArgs& a, const floatx16& acc) {
   constexpr int HB = S::bias_off(S::NL - 1);
   const int row = c.row0 + 32 * c.wave + c.s;
-  if (row >= a.rows || c.wave >= kLossWaves) return;
+  if (row >= a.rows || c.wave >= S::nrt) return;
   if (c.net == 0) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -480,13 +575,13 @@ template <class S, int SEG>
 __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
   if constexpr (SEG < n_run<S>()) {
     using G = Seg<S, SEG>;
-    const int wseg = seg_weights<S, SEG>(c);
+    const WeightPos wseg = seg_weights<S, SEG>(c);
     if constexpr (!G::bwd && !G::head) {
       // the accumulators start at the bias (register i of a lane = feature 8 (i / 4) + 4 hh + i % 4 of the tile)
       constexpr int boff = S::bias_off(G::layer);
 #pragma unroll
       for (int ta = 0; ta < G::FTW; ++ta) {
-        const float* bp = c.s_bias + boff + 32 * (first_ft<G>(c) + ta) + 4 * c.hh;
+        const float* bp = c.s_bias + boff + 32 * tile_of<G>(c, ta) + 4 * c.hh;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const float4 b4 = *reinterpret_cast<const float4*>(bp + 8 * q);
@@ -521,13 +616,14 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
       tile_epilogue<S, SEG, 0>(c, a);
     }
     __syncthreads();
+    if constexpr (G::head && !S::fwd) loss_sums<S>(c, a);
     if constexpr (G::last) {
       // nothing consumes the last results on chip: the activation area goes to dz[layer - 1] block by block, the way a k
       // loop moves its input
-      uint4* arr = reinterpret_cast<uint4*>(a.dz[c.net][G::layer - 1]);
+      uint4* arr = reinterpret_cast<uint4*>(a.dz[c.net][G::layer - 1]) + block_word(c.tr, G::F / 16, c.wave / S::nrt, c.rt0 + c.wave % S::nrt);
 #pragma unroll 8
       for (int k2 = 0; k2 < G::F / 16; k2 += 2) {
-        store_block(arr + block_word(blockIdx.x, G::F / 16, k2, c.wave), c.lane16, c.X[(k2 * 4 + c.wave) * 64 + c.lane]);      // arrays hold whole tiles
+        store_block(arr, c.lane16, c.X[(k2 * S::nrt + c.wave) * 64 + c.lane], k2 * 4096);      // arrays hold whole tiles
       }
     }
     run_segment<S, SEG + 1>(c, a);
@@ -535,7 +631,7 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
 }
 
 template <class S>
-__global__ __launch_bounds__(kWaves * 64) void train_tile_kernel(ChainArgs a) {
+__global__ __launch_bounds__(S::threads, 2) void train_tile_kernel(ChainArgs a) {
   static_assert(S::valid(), "shape not supported by the row-tile trainer kernel");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   constexpr ChainDims D = S::dims();
@@ -546,45 +642,49 @@ __global__ __launch_bounds__(kWaves * 64) void train_tile_kernel(ChainArgs a) {
   c.s = c.lane & 31;
   c.hh = c.lane >> 5;
   c.net = S::fwd ? (int)blockIdx.y + a.net0 : (int)blockIdx.y;
-  c.row0 = blockIdx.x * kRows;
+  c.row0 = blockIdx.x * S::rows;
+  c.tr = c.row0 / 128;
+  c.rt0 = c.row0 / 32 & 3;
   c.X = reinterpret_cast<uint4*>(smem_raw);
   c.lane16 = c.lane * 16;
+  c.log2e = 1.44269504f;
+  asm("" : "+s"(c.log2e));
   c.xo[0] = c.lane16;
   c.xo[1] = c.lane16 + 65536;
   asm volatile("" : "+v"(c.xo[1]));
   float* s_bias = reinterpret_cast<float*>(smem_raw + S::x_bytes());
   c.s_bias = s_bias;
   c.s_red = s_bias + S::bias_total();
-  c.scr = reinterpret_cast<char*>(smem_raw) + 65536 + (c.wave & 3) * kScrBytes;
+  c.scr = reinterpret_cast<char*>(smem_raw) + S::scr_offset() + (c.wave & (S::nrt - 1)) * kScrBytes;
   c.wnet = reinterpret_cast<const uint4*>(a.wstream[c.net]);
 
   // Everything a workgroup starts from is requested before anything is waited for, in the order in which it is needed: the memory
   // counter is in order.  (Indices, biases and scales loaded and stored one after another behind the first weights: 17 thousand
   // cycles up to the first product, of 170.)
-  constexpr int NG = kRows / 16 / kWaves;
+  constexpr int NG = S::rows / 16 / S::waves;
   const int rr = c.lane & 15, jj = c.lane >> 4;
   int sm[NG], srow[NG], hrow = 0, hsm = 0;
   const void* ixp = a.idx ? (const void*)a.idx : (const void*)a.log_std;      // no index: rows in order
   const auto ix = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(ixp), 0, 0xFFFFFFFFu, 0x00020000);
 #pragma unroll
   for (int gi = 0; gi < NG; ++gi) {
-    const int row = c.row0 + 16 * (c.wave + kWaves * gi) + rr;
+    const int row = c.row0 + 16 * (c.wave + S::waves * gi) + rr;
     srow[gi] = row < a.rows ? row : a.rows - 1;
     sm[gi] = __builtin_amdgcn_raw_buffer_load_b32(ix, a.idx ? srow[gi] * 4 : 0, 0, 0);
   }
   if constexpr (!S::fwd) {
     // this lane's sample of the head layer (rows past the batch take the last sample, the waves without a part in the loss one
     // sample for all lanes; their results are dropped)
-    const int row = c.row0 + (c.wave < kLossWaves ? 32 * c.wave + c.s : 0);
+    const int row = c.row0 + (c.wave < S::nrt ? 32 * c.wave + c.s : 0);
     hrow = row < a.rows ? row : a.rows - 1;
     hsm = __builtin_amdgcn_raw_buffer_load_b32(ix, a.idx ? hrow * 4 : 0, 0, 0);
   }
-  float bv[S::NL][S::maxks() * 16 / (kWaves * 64)];
+  float bv[S::NL][(S::maxks() * 16 + S::waves * 64 - 1) / (S::waves * 64)];
 #pragma unroll
   for (int l = 0; l < S::NL; ++l)
 #pragma unroll
-    for (int i = 0; i * kWaves * 64 < D.d[l + 1]; ++i) {
-      const int f = c.tid + i * kWaves * 64;
+    for (int i = 0; i * S::waves * 64 < D.d[l + 1]; ++i) {
+      const int f = c.tid + i * S::waves * 64;
       bv[l][i] = a.bias[c.net][l][f < D.d[l + 1] ? f : D.d[l + 1] - 1];
     }
   const float ls = a.log_std[c.tid < a.act_dim ? c.tid : a.act_dim - 1];
@@ -603,7 +703,7 @@ __global__ __launch_bounds__(kWaves * 64) void train_tile_kernel(ChainArgs a) {
     if (a.x0_ready != 0) {                               // workgroup-uniform; no branch around a single load
 #pragma unroll
       for (int gi = 0; gi < NG; ++gi) {
-        const int row = c.row0 + 16 * (c.wave + kWaves * gi) + rr;
+        const int row = c.row0 + 16 * (c.wave + S::waves * gi) + rr;
         const uint16_t* src = a.x0_ready == 1 ? a.x0 + (int64_t)row * D.d[0] : a.x16 + (int64_t)sm[gi] * D.d[0];
 #pragma unroll
         for (int it = 0; it < NI; ++it) {
@@ -638,33 +738,33 @@ __global__ __launch_bounds__(kWaves * 64) void train_tile_kernel(ChainArgs a) {
 #pragma unroll
       for (int l = 0; l < S::NL; ++l) {
 #pragma unroll
-        for (int i = 0; i * kWaves * 64 < D.d[l + 1]; ++i) {
-          const int f = c.tid + i * kWaves * 64;
+        for (int i = 0; i * S::waves * 64 < D.d[l + 1]; ++i) {
+          const int f = c.tid + i * S::waves * 64;
           if (f < D.d[l + 1]) s_bias[off + f] = bv[l][i];
         }
         off += D.d[l + 1];
       }
-      if (c.tid < kLossWaves * 40) c.s_red[c.tid] = 0.f;
+      if (c.tid < S::nrt * 40) c.s_red[c.tid] = 0.f;
       if (c.tid < 32) {                      // per-feature constants of the Gaussian log-prob (policy net)
-        c.s_red[kLossWaves * 40 + c.tid] = ls;
-        c.s_red[kLossWaves * 40 + 32 + c.tid] = c.tid < a.act_dim ? expf(-ls) : 0.f;
+        c.s_red[S::nrt * 40 + c.tid] = ls;
+        c.s_red[S::nrt * 40 + 32 + c.tid] = c.tid < a.act_dim ? expf(-ls) : 0.f;
       }
       if constexpr (!S::fwd) {
         hsm = a.idx ? hsm : hrow;
         c.slot = (int64_t)(hsm / a.n_envs) * a.ld_envs + (hsm % a.n_envs);
       }
     }
-    uint4* xb = reinterpret_cast<uint4*>(a.x0b) + block_word(blockIdx.x, D.d[0] / 16, 0, 0);
+    uint4* xb = reinterpret_cast<uint4*>(a.x0b) + block_word(c.tr, D.d[0] / 16, 0, c.rt0);
 #pragma unroll
     for (int gi = 0; gi < NG; ++gi) {
-      const int r = 16 * (c.wave + kWaves * gi) + rr;
+      const int r = 16 * (c.wave + S::waves * gi) + rr;
 #pragma unroll
       for (int it = 0; it < NI; ++it) {
         const int j = 4 * it + jj;
         if (j < NP) {
-          const int w = ((j >> 1) * 4 + (r >> 5)) * 64 + (r & 31) + 32 * (j & 1);
-          c.X[w] = v[gi][it];
-          if (!S::fwd && c.net == 0) xb[w] = v[gi][it];      // arrays hold whole tiles
+          const int w = (r >> 5) * 64 + (r & 31) + 32 * (j & 1);
+          c.X[(j >> 1) * S::nrt * 64 + w] = v[gi][it];
+          if (!S::fwd && c.net == 0) xb[(j >> 1) * 256 + w] = v[gi][it];      // arrays hold whole tiles
         }
       }
     }
@@ -683,19 +783,28 @@ bool shape_matches(const ModelLayout& L) {
   return true;
 }
 
+// The widest shapes: 128 samples per workgroup, which read the weights half as often, where such workgroups fill the compute units
+// (one each) evenly; else 64, of which two share a compute unit.  A minibatch of 211:512:512:256:128:20 with its weight gradients
+// and update, us, 64 / 128: 6000 rows 90 / 100, 8192 100 / 105, 12288 134 / 127, 16384 168 / 162, 20000 211 / 228, 24576 239 / 252, 32768
+// 322 / 317, 40960 384 / 393, 65536 574 / 575; on 64 compute units 2048 rows 133 / 147, 4096 173 / 167, 6144 215 / 230, 8192 256 / 249.
+inline bool wide_rows(int rows, int cus) {
+  const int n = 2 * ((rows + 127) / 128), last = (n - 1) % cus + 1;      // workgroups, of the last round
+  return n <= cus ? 4 * last >= 3 * cus : 16 * last >= 15 * cus;
+}
+
 template <class S>
 int launch_shape(gmi_instance* g, const ChainArgs& a, int rows, int* tiles_out, double flops, double bytes) {
   static gmi::DeviceSet allowed;
   const size_t lds = S::lds_bytes();
-  const int tiles = (rows + kRows - 1) / kRows;
+  const int tiles = (rows + S::rows - 1) / S::rows;
   *tiles_out = tiles;
-  if (!S::fwd && tiles > gmi::kLossBlocksMax) return GMI_ERR_UNSUPPORTED;      // one statistics row per tile
+  if (!S::fwd && tiles > gmi::kStatRowsMax) return GMI_ERR_UNSUPPORTED;      // one statistics row per tile
   if (a.x0_ready == 0 && (a.obs_dim % 4 != 0 || a.obs_dim < 4)) return GMI_ERR_UNSUPPORTED;
   const int rc = gmi::allow_lds((const void*)train_tile_kernel<S>, lds, g->device, &allowed);
   if (rc != GMI_OK) return rc;
   gmi::ProfScope ps(g, S::fwd ? gmi::kClsFusedAgent : gmi::kClsChainTrain);
   ps.work(flops, bytes);
-  ps.launch(train_tile_kernel<S>, dim3(tiles, S::fwd ? 2 - a.net0 : 2), dim3(kWaves * 64), lds, a);
+  ps.launch(train_tile_kernel<S>, dim3(tiles, S::fwd ? 2 - a.net0 : 2), dim3(S::waves * 64), lds, a);
   GMI_LAUNCH_CHECK();
   return GMI_OK;
 }
@@ -703,31 +812,40 @@ int launch_shape(gmi_instance* g, const ChainArgs& a, int rows, int* tiles_out, 
 }  // namespace gmi_tile
 
 namespace gmi {
-// One function per shape compiled for the row-tile kernel (tile_p<k>.hip), with the contract of the chained kernel's
-// parts (chain_kernel.h): GMI_ERR_UNSUPPORTED if the model has another shape; rows == 0 only asks (the answer: the
-// stream's group size 4, plus 256 for the gather from the bf16 copy of all observations).
-constexpr int kTileParts = 2;
+// One function per shape compiled for the row-tile kernel (trainers tile_p<k>.hip, forward-only kernels tile_f<k>.hip): launches it if
+// the model has exactly that shape, GMI_ERR_UNSUPPORTED otherwise; rows == 0 only asks.
+constexpr int kTileParts = 6;
 constexpr int kTileFwdParts = 2;
 #define GMI_TILE_PART_DECL(k)                                                                              \
   int launch_tile_part##k(gmi_instance* g, const ModelLayout& L, const gmi_chain::ChainArgs& a, int rows, \
                           int* tiles_out, double flops, double bytes)
-GMI_TILE_PART_DECL(0); GMI_TILE_PART_DECL(1);
+GMI_TILE_PART_DECL(0); GMI_TILE_PART_DECL(1); GMI_TILE_PART_DECL(2); GMI_TILE_PART_DECL(3); GMI_TILE_PART_DECL(4); GMI_TILE_PART_DECL(5);
 #define GMI_TILE_FWD_PART_DECL(k)                                                                              \
   int launch_tile_fwd_part##k(gmi_instance* g, const ModelLayout& L, const gmi_chain::ChainArgs& a, int rows, \
                               int* tiles_out, double flops, double bytes)
 GMI_TILE_FWD_PART_DECL(0); GMI_TILE_FWD_PART_DECL(1);
 #define GMI_TILE_FWD_PART_DEFINE(k, ...)                                                          \
   GMI_TILE_FWD_PART_DECL(k) {                                                                     \
-    using S = gmi_tile::TileShapeFwd<__VA_ARGS__>;                                                \
+    using S = gmi_tile::TileShapeFwd<64, __VA_ARGS__>;                                            \
     if (!gmi_tile::shape_matches<S>(L)) return GMI_ERR_UNSUPPORTED;                               \
-    if (rows == 0) { *tiles_out = 4; return GMI_OK; }                                             \
+    if (rows == 0) return GMI_OK;                                                                 \
     return gmi_tile::launch_shape<S>(g, a, rows, tiles_out, flops, bytes);                        \
   }
 #define GMI_TILE_PART_DEFINE(k, ...)                                                              \
   GMI_TILE_PART_DECL(k) {                                                                         \
-    using S = gmi_tile::TileShape<__VA_ARGS__>;                                                   \
+    using S = gmi_tile::TileShape<64, __VA_ARGS__>;                                               \
     if (!gmi_tile::shape_matches<S>(L)) return GMI_ERR_UNSUPPORTED;                               \
-    if (rows == 0) { *tiles_out = 4 | 256; return GMI_OK; }                                       \
+    if (rows == 0) return GMI_OK;                                                                 \
+    return gmi_tile::launch_shape<S>(g, a, rows, tiles_out, flops, bytes);                        \
+  }
+#define GMI_TILE_WIDE_PART_DEFINE(k, ...)                                                         \
+  GMI_TILE_PART_DECL(k) {                                                                         \
+    using S = gmi_tile::TileShape<64, __VA_ARGS__>;                                               \
+    using W = gmi_tile::TileShape<128, __VA_ARGS__>;                                              \
+    if (!gmi_tile::shape_matches<S>(L)) return GMI_ERR_UNSUPPORTED;                               \
+    if (rows == 0) return GMI_OK;                                                                 \
+    if (gmi_tile::wide_rows(rows, g->cu_count))                                                   \
+      return gmi_tile::launch_shape<W>(g, a, rows, tiles_out, flops, bytes);                      \
     return gmi_tile::launch_shape<S>(g, a, rows, tiles_out, flops, bytes);                        \
   }
 }  // namespace gmi

@@ -3,5 +3,5 @@
 #include "tile_kernel.h"
 
 namespace gmi {
-GMI_TILE_PART_DEFINE(1, 224, 512, 512, 512, 256, 32)
+GMI_TILE_WIDE_PART_DEFINE(1, 224, 512, 512, 512, 256, 32)
 }  // namespace gmi

@@ -536,8 +536,10 @@ int minibatch_pass(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_h
     if (rc == GMI_OK && *n_split_out > 0) return GMI_OK;
   }
   if (rc == GMI_ERR_UNSUPPORTED && g->fusion >= 1 && want_grad && bf) {
-    // register-chained kernel (gather + forward + loss + input gradients in one launch) where this shape has one
-    rc = gmi::launch_train_chain(g, m, b, hp, idx, rows, n_loss_blocks_out, obs16_ready, &blocks);
+    // row-tile kernel (gather + forward + loss + input gradients in one launch) where this shape has one; it leaves the hidden
+    // activations and the gradients in its block layout
+    rc = gmi::launch_train_chain(g, m, b, hp, idx, rows, n_loss_blocks_out, obs16_ready);
+    blocks = rc == GMI_OK;
   }
   if (rc == GMI_ERR_UNSUPPORTED) rc = layers_pass(g, m, b, hp, idx, rows, want_grad, n_loss_blocks_out);
   if (rc != GMI_OK || !want_grad) return rc;

@@ -83,7 +83,7 @@ def test_gradient_equals_the_per_layer_kernels(g, inst, obs, act, hidden, dtype,
 @pytest.mark.parametrize("act", [1, 2, 3, 4, 5, 7, 31, 32])
 @pytest.mark.parametrize("rows", [1, 3, 301])
 def test_gradient_of_every_remainder_of_the_actions(g, inst, obs, act, hidden, rows):
-    """The row-tile and the chained trainer kernel read a sample's actions four at a time (rows < 4 of one action: neither runs)."""
+    """The row-tile trainer kernel reads a sample's actions four at a time (fewer than 4 actions in all: it does not run)."""
     model, buf, keep = _setup(g, inst, obs, act, hidden, "bf16", 1, rows, rows)
     n = keep[0].numel()
     a, sa = _gradients(g, inst, model, buf, n, 1, rows, rows, 1)
