@@ -623,20 +623,24 @@ int launch(gmi_instance* g, const ResArgs& a, int grid, size_t lds) {
 namespace gmi {
 
 bool resident_supported(const ModelLayout& L) { return shape_ok(L); }
-// Where a row-tile kernel is compiled for the shape, this kernel is the faster one while every tile has a
-// workgroup of its own (one per net and two of the instance's compute units; 128-row tiles with the gradients in registers,
-// else 64 or, where only those fit LDS, 32).  Per minibatch with Adam, us, this kernel / the compiled one:
-//   60:256:128:64:8 (128 rows): 34.7 / 45.5 at 1000 rows, 48.5 / 50.8 at 8192, 56.6 / 57.1 at 16384, 91.9 / 89.9 at 32768;
-//     on 64 compute units 39 / 52 at 1024, 52 / 66 at 4096, 117 / 72 at 8192; on 128 46 / 53 at 4096, 53 / 56 at 8192;
-//   108:400:200:100:21 (64): 49.8 / 64.1 at 1000, 55.4 / 68.5 at 4096, 68.6 / 74.6 at 8192, 117 / 98 at 16384; on 64
-//     compute units 67 / 83 at 1024, 81 / 88 at 2048, 143 / 95 at 4096;
-//   211:512:512:256:128:20 (32): 81.9 / 98.1 at 1000, 91.7 / 107.4 at 4096, 137 / 113 at 6000, 145 / 119 at 8192; on 64
-//     compute units 134 / 151 at 1024, 184 / 159 at 2048;
-//   211:512:512:512:256:20 (32): 101 / 124 at 1000, 114 / 135 at 4096, 184 / 153 at 8192.
+// Where a row-tile kernel is compiled for the shape too.  Per minibatch with Adam, us, this kernel / that one:
+//   60:256:128:64:8: 32.2 / 28.4 at 1000 rows, 44.9 / 30.9 at 4096, 50.1 / 34.1 at 8192, 54.7 / 41.9 at 12288, 54.8 / 46.0 at 16384;
+//     on 128 compute units 49.9 / 41.0 at 6000; on 64 31.9 / 30.3 at 500, 40.9 / 46.1 at 2000, 46.5 / 52.2 at 3000, 47.3 / 51.6 at
+//     4096; on 16 46.7 / 48.1 at 256;
+//   108:400:200:100:21: 47.7 / 43.0 at 1000, 50.8 / 46.8 at 4096, 63.5 / 53.7 at 8192; on 64 compute units 64.6 / 61.3 at 1024;
+//   211:512:512:256:128:20: 75.9 / 70.9 at 1000, 86.1 / 80.3 at 4096; on 64 compute units 129 / 124 at 1000;
+//   211:512:512:512:256:20: 93.3 / 89.7 at 1000, 105 / 101 at 4096.
+// So this kernel serves such a shape on less than half the device, where it keeps the gradients in registers, while every tile
+// has a workgroup of its own (one per net and two of the instance's compute units; 128-row tiles with the gradients in registers, else
+// 64 or, where only those fit LDS, 32), and elsewhere only the one tile count that gives every workgroup a tile, which has
+// always been its own: a caller who relies on that does not see another kernel's rounding there.
 bool use_resident(const ModelLayout& L, int rows, int cus) {
   if (!shape_ok(L)) return false;
+  if (!chain_compiled(L)) return true;
   Plan p;
-  return !chain_compiled(L) || rows <= 32 * (int64_t)pick_tiles(L, INT32_MAX, 1, &p) * trainer_groups(cus);
+  const int64_t tile = 32 * pick_tiles(L, INT32_MAX, 1, &p), full = tile * trainer_groups(cus);
+  if (rows > full) return false;
+  return (cus < 128 && grad_sets(L) > 0) || rows > full - tile;
 }
 
 // Rows of gradient partials the kernel may fill with this model.
