@@ -65,6 +65,20 @@ int allow_lds(const void* kernel, size_t bytes, int device, DeviceSet* done);
 static inline int pad32(int x) { return (x + 31) & ~31; }
 static inline int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
+// ELU through the hardware base-2 exponential (abs. error ~1e-7, far below bf16 resolution).  The [0, 1] clamp (an output modifier
+// of the exponential, no instruction of its own) makes the exponential term 0 for z > 0, so that one maximum replaces the compare
+// and select; for z <= 0, e^z - 1 >= z, and where rounding puts the computed difference below z (|z| < 1e-7) z is the closer value
+// anyway.  In 24 bytes of code instead of 32, because the epilogues run at the rate at which instructions come: log2 e from a scalar
+// register, and the maximum without the compiler's canonicalisation of z, another instruction (z is the result of an arithmetic
+// one).  The maximum's operands depend on the product z log2 e, so z has left the matrix unit.
+__device__ __forceinline__ float elu_f(float z) {
+  float log2e, y;
+  asm("s_mov_b32 %0, 0x3fb8aa3b" : "=s"(log2e));      // 1.44269504
+  const float e = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(z * log2e), 0.f, 1.f) - 1.0f;
+  asm("v_max_f32 %0, %1, %2" : "=v"(y) : "v"(z), "v"(e));
+  return y;
+}
+
 // 16 bytes per lane from base + s_off + lane_off, base and s_off wave-uniform: the address takes no vector instruction and no
 // vector registers beside lane_off.
 __device__ __forceinline__ uint4 load_uniform(const void* base, int s_off, uint32_t lane_off) {

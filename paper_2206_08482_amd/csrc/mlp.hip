@@ -20,14 +20,7 @@ constexpr int kLds = kBK + 8;    // LDS row stride in bf16 elements (144 B: conf
 typedef float float2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
 
-// ELU through the hardware base-2 exponential (abs. error ~1e-7, far below bf16 resolution)
-__device__ __forceinline__ float elu_f(float z) {
-  // The [0, 1] clamp (an output modifier of the exponential, no instruction of its own) makes the exponential term
-  // 0 for z > 0, so that one maximum replaces the compare and select; for z <= 0, e^z - 1 >= z, and where rounding
-  // puts the computed difference below z (|z| < 1e-7) z is the closer value anyway.
-  const float e = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(z * 1.44269504f), 0.f, 1.f);
-  return __builtin_fmaxf(z, e - 1.0f);
-}
+using gmi::elu_f;
 // ELU'(z) from the stored output h = ELU(z) >= -1: 1 if h > 0 else h + 1, as one add with the [0, 1] clamp
 __device__ __forceinline__ float elu_grad_f(float h) { return __builtin_amdgcn_fmed3f(h + 1.0f, 0.f, 1.f); }
 __device__ __forceinline__ float bf16_to_f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }

@@ -160,7 +160,6 @@ struct Ctx {
   const uint4* wnet;                 // this net's stream
   uint4* X;                          // activation area
   uint32_t lane16;                   // 16 lane
-  float log2e;                       // of e, in a scalar register
   uint32_t xo[2];                    // this lane's byte offset in the first 64 KiB of the activation area and behind them
   const float* s_bias;
   float* s_red;
@@ -359,16 +358,6 @@ __device__ __forceinline__ void k_steps(Ctx<S>& c, const ChainArgs& a, const Wei
   }
 }
 
-// elu_f (chain_stream.h) in 24 bytes of code instead of 32: an epilogue runs at the rate at which instructions come.  The factor from
-// a scalar register, and the maximum without the compiler's canonicalisation of z (an instruction; z is a matrix
-// product's result).  The maximum's operands depend on the product z * log2e, so z has left the matrix unit.
-__device__ __forceinline__ float tile_elu(float z, float log2e) {
-  const float e = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(z * log2e), 0.f, 1.f) - 1.0f;
-  float y;
-  asm("v_max_f32 %0, %1, %2" : "=v"(y) : "v"(z), "v"(e));
-  return y;
-}
-
 // Epilogue of tile T of a hidden forward layer or of an input-gradient layer.
 template <class S, int SEG, int T>
 __device__ __forceinline__ void tile_epilogue(Ctx<S>& c, const ChainArgs& a) {
@@ -388,8 +377,7 @@ __device__ __forceinline__ void tile_epilogue(Ctx<S>& c, const ChainArgs& a) {
         v0 *= elu_grad_f(bf16_lo(h01)); v1 *= elu_grad_f(bf16_hi(h01));
         v2 *= elu_grad_f(bf16_lo(h23)); v3 *= elu_grad_f(bf16_hi(h23));
       } else {
-        v0 = tile_elu(v0, c.log2e); v1 = tile_elu(v1, c.log2e);
-        v2 = tile_elu(v2, c.log2e); v3 = tile_elu(v3, c.log2e);      // the bias is in the sums already
+        v0 = elu_f(v0); v1 = elu_f(v1); v2 = elu_f(v2); v3 = elu_f(v3);      // the bias is in the sums already
       }
       w[2 * q] = pack_bf16(v0, v1);
       w[2 * q + 1] = pack_bf16(v2, v3);
@@ -647,8 +635,6 @@ __global__ __launch_bounds__(S::threads, 2) void train_tile_kernel(ChainArgs a) 
   c.rt0 = c.row0 / 32 & 3;
   c.X = reinterpret_cast<uint4*>(smem_raw);
   c.lane16 = c.lane * 16;
-  c.log2e = 1.44269504f;
-  asm("" : "+s"(c.log2e));
   c.xo[0] = c.lane16;
   c.xo[1] = c.lane16 + 65536;
   asm volatile("" : "+v"(c.xo[1]));
