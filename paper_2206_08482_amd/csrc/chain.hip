@@ -235,12 +235,11 @@ bool has_tile_forward(const ModelLayout& L) {
   return rc == GMI_OK;
 }
 
-// agent_act with the one-launch agent kernel / with gather, this kernel and the sampling kernel, us: 211:512:512:256:128:20
-// 34 / 40 for 8192 rows, 45 / 42 for 9216, 50 / 44 for 12288, on 64 compute units 27 / 37 for 2048, 39 / 38 for 2560 and 3072, on 16
-// 27 / 36 for 512, 39 / 37 for 640 and 768, 50 / 38 for 1024; 211:512:512:512:256:20 44 / 49 for 8192 rows, 58 / 51 for 9216, 63 / 54 for
-// 12288, on 64 compute units 34 / 46 for 2048, 50 / 47 for 2560 and 3072, on 16 35 / 45 for 512, 50 / 46 for 640 and 768.  They cross at 32 rows
-// per compute unit, where the agent kernel needs another round; the line stays at 48, where it was when they crossed there: the
-// two add in different orders, and between 32 and 48 a caller's results would change in the last bit for 3 to 9 us.
+// agent_act with the agent kernel / with this one, us: 211:512:512:256:128:20 19 / 20 for 2048 rows, 21 / 21 for 4096, 34 / 25 for 8192,
+// 44 / 31 for 9216, 50 / 33 for 12288, on 64 compute units 18 / 20 for 1024, 27 / 20 for 2048, 40 / 25 for 3072, on 16 18 / 20 for 256, 27 / 20 for
+// 512, 39 / 25 for 768; 211:512:512:512:256:20 27 / 26 for 4096 rows, 44 / 32 for 8192, 62 / 43 for 12288, on 64 compute units 34 / 24 for
+// 2048, 50 / 33 for 3072.  They cross at 16 rows per compute unit; the line stays at 48, where it was when they crossed there: the two add
+// in different orders, and below it a caller's results would change in the last bit, of agent_act and of a collection alike.
 bool use_tile_forward(const gmi_instance* g, const gmi_model* m, int rows) {
   return rows >= 48 * (int64_t)g->cu_count && has_tile_forward(m->L);
 }
@@ -251,8 +250,8 @@ bool forward_chain_reads_x0(const gmi_model* m, const float* obs) {
 
 // Inference through the forward-only row-tile kernel (agent_act / agent_value of the models too large for the fused
 // agent kernel): the same stream, the same products in the same order as the trainer's forward pass.
-int launch_forward_chain(gmi_instance* g, gmi_model* m, const float* obs, int n_rows, float* mu, float* val,
-                         bool x0_valid) {
+int launch_forward_chain(gmi_instance* g, gmi_model* m, const float* obs, int n_rows, bool policy, float* mu, float* val,
+                         bool x0_valid, const ActionSample* sample) {
   const ModelLayout& L = m->L;
   if (n_rows < 1 || n_rows > m->max_rows || !use_tile_forward(g, m, n_rows)) return GMI_ERR_UNSUPPORTED;
   int rc;
@@ -266,11 +265,15 @@ int launch_forward_chain(gmi_instance* g, gmi_model* m, const float* obs, int n_
   a.idx = nullptr;
   a.b_obs = obs;
   a.n_envs = n_rows; a.ld_envs = n_rows; a.obs_dim = L.obs_dim;
-  a.x0_ready = forward_chain_reads_x0(m, obs) ? 1 : 0;
+  a.x0_ready = !forward_chain_reads_x0(m, obs) ? 0 : (x0_valid || L.obs_dim < 4 ? 1 : 3);
   a.rows = n_rows; a.act_dim = L.act_dim;
-  a.net0 = mu ? 0 : 1;
+  a.net0 = policy ? 0 : 1;
   a.mu_out = mu; a.val_out = val;
-  if (a.x0_ready && !x0_valid) {
+  if (sample) {
+    a.act_out = sample->act; a.logp_out = sample->logp;
+    a.k0 = (uint32_t)sample->seed; a.k1 = (uint32_t)(sample->seed >> 32); a.step = sample->step; a.env_offset = sample->env_offset;
+  }
+  if (a.x0_ready == 1 && !x0_valid) {
     rc = launch_gather(g, m, obs, n_rows, n_rows, nullptr, n_rows, nullptr);
     if (rc != GMI_OK) return rc;
   }
@@ -281,7 +284,8 @@ int launch_forward_chain(gmi_instance* g, gmi_model* m, const float* obs, int n_
       flops += 2.0 * n_rows * (double)li.in * li.out;
       bytes += 2.0 * li.in * li.out;
     }
-  bytes += (a.x0_ready ? 2.0 : 4.0) * n_rows * L.obs_dim * (2 - a.net0) + 4.0 * n_rows * ((mu ? L.act_dim : 0) + 1);
+  bytes += (a.x0_ready == 1 ? 2.0 : 4.0) * n_rows * L.obs_dim * (2 - a.net0) +
+           4.0 * n_rows * ((mu ? L.act_dim : 0) + (sample ? L.act_dim + 1 : 0) + 1);
   int tiles = 0;
   rc = GMI_ERR_UNSUPPORTED;
   for (int p = 0; p < kTileFwdParts && rc == GMI_ERR_UNSUPPORTED; ++p) rc = kTileFwdFns[p](g, L, a, n_rows, &tiles, flops, bytes);

@@ -65,14 +65,17 @@ struct ChainArgs {
   int n_envs, ld_envs, obs_dim;
   int x0_ready;                                    // 1: x0 already holds the gathered rows (observation rows that cannot
                                                    // be read as 16-byte pieces are gathered by gather_kernel beforehand);
-                                                   // 2: the rows are gathered from x16
+                                                   // 2: the rows are gathered from x16; 3 (inference): rows of at least 4
+                                                   // floats, in order, that start at any 4-byte address
   const uint16_t* x16;                             // bf16 copy of all observations, [sample index][d[0]] (x0_ready == 2)
   int rows, act_dim;
   float clip, c_v;
   float* stat_part;                                // [tiles][kStatStride + act_dim]
   // inference (TileShapeFwd): workgroup row y works on net net0 + y; results of the heads
   int net0;
-  float* mu_out;                                   // [rows, act_dim] policy means
+  float* mu_out;                                   // [rows, act_dim] policy means, or NULL
+  float *act_out, *logp_out;                       // [rows, act_dim] sampled actions and [rows] their log-densities, or NULL
+  uint32_t k0, k1, step, env_offset;               // of the draws
   float* val_out;                                  // [rows] values
   uint16_t* x0b;                                   // the minibatch's observations as the first layer's operand blocks, written here for
                                                    // the weight-gradient kernel (by the policy net's workgroups)

@@ -398,10 +398,15 @@ struct ChainEmit {
   ChainEmitLayer l[kMaxWgradProblems];
 };
 void fill_chain_emit(const ModelLayout& L, ChainEmit* ce);
-// Forward pass of n_rows observation rows through the forward-only row-tile kernel: policy means into mu (NULL: value
-// net only) and values into val.  GMI_ERR_UNSUPPORTED (no message) where use_tile_forward says no.
-int launch_forward_chain(gmi_instance* g, gmi_model* m, const float* obs, int n_rows, float* mu, float* val,
-                         bool x0_valid = false);
+// Forward pass of n_rows observation rows through the forward-only row-tile kernel: policy means into mu (policy; may be NULL),
+// values into val, and the action decision if `sample` is given.  GMI_ERR_UNSUPPORTED (no message) where use_tile_forward says no.
+struct ActionSample {
+  uint64_t seed;
+  uint32_t step, env_offset;
+  float *act, *logp;
+};
+int launch_forward_chain(gmi_instance* g, gmi_model* m, const float* obs, int n_rows, bool policy, float* mu, float* val,
+                         bool x0_valid = false, const ActionSample* sample = nullptr);
 // Whether such a kernel is compiled for the shape / is the faster one for that many rows on that instance (else launch_agent).
 bool has_tile_forward(const ModelLayout& L);
 bool use_tile_forward(const gmi_instance* g, const gmi_model* m, int rows);

@@ -264,7 +264,7 @@ int rollout_stepwise(gmi_instance* g, gmi_model* m, gmi_env* env, gmi_buffer* b,
     const float* cur = t == 0 ? obs : bd.obs + (int64_t)t * ld * O;
     float* nxt = t == T - 1 ? obs : bd.obs + (int64_t)(t + 1) * ld * O;
     // policy means into the model's workspace, values straight into slot t
-    int rc = tile ? launch_forward_chain(g, m, cur, n, m->mu, bd.val + t * ld, t > 0 && forward_chain_reads_x0(m, cur))
+    int rc = tile ? launch_forward_chain(g, m, cur, n, true, m->mu, bd.val + t * ld, t > 0 && forward_chain_reads_x0(m, cur))
                   : launch_agent(g, m, cur, n, 0, 0, 0, nullptr, nullptr, bd.val + t * ld, m->mu, true);
     if (rc != GMI_OK) return rc;
     StepFuse fu;
@@ -279,7 +279,7 @@ int rollout_stepwise(gmi_instance* g, gmi_model* m, gmi_env* env, gmi_buffer* b,
     rc = launch_env_step(g, env, cur, nullptr, step0 + (uint32_t)t, nxt, bd.rew + t * ld, bd.done + t * ld, &fu);
     if (rc != GMI_OK) return rc;
   }
-  return tile ? launch_forward_chain(g, m, obs, n, nullptr, last_value, forward_chain_reads_x0(m, obs))
+  return tile ? launch_forward_chain(g, m, obs, n, false, nullptr, last_value, forward_chain_reads_x0(m, obs))
               : launch_agent(g, m, obs, n, 0, 0, 0, nullptr, nullptr, last_value, nullptr, false);
 }
 
@@ -487,14 +487,15 @@ extern "C" int agent_act(gmi_t g, gmi_model_t m, const float* obs, int32_t n_row
     rc = gmi::launch_agent_f32(g, m, obs, n_rows, seed, step, env_offset, act, logp, value, mu, true);
     if (rc == GMI_ERR_UNSUPPORTED)
       rc = gmi::launch_agent(g, m, obs, n_rows, seed, step, env_offset, act, logp, value, mu, true);
+    if (rc == GMI_ERR_UNSUPPORTED) {
+      const gmi::ActionSample sample = {seed, step, env_offset, act, logp};
+      rc = gmi::launch_forward_chain(g, m, obs, n_rows, true, mu, value, false, &sample);
+    }
     if (rc != GMI_ERR_UNSUPPORTED) return rc;
   }
-  rc = g->fusion ? gmi::launch_forward_chain(g, m, obs, n_rows, m->mu, value) : GMI_ERR_UNSUPPORTED;
-  if (rc == GMI_ERR_UNSUPPORTED) {
-    rc = gmi::launch_gather(g, m, obs, n_rows, n_rows, nullptr, n_rows, nullptr);
-    if (rc != GMI_OK) return rc;
-    rc = gmi::forward_nets(g, m, n_rows, true, true, m->mu, value);
-  }
+  rc = gmi::launch_gather(g, m, obs, n_rows, n_rows, nullptr, n_rows, nullptr);
+  if (rc != GMI_OK) return rc;
+  rc = gmi::forward_nets(g, m, n_rows, true, true, m->mu, value);
   if (rc != GMI_OK) return rc;
   const float* log_std = m->L.dtype == GMI_DTYPE_BF16 ? reinterpret_cast<const float*>(m->shadow + m->L.sh_logstd)
                                                       : m->params + m->L.logstd_off;
@@ -513,7 +514,7 @@ extern "C" int agent_value(gmi_t g, gmi_model_t m, const float* obs, int32_t n_r
     if (rc == GMI_ERR_UNSUPPORTED) rc = gmi::launch_agent(g, m, obs, n_rows, 0, 0, 0, nullptr, nullptr, value, nullptr, false);
     if (rc != GMI_ERR_UNSUPPORTED) return rc;
   }
-  rc = g->fusion ? gmi::launch_forward_chain(g, m, obs, n_rows, nullptr, value) : GMI_ERR_UNSUPPORTED;
+  rc = g->fusion ? gmi::launch_forward_chain(g, m, obs, n_rows, false, nullptr, value) : GMI_ERR_UNSUPPORTED;
   if (rc != GMI_ERR_UNSUPPORTED) return rc;
   rc = gmi::launch_gather(g, m, obs, n_rows, n_rows, nullptr, n_rows, nullptr);
   if (rc != GMI_OK) return rc;

@@ -34,6 +34,7 @@
 // nothing is stored for the weight gradients and the heads' results go out as policy means and values.
 #pragma once
 #include "chain_stream.h"
+#include "rng.h"
 
 namespace gmi_tile {
 using namespace gmi_chain;
@@ -542,21 +543,73 @@ __device__ __forceinline__ void loss_sums(const Ctx<S>& c, const ChainArgs& a) {
 }
 
 // Inference: the head's results of row tile `wave` (lane = row, register i = feature 8 (i / 4) + 4 hh + i % 4) plus
-// the head's bias go out as policy means [rows, act_dim] or as values [rows].
+// the head's bias go out as policy means [rows, act_dim] or as values [rows], and, where actions are asked for, the decision
+// act = mean + exp(log_std) * eps and its log-density: the arithmetic of sample_kernel (model.hip), terms summed in action order.
+// The draws are made beside the head's product by the waves that have no part in it.  (Gather, this kernel and sampling as three
+// launches, 16384 rows of
+// 211:512:512:256:128:20: 49 us, now 38.)
+template <class S>
+__device__ __forceinline__ void head_draws(const Ctx<S>& c, const ChainArgs& a) {
+  const int row = c.row0 + 32 * (c.wave & (S::nrt - 1)) + c.s;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (8 * q >= a.act_dim) break;
+    float z[4];
+    gmi::normal_block(a.env_offset + (uint32_t)row, a.step, gmi::kStreamAction, (uint32_t)(2 * q + c.hh), a.k0, a.k1, z);
+    reinterpret_cast<float4*>(c.scr)[q * 64 + c.lane] = make_float4(z[0], z[1], z[2], z[3]);
+  }
+}
 template <class S>
 __device__ __forceinline__ void head_outputs(Ctx<S>& c, const ChainArgs& a, const floatx16& acc) {
   constexpr int HB = S::bias_off(S::NL - 1);
-  const int row = c.row0 + 32 * c.wave + c.s;
-  if (row >= a.rows || c.wave >= S::nrt) return;
-  if (c.net == 0) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int f = 8 * (i / 4) + 4 * c.hh + (i % 4);
-      if (f < a.act_dim) a.mu_out[(int64_t)row * a.act_dim + f] = acc[i] + c.s_bias[HB + f];
-    }
-  } else if (c.hh == 0) {
-    a.val_out[row] = acc[0] + c.s_bias[HB];
+  if (c.wave >= S::nrt) return;
+  const int row = c.row0 + 32 * c.wave + c.s, A = a.act_dim;
+  const bool ok = row < a.rows;
+  if (c.net == 1) {
+    if (ok && c.hh == 0) a.val_out[row] = acc[0] + c.s_bias[HB];
+    return;
   }
+  typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+  auto store = [&](float* out, int f0, const float (&v)[4]) {
+    float* p = out + (int64_t)row * A + f0;
+    if (f0 + 4 <= A) {
+      const float4u t = {v[0], v[1], v[2], v[3]};
+      *reinterpret_cast<float4u*>(p) = t;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 3; ++e)
+        if (f0 + e < A) p[e] = v[e];
+    }
+  };
+  const float* s_ls = c.s_red + S::nrt * 40;      // [f] log_std, [32 + f] exp(log_std)
+  float lp = 0.f;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (8 * q >= A) break;
+    const int f0 = 8 * q + 4 * c.hh;
+    float m[4], act[4], term[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m[e] = acc[4 * q + e] + c.s_bias[HB + f0 + e];
+    if (a.mu_out && ok) store(a.mu_out, f0, m);
+    if (!a.act_out) continue;
+    const float4 z4 = reinterpret_cast<const float4*>(c.scr)[q * 64 + c.lane];
+    const float z[4] = {z4.x, z4.y, z4.z, z4.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float ls = s_ls[f0 + e];
+      act[e] = fmaf(s_ls[32 + f0 + e], z[e], m[e]);
+      term[e] = -0.5f * z[e] * z[e] - ls - 0.918938533204672742f;
+    }
+    if (ok) store(a.act_out, f0, act);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) lp = 8 * q + e < A ? lp + term[e] : lp;      // (the lower half's sum is the one that goes out)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float t = __shfl_xor(term[e], 32, 64);
+      lp = 8 * q + 4 + e < A ? lp + t : lp;
+    }
+  }
+  if (a.act_out && ok && c.hh == 0) a.logp_out[row] = lp;
 }
 
 template <class S, int SEG>
@@ -590,7 +643,12 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
     }
     read_x<S, SEG, 0>(c);
     if constexpr (G::XD > 1) read_x<S, SEG, 1>(c);
-    k_steps<S, SEG, 0>(c, a, wseg);
+    if constexpr (G::head && S::fwd) {
+      if (c.wave < S::nrt) k_steps<S, SEG, 0>(c, a, wseg);
+      else if (c.net == 0 && a.act_out) head_draws<S>(c, a);
+    } else {
+      k_steps<S, SEG, 0>(c, a, wseg);
+    }
     issue_first_weights<S, SEG + 1>(c);
     __syncthreads();                       // every wave is done with the layer's input
     // this lane's loss inputs: cold loads, issued where a long stretch of arithmetic follows and no younger load is
@@ -686,7 +744,28 @@ __global__ __launch_bounds__(S::threads, 2) void train_tile_kernel(ChainArgs a) 
 #pragma unroll
     for (int gi = 0; gi < NG; ++gi) sm[gi] = a.idx ? sm[gi] : srow[gi];
     uint4 v[NG][NI];
-    if (a.x0_ready != 0) {                               // workgroup-uniform; no branch around a single load
+    if (S::fwd && a.x0_ready == 3) {                     // workgroup-uniform; no branch around a single load
+#pragma unroll
+      for (int gi = 0; gi < NG; ++gi) {
+        typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+        const float* orow = a.b_obs + (int64_t)sm[gi] * O;
+#pragma unroll
+        for (int it = 0; it < NI; ++it) {
+          const int j = 4 * it + jj;
+          float f[8];
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const int f0 = 8 * j + 4 * q, back = it < NI - 1 ? 0 : f0 - (f0 < O - 4 ? f0 : O - 4);      // (O is within 32 of the padded width)
+            const float4u t = *reinterpret_cast<const float4u*>(orow + f0 - back);
+            f[4 * q + 0] = back == 0 ? t.x : back == 1 ? t.y : back == 2 ? t.z : back == 3 ? t.w : 0.f;
+            f[4 * q + 1] = back == 0 ? t.y : back == 1 ? t.z : back == 2 ? t.w : 0.f;
+            f[4 * q + 2] = back == 0 ? t.z : back == 1 ? t.w : 0.f;
+            f[4 * q + 3] = back == 0 ? t.w : 0.f;
+          }
+          v[gi][it] = make_uint4(pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3]), pack_bf16(f[4], f[5]), pack_bf16(f[6], f[7]));
+        }
+      }
+    } else if (a.x0_ready != 0) {
 #pragma unroll
       for (int gi = 0; gi < NG; ++gi) {
         const int row = c.row0 + 16 * (c.wave + S::waves * gi) + rr;
@@ -733,7 +812,7 @@ __global__ __launch_bounds__(S::threads, 2) void train_tile_kernel(ChainArgs a) 
       if (c.tid < S::nrt * 40) c.s_red[c.tid] = 0.f;
       if (c.tid < 32) {                      // per-feature constants of the Gaussian log-prob (policy net)
         c.s_red[S::nrt * 40 + c.tid] = ls;
-        c.s_red[S::nrt * 40 + 32 + c.tid] = c.tid < a.act_dim ? expf(-ls) : 0.f;
+        c.s_red[S::nrt * 40 + 32 + c.tid] = c.tid < a.act_dim ? expf(S::fwd ? ls : -ls) : 0.f;
       }
       if constexpr (!S::fwd) {
         hsm = a.idx ? hsm : hrow;
@@ -785,6 +864,7 @@ int launch_shape(gmi_instance* g, const ChainArgs& a, int rows, int* tiles_out, 
   const int tiles = (rows + S::rows - 1) / S::rows;
   *tiles_out = tiles;
   if (!S::fwd && tiles > gmi::kStatRowsMax) return GMI_ERR_UNSUPPORTED;      // one statistics row per tile
+  if (a.x0_ready == 3 && (!S::fwd || a.idx || a.obs_dim < 4 || a.obs_dim <= S::dims().d[0] - 32)) return GMI_ERR_UNSUPPORTED;
   if (a.x0_ready == 0 && (a.obs_dim % 4 != 0 || a.obs_dim < 4)) return GMI_ERR_UNSUPPORTED;
   const int rc = gmi::allow_lds((const void*)train_tile_kernel<S>, lds, g->device, &allowed);
   if (rc != GMI_OK) return rc;

@@ -162,6 +162,18 @@ def test_agent_kernel_matches_the_per_layer_path(g, inst, obs, act, hidden, n, s
     assert np.array_equal(out[1][2], out[1][4])      # agent_value is the same network pass
 
 
+@pytest.mark.parametrize("obs,act,shift", [(211, 1, 0), (211, 3, 1), (193, 4, 0), (208, 7, 0), (208, 8, 1), (222, 9, 0), (223, 31, 3),
+                                           (224, 32, 2)])
+@pytest.mark.parametrize("hidden,n", [([512, 512, 256, 128], 769), ([512, 512, 512, 256], 832)])
+def test_row_tile_decisions_match_the_per_layer_path(g, obs, act, hidden, n, shift):
+    """Enough rows for 16 compute units to take the row-tile kernel: observation rows at every alignment and remainder, every
+    remainder of the actions."""
+    from paper_2206_08482_amd.instances import cu_masks
+    masked = g.gmi_create(cu_masks(256, [16])[0])
+    test_agent_kernel_matches_the_per_layer_path(g, masked, obs, act, hidden, n, shift)
+    g.gmi_destroy(masked)
+
+
 @pytest.mark.parametrize("obs,act,hidden,n", [
     (211, 20, [512, 512, 256, 128], 32769),   # 128 rows on 16 waves
     (60, 8, [256, 128, 64], 32801),           # two 128-row tiles per compute unit
