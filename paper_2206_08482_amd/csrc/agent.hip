@@ -63,6 +63,8 @@ int launch_agent(gmi_instance* g, gmi_model* m, const float* obs, int n, uint64_
 
 int launch_values(gmi_instance* g, gmi_model* m, const float* obs, int T, int n, int64_t ld, float* value, const float* obs_last,
                   float* value_last) {
+  const int tile = launch_forward_values(g, m, obs, T, n, ld, value, obs_last, value_last);
+  if (tile != GMI_ERR_UNSUPPORTED) return tile;
   const int per = std::max(1, (1 << 30) / ((n + 31) / 32) - 1);      // slots of a launch: its items are a 32-bit count
   for (int t0 = 0; t0 < T; t0 += per) {
     AgentArgs a = {};

@@ -76,7 +76,8 @@ ChainDims dims_of(const ModelLayout& L) {
 typedef int (*part_fn)(gmi_instance*, const ModelLayout&, const ChainArgs&, int, int*, double, double);
 const part_fn kTileFns[gmi::kTileParts] = {gmi::launch_tile_part0, gmi::launch_tile_part1, gmi::launch_tile_part2,
                                            gmi::launch_tile_part3, gmi::launch_tile_part4, gmi::launch_tile_part5};
-const part_fn kTileFwdFns[gmi::kTileFwdParts] = {gmi::launch_tile_fwd_part0, gmi::launch_tile_fwd_part1};
+const part_fn kTileFwdFns[gmi::kTileFwdParts] = {gmi::launch_tile_fwd_part0, gmi::launch_tile_fwd_part1, gmi::launch_tile_fwd_part2,
+                                                 gmi::launch_tile_fwd_part3, gmi::launch_tile_fwd_part4, gmi::launch_tile_fwd_part5};
 
 // True if a trainer kernel is compiled for this model's shape.
 bool compiled(const ModelLayout& L) {
@@ -227,46 +228,84 @@ int launch_train_chain(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_p
   return GMI_OK;
 }
 
-bool has_tile_forward(const ModelLayout& L) {
-  if (L.dtype != GMI_DTYPE_BF16 || L.sh_chain_bytes == 0 || L.act_dim > 32) return false;
+// What the forward-only kernel of the shape answers: 0 its own order of summation, 1 the agent kernel's; -1 if there is none.
+static int forward_kind(const ModelLayout& L) {
+  if (L.dtype != GMI_DTYPE_BF16 || L.sh_chain_bytes == 0 || L.act_dim > 32) return -1;
   const ChainArgs a = {};
-  int probe = 0, rc = GMI_ERR_UNSUPPORTED;
-  for (int p = 0; p < kTileFwdParts && rc == GMI_ERR_UNSUPPORTED; ++p) rc = kTileFwdFns[p](nullptr, L, a, 0, &probe, 0.0, 0.0);
-  return rc == GMI_OK;
+  int kind = 0;
+  for (int p = 0; p < kTileFwdParts; ++p)
+    if (kTileFwdFns[p](nullptr, L, a, 0, &kind, 0.0, 0.0) == GMI_OK) return kind;
+  return -1;
 }
+bool has_tile_forward(const ModelLayout& L) { return forward_kind(L) == 0; }
 
 // agent_act with the agent kernel / with this one, us: 211:512:512:256:128:20 19 / 20 for 2048 rows, 21 / 21 for 4096, 34 / 25 for 8192,
 // 44 / 31 for 9216, 50 / 33 for 12288, on 64 compute units 18 / 20 for 1024, 27 / 20 for 2048, 40 / 25 for 3072, on 16 18 / 20 for 256, 27 / 20 for
 // 512, 39 / 25 for 768; 211:512:512:512:256:20 27 / 26 for 4096 rows, 44 / 32 for 8192, 62 / 43 for 12288, on 64 compute units 34 / 24 for
 // 2048, 50 / 33 for 3072.  They cross at 16 rows per compute unit; the line stays at 48, where it was when they crossed there: the two add
 // in different orders, and below it a caller's results would change in the last bit, of agent_act and of a collection alike.
-bool use_tile_forward(const gmi_instance* g, const gmi_model* m, int rows) {
-  return rows >= 48 * (int64_t)g->cu_count && has_tile_forward(m->L);
+// The shapes whose kernel computes in the agent kernel's order are free to choose.  Agent kernel / this one, us:
+//   60:256:128:64:8 8.6 / 7.6 for 64 rows, 9.0 / 8.3 for 4096, 11.0 / 8.5 for 8192, 25 / 16 for 32768, 168 / 102 for 262144, on 64 compute
+//     units 8.6 / 7.8 for 256, 10.4 / 8.2 for 2048;
+//   108:400:200:100:21 11.9 / 13.7 for 512 rows, 12.6 / 14.0 for 4096, 15.7 / 14.2 for 5000, 31 / 19 for 16384, 428 / 262 for 262144, on 64
+//     compute units 11.9 / 13.7 for 1024, 15.0 / 13.7 for 2048, on 16 11.8 / 13.3 for 256, 14.9 / 13.7 for 512;
+//   23:256:128:64:9, whose rows start at any 4-byte address, 9.1 / 9.3 for 2048, 9.3 / 9.3 for 4096, 10.8 / 9.3 for 5000, 172 / 99 for 262144.
+// The values of a collection of 108:400:200:100:21 (4096 envs, 32 steps) 128 / 79.
+// So: layers of more than 8 feature tiles, which this kernel's 4 waves take 4 at a time and the agent kernel's 8 waves 2, and unaligned
+// rows, from the rows on that give the agent kernel more than one workgroup per compute unit; else always.
+bool use_tile_forward(const gmi_instance* g, const gmi_model* m, int64_t rows) {
+  const ModelLayout& L = m->L;
+  const int kind = forward_kind(L);
+  if (kind == 0) return rows >= 48 * (int64_t)g->cu_count;
+  if (kind < 0 || L.obs_dim < 4) return false;
+  return (cd_maxdim(dims_of(L)) <= 256 && L.obs_dim % 4 == 0) || rows > 16 * (int64_t)g->cu_count;
 }
 
 bool forward_chain_reads_x0(const gmi_model* m, const float* obs) {
   return !(m->L.obs_dim % 4 == 0 && ((uintptr_t)obs & 15) == 0);
 }
 
-// Inference through the forward-only row-tile kernel (agent_act / agent_value of the models too large for the fused
-// agent kernel): the same stream, the same products in the same order as the trainer's forward pass.
+static void fill_forward(const gmi_model* m, ChainArgs* a) {
+  const ModelLayout& L = m->L;
+  const bool nat = forward_kind(L) == 1;
+  for (int net = 0; net < 2; ++net) {
+    a->wstream[net] = m->shadow + (nat ? 0 : L.sh_chain[net]);
+    for (int l = 0; l < L.n_layers; ++l) {
+      a->bias[net][l] = reinterpret_cast<const float*>(m->shadow + L.net[net][l].sh_b);
+      a->wf_off[net][l] = (int)L.net[net][l].sh_wf;
+    }
+  }
+  a->x0 = (uint16_t*)m->x0;
+  a->log_std = reinterpret_cast<const float*>(m->shadow + L.sh_logstd);
+  a->obs_dim = L.obs_dim; a->act_dim = L.act_dim;
+  a->T = 1;
+}
+static int launch_forward(gmi_instance* g, const gmi_model* m, const ChainArgs& a, double out_floats) {
+  const ModelLayout& L = m->L;
+  const double rows = (double)a.rows * (a.T + (a.val_last ? 1 : 0));
+  double flops = 0.0, bytes = 0.0;
+  for (int net = a.net0; net < 2; ++net)
+    for (int l = 0; l < L.n_layers; ++l) {
+      const LayerInfo& li = L.net[net][l];
+      flops += 2.0 * rows * (double)li.in * li.out;
+      bytes += 2.0 * li.in * li.out;
+    }
+  bytes += (a.x0_ready == 1 ? 2.0 : 4.0) * rows * L.obs_dim * (2 - a.net0) + 4.0 * rows * out_floats;
+  int tiles = 0, rc = GMI_ERR_UNSUPPORTED;
+  for (int p = 0; p < kTileFwdParts && rc == GMI_ERR_UNSUPPORTED; ++p) rc = kTileFwdFns[p](g, L, a, a.rows, &tiles, flops, bytes);
+  return rc;
+}
+
+// Inference through the forward-only row-tile kernel.
 int launch_forward_chain(gmi_instance* g, gmi_model* m, const float* obs, int n_rows, bool policy, float* mu, float* val,
                          bool x0_valid, const ActionSample* sample) {
   const ModelLayout& L = m->L;
   if (n_rows < 1 || n_rows > m->max_rows || !use_tile_forward(g, m, n_rows)) return GMI_ERR_UNSUPPORTED;
-  int rc;
   ChainArgs a = {};
-  for (int net = 0; net < 2; ++net) {
-    a.wstream[net] = m->shadow + L.sh_chain[net];
-    for (int l = 0; l < L.n_layers; ++l) a.bias[net][l] = reinterpret_cast<const float*>(m->shadow + L.net[net][l].sh_b);
-  }
-  a.x0 = (uint16_t*)m->x0;
-  a.log_std = reinterpret_cast<const float*>(m->shadow + L.sh_logstd);
-  a.idx = nullptr;
+  fill_forward(m, &a);
   a.b_obs = obs;
-  a.n_envs = n_rows; a.ld_envs = n_rows; a.obs_dim = L.obs_dim;
   a.x0_ready = !forward_chain_reads_x0(m, obs) ? 0 : (x0_valid || L.obs_dim < 4 ? 1 : 3);
-  a.rows = n_rows; a.act_dim = L.act_dim;
+  a.rows = n_rows;
   a.net0 = policy ? 0 : 1;
   a.mu_out = mu; a.val_out = val;
   if (sample) {
@@ -274,22 +313,27 @@ int launch_forward_chain(gmi_instance* g, gmi_model* m, const float* obs, int n_
     a.k0 = (uint32_t)sample->seed; a.k1 = (uint32_t)(sample->seed >> 32); a.step = sample->step; a.env_offset = sample->env_offset;
   }
   if (a.x0_ready == 1 && !x0_valid) {
-    rc = launch_gather(g, m, obs, n_rows, n_rows, nullptr, n_rows, nullptr);
+    const int rc = launch_gather(g, m, obs, n_rows, n_rows, nullptr, n_rows, nullptr);
     if (rc != GMI_OK) return rc;
   }
-  double flops = 0.0, bytes = 0.0;
-  for (int net = a.net0; net < 2; ++net)
-    for (int l = 0; l < L.n_layers; ++l) {
-      const LayerInfo& li = L.net[net][l];
-      flops += 2.0 * n_rows * (double)li.in * li.out;
-      bytes += 2.0 * li.in * li.out;
-    }
-  bytes += (a.x0_ready == 1 ? 2.0 : 4.0) * n_rows * L.obs_dim * (2 - a.net0) +
-           4.0 * n_rows * ((mu ? L.act_dim : 0) + (sample ? L.act_dim + 1 : 0) + 1);
-  int tiles = 0;
-  rc = GMI_ERR_UNSUPPORTED;
-  for (int p = 0; p < kTileFwdParts && rc == GMI_ERR_UNSUPPORTED; ++p) rc = kTileFwdFns[p](g, L, a, n_rows, &tiles, flops, bytes);
-  return rc;
+  return launch_forward(g, m, a, (mu ? L.act_dim : 0) + (sample ? L.act_dim + 1 : 0) + 1);
+}
+
+int launch_forward_values(gmi_instance* g, gmi_model* m, const float* obs, int T, int n, int64_t ld, float* value, const float* obs_last,
+                          float* value_last) {
+  const ModelLayout& L = m->L;
+  const int64_t slots = T + (value_last ? 1 : 0), tiles = (n + 63) / 64;
+  if (forward_kind(L) != 1 || T < 1 || tiles * slots >= (1 << 30) || 3 * (int64_t)n < 2 * 64 * tiles || !use_tile_forward(g, m, slots * n))
+    return GMI_ERR_UNSUPPORTED;
+  ChainArgs a = {};
+  fill_forward(m, &a);
+  a.b_obs = obs; a.obs_last = obs_last;
+  a.T = T; a.obs_step = ld * L.obs_dim; a.val_step = ld;
+  a.val_out = value; a.val_last = value_last;
+  a.rows = n;
+  a.net0 = 1;
+  a.x0_ready = forward_chain_reads_x0(m, obs) || (a.obs_step & 3) != 0 || (value_last && forward_chain_reads_x0(m, obs_last)) ? 3 : 0;
+  return launch_forward(g, m, a, 1.0);
 }
 
 }  // namespace gmi

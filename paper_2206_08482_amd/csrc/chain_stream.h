@@ -76,6 +76,13 @@ struct ChainArgs {
   float* mu_out;                                   // [rows, act_dim] policy means, or NULL
   float *act_out, *logp_out;                       // [rows, act_dim] sampled actions and [rows] their log-densities, or NULL
   uint32_t k0, k1, step, env_offset;               // of the draws
+  // inference over several slots of rows: slot t < T reads b_obs + t obs_step and writes val_out + t val_step, slot T reads obs_last
+  // and writes val_last; item = slot * slot_tiles + row tile
+  int T, slot_tiles, items;
+  int64_t obs_step, val_step;
+  const float* obs_last;
+  float* val_last;
+  int wf_off[2][GMI_MAX_HIDDEN + 1];               // TileShapeNat: bytes from wstream to a layer's fragment-major weights
   float* val_out;                                  // [rows] values
   uint16_t* x0b;                                   // the minibatch's observations as the first layer's operand blocks, written here for
                                                    // the weight-gradient kernel (by the policy net's workgroups)

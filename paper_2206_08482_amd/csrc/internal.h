@@ -409,7 +409,10 @@ int launch_forward_chain(gmi_instance* g, gmi_model* m, const float* obs, int n_
                          bool x0_valid = false, const ActionSample* sample = nullptr);
 // Whether such a kernel is compiled for the shape / is the faster one for that many rows on that instance (else launch_agent).
 bool has_tile_forward(const ModelLayout& L);
-bool use_tile_forward(const gmi_instance* g, const gmi_model* m, int rows);
+bool use_tile_forward(const gmi_instance* g, const gmi_model* m, int64_t rows);
+// launch_values through it: GMI_ERR_UNSUPPORTED (no message) where values_kernel is the faster one.
+int launch_forward_values(gmi_instance* g, gmi_model* m, const float* obs, int T, int n, int64_t ld, float* value, const float* obs_last,
+                          float* value_last);
 // Whether that kernel would read the bf16 rows m->x0 (made by the gather kernel) instead of obs itself.
 bool forward_chain_reads_x0(const gmi_model* m, const float* obs);
 // The collection stage for the models too large for the one-launch rollout kernel: per step the forward-only kernel

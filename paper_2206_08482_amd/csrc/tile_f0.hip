@@ -2,5 +2,5 @@
 #include "tile_kernel.h"
 
 namespace gmi {
-GMI_TILE_FWD_PART_DEFINE(0, 224, 512, 512, 256, 128, 32)
+GMI_TILE_FWD_PART_DEFINE(0, TileShapeFwd, 224, 512, 512, 256, 128, 32)
 }

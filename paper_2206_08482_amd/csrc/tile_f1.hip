@@ -2,5 +2,5 @@
 #include "tile_kernel.h"
 
 namespace gmi {
-GMI_TILE_FWD_PART_DEFINE(1, 224, 512, 512, 512, 256, 32)
+GMI_TILE_FWD_PART_DEFINE(1, TileShapeFwd, 224, 512, 512, 512, 256, 32)
 }

@@ -47,7 +47,8 @@ template <int ROWS, int... DIMS>
 struct TileShape {
   static constexpr int rows = ROWS, nrt = ROWS / 32, waves = 2 * nrt, threads = 64 * waves;
   static constexpr int acc_ft = 16 / waves, ring = 8;      // feature tiles of a wave; weight blocks in flight per wave
-  static constexpr bool fwd = false;      // TileShapeFwd: the forward pass alone (inference)
+  static constexpr bool fwd = false;      // TileShapeFwd, TileShapeNat: the forward pass alone (inference)
+  static constexpr bool nat = false;      // TileShapeNat
   static constexpr int NL = (int)sizeof...(DIMS) - 1;
   static constexpr ChainDims dims() { return ChainDims{NL, {DIMS...}}; }
   static constexpr int nseg() { return cd_nseg(dims()); }
@@ -85,6 +86,13 @@ struct TileShape {
 template <int ROWS, int... DIMS>
 struct TileShapeFwd : TileShape<ROWS, DIMS...> {
   static constexpr bool fwd = true;
+};
+// The forward pass as the agent kernel computes it (agent_kernel.h), bit for bit: weights from the fragment-major copy in natural k
+// order, activations in natural order, the bias added last, log-densities by blocks of four actions.  For the shapes whose
+// collection (fused.hip) computes that way.
+template <int ROWS, int... DIMS>
+struct TileShapeNat : TileShape<ROWS, DIMS...> {
+  static constexpr bool fwd = true, nat = true;
 };
 // Segments the kernel runs for shape S.
 template <class S>
@@ -170,6 +178,8 @@ struct Ctx {
   float l_act[16], l_lo, l_ad, l_rt;
   int tid, lane, wave, s, hh;
   int row0, net;                     // first row of the workgroup's tile
+  const float* obs;                  // inference: the slot's observation rows and values
+  float* val_out;
   int tr, rt0;                       // 128-row tile of the stored arrays that it lies in, and its first row tile there
 };
 
@@ -193,9 +203,17 @@ __device__ __forceinline__ int first_rt(const Ctx<S>& c) {
 // Where the weight blocks of a wave's feature tiles begin in the stream and how far apart its k steps are, in bytes.
 struct WeightPos { int base[4], step[4]; };
 template <class S, int SEG>
-__device__ __forceinline__ WeightPos seg_weights(const Ctx<S>& c) {
+__device__ __forceinline__ WeightPos seg_weights(const Ctx<S>& c, const ChainArgs& args) {
   using G = Seg<S, SEG>;
   WeightPos p;
+  if constexpr (S::nat) {
+#pragma unroll
+    for (int a = 0; a < G::FTW; ++a) {
+      p.base[a] = args.wf_off[c.net][G::layer] + tile_of<G>(c, a) * G::NKS * 1024;
+      p.step[a] = 1024;
+    }
+    return p;
+  }
 #pragma unroll
   for (int a = 0; a < G::FTW; ++a) {
     const int ft = tile_of<G>(c, a);
@@ -233,11 +251,11 @@ __device__ __forceinline__ void issue_weights(Ctx<S>& c, const WeightPos& wseg) 
 }
 // The first DEP k steps of segment SEG (issued before the previous segment's epilogue).
 template <class S, int SEG, int KS = 0>
-__device__ __forceinline__ void issue_first_weights(Ctx<S>& c) {
+__device__ __forceinline__ void issue_first_weights(Ctx<S>& c, const ChainArgs& a) {
   if constexpr (SEG < n_run<S>()) {
     if constexpr (KS < Seg<S, SEG>::DEP) {
-      issue_weights<S, SEG, KS>(c, seg_weights<S, SEG>(c));
-      issue_first_weights<S, SEG, KS + 1>(c);
+      issue_weights<S, SEG, KS>(c, seg_weights<S, SEG>(c, a));
+      issue_first_weights<S, SEG, KS + 1>(c, a);
     }
   }
 }
@@ -378,14 +396,25 @@ __device__ __forceinline__ void tile_epilogue(Ctx<S>& c, const ChainArgs& a) {
         v0 *= elu_grad_f(bf16_lo(h01)); v1 *= elu_grad_f(bf16_hi(h01));
         v2 *= elu_grad_f(bf16_lo(h23)); v3 *= elu_grad_f(bf16_hi(h23));
       } else {
-        v0 = elu_f(v0); v1 = elu_f(v1); v2 = elu_f(v2); v3 = elu_f(v3);      // the bias is in the sums already
+        if constexpr (S::nat) {
+          const float4 b4 = *reinterpret_cast<const float4*>(c.s_bias + S::bias_off(G::layer) + 32 * ft + 8 * q + 4 * c.hh);
+          v0 += b4.x; v1 += b4.y; v2 += b4.z; v3 += b4.w;
+        }                                                                    // else the bias is in the sums already
+        v0 = elu_f(v0); v1 = elu_f(v1); v2 = elu_f(v2); v3 = elu_f(v3);
       }
       w[2 * q] = pack_bf16(v0, v1);
       w[2 * q + 1] = pack_bf16(v2, v3);
     }
-    uint4* x = c.X + ((2 * ft) * S::nrt + rt) * 64 + c.lane;
-    x[0] = make_uint4(w[0], w[1], w[2], w[3]);
-    x[S::nrt * 64] = make_uint4(w[4], w[5], w[6], w[7]);
+    if constexpr (S::nat) {      // quad q: features 8 (q % 2) + 4 hh .. of k step 2 ft + q / 2
+      char* x = reinterpret_cast<char*>(c.X + ((2 * ft) * S::nrt + rt) * 64 + c.s) + 8 * c.hh;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<uint2*>(x + (q / 2) * S::nrt * 1024 + (q % 2) * 512) = make_uint2(w[2 * q], w[2 * q + 1]);
+    } else {
+      uint4* x = c.X + ((2 * ft) * S::nrt + rt) * 64 + c.lane;
+      x[0] = make_uint4(w[0], w[1], w[2], w[3]);
+      x[S::nrt * 64] = make_uint4(w[4], w[5], w[6], w[7]);
+    }
     tile_epilogue<S, SEG, T + 1>(c, a);
   }
 }
@@ -544,7 +573,8 @@ __device__ __forceinline__ void loss_sums(const Ctx<S>& c, const ChainArgs& a) {
 
 // Inference: the head's results of row tile `wave` (lane = row, register i = feature 8 (i / 4) + 4 hh + i % 4) plus
 // the head's bias go out as policy means [rows, act_dim] or as values [rows], and, where actions are asked for, the decision
-// act = mean + exp(log_std) * eps and its log-density: the arithmetic of sample_kernel (model.hip), terms summed in action order.
+// act = mean + exp(log_std) * eps and its log-density: the arithmetic of sample_kernel (model.hip), terms summed in
+// its order.
 // The draws are made beside the head's product by the waves that have no part in it.  (Gather, this kernel and sampling as three
 // launches, 16384 rows of
 // 211:512:512:256:128:20: 49 us, now 38.)
@@ -566,7 +596,7 @@ __device__ __forceinline__ void head_outputs(Ctx<S>& c, const ChainArgs& a, cons
   const int row = c.row0 + 32 * c.wave + c.s, A = a.act_dim;
   const bool ok = row < a.rows;
   if (c.net == 1) {
-    if (ok && c.hh == 0) a.val_out[row] = acc[0] + c.s_bias[HB];
+    if (ok && c.hh == 0) c.val_out[row] = acc[0] + c.s_bias[HB];
     return;
   }
   typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
@@ -601,12 +631,18 @@ __device__ __forceinline__ void head_outputs(Ctx<S>& c, const ChainArgs& a, cons
       term[e] = -0.5f * z[e] * z[e] - ls - 0.918938533204672742f;
     }
     if (ok) store(a.act_out, f0, act);
+    float up[4];                                                             // the upper half's; the lower one's sum goes out
 #pragma unroll
-    for (int e = 0; e < 4; ++e) lp = 8 * q + e < A ? lp + term[e] : lp;      // (the lower half's sum is the one that goes out)
+    for (int e = 0; e < 4; ++e) up[e] = __shfl_xor(term[e], 32, 64);
+    if constexpr (S::nat) {
+      lp += ((term[0] + (8 * q + 1 < A ? term[1] : 0.f)) + (8 * q + 2 < A ? term[2] : 0.f)) + (8 * q + 3 < A ? term[3] : 0.f);
+      if (8 * q + 4 < A)
+        lp += ((up[0] + (8 * q + 5 < A ? up[1] : 0.f)) + (8 * q + 6 < A ? up[2] : 0.f)) + (8 * q + 7 < A ? up[3] : 0.f);
+    } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float t = __shfl_xor(term[e], 32, 64);
-      lp = 8 * q + 4 + e < A ? lp + t : lp;
+      for (int e = 0; e < 4; ++e) lp = 8 * q + e < A ? lp + term[e] : lp;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) lp = 8 * q + 4 + e < A ? lp + up[e] : lp;
     }
   }
   if (a.act_out && ok && c.hh == 0) a.logp_out[row] = lp;
@@ -616,8 +652,8 @@ template <class S, int SEG>
 __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
   if constexpr (SEG < n_run<S>()) {
     using G = Seg<S, SEG>;
-    const WeightPos wseg = seg_weights<S, SEG>(c);
-    if constexpr (!G::bwd && !G::head) {
+    const WeightPos wseg = seg_weights<S, SEG>(c, a);
+    if constexpr (!G::bwd && !G::head && !S::nat) {
       // the accumulators start at the bias (register i of a lane = feature 8 (i / 4) + 4 hh + i % 4 of the tile)
       constexpr int boff = S::bias_off(G::layer);
 #pragma unroll
@@ -649,7 +685,7 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
     } else {
       k_steps<S, SEG, 0>(c, a, wseg);
     }
-    issue_first_weights<S, SEG + 1>(c);
+    issue_first_weights<S, SEG + 1>(c, a);
     __syncthreads();                       // every wave is done with the layer's input
     // this lane's loss inputs: cold loads, issued where a long stretch of arithmetic follows and no younger load is
     // waited for (the memory counter is in order)
@@ -677,9 +713,8 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
 }
 
 template <class S>
-__global__ __launch_bounds__(S::threads, 2) void train_tile_kernel(ChainArgs a) {
+__device__ __forceinline__ void row_tile(const ChainArgs& a, int item, unsigned char* smem_raw) {
   static_assert(S::valid(), "shape not supported by the row-tile trainer kernel");
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   constexpr ChainDims D = S::dims();
   Ctx<S> c;
   c.tid = threadIdx.x;
@@ -688,7 +723,14 @@ __global__ __launch_bounds__(S::threads, 2) void train_tile_kernel(ChainArgs a) 
   c.s = c.lane & 31;
   c.hh = c.lane >> 5;
   c.net = S::fwd ? (int)blockIdx.y + a.net0 : (int)blockIdx.y;
-  c.row0 = blockIdx.x * S::rows;
+  if constexpr (S::fwd) {
+    const int t = item / a.slot_tiles;
+    c.row0 = (item - t * a.slot_tiles) * S::rows;
+    c.obs = t < a.T ? a.b_obs + t * a.obs_step : a.obs_last;
+    c.val_out = t < a.T ? a.val_out + t * a.val_step : a.val_last;
+  } else {
+    c.row0 = item * S::rows;
+  }
   c.tr = c.row0 / 128;
   c.rt0 = c.row0 / 32 & 3;
   c.X = reinterpret_cast<uint4*>(smem_raw);
@@ -714,7 +756,7 @@ __global__ __launch_bounds__(S::threads, 2) void train_tile_kernel(ChainArgs a) 
   for (int gi = 0; gi < NG; ++gi) {
     const int row = c.row0 + 16 * (c.wave + S::waves * gi) + rr;
     srow[gi] = row < a.rows ? row : a.rows - 1;
-    sm[gi] = __builtin_amdgcn_raw_buffer_load_b32(ix, a.idx ? srow[gi] * 4 : 0, 0, 0);
+    if constexpr (!S::fwd) sm[gi] = __builtin_amdgcn_raw_buffer_load_b32(ix, a.idx ? srow[gi] * 4 : 0, 0, 0);
   }
   if constexpr (!S::fwd) {
     // this lane's sample of the head layer (rows past the batch take the last sample, the waves without a part in the loss one
@@ -742,13 +784,13 @@ __global__ __launch_bounds__(S::threads, 2) void train_tile_kernel(ChainArgs a) 
     const int O = a.obs_dim;
     constexpr int NI = (NP + 3) / 4;
 #pragma unroll
-    for (int gi = 0; gi < NG; ++gi) sm[gi] = a.idx ? sm[gi] : srow[gi];
+    for (int gi = 0; gi < NG; ++gi) sm[gi] = !S::fwd && a.idx ? sm[gi] : srow[gi];
     uint4 v[NG][NI];
     if (S::fwd && a.x0_ready == 3) {                     // workgroup-uniform; no branch around a single load
 #pragma unroll
       for (int gi = 0; gi < NG; ++gi) {
         typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
-        const float* orow = a.b_obs + (int64_t)sm[gi] * O;
+        const float* orow = c.obs + (int64_t)sm[gi] * O;
 #pragma unroll
         for (int it = 0; it < NI; ++it) {
           const int j = 4 * it + jj;
@@ -779,8 +821,9 @@ __global__ __launch_bounds__(S::threads, 2) void train_tile_kernel(ChainArgs a) 
     } else {
 #pragma unroll
       for (int gi = 0; gi < NG; ++gi) {
-        const int64_t slot = (int64_t)(sm[gi] / a.n_envs) * a.ld_envs + (sm[gi] % a.n_envs);
-        const float* orow = a.b_obs + slot * O;
+        const float* orow;
+        if constexpr (S::fwd) orow = c.obs + (int64_t)sm[gi] * O;
+        else orow = a.b_obs + ((int64_t)(sm[gi] / a.n_envs) * a.ld_envs + (sm[gi] % a.n_envs)) * O;
 #pragma unroll
         for (int it = 0; it < NI; ++it) {
           const int j = 4 * it + jj;
@@ -797,7 +840,7 @@ __global__ __launch_bounds__(S::threads, 2) void train_tile_kernel(ChainArgs a) 
         }
       }
     }
-    issue_first_weights<S, 0>(c);
+    issue_first_weights<S, 0>(c, a);
     {
       int off = 0;
 #pragma unroll
@@ -839,6 +882,26 @@ __global__ __launch_bounds__(S::threads, 2) void train_tile_kernel(ChainArgs a) 
 }
 
 template <class S>
+__global__ __launch_bounds__(S::threads, 2) void train_tile_kernel(ChainArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  row_tile<S>(a, blockIdx.x, smem_raw);
+}
+// Items one after the other: a launch that its compute units cannot hold keeps kernels of other streams waiting.  The arguments are
+// read again for every item: kept over the loop, they and what follows from them spilled 170 scalar registers.
+template <class S>
+__global__ __launch_bounds__(S::threads, 2) void tile_items_kernel(ChainArgs) {
+  typedef const __attribute__((address_space(4))) ChainArgs KernelArgs;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  KernelArgs* p = (KernelArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  const int items = p->items;
+  for (int item = blockIdx.x; item < items; item += gridDim.x) {
+    asm volatile("" : "+s"(p));
+    row_tile<S>(*(const ChainArgs*)p, item, smem_raw);
+    __syncthreads();
+  }
+}
+
+template <class S>
 bool shape_matches(const ModelLayout& L) {
   constexpr ChainDims D = S::dims();
   if (L.n_layers != D.nl) return false;
@@ -858,19 +921,38 @@ inline bool wide_rows(int rows, int cus) {
 }
 
 template <class S>
-int launch_shape(gmi_instance* g, const ChainArgs& a, int rows, int* tiles_out, double flops, double bytes) {
+int launch_shape(gmi_instance* g, ChainArgs a, int rows, int* tiles_out, double flops, double bytes) {
   static gmi::DeviceSet allowed;
   const size_t lds = S::lds_bytes();
-  const int tiles = (rows + S::rows - 1) / S::rows;
+  int tiles = (rows + S::rows - 1) / S::rows;
   *tiles_out = tiles;
   if (!S::fwd && tiles > gmi::kStatRowsMax) return GMI_ERR_UNSUPPORTED;      // one statistics row per tile
-  if (a.x0_ready == 3 && (!S::fwd || a.idx || a.obs_dim < 4 || a.obs_dim <= S::dims().d[0] - 32)) return GMI_ERR_UNSUPPORTED;
+  if (a.x0_ready == 3 && (!S::fwd || a.obs_dim < 4 || a.obs_dim <= S::dims().d[0] - 32)) return GMI_ERR_UNSUPPORTED;
   if (a.x0_ready == 0 && (a.obs_dim % 4 != 0 || a.obs_dim < 4)) return GMI_ERR_UNSUPPORTED;
-  const int rc = gmi::allow_lds((const void*)train_tile_kernel<S>, lds, g->device, &allowed);
+  int rc = gmi::allow_lds((const void*)train_tile_kernel<S>, lds, g->device, &allowed);
   if (rc != GMI_OK) return rc;
   gmi::ProfScope ps(g, S::fwd ? gmi::kClsFusedAgent : gmi::kClsChainTrain);
   ps.work(flops, bytes);
-  ps.launch(train_tile_kernel<S>, dim3(tiles, S::fwd ? 2 - a.net0 : 2), dim3(S::waves * 64), lds, a);
+  if constexpr (S::fwd) {
+    a.slot_tiles = tiles;
+    a.items = tiles * (a.T + (a.val_last ? 1 : 0));
+    tiles = a.items;
+  }
+  if constexpr (S::nat) {
+    if (a.T > 1 || a.val_last) {
+      static gmi::DeviceSet allowed_items;
+      rc = gmi::allow_lds((const void*)tile_items_kernel<S>, lds, g->device, &allowed_items);
+      if (rc != GMI_OK) return rc;
+      int64_t resident = 1;
+      rc = gmi::resident_groups(g, (const void*)tile_items_kernel<S>, S::threads, lds, &resident);
+      if (rc != GMI_OK) return rc;
+      const int64_t rounds = (a.items + resident - 1) / resident;
+      ps.launch(tile_items_kernel<S>, dim3((unsigned)((a.items + rounds - 1) / rounds)), dim3(S::threads), lds, a);
+      GMI_LAUNCH_CHECK();
+      return GMI_OK;
+    }
+  }
+  ps.launch(train_tile_kernel<S>, dim3(tiles, S::fwd ? 2 - a.net0 : 2), dim3(S::threads), lds, a);
   GMI_LAUNCH_CHECK();
   return GMI_OK;
 }
@@ -879,9 +961,10 @@ int launch_shape(gmi_instance* g, const ChainArgs& a, int rows, int* tiles_out, 
 
 namespace gmi {
 // One function per shape compiled for the row-tile kernel (trainers tile_p<k>.hip, forward-only kernels tile_f<k>.hip): launches it if
-// the model has exactly that shape, GMI_ERR_UNSUPPORTED otherwise; rows == 0 only asks.
+// the model has exactly that shape, GMI_ERR_UNSUPPORTED otherwise; rows == 0 only asks (a forward-only kernel's answer: 1 if it
+// computes as the agent kernel does).
 constexpr int kTileParts = 6;
-constexpr int kTileFwdParts = 2;
+constexpr int kTileFwdParts = 6;
 #define GMI_TILE_PART_DECL(k)                                                                              \
   int launch_tile_part##k(gmi_instance* g, const ModelLayout& L, const gmi_chain::ChainArgs& a, int rows, \
                           int* tiles_out, double flops, double bytes)
@@ -889,11 +972,13 @@ GMI_TILE_PART_DECL(0); GMI_TILE_PART_DECL(1); GMI_TILE_PART_DECL(2); GMI_TILE_PA
 #define GMI_TILE_FWD_PART_DECL(k)                                                                              \
   int launch_tile_fwd_part##k(gmi_instance* g, const ModelLayout& L, const gmi_chain::ChainArgs& a, int rows, \
                               int* tiles_out, double flops, double bytes)
-GMI_TILE_FWD_PART_DECL(0); GMI_TILE_FWD_PART_DECL(1);
-#define GMI_TILE_FWD_PART_DEFINE(k, ...)                                                          \
+GMI_TILE_FWD_PART_DECL(0); GMI_TILE_FWD_PART_DECL(1); GMI_TILE_FWD_PART_DECL(2); GMI_TILE_FWD_PART_DECL(3);
+GMI_TILE_FWD_PART_DECL(4); GMI_TILE_FWD_PART_DECL(5);
+#define GMI_TILE_FWD_PART_DEFINE(k, SHAPE, ...)                                                   \
   GMI_TILE_FWD_PART_DECL(k) {                                                                     \
-    using S = gmi_tile::TileShapeFwd<64, __VA_ARGS__>;                                            \
+    using S = gmi_tile::SHAPE<64, __VA_ARGS__>;                                                   \
     if (!gmi_tile::shape_matches<S>(L)) return GMI_ERR_UNSUPPORTED;                               \
+    *tiles_out = S::nat ? 1 : 0;                                                                  \
     if (rows == 0) return GMI_OK;                                                                 \
     return gmi_tile::launch_shape<S>(g, a, rows, tiles_out, flops, bytes);                        \
   }

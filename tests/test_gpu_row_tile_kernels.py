@@ -174,6 +174,36 @@ def test_row_tile_decisions_match_the_per_layer_path(g, obs, act, hidden, n, shi
     g.gmi_destroy(masked)
 
 
+@pytest.mark.parametrize("obs,act,hidden,shift", [
+    (108, 21, [400, 200, 100], 0), (107, 32, [400, 200, 100], 1), (97, 1, [200, 400, 100], 3), (110, 4, [200, 400, 100], 0),
+    (57, 6, [256, 128, 64], 0), (62, 31, [256, 128, 64], 2), (23, 9, [256, 128, 64], 0), (5, 2, [256, 128, 64], 1)])
+@pytest.mark.parametrize("n", [257, 321])
+def test_row_tile_decisions_are_those_of_the_agent_kernel(g, inst, obs, act, hidden, n, shift):
+    """The same rows on the whole device (the agent kernel) and on 16 compute units (enough rows for the row-tile kernel): bit for bit."""
+    from paper_2206_08482_amd.instances import cu_masks
+    dev = torch.device("cuda:0")
+    masked = g.gmi_create(cu_masks(256, [16])[0])
+    theta = torch.tensor(syn.make_model_params(obs, act, hidden, 5, policy_head_scale=0.5), device=dev)
+    desc = g.model_desc(obs, act, list(hidden), g.dtype_code("bf16"), n)
+    shadow = torch.zeros(g.gmi_model_shadow_bytes(desc), dtype=torch.uint8, device=dev)
+    x = torch.randn(n * obs + shift, generator=torch.Generator().manual_seed(n)).to(dev)[shift:]
+    torch.cuda.synchronize()
+    out = []
+    for h in (inst, masked):
+        model = g.gmi_model_bind(h, desc, theta, shadow)
+        g.gmi_model_refresh_shadow(h, model)
+        o = [torch.full(s, float("nan"), device=dev) for s in ((n, act), (n,), (n,), (n, act), (n,))]
+        torch.cuda.synchronize()
+        g.agent_act(h, model, x, n, 42, 9, 100, *o[:4])
+        g.agent_value(h, model, x, n, o[4])
+        g.gmi_sync(h)
+        out.append([t.cpu().numpy() for t in o])
+        g.gmi_model_destroy(model)
+    g.gmi_destroy(masked)
+    for a, b in zip(*out):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("obs,act,hidden,n", [
     (211, 20, [512, 512, 256, 128], 32769),   # 128 rows on 16 waves
     (60, 8, [256, 128, 64], 32801),           # two 128-row tiles per compute unit
