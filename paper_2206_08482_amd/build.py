@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libgmidrl.so")
 # the slowest compiles first, so that they overlap all the others
-SOURCES = ["fused.hip", "fp8.hip", "agent.hip", "mlp.hip", "tile_p0.hip", "tile_p1.hip", "tile_p2.hip", "tile_p3.hip", "tile_p4.hip", "tile_p5.hip", "tile_f0.hip", "tile_f1.hip", "tile_f2.hip", "tile_f3.hip", "tile_f4.hip", "tile_f5.hip",
+SOURCES = ["fused.hip", "fp8.hip", "agent.hip", "mlp.hip", "tile_p0.hip", "tile_p1.hip", "tile_p2.hip", "tile_p3.hip", "tile_p4.hip", "tile_p5.hip", "tile_f0.hip", "tile_f1.hip", "tile_f2.hip", "tile_f3.hip", "tile_f4.hip", "tile_f5.hip", "tile_q0.hip", "tile_q1.hip", "tile_q2.hip", "tile_q3.hip", "tile_q4.hip",
            "core.hip", "env.hip", "experience.hip", "model.hip", "update.hip", "peaks.hip", "select.hip", "channels.hip", "chain.hip", "f32.hip", "resident.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Wno-unused-value", "-Wno-unused-result", "-fhip-fp32-correctly-rounded-divide-sqrt",

@@ -26,7 +26,6 @@ using namespace gmi_chain;
 
 constexpr int kMaxLayers = GMI_MAX_HIDDEN + 1;
 constexpr size_t kLdsMax = 160 * 1024;
-typedef int intx8 __attribute__((ext_vector_type(8)));
 
 struct AgentLayer {
   const uint4* w;          // fragment-major W
@@ -65,17 +64,11 @@ struct Bf16 {
   static __device__ __forceinline__ void store4(unsigned char* p, float a, float b, float c, float d) {
     *reinterpret_cast<uint2*>(p) = make_uint2(pack_bf16(a, b), pack_bf16(c, d));
   }
+  static __device__ __forceinline__ void store_elu4(unsigned char* p, float a, float b, float c, float d) {
+    store4(p, elu_f(a), elu_f(b), elu_f(c), elu_f(d));
+  }
   static __device__ __forceinline__ void store1(unsigned char* p, float a) { *reinterpret_cast<uint16_t*>(p) = (uint16_t)pack_bf16(a, 0.f); }
 };
-
-__device__ __forceinline__ uint32_t to_e4m3x4(float a, float b, float c, float d) {
-  // the conversion rounds to nearest even; its inputs are kept within the format's range, so it never overflows
-  a = __builtin_amdgcn_fmed3f(a, -448.f, 448.f); b = __builtin_amdgcn_fmed3f(b, -448.f, 448.f);
-  c = __builtin_amdgcn_fmed3f(c, -448.f, 448.f); d = __builtin_amdgcn_fmed3f(d, -448.f, 448.f);
-  int v = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, 0, false);
-  v = __builtin_amdgcn_cvt_pk_fp8_f32(c, d, v, true);
-  return (uint32_t)v;
-}
 
 // 32x32x64 products of E4M3: a lane's operand is 32 consecutive k of its row.
 struct Fp8 {
@@ -92,6 +85,9 @@ struct Fp8 {
   }
   static __device__ __forceinline__ void store4(unsigned char* p, float a, float b, float c, float d) {
     *reinterpret_cast<uint32_t*>(p) = to_e4m3x4(a, b, c, d);
+  }
+  static __device__ __forceinline__ void store_elu4(unsigned char* p, float a, float b, float c, float d) {
+    *reinterpret_cast<uint32_t*>(p) = elu_e4m3x4(a, b, c, d);
   }
   static __device__ __forceinline__ void store1(unsigned char* p, float a) { *p = (unsigned char)to_e4m3x4(a, 0.f, 0.f, 0.f); }
 };
@@ -218,7 +214,7 @@ __device__ __forceinline__ void net_layers(const AgentLayer* N, int nl, Ring<P, 
               v[0] += b.x; v[1] += b.y; v[2] += b.z; v[3] += b.w;
             }
             if (!head) {
-              P::store4(y + r * sy + f * P::size, elu_f(v[0]), elu_f(v[1]), elu_f(v[2]), elu_f(v[3]));
+              P::store_elu4(y + r * sy + f * P::size, v[0], v[1], v[2], v[3]);
             } else {
               float* d = s_head + r * ho + f;
 #pragma unroll

@@ -9,6 +9,7 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 typedef float float2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+typedef int intx8 __attribute__((ext_vector_type(8)));
 
 using gmi::elu_f;
 // ELU'(z) from the stored output h = ELU(z) >= -1: 1 if h > 0 else h + 1, as one add with the [0, 1] clamp
@@ -20,7 +21,33 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
+__device__ __forceinline__ uint32_t to_e4m3x4(float a, float b, float c, float d) {
+  // the conversion rounds to nearest even; its inputs are kept within the format's range, so it never overflows
+  a = __builtin_amdgcn_fmed3f(a, -448.f, 448.f); b = __builtin_amdgcn_fmed3f(b, -448.f, 448.f);
+  c = __builtin_amdgcn_fmed3f(c, -448.f, 448.f); d = __builtin_amdgcn_fmed3f(d, -448.f, 448.f);
+  int v = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, 0, false);
+  v = __builtin_amdgcn_cvt_pk_fp8_f32(c, d, v, true);
+  return (uint32_t)v;
+}
+
 // ---------------------------------------------------------------------------------------------------------
+// ELU, then E4M3.  Its results are never below -1, so the upper bound of the format's range is the only one to keep, and one median of
+// three is both ELU's maximum and that bound.
+__device__ __forceinline__ uint32_t elu_e4m3x4(float a, float b, float c, float d) {
+  float log2e, most;
+  asm("s_mov_b32 %0, 0x3fb8aa3b" : "=s"(log2e));      // 1.44269504
+  asm("s_mov_b32 %0, 0x43e00000" : "=s"(most));       // 448
+  auto elu = [&](float z) {
+    const float e = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(z * log2e), 0.f, 1.f) - 1.0f;
+    float y;
+    asm("v_med3_f32 %0, %1, %2, %3" : "=v"(y) : "v"(z), "v"(e), "s"(most));
+    return y;
+  };
+  int v = __builtin_amdgcn_cvt_pk_fp8_f32(elu(a), elu(b), 0, false);
+  v = __builtin_amdgcn_cvt_pk_fp8_f32(elu(c), elu(d), v, true);
+  return (uint32_t)v;
+}
+
 // The plan: which 1 KiB weight blocks the row-tile kernel (tile_kernel.h) consumes in which order.  Pure functions of the padded layer
 // widths d[0..nl] (d[0] = input, d[nl] = head), used at compile time by the kernel and at run time by the
 // host when it describes the stream to the packing kernel.
@@ -82,7 +109,8 @@ struct ChainArgs {
   int64_t obs_step, val_step;
   const float* obs_last;
   float* val_last;
-  int wf_off[2][GMI_MAX_HIDDEN + 1];               // TileShapeNat: bytes from wstream to a layer's fragment-major weights
+  int wf_off[2][GMI_MAX_HIDDEN + 1];               // TileShapeNat, TileShapeFp8: bytes from wstream to a layer's weights
+  const float* scale;                              // TileShapeFp8: [2 nl]
   float* val_out;                                  // [rows] values
   uint16_t* x0b;                                   // the minibatch's observations as the first layer's operand blocks, written here for
                                                    // the weight-gradient kernel (by the policy net's workgroups)

@@ -15,6 +15,7 @@
 // 1).  Results therefore follow an exact-sum model of the same roundings to ~1e-4 per activation, not to fp32
 // rounding.
 #include "agent_kernel.h"
+#include "tile_kernel.h"
 
 #include <vector>
 
@@ -126,6 +127,46 @@ int table_of(gmi_fp8* w, const float* params, Fp8Table* t) {
   return GMI_OK;
 }
 
+typedef int (*fp8_part_fn)(gmi_instance*, const ModelLayout&, const gmi_chain::ChainArgs&, int);
+const fp8_part_fn kTileParts[gmi::kTileFp8Parts] = {gmi::launch_tile_fp8_part0, gmi::launch_tile_fp8_part1, gmi::launch_tile_fp8_part2,
+                                                    gmi::launch_tile_fp8_part3, gmi::launch_tile_fp8_part4};
+
+// The row-tile kernel computes in agent_kernel's order, so either may serve a call.  agent_kernel / this one, us:
+//   60:256:128:64:8 8.4 / 7.2 for 64 rows, 8.7 / 7.6 for 4096, 10.2 / 7.8 for 8192, 32 / 24 for 65536, 111 / 83 for 262144, on 64 compute
+//     units 8.5 / 7.2 for 256;
+//   108:400:200:100:21 10.8 / 13.9 for 512 rows, 13.0 / 14.1 for 5000, 14.0 / 14.6 for 8192, 17.6 / 15.2 for 12000, 67 / 58 for 65536, on 64
+//     compute units 12.4 / 13.9 for 2048, 16.6 / 14.3 for 4096;
+//   211:512:512:256:128:20 14 / 19 for 512 rows, 19.4 / 19.8 for 5000, 21.2 / 21.0 for 8192, 28 / 23 for 12000, 126 / 103 for 65536, on 64
+//     compute units 18.2 / 19.3 for 2048, 28.5 / 20.4 for 4096.
+// Layers of more than 8 feature tiles, which its 4 waves take 4 at a time, beyond 32 rows per compute unit; narrower models always.
+bool use_tile(const gmi_instance* g, const ModelLayout& L, int rows) {
+  return L.obs_dim >= 4 && (pad64(L.max_width_pad) <= 256 || rows > 32 * (int64_t)g->cu_count);
+}
+
+// The decision through the row-tile kernel (tile_kernel.h): GMI_ERR_UNSUPPORTED if none is compiled for the shape.
+int launch_tile(gmi_instance* g, const gmi_fp8* w, const AgentArgs& in) {
+  const ModelLayout& L = w->L;
+  gmi_chain::ChainArgs a = {};
+  for (int net = 0; net < 2; ++net) {
+    a.wstream[net] = w->base;
+    for (int l = 0; l < L.n_layers; ++l) {
+      a.bias[net][l] = in.l[net][l].bias;
+      a.wf_off[net][l] = (int)w->w_off[net][l];
+    }
+  }
+  a.scale = in.l[0][0].scale;
+  a.log_std = in.log_std;
+  a.b_obs = in.obs; a.obs_dim = in.O; a.act_dim = in.A;
+  a.T = 1;
+  a.x0_ready = 3;
+  a.rows = in.n;
+  a.mu_out = in.mu_out; a.val_out = in.value; a.act_out = in.act; a.logp_out = in.logp;
+  a.k0 = in.k0; a.k1 = in.k1; a.step = in.step; a.env_offset = in.env_offset;
+  int rc = GMI_ERR_UNSUPPORTED;
+  for (int p = 0; p < gmi::kTileFp8Parts && rc == GMI_ERR_UNSUPPORTED; ++p) rc = kTileParts[p](g, L, a, in.n);
+  return rc;
+}
+
 }  // namespace
 
 extern "C" int gmi_fp8_bind(gmi_t g, const gmi_model_desc* d, gmi_fp8_t* out) {
@@ -222,6 +263,10 @@ extern "C" int agent_act_fp8(gmi_t g, gmi_fp8_t w, const float* obs, int32_t n_r
   a.k0 = (uint32_t)seed; a.k1 = (uint32_t)(seed >> 32); a.step = step; a.env_offset = env_offset;
   a.log_std = reinterpret_cast<const float*>(w->base + w->logstd_off);
   a.obs = obs; a.act = act; a.logp = logp; a.value = value; a.mu_out = mu;
+  if (use_tile(g, L, n_rows)) {
+    const int rc = launch_tile(g, w, a);
+    if (rc != GMI_ERR_UNSUPPORTED) return rc;
+  }
   // draws and densities in the same launch unless the action is so wide that they do not fit beside a 32-row tile
   const bool sample = agent_lds<Fp8>(a, 1, true) <= kLdsMax;
   if (!sample) { a.act = nullptr; a.mu_out = mu_ws; }

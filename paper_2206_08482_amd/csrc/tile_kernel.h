@@ -42,13 +42,20 @@ using namespace gmi_chain;
 constexpr int kScrBytes = 32 * 33 * 4;      // a loss wave's transposition buffer
 constexpr int kHPre = 4;          // tiles whose stored activations are fetched ahead in an input-gradient epilogue
 
+__device__ __forceinline__ intx8 join8(const uint4& a, const uint4& b) {
+  const intx8 r = {(int)a.x, (int)a.y, (int)a.z, (int)a.w, (int)b.x, (int)b.y, (int)b.z, (int)b.w};
+  return r;
+}
+
 // ROWS: samples per workgroup, 128 (8 waves) or 64 (4 waves).
 template <int ROWS, int... DIMS>
 struct TileShape {
   static constexpr int rows = ROWS, nrt = ROWS / 32, waves = 2 * nrt, threads = 64 * waves;
   static constexpr int acc_ft = 16 / waves, ring = 8;      // feature tiles of a wave; weight blocks in flight per wave
   static constexpr bool fwd = false;      // TileShapeFwd, TileShapeNat: the forward pass alone (inference)
-  static constexpr bool nat = false;      // TileShapeNat
+  static constexpr bool nat = false;      // TileShapeNat, TileShapeFp8
+  static constexpr bool fp8 = false;      // TileShapeFp8
+  static constexpr bool lp_blocks = false;      // log-densities by blocks of four actions
   static constexpr int NL = (int)sizeof...(DIMS) - 1;
   static constexpr ChainDims dims() { return ChainDims{NL, {DIMS...}}; }
   static constexpr int nseg() { return cd_nseg(dims()); }
@@ -92,7 +99,23 @@ struct TileShapeFwd : TileShape<ROWS, DIMS...> {
 // collection (fused.hip) computes that way.
 template <int ROWS, int... DIMS>
 struct TileShapeNat : TileShape<ROWS, DIMS...> {
-  static constexpr bool fwd = true, nat = true;
+  static constexpr bool fwd = true, nat = true, lp_blocks = true;
+};
+// The same in fp8 (E4M3): agent_kernel's results for fp8, bit for bit.  A k step is 64 wide and its operands are two blocks: a lane's
+// 32 k values of its row, 16 per block.
+template <int ROWS, int... DIMS>
+struct TileShapeFp8 : TileShape<ROWS, DIMS...> {
+  static constexpr bool fwd = true, nat = true, fp8 = true;
+  static constexpr int ring = 16;
+  static constexpr size_t scr_offset() { return TileShape<ROWS, DIMS...>::scr_offset() / 2; }
+  static constexpr size_t x_bytes() { return TileShape<ROWS, DIMS...>::x_bytes() / 2; }
+  static constexpr size_t lds_bytes() { return TileShape<ROWS, DIMS...>::lds_bytes() - x_bytes(); }
+  static constexpr bool valid() {
+    const ChainDims D = TileShape<ROWS, DIMS...>::dims();
+    for (int l = 0; l < D.nl; ++l)
+      if (D.d[l] % 64 != 0) return false;
+    return TileShape<ROWS, DIMS...>::valid() && x_bytes() >= scr_offset() + (size_t)TileShape<ROWS, DIMS...>::nrt * kScrBytes;
+  }
 };
 // Segments the kernel runs for shape S.
 template <class S>
@@ -101,7 +124,8 @@ constexpr int n_run() { return S::fwd ? S::NL : S::nseg(); }
 template <class S, int SEG>
 struct Seg {
   static constexpr ChainDims D = S::dims();
-  static constexpr int K = cd_K(D, SEG), F = cd_F(D, SEG), NKS = K / 16, NFT = F / 32;
+  static constexpr int K = cd_K(D, SEG), F = cd_F(D, SEG), NKS = K / (S::fp8 ? 64 : 16), NFT = F / 32;
+  static constexpr int NP = S::fp8 ? 2 : 1;               // blocks of an operand
   static constexpr bool head = SEG == S::NL - 1;
   static constexpr bool bwd = SEG >= S::NL;
   static constexpr bool last = !S::fwd && SEG == S::nseg() - 1;
@@ -114,8 +138,8 @@ struct Seg {
   static constexpr bool even = NFT == NWF * FTW;          // every wave has FTW tiles of its own
   static constexpr int GS = NFT >= 4 ? 4 : NFT;           // tiles per group of the stream (chain_stream.h) ..
   static constexpr bool one_gs = NFT % 4 == 0 || NFT <= 2;      // .. if all its groups are alike
-  static constexpr int DEP = S::ring / FTW < NKS ? S::ring / FTW : NKS;      // k steps of weight blocks in flight
-  static constexpr int XD = FTW >= 2 ? 1 : 2;             // k steps the activation blocks are read ahead (a k step of
+  static constexpr int DEP = S::ring / (FTW * NP) < NKS ? S::ring / (FTW * NP) : NKS;      // k steps of weight blocks in flight
+  static constexpr int XD = FTW >= 2 || S::fp8 ? 1 : 2;             // k steps the activation blocks are read ahead (a k step of
                                                           // fewer products is shorter than an LDS round trip)
   static constexpr int blk0 = S::seg_blk0(SEG);
   // The segment's input, which the previous segment's epilogue left in LDS, goes to memory block by block (for the
@@ -163,7 +187,7 @@ template <class S>
 struct Ctx {
   floatx16 acc[S::acc_ft][S::nrt];
   uint4 wq[S::ring];                   // weight blocks of k steps g .. g + DEP - 1: block (ks, a) at (ks % DEP) * FTW + a
-  uint4 xq[3][S::nrt];                    // activation blocks of k steps g .. g + XD (ring indexed by k step % 3)
+  uint4 xq[S::fp8 ? 2 : 3][S::nrt][S::fp8 ? 2 : 1];                    // activation blocks of k steps g .. g + XD (ring indexed by k step)
   uint4 sx;                          // block of the activation area on its way to memory (store_x)
   uint4 hq[kHPre + 1][2];            // stored activations of the tiles ahead (input-gradient epilogues)
   const uint4* wnet;                 // this net's stream
@@ -178,6 +202,7 @@ struct Ctx {
   float l_act[16], l_lo, l_ad, l_rt;
   int tid, lane, wave, s, hh;
   int row0, net;                     // first row of the workgroup's tile
+  float scale;                       // fp8: what the layer's weight codes are multiples of
   const float* obs;                  // inference: the slot's observation rows and values
   float* val_out;
   int tr, rt0;                       // 128-row tile of the stored arrays that it lies in, and its first row tile there
@@ -209,8 +234,8 @@ __device__ __forceinline__ WeightPos seg_weights(const Ctx<S>& c, const ChainArg
   if constexpr (S::nat) {
 #pragma unroll
     for (int a = 0; a < G::FTW; ++a) {
-      p.base[a] = args.wf_off[c.net][G::layer] + tile_of<G>(c, a) * G::NKS * 1024;
-      p.step[a] = 1024;
+      p.base[a] = args.wf_off[c.net][G::layer] + tile_of<G>(c, a) * G::NKS * G::NP * 1024;
+      p.step[a] = G::NP * 1024;
     }
     return p;
   }
@@ -238,15 +263,17 @@ __device__ __forceinline__ uint4* x_block(const Ctx<S>& c, int ks, int rt) {
   return reinterpret_cast<uint4*>(reinterpret_cast<char*>(c.X) + c.xo[ks * S::nrt / 64] + rt * 1024) + (ks * S::nrt % 64) * 64;
 }
 template <class S, int SEG, int KS>
-__device__ __forceinline__ uint4 weight_block(const Ctx<S>& c, const WeightPos& w, int ta) {
-  return gmi::load_uniform(c.wnet, w.base[ta] + KS * w.step[ta], c.lane16);
+__device__ __forceinline__ uint4 weight_block(const Ctx<S>& c, const WeightPos& w, int ta, int p) {
+  return gmi::load_uniform(c.wnet, w.base[ta] + KS * w.step[ta] + p * 1024, c.lane16);
 }
 template <class S, int SEG, int KS>
 __device__ __forceinline__ void issue_weights(Ctx<S>& c, const WeightPos& wseg) {
   using G = Seg<S, SEG>;
   if constexpr (KS < G::NKS) {
 #pragma unroll
-    for (int a = 0; a < G::FTW; ++a) c.wq[(KS % G::DEP) * G::FTW + a] = weight_block<S, SEG, KS>(c, wseg, a);
+    for (int a = 0; a < G::FTW; ++a)
+#pragma unroll
+      for (int p = 0; p < G::NP; ++p) c.wq[((KS % G::DEP) * G::FTW + a) * G::NP + p] = weight_block<S, SEG, KS>(c, wseg, a, p);
   }
 }
 // The first DEP k steps of segment SEG (issued before the previous segment's epilogue).
@@ -260,12 +287,16 @@ __device__ __forceinline__ void issue_first_weights(Ctx<S>& c, const ChainArgs& 
   }
 }
 
+template <class S>
+constexpr int kXRing = S::fp8 ? 2 : 3;
 template <class S, int SEG, int KS>
 __device__ __forceinline__ void read_x(Ctx<S>& c) {
   using G = Seg<S, SEG>;
   if constexpr (KS < G::NKS) {
 #pragma unroll
-    for (int b = 0; b < G::RT; ++b) c.xq[KS % 3][b] = *x_block(c, KS, first_rt<G>(c) + b);
+    for (int b = 0; b < G::RT; ++b)
+#pragma unroll
+      for (int p = 0; p < G::NP; ++p) c.xq[KS % kXRing<S>][b][p] = *x_block(c, KS * G::NP + p, first_rt<G>(c) + b);
   }
 }
 
@@ -314,12 +345,12 @@ __device__ __forceinline__ uint4* store_x_array(const Ctx<S>& c, const ChainArgs
 template <class S, int SEG, int KS, int I>
 __device__ __forceinline__ void aux_op(Ctx<S>& c, const ChainArgs& a) {
   using G = Seg<S, SEG>;
-  if constexpr (I < G::RT) {
+  if constexpr (I < G::RT * G::NP) {
     if constexpr (KS + G::XD < G::NKS)
-      c.xq[(KS + G::XD) % 3][I] = *x_block(c, KS + G::XD, first_rt<G>(c) + I);
+      c.xq[(KS + G::XD) % kXRing<S>][I / G::NP][I % G::NP] = *x_block(c, (KS + G::XD) * G::NP + I % G::NP, first_rt<G>(c) + I / G::NP);
   } else if constexpr (G::store_x) {
     static_assert(G::NKS % 2 == 0, "a wave moves a block every two k steps");
-    if constexpr (I == G::RT) {
+    if constexpr (I == G::RT * G::NP) {
       if constexpr (KS % 2 == 0) c.sx = *x_block(c, KS, c.wave);      // the second half of the waves: k step KS + 1
     } else if constexpr (KS % 2 == 1) {
       store_block(store_x_array<S, SEG>(c, a) + block_word(c.tr, G::NKS, c.wave / S::nrt, c.rt0 + c.wave % S::nrt), c.lane16, c.sx,
@@ -330,7 +361,7 @@ __device__ __forceinline__ void aux_op(Ctx<S>& c, const ChainArgs& a) {
 template <class S, int SEG, int KS, int FIDX, int I>
 __device__ __forceinline__ void aux_slot(Ctx<S>& c, const ChainArgs& a) {
   using G = Seg<S, SEG>;
-  constexpr int NAUX = G::RT + 2, NFREE = G::FTW * (G::RT - 1);
+  constexpr int NAUX = G::RT * G::NP + 2, NFREE = G::FTW * (G::RT - 1);
   if constexpr (I < NAUX) {
     if constexpr (I % NFREE == FIDX) aux_op<S, SEG, KS, I>(c, a);
     aux_slot<S, SEG, KS, FIDX, I + 1>(c, a);
@@ -346,16 +377,23 @@ __device__ __forceinline__ void k_products(Ctx<S>& c, const ChainArgs& a, const 
   using G = Seg<S, SEG>;
   if constexpr (M < G::FTW * G::RT) {
     constexpr int ta = M / G::RT, tb = M % G::RT;
-    c.acc[ta][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-        __builtin_bit_cast(bf16x8, c.wq[(KS % G::DEP) * G::FTW + ta]), __builtin_bit_cast(bf16x8, c.xq[KS % 3][tb]),
-        c.acc[ta][tb], 0, 0, 0);
+    const uint4* w = c.wq + ((KS % G::DEP) * G::FTW + ta) * G::NP;
+    const uint4(&x)[G::NP] = c.xq[KS % kXRing<S>][tb];
+    if constexpr (S::fp8)
+      c.acc[ta][tb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(join8(w[0], w[1]), join8(x[0], x[1]), c.acc[ta][tb], 0, 0, 0, 0, 0, 0);
+    else
+      c.acc[ta][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w[0]), __builtin_bit_cast(bf16x8, x[0]),
+                                                              c.acc[ta][tb], 0, 0, 0);
     if constexpr (tb == G::RT - 1) {
       if constexpr (KS + G::DEP < G::NKS)
-        c.wq[(KS % G::DEP) * G::FTW + ta] = weight_block<S, SEG, KS + G::DEP>(c, wseg, ta);
+#pragma unroll
+        for (int p = 0; p < G::NP; ++p)
+          c.wq[((KS % G::DEP) * G::FTW + ta) * G::NP + p] = weight_block<S, SEG, KS + G::DEP>(c, wseg, ta, p);
       if constexpr (G::RT == 1) {                                 // the head: one product per k step
         aux_op<S, SEG, KS, 0>(c, a);
         aux_op<S, SEG, KS, 1>(c, a);
         aux_op<S, SEG, KS, 2>(c, a);
+        if constexpr (G::NP > 1) aux_op<S, SEG, KS, 3>(c, a);
       }
     } else {
       aux_slot<S, SEG, KS, ta * (G::RT - 1) + tb, 0>(c, a);
@@ -396,16 +434,27 @@ __device__ __forceinline__ void tile_epilogue(Ctx<S>& c, const ChainArgs& a) {
         v0 *= elu_grad_f(bf16_lo(h01)); v1 *= elu_grad_f(bf16_hi(h01));
         v2 *= elu_grad_f(bf16_lo(h23)); v3 *= elu_grad_f(bf16_hi(h23));
       } else {
-        if constexpr (S::nat) {
+        if constexpr (S::fp8) {
+          const float4 b4 = *reinterpret_cast<const float4*>(c.s_bias + S::bias_off(G::layer) + 32 * ft + 8 * q + 4 * c.hh);
+          v0 = fmaf(v0, c.scale, b4.x); v1 = fmaf(v1, c.scale, b4.y); v2 = fmaf(v2, c.scale, b4.z); v3 = fmaf(v3, c.scale, b4.w);
+        } else if constexpr (S::nat) {
           const float4 b4 = *reinterpret_cast<const float4*>(c.s_bias + S::bias_off(G::layer) + 32 * ft + 8 * q + 4 * c.hh);
           v0 += b4.x; v1 += b4.y; v2 += b4.z; v3 += b4.w;
         }                                                                    // else the bias is in the sums already
-        v0 = elu_f(v0); v1 = elu_f(v1); v2 = elu_f(v2); v3 = elu_f(v3);
+        if constexpr (!S::fp8) { v0 = elu_f(v0); v1 = elu_f(v1); v2 = elu_f(v2); v3 = elu_f(v3); }
       }
-      w[2 * q] = pack_bf16(v0, v1);
-      w[2 * q + 1] = pack_bf16(v2, v3);
+      if constexpr (S::fp8) {
+        w[q] = elu_e4m3x4(v0, v1, v2, v3);
+      } else {
+        w[2 * q] = pack_bf16(v0, v1);
+        w[2 * q + 1] = pack_bf16(v2, v3);
+      }
     }
-    if constexpr (S::nat) {      // quad q: features 8 (q % 2) + 4 hh .. of k step 2 ft + q / 2
+    if constexpr (S::fp8) {      // word q: features 8 q + 4 hh .. of the tile.  The halves of the wave trade words: the lower one gets
+                                 // quads 0 and 1 of both, the first block's 16 bytes of its row, the upper one quads 2 and 3
+      const auto u = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false), v = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+      c.X[((ft / 2 * 2 + c.hh) * S::nrt + rt) * 64 + c.s + 32 * (ft & 1)] = make_uint4(u[0], u[1], v[0], v[1]);
+    } else if constexpr (S::nat) {      // quad q: features 8 (q % 2) + 4 hh .. of k step 2 ft + q / 2
       char* x = reinterpret_cast<char*>(c.X + ((2 * ft) * S::nrt + rt) * 64 + c.s) + 8 * c.hh;
 #pragma unroll
       for (int q = 0; q < 4; ++q)
@@ -596,7 +645,7 @@ __device__ __forceinline__ void head_outputs(Ctx<S>& c, const ChainArgs& a, cons
   const int row = c.row0 + 32 * c.wave + c.s, A = a.act_dim;
   const bool ok = row < a.rows;
   if (c.net == 1) {
-    if (ok && c.hh == 0) c.val_out[row] = acc[0] + c.s_bias[HB];
+    if (ok && c.hh == 0) c.val_out[row] = S::fp8 ? fmaf(acc[0], c.scale, c.s_bias[HB]) : acc[0] + c.s_bias[HB];
     return;
   }
   typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
@@ -619,7 +668,10 @@ __device__ __forceinline__ void head_outputs(Ctx<S>& c, const ChainArgs& a, cons
     const int f0 = 8 * q + 4 * c.hh;
     float m[4], act[4], term[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) m[e] = acc[4 * q + e] + c.s_bias[HB + f0 + e];
+    for (int e = 0; e < 4; ++e) {
+      const float b = c.s_bias[HB + f0 + e];
+      m[e] = S::fp8 ? fmaf(acc[4 * q + e], c.scale, b) : acc[4 * q + e] + b;
+    }
     if (a.mu_out && ok) store(a.mu_out, f0, m);
     if (!a.act_out) continue;
     const float4 z4 = reinterpret_cast<const float4*>(c.scr)[q * 64 + c.lane];
@@ -634,7 +686,7 @@ __device__ __forceinline__ void head_outputs(Ctx<S>& c, const ChainArgs& a, cons
     float up[4];                                                             // the upper half's; the lower one's sum goes out
 #pragma unroll
     for (int e = 0; e < 4; ++e) up[e] = __shfl_xor(term[e], 32, 64);
-    if constexpr (S::nat) {
+    if constexpr (S::lp_blocks) {
       lp += ((term[0] + (8 * q + 1 < A ? term[1] : 0.f)) + (8 * q + 2 < A ? term[2] : 0.f)) + (8 * q + 3 < A ? term[3] : 0.f);
       if (8 * q + 4 < A)
         lp += ((up[0] + (8 * q + 5 < A ? up[1] : 0.f)) + (8 * q + 6 < A ? up[2] : 0.f)) + (8 * q + 7 < A ? up[3] : 0.f);
@@ -653,6 +705,7 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
   if constexpr (SEG < n_run<S>()) {
     using G = Seg<S, SEG>;
     const WeightPos wseg = seg_weights<S, SEG>(c, a);
+    if constexpr (S::fp8) c.scale = a.scale[c.net * S::NL + G::layer];
     if constexpr (!G::bwd && !G::head && !S::nat) {
       // the accumulators start at the bias (register i of a lane = feature 8 (i / 4) + 4 hh + i % 4 of the tile)
       constexpr int boff = S::bias_off(G::layer);
@@ -710,6 +763,17 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
     }
     run_segment<S, SEG + 1>(c, a);
   }
+}
+
+// Floats f0 .. f0 + 3 of a row of O (>= 4) floats at any 4-byte address, zero beyond it; `ragged`: whether f0 + 3 may lie beyond.
+__device__ __forceinline__ void row_quad(const float* row, int f0, int O, bool ragged, float (&f)[4]) {
+  typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+  const int back = ragged ? f0 - (f0 < O - 4 ? f0 : O - 4) : 0;
+  const float4u t = *reinterpret_cast<const float4u*>(row + f0 - back);
+  f[0] = back == 0 ? t.x : back == 1 ? t.y : back == 2 ? t.z : back == 3 ? t.w : 0.f;
+  f[1] = back == 0 ? t.y : back == 1 ? t.z : back == 2 ? t.w : 0.f;
+  f[2] = back == 0 ? t.z : back == 1 ? t.w : 0.f;
+  f[3] = back == 0 ? t.w : 0.f;
 }
 
 template <class S>
@@ -780,30 +844,34 @@ __device__ __forceinline__ void row_tile(const ChainArgs& a, int item, unsigned 
     // 16-byte piece jj + 4 it of row 16 g + rr: 16 lanes write 256 consecutive bytes of LDS, 4 lanes read 64
     // consecutive bytes of a row.  The policy net's workgroups also leave the same blocks in x0b for the
     // weight-gradient kernel.  All loads unconditional (clamped addresses, selected values).
-    constexpr int NP = D.d[0] / 8;                       // 16-byte pieces of a row
+    constexpr int NP = D.d[0] / (S::fp8 ? 16 : 8);       // 16-byte pieces of a row
     const int O = a.obs_dim;
     constexpr int NI = (NP + 3) / 4;
 #pragma unroll
     for (int gi = 0; gi < NG; ++gi) sm[gi] = !S::fwd && a.idx ? sm[gi] : srow[gi];
     uint4 v[NG][NI];
-    if (S::fwd && a.x0_ready == 3) {                     // workgroup-uniform; no branch around a single load
+    if constexpr (S::fp8) {
+#pragma unroll
+      for (int it = 0; it < NI; ++it) {
+        uint32_t e[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float f[4];
+          row_quad(c.obs + (int64_t)sm[0] * O, 16 * (4 * it + jj) + 4 * q, O, it == NI - 1, f);
+          e[q] = to_e4m3x4(f[0], f[1], f[2], f[3]);
+        }
+        v[0][it] = make_uint4(e[0], e[1], e[2], e[3]);
+      }
+    } else if (S::fwd && a.x0_ready == 3) {                     // workgroup-uniform; no branch around a single load
 #pragma unroll
       for (int gi = 0; gi < NG; ++gi) {
-        typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
         const float* orow = c.obs + (int64_t)sm[gi] * O;
 #pragma unroll
         for (int it = 0; it < NI; ++it) {
           const int j = 4 * it + jj;
           float f[8];
 #pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const int f0 = 8 * j + 4 * q, back = it < NI - 1 ? 0 : f0 - (f0 < O - 4 ? f0 : O - 4);      // (O is within 32 of the padded width)
-            const float4u t = *reinterpret_cast<const float4u*>(orow + f0 - back);
-            f[4 * q + 0] = back == 0 ? t.x : back == 1 ? t.y : back == 2 ? t.z : back == 3 ? t.w : 0.f;
-            f[4 * q + 1] = back == 0 ? t.y : back == 1 ? t.z : back == 2 ? t.w : 0.f;
-            f[4 * q + 2] = back == 0 ? t.z : back == 1 ? t.w : 0.f;
-            f[4 * q + 3] = back == 0 ? t.w : 0.f;
-          }
+          for (int q = 0; q < 2; ++q) row_quad(orow, 8 * j + 4 * q, O, it == NI - 1, reinterpret_cast<float(&)[4]>(f[4 * q]));
           v[gi][it] = make_uint4(pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3]), pack_bf16(f[4], f[5]), pack_bf16(f[6], f[7]));
         }
       }
@@ -869,7 +937,9 @@ __device__ __forceinline__ void row_tile(const ChainArgs& a, int item, unsigned 
 #pragma unroll
       for (int it = 0; it < NI; ++it) {
         const int j = 4 * it + jj;
-        if (j < NP) {
+        if constexpr (S::fp8) {      // piece j: k step j / 4, half j / 2 % 2 of the lanes, block j % 2
+          if (j < NP) c.X[(((j >> 2) * 2 + (j & 1)) * S::nrt + (r >> 5)) * 64 + (r & 31) + 32 * ((j >> 1) & 1)] = v[gi][it];
+        } else if (j < NP) {
           const int w = (r >> 5) * 64 + (r & 31) + 32 * (j & 1);
           c.X[(j >> 1) * S::nrt * 64 + w] = v[gi][it];
           if (!S::fwd && c.net == 0) xb[(j >> 1) * 256 + w] = v[gi][it];      // arrays hold whole tiles
@@ -905,9 +975,11 @@ template <class S>
 bool shape_matches(const ModelLayout& L) {
   constexpr ChainDims D = S::dims();
   if (L.n_layers != D.nl) return false;
+  auto pad = [](int x) { return S::fp8 ? (x + 63) & ~63 : x; };
   for (int net = 0; net < 2; ++net)
     for (int l = 0; l < D.nl; ++l)
-      if (L.net[net][l].in_pad != D.d[l] || L.net[net][l].out_pad != D.d[l + 1]) return false;
+      if (pad(L.net[net][l].in_pad) != D.d[l] || (l == D.nl - 1 ? L.net[net][l].out_pad : pad(L.net[net][l].out_pad)) != D.d[l + 1])
+        return false;
   return true;
 }
 
@@ -927,7 +999,7 @@ int launch_shape(gmi_instance* g, ChainArgs a, int rows, int* tiles_out, double 
   int tiles = (rows + S::rows - 1) / S::rows;
   *tiles_out = tiles;
   if (!S::fwd && tiles > gmi::kStatRowsMax) return GMI_ERR_UNSUPPORTED;      // one statistics row per tile
-  if (a.x0_ready == 3 && (!S::fwd || a.obs_dim < 4 || a.obs_dim <= S::dims().d[0] - 32)) return GMI_ERR_UNSUPPORTED;
+  if (a.x0_ready == 3 && (!S::fwd || a.obs_dim < 4 || a.obs_dim <= S::dims().d[0] - (S::fp8 ? 64 : 32))) return GMI_ERR_UNSUPPORTED;
   if (a.x0_ready == 0 && (a.obs_dim % 4 != 0 || a.obs_dim < 4)) return GMI_ERR_UNSUPPORTED;
   int rc = gmi::allow_lds((const void*)train_tile_kernel<S>, lds, g->device, &allowed);
   if (rc != GMI_OK) return rc;
@@ -938,7 +1010,7 @@ int launch_shape(gmi_instance* g, ChainArgs a, int rows, int* tiles_out, double 
     a.items = tiles * (a.T + (a.val_last ? 1 : 0));
     tiles = a.items;
   }
-  if constexpr (S::nat) {
+  if constexpr (S::nat && !S::fp8) {
     if (a.T > 1 || a.val_last) {
       static gmi::DeviceSet allowed_items;
       rc = gmi::allow_lds((const void*)tile_items_kernel<S>, lds, g->device, &allowed_items);
@@ -960,11 +1032,12 @@ int launch_shape(gmi_instance* g, ChainArgs a, int rows, int* tiles_out, double 
 }  // namespace gmi_tile
 
 namespace gmi {
-// One function per shape compiled for the row-tile kernel (trainers tile_p<k>.hip, forward-only kernels tile_f<k>.hip): launches it if
+// One function per shape compiled for the row-tile kernel (trainers tile_p<k>.hip, forward-only kernels tile_f<k>.hip, fp8
+// tile_q<k>.hip): launches it if
 // the model has exactly that shape, GMI_ERR_UNSUPPORTED otherwise; rows == 0 only asks (a forward-only kernel's answer: 1 if it
 // computes as the agent kernel does).
 constexpr int kTileParts = 6;
-constexpr int kTileFwdParts = 6;
+constexpr int kTileFwdParts = 6, kTileFp8Parts = 5;
 #define GMI_TILE_PART_DECL(k)                                                                              \
   int launch_tile_part##k(gmi_instance* g, const ModelLayout& L, const gmi_chain::ChainArgs& a, int rows, \
                           int* tiles_out, double flops, double bytes)
@@ -974,6 +1047,16 @@ GMI_TILE_PART_DECL(0); GMI_TILE_PART_DECL(1); GMI_TILE_PART_DECL(2); GMI_TILE_PA
                               int* tiles_out, double flops, double bytes)
 GMI_TILE_FWD_PART_DECL(0); GMI_TILE_FWD_PART_DECL(1); GMI_TILE_FWD_PART_DECL(2); GMI_TILE_FWD_PART_DECL(3);
 GMI_TILE_FWD_PART_DECL(4); GMI_TILE_FWD_PART_DECL(5);
+#define GMI_TILE_FP8_PART_DECL(k) \
+  int launch_tile_fp8_part##k(gmi_instance* g, const ModelLayout& L, const gmi_chain::ChainArgs& a, int rows)
+GMI_TILE_FP8_PART_DECL(0); GMI_TILE_FP8_PART_DECL(1); GMI_TILE_FP8_PART_DECL(2); GMI_TILE_FP8_PART_DECL(3); GMI_TILE_FP8_PART_DECL(4);
+#define GMI_TILE_FP8_PART_DEFINE(k, ...)                                                          \
+  GMI_TILE_FP8_PART_DECL(k) {                                                                     \
+    using S = gmi_tile::TileShapeFp8<64, __VA_ARGS__>;                                            \
+    if (!gmi_tile::shape_matches<S>(L)) return GMI_ERR_UNSUPPORTED;                               \
+    int tiles = 0;                                                                                \
+    return rows == 0 ? GMI_OK : gmi_tile::launch_shape<S>(g, a, rows, &tiles, 0.0, 0.0);          \
+  }
 #define GMI_TILE_FWD_PART_DEFINE(k, SHAPE, ...)                                                   \
   GMI_TILE_FWD_PART_DECL(k) {                                                                     \
     using S = gmi_tile::SHAPE<64, __VA_ARGS__>;                                                   \

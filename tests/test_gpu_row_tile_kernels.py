@@ -204,6 +204,33 @@ def test_row_tile_decisions_are_those_of_the_agent_kernel(g, inst, obs, act, hid
         assert np.isfinite(a).all() and np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("obs,act,hidden,shift", [
+    (108, 21, [400, 200, 100], 0), (66, 32, [400, 200, 100], 1), (127, 1, [200, 400, 100], 3), (211, 20, [512, 512, 256, 128], 0),
+    (193, 7, [512, 512, 256, 128], 2), (256, 4, [512, 512, 512, 256], 1)])
+@pytest.mark.parametrize("n", [513, 577])
+def test_fp8_row_tile_decisions_are_those_of_the_agent_kernel(g, inst, obs, act, hidden, n, shift):
+    """As above: more than 32 rows per compute unit."""
+    from paper_2206_08482_amd.instances import cu_masks
+    dev = torch.device("cuda:0")
+    masked = g.gmi_create(cu_masks(256, [16])[0])
+    theta = torch.tensor(syn.make_model_params(obs, act, hidden, 5, policy_head_scale=0.5), device=dev)
+    x = torch.randn(n * obs + shift, generator=torch.Generator().manual_seed(n)).to(dev)[shift:]
+    torch.cuda.synchronize()
+    out = []
+    for h in (inst, masked):
+        w = g.gmi_fp8_bind(h, g.model_desc(obs, act, list(hidden), g.dtype_code("bf16"), n))
+        g.gmi_fp8_refresh(h, w, theta)
+        o = [torch.full(s, float("nan"), device=dev) for s in ((n, act), (n,), (n,), (n, act))]
+        torch.cuda.synchronize()
+        g.agent_act_fp8(h, w, x, n, 42, 9, 100, *o)
+        g.gmi_sync(h)
+        out.append([t.cpu().numpy() for t in o])
+        g.gmi_fp8_destroy(w)
+    g.gmi_destroy(masked)
+    for a, b in zip(*out):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("obs,act,hidden,n", [
     (211, 20, [512, 512, 256, 128], 32769),   # 128 rows on 16 waves
     (60, 8, [256, 128, 64], 32801),           # two 128-row tiles per compute unit
