@@ -190,10 +190,20 @@ __device__ __forceinline__ void finish_stats(const gmi::ShadowTable& tab, float*
     float s = 0.f;
     if (have_stat && grp < groups && col < C)
       for (int i = 0; i < ps.n; ++i) {
-        // rows grp, grp + groups, ...: eight loads in flight, fixed order of additions
+        // rows grp, grp + groups, ...: 16 loads in flight, fixed order of additions
         const float* q = ps.r[i].stat + col;
         const int n_stat = ps.r[i].n_stat;
         int b = grp;
+        for (; b + 15 * groups < n_stat; b += 16 * groups) {
+          float t[16];
+#pragma unroll
+          for (int u = 0; u < 16; ++u) t[u] = q[(int64_t)(b + u * groups) * C];
+#pragma unroll
+          for (int w = 8; w > 0; w >>= 1)
+#pragma unroll
+            for (int u = 0; u < w; ++u) t[u] += t[u + w];
+          s += t[0];
+        }
         for (; b + 7 * groups < n_stat; b += 8 * groups) {
           float t[8];
 #pragma unroll
@@ -231,8 +241,8 @@ __device__ __forceinline__ void finish_stats(const gmi::ShadowTable& tab, float*
 // fp32 models and caller-supplied gradients (partials in flat parameter order): a workgroup of 64 G waves'
 // worth of threads owns 256 consecutive parameters, G threads per parameter each summing every G-th partial row.
 // grad(p) = (1/n) sum_i sum_s part_i[s * part_stride + p]: the in-memory mean over the n replicas (Section 4.1's gradient
-// reduction for instances that share one address space), fixed summation order.  The last workgroup finalises the
-// statistics and log_std.
+// reduction for instances that share one address space), fixed summation order.  The first workgroup finalises the
+// statistics and log_std: its walk over the statistics rows is the longest way of all.
 template <int G>
 __global__ __launch_bounds__(256 * G) void adam_kernel(gmi::ShadowTable tab, float* __restrict__ params,
                                                        float* __restrict__ am, float* __restrict__ av, PartSet ps,
@@ -240,13 +250,13 @@ __global__ __launch_bounds__(256 * G) void adam_kernel(gmi::ShadowTable tab, flo
                                                        float* __restrict__ stats_out, float* __restrict__ grad_out,
                                                        int do_update) {
   __shared__ float s_sum[256 * G];
-  if (blockIdx.x == gridDim.x - 1) {
+  if (blockIdx.x == 0) {
     finish_stats<256 * G>(tab, params, am, av, ps, part_stride, A, c_e, inv_rows, hs, nullptr,
                           stats_out, grad_out, do_update, s_sum);
     return;
   }
   const int t = threadIdx.x & 255, grp = threadIdx.x >> 8;
-  const int64_t p = (int64_t)blockIdx.x * 256 + t;
+  const int64_t p = (int64_t)(blockIdx.x - 1) * 256 + t;
   const bool ok = p < tab.logstd_off;
   // the moments and the parameter are fetched ahead of the partials (their latency would otherwise follow the sum's)
   float m0 = 0.f, v0 = 0.f, w0 = 0.f;
@@ -311,14 +321,15 @@ __global__ __launch_bounds__(256) void adam_shadow_kernel(gmi::ShadowTable tab, 
   __shared__ float s_bsum[4][8];
   __shared__ __attribute__((aligned(16))) uint16_t s_t[8][40];
   const int n_tiles = gridDim.x - 1;
-  if ((int)blockIdx.x == n_tiles) {
+  if (blockIdx.x == 0) {      // first: its walk over the statistics rows is the longest way of all (last and with half the loads in
+                              // flight, us: 108:400:200:100:21 with 512 rows of them 13.5, now 11.0; 211:512:512:256:128:20 with 256 26.6, now 24.0)
     finish_stats<256>(tab, params, am, av, ps, part_stride, A, c_e, inv_rows, hs,
                       do_update ? reinterpret_cast<float*>(shadow + tab.sh_logstd) : nullptr, stats_out, grad_out, do_update, &s_sum[0][0]);
     return;
   }
   // neighbouring tiles, which share memory lines of the parameters and moments, on the same die (ids go round-robin over 8)
   const int per = n_tiles >> 3, whole = per << 3;
-  const int tile = (int)blockIdx.x < whole ? (blockIdx.x & 7) * per + (blockIdx.x >> 3) : blockIdx.x;
+  const int id = (int)blockIdx.x - 1, tile = id < whole ? (id & 7) * per + (id >> 3) : id;
   int li = 0;      // the layer whose tiles hold this one (entries past the last layer hold no tile: all loads at once)
 #pragma unroll
   for (int k = 1; k < gmi::kMaxWgradProblems; ++k) li += tile >= tt.start[k] ? 1 : 0;
