@@ -46,27 +46,48 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// What (A - mean) / (std + 1e-8) takes from the sums of A and A^2 over n elements.
+__device__ __forceinline__ void norm_factors(double s1, double s2, double n, float* mean_out, float* inv_out) {
+  const double mean = s1 / n;
+  double var = s2 / n - mean * mean;
+  if (var < 0.0) var = 0.0;
+  *mean_out = (float)mean;
+  *inv_out = 1.0f / ((float)sqrt(var) + 1e-8f);
+}
+
 // Reverse recurrence over the horizon, one lane per env: the time-major layout makes every step's
-// loads and stores of a wave one contiguous segment.  Also leaves per-workgroup sums of A and A^2.
+// loads and stores of a wave one contiguous segment.  Also leaves per-workgroup sums of A and A^2.  The recurrence waits for memory
+// once per kGaeAhead steps, whose loads go out together (us with 4 / 16 steps: 4096 envs and 32 steps 14.2 / 6.6, 512 and 32 11.2 / 5.4).
+// norm: the only workgroup normalises its advantages itself, as normalize_kernel would in another launch (64 envs and 16 steps 5.6 + 4.5 us,
+// now 4.6).
+constexpr int kGaeAhead = 16;
 __global__ __launch_bounds__(256) void gae_kernel(gmi_buffer_desc d, const float* __restrict__ last_value,
-                                                  float gamma, float gl, double* __restrict__ part) {
+                                                  float gamma, float gl, double* __restrict__ part, int norm) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   double s1 = 0.0, s2 = 0.0;
   if (e < d.n_envs) {
     float adv_next = 0.f;
     float v_next = last_value[e];
-#pragma unroll 4
-    for (int t = d.horizon - 1; t >= 0; --t) {
-      const int64_t i = (int64_t)t * d.ld_envs + e;
-      const float r = d.rew[i], v = d.val[i];
-      const float nd = 1.0f - (float)d.done[i];
-      const float delta = r + gamma * v_next * nd - v;
-      adv_next = delta + gl * nd * adv_next;
-      d.adv[i] = adv_next;
-      d.ret[i] = adv_next + v;
-      v_next = v;
-      s1 += (double)adv_next;
-      s2 += (double)adv_next * (double)adv_next;
+    for (int t0 = d.horizon - 1; t0 >= 0; t0 -= kGaeAhead) {
+      float r[kGaeAhead], v[kGaeAhead], nd[kGaeAhead];
+#pragma unroll
+      for (int u = 0; u < kGaeAhead; ++u) {
+        const int64_t i = (int64_t)max(t0 - u, 0) * d.ld_envs + e;
+        r[u] = d.rew[i]; v[u] = d.val[i]; nd[u] = (float)d.done[i];
+      }
+#pragma unroll
+      for (int u = 0; u < kGaeAhead; ++u) {
+        if (t0 - u < 0) break;
+        const int64_t i = (int64_t)(t0 - u) * d.ld_envs + e;
+        const float n = 1.0f - nd[u];
+        const float delta = r[u] + gamma * v_next * n - v[u];
+        adv_next = delta + gl * n * adv_next;
+        d.adv[i] = adv_next;
+        d.ret[i] = adv_next + v[u];
+        v_next = v[u];
+        s1 += (double)adv_next;
+        s2 += (double)adv_next * (double)adv_next;
+      }
     }
   }
   if (part) {
@@ -76,7 +97,20 @@ __global__ __launch_bounds__(256) void gae_kernel(gmi_buffer_desc d, const float
     const int w = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) { sh[0][w] = s1; sh[1][w] = s2; }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (norm) {
+      float mean, inv;
+      norm_factors(sh[0][0] + sh[0][1] + sh[0][2] + sh[0][3], sh[1][0] + sh[1][1] + sh[1][2] + sh[1][3],
+                   (double)d.horizon * (double)d.n_envs, &mean, &inv);
+      if (e < d.n_envs)
+        for (int t0 = 0; t0 < d.horizon; t0 += kGaeAhead) {
+          float a[kGaeAhead];
+#pragma unroll
+          for (int u = 0; u < kGaeAhead; ++u) a[u] = d.adv[(int64_t)min(t0 + u, d.horizon - 1) * d.ld_envs + e];
+#pragma unroll
+          for (int u = 0; u < kGaeAhead; ++u)
+            if (t0 + u < d.horizon) d.adv[(int64_t)(t0 + u) * d.ld_envs + e] = (a[u] - mean) * inv;
+        }
+    } else if (threadIdx.x == 0) {
       part[2 * blockIdx.x + 0] = sh[0][0] + sh[0][1] + sh[0][2] + sh[0][3];
       part[2 * blockIdx.x + 1] = sh[1][0] + sh[1][1] + sh[1][2] + sh[1][3];
     }
@@ -93,7 +127,7 @@ __global__ __launch_bounds__(256) void gae_kernel(gmi_buffer_desc d, const float
 constexpr int kScanEnvs = 64;
 template <int TP>
 __global__ __launch_bounds__(256) void gae_scan_kernel(gmi_buffer_desc d, const float* __restrict__ last_value,
-                                                       float gamma, float gl, double* __restrict__ part) {
+                                                       float gamma, float gl, double* __restrict__ part, int) {
   extern __shared__ float s_gae[];                      // [T + 1][65] values, [T][65] rewards -> advantages, [T][65] done
   const int T = d.horizon, ldl = kScanEnvs + 1;
   float* s_v = s_gae;
@@ -160,7 +194,8 @@ __global__ __launch_bounds__(256) void gae_scan_kernel(gmi_buffer_desc d, const 
 // the measurement interface can force either.
 int g_gae_variant = 0;
 
-// Launches the chosen GAE kernel on `stream`; returns the number of partial-sum pairs it leaves in `part`.
+// Launches the chosen GAE kernel on `stream`; returns the number of partial-sum pairs it leaves in `part`, 0 if the kernel has
+// normalised the advantages itself: one workgroup that holds them all, while its walk is short (256 envs and 64 steps 15.0 us for both launches, now 11.1).
 template <typename Launch>
 int launch_gae(int variant, const gmi_buffer_desc& d, const float* last_value, float gamma, float gl, double* part,
                Launch&& launch) {
@@ -170,19 +205,20 @@ int launch_gae(int variant, const gmi_buffer_desc& d, const float* last_value, f
     int tp = 1;
     while (tp < d.horizon) tp <<= 1;
     switch (tp) {
-      case 1: launch(gae_scan_kernel<1>, n_part, lds); break;
-      case 2: launch(gae_scan_kernel<2>, n_part, lds); break;
-      case 4: launch(gae_scan_kernel<4>, n_part, lds); break;
-      case 8: launch(gae_scan_kernel<8>, n_part, lds); break;
-      case 16: launch(gae_scan_kernel<16>, n_part, lds); break;
-      case 32: launch(gae_scan_kernel<32>, n_part, lds); break;
-      default: launch(gae_scan_kernel<64>, n_part, lds); break;
+      case 1: launch(gae_scan_kernel<1>, n_part, lds, 0); break;
+      case 2: launch(gae_scan_kernel<2>, n_part, lds, 0); break;
+      case 4: launch(gae_scan_kernel<4>, n_part, lds, 0); break;
+      case 8: launch(gae_scan_kernel<8>, n_part, lds, 0); break;
+      case 16: launch(gae_scan_kernel<16>, n_part, lds, 0); break;
+      case 32: launch(gae_scan_kernel<32>, n_part, lds, 0); break;
+      default: launch(gae_scan_kernel<64>, n_part, lds, 0); break;
     }
     return n_part;
   }
   const int n_part = (d.n_envs + 255) / 256;
-  launch(gae_kernel, n_part, (size_t)0);
-  return n_part;
+  const int norm = part && n_part == 1 && d.horizon <= 64 ? 1 : 0;
+  launch(gae_kernel, n_part, (size_t)0, norm);
+  return norm ? 0 : n_part;
 }
 
 // A <- (A - mean) / (std + 1e-8); every workgroup re-reduces the (small) partial array in the same
@@ -199,12 +235,8 @@ __global__ __launch_bounds__(256) void normalize_kernel(gmi_buffer_desc d, const
   if ((threadIdx.x & 63) == 0) { sh[0][w] = s1; sh[1][w] = s2; }
   __syncthreads();
   if (threadIdx.x == 0) {
-    const double n = (double)d.horizon * (double)d.n_envs;
-    const double mean = (sh[0][0] + sh[0][1] + sh[0][2] + sh[0][3]) / n;
-    double var = (sh[1][0] + sh[1][1] + sh[1][2] + sh[1][3]) / n - mean * mean;
-    if (var < 0.0) var = 0.0;
-    s_mean = (float)mean;
-    s_inv = 1.0f / ((float)sqrt(var) + 1e-8f);
+    norm_factors(sh[0][0] + sh[0][1] + sh[0][2] + sh[0][3], sh[1][0] + sh[1][1] + sh[1][2] + sh[1][3],
+                 (double)d.horizon * (double)d.n_envs, &s_mean, &s_inv);
   }
   __syncthreads();
   const float mean = s_mean, inv = s_inv;
@@ -298,12 +330,12 @@ extern "C" int gae_compute(gmi_t g, gmi_buffer_t b, const float* last_value, flo
   if (!last_value) GMI_FAIL(GMI_ERR_INVALID_ARG, "gae_compute: last_value is NULL");
   gmi::ProfScope ps(g, gmi::kClsGae);
   const int n_part = launch_gae(g_gae_variant, b->d, last_value, gamma, gamma * lambda, normalize ? b->part : nullptr,
-                                [&](auto kernel, int grid, size_t lds) {
+                                [&](auto kernel, int grid, size_t lds, int norm) {
                                   ps.launch(kernel, dim3(grid), dim3(256), lds, b->d, last_value, gamma, gamma * lambda,
-                                            normalize ? b->part : nullptr);
+                                            normalize ? b->part : nullptr, norm);
                                 });
   GMI_LAUNCH_CHECK();
-  if (normalize) {
+  if (normalize && n_part > 0) {
     const int64_t total = (int64_t)b->d.horizon * b->d.n_envs;
     int grid = (int)((total + 1023) / 1024);
     if (grid > 2048) grid = 2048;
@@ -368,12 +400,12 @@ extern "C" int gae_compute_static(gmi_t g, int32_t horizon, int32_t n_envs, int3
   // every workgroup of gae_kernel writes its own two partials and normalize_kernel reads exactly those: nothing
   // of an earlier call is read, so nothing needs clearing
   const int n_part = launch_gae(variant, d, last_value, gamma, gamma * lambda, normalize ? part : nullptr,
-                                [&](auto kernel, int grid, size_t lds) {
+                                [&](auto kernel, int grid, size_t lds, int norm) {
                                   hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), lds, g->stream, d, last_value, gamma,
-                                                     gamma * lambda, normalize ? part : nullptr);
+                                                     gamma * lambda, normalize ? part : nullptr, norm);
                                 });
   GMI_LAUNCH_CHECK();
-  if (normalize) {
+  if (normalize && n_part > 0) {
     const int64_t total = (int64_t)horizon * n_envs;
     int grid = (int)((total + 1023) / 1024);
     if (grid > 2048) grid = 2048;

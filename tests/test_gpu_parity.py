@@ -171,6 +171,13 @@ def test_gae_matches_oracle(g, inst, T, N, ld, normalize, variant):
     g.gmi_bench_gae_variant(0)
 
 
+@pytest.mark.parametrize("T,N,ld", [(1, 2, 3), (15, 255, 256), (16, 256, 256), (17, 256, 300), (33, 257, 257), (64, 100, 128), (65, 100, 100)])
+@pytest.mark.parametrize("normalize", [True, False])
+def test_gae_at_the_edges_of_its_chunks(g, inst, T, N, ld, normalize):
+    """Steps around 16 (the loads that go out together), envs around 256 and steps around 64 (one workgroup normalises itself)."""
+    test_gae_matches_oracle(g, inst, T, N, ld, normalize, 0)
+
+
 # ----------------------------------------------------------------------------- agent
 def _bind_model(g, inst, cfg, theta, rows, dtype=None, with_adam=True):
     dt = cfg.dtype if dtype is None else dtype
