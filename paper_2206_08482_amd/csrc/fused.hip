@@ -483,6 +483,7 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
   }
 
   const SimLane sl = sim_lane(a, wave8, OS, lane);
+  const int draw_top = draw_thread(a, npr);
   // The grid never exceeds what the instance's compute units hold at once: a workgroup takes the tiles
   // blockIdx.x, blockIdx.x + gridDim.x, ... one after the other, each through all T steps.  (Workgroups
   // that wait for a free compute unit would keep the dispatcher from placing other instances' kernels.)
@@ -570,7 +571,7 @@ __global__ __launch_bounds__(512) void rollout_fused_kernel(RolloutArgs a) {
         a.b_logp[slot0 + et] = block_sum(s_lp + et * nba, nba);
         if constexpr (kStationary) a.b_val[slot0 + et] = s_val[et];
       }
-      if (a.ahead && t + 1 < a.T) draw_rest(a, s_draws + ((t + 1) & 1) * Rv * npr, step + 1u, r0, npr, nba, tid);
+      if (a.ahead && t + 1 < a.T) draw_rest(a, s_draws + ((t + 1) & 1) * Rv * npr, step + 1u, r0, npr, nba, tid, draw_top);
       __syncthreads();
     }
     // the final state

@@ -192,8 +192,14 @@ __device__ __forceinline__ void draw_all(const RolloutEnv& a, float4* dst, uint3
 }
 // The same beside the simulator, whose items go to the first waves: last threads first.  (Handed out 64 at a time through a
 // counter in LDS, the collection of 17:64:64:6 took 196 us instead of 185.)
-__device__ __forceinline__ void draw_rest(const RolloutEnv& a, float4* dst, uint32_t stp, int r0, int npr, int nba, int tid) {
-  for (int item = 511 - tid; item < a.rows_per_wg * npr; item += 512) draw_item(a, dst, stp, r0, npr, nba, item);
+__device__ __forceinline__ void draw_rest(const RolloutEnv& a, float4* dst, uint32_t stp, int r0, int npr, int nba, int tid, int top) {
+  for (int item = top - tid; item >= 0 && item < a.rows_per_wg * npr; item += 512) draw_item(a, dst, stp, r0, npr, nba, item);
+}
+// The thread with the first of them: the last one, or the last of the wave before where the waves beside the simulator's are enough
+// without the last, which writes the step's sums first.
+__device__ __forceinline__ int draw_thread(const RolloutEnv& a, int npr) {
+  const int sim = (((a.o4 >> 2) + 3) >> 2) * (a.rows_per_wg >> 4), draws = (a.rows_per_wg * npr + 63) >> 6;
+  return sim + draws <= 7 ? 447 : 511;
 }
 
 // Thread e < rows_per_wg: env r0 + e's done flag, and its episode counter.
