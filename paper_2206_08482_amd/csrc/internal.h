@@ -93,10 +93,13 @@ __device__ __forceinline__ uint4 load_uniform(const void* base, int s_off, uint3
 // train_resident_kernel of 45:128:128:12 with 6000 rows (17 MB of gradient partials) 25.8 / 23.7, train_tile_kernel of
 // 211:512:512:256:128:20 with 32768 rows 220 / 216.  Non-temporal stores
 // bypass the memory-side cache as well: the kernel that reads them waits longer (Adam 7.2 / 8.4).
+// s_off goes into the vector offset, not into the instruction's scalar one: the compiler takes a store with a register there to have
+// read its data at once and lets the next instruction overwrite them, and the first word of the data was then sometimes that
+// instruction's (seen in a build of train_tile_kernel with a v_ashrrev right behind the store).  Without one it keeps them apart.
 __device__ __forceinline__ void store_through(void* base, uint32_t off, const uint4& v, int s_off = 0) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   const u32x4 x = {v.x, v.y, v.z, v.w};
-  __builtin_amdgcn_raw_buffer_store_b128(x, __builtin_amdgcn_make_buffer_rsrc(base, 0, 0xFFFFFFFFu, 0x00020000), off, s_off, 17);
+  __builtin_amdgcn_raw_buffer_store_b128(x, __builtin_amdgcn_make_buffer_rsrc(base, 0, 0xFFFFFFFFu, 0x00020000), off + s_off, 0, 17);
 }
 __device__ __forceinline__ void store_through(void* base, uint32_t off, float x, float y, float z, float w) {
   store_through(base, off, make_uint4(__float_as_uint(x), __float_as_uint(y), __float_as_uint(z), __float_as_uint(w)));
