@@ -123,8 +123,8 @@ def _stated_work(g, inst, cls_name, call):
     ("C3", 2, 4200, 8205), ("HM", 3, 2800, 8321),      # 8192
     ("C4", 2, 2100, 4099), ("SH", 3, 1400, 4133), ("C4", 2, 4300, 8191)])      # 4096 rows of the resident kernel
 def test_gradient_of_the_compiled_trainer_kernels_at_ragged_rows(g, inst, name, T, N, rows):
-    """The register-chained and the row-tile trainer kernels just beyond the rows up to which the resident kernel serves
-    their shapes (use_resident).  Only their launchers state work for the class, so this also checks which kernel ran."""
+    """The row-tile trainer kernel just beyond the rows at which the resident kernel serves
+    its shapes (use_resident).  Only their launchers state work for the class, so this also checks which kernel ran."""
     (shape, (got_g, got_s), args), launches, flops = _stated_work(
         g, inst, "chain_train", lambda: _gradient_case(g, inst, name, T, N, rows))
     assert launches == 1 and flops > 0

@@ -21,7 +21,7 @@ def _iterate(ses, cfg, it, minibatch):
 
 @pytest.mark.parametrize("name,dtype,n_envs,horizon", [
     ("C1", "f32", 64, 8), ("C2", "bf16", 512, 4), ("C4", "bf16", 384, 3),      # fp32 and resident trainer kernels
-    ("C2", "bf16", 4200, 8), ("C4", "bf16", 2100, 4)])                         # register-chained and row-tile ones
+    ("C2", "bf16", 4200, 8), ("C4", "bf16", 2100, 4)])                         # row-tile ones
 def test_resume_from_a_snapshot_continues_bit_for_bit(name, dtype, n_envs, horizon):
     """Three iterations in one session against two iterations, a snapshot of everything the method carries
     (parameters, Adam moments and step count, env states, episode counters) and a third iteration in a NEW session
