@@ -64,7 +64,10 @@ __device__ __forceinline__ void stage_inputs(const float* __restrict__ obs, cons
 // elements) of envs g*EPT .. g*EPT+EPT-1.  Inputs of the workgroup's envs are staged in LDS once, rows OS floats apart.
 // The phases before the product are round trips to memory: loads of a phase are issued together, and every element has a
 // thread (one element after the other, the staging of 16 envs of 211 + 20 and their actions cost 33 round trips).
-template <int EPT, bool FUSED>
+// MF: the product on the 4x4x1 fp32 matrix instruction, whose chain over k is the vector form's sequence of fused multiply-adds, bit for
+// bit, in half its cycles and beside the vector unit's work for other waves.  A wave owns 16 of up to 64 output blocks (lane L: block
+// L / 4) of all 4 EPT envs, a thread's env i = 4 i + L % 4 of them; a matrix row is one load of 64 consecutive floats per wave.
+template <int EPT, bool FUSED, bool MF>
 __global__ __launch_bounds__(256) void env_step_kernel(
     const float* __restrict__ obs, const float* __restrict__ act, const float* __restrict__ m_t,
     uint32_t* __restrict__ episode_step, float* __restrict__ next_obs, float* __restrict__ reward,
@@ -135,16 +138,61 @@ __global__ __launch_bounds__(256) void env_step_kernel(
   }
   __syncthreads();
 
-  const int b = tid % nb, g = tid / nb;
-  const bool active = g < G;
+  const int b = MF ? tid >> 2 : tid % nb;
+  const int e0 = MF ? tid & 3 : tid / nb * EPT;      // the thread's envs: e0 + ES i
+  constexpr int ES = MF ? 4 : 1;
+  const bool active = MF ? b < nb : tid / nb < G;
   float acc[EPT][4];
 #pragma unroll
   for (int i = 0; i < EPT; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
+  const float* xin = s_in + e0 * OS;
 
-  if (active) {
-    const float* xin = s_in + (g * EPT) * OS;
+  if constexpr (MF) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    f4 c[EPT];
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) c[i] = f4{0.f, 0.f, 0.f, 0.f};
+    const float* mcol = m_t + min(tid, o4 - 1);
+    float m[2][4];
+    auto fetch = [&](int buf, int k) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) m[buf][u] = mcol[min(k + u, OA - 1) * o4];
+    };
+    auto multiply = [&](int buf, int k) {      // OS is a multiple of 4
+      float4 x[EPT];
+#pragma unroll
+      for (int i = 0; i < EPT; ++i) x[i] = *reinterpret_cast<const float4*>(xin + 4 * i * OS + k);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int i = 0; i < EPT; ++i)
+          c[i] = __builtin_amdgcn_mfma_f32_4x4x1f32(m[buf][u], u == 0 ? x[i].x : u == 1 ? x[i].y : u == 2 ? x[i].z : x[i].w, c[i], 0, 0, 0);
+    };
+    fetch(0, 0);
+    int k = 0;
+    for (; k + 8 <= OA; k += 8) {
+      fetch(1, k + 4);
+      multiply(0, k);
+      fetch(0, k + 8);
+      multiply(1, k + 4);
+    }
+    if (k + 4 <= OA) {
+      multiply(0, k);
+      k += 4;
+    }
+    for (; k < OA; ++k) {
+      const float mk = mcol[k * o4];
+#pragma unroll
+      for (int i = 0; i < EPT; ++i) c[i] = __builtin_amdgcn_mfma_f32_4x4x1f32(mk, xin[4 * i * OS + k], c[i], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < EPT; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = c[i][j];
+  }
+  if (!MF && active) {
     const float4* mrow = reinterpret_cast<const float4*>(m_t) + b;
     const int stride4 = o4 / 4;
     // four matrix rows are fetched while the four before them are multiplied
@@ -200,6 +248,8 @@ __global__ __launch_bounds__(256) void env_step_kernel(
         acc[i][3] = fmaf(x, mk.w, acc[i][3]);
       }
     }
+  }
+  if (active) {
     // partial squared norms for the reward: this thread's 4 state elements, and its share of the action
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
@@ -207,10 +257,10 @@ __global__ __launch_bounds__(256) void env_step_kernel(
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int o = 4 * b + j;
-        if (o < O) { const float x = xin[i * OS + o]; ps = fmaf(x, x, ps); }
+        if (o < O) { const float x = xin[ES * i * OS + o]; ps = fmaf(x, x, ps); }
       }
-      for (int a = b; a < A; a += nb) { const float x = xin[i * OS + O + a]; pa = fmaf(x, x, pa); }
-      s_part[(g * EPT + i) * nb + b] = gmi::reward_part(ps, pa);
+      for (int a = b; a < A; a += nb) { const float x = xin[ES * i * OS + O + a]; pa = fmaf(x, x, pa); }
+      s_part[(e0 + ES * i) * nb + b] = gmi::reward_part(ps, pa);
     }
   }
   __syncthreads();
@@ -223,7 +273,7 @@ __global__ __launch_bounds__(256) void env_step_kernel(
   if (!active) return;
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
-    const int e = g * EPT + i;
+    const int e = e0 + ES * i;
     const int env = env0 + e;
     if (env >= N) continue;
     float z[4];
@@ -317,13 +367,18 @@ int launch_env_step(gmi_instance* g, gmi_env* env, const float* obs, const float
   int OS = (O + A + 3) & ~3;      // rows of 16-byte pieces where the padding fits
   if (lds_bytes(ept) + (size_t)EB * (OS - O - A) * sizeof(float) > 64 * 1024) OS = O + A;
   const size_t lds = lds_bytes(ept) + (size_t)EB * (OS - O - A) * sizeof(float);
+  // Four waves of 16 output blocks are the 4 envs' workgroup of 52 to 64 blocks.  Vector form / matrix instruction, us: 211 + 20, 512 envs
+  // 13.8 / 11.2, 4096 32.6 / 19.4, 12288 49.1 / 36.2, 16384 43.3 / 41.5, 65536 149 / 135, 262144 629 / 566; 256 + 32, 4096 38.5 / 22.3, 65536 185 / 165;
+  // a step of the collection of 16384 envs of 211 + 20 53.6 / 51.8.  Two or four groups of envs beside fewer blocks lose at large numbers:
+  // 108 + 21, 524288 envs 423 / 435, 60 + 8, 1048576 envs 344 / 372.
+  const bool mf = G == 4 && (OS & 3) == 0;
   const unsigned grid = (unsigned)((N + EB - 1) / EB);
   const int vec_store = ((O & 3) == 0) && (((uintptr_t)next_obs & 15) == 0);
   const uint32_t k0 = (uint32_t)d.seed, k1 = (uint32_t)(d.seed >> 32);
   const StepFuse fu = fuse ? *fuse : StepFuse{};
   gmi::ProfScope ps(g, gmi::kClsEnvStep);
 #define GMI_ENV_LAUNCH(E, F)                                                                       \
-  ps.launch(env_step_kernel<E, F>, dim3(grid), dim3(256), lds,                                    \
+  ps.launch(mf ? env_step_kernel<E, F, true> : env_step_kernel<E, F, false>, dim3(grid), dim3(256), lds,                                    \
       obs, act, env->m_t, env->episode_step, next_obs, reward, done, N, O, A, OS, o4, nb, G,          \
       d.noise_std, d.reward_scale, d.done_period, d.done_threshold, k0, k1, d.env_offset, step, vec_store, fu)
   if (fuse) {

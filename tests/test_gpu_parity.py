@@ -120,6 +120,14 @@ def test_env_step_matches_oracle(g, inst, n, o, a, period, prob_inv):
     g.gmi_env_destroy(h)
 
 
+# The product's two forms: 52 to 64 output blocks of 4 elements, or other numbers;
+# 1, 2 and 4 envs per thread; every remainder of the contraction by 4.
+@pytest.mark.parametrize("n,o,a", [(65, 45, 3), (40, 129, 3), (19, 204, 5), (17, 205, 6), (6, 207, 4), (1, 211, 20), (5, 256, 9), (9, 257, 2),
+                                   (8197, 256, 2), (16387, 206, 5)])
+def test_env_step_at_the_edges_of_its_output_blocks(g, inst, n, o, a):
+    test_env_step_matches_oracle(g, inst, n, o, a, 0, 50)
+
+
 # ----------------------------------------------------------------------------- experience + GAE
 def _bind_buffer(g, inst, T, N, ld, O, A, col0=0):
     from paper_2206_08482_amd.runner import RolloutBuffers
