@@ -534,7 +534,7 @@ __device__ __forceinline__ void loss_epilogue(Ctx<S>& c, const ChainArgs& a, con
     float s_pl = 0.f, s_kl = 0.f, s_cf = 0.f, g_lp = 0.f;
     if (ok) {
       const float lo = c.l_lo, ad = c.l_ad;
-      const float ratio = __expf(lp - lo);
+      const float ratio = expf(lp - lo);
       const float u1 = ratio * ad;
       const float u2 = fminf(fmaxf(ratio, 1.0f - a.clip), 1.0f + a.clip) * ad;
       g_lp = (u1 <= u2) ? -(ad * ratio) * inv_m : 0.f;

@@ -331,6 +331,44 @@ def test_probability_ratio_is_the_accurate_exponential(g, inst, dtype, fused):
     g.gmi_model_destroy(model)
 
 
+@pytest.mark.parametrize("obs,hidden", [(60, (256, 128, 64)), (23, (256, 128, 64)), (108, (400, 200, 100)), (108, (200, 400, 100)),
+                                        (211, (512, 512, 256, 128)), (211, (512, 512, 512, 256))])
+def test_probability_ratio_of_the_row_tile_kernel(g, inst, obs, hidden):
+    """As above, for every shape with a compiled trainer kernel: the policy loss is the ratio, the gradient of log_std (a mean at
+    the action: g (0 - 1) with g = -ratio advantage) the ratio times the advantage, both to 4e-7.  The class's stated work says
+    that the row-tile kernel ran."""
+    act, N = 1, 12
+    model, buf, keep = _setup(g, inst, obs, act, hidden, "bf16", 1, N, N)
+    theta, shadow, m, v, rb = keep
+    theta.zero_()
+    x = np.array([0.0, 0.3, -0.7, 2.5, -3.3, 7.9, -9.1, 13.7, 21.3, -25.9, 37.7, 43.1], np.float32)
+    lp = np.float32(-0.918938533204672742)
+    logp = (lp - x).astype(np.float32)
+    adv = np.where(x > 0, -1, 1).astype(np.float32)
+    rb.act.zero_()
+    rb.logp.copy_(torch.tensor(logp)[None])
+    rb.adv.copy_(torch.tensor(adv)[None])
+    torch.cuda.synchronize()
+    g.gmi_model_refresh_shadow(inst, model)
+    hp = g.ppo_hparams(clip=0.2, c_v=0.5, c_e=0.0, minibatch=1)
+    grad = torch.zeros(N, theta.numel(), device="cuda:0")
+    stats = torch.zeros(N, 5, device="cuda:0")
+    idx = torch.arange(N, dtype=torch.int32, device="cuda:0")
+    torch.cuda.synchronize()
+    cls = [g.gmi_profile_class_name(c) for c in range(g.gmi_profile_classes())].index("chain_train")
+    g.gmi_profile_enable(inst, 1 << cls)
+    for i in range(N):
+        g.ppo_gradient(inst, model, buf, hp, idx[i:], 1, grad[i], stats[i])
+    g.gmi_sync(inst)
+    assert g.gmi_profile_read(inst, cls)[1] == N and g.gmi_profile_work(inst, cls)[0] > 0
+    g.gmi_profile_enable(inst, 0)
+    want = np.exp((lp - logp).astype(np.float32).astype(np.float64))
+    for got in (-stats[:, 0].cpu().numpy(), grad[:, -1].cpu().numpy()):
+        assert np.abs(got * adv / want - 1).max() <= 4e-7, np.abs(got * adv / want - 1)
+    g.gmi_buffer_destroy(buf)
+    g.gmi_model_destroy(model)
+
+
 def _collecting_sessions(obs, act, hidden, dtype, n, T, cus, seed=9):
     """The same session with the one-launch collection and with the step-by-step calls, on `cus` compute units (None: all)."""
     from paper_2206_08482_amd.instances import cu_masks
