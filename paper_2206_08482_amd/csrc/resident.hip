@@ -624,23 +624,27 @@ namespace gmi {
 
 bool resident_supported(const ModelLayout& L) { return shape_ok(L); }
 // Where a row-tile kernel is compiled for the shape too.  Per minibatch with Adam, us, this kernel / that one:
-//   60:256:128:64:8: 32.2 / 28.4 at 1000 rows, 44.9 / 30.9 at 4096, 50.1 / 34.1 at 8192, 54.7 / 41.9 at 12288, 54.8 / 46.0 at 16384;
-//     on 128 compute units 49.9 / 41.0 at 6000; on 64 31.9 / 30.3 at 500, 40.9 / 46.1 at 2000, 46.5 / 52.2 at 3000, 47.3 / 51.6 at
-//     4096; on 16 46.7 / 48.1 at 256;
-//   108:400:200:100:21: 47.7 / 43.0 at 1000, 50.8 / 46.8 at 4096, 63.5 / 53.7 at 8192; on 64 compute units 64.6 / 61.3 at 1024;
-//   211:512:512:256:128:20: 75.9 / 70.9 at 1000, 86.1 / 80.3 at 4096; on 64 compute units 129 / 124 at 1000;
-//   211:512:512:512:256:20: 93.3 / 89.7 at 1000, 105 / 101 at 4096.
-// So this kernel serves such a shape on less than half the device, where it keeps the gradients in registers, while every tile
-// has a workgroup of its own (one per net and two of the instance's compute units; 128-row tiles with the gradients in registers, else
-// 64 or, where only those fit LDS, 32), and elsewhere only the one tile count that gives every workgroup a tile, which has
-// always been its own: a caller who relies on that does not see another kernel's rounding there.
+//   60:256:128:64:8: 32.2 / 28.4 at 1000 rows, 44.9 / 30.9 at 4096, 50.1 / 34.1 at 8192, 54.7 / 41.9 at 12288, 56.1 / 46.4 at 16384,
+//     where each of this kernel's workgroups has one tile; on 128 compute units 52.5 / 41.9 at 8192; on 120 33.9 / 32.2 at 1000,
+//     76.9 / 53.7 at 7680; on 96 34.8 / 32.0 at 1000, 45.3 / 42.4 at 3000, 52.5 / 47.9 at 6144; on 80 40.2 / 40.4 at 1304,
+//     41.4 / 46.2 at 2000, 46.8 / 52.3 at 3000, 78.6 / 60.2 at 5120; on 64 32.1 / 30.2 at 504, 34.8 / 34.1 at 752, 35.9 / 35.0 at 1000,
+//     40.7 / 41.1 at 1504, 41.7 / 46.9 at 2000, 48.2 / 52.0 at 4096; on 32 36.9 / 34.8 at 256, 37.9 / 39.0 at 384, 43.5 / 48.9 at
+//     1000, 49.6 / 70.4 at 2048; on 16 46.8 / 44.0 at 128, 46.8 / 48.2 at 256, 59.1 / 78.6 at 1024; on 8 64.6 / 61.8 at 64,
+//     65.7 / 66.1 at 128, 77.9 / 97.3 at 512;
+//   108:400:200:100:21: 47.7 / 43.0 at 1000, 50.8 / 46.8 at 4096, 63.5 / 54.6 at 8192; on 128 compute units 65.0 / 54.6 at 4096; on 64
+//     64.6 / 61.3 at 1024, 77.9 / 67.2 at 2048; on 8 179 / 168 at 256;
+//   211:512:512:256:128:20: 75.9 / 70.9 at 1000, 86.2 / 80.8 at 4096; on 64 compute units 129 / 124 at 1000; on 8 450 / 447 at 128;
+//   211:512:512:512:256:20: 93.3 / 89.7 at 1000, 104.7 / 102.2 at 4096; on 64 compute units 162 / 158 at 1024; on 8 628 / 626 at 128.
+// So this kernel serves such a shape only on fewer than 96 compute units, where it keeps the gradients in registers, from 12 rows per
+// compute unit on (the first of the sizes above at which it is no slower, within 3 %) and while every tile has a workgroup of its own
+// (one per net and two of the instance's compute units; 128-row tiles).  Between 64 and 96 compute units the tallest tiles lose and the
+// lower ones win (80, above); one line for both, where most sizes win.
 bool use_resident(const ModelLayout& L, int rows, int cus) {
   if (!shape_ok(L)) return false;
   if (!chain_compiled(L)) return true;
+  if (cus >= 96 || grad_sets(L) == 0 || rows < 12 * (int64_t)cus) return false;
   Plan p;
-  const int64_t tile = 32 * pick_tiles(L, INT32_MAX, 1, &p), full = tile * trainer_groups(cus);
-  if (rows > full) return false;
-  return (cus < 128 && grad_sets(L) > 0) || rows > full - tile;
+  return rows <= 32 * (int64_t)pick_tiles(L, INT32_MAX, 1, &p) * trainer_groups(cus);
 }
 
 // Rows of gradient partials the kernel may fill with this model.

@@ -119,12 +119,12 @@ def _stated_work(g, inst, cls_name, call):
 
 
 @pytest.mark.parametrize("name,T,N,rows", [
-    ("C2", 3, 5600, 16397), ("BB", 2, 8300, 16413), ("FC", 3, 5500, 16389), ("AY", 2, 8200, 16386),      # 16384: the last
-    ("C3", 2, 4200, 8205), ("HM", 3, 2800, 8321),      # 8192
-    ("C4", 2, 2100, 4099), ("SH", 3, 1400, 4133), ("C4", 2, 4300, 8191)])      # 4096 rows of the resident kernel
+    ("C2", 3, 5600, 16397), ("BB", 2, 8300, 16413), ("FC", 3, 5500, 16389), ("AY", 2, 8200, 16386),
+    ("C3", 2, 4200, 8205), ("HM", 3, 2800, 8321),
+    ("C4", 2, 2100, 4099), ("SH", 3, 1400, 4133), ("C4", 2, 4300, 8191)])
 def test_gradient_of_the_compiled_trainer_kernels_at_ragged_rows(g, inst, name, T, N, rows):
-    """The row-tile trainer kernel just beyond the rows at which the resident kernel serves
-    its shapes (use_resident).  Only their launchers state work for the class, so this also checks which kernel ran."""
+    """The row-tile trainer kernel where the last of its 64- or 128-row tiles is ragged.  Only its launchers state work for the
+    class, so this also checks which kernel ran."""
     (shape, (got_g, got_s), args), launches, flops = _stated_work(
         g, inst, "chain_train", lambda: _gradient_case(g, inst, name, T, N, rows))
     assert launches == 1 and flops > 0
@@ -135,19 +135,16 @@ def test_gradient_of_the_compiled_trainer_kernels_at_ragged_rows(g, inst, name, 
     assert np.allclose(got_s[:2], m_stats[:2], rtol=TOL_MODEL, atol=1e-5)
 
 
-@pytest.mark.parametrize("name,rows", [("C2", 16384), ("C3", 8192), ("C4", 4096), ("SH", 4096)])
-def test_the_resident_kernel_serves_the_last_rows_it_is_faster_at(g, inst, name, rows):
-    (_, (got_g, _), _), launches, flops = _stated_work(
-        g, inst, "chain_train", lambda: _gradient_case(g, inst, name, 2, rows // 2, rows))
-    assert launches == 1 and flops == 0
-    assert np.isfinite(got_g).all()
-
-
 @pytest.mark.parametrize("name,rows,cus,compiled", [
-    ("C2", 16256, 256, True), ("C2", 16258, 256, False), ("C2", 2, 256, True), ("C3", 8128, 256, True), ("C4", 4064, 256, True),
-    ("C4", 4066, 256, False), ("C2", 8064, 128, True), ("C2", 2000, 64, False), ("C3", 1000, 64, True), ("BB", 1, 256, True),
-    ("HM", 63, 256, True), ("SH", 65, 256, True)])
-def test_the_row_tile_kernel_serves_fewer_rows_than_fill_the_resident_one(g, name, rows, cus, compiled):
+    ("C2", 16256, 256, True), ("C2", 16258, 256, True), ("C2", 2, 256, True), ("C3", 8128, 256, True), ("C4", 4064, 256, True),
+    ("C4", 4066, 256, True), ("C2", 8064, 128, True), ("C2", 2000, 64, False), ("C3", 1000, 64, True), ("BB", 1, 256, True),
+    ("HM", 63, 256, True), ("SH", 65, 256, True), ("C2", 16384, 256, True), ("C3", 8192, 256, True), ("C4", 4096, 256, True),
+    ("SH", 4096, 256, True), ("C2", 8192, 128, True), ("C2", 6144, 96, True),
+    ("C2", 3000, 88, False), ("C2", 768, 64, False), ("C2", 766, 64, True)])
+def test_the_row_tile_kernel_serves_compiled_shapes_from_96_compute_units_on(g, name, rows, cus, compiled):
+    """Also the row counts that give each of the resident kernel's workgroups one tile of its own (16384, 8192, 4096 on the whole
+    device).  On fewer compute units the resident kernel, from 12 rows of each on, where it keeps the gradients in registers (C2's
+    family)."""
     from paper_2206_08482_amd.instances import cu_masks
     masked = g.gmi_create(cu_masks(256, [cus])[0]) if cus < 256 else g.gmi_create()
     (shape, (got_g, _), args), launches, flops = _stated_work(
@@ -159,11 +156,11 @@ def test_the_row_tile_kernel_serves_fewer_rows_than_fill_the_resident_one(g, nam
     g.gmi_destroy(masked)
 
 
-@pytest.mark.parametrize("name,rows,cus,compiled", [("C2", 4096, 64, False), ("C2", 4099, 64, True), ("C3", 1024, 32, False),
-                                                    ("C3", 1029, 32, True), ("C4", 512, 32, False), ("C4", 515, 32, True)])
+@pytest.mark.parametrize("name,rows,cus,compiled", [("C2", 4096, 64, False), ("C2", 4099, 64, True), ("C3", 1024, 32, True),
+                                                    ("C3", 1029, 32, True), ("C4", 512, 32, True), ("C4", 515, 32, True)])
 def test_the_trainer_kernel_follows_the_compute_units_of_the_instance(g, name, rows, cus, compiled):
-    """The resident kernel serves a compiled shape while each of its tiles has a workgroup of its own: on 64 compute units
-    a quarter of the rows that the whole device takes."""
+    """The resident kernel serves a compiled shape on fewer than 96 compute units, where it keeps the gradients in registers, while each
+    of its tiles has a workgroup of its own: on 64 compute units 32 tiles of 128 rows."""
     from paper_2206_08482_amd.instances import cu_masks
     masked = g.gmi_create(cu_masks(256, [cus])[0])
     (shape, (got_g, _), args), launches, flops = _stated_work(

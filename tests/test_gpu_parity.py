@@ -267,7 +267,7 @@ def _theta_and_batch(cfg, T, N, seed=1):
 @pytest.mark.parametrize("path", ["chain", "layers"])
 def test_gradient_and_stats_match_oracle(g, inst, name, T, N, rows, dtype, ratios, path):
     """path: which trainer kernels compute forward, loss and input gradients: "chain" the one-launch kernels (the
-    library's default: the resident kernel or, by use_resident, the row-tile kernel; just beyond the resident kernel's rows:
+    library's default: of these shapes the row-tile kernel; more of its rows:
     test_gradient_of_the_compiled_trainer_kernels_at_ragged_rows), "layers" the per-layer kernels.
     ratios = "straddle": old/new probability ratios spread smoothly across the clip range, so some
     samples sit within rounding distance of a clip boundary.  Which side such a sample falls on is a
