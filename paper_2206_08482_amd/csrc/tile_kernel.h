@@ -526,7 +526,7 @@ __device__ __forceinline__ void loss_epilogue(Ctx<S>& c, const ChainArgs& a, con
         const int i = 4 * q + e;
         const float mu = acc[i] + bv[e];
         isg[i] = igv[e];
-        z[i] = (av[e] - mu) * igv[e];                         // 0 for f >= A
+        z[i] = f0 + e < A ? (av[e] - mu) * igv[e] : 0.f;      // there av may be what follows the sample (fetch_actions)
         lp += f0 + e < A ? -0.5f * z[i] * z[i] - lsv[e] - 0.918938533204672742f : 0.f;
       }
     }

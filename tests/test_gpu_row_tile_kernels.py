@@ -96,6 +96,38 @@ def test_gradient_of_every_remainder_of_the_actions(g, inst, obs, act, hidden, r
     g.gmi_model_destroy(model)
 
 
+@pytest.mark.parametrize("obs,hidden", [(60, (256, 128, 64)), (23, (256, 128, 64)), (108, (400, 200, 100)), (108, (200, 400, 100)),
+                                        (211, (512, 512, 256, 128)), (211, (512, 512, 512, 256))])
+@pytest.mark.parametrize("act,N", [(1, 1), (1, 3), (2, 1), (3, 1), (3, 2)])
+def test_gradient_does_not_depend_on_what_lies_between_the_slots(g, inst, obs, hidden, act, N):
+    """Columns of a wider experience array: the row-tile trainer kernel reads actions four at a time, at the array's start beyond a
+    sample's own.  What lies in the other columns -- NaN, infinities -- does not reach the gradient: bit for bit that with zeros."""
+    from paper_2206_08482_amd.runner import RolloutBuffers
+    T, ld = 4, N + 5
+    dev = torch.device("cuda:0")
+    theta = torch.tensor(syn.make_model_params(obs, act, hidden, 3, policy_head_scale=0.5), device=dev)
+    desc = g.model_desc(obs, act, list(hidden), g.dtype_code("bf16"), T * N)
+    shadow = torch.zeros(g.gmi_model_shadow_bytes(desc), dtype=torch.uint8, device=dev)
+    b = syn.make_rollout_batch(T, N, obs, act, seed=3)
+    b.update(adv=b["val"], ret=b["rew"])
+    torch.cuda.synchronize()
+    model = g.gmi_model_bind(inst, desc, theta, shadow, torch.zeros_like(theta), torch.zeros_like(theta))
+    g.gmi_model_refresh_shadow(inst, model)
+    out = []
+    for other in (0.0, float("nan"), float("inf")):
+        rb = RolloutBuffers(T, ld, obs, act, dev)
+        for k in ("obs", "act", "logp", "val", "rew", "adv", "ret"):
+            getattr(rb, k).fill_(other)
+            getattr(rb, k)[:, :N].copy_(torch.tensor(b[k]))
+        torch.cuda.synchronize()
+        buf = g.gmi_buffer_bind(inst, rb.desc(0, N))
+        out.append(_gradients(g, inst, model, buf, theta.numel(), T, N, T * N, 1))
+        g.gmi_buffer_destroy(buf)
+    g.gmi_model_destroy(model)
+    for grad, stats in out:
+        assert np.isfinite(grad).all() and np.array_equal(grad, out[0][0]) and np.array_equal(stats, out[0][1])
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("obs,act,hidden,rows", [(45, 12, (128, 128), 3001), (17, 6, (64, 64), 700), (8, 2, (32, 32), 130),
                                                  (44, 18, (300, 200, 200), 1500)])
