@@ -239,11 +239,13 @@ static int forward_kind(const ModelLayout& L) {
 }
 bool has_tile_forward(const ModelLayout& L) { return forward_kind(L) == 0; }
 
-// agent_act with the agent kernel / with this one, us: 211:512:512:256:128:20 19 / 20 for 2048 rows, 21 / 21 for 4096, 34 / 25 for 8192,
-// 44 / 31 for 9216, 50 / 33 for 12288, on 64 compute units 18 / 20 for 1024, 27 / 20 for 2048, 40 / 25 for 3072, on 16 18 / 20 for 256, 27 / 20 for
-// 512, 39 / 25 for 768; 211:512:512:512:256:20 27 / 26 for 4096 rows, 44 / 32 for 8192, 62 / 43 for 12288, on 64 compute units 34 / 24 for
-// 2048, 50 / 33 for 3072.  They cross at 16 rows per compute unit; the line stays at 48, where it was when they crossed there: the two add
-// in different orders, and below it a caller's results would change in the last bit, of agent_act and of a collection alike.
+// agent_act with the agent kernel / with this one, us: 211:512:512:256:128:20 18.4 / 20.3 for 2048 rows, 19.5 / 20.8 for 4096, 27.2 / 20.8 for
+// 4352, 30.2 / 23.7 for 8192, 41.9 / 28.6 for 9216, 43.0 / 30.2 for 12032, on 64 compute units 18.3 / 20.3 for 1024, 26.7 / 20.2 for 1088,
+// 39.1 / 25.7 for 2304, on 16 18.2 / 19.9 for 256, 26.5 / 20.0 for 272; 211:512:512:512:256:20 24.4 / 25.3 for 4096 rows, 33.7 / 27.0 for 4352,
+// 39.1 / 29.2 for 8192, 54.7 / 35.6 for 9216, on 64 compute units 23.1 / 24.4 for 1024, 33.0 / 24.5 for 1088.  A collection of 16 steps of
+// them: 661 / 676 for 4096 envs, 901 / 781 for 6144, 1319 / 1090 for 12280; 750 / 785, 1024 / 877, 1541 / 1238.  agent_value alone, the same
+// network pass bit for bit and so the same line: 16.9 / 17.3 and 20.6 / 21.5 from 17 to 32 rows per compute unit, 26.8 / 17.3 and 34.0 / 21.6
+// beyond.  The two add in different orders (error against 64 bits 5.39e-3 and 5.39e-3): a row's last bit depends on the side of the line.
 // The shapes whose kernel computes in the agent kernel's order are free to choose.  Agent kernel / this one, us:
 //   60:256:128:64:8 8.6 / 7.6 for 64 rows, 9.0 / 8.3 for 4096, 11.0 / 8.5 for 8192, 25 / 16 for 32768, 168 / 102 for 262144, on 64 compute
 //     units 8.6 / 7.8 for 256, 10.4 / 8.2 for 2048;
@@ -252,11 +254,10 @@ bool has_tile_forward(const ModelLayout& L) { return forward_kind(L) == 0; }
 //   23:256:128:64:9, whose rows start at any 4-byte address, 9.1 / 9.3 for 2048, 9.3 / 9.3 for 4096, 10.8 / 9.3 for 5000, 172 / 99 for 262144.
 // The values of a collection of 108:400:200:100:21 (4096 envs, 32 steps) 128 / 79.
 // So: layers of more than 8 feature tiles, which this kernel's 4 waves take 4 at a time and the agent kernel's 8 waves 2, and unaligned
-// rows, from the rows on that give the agent kernel more than one workgroup per compute unit; else always.
+// rows, from the rows on that give the agent kernel more than one workgroup per compute unit (32 rows of one net each); else always.
 bool use_tile_forward(const gmi_instance* g, const gmi_model* m, int64_t rows) {
   const ModelLayout& L = m->L;
   const int kind = forward_kind(L);
-  if (kind == 0) return rows >= 48 * (int64_t)g->cu_count;
   if (kind < 0 || L.obs_dim < 4) return false;
   return (cd_maxdim(dims_of(L)) <= 256 && L.obs_dim % 4 == 0) || rows > 16 * (int64_t)g->cu_count;
 }

@@ -159,11 +159,13 @@ def test_gradient_on_eight_compute_units_equals_the_per_layer_kernels(g, obs, ac
     (108, 21, [400, 200, 100], 8200, 0),      # the same where two 64-row tiles do not fit: 32-row tiles in turn
     (200, 33, [512, 512, 300], 130, 0),       # a head of two feature tiles; weights beyond 1 MB
     (200, 20, [512, 512, 300], 65600, 0),     # ... and 64-row tiles one per compute unit
-    (211, 20, [512, 512, 256, 128], 12287, 0),      # the last size below the row-tile forward kernel
+    (211, 20, [512, 512, 256, 128], 4096, 0),       # the last size below the row-tile forward kernel
     (30, 5, [64] * 8, 100, 0),                # the most layers
     (211, 20, [512, 512, 256, 128], 12293, 0),      # row-tile forward kernel: rows gathered 16 at a time, ragged last ones
     (211, 20, [512, 512, 256, 128], 12293, 1),      # ... row by row (not 16-byte aligned)
-    (211, 20, [512, 512, 512, 256], 12287, 0), (211, 20, [512, 512, 512, 256], 12307, 0),      # the same two kernels, widest shape
+    (211, 20, [512, 512, 256, 128], 4097, 1), (211, 20, [512, 512, 256, 128], 12287, 0),
+    (211, 20, [512, 512, 512, 256], 4096, 0), (211, 20, [512, 512, 512, 256], 4097, 0),      # the same two kernels, widest shape
+    (211, 20, [512, 512, 512, 256], 12287, 0), (211, 20, [512, 512, 512, 256], 12307, 0),
 ])
 def test_agent_kernel_matches_the_per_layer_path(g, inst, obs, act, hidden, n, shift):
     """Both paths round the same activations to bf16 after sums in another order: an activation may land on the other
@@ -498,10 +500,11 @@ def test_values_of_a_collection_on_few_compute_units(g, obs, act, hidden, n, T):
         s.close()
 
 
-@pytest.mark.parametrize("n,cus,tile", [(12341, None, True), (12287, None, False), (777, 16, True), (767, 16, False)])
+@pytest.mark.parametrize("n,cus,tile", [(12341, None, True), (4097, None, True), (4096, None, False), (777, 16, True), (257, 16, True),
+                                        (256, 16, False)])
 @pytest.mark.parametrize("hidden", [[512, 512, 256, 128], [512, 512, 512, 256]])
 def test_two_launch_collection_through_the_row_tile_kernel(g, hidden, n, cus, tile):
-    """From 48 envs per compute unit on (12288 on the whole device) the 512-wide models collect through the forward-only
+    """Beyond 16 envs per compute unit (4096 on the whole device) the 512-wide models collect through the forward-only
     row-tile kernel, as agent_act does: bit for bit the step-by-step calls, a ragged last tile included.  Of the class's
     kernels only that one states its work."""
     ses = _collecting_sessions(211, 20, hidden, "bf16", n, 2, cus)
