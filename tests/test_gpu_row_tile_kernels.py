@@ -265,6 +265,50 @@ def test_fp8_row_tile_decisions_are_those_of_the_agent_kernel(g, inst, obs, act,
         assert np.isfinite(a).all() and np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("dtype,obs", [("bf16", 60), ("bf16", 48), ("bf16", 24), ("bf16", 4), ("fp8", 60), ("fp8", 23), ("fp8", 4)])
+@pytest.mark.parametrize("act", [1, 8, 31])
+@pytest.mark.parametrize("n", [1, 63, 65, 300])
+def test_narrow_row_tile_decisions_are_those_of_the_agent_kernel(g, inst, dtype, obs, act, n):
+    """256:128:64, which the row-tile kernel serves at every number of rows: against the same network on its first three observations
+    alone, which the agent kernel serves (rows of fewer than four), the others being zero: products that add nothing.  Bit for bit."""
+    hidden, dev = [256, 128, 64], torch.device("cuda:0")
+    small = syn.make_model_params(3, act, hidden, 5, policy_head_scale=0.5)
+    big, at = [], 0
+    for out in (act, 1):
+        prev = 3
+        for i, w in enumerate(hidden + [out]):
+            m = small[at:at + w * prev].reshape(w, prev)
+            at += w * prev
+            # the new columns repeat the first one: a layer's largest weight, and with it the fp8 scale, stays
+            big += [np.concatenate([m, np.repeat(m[:, :1], obs - 3, 1)], 1).ravel() if i == 0 else m.ravel(), small[at:at + w]]
+            at += w
+            prev = w
+    big = np.concatenate(big + [small[at:]]).astype(np.float32)
+    x = torch.randn(n, 3, generator=torch.Generator().manual_seed(n)).to(dev)
+    wide = torch.zeros(n, obs, device=dev)
+    wide[:, :3] = x
+    out = []
+    for o, t, rows in ((3, small, x), (obs, big, wide)):
+        theta = torch.tensor(t, device=dev)
+        desc = g.model_desc(o, act, hidden, g.dtype_code("bf16"), n)
+        r = [torch.full(s, float("nan"), device=dev) for s in ((n, act), (n,), (n,), (n, act))]
+        shadow = torch.zeros(g.gmi_model_shadow_bytes(desc), dtype=torch.uint8, device=dev)
+        torch.cuda.synchronize()
+        if dtype == "fp8":
+            model = g.gmi_fp8_bind(inst, desc)
+            g.gmi_fp8_refresh(inst, model, theta)
+            g.agent_act_fp8(inst, model, rows, n, 42, 9, 100, *r)
+        else:
+            model = g.gmi_model_bind(inst, desc, theta, shadow)
+            g.gmi_model_refresh_shadow(inst, model)
+            g.agent_act(inst, model, rows, n, 42, 9, 100, *r)
+        g.gmi_sync(inst)
+        (g.gmi_fp8_destroy if dtype == "fp8" else g.gmi_model_destroy)(model)
+        out.append([v.cpu().numpy() for v in r])
+    for a, b in zip(*out):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("obs,act,hidden,n", [
     (211, 20, [512, 512, 256, 128], 32769),   # 128 rows on 16 waves
     (60, 8, [256, 128, 64], 32801),           # two 128-row tiles per compute unit
