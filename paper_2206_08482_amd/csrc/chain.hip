@@ -157,7 +157,8 @@ void fill_chain_emit(const ModelLayout& L, ChainEmit* ce) {
 
 // Gather of the minibatch rows idx[0..rows) of buffer b + forward + loss + input gradients.
 // Leaves m->h, m->dz ready for the weight-gradient launch and one row of statistics / log_std partials per
-// tile in m->stat_part (*n_stat_rows rows, the layout of the loss kernel's per-workgroup rows).  GMI_ERR_UNSUPPORTED (no message) if no kernel is compiled for this shape.
+// tile in m->stat_part (*n_stat_rows rows, the layout of the loss kernel's per-workgroup rows).  GMI_ERR_UNSUPPORTED (no message) if
+// no kernel is compiled for this shape.
 int prepare_obs16(gmi_instance* g, gmi_model* m, gmi_buffer* b, int rows, int cus, bool* ready) {
   const ModelLayout& L = m->L;
   *ready = false;
@@ -239,19 +240,23 @@ static int forward_kind(const ModelLayout& L) {
 }
 bool has_tile_forward(const ModelLayout& L) { return forward_kind(L) == 0; }
 
-// agent_act with the agent kernel / with this one, us: 211:512:512:256:128:20 18.4 / 20.3 for 2048 rows, 19.5 / 20.8 for 4096, 27.2 / 20.8 for
-// 4352, 30.2 / 23.7 for 8192, 41.9 / 28.6 for 9216, 43.0 / 30.2 for 12032, on 64 compute units 18.3 / 20.3 for 1024, 26.7 / 20.2 for 1088,
-// 39.1 / 25.7 for 2304, on 16 18.2 / 19.9 for 256, 26.5 / 20.0 for 272; 211:512:512:512:256:20 24.4 / 25.3 for 4096 rows, 33.7 / 27.0 for 4352,
-// 39.1 / 29.2 for 8192, 54.7 / 35.6 for 9216, on 64 compute units 23.1 / 24.4 for 1024, 33.0 / 24.5 for 1088.  A collection of 16 steps of
-// them: 661 / 676 for 4096 envs, 901 / 781 for 6144, 1319 / 1090 for 12280; 750 / 785, 1024 / 877, 1541 / 1238.  agent_value alone, the same
-// network pass bit for bit and so the same line: 16.9 / 17.3 and 20.6 / 21.5 from 17 to 32 rows per compute unit, 26.8 / 17.3 and 34.0 / 21.6
-// beyond.  The two add in different orders (error against 64 bits 5.39e-3 and 5.39e-3): a row's last bit depends on the side of the line.
+// agent_act with the agent kernel / with this one, us:
+//   211:512:512:256:128:20 18.4 / 20.3 for 2048 rows, 19.5 / 20.8 for 4096, 27.2 / 20.8 for 4352, 30.2 / 23.7 for 8192, 41.9 / 28.6 for 9216,
+//     43.0 / 30.2 for 12032, on 64 compute units 18.3 / 20.3 for 1024, 26.7 / 20.2 for 1088, 39.1 / 25.7 for 2304, on 16 18.2 / 19.9 for
+//     256, 26.5 / 20.0 for 272;
+//   211:512:512:512:256:20 24.4 / 25.3 for 4096 rows, 33.7 / 27.0 for 4352, 39.1 / 29.2 for 8192, 54.7 / 35.6 for 9216, on 64 compute
+//     units 23.1 / 24.4 for 1024, 33.0 / 24.5 for 1088.
+// A collection of 16 steps of them: 661 / 676 for 4096 envs, 901 / 781 for 6144, 1319 / 1090 for 12280; 750 / 785, 1024 / 877, 1541 / 1238.
+// agent_value alone, the same network pass bit for bit and so the same line: 16.9 / 17.3 and 20.6 / 21.5 from 17 to 32 rows per
+// compute unit, 26.8 / 17.3 and 34.0 / 21.6 beyond.  The two add in different orders (error against 64 bits 5.39e-3 and 5.39e-3): a
+// row's last bit depends on the side of the line.
 // The shapes whose kernel computes in the agent kernel's order are free to choose.  Agent kernel / this one, us:
 //   60:256:128:64:8 8.6 / 7.6 for 64 rows, 9.0 / 8.3 for 4096, 11.0 / 8.5 for 8192, 25 / 16 for 32768, 168 / 102 for 262144, on 64 compute
 //     units 8.6 / 7.8 for 256, 10.4 / 8.2 for 2048;
 //   108:400:200:100:21 11.9 / 13.7 for 512 rows, 12.6 / 14.0 for 4096, 15.7 / 14.2 for 5000, 31 / 19 for 16384, 428 / 262 for 262144, on 64
 //     compute units 11.9 / 13.7 for 1024, 15.0 / 13.7 for 2048, on 16 11.8 / 13.3 for 256, 14.9 / 13.7 for 512;
-//   23:256:128:64:9, whose rows start at any 4-byte address, 9.1 / 9.3 for 2048, 9.3 / 9.3 for 4096, 10.8 / 9.3 for 5000, 172 / 99 for 262144.
+//   23:256:128:64:9, whose rows start at any 4-byte address, 9.1 / 9.3 for 2048, 9.3 / 9.3 for 4096, 10.8 / 9.3 for 5000, 172 / 99 for
+//     262144.
 // The values of a collection of 108:400:200:100:21 (4096 envs, 32 steps) 128 / 79.
 // So: layers of more than 8 feature tiles, which this kernel's 4 waves take 4 at a time and the agent kernel's 8 waves 2, and unaligned
 // rows, from the rows on that give the agent kernel more than one workgroup per compute unit (32 rows of one net each); else always.
@@ -305,17 +310,13 @@ int launch_forward_chain(gmi_instance* g, gmi_model* m, const float* obs, int n_
   ChainArgs a = {};
   fill_forward(m, &a);
   a.b_obs = obs;
-  a.x0_ready = !forward_chain_reads_x0(m, obs) ? 0 : (x0_valid || L.obs_dim < 4 ? 1 : 3);
+  a.x0_ready = !forward_chain_reads_x0(m, obs) ? 0 : (x0_valid ? 1 : 3);
   a.rows = n_rows;
   a.net0 = policy ? 0 : 1;
   a.mu_out = mu; a.val_out = val;
   if (sample) {
     a.act_out = sample->act; a.logp_out = sample->logp;
     a.k0 = (uint32_t)sample->seed; a.k1 = (uint32_t)(sample->seed >> 32); a.step = sample->step; a.env_offset = sample->env_offset;
-  }
-  if (a.x0_ready == 1 && !x0_valid) {
-    const int rc = launch_gather(g, m, obs, n_rows, n_rows, nullptr, n_rows, nullptr);
-    if (rc != GMI_OK) return rc;
   }
   return launch_forward(g, m, a, (mu ? L.act_dim : 0) + (sample ? L.act_dim + 1 : 0) + 1);
 }

@@ -368,8 +368,8 @@ int launch_env_step(gmi_instance* g, gmi_env* env, const float* obs, const float
   if (lds_bytes(ept) + (size_t)EB * (OS - O - A) * sizeof(float) > 64 * 1024) OS = O + A;
   const size_t lds = lds_bytes(ept) + (size_t)EB * (OS - O - A) * sizeof(float);
   // Four waves of 16 output blocks are the 4 envs' workgroup of 52 to 64 blocks.  Vector form / matrix instruction, us: 211 + 20, 512 envs
-  // 13.8 / 11.2, 4096 32.6 / 19.4, 12288 49.1 / 36.2, 16384 43.3 / 41.5, 65536 149 / 135, 262144 629 / 566; 256 + 32, 4096 38.5 / 22.3, 65536 185 / 165;
-  // a step of the collection of 16384 envs of 211 + 20 53.6 / 51.8.  Two or four groups of envs beside fewer blocks lose at large numbers:
+  // 13.8 / 11.2, 4096 32.6 / 19.4, 12288 49.1 / 36.2, 16384 43.3 / 41.5, 65536 149 / 135, 262144 629 / 566; 256 + 32, 4096 38.5 / 22.3,
+  // 65536 185 / 165; a step of the collection of 16384 envs of 211 + 20 53.6 / 51.8.  Two or four groups of envs beside fewer blocks lose at large numbers:
   // 108 + 21, 524288 envs 423 / 435, 60 + 8, 1048576 envs 344 / 372.
   const bool mf = G == 4 && (OS & 3) == 0;
   const unsigned grid = (unsigned)((N + EB - 1) / EB);
@@ -378,7 +378,7 @@ int launch_env_step(gmi_instance* g, gmi_env* env, const float* obs, const float
   const StepFuse fu = fuse ? *fuse : StepFuse{};
   gmi::ProfScope ps(g, gmi::kClsEnvStep);
 #define GMI_ENV_LAUNCH(E, F)                                                                       \
-  ps.launch(mf ? env_step_kernel<E, F, true> : env_step_kernel<E, F, false>, dim3(grid), dim3(256), lds,                                    \
+  ps.launch(mf ? env_step_kernel<E, F, true> : env_step_kernel<E, F, false>, dim3(grid), dim3(256), lds,  \
       obs, act, env->m_t, env->episode_step, next_obs, reward, done, N, O, A, OS, o4, nb, G,          \
       d.noise_std, d.reward_scale, d.done_period, d.done_threshold, k0, k1, d.env_offset, step, vec_store, fu)
   if (fuse) {

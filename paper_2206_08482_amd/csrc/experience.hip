@@ -58,8 +58,8 @@ __device__ __forceinline__ void norm_factors(double s1, double s2, double n, flo
 // Reverse recurrence over the horizon, one lane per env: the time-major layout makes every step's
 // loads and stores of a wave one contiguous segment.  Also leaves per-workgroup sums of A and A^2.  The recurrence waits for memory
 // once per kGaeAhead steps, whose loads go out together (us with 4 / 16 steps: 4096 envs and 32 steps 14.2 / 6.6, 512 and 32 11.2 / 5.4).
-// norm: the only workgroup normalises its advantages itself, as normalize_kernel would in another launch (64 envs and 16 steps 5.6 + 4.5 us,
-// now 4.6).
+// norm: the only workgroup normalises its advantages itself, as normalize_kernel would in another launch (64 envs and 16 steps
+// 5.6 + 4.5 us, now 4.6).
 constexpr int kGaeAhead = 16;
 __global__ __launch_bounds__(256) void gae_kernel(gmi_buffer_desc d, const float* __restrict__ last_value,
                                                   float gamma, float gl, double* __restrict__ part, int norm) {
@@ -195,7 +195,8 @@ __global__ __launch_bounds__(256) void gae_scan_kernel(gmi_buffer_desc d, const 
 int g_gae_variant = 0;
 
 // Launches the chosen GAE kernel on `stream`; returns the number of partial-sum pairs it leaves in `part`, 0 if the kernel has
-// normalised the advantages itself: one workgroup that holds them all, while its walk is short (256 envs and 64 steps 15.0 us for both launches, now 11.1).
+// normalised the advantages itself: one workgroup that holds them all, while its walk is short (256 envs and 64 steps 15.0 us for
+// both launches, now 11.1).
 template <typename Launch>
 int launch_gae(int variant, const gmi_buffer_desc& d, const float* last_value, float gamma, float gl, double* part,
                Launch&& launch) {

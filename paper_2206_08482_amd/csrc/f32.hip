@@ -473,8 +473,9 @@ struct TrainF32Args {
 };
 
 // What the kernel waits for first -- sample indices, then the rows they name -- is requested first; the biases travel meanwhile.
-// The weights are read from L2: an LDS copy of them made by every workgroup costs more instructions than its reads save.  Loss: 8 lanes per sample share its actions.  Backward, a layer: input-gradient tiles, weight-gradient tiles
-// and, with the head's, the sums over the tile's samples (statistics, log_std) are items of one list, dealt to the waves.
+// The weights are read from L2: an LDS copy of them made by every workgroup costs more instructions than its reads save.  Loss: 8
+// lanes per sample share its actions.  Backward, a layer: input-gradient tiles, weight-gradient tiles and, with the head's, the sums
+// over the tile's samples (statistics, log_std) are items of one list, dealt to the waves.
 template <int RT>
 __global__ __launch_bounds__(kNT) void train_f32_kernel(TrainF32Args a) {
   constexpr int R = 16 * RT;
@@ -539,7 +540,8 @@ __global__ __launch_bounds__(kNT) void train_f32_kernel(TrainF32Args a) {
         const F32Layer L = N[l];
         const float* x = s_h + a.h_off[l];
         if (l < nl - 1)
-          layer<false, kHidden>(a.params, L, nullptr, bias, x, rstride(L.in), nullptr, s_h + a.h_off[l + 1], rstride(L.out), RT, wave, kNW, lane);
+          layer<false, kHidden>(a.params, L, nullptr, bias, x, rstride(L.in), nullptr, s_h + a.h_off[l + 1], rstride(L.out), RT, wave,
+                                kNW, lane);
         else
           layer<false, kHead>(a.params, L, nullptr, bias, x, rstride(L.in), nullptr, s_out, so, RT, wave, kNW, lane);
         __syncthreads();
@@ -735,7 +737,8 @@ __global__ __launch_bounds__(kNT) void rollout_f32_kernel(RolloutF32Args a) {
   const SimLane sl = sim_lane(a, wave8, OS, lane);
   auto at = [&](const float* p) { return (int)(p - smem); };
   const int draw_top = draw_thread(a, npr);
-  const NetPlan plan(N, a.nl, at(s_wn), at(s_bn), at(s_x0), sx0, at(s_a), at(s_b), a.sh, at(half ? s_val : s_mu), half ? rstride(1) : so, wave4, lane);
+  const NetPlan plan(N, a.nl, at(s_wn), at(s_bn), at(s_x0), sx0, at(s_a), at(s_b), a.sh, at(half ? s_val : s_mu), half ? rstride(1) : so,
+                     wave4, lane);
   __syncthreads();
 
   for (int tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {

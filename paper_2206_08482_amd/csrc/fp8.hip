@@ -134,8 +134,8 @@ const fp8_part_fn kTileParts[gmi::kTileFp8Parts] = {gmi::launch_tile_fp8_part0, 
 // The row-tile kernel computes in agent_kernel's order, so either may serve a call.  agent_kernel / this one, us:
 //   60:256:128:64:8 8.4 / 7.2 for 64 rows, 8.7 / 7.6 for 4096, 10.2 / 7.8 for 8192, 32 / 24 for 65536, 111 / 83 for 262144, on 64 compute
 //     units 8.5 / 7.2 for 256;
-//   108:400:200:100:21 10.8 / 13.9 for 512 rows, 13.0 / 14.1 for 5000, 14.0 / 14.6 for 8192, 17.6 / 15.2 for 12000, 67 / 58 for 65536, on 64
-//     compute units 12.4 / 13.9 for 2048, 16.6 / 14.3 for 4096;
+//   108:400:200:100:21 10.8 / 13.9 for 512 rows, 13.0 / 14.1 for 5000, 14.0 / 14.6 for 8192, 17.6 / 15.2 for 12000, 67 / 58 for 65536, on
+//     64 compute units 12.4 / 13.9 for 2048, 16.6 / 14.3 for 4096;
 //   211:512:512:256:128:20 14 / 19 for 512 rows, 19.4 / 19.8 for 5000, 21.2 / 21.0 for 8192, 28 / 23 for 12000, 126 / 103 for 65536, on 64
 //     compute units 18.2 / 19.3 for 2048, 28.5 / 20.4 for 4096.
 // Layers of more than 8 feature tiles, which its 4 waves take 4 at a time, beyond 32 rows per compute unit; narrower models always.

@@ -14,13 +14,10 @@ typedef float float2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
 
 using gmi::elu_f;
-// ELU'(z) from the stored output h = ELU(z) >= -1: 1 if h > 0 else h + 1, as one add with the [0, 1] clamp
-__device__ __forceinline__ float elu_grad_f(float h) { return __builtin_amdgcn_fmed3f(h + 1.0f, 0.f, 1.f); }
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   float2v v = {lo, hi};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2v));
 }
-__device__ __forceinline__ float bf16_to_f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 struct FusedNet {
   const uint16_t* w[GMI_MAX_HIDDEN + 1];     // bf16, fragment-major copy of W [out_pad, in_pad]
@@ -726,14 +723,18 @@ extern "C" int rollout_collect(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_buffer
       if (lds <= kLdsMax && (o[0] != 1 || (size_t)a.m_off + (size_t)a.o4 * a.ms * 4 <= (size_t)a.hid_off + hid)) break;
     }
   }
-  if (lds > kLdsMax) GMI_FAIL(GMI_ERR_UNSUPPORTED, "rollout_collect: a 16-env tile of this model needs %zu bytes of LDS (limit %zu)", lds, kLdsMax);
+  if (lds > kLdsMax)
+    GMI_FAIL(GMI_ERR_UNSUPPORTED, "rollout_collect: a 16-env tile of this model needs %zu bytes of LDS (limit %zu)", lds, kLdsMax);
   set_rows(&a, rows_per_wg);
   // weight-stationary variant where this model's padded widths have one (both nets share them)
   typedef void (*rollout_fn)(RolloutArgs);
   rollout_fn kfn = rows_per_wg == 64 ? rollout_fused_kernel<2> : rollout_fused_kernel<1>;
   int variant = rows_per_wg == 64 ? 1 : 0;
   if (ws_matches<WsAnt>(L)) { kfn = rows_per_wg == 64 ? rollout_fused_kernel<2, WsAnt> : rollout_fused_kernel<1, WsAnt>; variant += 2; }
-  else if (ws_matches<WsSmallObs>(L)) { kfn = rows_per_wg == 64 ? rollout_fused_kernel<2, WsSmallObs> : rollout_fused_kernel<1, WsSmallObs>; variant += 4; }
+  else if (ws_matches<WsSmallObs>(L)) {
+    kfn = rows_per_wg == 64 ? rollout_fused_kernel<2, WsSmallObs> : rollout_fused_kernel<1, WsSmallObs>;
+    variant += 4;
+  }
   // 16 envs per workgroup: the nets on 16-row products
   if (rows_per_wg == 16) {
     if (variant == 2) { kfn = rollout_fused_kernel<1, WsAnt, true>; variant = 6; }

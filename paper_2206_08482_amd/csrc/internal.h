@@ -87,12 +87,12 @@ __device__ __forceinline__ uint4 load_uniform(const void* base, int s_off, uint3
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
-// 16 bytes to base + off + s_off (base and s_off wave-uniform, offsets < 4 GiB) written through the second-level cache (sc0 sc1).  For what a kernel
-// leaves to the next one: written back otherwise, up to 4 MB per die stay dirty until the kernel's end, and the write-back that
-// ends a kernel runs at 2.5 TB/s with the compute units idle.  Measured, us per launch with ordinary stores / these:
-// train_resident_kernel of 45:128:128:12 with 6000 rows (17 MB of gradient partials) 25.8 / 23.7, train_tile_kernel of
-// 211:512:512:256:128:20 with 32768 rows 220 / 216.  Non-temporal stores
-// bypass the memory-side cache as well: the kernel that reads them waits longer (Adam 7.2 / 8.4).
+// 16 bytes to base + off + s_off (base and s_off wave-uniform, offsets < 4 GiB) written through the second-level cache (sc0 sc1).
+// For what a kernel leaves to the next one: written back otherwise, up to 4 MB per die stay dirty until the kernel's end, and the
+// write-back that ends a kernel runs at 2.5 TB/s with the compute units idle.  Measured, us per launch with ordinary stores /
+// these: train_resident_kernel of 45:128:128:12 with 6000 rows (17 MB of gradient partials) 25.8 / 23.7; train_tile_kernel with 32768
+// rows, whose last stores are a small part of all, 186.1 / 185.2 (211:512:512:256:128:20), 41.5 / 41.2 (60:256:128:64:8).  Non-temporal
+// stores bypass the memory-side cache as well: the kernel that reads them waits longer (Adam 7.2 / 8.4).
 // s_off goes into the vector offset, not into the instruction's scalar one: the compiler takes a store with a register there to have
 // read its data at once and lets the next instruction overwrite them, and the first word of the data was then sometimes that
 // instruction's (seen in a build of train_tile_kernel with a v_ashrrev right behind the store).  Without one it keeps them apart.

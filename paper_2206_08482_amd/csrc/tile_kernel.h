@@ -3,19 +3,16 @@
 // of Section 5.1 of the paper, the "DRL Trainer" role of Section 3) in one launch per minibatch.
 //
 // A workgroup owns 64 samples (4 waves, two workgroups per compute unit) or 128 (8 waves) and keeps their current activations in
-// LDS, as the second operands of
-// the 32x32x16 matrix instruction: block (k step ks, row tile rt) = 1 KiB, lane L of it = the 8 contraction
-// values of sample 32 rt + L % 32 that operand lane L takes.  Every product is computed transposed,
-// H^T = W X^T, and a wave owns a slice of the layer's OUTPUT FEATURES for all samples (8 accumulator tiles = 128 registers at
-// most; where there are fewer feature tiles than waves, two or four waves share one and split its rows): per k step it fetches its own
-// weight blocks straight
-// from the second-level cache into registers (no other wave of the workgroup needs them) and the activation
-// blocks from LDS, i.e. 6 KiB of operands for 8 matrix instructions.  (With a wave per 32 samples and the weights
-// in LDS every wave reads every weight block: 1 KiB of LDS traffic per matrix instruction, which is the LDS
-// bandwidth of a compute unit.)  The weights come from the weight stream (chain_stream.h): its blocks are the first operands of
-// exactly these products, its k order inside a 16-wide
-// step is the order in which the matrix instruction leaves its results in a lane, so a lane's 8 results of a
-// k step are written back to LDS as one 16-byte piece at its own lane's slot.
+// LDS, as the second operands of the 32x32x16 matrix instruction: block (k step ks, row tile rt) = 1 KiB, lane L of it = the 8
+// contraction values of sample 32 rt + L % 32 that operand lane L takes.  Every product is computed transposed, H^T = W X^T, and a
+// wave owns a slice of the layer's OUTPUT FEATURES for all samples (8 accumulator tiles = 128 registers at most; where there are
+// fewer feature tiles than waves, two or four waves share one and split its rows): per k step it fetches its own weight blocks
+// straight from the second-level cache into registers (no other wave of the workgroup needs them) and the activation blocks from
+// LDS, i.e. 6 KiB of operands for 8 matrix instructions.  (With a wave per 32 samples and the weights in LDS every wave reads every
+// weight block: 1 KiB of LDS traffic per matrix instruction, which is the LDS bandwidth of a compute unit.)  The weights come from
+// the weight stream (chain_stream.h): its blocks are the first operands of exactly these products, its k order inside a 16-wide step
+// is the order in which the matrix instruction leaves its results in a lane, so a lane's 8 results of a k step are written back to
+// LDS as one 16-byte piece at its own lane's slot.
 //
 // A layer is: k loop (all accumulators of the layer live at once) - barrier - epilogue (bias + ELU, or x ELU' of
 // the stored activation; conversion; the results into LDS in place of the layer's input; from there they go to memory
@@ -308,7 +305,9 @@ __device__ __forceinline__ void read_x(Ctx<S>& c) {
 __device__ __forceinline__ int64_t block_word(int tr, int nks, int ks, int rt) { return (((int64_t)tr * nks + ks) * 4 + rt) * 64; }
 
 // One block to memory for the weight-gradient kernel.
-__device__ __forceinline__ void store_block(uint4* blk, uint32_t lane16, const uint4& v, int off = 0) { gmi::store_through(blk, lane16, v, off); }
+__device__ __forceinline__ void store_block(uint4* blk, uint32_t lane16, const uint4& v, int off = 0) {
+  gmi::store_through(blk, lane16, v, off);
+}
 
 // Stored activations h[layer] of tile T = a * RT + b of this wave (input-gradient epilogue of segment SEG): the
 // lane's own slots of the blocks (2 ft, b) and (2 ft + 1, b), i.e. the values at the positions of its 16 results.
@@ -334,9 +333,8 @@ __device__ __forceinline__ void fetch_h_first(Ctx<S>& c, const ChainArgs& a) {
 }
 
 // The small operations that ride along with the products of k step KS, by index I: I < RT: the activation block of
-// row tile I for k step KS + XD; then, where the segment's input goes to memory (store_x), wave w's share of that
-// move, row tile w % 4 of every other k step: I = RT reads a block of the activation area at even k steps, I = RT + 1 stores it at
-// odd ones.
+// row tile I for k step KS + XD; then, where the segment's input goes to memory (store_x), wave w's share of that move, row tile
+// w % nrt of every other k step: I = RT reads a block of the activation area at even k steps, I = RT + 1 stores it at odd ones.
 template <class S, int SEG>
 __device__ __forceinline__ uint4* store_x_array(const Ctx<S>& c, const ChainArgs& a) {
   using G = Seg<S, SEG>;
@@ -452,7 +450,8 @@ __device__ __forceinline__ void tile_epilogue(Ctx<S>& c, const ChainArgs& a) {
     }
     if constexpr (S::fp8) {      // word q: features 8 q + 4 hh .. of the tile.  The halves of the wave trade words: the lower one gets
                                  // quads 0 and 1 of both, the first block's 16 bytes of its row, the upper one quads 2 and 3
-      const auto u = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false), v = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+      const auto u = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+      const auto v = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
       c.X[((ft / 2 * 2 + c.hh) * S::nrt + rt) * 64 + c.s + 32 * (ft & 1)] = make_uint4(u[0], u[1], v[0], v[1]);
     } else if constexpr (S::nat) {      // quad q: features 8 (q % 2) + 4 hh .. of k step 2 ft + q / 2
       char* x = reinterpret_cast<char*>(c.X + ((2 * ft) * S::nrt + rt) * 64 + c.s) + 8 * c.hh;
@@ -623,10 +622,8 @@ __device__ __forceinline__ void loss_sums(const Ctx<S>& c, const ChainArgs& a) {
 // Inference: the head's results of row tile `wave` (lane = row, register i = feature 8 (i / 4) + 4 hh + i % 4) plus
 // the head's bias go out as policy means [rows, act_dim] or as values [rows], and, where actions are asked for, the decision
 // act = mean + exp(log_std) * eps and its log-density: the arithmetic of sample_kernel (model.hip), terms summed in
-// its order.
-// The draws are made beside the head's product by the waves that have no part in it.  (Gather, this kernel and sampling as three
-// launches, 16384 rows of
-// 211:512:512:256:128:20: 49 us, now 38.)
+// its order.  The draws are made beside the head's product by the waves that have no part in it.  (Gather, this kernel and sampling as
+// three launches, 16384 rows of 211:512:512:256:128:20: 49 us, now 38.)
 template <class S>
 __device__ __forceinline__ void head_draws(const Ctx<S>& c, const ChainArgs& a) {
   const int row = c.row0 + 32 * (c.wave & (S::nrt - 1)) + c.s;
@@ -755,7 +752,8 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
     if constexpr (G::last) {
       // nothing consumes the last results on chip: the activation area goes to dz[layer - 1] block by block, the way a k
       // loop moves its input
-      uint4* arr = reinterpret_cast<uint4*>(a.dz[c.net][G::layer - 1]) + block_word(c.tr, G::F / 16, c.wave / S::nrt, c.rt0 + c.wave % S::nrt);
+      uint4* arr = reinterpret_cast<uint4*>(a.dz[c.net][G::layer - 1]) +
+                   block_word(c.tr, G::F / 16, c.wave / S::nrt, c.rt0 + c.wave % S::nrt);
 #pragma unroll 8
       for (int k2 = 0; k2 < G::F / 16; k2 += 2) {
         store_block(arr, c.lane16, c.X[(k2 * S::nrt + c.wave) * 64 + c.lane], k2 * 4096);      // arrays hold whole tiles
@@ -839,7 +837,7 @@ __device__ __forceinline__ void row_tile(const ChainArgs& a, int item, unsigned 
     }
   const float ls = a.log_std[c.tid < a.act_dim ? c.tid : a.act_dim - 1];
   {
-    // The gather: the workgroup's 128 observation rows as the first layer's operand blocks in natural k order (lane
+    // The gather: the workgroup's observation rows as the first layer's operand blocks in natural k order (lane
     // (s, h) of block (ks, rt) holds features 16 ks + 8 h .. + 7 of sample 32 rt + s), zero padded.  A lane takes
     // 16-byte piece jj + 4 it of row 16 g + rr: 16 lanes write 256 consecutive bytes of LDS, 4 lanes read 64
     // consecutive bytes of a row.  The policy net's workgroups also leave the same blocks in x0b for the
@@ -1033,9 +1031,8 @@ int launch_shape(gmi_instance* g, ChainArgs a, int rows, int* tiles_out, double 
 
 namespace gmi {
 // One function per shape compiled for the row-tile kernel (trainers tile_p<k>.hip, forward-only kernels tile_f<k>.hip, fp8
-// tile_q<k>.hip): launches it if
-// the model has exactly that shape, GMI_ERR_UNSUPPORTED otherwise; rows == 0 only asks (a forward-only kernel's answer: 1 if it
-// computes as the agent kernel does).
+// tile_q<k>.hip): launches it if the model has exactly that shape, GMI_ERR_UNSUPPORTED otherwise; rows == 0 only asks (a
+// forward-only kernel's answer: 1 if it computes as the agent kernel does).
 constexpr int kTileParts = 6;
 constexpr int kTileFwdParts = 6, kTileFp8Parts = 5;
 #define GMI_TILE_PART_DECL(k)                                                                              \

@@ -321,8 +321,9 @@ __global__ __launch_bounds__(256) void adam_shadow_kernel(gmi::ShadowTable tab, 
   __shared__ float s_bsum[4][8];
   __shared__ __attribute__((aligned(16))) uint16_t s_t[8][40];
   const int n_tiles = gridDim.x - 1;
-  if (blockIdx.x == 0) {      // first: its walk over the statistics rows is the longest way of all (last and with half the loads in
-                              // flight, us: 108:400:200:100:21 with 512 rows of them 13.5, now 11.0; 211:512:512:256:128:20 with 256 26.6, now 24.0)
+  // first: its walk over the statistics rows is the longest way of all (last and with half the loads in flight, us:
+  // 108:400:200:100:21 with 512 rows of them 13.5, now 11.0; 211:512:512:256:128:20 with 256 26.6, now 24.0)
+  if (blockIdx.x == 0) {
     finish_stats<256>(tab, params, am, av, ps, part_stride, A, c_e, inv_rows, hs,
                       do_update ? reinterpret_cast<float*>(shadow + tab.sh_logstd) : nullptr, stats_out, grad_out, do_update, &s_sum[0][0]);
     return;
