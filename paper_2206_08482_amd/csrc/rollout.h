@@ -171,16 +171,21 @@ __device__ __forceinline__ void sim_items(const RolloutEnv& a, int r0, uint32_t 
   }
 }
 
-// One random block of a step: env r of the tile, block q of its npr blocks (nba action-noise blocks, nbo env-noise blocks, then
-// the done draw: raw word in .x).
+// Words of random block q of env r of the tile: its npr blocks are nba action-noise blocks, the env-noise blocks, then the done draw.
+// (Left as kernel arguments the keys are chosen between by address: loads of their own in front of every draw.)
+__device__ __forceinline__ gmi::Words4 draw_words(const RolloutEnv& a, uint32_t stp, int r0, int r, bool is_act, bool is_done, uint32_t blk) {
+  auto uniform = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+  const uint32_t ak0 = uniform(a.ak0), ak1 = uniform(a.ak1), ao = uniform(a.a_env_offset);
+  const uint32_t ek0 = uniform(a.ek0), ek1 = uniform(a.ek1), eo = uniform(a.e_env_offset);
+  const uint32_t e = (uint32_t)(r0 + r < a.n ? r0 + r : a.n - 1);
+  const uint32_t strm = is_act ? gmi::kStreamAction : (is_done ? gmi::kStreamDone : gmi::kStreamEnv);
+  return gmi::philox4x32_10((is_act ? ao : eo) + e, stp, strm, blk, is_act ? ak0 : ek0, is_act ? ak1 : ek1);
+}
+// One random block of a step (the done draw: raw word in .x).
 __device__ __forceinline__ void draw_item(const RolloutEnv& a, float4* dst, uint32_t stp, int r0, int npr, int nba, int item) {
   const int r = (int)__umulhi((uint32_t)item, a.npr_magic), q = item - r * npr;
-  const uint32_t e = (uint32_t)(r0 + r < a.n ? r0 + r : a.n - 1);
   const bool is_act = q < nba, is_done = q == npr - 1;
-  const uint32_t strm = is_act ? gmi::kStreamAction : (is_done ? gmi::kStreamDone : gmi::kStreamEnv);
-  const uint32_t blk = is_act ? (uint32_t)q : (is_done ? 0u : (uint32_t)(q - nba));
-  const gmi::Words4 w = gmi::philox4x32_10((is_act ? a.a_env_offset : a.e_env_offset) + e, stp, strm, blk,
-                                           is_act ? a.ak0 : a.ek0, is_act ? a.ak1 : a.ek1);
+  const gmi::Words4 w = draw_words(a, stp, r0, r, is_act, is_done, is_act ? (uint32_t)q : (is_done ? 0u : (uint32_t)(q - nba)));
   float z0, z1, z2, z3;
   gmi::normal_pair(w.w[0], w.w[1], z0, z1);
   gmi::normal_pair(w.w[2], w.w[3], z2, z3);
