@@ -328,60 +328,58 @@ __device__ __forceinline__ void net_forward(const float* params, const Layers& N
   }
 }
 
-// The same for 16 rows and layers of at most four feature tiles, weights in LDS, with everything that does not change from one call
-// to the next worked out once: where a lane's operands, bias and results lie (floats from the start of LDS).  A layer of such a
-// net is a few products; what a wave worked out in front of them took 1000 cycles per layer of 2500, step after step: a collection of
-// 8:32:32:2 (64 envs, 16 steps) 90.7 us, now 67.6, of 17:64:64:6 (512 envs, 32 steps) 187, now 145.
+// The same for 16 rows and layers of at most four feature tiles, for a kernel that passes over the net many times: the wave's tile of
+// every layer stays in its registers, that of the first (W0 = false: an input of more than 64 features) in LDS.
 constexpr int kPlanLayers = 4;
-struct NetPlan {
-  int w[kPlanLayers], x[kPlanLayers], b[kPlanLayers], y[kPlanLayers];
-  int meta[kPlanLayers];      // k chunks | results that are features (4 bits) << 8 | this wave has a tile << 12 | hidden << 13
-  __device__ __forceinline__ NetPlan(const Layers& N, int nl, int w0, int b0, int x0, int sx0, int ha, int hb, int sh, int out, int so, int wave,
-                                     int lane) {
-    const int j = lane & 15, g = lane >> 4;
-    int xin = x0, sx = sx0;
+template <int NL, bool W0>
+struct NetRegs {
+  float4 w[NL][4];      // this lane's pieces of row f of W
+  int nc[NL];           // k chunks; 0: the wave has no tile
+  __device__ __forceinline__ void load(const float* params, const Layers& N, int wave, int lane, float* s_w0) {
+    const int j = lane & 15, g = lane >> 4, f = 16 * wave + j;
 #pragma unroll
-    for (int l = 0; l < kPlanLayers; ++l) {
-      const F32Layer L = N[min(l, nl - 1)];
-      const bool head = l >= nl - 1;
-      const int f0 = 16 * min(wave, (pad16(L.out) >> 4) - 1), fr = f0 + 4 * g;
-      const int yo = head ? out : (l & 1 ? hb : ha), sy = head ? so : sh;
-      w[l] = w0 + (f0 + j) * rstride(L.in) + 4 * g;
-      x[l] = xin + j * sx + 4 * g;
-      b[l] = b0 + fr;
-      y[l] = yo + j * sy + fr;
-      meta[l] = (pad16(L.in) >> 4) | (wave < pad16(L.out) >> 4 ? 1 << 12 : 0) | (head ? 0 : 1 << 13);
+    for (int l = 0; l < NL; ++l) {
+      const F32Layer L = N[l];
+      nc[l] = 16 * wave < L.out ? pad16(L.in) >> 4 : 0;
+      const float* row = params + L.w_off + (int64_t)min(f, L.out - 1) * L.in;
+      auto piece = [&](int c) {      // (load_piece reads inside the row wherever the piece lies)
+        float4 v = load_piece(row, 4 * c + g, L.in);
+        if (f >= L.out) v = make_float4(0.f, 0.f, 0.f, 0.f);
+        return v;
+      };
+      if (l == 0 && !W0) {
+        for (int c = 0; c < nc[0]; ++c) *reinterpret_cast<float4*>(s_w0 + f * rstride(L.in) + 16 * c + 4 * g) = piece(c);
+      } else {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) meta[l] |= fr + v < L.out ? 256 << v : 0;
-      w0 += pad16(L.out) * rstride(L.in);
-      b0 += pad16(L.out);
-      xin = yo;
-      sx = sy;
+        for (int c = 0; c < 4; ++c)
+          if (c < nc[l]) w[l][c] = piece(c);
+      }
     }
   }
 };
-template <class Beside>
-__device__ __forceinline__ void net_forward(const NetPlan& p, float* smem, int nl, bool run, Beside beside) {
-#pragma unroll
-  for (int l = 0; l < kPlanLayers; ++l) {
-    if (l >= nl) break;
-    const int meta = __builtin_amdgcn_readfirstlane(p.meta[l]);
-    if (run && (meta & 1 << 12)) {
-      const float4 bv = *reinterpret_cast<const float4*>(smem + p.b[l]);
-      floatx4 acc[1] = {{0.f, 0.f, 0.f, 0.f}};
-      const float* wp = smem + p.w[l];
-      products<1, 4>(acc, meta & 255, [&](int c) { return *reinterpret_cast<const float4*>(wp + 16 * c); }, smem + p.x[l], 0);
-      float o[4] = {acc[0][0] + bv.x, acc[0][1] + bv.y, acc[0][2] + bv.z, acc[0][3] + bv.w};
-      if (meta & 1 << 13)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) o[v] = elu32(o[v]);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) o[v] = p.meta[l] & 256 << v ? o[v] : 0.f;
-      *reinterpret_cast<float4*>(smem + p.y[l]) = make_float4(o[0], o[1], o[2], o[3]);
-    }
-    if (l == nl - 1) beside();
-    __syncthreads();
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_for(F f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
   }
+}
+// x W^T of the wave's tile (padding features: zero) for inputs of nc chunks; xp: this lane's row and lane group of the input.
+__device__ __forceinline__ floatx4 tile_of_regs(const float4 (&w)[4], int nc, const float* xp) {
+  floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+  float4 x[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (u < nc) x[u] = *reinterpret_cast<const float4*>(xp + 16 * u);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if (u >= nc) break;
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u].x, x[u].x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u].y, x[u].y, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u].z, x[u].z, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u].w, x[u].w, acc, 0, 0, 0);
+  }
+  return acc;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -693,7 +691,7 @@ struct RolloutF32Args : RolloutEnv {
 
 __host__ __device__ __forceinline__ int in_stride(int O, int A) { return (O + A + 3) & ~3; }
 
-template <bool WL, bool PLAN>
+template <bool WL>
 __global__ __launch_bounds__(kNT) void rollout_f32_kernel(RolloutF32Args a) {
   extern __shared__ __attribute__((aligned(16))) float smem[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -735,10 +733,7 @@ __global__ __launch_bounds__(kNT) void rollout_f32_kernel(RolloutF32Args a) {
   for (int i = tid; i < R * sx0; i += kNT) s_x0[i] = 0.f;
   for (int i = tid; i < R * OS; i += kNT) s_in2[R * OS + i] = 0.f;
   const SimLane sl = sim_lane(a, wave8, OS, lane);
-  auto at = [&](const float* p) { return (int)(p - smem); };
   const int draw_top = draw_thread(a, npr);
-  const NetPlan plan(N, a.nl, at(s_wn), at(s_bn), at(s_x0), sx0, at(s_a), at(s_b), a.sh, at(half ? s_val : s_mu), half ? rstride(1) : so,
-                     wave4, lane);
   __syncthreads();
 
   for (int tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
@@ -770,9 +765,8 @@ __global__ __launch_bounds__(kNT) void rollout_f32_kernel(RolloutF32Args a) {
         if (t > 0) reward();
         if (a.ahead && t < a.T) finish_env(a, r0, slot0, et, s_noise, npr, ep, s_done);
       };
-      if constexpr (PLAN) net_forward(plan, smem, a.nl, half == 1 || t < a.T, beside);
-      else net_forward<WL>(a.params, N, a.nl, s_wn, s_bn, s_x0, sx0, s_a, s_b, a.sh, half ? s_val : s_mu, half ? rstride(1) : so, R / 16,
-                           half == 1 || t < a.T, wave4, 4, lane, beside);
+      net_forward<WL>(a.params, N, a.nl, s_wn, s_bn, s_x0, sx0, s_a, s_b, a.sh, half ? s_val : s_mu, half ? rstride(1) : so, R / 16,
+                      half == 1 || t < a.T, wave4, 4, lane, beside);
       if (t == a.T) {
         if (env_ok) a.last_value[r0 + et] = s_val[et * rstride(1)];
         break;
@@ -807,6 +801,185 @@ __global__ __launch_bounds__(kNT) void rollout_f32_kernel(RolloutF32Args a) {
     }
     if (env_ok) a.episode_step[r0 + et] = ep;
     __syncthreads();
+  }
+}
+
+// The same for small nets, 16 envs per workgroup, with the roles on waves of their own (rollout.h): waves 0-3 have the policy net, waves
+// 4-7 the value net in their registers.  LDS, in floats: what split_lds lays out.
+struct SplitLds { int x0, hid, in2, noise, lp, part, done, val, bias, ls, w0, m, floats; };
+__host__ __device__ __forceinline__ SplitLds split_lds(int O, int A, int sh, int w0_rows, int m_floats) {
+  const int OS = split_stride(O, A), nbo = (O + 3) >> 2, nba = (A + 3) >> 2, npr = nba + nbo + 1;
+  SplitLds s;
+  s.x0 = 0;                                   // [16][rstride(O)]
+  s.hid = s.x0 + 16 * rstride(O);             // [2 nets][2][16][sh]
+  s.in2 = s.hid + 64 * sh;                    // [2][16][OS]
+  s.noise = s.in2 + 32 * OS;                  // [2][16][npr] float4
+  s.lp = s.noise + 128 * npr;                 // [16][nba]
+  s.part = s.lp + 16 * nba;                   // [16][nbo]
+  s.done = s.part + 16 * nbo;                 // [16]
+  s.val = s.done + 16;                        // [16]
+  s.bias = s.val + 16;                        // [2 nets][kPlanLayers][64]
+  s.ls = s.bias + 128 * kPlanLayers;          // [A]
+  s.w0 = s.ls + ((A + 3) & ~3);               // [2 nets][w0_rows][rstride(O)] where the first layer is not in registers
+  s.m = s.w0 + 2 * w0_rows * rstride(O);      // [o4][ms] when it fits
+  s.floats = s.m + m_floats;
+  return s;
+}
+
+// NL: layers of a net.
+template <int NL, bool W0, bool MR>
+__global__ __launch_bounds__(kSplitThreads) void rollout_split_kernel(RolloutF32Args) {
+  // The kinds of waves part early, for all tiles, and each reads the arguments for itself: what one keeps in registers is nothing to
+  // the others.
+  typedef const __attribute__((address_space(4))) RolloutF32Args KernelArgs;
+  auto arguments = []() -> const RolloutF32Args& {
+    KernelArgs* p = (KernelArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const RolloutF32Args*)p;
+  };
+  auto layout = [](const RolloutF32Args& a) { return split_lds(a.obs_dim, a.act_dim, a.sh, W0 ? 0 : pad16(a.net[0].l[0].out), 0); };
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  {
+    const RolloutF32Args& a = arguments();
+    const SplitLds s = layout(a);
+    for (int j = tid; j < a.act_dim; j += kSplitThreads) smem[s.ls + j] = a.log_std[j];
+    if constexpr (MR)
+      for (int i = tid; i < a.o4 * (a.ms >> 2); i += kSplitThreads)
+        reinterpret_cast<float4*>(smem + s.m)[i] = reinterpret_cast<const float4*>(a.m_r)[i];
+    for (int i = tid; i < s.hid - s.x0; i += kSplitThreads) smem[s.x0 + i] = 0.f;
+    for (int i = tid; i < s.noise - s.in2; i += kSplitThreads) smem[s.in2 + i] = 0.f;
+  }
+  if (wave < kNetWaves) {
+    const RolloutF32Args& a = arguments();
+    const SplitLds s = layout(a);
+    const int half = wave >> 2, wave4 = (wave + 2 * half) & 3;      // (a net of two tiles: SIMDs 0, 1 and 2, 3)
+    const int O = a.obs_dim, A = a.act_dim, OS = split_stride(O, A), nba = (A + 3) >> 2, npr = nba + ((O + 3) >> 2) + 1, sx0 = rstride(O);
+    const int j = lane & 15, g = lane >> 4, b = 4 * wave4 + g;
+    const Layers N(a.net[half]);
+    NetRegs<NL, W0> net;
+    float* s_w0 = smem + s.w0 + half * (W0 ? 0 : pad16(a.net[0].l[0].out)) * sx0;
+    net.load(a.params, N, wave4, lane, s_w0);
+    float* s_bias = smem + s.bias + half * 64 * kPlanLayers;
+    if (wave4 < NL) {      // of layer wave4, feature `lane`
+      const F32Layer L = N[wave4];
+      const float v = a.params[L.b_off + min(lane, L.out - 1)];
+      s_bias[64 * wave4 + lane] = lane < L.out ? v : 0.f;
+    }
+    // exp(log_std) of the actions that this lane decides
+    auto std_of = [&](int i) { return expf(a.log_std[min(4 * b + i, A - 1)]); };
+    const float4 std = make_float4(std_of(0), std_of(1), std_of(2), std_of(3));
+    float* s_a = smem + s.hid + half * 32 * a.sh + j * a.sh + 4 * g;      // this lane's row and lane group
+    float* s_b = s_a + 16 * a.sh;
+    const float* x0 = smem + s.x0 + j * sx0 + 4 * g;
+    const float* wp = s_w0 + (16 * wave4 + j) * sx0 + 4 * g;
+    const float* bias = s_bias + 4 * b;
+    auto layer = [&](auto l_, float (&o)[4]) {      // of the wave's tile: x W^T + b
+      constexpr int l = decltype(l_)::value;
+      const float4 bv = *reinterpret_cast<const float4*>(bias + 64 * l);
+      floatx4 acc[1] = {{0.f, 0.f, 0.f, 0.f}};
+      if constexpr (l == 0 && !W0)
+        products<1, 4>(acc, net.nc[0], [&](int c) { return *reinterpret_cast<const float4*>(wp + 16 * c); }, x0, 0);
+      else
+        acc[0] = tile_of_regs(net.w[l], net.nc[l], l == 0 ? x0 : l & 1 ? s_a : s_b);
+      o[0] = acc[0][0] + bv.x; o[1] = acc[0][1] + bv.y; o[2] = acc[0][2] + bv.z; o[3] = acc[0][3] + bv.w;
+      if constexpr (l < NL - 1) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[v] = elu32(o[v]);
+        *reinterpret_cast<float4*>((l & 1 ? s_b : s_a) + 16 * wave4) = make_float4(o[0], o[1], o[2], o[3]);
+      }
+    };
+    float4* s_noise2 = reinterpret_cast<float4*>(smem + s.noise);
+    __syncthreads();
+#pragma unroll 1
+    for (int tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
+      first_draws(a, s_noise2, tile * 16, npr, nba, wave, lane);
+      if (half == 0) {
+        __builtin_amdgcn_s_setprio(2);
+#pragma unroll 1
+        for (int t = 0; t <= a.T; ++t) {
+          const bool step = t < a.T;
+          static_for<NL>([&](auto l) {
+            if (net.nc[l.value] > 0 && step) {
+              float o[4];
+              if constexpr (l.value == NL - 1) {
+                const float4 z = s_noise2[(t & 1) * 16 * npr + j * npr + min(b, nba - 1)];
+                layer(l, o);
+                if (b < nba) decide_actions(smem + s.in2 + (t & 1) * 16 * OS, OS, O, z, std, j, b, o);
+              } else {
+                layer(l, o);
+              }
+            }
+            __syncthreads();
+          });
+          __syncthreads();                    // the simulator's
+        }
+        __builtin_amdgcn_s_setprio(0);
+      } else {
+#pragma unroll 1
+        for (int t = 0; t <= a.T; ++t) {
+          static_for<NL>([&](auto l) {
+            __syncthreads();                  // an interval behind the policy
+            if (net.nc[l.value] > 0) {
+              float o[4];
+              layer(l, o);
+              if constexpr (l.value == NL - 1)
+                if (g == 0) smem[s.val + j] = o[0];
+            }
+          });
+          __syncthreads();
+        }
+      }
+      __syncthreads();                        // the final states are out
+    }
+    return;
+  }
+  auto tiles = [&](const RolloutF32Args& a, auto steps) {
+    const SplitLds s = layout(a);
+    const int O = a.obs_dim, A = a.act_dim, OS = split_stride(O, A), nba = (A + 3) >> 2, npr = nba + ((O + 3) >> 2) + 1, sx0 = rstride(O);
+    const SplitArrays arr{smem + s.in2, reinterpret_cast<float4*>(smem + s.noise), smem + s.lp, smem + s.part,
+                          reinterpret_cast<int*>(smem + s.done), smem + s.val, smem + s.ls};
+    const int at = tid - 64 * kNetWaves, r = at >> 5, c = at & 31;      // 32 threads per env
+    __syncthreads();
+#pragma unroll 1
+    for (int tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
+      const int r0 = tile * 16;
+      float* state = a.obs_state + (int64_t)min(r0 + r, a.n - 1) * O;
+      for (int k = c; k < O; k += 32) {
+        const float v = r0 + r < a.n ? state[k] : 0.f;
+        arr.in2[r * OS + k] = v;
+        smem[s.x0 + r * sx0 + k] = v;
+      }
+      first_draws(a, arr.noise2, r0, npr, nba, wave, lane);
+      steps(s, arr, r0);
+      if (r0 + r < a.n)
+        for (int k = c; k < O; k += 32) state[k] = arr.in2[(a.T & 1) * 16 * OS + r * OS + k];
+      __syncthreads();
+    }
+  };
+  if (wave < kNetWaves + kSimWaves) {
+    const RolloutF32Args& a = arguments();
+    tiles(a, [&](const SplitLds& s, const SplitArrays& arr, int r0) {
+      sim_wave_steps<NL>(a, arr, MR ? smem + s.m : a.m_r, r0, (wave + 1) & 3, lane, [&](int t, int r, int o, const float (&v)[4]) {
+        const int O = fresh(a.obs_dim), OS = split_stride(O, a.act_dim);
+        // (what lies beyond the state belongs to the next step's actions)
+        *reinterpret_cast<float4*>(arr.in2 + (~t & 1) * 16 * OS + r * OS + o) = make_float4(v[0], v[1], v[2], v[3]);
+        *reinterpret_cast<float4*>(smem + s.x0 + r * rstride(O) + o) =
+            make_float4(v[0], o + 1 < O ? v[1] : 0.f, o + 2 < O ? v[2] : 0.f, o + 3 < O ? v[3] : 0.f);
+      });
+    });
+  } else {
+    const RolloutF32Args& a = arguments();
+    tiles(a, [&](const SplitLds& s, const SplitArrays& arr, int r0) {
+      const int m = wave - kNetWaves - kSimWaves;
+      const bool env_ok = m == 0 && lane < 16 && r0 + lane < a.n;
+      uint32_t ep = env_ok ? a.episode_step[r0 + lane] : 0u;
+      draw_wave_steps<NL>(a, arr, r0, m, lane, ep);
+      if (env_ok) {
+        a.last_value[r0 + lane] = smem[s.val + lane];
+        a.episode_step[r0 + lane] = ep;
+      }
+    });
   }
 }
 
@@ -973,8 +1146,7 @@ extern "C" int rollout_collect_f32(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_bu
                 ((2 * A + 3) & ~3) + (mr ? (size_t)a.o4 * a.ms : 0));
   };
   // 32 envs per workgroup once tiles of 16 are more than the compute units, which hold one workgroup each.  us for 16 steps,
-  // 16 / 32 envs (the kernel's first form): 17:64:64:6 133 / 159 for 4096 envs, 245 / 159 for 5000; 45:128:128:12 289 / 362, 569 /
-  // 360; 60:128:64:8 243 / 301, 475 / 305
+  // 16 / 32 envs (the kernel's first form): 45:128:128:12 289 / 362 for 4096 envs, 569 / 360 for 5000; 60:128:64:8 243 / 301, 475 / 305
   // Height and refusal go by the bytes of the kernel's first form (one state per env, two steps' draws): what was refused stays
   // refused.  Without draws ahead the present form never takes more.
   auto admission = [&](int R) {
@@ -982,34 +1154,56 @@ extern "C" int rollout_collect_f32(gmi_t g, gmi_model_t m, gmi_env_t env, gmi_bu
                 (size_t)R * (rstride(O) + 4 * a.sh + rstride(A) + rstride(1) + a.o4 + 8 * npr + nba + nbo + 1) + ((R * (O + A) + 3) & ~3) +
                 ((2 * A + 3) & ~3));
   };
-  const int R = (a.n + 15) / 16 > g->cu_count && admission(32) <= kLdsMax ? 32 : 16;
+  // layers of at most four feature tiles give each of a net's four waves one tile at most: then the networks in registers and the roles
+  // of a step on waves of their own, 16 envs at any number of them.  us for 16 steps, against the other kernel (32 envs beyond 4096): 17:64:64:6 55 / 81 for 4096 envs, 98 /
+  // 126 for 8192, 141 / 244 for 9000, 231 / 364 for 20000; 100:64:64:6 112 / 153 for 1000, 320 / 478 for 9000; 8:32:2 29 / 55 for 64, 126 /
+  // 206 for 20000.
+  const int w0_rows = O <= 64 ? 0 : pad16(L.net[0][0].out), m_floats = a.o4 * a.ms;
+  const size_t split_bytes = (size_t)split_lds(O, A, a.sh, w0_rows, 0).floats * 4;
+  bool split = L.n_layers <= kPlanLayers && split_bytes <= kLdsMax && admission(16) <= kLdsMax;
+  for (int net = 0; net < 2; ++net)
+    for (const LayerInfo& li : L.net[net]) split = split && li.out <= 64;
+  const int R = !split && (a.n + 15) / 16 > g->cu_count && admission(32) <= kLdsMax ? 32 : 16;
   if (admission(R) > kLdsMax)
     GMI_FAIL(GMI_ERR_UNSUPPORTED, "rollout_collect_f32: a 16-env tile of this model needs %zu bytes of LDS (limit %zu); "
              "use agent_act / env_step / collect_experience", admission(R), kLdsMax);
   a.ahead = lds(R, false, false, true) <= kLdsMax ? 1 : 0;
   a.hid_floats = hid_floats(R, a.ahead != 0);
-  // what stays on chip for all steps: the networks' weights first (read by every layer; 17:64:64:6, 16 steps: 129 us with them,
-  // 153 without), then the simulator's matrix
-  const bool wl = lds(R, true, false, a.ahead != 0) <= kLdsMax;
-  a.mr_lds = lds(R, wl, true, a.ahead != 0) <= kLdsMax ? 1 : 0;
-  const size_t bytes = lds(R, wl, a.mr_lds != 0, a.ahead != 0);
-  set_rows(&a, R);
-  // a layer of at most four feature tiles for one row tile gives every wave one tile at most: then the networks by plan
-  bool plan = wl && R == 16 && L.n_layers <= kPlanLayers;
-  for (int net = 0; net < 2; ++net)
-    for (const LayerInfo& li : L.net[net]) plan = plan && li.out <= 64;
-  static gmi::DeviceSet allowed[3];
   typedef void (*kernel_fn)(RolloutF32Args);
-  const kernel_fn kernel = plan ? rollout_f32_kernel<true, true> : wl ? rollout_f32_kernel<true, false> : rollout_f32_kernel<false, false>;
-  const int rc2 = gmi::allow_lds((const void*)kernel, kLdsMax, g->device, &allowed[plan ? 2 : wl]);
+  kernel_fn kernel;
+  size_t bytes;
+  int variant, threads = kNT;
+  if (split) {
+    a.mr_lds = split_bytes + (size_t)m_floats * 4 <= kLdsMax ? 1 : 0;
+    bytes = split_bytes + (a.mr_lds ? (size_t)m_floats * 4 : 0);
+    auto pick = [&](auto nl) -> kernel_fn {      // (inputs of at most 64 features: the matrix always fits)
+      constexpr int NL = decltype(nl)::value;
+      return O <= 64 ? rollout_split_kernel<NL, true, true> : a.mr_lds ? rollout_split_kernel<NL, false, true> : rollout_split_kernel<NL, false, false>;
+    };
+    kernel = L.n_layers == 2   ? pick(std::integral_constant<int, 2>{})
+             : L.n_layers == 3 ? pick(std::integral_constant<int, 3>{})
+                               : pick(std::integral_constant<int, 4>{});
+    variant = 2 + 3 * (L.n_layers - 2) + (O <= 64 ? 0 : a.mr_lds ? 1 : 2);
+    threads = kSplitThreads;
+  } else {
+    // what stays on chip for all steps: the networks' weights first (read by every layer), then the simulator's matrix
+    const bool wl = lds(R, true, false, a.ahead != 0) <= kLdsMax;
+    a.mr_lds = lds(R, wl, true, a.ahead != 0) <= kLdsMax ? 1 : 0;
+    bytes = lds(R, wl, a.mr_lds != 0, a.ahead != 0);
+    kernel = wl ? rollout_f32_kernel<true> : rollout_f32_kernel<false>;
+    variant = wl;
+  }
+  set_rows(&a, R);
+  static gmi::DeviceSet allowed[11];
+  const int rc2 = gmi::allow_lds((const void*)kernel, kLdsMax, g->device, &allowed[variant]);
   if (rc2 != GMI_OK) return rc2;
-  // no more workgroups than the instance's compute units hold at once (see rollout_collect): one each, by registers (164)
+  // no more workgroups than the instance's compute units hold at once (see rollout_collect)
   int64_t resident = 1;
-  const int rc3 = gmi::resident_groups(g, (const void*)kernel, kNT, bytes, &resident);
+  const int rc3 = gmi::resident_groups(g, (const void*)kernel, threads, bytes, &resident);
   if (rc3 != GMI_OK) return rc3;
   const int grid = (int)std::min<int64_t>(a.n_tiles, resident);
   gmi::ProfScope ps(g, gmi::kClsFusedRollout);
-  ps.launch(kernel, dim3(grid), dim3(kNT), bytes, a);
+  ps.launch(kernel, dim3(grid), dim3(threads), bytes, a);
   GMI_LAUNCH_CHECK();
   return GMI_OK;
 }

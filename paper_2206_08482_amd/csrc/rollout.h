@@ -222,16 +222,326 @@ __device__ __forceinline__ void finish_env(const RolloutEnv& a, int r0, int64_t 
 // Its log-density and its reward: sums over the blocks, in order.
 __device__ __forceinline__ float block_sum(const float* q, int n) {
   float sum = 0.f;
-  int j = 0;
-  for (; j + 8 <= n; j += 8) {      // eight LDS reads in flight
+  for (int j = 0; j < n; j += 8) {      // eight LDS reads in flight
     float t8[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) t8[u] = q[j + u];
+    for (int u = 0; u < 8; ++u) t8[u] = q[min(j + u, n - 1)];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) sum += t8[u];
+    for (int u = 0; u < 8; ++u) sum = j + u < n ? sum + t8[u] : sum;
   }
-  for (; j < n; ++j) sum += q[j];
   return sum;
+}
+
+// ------------------------------------------------------------------------------------------------
+// The collection of 16 envs per workgroup with the roles of a step on waves of their own: 8 waves carry the networks (the wave with a
+// tile of the policy's head decides its actions from the products in its registers), 4 the simulator, 4 the draws and sums.  A step has
+// an interval per layer and one of the simulator's, each with a barrier at its end.  What the actions do not decide is done beside the
+// policy's layers: the state's part of the simulator's product, whose sums stay in registers, the next step's draws, done flags,
+// observations on their way to memory, the sums of the step before; behind the head's barrier only the actions' part of the product
+// is left.  The value net is an interval behind the policy, its head beside the simulator.
+// A step is a chain of dependent latencies, 16 envs being a fraction of what a compute unit could work on; but waves on one SIMD
+// take its vector unit (4 cycles an instruction) and its matrix unit (32 a product of 16x16x4) in turn, so what runs beside the
+// policy's layers is kept small, spread over the SIMDs (wave % 4), and yields to them.  With every phase on 8 waves in turn a step of
+// 8:32:32:2 took 10100 cycles, of 17:64:64:6 11100; now 4900 and 7000, of which the policy's layers 850, 1000 and 1450 and the rest of
+// the simulator 850.
+constexpr int kNetWaves = 8, kSimWaves = 4, kDrawWaves = 4, kSplitThreads = 64 * (kNetWaves + kSimWaves + kDrawWaves);
+// floats of a row of state | action: whole blocks of four actions
+__host__ __device__ __forceinline__ int split_stride(int O, int A) { return (O + ((A + 3) & ~3) + 3) & ~3; }
+
+// Where the waves find a tile's arrays in LDS.
+struct SplitArrays {
+  float* in2;                 // [2][16][OS] state | action, of this and the next step
+  float4* noise2;             // [2][16][npr]
+  float* lp;                  // [16][nba]
+  float* part;                // [16][nbo]
+  int* done;                  // [16]
+  const float* val;           // [16] values of the step; NULL: not computed here
+  const float* ls;            // [act_dim] log_std
+};
+
+// A step's draws in two passes with a barrier between them: the random words of every block, then -- a thread per half of a block, in
+// place -- their normals (the done draw stays a raw word).  Blocks whole, a wave's 64 take longer than a small net's layer.
+// Both: 64 items from i0 on.
+__device__ __forceinline__ void draw_word_items(const RolloutEnv& a, float4* dst, uint32_t stp, int r0, int npr, int nba, int i0, int lane) {
+  const int item = i0 + lane;
+  if (item >= 16 * npr) return;
+  const int r = (int)__umulhi((uint32_t)item, a.npr_magic), q = item - r * npr;
+  const bool is_act = q < nba, is_done = q == npr - 1;
+  const gmi::Words4 w = draw_words(a, stp, r0, r, is_act, is_done, is_act ? (uint32_t)q : (is_done ? 0u : (uint32_t)(q - nba)));
+  reinterpret_cast<uint4*>(dst)[item] = make_uint4(w.w[0], w.w[1], w.w[2], w.w[3]);
+}
+__device__ __forceinline__ void draw_normal_items(const RolloutEnv& a, float4* dst, int npr, int i0, int lane) {
+  const int half = i0 + lane, item = half >> 1;
+  if (half >= 2 * 16 * npr) return;
+  const int r = (int)__umulhi((uint32_t)item, a.npr_magic);
+  if (item - r * npr == npr - 1) return;
+  const uint2 w = reinterpret_cast<const uint2*>(dst)[half];
+  float z0, z1;
+  gmi::normal_pair(w.x, w.y, z0, z1);
+  reinterpret_cast<float2*>(dst)[half] = make_float2(z0, z1);
+}
+// The first step's, by all waves; ends with a barrier.
+__device__ __forceinline__ void first_draws(const RolloutEnv& a, float4* dst, int r0, int npr, int nba, int wave, int lane) {
+#pragma unroll 1
+  for (int i = 64 * wave; i < 16 * npr; i += kSplitThreads) draw_word_items(a, dst, a.step0, r0, npr, nba, i, lane);
+  __syncthreads();
+#pragma unroll 1
+  for (int i = 64 * wave; i < 32 * npr; i += kSplitThreads) draw_normal_items(a, dst, npr, i, lane);
+  __syncthreads();
+}
+// Items of a place of `places`, 64 at a time, for draw wave d of kDrawWaves: as few as possible in each.
+template <class Draw>
+__device__ __forceinline__ void place_items(int place, int places, int n, int d, Draw draw) {
+#pragma unroll 1
+  for (int u = place + places * d; 64 * u < n; u += places * kDrawWaves) draw(64 * u);
+}
+
+// The decision of four actions, block b of env r of the tile, from the policy's means, into the state row.  std: exp(log_std).
+__device__ __forceinline__ void decide_actions(float* s_in, int OS, int O, const float4& z, const float4& std, int r, int b, const float (&mu)[4]) {
+  float* row = s_in + r * OS + O + 4 * b;
+  row[0] = fmaf(std.x, z.x, mu[0]);
+  row[1] = fmaf(std.y, z.y, mu[1]);
+  row[2] = fmaf(std.z, z.z, mu[2]);
+  row[3] = fmaf(std.w, z.w, mu[3]);
+}
+
+// The simulator's product over the k groups g0 .. g1 - 1 of four, in order (see sim_items).
+__device__ __forceinline__ void sim_groups(simx4& acc, const float* mp, const float* xp, int g0, int g1) {
+  if (g0 >= g1) return;
+  float4 m[4], x[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int gu = min(g0 + u, g1 - 1);      // past the end: read again, not used (no load behind a branch)
+    m[u] = *reinterpret_cast<const float4*>(mp + 4 * gu);
+    x[u] = *reinterpret_cast<const float4*>(xp + 4 * gu);
+  }
+  auto step4 = [&](const float4& mv, const float4& xv) {
+    acc = __builtin_amdgcn_mfma_f32_4x4x1f32(mv.x, xv.x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_4x4x1f32(mv.y, xv.y, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_4x4x1f32(mv.z, xv.z, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_4x4x1f32(mv.w, xv.w, acc, 0, 0, 0);
+  };
+  int g = g0;
+#pragma unroll 1
+  for (; g + 4 < g1; g += 4)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      step4(m[u], x[u]);
+      const int gn = min(g + 4 + u, g1 - 1);
+      m[u] = *reinterpret_cast<const float4*>(mp + 4 * gn);
+      x[u] = *reinterpret_cast<const float4*>(xp + 4 * gn);
+    }
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (g + u < g1) step4(m[u], x[u]);
+}
+
+// A uniform value that is not known to be the one of the step before: what follows from it is worked out where it is used.  (Kept over
+// the steps, every condition of a lane takes two scalar registers; 200 of them were spilled and read back one by one.)
+__device__ __forceinline__ int fresh(int v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
+// What a simulator wave has of an item before the actions are there: the state's part of the sums and the other operands.
+struct SimItem {
+  SimLane sl;
+  simx4 acc;
+  float4 m0, m1, mt, zn;      // the matrix behind the state's part: two groups of k and the ragged one; the noise
+  int done;
+};
+
+// All steps of a tile for simulator wave w: an interval per layer and the simulator's own, each with a barrier at its end, and once
+// more those after the last step, for the value net.  mr: the simulator's matrix, LDS or global.  put(t, row, first element, 4
+// elements): the next state.
+template <int NL, class Put>
+__device__ __forceinline__ void sim_wave_steps(const RolloutEnv& a, const SplitArrays& s, const float* mr, int r0, int w, int lane, Put put) {
+  typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+  const int OS = split_stride(a.obs_dim, a.act_dim), w_items = ((a.o4 >> 2) + 3) >> 2;
+  const int mine = (w_items - w + kSimWaves - 1) / kSimWaves;      // (0 or less: none)
+  auto item_lane = [&](int u) { return sim_lane(a, min(w + kSimWaves * u, w_items - 1), OS, lane); };
+  SimItem i0, i1;      // (rows of up to 128 elements have no more)
+  i0.sl = item_lane(0);
+  i1.sl = item_lane(1);
+  int64_t slot0 = r0;
+#pragma unroll 1
+  for (int t = 0; t <= a.T; ++t, slot0 += a.ld_envs) {
+    const int O = fresh(a.obs_dim), A = fresh(a.act_dim), OA = O + A, nbo = (O + 3) >> 2, nba = (A + 3) >> 2, npr = nba + nbo + 1;
+    const int gs = O >> 2, ng = OA >> 2, rem = OA & 3, gt = rem ? ng : 0, left = fresh(a.n - r0);
+    const float* s_in = s.in2 + (t & 1) * 16 * OS;
+    const float4* s_noise = s.noise2 + (t & 1) * 16 * npr;
+    const bool step = t < a.T;
+    auto observe = [&](const SimLane& sl) {      // the item's part of the observations goes out
+      if (sl.blk >= nbo || sl.r >= left) return;
+      const float4 x = *reinterpret_cast<const float4*>(s_in + sl.x_off + 4 * sl.blk);
+      float* dst = a.b_obs + (slot0 + sl.r) * O + 4 * sl.blk;
+      if (4 * sl.blk + 4 <= O) {
+        *reinterpret_cast<float4u*>(dst) = float4u{x.x, x.y, x.z, x.w};
+      } else {
+        dst[0] = x.x;
+        if (4 * sl.blk + 1 < O) dst[1] = x.y;
+        if (4 * sl.blk + 2 < O) dst[2] = x.z;
+      }
+    };
+    auto operands = [&](SimItem& it) {      // what does not wait for the actions
+      const float* mp = mr + it.sl.m_off;
+      it.m0 = *reinterpret_cast<const float4*>(mp + 4 * min(gs, ng));
+      it.m1 = *reinterpret_cast<const float4*>(mp + 4 * min(gs + 1, ng));
+      it.mt = *reinterpret_cast<const float4*>(mp + 4 * gt);
+      it.zn = s_noise[it.sl.r * npr + nba + min(it.sl.blk, nbo - 1)];
+      it.done = s.done[it.sl.r];
+    };
+    i0.acc = i1.acc = simx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int l = 0; l < NL; ++l) {
+      if (mine > 0) {
+        if (step) {      // a share of the state's part per interval
+          const int g0 = gs * l / NL, g1 = gs * (l + 1) / NL;
+          sim_groups(i0.acc, mr + i0.sl.m_off, s_in + i0.sl.x_off, g0, g1);
+          if (mine > 1) sim_groups(i1.acc, mr + i1.sl.m_off, s_in + i1.sl.x_off, g0, g1);
+          if (l == NL - 1) {
+            operands(i0);
+            if (mine > 1) operands(i1);
+          }
+        }
+        if (l == 0 && step) {
+          observe(i0.sl);
+          if (mine > 1) observe(i1.sl);
+#pragma unroll 1
+          for (int u = 2; u < mine; ++u) observe(item_lane(u));
+        }
+      }
+      __syncthreads();
+    }
+    if (step && mine > 0) {
+      __builtin_amdgcn_s_setprio(3);
+      int dones = 0;
+      auto finish = [&](SimItem& it) {
+        const float* xp = s_in + it.sl.x_off;
+        const float4 x0 = *reinterpret_cast<const float4*>(xp + 4 * min(gs, ng)), x1 = *reinterpret_cast<const float4*>(xp + 4 * min(gs + 1, ng));
+        const float4 xt = *reinterpret_cast<const float4*>(xp + 4 * gt);
+        auto step4 = [&](const float4& mv, const float4& xv) {
+          it.acc = __builtin_amdgcn_mfma_f32_4x4x1f32(mv.x, xv.x, it.acc, 0, 0, 0);
+          it.acc = __builtin_amdgcn_mfma_f32_4x4x1f32(mv.y, xv.y, it.acc, 0, 0, 0);
+          it.acc = __builtin_amdgcn_mfma_f32_4x4x1f32(mv.z, xv.z, it.acc, 0, 0, 0);
+          it.acc = __builtin_amdgcn_mfma_f32_4x4x1f32(mv.w, xv.w, it.acc, 0, 0, 0);
+        };
+        if (gs < ng) step4(it.m0, x0);
+        if (gs + 1 < ng) step4(it.m1, x1);
+        if (gs + 2 < ng) sim_groups(it.acc, mr + it.sl.m_off, xp, gs + 2, ng);
+        if (rem) {
+          it.acc = __builtin_amdgcn_mfma_f32_4x4x1f32(it.mt.x, xt.x, it.acc, 0, 0, 0);
+          if (rem > 1) it.acc = __builtin_amdgcn_mfma_f32_4x4x1f32(it.mt.y, xt.y, it.acc, 0, 0, 0);
+          if (rem > 2) it.acc = __builtin_amdgcn_mfma_f32_4x4x1f32(it.mt.z, xt.z, it.acc, 0, 0, 0);
+        }
+        dones |= it.done;
+        const float out[4] = {fmaf(a.noise_std, it.zn.x, it.acc[0]), fmaf(a.noise_std, it.zn.y, it.acc[1]),
+                              fmaf(a.noise_std, it.zn.z, it.acc[2]), fmaf(a.noise_std, it.zn.w, it.acc[3])};
+        if (it.sl.blk < nbo) put(t, it.sl.r, 4 * it.sl.blk, out);
+      };
+      finish(i0);
+      if (mine > 1) finish(i1);
+#pragma unroll 1
+      for (int u = 2; u < mine; ++u) {
+        SimItem it;
+        it.sl = item_lane(u);
+        it.acc = simx4{0.f, 0.f, 0.f, 0.f};
+        operands(it);
+        sim_groups(it.acc, mr + it.sl.m_off, s_in + it.sl.x_off, 0, gs);
+        finish(it);
+      }
+      if (__ballot(dones != 0))      // a fresh state for the envs that ended
+#pragma unroll 1
+        for (int u = 0; u < mine; ++u) {
+          const SimLane sl = u == 0 ? i0.sl : u == 1 ? i1.sl : item_lane(u);
+          if (sl.blk >= nbo || !s.done[sl.r]) continue;
+          float z[4] = {0.f, 0.f, 0.f, 0.f};
+          if (r0 + sl.r < a.n)
+            gmi::normal_block(a.e_env_offset + (uint32_t)(r0 + sl.r), a.step0 + (uint32_t)t, gmi::kStreamReset, (uint32_t)sl.blk, a.ek0, a.ek1, z);
+          put(t, sl.r, 4 * sl.blk, z);
+        }
+      __builtin_amdgcn_s_setprio(0);
+    }
+    __syncthreads();
+  }
+}
+
+// The same for draw wave m; waves 0 and 1 have the sums.  Lane e of wave 0 carries env e's episode counter.
+template <int NL>
+__device__ __forceinline__ void draw_wave_steps(const RolloutEnv& a, const SplitArrays& s, int r0, int m, int lane, uint32_t& ep) {
+  const int OS = split_stride(a.obs_dim, a.act_dim);
+  const uint32_t a_magic = 0xFFFFFFFFu / (uint32_t)a.act_dim + 1u;      // (A = 1: 0, see below)
+  int64_t slot0 = r0;
+#pragma unroll 1
+  for (int t = 0; t <= a.T; ++t, slot0 += a.ld_envs) {
+    const int O = fresh(a.obs_dim), A = fresh(a.act_dim), nbo = (O + 3) >> 2, nba = (A + 3) >> 2, npr = nba + nbo + 1;
+    const int left = fresh(a.n - r0), n_act = min(16, left) * A, d = kDrawWaves - 1 - m;
+    const bool env = lane < 16, env_ok = lane < min(16, left);
+    const float* s_in = s.in2 + (t & 1) * 16 * OS;
+    const float* s_prev = s.in2 + (~t & 1) * 16 * OS;
+    float4* s_noise = s.noise2 + (t & 1) * 16 * npr;
+    float4* next = s.noise2 + (~t & 1) * 16 * npr;
+    const bool step = t < a.T;
+#pragma unroll
+    for (int l = 0; l <= NL; ++l) {      // l = NL: the simulator's
+      // the next step's words, then their normals
+      if (l < NL && t + 1 < a.T) {
+        if (l == 0) place_items(0, 1, 16 * npr, d, [&](int i) { draw_word_items(a, next, a.step0 + (uint32_t)t + 1u, r0, npr, nba, i, lane); });
+        else place_items(l - 1, NL - 1, 32 * npr, d, [&](int i) { draw_normal_items(a, next, npr, i, lane); });
+      }
+      if (l == NL - 2 && t > 0)      // the parts of the last step's rewards
+#pragma unroll 1
+        for (int i = 64 * m + lane; i < 16 * nbo; i += 64 * kDrawWaves) {
+          const int r = i & 15, blk = i >> 4;
+          const float* xp = s_prev + r * OS;
+          const float4 y = *reinterpret_cast<const float4*>(xp + 4 * blk);
+          const float v0 = xp[O + min(blk, A - 1)], v1 = xp[O + min(blk + nbo, A - 1)];
+          float ps = y.x * y.x;
+          ps = 4 * blk + 1 < O ? fmaf(y.y, y.y, ps) : ps;
+          ps = 4 * blk + 2 < O ? fmaf(y.z, y.z, ps) : ps;
+          ps = 4 * blk + 3 < O ? fmaf(y.w, y.w, ps) : ps;
+          float pa = blk < A ? v0 * v0 : 0.f;
+          pa = blk + nbo < A ? fmaf(v1, v1, pa) : pa;
+          if (A > 2 * nbo)
+#pragma unroll 1
+            for (int q = blk + 2 * nbo; q < A; q += nbo) { const float v = xp[O + q]; pa = fmaf(v, v, pa); }
+          s.part[r * nbo + blk] = gmi::reward_part(ps, pa);
+        }
+      if (m == 0) {
+        if (l == 0) {
+          if (step && env) finish_env(a, r0, slot0, lane, s_noise, npr, ep, s.done);
+          if (s.val && t > 0 && env_ok) a.b_val[slot0 - a.ld_envs + lane] = s.val[lane];
+        } else if (l == NL - 1) {
+          if (t > 0 && env_ok) a.b_rew[slot0 - a.ld_envs + lane] = -a.reward_scale * block_sum(s.part + lane * nbo, nbo);
+        }
+      } else if (m == 1 && step) {
+        if (l == 0) {      // the step's log-densities per block of four actions, its terms in index order
+#pragma unroll 1
+          for (int i = lane; i < 16 * nba; i += 64) {
+            const int r = i & 15, b = i >> 4;
+            const float4 z4 = s_noise[r * npr + b];
+            const float z[4] = {z4.x, z4.y, z4.z, z4.w};
+            float lp = 0.f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const float ls = s.ls[min(4 * b + j, A - 1)], term = -0.5f * z[j] * z[j] - ls - 0.918938533204672742f;
+              lp = j == 0 ? term : lp + (4 * b + j < A ? term : 0.f);
+            }
+            s.lp[r * nba + b] = lp;
+          }
+        } else if (l == NL) {
+          if (env_ok) a.b_logp[slot0 + lane] = block_sum(s.lp + lane * nba, nba);
+        }
+      }
+      if (l == NL && step)      // the actions
+#pragma unroll 1
+        for (int i = 64 * m + lane; i < n_act; i += 64 * kDrawWaves) {
+          const int r = A == 1 ? i : (int)__umulhi((uint32_t)i, a_magic);
+          a.b_act[slot0 * A + i] = s_in[r * OS + O + i - r * A];
+        }
+      __syncthreads();
+    }
+  }
 }
 
 // Whether a model, a simulator and an experience buffer fit together.

@@ -636,3 +636,30 @@ def test_fp32_collection_at_the_edges_of_its_layout(g, obs, act, hidden, n):
         assert rel_l2(ga[k], gb[k]) <= 1e-5, (k, rel_l2(ga[k], gb[k]))
     for s in reversed(ses):
         s.close()
+
+
+@pytest.mark.parametrize("obs,act,hidden,n,T,cus", [
+    (64, 1, [64], 16, 4, None),                # two layers; the widest input in registers, whole tiles
+    (65, 7, [17, 64], 33, 3, None),            # the first layer's weights in LDS; a ragged third tile
+    (3, 24, [64, 33, 16], 70, 3, 8),           # more blocks of actions than of states; two heads' tiles; one workgroup per tile
+    (130, 9, [16, 16], 40, 3, None),           # nine state tiles: a simulator wave has three
+    (256, 24, [16], 18, 2, None),              # the simulator's matrix in memory
+    (6, 2, [64, 64], 300, 5, 8),               # nineteen tiles on eight compute units; two products behind the state's
+])
+def test_fp32_collection_with_the_roles_on_waves_of_their_own(g, obs, act, hidden, n, T, cus):
+    """Small nets (layers of at most 64 units).  1e-5 as everywhere on this path; done flags and counters exactly."""
+    ses = _collecting_sessions(obs, act, hidden, "f32", n, T, cus)
+    for it in range(2):
+        for s in ses:
+            s.rollout(it)
+            s.sync()
+        assert ses[0].fused_rollout_f32 and not ses[1].fused_rollout_f32
+        ga, gb = (s.buf.to_numpy() for s in ses)
+        assert np.array_equal(ga["done"], gb["done"]) and ga["done"].any()
+        for k in ("obs", "act", "logp", "val", "rew"):
+            assert rel_l2(ga[k], gb[k]) <= 1e-5, (it, k, rel_l2(ga[k], gb[k]))
+        assert rel_l2(ses[0].state().cpu().numpy(), ses[1].state().cpu().numpy()) <= 1e-5
+        assert rel_l2(ses[0].last_value.cpu().numpy(), ses[1].last_value.cpu().numpy()) <= 1e-5
+        assert torch.equal(ses[0].episode_step, ses[1].episode_step)
+    for s in reversed(ses):
+        s.close()
