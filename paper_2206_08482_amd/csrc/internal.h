@@ -215,6 +215,12 @@ struct ModelLayout {
 
 int build_layout(const gmi_model_desc* d, ModelLayout* L);
 
+namespace gmi {
+constexpr int kMaxWgradProblems = 2 * (GMI_MAX_HIDDEN + 1);
+// Row splits of every layer's weight gradient, both nets one after the other.
+struct alignas(4) WgradSplits { uint8_t n[kMaxWgradProblems]; };
+}  // namespace gmi
+
 struct gmi_model {
   uint32_t magic;
   int device;
@@ -237,7 +243,8 @@ struct gmi_model {
   float *mb_act, *mb_logp, *mb_adv, *mb_ret;
   // gradient partials [part_rows, L.part_floats] and stats partials
   float* grad_part;
-  int n_split_max;  // most row splits of a weight-gradient launch
+  gmi::WgradSplits split;      // most row splits of each layer's weight gradient (bf16) ..
+  int n_split_max;  // .. and of any (fp32: of all)
   int part_rows;    // rows of grad_part (at least n_split_max)
   float* stat_part; // [n_split_max, 8]
 };
@@ -304,7 +311,7 @@ struct LinearBatch {
 
 int launch_linear(gmi_instance* g, int dtype, int epi, int rows, const LinearBatch& batch);
 
-// dW[o, i] = sum_r dz[r, o] * x[r, i],  db[o] = sum_r dz[r, o], reduced over row splits:
+// dW[o, i] = sum_r dz[r, o] * x[r, i],  db[o] = sum_r dz[r, o], reduced over row splits (bf16: n_split of them, per problem):
 // split sp covers rows [sp*chunk, min(rows, (sp+1)*chunk)) and writes
 // part[sp * part_stride + w_off + o*in + i] and part[sp * part_stride + b_off + o] (fp32), or the tiled form described at
 // ModelLayout::part_floats with w_off = part_w, b_off = part_b (bf16).
@@ -317,14 +324,18 @@ struct WgradProblem {
   // or 16 ks + 8 h + {0..7} (2: the gathered observation rows).  Either both operands are row-major or none is.
   int dz_blocks, x_blocks;
   int out, in, out_pad, in_pad;
+  int n_split, chunk;      // bf16 only
   int64_t w_off, b_off;
 };
-constexpr int kMaxWgradProblems = 2 * (GMI_MAX_HIDDEN + 1);
+// bf16, filled by launch_wgrad: the workgroups of one problem, or of the two nets' problems of one shape (n_nets 2: p[first] and
+// p[second]), n_tiles per net and split.
+struct WgradEntry { int first, second, n_nets, n_tiles, n_split, start; };
 struct WgradBatch {
-  int n;
+  int n, n_entries;
   WgradProblem p[kMaxWgradProblems];
-  int tiles[kMaxWgradProblems], net_tiles[2];      // bf16, filled by launch_wgrad: output tiles per problem and per net
+  WgradEntry e[kMaxWgradProblems];
 };
+// n_split, chunk: fp32 (of all problems alike); bf16 takes the problems' own.
 int launch_wgrad(gmi_instance* g, int dtype, int rows, int n_split, int chunk, WgradBatch& batch,
                  float* part, int64_t part_stride);
 
@@ -451,17 +462,12 @@ int prepare_obs16(gmi_instance* g, gmi_model* m, gmi_buffer* b, int rows, int cu
 }  // namespace gmi
 
 namespace gmi {
-// Row splits for a weight-gradient launch over n_tiles 256 x 256 output tiles of both nets: as many as keep it in one round
-// of one workgroup per compute unit, in multiples of 4 (a split's two nets are the units that are dealt to the 8 dies),
-// at least 8 and at most 32 (each is a partial gradient that Adam reads).
-constexpr int kSplitMin = 8, kSplitMax = 32;
-static inline int wgrad_tiles(int out_pad, int in_pad) { return ((out_pad + 255) / 256) * ((in_pad + 255) / 256); }
-static inline int wgrad_split_limit(int n_tiles) {
-  int s = (256 / (n_tiles > 0 ? n_tiles : 1)) / 4 * 4;
-  if (s < kSplitMin) s = kSplitMin;
-  if (s > kSplitMax) s = kSplitMax;
-  return s;
-}
+// Weight-gradient tiles: at most 256 x 256, of equal size along a side (416 features: 224 + 192).
+static inline int wgrad_tile_count(int pad) { return (pad + 255) / 256; }
+__host__ __device__ static inline int wgrad_tile(int pad) { const int n = (pad + 255) / 256; return ((pad >> 5) + n - 1) / n * 32; }
+static inline int wgrad_tiles(int out_pad, int in_pad) { return wgrad_tile_count(out_pad) * wgrad_tile_count(in_pad); }
+// Row splits per layer of a weight-gradient launch (model.hip).
+WgradSplits plan_wgrad(const int* out_pad, const int* in_pad, int n);
 constexpr int kLossBlocksMax = 2048; // workgroups of the loss kernel
 constexpr int kStatRowsMax = 8192;   // rows of per-workgroup loss statistics (one more row holds their sum)
 constexpr int kStatStride = 8;       // per-workgroup statistics slots before the log_std partials

@@ -374,6 +374,7 @@ constexpr int kWgradOperand = kWgradT * kWgradRows * 2; // bytes
 constexpr int kWgradStage = 2 * kWgradOperand;
 constexpr int kWgradRing = 5;
 constexpr int kWgradLds = kWgradRing * kWgradStage;
+constexpr int kWgradGroups = 256, kSplitMin = 4, kSplitMax = 64, kWgradNarrow = 224;      // plan_wgrad
 __device__ const uint4 g_zero_piece = {0, 0, 0, 0};     // what rows past the end load
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -395,26 +396,35 @@ __device__ __forceinline__ void load_to_lds(const void* src, uint32_t lds) {
 
 // LAYOUT: 0 both operands row-major, 1 both in the block layout of the row-tile trainer kernel.
 template <int LAYOUT>
-__global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, int rows, int n_split, int chunk,
-                                                         float* __restrict__ part, int64_t part_stride) {
+__global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, int rows, float* __restrict__ part, int64_t part_stride) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  // workgroup -> (unit, tile of the unit's net), unit = (split, net): a unit's tiles read the same rows, so they belong
-  // on one die (ids go round-robin over the 8 dies and the unit count is a multiple of 8)
-  const int n_units = n_split * 2, unit = blockIdx.x % n_units, net = unit & 1, sp = unit >> 1;
-  int tile = blockIdx.x / n_units;
-  int pi = net * (batch.n >> 1);
-  if (tile >= batch.net_tiles[net]) return;
-  while (tile >= batch.tiles[pi]) tile -= batch.tiles[pi++];
-  const gmi::WgradProblem& P = batch.p[pi];
-  const int n_ti = (P.in_pad + kWgradT - 1) / kWgradT;
-  const int o0 = (tile / n_ti) * kWgradT, i0 = (tile % n_ti) * kWgradT;
-  const int row_begin = sp * chunk;
-  const int row_end = min(rows, row_begin + chunk);
+  // workgroup -> (entry, split and net, tile): the tiles of a split read the same rows, so they belong on one die (ids go round-robin
+  // over the 8 dies): whole eights of (split, net) pairs tile by tile, what is left over as it comes
+  int ei = 0;
+  while (ei + 1 < batch.n_entries && (int)blockIdx.x >= batch.e[ei + 1].start) ++ei;
+  const gmi::WgradEntry& E = batch.e[ei];
+  const int local = blockIdx.x - E.start, pairs = E.n_split * E.n_nets, whole = pairs & ~7;
+  int pair, tile;
+  if (local < whole * E.n_tiles) {
+    pair = (local >> 3) / E.n_tiles * 8 + (local & 7);
+    tile = (local >> 3) % E.n_tiles;
+  } else {
+    pair = whole + (local - whole * E.n_tiles) % (pairs - whole);
+    tile = (local - whole * E.n_tiles) / (pairs - whole);
+  }
+  const int sp = pair / E.n_nets;
+  const gmi::WgradProblem& P = batch.p[pair % E.n_nets ? E.second : E.first];
+  const int To = gmi::wgrad_tile(P.out_pad), Ti = gmi::wgrad_tile(P.in_pad);
+  const int n_ti = (P.in_pad + Ti - 1) / Ti;
+  const int o0 = (tile / n_ti) * To, i0 = (tile % n_ti) * Ti;
+  const int o_end = min(P.out_pad, o0 + To), i_end = min(P.in_pad, i0 + Ti);
+  const int row_begin = sp * P.chunk;
+  const int row_end = min(rows, row_begin + P.chunk);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
   // ---- loading: waves 0-3 the dz features, waves 4-7 the x features, four 1 KiB pieces per wave and stage
   const bool is_x = wave >= 4;
-  const int fmax = is_x ? P.in_pad : P.out_pad, f0 = is_x ? i0 : o0;
+  const int fmax = is_x ? P.in_pad : P.out_pad, f0 = is_x ? i0 : o0, fend = is_x ? i_end : o_end;
   const char* opnd = is_x ? (const char*)P.x : (const char*)P.dz;
   const int ld = is_x ? P.ldx : P.lddz;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
@@ -426,9 +436,9 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
   // in odd steps L ^ 8 (for the same reason)
   const int bs = (lane >> 3) * 4 + (lane & 3), bh = (lane >> 2) & 1;      // odd steps: row bs ^ 4
   const int nks_op = fmax >> 4;
-  // loads of this wave per stage: features past the operand are not loaded (what the LDS holds there feeds results that
+  // loads of this wave per stage: features past the tile are not loaded (what the LDS holds there feeds results that
   // are never stored)
-  const int n_ld = LAYOUT == 1 ? min(max(nks_op - (f0 >> 4) - (wave & 3) * 4, 0), 4) : 4;
+  const int n_ld = LAYOUT == 1 ? min(max(((fend - f0) >> 4) - (wave & 3) * 4, 0), 4) : 4;
   const int j0 = (wave & 3) * 4;
   // per-lane byte offsets of pieces with even and odd k (everything else of an address is wave-uniform), and whether the
   // lane's features exist
@@ -442,7 +452,7 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
     } else {
       const int f = f0 + 8 * ((lane & 31) ^ (((2 * par + rl) & 3) << 2));
       voff[par] = (uint32_t)(rl * ld + f) * 2;
-      f_ok[par] = f < fmax;
+      f_ok[par] = f < fend;
     }
   }
   auto issue = [&](int stage) {
@@ -488,7 +498,7 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
   // Waves share the tile's 32 x 32 tiles as a 2 x 4 grid (4 x 2 where there are at most two input tiles), so that a narrow
   // matrix still gives every wave its part: wave (wo, wi) has the output tiles ot0 .. ot0 + nz - 1 and the input tiles
   // xt0 .. xt0 + nx - 1.
-  const int n_ot = min((P.out_pad - o0) >> 5, 8), n_xt = min((P.in_pad - i0) >> 5, 8);
+  const int n_ot = (o_end - o0) >> 5, n_xt = (i_end - i0) >> 5;
   const int go = n_xt <= 2 ? 4 : 2, gi = 8 / go, wo = wave / gi, wi = wave % gi;
   const int zmax = (n_ot + go - 1) / go, xmax = (n_xt + gi - 1) / gi;
   const int ot0 = wo * zmax, xt0 = wi * xmax;
@@ -803,6 +813,39 @@ int launch_linear(gmi_instance* g, int dtype, int epi, int rows, const LinearBat
   }
 }
 
+// Splits of each layer's rows such that its workgroups read about as much as any other's: as many workgroups in all as keep the
+// launch in one round of one per compute unit.  A workgroup's time goes by the bytes of its rows, its tile's features of both operands
+// (a stage of few features is bound by the round trip instead: kWgradNarrow), and with the same splits for all layers the launch
+// took as long as the widest tile's.
+WgradSplits plan_wgrad(const int* out_pad, const int* in_pad, int n) {
+  WgradSplits r = {};
+  int tiles[kMaxWgradProblems], feats[kMaxWgradProblems], used = 0;
+  for (int i = 0; i < n; ++i) {
+    tiles[i] = wgrad_tiles(out_pad[i], in_pad[i]);
+    feats[i] = std::max(wgrad_tile(out_pad[i]) + wgrad_tile(in_pad[i]), kWgradNarrow);
+    used += tiles[i] * kSplitMin;
+  }
+  for (int i = 0; i < n; ++i) r.n[i] = kSplitMin;
+  if (used > kWgradGroups) {
+    for (int i = 0; i < n; ++i) r.n[i] = 2 * kSplitMin;
+    return r;
+  }
+  for (;;) {
+    int most = 0;
+    for (int i = 1; i < n; ++i)
+      if (feats[i] * r.n[most] > feats[most] * r.n[i]) most = i;
+    int add = 0;      // all problems alike, i.e. both nets' layers of one shape, together
+    auto alike = [&](int i) { return out_pad[i] == out_pad[most] && in_pad[i] == in_pad[most] && r.n[i] == r.n[most]; };
+    for (int i = 0; i < n; ++i) add += alike(i) ? tiles[i] : 0;
+    if (used + add > kWgradGroups || r.n[most] == kSplitMax) return r;
+    used += add;
+    const int to = r.n[most] + 1;
+    for (int i = n - 1; i >= 0; --i)
+      if (i != most && alike(i)) r.n[i] = to;
+    r.n[most] = to;
+  }
+}
+
 int launch_wgrad(gmi_instance* g, int dtype, int rows, int n_split, int chunk, WgradBatch& b, float* part,
                  int64_t part_stride) {
   if (b.n <= 0) return GMI_OK;
@@ -814,7 +857,8 @@ int launch_wgrad(gmi_instance* g, int dtype, int rows, int n_split, int chunk, W
     double fl = 0.0, by = 0.0;
     for (int i = 0; i < b.n; ++i) {
       fl += 2.0 * rows * (double)b.p[i].in * b.p[i].out;
-      by += rows * es * (b.p[i].in + b.p[i].out) + 4.0 * n_split * ((double)b.p[i].in * b.p[i].out + b.p[i].out);
+      by += rows * es * (b.p[i].in + b.p[i].out) +
+            4.0 * (dtype == GMI_DTYPE_F32 ? n_split : b.p[i].n_split) * ((double)b.p[i].in * b.p[i].out + b.p[i].out);
     }
     ps.work(fl, by);
   }
@@ -829,21 +873,30 @@ int launch_wgrad(gmi_instance* g, int dtype, int rows, int n_split, int chunk, W
     GMI_LAUNCH_CHECK();
     return GMI_OK;
   }
-  // problems 0 .. n / 2 - 1 are the policy net's layers, the rest the value net's (one problem alone: net 0 is empty)
-  const int half = b.n >> 1;
-  b.net_tiles[0] = b.net_tiles[1] = 0;
-  for (int i = 0; i < b.n; ++i) {
-    b.tiles[i] = wgrad_tiles(b.p[i].out_pad, b.p[i].in_pad);
-    b.net_tiles[i < half ? 0 : 1] += b.tiles[i];
+  // problems 0 .. n / 2 - 1 are the policy net's layers, the rest the value net's
+  const int half = b.n / 2;
+  int total = 0;
+  b.n_entries = 0;
+  auto entry = [&](int first, int second, int n_nets) {
+    const WgradProblem& p = b.p[first];
+    WgradEntry& e = b.e[b.n_entries++];
+    e.first = first; e.second = second; e.n_nets = n_nets;
+    e.n_tiles = wgrad_tiles(p.out_pad, p.in_pad); e.n_split = p.n_split; e.start = total;
+    total += n_nets * e.n_tiles * e.n_split;
+  };
+  for (int i = 0; i < (b.n % 2 ? b.n : half); ++i) {
+    const WgradProblem &p = b.p[i], &q = b.p[(i + half) % b.n];
+    if (b.n % 2) entry(i, i, 1);
+    else if (p.out_pad == q.out_pad && p.in_pad == q.in_pad && p.n_split == q.n_split && p.chunk == q.chunk) entry(i, i + half, 2);
+    else { entry(i, i, 1); entry(i + half, i + half, 1); }
   }
-  const int total = 2 * n_split * std::max(b.net_tiles[0], b.net_tiles[1]);
   static DeviceSet allowed[2];
   const int layout = b.p[0].dz_blocks ? 1 : 0;
   const void* kernel = layout ? (const void*)wgrad_bf16_kernel<1> : (const void*)wgrad_bf16_kernel<0>;
   const int rc = allow_lds(kernel, kWgradLds, g->device, &allowed[layout]);
   if (rc != GMI_OK) return rc;
-  if (layout) ps.launch(wgrad_bf16_kernel<1>, dim3(total), dim3(512), kWgradLds, b, rows, n_split, chunk, part, part_stride);
-  else ps.launch(wgrad_bf16_kernel<0>, dim3(total), dim3(512), kWgradLds, b, rows, n_split, chunk, part, part_stride);
+  if (layout) ps.launch(wgrad_bf16_kernel<1>, dim3(total), dim3(512), kWgradLds, b, rows, part, part_stride);
+  else ps.launch(wgrad_bf16_kernel<0>, dim3(total), dim3(512), kWgradLds, b, rows, part, part_stride);
   GMI_LAUNCH_CHECK();
   return GMI_OK;
 }

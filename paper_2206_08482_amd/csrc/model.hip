@@ -387,11 +387,20 @@ extern "C" int gmi_model_bind(gmi_t g, const gmi_model_desc* d, float* params, v
   m->adam_m = adam_m;
   m->adam_v = adam_v;
   {
-    int n_tiles = 0;
+    int out_pad[gmi::kMaxWgradProblems], in_pad[gmi::kMaxWgradProblems], n = 0;
     for (int net = 0; net < 2; ++net)
-      for (int l = 0; l < L.n_layers; ++l)
-        n_tiles += gmi::wgrad_tiles(L.net[net][l].out_pad, L.net[net][l].in_pad);
-    m->n_split_max = gmi::wgrad_split_limit(n_tiles);
+      for (int l = 0; l < L.n_layers; ++l) {
+        out_pad[n] = L.net[net][l].out_pad;
+        in_pad[n++] = L.net[net][l].in_pad;
+      }
+    m->split = gmi::plan_wgrad(out_pad, in_pad, n);
+    if (L.dtype == GMI_DTYPE_F32) {
+      int n_tiles = 0;
+      for (int i = 0; i < n; ++i) n_tiles += gmi::wgrad_tiles(out_pad[i], in_pad[i]);
+      m->n_split_max = std::min(std::max(256 / n_tiles / 4 * 4, 8), 32);
+    } else {
+      m->n_split_max = *std::max_element(m->split.n, m->split.n + n);
+    }
     m->part_rows = m->n_split_max;
     if (L.dtype == GMI_DTYPE_BF16 && adam_m) m->part_rows = std::max(m->part_rows, gmi::resident_part_rows(L));
     if (L.dtype == GMI_DTYPE_F32 && adam_m) m->part_rows = std::max(m->part_rows, gmi::f32_part_rows(L));

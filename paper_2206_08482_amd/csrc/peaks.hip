@@ -145,12 +145,16 @@ extern "C" int gmi_bench_linear(gmi_t g, int kind, int rows, int K, int F, int n
     r.dz = y; r.lddz = F; r.x = x; r.ldx = K; r.out = F; r.in = K; r.out_pad = F; r.in_pad = K; r.dz_blocks = r.x_blocks = 0;
     r.w_off = (int64_t)z * ((int64_t)K * F + F); r.b_off = r.w_off + (int64_t)K * F;
   }
-  const int n_split = gmi::wgrad_split_limit(n_nets * gmi::wgrad_tiles(F, K));
+  const int fs[2] = {F, F}, ks[2] = {K, K};
+  const int n_split = gmi::plan_wgrad(fs, ks, n_nets).n[0];
   if (kind == 3) part = (float*)take((size_t)n_split * P * 4);
   if (off > scratch_bytes) GMI_FAIL(GMI_ERR_BAD_SHAPE, "gmi_bench_linear: scratch too small (%zu needed)", off);
-  const int chunk = ((rows + n_split - 1) / n_split + 63) / 64 * 64;
+  for (int z = 0; z < n_nets; ++z) {
+    wb.p[z].n_split = n_split;
+    wb.p[z].chunk = ((rows + n_split - 1) / n_split + 31) / 32 * 32;
+  }
   auto launch = [&]() -> int {
-    if (kind == 3) return gmi::launch_wgrad(g, GMI_DTYPE_BF16, rows, n_split, chunk, wb, part, P);
+    if (kind == 3) return gmi::launch_wgrad(g, GMI_DTYPE_BF16, rows, 0, 0, wb, part, P);
     return gmi::launch_linear(g, GMI_DTYPE_BF16, kind == 0 ? gmi::kEpiBiasElu : gmi::kEpiEluGrad, rows, lb);
   };
   hipEvent_t e0, e1;

@@ -125,18 +125,23 @@ __device__ __forceinline__ void adam_step(float g, float& m, float& v, float& w,
 }
 
 // Gradient partials of the trainer instances whose replicas are reduced into one update (one entry for an
-// ordinary single-instance update): per instance [n_split, part_stride] weight partials and the loss
-// kernel's [n_stat, kStatStride + A] statistics partials.  The counts are the replica's own: they follow from the path
+// ordinary single-instance update): per instance [n_split, part_stride] weight partials (of tiled ones as many rows as the layer
+// has splits) and the loss kernel's [n_stat, kStatStride + A] statistics partials.  The counts are the replica's own: they follow from the path
 // its instance takes (gmi_set_fusion, compute units).
 constexpr int kMaxGroup = 16;
 struct Partials {
   const float *part, *stat;      // stat NULL: a caller-supplied gradient
-  int n_split, n_stat;
+  int n_split, n_stat;           // n_split: partials in flat order
 };
 struct PartSet {
   int n;
   Partials r[kMaxGroup];
+  gmi::WgradSplits split[kMaxGroup];      // partials in tiled order
 };
+// (by words: the argument segment has no scalar byte loads)
+__device__ __forceinline__ int layer_splits(const PartSet& ps, int replica, int li) {
+  return reinterpret_cast<const uint32_t*>(ps.split[replica].n)[li >> 2] >> (8 * (li & 3)) & 255;
+}
 
 // Sum over the replicas and splits of the partials at p, splits grp, grp + G, grp + 2 G, ...: fixed order of additions,
 // 16 (then 4) loads in flight.
@@ -353,10 +358,10 @@ __global__ __launch_bounds__(256) void adam_shadow_kernel(gmi::ShadowTable tab, 
   float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
   float gb = 0.f;
   Partials r = ps.r[0];      // the first entry comes with the other arguments, ahead of the loop
+  int n_split = layer_splits(ps, 0, li);
   for (int k = 1;; ++k) {
     const float* q = r.part + src;
     const float* qb = r.part + srcb;
-    const int n_split = r.n_split;
     auto add = [&](int s, auto n) {      // rows s, s + 4, ...: all loads before the first addition, fixed order
       constexpr int U = decltype(n)::value;
       float4 x[U];
@@ -379,6 +384,7 @@ __global__ __launch_bounds__(256) void adam_shadow_kernel(gmi::ShadowTable tab, 
     if (s < n_split) add(s, std::integral_constant<int, 4>{});
     if (k >= ps.n) break;
     r = ps.r[k];
+    n_split = layer_splits(ps, k, li);
   }
   *reinterpret_cast<float4*>(&s_sum[wave][lane * 4]) = g;
   if (lane < 8) s_bsum[wave][lane] = gb;
@@ -527,25 +533,33 @@ int layers_pass(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_hpar
   return GMI_OK;
 }
 
+// Rows of gradient partials a minibatch leaves: in flat parameter order (fp32), in tiled order per layer (bf16).
+struct PartRows {
+  int flat;
+  gmi::WgradSplits split;
+};
+
 // Forward + loss (+ backward products) of the `rows` samples idx[0..rows) of the buffer.
 // Leaves gradient partials in m->grad_part / m->stat_part; their numbers of rows follow from the path, and with that from
 // the instance's switch and compute units.
 int minibatch_pass(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_hparams* hp, const int32_t* idx,
-                   int rows, int cus, bool want_grad, int* n_split_out, int* n_loss_blocks_out, bool obs16_ready = false) {
+                   int rows, int cus, bool want_grad, PartRows* parts, int* n_loss_blocks_out, bool obs16_ready = false) {
   const ModelLayout& L = m->L;
   const bool bf = L.dtype == GMI_DTYPE_BF16;
   int rc = GMI_ERR_UNSUPPORTED;
   bool blocks = false;
   if (g->fusion >= 1 && want_grad && !bf) {
     // fp32: everything up to the gradient partials in one launch
-    rc = gmi::launch_train_f32(g, m, b, hp, idx, rows, cus, n_split_out);
-    if (rc == GMI_OK) { *n_loss_blocks_out = *n_split_out; return GMI_OK; }
+    rc = gmi::launch_train_f32(g, m, b, hp, idx, rows, cus, &parts->flat);
+    if (rc == GMI_OK) { *n_loss_blocks_out = parts->flat; return GMI_OK; }
     if (rc != GMI_ERR_UNSUPPORTED) return rc;
   }
   if (g->fusion >= 1 && want_grad && bf && gmi::use_resident(L, rows, cus)) {
     // the tile's activations resident in LDS; small nets' weight gradients in the same launch
-    rc = gmi::launch_train_resident(g, m, b, hp, idx, rows, cus, n_split_out, n_loss_blocks_out);
-    if (rc == GMI_OK && *n_split_out > 0) return GMI_OK;
+    int n = 0;
+    rc = gmi::launch_train_resident(g, m, b, hp, idx, rows, cus, &n, n_loss_blocks_out);
+    for (int i = 0; i < gmi::kMaxWgradProblems; ++i) parts->split.n[i] = (uint8_t)n;
+    if (rc == GMI_OK && n > 0) return GMI_OK;
   }
   if (rc == GMI_ERR_UNSUPPORTED && g->fusion >= 1 && want_grad && bf) {
     // row-tile kernel (gather + forward + loss + input gradients in one launch) where this shape has one; it leaves the hidden
@@ -561,7 +575,7 @@ int minibatch_pass(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_h
   if (n_split < 1) n_split = 1;
   int chunk = (rows + n_split - 1) / n_split;
   chunk = (chunk + 63) / 64 * 64;
-  *n_split_out = n_split;
+  parts->flat = n_split;
   gmi::WgradBatch wb;
   wb.n = 0;
   for (int net = 0; net < 2; ++net)
@@ -572,6 +586,10 @@ int minibatch_pass(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_h
       p.x = m->h[net][l]; p.ldx = li.in_pad;
       p.out = li.out; p.in = li.in; p.out_pad = li.out_pad; p.in_pad = li.in_pad;
       p.w_off = li.part_w; p.b_off = li.part_b;
+      const int most = std::min<int>(m->split.n[wb.n - 1], (rows + 63) / 64);      // at least 64 rows each
+      p.chunk = ((rows + most - 1) / most + 31) / 32 * 32;
+      p.n_split = (rows + p.chunk - 1) / p.chunk;
+      parts->split.n[wb.n - 1] = (uint8_t)p.n_split;
       // the row-tile kernel leaves every activation and every gradient in its block layout
       if (blocks && l == 0) p.x = m->x0b;
       p.x_blocks = blocks ? (l == 0 ? 2 : 1) : 0;
@@ -581,8 +599,8 @@ int minibatch_pass(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_h
 }
 
 // Reduces the partials of the n bindings ms[0..n) (replicas of one model: same parameter arrays, own
-// workspaces; n_split[i] and n_stat[i] rows of them) and applies one Adam step through ms[0]; launched on instance g.
-int launch_adam(gmi_instance* g, gmi_model* const* ms, int n, const int* n_split, const int* n_stat,
+// workspaces; parts[i] and n_stat[i] rows of them) and applies one Adam step through ms[0]; launched on instance g.
+int launch_adam(gmi_instance* g, gmi_model* const* ms, int n, const PartRows* parts, const int* n_stat,
                 const gmi_ppo_hparams* hp, int rows, uint32_t k, float* stats_out, float* grad_out, bool do_update) {
   gmi_model* m = ms[0];
   const gmi::ShadowTable tab = gmi::make_shadow_table(m->L);
@@ -591,8 +609,9 @@ int launch_adam(gmi_instance* g, gmi_model* const* ms, int n, const int* n_split
   set.n = n;
   int most = 0;
   for (int i = 0; i < n; ++i) {
-    set.r[i] = Partials{ms[i]->grad_part, ms[i]->stat_part, n_split[i], n_stat[i]};
-    most = std::max(most, n_split[i]);
+    set.r[i] = Partials{ms[i]->grad_part, ms[i]->stat_part, parts[i].flat, n_stat[i]};
+    set.split[i] = parts[i].split;
+    most = std::max(most, parts[i].flat);
   }
   if (m->L.dtype == GMI_DTYPE_BF16) {
     AdamTiles tt;
@@ -657,12 +676,13 @@ extern "C" int ppo_update(gmi_t g, gmi_model_t m, gmi_buffer_t b, const gmi_ppo_
       if (rc != GMI_OK) return rc;
     }
     for (int j = 0; j < nmb; ++j) {
-      int n_split = 1, nlb = 1;
-      rc = minibatch_pass(g, m, b, hp, perm + (int64_t)j * hp->minibatch, hp->minibatch, cus, true, &n_split, &nlb,
+      PartRows parts = {};
+      int nlb = 1;
+      rc = minibatch_pass(g, m, b, hp, perm + (int64_t)j * hp->minibatch, hp->minibatch, cus, true, &parts, &nlb,
                           obs16);
       if (rc != GMI_OK) return rc;
       ++k;
-      rc = launch_adam(g, &m, 1, &n_split, &nlb, hp, hp->minibatch, k,
+      rc = launch_adam(g, &m, 1, &parts, &nlb, hp, hp->minibatch, k,
                        stats_out ? stats_out + 5 * ((int64_t)e * nmb + j) : nullptr, nullptr, true);
       if (rc != GMI_OK) return rc;
     }
@@ -726,10 +746,11 @@ extern "C" int ppo_update_group(const gmi_t* gs, const gmi_model_t* ms, const gm
     }
     const int64_t perm_off = (int64_t)(e % gmi::kPermEpochs) * B;
     for (int j = 0; j < nmb; ++j) {
-      int n_split[kMaxGroup], nlb[kMaxGroup];
+      PartRows parts[kMaxGroup] = {};
+      int nlb[kMaxGroup];
       for (int i = 0; i < n; ++i) {
         rc = minibatch_pass(gs[i], ms[i], bs[i], hp, bs[i]->perm + perm_off + (int64_t)j * hp->minibatch, hp->minibatch,
-                            gmi::trainer_cus(gs[i], n), true, &n_split[i], &nlb[i], obs16[i]);
+                            gmi::trainer_cus(gs[i], n), true, &parts[i], &nlb[i], obs16[i]);
         if (rc != GMI_OK) return rc;
         // replica i's partials are complete: let instance 0 see them
         if (i > 0) {
@@ -738,7 +759,7 @@ extern "C" int ppo_update_group(const gmi_t* gs, const gmi_model_t* ms, const gm
         }
       }
       ++k;
-      rc = launch_adam(g0, models, n, n_split, nlb, hp, hp->minibatch, k,
+      rc = launch_adam(g0, models, n, parts, nlb, hp, hp->minibatch, k,
                        stats_out ? stats_out + 5 * ((int64_t)e * nmb + j) : nullptr, nullptr, true);
       if (rc != GMI_OK) return rc;
       // the updated parameters are complete: the other instances may start their next forward pass
@@ -770,10 +791,11 @@ extern "C" int ppo_evaluate(gmi_t g, gmi_model_t m, gmi_buffer_t b, const gmi_pp
   int rc = check_idx_call("ppo_evaluate", g, m, b, hp, idx, n);
   if (rc != GMI_OK) return rc;
   if (!stats_out) GMI_FAIL(GMI_ERR_INVALID_ARG, "ppo_evaluate: stats_out is NULL");
-  int n_split = 0, nlb = 1;
-  rc = minibatch_pass(g, m, b, hp, idx, n, gmi::trainer_cus(g, 1), false, &n_split, &nlb);
+  PartRows parts = {};
+  int nlb = 1;
+  rc = minibatch_pass(g, m, b, hp, idx, n, gmi::trainer_cus(g, 1), false, &parts, &nlb);
   if (rc != GMI_OK) return rc;
-  return launch_adam(g, &m, 1, &n_split, &nlb, hp, n, 1, stats_out, nullptr, false);
+  return launch_adam(g, &m, 1, &parts, &nlb, hp, n, 1, stats_out, nullptr, false);
 }
 
 extern "C" int ppo_gradient(gmi_t g, gmi_model_t m, gmi_buffer_t b, const gmi_ppo_hparams* hp, const int32_t* idx,
@@ -781,10 +803,11 @@ extern "C" int ppo_gradient(gmi_t g, gmi_model_t m, gmi_buffer_t b, const gmi_pp
   int rc = check_idx_call("ppo_gradient", g, m, b, hp, idx, n);
   if (rc != GMI_OK) return rc;
   if (!grad_out) GMI_FAIL(GMI_ERR_INVALID_ARG, "ppo_gradient: grad_out is NULL");
-  int n_split = 1, nlb = 1;
-  rc = minibatch_pass(g, m, b, hp, idx, n, gmi::trainer_cus(g, 1), true, &n_split, &nlb);
+  PartRows parts = {};
+  int nlb = 1;
+  rc = minibatch_pass(g, m, b, hp, idx, n, gmi::trainer_cus(g, 1), true, &parts, &nlb);
   if (rc != GMI_OK) return rc;
-  return launch_adam(g, &m, 1, &n_split, &nlb, hp, n, 1, stats_out, grad_out, false);
+  return launch_adam(g, &m, 1, &parts, &nlb, hp, n, 1, stats_out, grad_out, false);
 }
 
 extern "C" int adam_update(gmi_t g, float* params, float* adam_m, float* adam_v, const float* grad, int64_t n,

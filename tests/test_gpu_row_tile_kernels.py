@@ -663,3 +663,44 @@ def test_fp32_collection_with_the_roles_on_waves_of_their_own(g, obs, act, hidde
         assert torch.equal(ses[0].episode_step, ses[1].episode_step)
     for s in reversed(ses):
         s.close()
+
+
+@pytest.mark.parametrize("obs,act,hidden,fused", [
+    (60, 8, (256, 128, 64), 1), (108, 21, (400, 200, 100), 1), (211, 20, (512, 512, 256, 128), 1), (108, 21, (400, 200, 100), 0),
+    (17, 40, (800, 300), 0), (3, 1, (32,), 0), (300, 5, (1100, 1100, 64), 0)])
+def test_weight_gradient_splits_sum_to_the_gradient_of_the_pieces(g, inst, obs, act, hidden, fused):
+    """The rows of a weight gradient are split among more or fewer workgroups layer by layer, tiles of a side are of equal size, and layers
+    that the two nets do not share (a policy head wider than 32) have workgroups of their own.  Against the mean of 64-row pieces, which are
+    not split: the gradient at the loss scales by a power of two, so every bf16 value is the same and only the order of the fp32 sums
+    differs (2048 terms: well within 1e-4 of a tensor's norm); and against the fp32 kernels at the bf16 band, per tensor."""
+    rows, piece = 2048, 64
+    hp = lambda n: g.ppo_hparams(clip=1e3, c_v=0.5, c_e=0.0, minibatch=n)      # no sample at a clip boundary
+    got = {}
+    for dtype in ("bf16", "f32"):
+        model, buf, keep = _setup(g, inst, obs, act, hidden, dtype, 2, rows // 2, rows)
+        n = keep[0].numel()
+        idx = torch.tensor(np.random.default_rng(1).permutation(rows).astype(np.int32), device="cuda:0")
+        grad, part, stats = torch.zeros(n, device="cuda:0"), torch.zeros(rows // piece, n, device="cuda:0"), torch.zeros(5, device="cuda:0")
+        torch.cuda.synchronize()
+        g.gmi_set_fusion(inst, fused)
+        g.ppo_gradient(inst, model, buf, hp(rows), idx, rows, grad, stats)
+        if dtype == "bf16":
+            for k in range(rows // piece):
+                g.ppo_gradient(inst, model, buf, hp(piece), idx[k * piece:(k + 1) * piece], piece, part[k], stats)
+        g.gmi_sync(inst)
+        g.gmi_set_fusion(inst, 1)
+        got[dtype] = grad.cpu().numpy()
+        if dtype == "bf16":
+            got["pieces"] = part.double().mean(0).cpu().numpy()
+        g.gmi_buffer_destroy(buf)
+        g.gmi_model_destroy(model)
+    off = 0
+    for out_dim in (act, 1):
+        prev = obs
+        for o in (*hidden, out_dim):
+            for n_el in (prev * o, o):
+                s = slice(off, off + n_el)
+                assert rel_l2(got["bf16"][s], got["pieces"][s]) <= 1e-4, (off, rel_l2(got["bf16"][s], got["pieces"][s]))
+                assert rel_l2(got["bf16"][s], got["f32"][s]) <= 2e-2, (off, rel_l2(got["bf16"][s], got["f32"][s]))
+                off += n_el
+            prev = o
