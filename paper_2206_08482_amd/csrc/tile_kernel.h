@@ -53,6 +53,7 @@ struct TileShape {
   static constexpr bool nat = false;      // TileShapeNat, TileShapeFp8
   static constexpr bool fp8 = false;      // TileShapeFp8
   static constexpr bool lp_blocks = false;      // log-densities by blocks of four actions
+  static constexpr bool keep = false;      // TileShapeKeep
   static constexpr int NL = (int)sizeof...(DIMS) - 1;
   static constexpr ChainDims dims() { return ChainDims{NL, {DIMS...}}; }
   static constexpr int nseg() { return cd_nseg(dims()); }
@@ -72,6 +73,8 @@ struct TileShape {
     for (int i = 0; i < s; ++i) n += cd_seg_blocks(dims(), i);
     return n;
   }
+  // first block of the activation area that holds layer l's input (TileShapeKeep: an area per layer; else they take turns)
+  static constexpr int area(int) { return 0; }
   // the loss epilogue's per-wave transposition buffers live in the activation area behind the head layer's input
   static constexpr size_t scr_offset() { return (size_t)dims().d[NL - 1] / 16 * nrt * 1024; }
   static constexpr size_t x_bytes() { return (size_t)maxks() * nrt * 1024; }
@@ -84,6 +87,29 @@ struct TileShape {
     return (ROWS == 64 || ROWS == 128) && x_bytes() >= scr_offset() + (size_t)nrt * kScrBytes;
   }
 };
+
+// The same with all layers' activations in LDS until the gradient takes their place: the backward epilogues read ELU's inputs there
+// (from memory they were 59 of the 219 MB that 32768 rows of 60:256:128:64:8 moved), and a layer's results do not go where its input
+// lies, so one barrier per layer is enough.  Area l: layer l's input, then the gradient at it; area NL: the heads' gradient.  The
+// first layer's area has no gradient and serves the loss as its transposition buffers.  For shapes of which two workgroups fit a
+// compute unit that way (kKeepBytes): with one (108:400:200:100:21) nothing covers a wave's waits.
+template <int ROWS, int... DIMS>
+struct TileShapeKeep : TileShape<ROWS, DIMS...> {
+  using B = TileShape<ROWS, DIMS...>;
+  static constexpr bool keep = true;
+  static constexpr int area(int l) {
+    int n = 0;
+    for (int i = 0; i < l; ++i) {
+      const int blocks = B::dims().d[i] / 16 * B::nrt, scr = (B::nrt * kScrBytes + 1023) / 1024;
+      n += i == 0 && blocks < scr ? scr : blocks;
+    }
+    return n;
+  }
+  static constexpr size_t scr_offset() { return 0; }
+  static constexpr size_t x_bytes() { return (size_t)(area(B::NL) + 2 * B::nrt) * 1024; }
+  static constexpr size_t lds_bytes() { return B::lds_bytes() - B::x_bytes() + x_bytes(); }
+};
+constexpr size_t kKeepBytes = 80 * 1024;
 
 // The same shape for inference: the walk ends after the heads, nothing is stored for the weight gradients, and the
 // heads' results go out as policy means and values (the products and their order are the trainer's forward pass).
@@ -139,6 +165,7 @@ struct Seg {
   static constexpr int XD = FTW >= 2 || S::fp8 ? 1 : 2;             // k steps the activation blocks are read ahead (a k step of
                                                           // fewer products is shorter than an LDS round trip)
   static constexpr int blk0 = S::seg_blk0(SEG);
+  static constexpr int in_area = S::area(bwd ? layer + 1 : layer), out_area = S::area(bwd ? layer : layer + 1);
   // The segment's input, which the previous segment's epilogue left in LDS, goes to memory block by block (for the
   // weight-gradient kernel and for ELU') DURING this segment's k loop: h[layer] in a forward segment, dz[layer] in an
   // input-gradient segment.  (Stores issued in the epilogue would all be older than the next k loop's weight
@@ -252,12 +279,13 @@ __device__ __forceinline__ WeightPos seg_weights(const Ctx<S>& c, const ChainArg
   }
   return p;
 }
-// This lane's 16 bytes of block (ks, rt).  An LDS instruction's constant reaches 64 KiB: with one offset per half of the area every
+// This lane's 16 bytes of block (ks, rt) of the area at block `at`.  An LDS instruction's constant reaches 64 KiB: with one offset per half of the area every
 // block is a constant away.  (Left to itself the compiler forms an address per block of the upper half, keeps them from one segment
 // to the next and spills them: 47 registers, each reload in a k loop behind every fetch and store in flight.)
 template <class S>
-__device__ __forceinline__ uint4* x_block(const Ctx<S>& c, int ks, int rt) {
-  return reinterpret_cast<uint4*>(reinterpret_cast<char*>(c.X) + c.xo[ks * S::nrt / 64] + rt * 1024) + (ks * S::nrt % 64) * 64;
+__device__ __forceinline__ uint4* x_block(const Ctx<S>& c, int at, int ks, int rt) {
+  const int blk = at + ks * S::nrt;
+  return reinterpret_cast<uint4*>(reinterpret_cast<char*>(c.X) + c.xo[blk / 64] + rt * 1024) + (blk % 64) * 64;
 }
 template <class S, int SEG, int KS>
 __device__ __forceinline__ uint4 weight_block(const Ctx<S>& c, const WeightPos& w, int ta, int p) {
@@ -293,7 +321,7 @@ __device__ __forceinline__ void read_x(Ctx<S>& c) {
 #pragma unroll
     for (int b = 0; b < G::RT; ++b)
 #pragma unroll
-      for (int p = 0; p < G::NP; ++p) c.xq[KS % kXRing<S>][b][p] = *x_block(c, KS * G::NP + p, first_rt<G>(c) + b);
+      for (int p = 0; p < G::NP; ++p) c.xq[KS % kXRing<S>][b][p] = *x_block(c, G::in_area, KS * G::NP + p, first_rt<G>(c) + b);
   }
 }
 
@@ -318,6 +346,12 @@ __device__ __forceinline__ void fetch_h(Ctx<S>& c, const ChainArgs& a) {
     constexpr int ta = T / G::RT, tb = T % G::RT;
     constexpr int nks = G::D.d[G::layer] / 16;
     const int ft = tile_of<G>(c, ta);
+    if constexpr (S::keep) {
+      const uint4* x = c.X + (G::out_area + 2 * ft * S::nrt + first_rt<G>(c) + tb) * 64 + c.lane;
+      c.hq[T % (kHPre + 1)][0] = x[0];
+      c.hq[T % (kHPre + 1)][1] = x[S::nrt * 64];
+      return;
+    }
     const uint4* p = reinterpret_cast<const uint4*>(a.h[c.net][G::layer]) + block_word(c.tr, nks, 2 * ft, c.rt0 + first_rt<G>(c) + tb);
     c.hq[T % (kHPre + 1)][0] = gmi::load_uniform(p, 0, c.lane16);
     c.hq[T % (kHPre + 1)][1] = gmi::load_uniform(p, 4 * 1024, c.lane16);
@@ -345,11 +379,11 @@ __device__ __forceinline__ void aux_op(Ctx<S>& c, const ChainArgs& a) {
   using G = Seg<S, SEG>;
   if constexpr (I < G::RT * G::NP) {
     if constexpr (KS + G::XD < G::NKS)
-      c.xq[(KS + G::XD) % kXRing<S>][I / G::NP][I % G::NP] = *x_block(c, (KS + G::XD) * G::NP + I % G::NP, first_rt<G>(c) + I / G::NP);
+      c.xq[(KS + G::XD) % kXRing<S>][I / G::NP][I % G::NP] = *x_block(c, G::in_area, (KS + G::XD) * G::NP + I % G::NP, first_rt<G>(c) + I / G::NP);
   } else if constexpr (G::store_x) {
     static_assert(G::NKS % 2 == 0, "a wave moves a block every two k steps");
     if constexpr (I == G::RT * G::NP) {
-      if constexpr (KS % 2 == 0) c.sx = *x_block(c, KS, c.wave);      // the second half of the waves: k step KS + 1
+      if constexpr (KS % 2 == 0) c.sx = *x_block(c, G::in_area, KS, c.wave);      // the second half of the waves: k step KS + 1
     } else if constexpr (KS % 2 == 1) {
       store_block(store_x_array<S, SEG>(c, a) + block_word(c.tr, G::NKS, c.wave / S::nrt, c.rt0 + c.wave % S::nrt), c.lane16, c.sx,
                   (KS - 1) * 4096);      // arrays hold whole tiles
@@ -459,7 +493,7 @@ __device__ __forceinline__ void tile_epilogue(Ctx<S>& c, const ChainArgs& a) {
       for (int q = 0; q < 4; ++q)
         *reinterpret_cast<uint2*>(x + (q / 2) * S::nrt * 1024 + (q % 2) * 512) = make_uint2(w[2 * q], w[2 * q + 1]);
     } else {
-      uint4* x = c.X + ((2 * ft) * S::nrt + rt) * 64 + c.lane;
+      uint4* x = c.X + (G::out_area + (2 * ft) * S::nrt + rt) * 64 + c.lane;
       x[0] = make_uint4(w[0], w[1], w[2], w[3]);
       x[S::nrt * 64] = make_uint4(w[4], w[5], w[6], w[7]);
     }
@@ -578,8 +612,8 @@ __device__ __forceinline__ void loss_epilogue(Ctx<S>& c, const ChainArgs& a, con
   uint32_t w[8];
 #pragma unroll
   for (int q = 0; q < 8; ++q) w[q] = pack_bf16(d[2 * q], d[2 * q + 1]);
-  c.X[(0 * S::nrt + c.wave) * 64 + c.lane] = make_uint4(w[0], w[1], w[2], w[3]);
-  c.X[(1 * S::nrt + c.wave) * 64 + c.lane] = make_uint4(w[4], w[5], w[6], w[7]);
+  c.X[(S::area(S::NL) + c.wave) * 64 + c.lane] = make_uint4(w[0], w[1], w[2], w[3]);
+  c.X[(S::area(S::NL) + S::nrt + c.wave) * 64 + c.lane] = make_uint4(w[4], w[5], w[6], w[7]);
   {
     uint4* arr = reinterpret_cast<uint4*>(a.dz[c.net][S::NL - 1]);
     store_block(arr + block_word(c.tr, 2, 0, c.rt0 + c.wave), c.lane16, make_uint4(w[0], w[1], w[2], w[3]));      // arrays hold whole tiles
@@ -736,7 +770,7 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
       k_steps<S, SEG, 0>(c, a, wseg);
     }
     issue_first_weights<S, SEG + 1>(c, a);
-    __syncthreads();                       // every wave is done with the layer's input
+    if constexpr (!S::keep) __syncthreads();                       // every wave is done with the layer's input
     // this lane's loss inputs: cold loads, issued where a long stretch of arithmetic follows and no younger load is
     // waited for (the memory counter is in order)
     if constexpr (!S::fwd && SEG == (S::NL >= 3 ? S::NL - 3 : 0)) fetch_loss_inputs<S>(c, a);
@@ -756,7 +790,7 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
                    block_word(c.tr, G::F / 16, c.wave / S::nrt, c.rt0 + c.wave % S::nrt);
 #pragma unroll 8
       for (int k2 = 0; k2 < G::F / 16; k2 += 2) {
-        store_block(arr, c.lane16, c.X[(k2 * S::nrt + c.wave) * 64 + c.lane], k2 * 4096);      // arrays hold whole tiles
+        store_block(arr, c.lane16, c.X[(G::out_area + k2 * S::nrt + c.wave) * 64 + c.lane], k2 * 4096);      // arrays hold whole tiles
       }
     }
     run_segment<S, SEG + 1>(c, a);
@@ -1064,7 +1098,8 @@ GMI_TILE_FP8_PART_DECL(0); GMI_TILE_FP8_PART_DECL(1); GMI_TILE_FP8_PART_DECL(2);
   }
 #define GMI_TILE_PART_DEFINE(k, ...)                                                              \
   GMI_TILE_PART_DECL(k) {                                                                         \
-    using S = gmi_tile::TileShape<64, __VA_ARGS__>;                                               \
+    using K = gmi_tile::TileShapeKeep<64, __VA_ARGS__>;                                           \
+    using S = std::conditional_t<K::lds_bytes() <= gmi_tile::kKeepBytes, K, gmi_tile::TileShape<64, __VA_ARGS__>>; \
     if (!gmi_tile::shape_matches<S>(L)) return GMI_ERR_UNSUPPORTED;                               \
     if (rows == 0) return GMI_OK;                                                                 \
     return gmi_tile::launch_shape<S>(g, a, rows, tiles_out, flops, bytes);                        \
