@@ -16,7 +16,8 @@
 //
 // A layer is: k loop (all accumulators of the layer live at once) - barrier - epilogue (bias + ELU, or x ELU' of
 // the stored activation; conversion; the results into LDS in place of the layer's input; from there they go to memory
-// for the weight-gradient kernel) - barrier.  The next layer's first weight blocks are fetched before the epilogue.
+// for the weight-gradient kernel) - barrier (variants: TileShapeKeep, late_write).  The next layer's first weight blocks are fetched
+// before the epilogue.
 //
 // Two waves per SIMD: an epilogue is straight-line code that runs once, and a wave gets its instructions at about a byte per cycle,
 // half of what the vector unit takes, so one wave alone is bound by them.  In the k loops one wave's fetches ride under the
@@ -54,6 +55,11 @@ struct TileShape {
   static constexpr bool fp8 = false;      // TileShapeFp8
   static constexpr bool lp_blocks = false;      // log-densities by blocks of four actions
   static constexpr bool keep = false;      // TileShapeKeep
+  // Two waves of the workgroup on a SIMD: the first four take the matrix unit first and are done with the k loop while the others
+  // are half way; a layer's results then wait in registers for the barrier behind which they may replace its input, so that the first
+  // waves' epilogue runs under the others' products.  (32768 rows of 211:512:512:256:128:20 184 us, 176 so.  With waves of two
+  // workgroups on a SIMD, which are at different places anyway, the writes in one piece only cost: 81 and 86 us of 108:400:200:100:21.)
+  static constexpr bool late_write = ROWS == 128;
   static constexpr int NL = (int)sizeof...(DIMS) - 1;
   static constexpr ChainDims dims() { return ChainDims{NL, {DIMS...}}; }
   static constexpr int nseg() { return cd_nseg(dims()); }
@@ -212,6 +218,7 @@ struct Ctx {
   floatx16 acc[S::acc_ft][S::nrt];
   uint4 wq[S::ring];                   // weight blocks of k steps g .. g + DEP - 1: block (ks, a) at (ks % DEP) * FTW + a
   uint4 xq[S::fp8 ? 2 : 3][S::nrt][S::fp8 ? 2 : 1];                    // activation blocks of k steps g .. g + XD (ring indexed by k step)
+  uint32_t touched;                  // what prefetch_weights loads
   uint4 sx;                          // block of the activation area on its way to memory (store_x)
   uint4 hq[kHPre + 1][2];            // stored activations of the tiles ahead (input-gradient epilogues)
   const uint4* wnet;                 // this net's stream
@@ -309,6 +316,23 @@ __device__ __forceinline__ void issue_first_weights(Ctx<S>& c, const ChainArgs& 
       issue_weights<S, SEG, KS>(c, seg_weights<S, SEG>(c, a));
       issue_first_weights<S, SEG, KS + 1>(c, a);
     }
+  }
+}
+
+// Touches segment SEG's weights, one word of every line, so that they are in the die's second-level cache when the k loop asks for
+// them: workgroup q of the 32 that a die holds takes every 32nd line.  The workgroups of a die go through the layers nearly in step,
+// and what they store and read back pushes the weights out between one round of workgroups and the next: without this every one
+// of them waits for the same misses (a workgroup of 211:512:512:256:128:20 191 thousand cycles, now 171).  The one-line shapes' 358 KB
+// and the forward kernels, which store next to nothing, gain nothing by it.
+template <class S, int SEG>
+__device__ __forceinline__ void prefetch_weights(Ctx<S>& c) {
+  if constexpr (S::late_write && SEG < n_run<S>()) {
+    asm volatile("" ::"v"(c.touched));
+    constexpr uint32_t bytes = cd_seg_blocks(S::dims(), SEG) * 1024;
+    static_assert(bytes <= 32u * 128 * S::threads, "a line per thread");
+    const uint32_t q = (blockIdx.x + gridDim.x * blockIdx.y) >> 3 & 31;
+    c.touched = __builtin_amdgcn_raw_buffer_load_b32(
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(c.wnet) + S::seg_blk0(SEG) * 64, 0, bytes, 0x00020000), (q + 32 * c.tid) * 128, 0, 0);
   }
 }
 
@@ -447,16 +471,44 @@ __device__ __forceinline__ void k_steps(Ctx<S>& c, const ChainArgs& a, const Wei
   }
 }
 
-// Epilogue of tile T of a hidden forward layer or of an input-gradient layer.
 template <class S, int SEG, int T>
-__device__ __forceinline__ void tile_epilogue(Ctx<S>& c, const ChainArgs& a) {
+__device__ __forceinline__ void write_tile(const Ctx<S>& c, const uint32_t (&w)[8]) {
+  using G = Seg<S, SEG>;
+  const int ft = tile_of<G>(c, T / G::RT), rt = first_rt<G>(c) + T % G::RT;
+  if constexpr (S::fp8) {      // word q: features 8 q + 4 hh .. of the tile.  The halves of the wave trade words: the lower one gets
+                               // quads 0 and 1 of both, the first block's 16 bytes of its row, the upper one quads 2 and 3
+    const auto u = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+    const auto v = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+    c.X[((ft / 2 * 2 + c.hh) * S::nrt + rt) * 64 + c.s + 32 * (ft & 1)] = make_uint4(u[0], u[1], v[0], v[1]);
+  } else if constexpr (S::nat) {      // quad q: features 8 (q % 2) + 4 hh .. of k step 2 ft + q / 2
+    char* x = reinterpret_cast<char*>(c.X + ((2 * ft) * S::nrt + rt) * 64 + c.s) + 8 * c.hh;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *reinterpret_cast<uint2*>(x + (q / 2) * S::nrt * 1024 + (q % 2) * 512) = make_uint2(w[2 * q], w[2 * q + 1]);
+  } else {
+    uint4* x = c.X + (G::out_area + (2 * ft) * S::nrt + rt) * 64 + c.lane;
+    x[0] = make_uint4(w[0], w[1], w[2], w[3]);
+    x[S::nrt * 64] = make_uint4(w[4], w[5], w[6], w[7]);
+  }
+}
+template <class S, int SEG, int T>
+__device__ __forceinline__ void write_tiles(const Ctx<S>& c, const uint32_t (&w)[Seg<S, SEG>::FTW * Seg<S, SEG>::RT][8]) {
+  if constexpr (T < Seg<S, SEG>::FTW * Seg<S, SEG>::RT) {
+    write_tile<S, SEG, T>(c, w[T]);
+    write_tiles<S, SEG, T + 1>(c, w);
+  }
+}
+
+// Epilogue of tile T of a hidden forward layer or of an input-gradient layer: the results as they go into the activation area.
+template <class S, int SEG, int T>
+__device__ __forceinline__ void tile_results(Ctx<S>& c, const ChainArgs& a, uint32_t (&out)[Seg<S, SEG>::FTW * Seg<S, SEG>::RT][8]) {
   using G = Seg<S, SEG>;
   if constexpr (T < G::FTW * G::RT) {
     constexpr int ta = T / G::RT, tb = T % G::RT;
-    const int ft = tile_of<G>(c, ta), rt = first_rt<G>(c) + tb;
+    const int ft = tile_of<G>(c, ta);
     fetch_h<S, SEG, T + kHPre>(c, a);
     const floatx16& acc = c.acc[ta][tb];
-    uint32_t w[8];
+    uint32_t(&w)[8] = out[T];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       float v0 = acc[4 * q + 0], v1 = acc[4 * q + 1], v2 = acc[4 * q + 2], v3 = acc[4 * q + 3];
@@ -482,22 +534,19 @@ __device__ __forceinline__ void tile_epilogue(Ctx<S>& c, const ChainArgs& a) {
         w[2 * q + 1] = pack_bf16(v2, v3);
       }
     }
-    if constexpr (S::fp8) {      // word q: features 8 q + 4 hh .. of the tile.  The halves of the wave trade words: the lower one gets
-                                 // quads 0 and 1 of both, the first block's 16 bytes of its row, the upper one quads 2 and 3
-      const auto u = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
-      const auto v = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
-      c.X[((ft / 2 * 2 + c.hh) * S::nrt + rt) * 64 + c.s + 32 * (ft & 1)] = make_uint4(u[0], u[1], v[0], v[1]);
-    } else if constexpr (S::nat) {      // quad q: features 8 (q % 2) + 4 hh .. of k step 2 ft + q / 2
-      char* x = reinterpret_cast<char*>(c.X + ((2 * ft) * S::nrt + rt) * 64 + c.s) + 8 * c.hh;
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        *reinterpret_cast<uint2*>(x + (q / 2) * S::nrt * 1024 + (q % 2) * 512) = make_uint2(w[2 * q], w[2 * q + 1]);
-    } else {
-      uint4* x = c.X + (G::out_area + (2 * ft) * S::nrt + rt) * 64 + c.lane;
-      x[0] = make_uint4(w[0], w[1], w[2], w[3]);
-      x[S::nrt * 64] = make_uint4(w[4], w[5], w[6], w[7]);
-    }
-    tile_epilogue<S, SEG, T + 1>(c, a);
+    if constexpr (!S::late_write) write_tile<S, SEG, T>(c, w);
+    tile_results<S, SEG, T + 1>(c, a, out);
+  }
+}
+template <class S, int SEG>
+__device__ __forceinline__ void layer_epilogue(Ctx<S>& c, const ChainArgs& a) {
+  using G = Seg<S, SEG>;
+  uint32_t out[G::FTW * G::RT][8];
+  if constexpr (!S::keep && !S::late_write) __syncthreads();                       // every wave is done with the layer's input
+  tile_results<S, SEG, 0>(c, a, out);
+  if constexpr (S::late_write) {
+    __syncthreads();                       // every wave is done with the layer's input
+    write_tiles<S, SEG, 0>(c, out);
   }
 }
 
@@ -770,7 +819,8 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
       k_steps<S, SEG, 0>(c, a, wseg);
     }
     issue_first_weights<S, SEG + 1>(c, a);
-    if constexpr (!S::keep) __syncthreads();                       // every wave is done with the layer's input
+    prefetch_weights<S, SEG + 1>(c);
+    if constexpr (!S::keep && G::head) __syncthreads();      // every wave is done with the layer's input
     // this lane's loss inputs: cold loads, issued where a long stretch of arithmetic follows and no younger load is
     // waited for (the memory counter is in order)
     if constexpr (!S::fwd && SEG == (S::NL >= 3 ? S::NL - 3 : 0)) fetch_loss_inputs<S>(c, a);
@@ -779,7 +829,7 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
     } else if constexpr (G::head) {
       loss_epilogue<S>(c, a, c.acc[0][0]);
     } else {
-      tile_epilogue<S, SEG, 0>(c, a);
+      layer_epilogue<S, SEG>(c, a);
     }
     __syncthreads();
     if constexpr (G::head && !S::fwd) loss_sums<S>(c, a);
@@ -941,6 +991,8 @@ __device__ __forceinline__ void row_tile(const ChainArgs& a, int item, unsigned 
       }
     }
     issue_first_weights<S, 0>(c, a);
+    c.touched = 0;
+    prefetch_weights<S, 0>(c);
     {
       int off = 0;
 #pragma unroll
@@ -980,6 +1032,7 @@ __device__ __forceinline__ void row_tile(const ChainArgs& a, int item, unsigned 
     }
   }
   __syncthreads();
+  if constexpr (S::late_write) { if (c.wave < 4) __builtin_amdgcn_s_setprio(1); }
   run_segment<S, 0>(c, a);
 }
 
