@@ -367,7 +367,10 @@ __global__ __launch_bounds__(128 * WRN) void linear_bf16_big_kernel(gmi::LinearB
 // same features were fetched by twice as many workgroups, whose second and third rounds found them evicted: 616 MB per
 // 32768-row minibatch of 211:512:512:256:128:20 for 403 MB of operands.  All workgroups now run in one round with at most
 // one per compute unit, and half as many splits are enough (their partials are another 6 MB each, written here and read
-// by Adam).  Measured on that minibatch: 145 us before, now 94 (467 MB fetched, 52 written).
+// by Adam): 467 MB fetched, 52 written.  Every layer has its own number of splits and a matrix's tiles are of equal size (plan_wgrad);
+// between two barriers there is one wait and no switch, and the bias sums are shared out among the waves.  us, with the same splits for
+// all layers / split per layer / as it is: 32768 rows of 60:256:128:64:8 29.9 / 26.7 / 24.4, of 108:400:200:100:21 56.9 / 51.1 / 42.9, of
+// 211:512:512:256:128:20 109 / 108 / 91.5.  Without its loads the last takes 57, without its products and reads of LDS 50.
 constexpr int kWgradT = 256;                            // features per operand and tile
 constexpr int kWgradRows = 32;                          // rows per stage
 constexpr int kWgradOperand = kWgradT * kWgradRows * 2; // bytes
@@ -391,6 +394,15 @@ __device__ __forceinline__ void load_to_lds(const void* base, uint32_t off, uint
 }
 __device__ __forceinline__ void load_to_lds(const void* src, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "m0", "memory");
+}
+// Four of the first kind, from base + off[k] to lds + 1024 k.
+__device__ __forceinline__ void load4_to_lds(const void* base, const uint32_t (&off)[4], uint32_t lds) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %5\n\t"
+      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %5\n\t"
+      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %5\n\t"
+      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %5" ::"s"(lds), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]),
+      "s"(base) : "m0", "scc", "memory");
 }
 #pragma clang diagnostic pop
 
@@ -436,33 +448,35 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
   // in odd steps L ^ 8 (for the same reason)
   const int bs = (lane >> 3) * 4 + (lane & 3), bh = (lane >> 2) & 1;      // odd steps: row bs ^ 4
   const int nks_op = fmax >> 4;
-  // loads of this wave per stage: features past the tile are not loaded (what the LDS holds there feeds results that
-  // are never stored)
-  const int n_ld = LAYOUT == 1 ? min(max(((fend - f0) >> 4) - (wave & 3) * 4, 0), 4) : 4;
   const int j0 = (wave & 3) * 4;
-  // per-lane byte offsets of pieces with even and odd k (everything else of an address is wave-uniform), and whether the
-  // lane's features exist
-  uint32_t voff[2];
+  // Blocks: a wave has n_ld pieces in the tile.  One with none loads nothing, any other issues four loads a stage, the last piece again
+  // in place of those past the tile (what the LDS holds there feeds results that are never stored): with the same number for all
+  // waves the wait for them is one instruction.  (As a switch over n_ld and the stages left it was 30 scalar instructions and 8
+  // branches, all of a compute unit's waves at the same time between two barriers.)
+  const int n_ld = LAYOUT == 1 ? min(max(((fend - f0) >> 4) - j0, 0), 4) : 4;
+  // per-lane byte offsets, everything else of an address is wave-uniform: of piece k; row-major, of pieces with even and odd k, and
+  // whether the lane's features exist
+  uint32_t voff[LAYOUT == 1 ? 4 : 2];
   bool f_ok[2];
+  if constexpr (LAYOUT == 1) {
 #pragma unroll
-  for (int par = 0; par < 2; ++par) {
-    if constexpr (LAYOUT == 1) {
-      voff[par] = ((bs ^ (4 * par)) + 32 * bh) * 16;
-      f_ok[par] = true;
-    } else {
+    for (int k = 0; k < 4; ++k) voff[k] = ((bs ^ (4 * (k & 1))) + 32 * bh) * 16 + min(k, max(n_ld, 1) - 1) * 4096;
+  } else {
+#pragma unroll
+    for (int par = 0; par < 2; ++par) {
       const int f = f0 + 8 * ((lane & 31) ^ (((2 * par + rl) & 3) << 2));
       voff[par] = (uint32_t)(rl * ld + f) * 2;
       f_ok[par] = f < fend;
     }
   }
+  uint32_t put = lds_w;      // where the next stage goes
   auto issue = [&](int stage) {
     const int r0 = row_begin + stage * kWgradRows;
-    const uint32_t dst = lds_w + (stage % kWgradRing) * kWgradStage;
+    const uint32_t dst = put;
+    put = put == lds_w + (kWgradRing - 1) * kWgradStage ? lds_w : put + kWgradStage;
     if constexpr (LAYOUT == 1) {
       const char* base = opnd + ((((int64_t)(r0 >> 7) * nks_op + (f0 >> 4) + j0) * 4 + ((r0 >> 5) & 3)) << 10);
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (k < n_ld) load_to_lds(base + k * 4096, voff[k & 1], dst + k * 1024);
+      if (n_ld > 0) load4_to_lds(base, voff, dst);
     } else if (r0 + kWgradRows <= row_end) {
       const char* base = opnd + (int64_t)(r0 + 2 * j0) * ld * 2;
 #pragma unroll
@@ -475,20 +489,6 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
         const void* src = row + rl < row_end ? (const void*)(opnd + (int64_t)row * ld * 2 + voff[k & 1]) : &g_zero_piece;
         if (f_ok[k & 1]) load_to_lds(src, dst + k * 1024);
       }
-    }
-  };
-  // at most the loads of the newest `stages` stages outstanding
-  auto landed = [&](int stages) {
-    switch (stages * n_ld) {
-      case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
-      case 1: asm volatile("s_waitcnt vmcnt(1)" ::: "memory"); break;
-      case 2: asm volatile("s_waitcnt vmcnt(2)" ::: "memory"); break;
-      case 3: asm volatile("s_waitcnt vmcnt(3)" ::: "memory"); break;
-      case 4: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
-      case 6: asm volatile("s_waitcnt vmcnt(6)" ::: "memory"); break;
-      case 8: asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); break;
-      case 9: asm volatile("s_waitcnt vmcnt(9)" ::: "memory"); break;
-      default: asm volatile("s_waitcnt vmcnt(12)" ::: "memory"); break;
     }
   };
 
@@ -539,21 +539,38 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
     return __builtin_bit_cast(bf16x8, v);
   };
 
-  floatx16 acc[4][2];
-  float sum[4];
+  // Bias sums: the na waves that share output tiles divide them, wave wi takes tiles wi and wi + na, through operands of its own.  (All
+  // of them by wave 0 from the operands that it has, every wave waited for it at every barrier: 10 of 110 us of
+  // 211:512:512:256:128:20.)
+  const int na = xmax > 0 ? (n_xt + xmax - 1) / xmax : 1;
+  const bool do_bias = i0 == 0 && nx > 0 && wi < nz;
+  const int n_bias = do_bias ? (wi + na < nz ? 2 : 1) : 0;
+  const unsigned char *zb[2], *zb4[2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    sum[i] = 0.f;
+  for (int t = 0; t < 2; ++t) {
+    const int i = min(wi + t * na, 3);
+    if constexpr (LAYOUT == 1) {
+      zb[t] = za[0] + i * 2048;
+      zb4[t] = za4[0] + i * 2048;
+    } else {
+      const int r = i16 >> 2;
+      zb[t] = smem + (8 * rh + r) * 512 + 8 * (i16 & 1) + ((4 * ((ot0 + i) & 7) + 2 * fh + ((i16 & 3) >> 1)) ^ (r << 2)) * 16;
+      zb4[t] = zb[t] + 2048;
+    }
+  }
+
+  floatx16 acc[4][2];
+  float sum[2] = {0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  }
-  const bool do_bias = i0 == 0 && wi == 0;
   typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
   const bf2 one = {(__bf16)1.0f, (__bf16)1.0f};
 
-  struct Operands { bf16x8 z[4], x[2]; };
+  struct Operands { bf16x8 z[4], x[2], b[2]; };
   constexpr int kAhead = kWgradRing - 1;
   const int nst = row_begin < row_end ? (row_end - row_begin + kWgradRows - 1) / kWgradRows : 0;
   // The stage loop of a wave with NZ x NX tiles.  The barrier of iteration s: every wave's pieces of the stages up to s + 1
@@ -562,7 +579,7 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
   // would leave the matrix cores idle meanwhile.
   auto run = [&](auto nzc, auto nxc, auto biasc) {
     constexpr int NZ = decltype(nzc)::value, NX = decltype(nxc)::value;
-    constexpr bool BIAS = decltype(biasc)::value;
+    constexpr int NB = decltype(biasc)::value;
     auto read = [&](int off, int k) {
       Operands q;
       const int o = off + k * kRowStep16;
@@ -576,6 +593,8 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
         if constexpr (LAYOUT == 1) q.x[j] = operand(xa[0] + o + j * 2048, xa4[0] + o + j * 2048);
         else q.x[j] = operand(xa[j] + o, xa4[j] + o);
       }
+#pragma unroll
+      for (int t = 0; t < NB; ++t) q.b[t] = operand(zb[t] + o, zb4[t] + o);
       return q;
     };
     auto multiply = [&](const Operands& q) {
@@ -583,21 +602,19 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
       for (int i = 0; i < NZ; ++i)
 #pragma unroll
         for (int j = 0; j < NX; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q.z[i], q.x[j], acc[i][j], 0, 0, 0);
-      if constexpr (BIAS) {
 #pragma unroll
-        for (int i = 0; i < NZ; ++i)
+      for (int t = 0; t < NB; ++t)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const bf2 v = {q.z[i][2 * e], q.z[i][2 * e + 1]};
-            sum[i] = __builtin_amdgcn_fdot2_f32_bf16(v, one, sum[i], false);
-          }
-      }
+        for (int e = 0; e < 4; ++e) {
+          const bf2 v = {q.b[t][2 * e], q.b[t][2 * e + 1]};
+          sum[t] = __builtin_amdgcn_fdot2_f32_bf16(v, one, sum[t], false);
+        }
     };
     // the reads of the next step between the products of this one: a wave issues in order, and a product keeps the matrix
     // core busy for 32 cycles
     auto interleave = [&]() {
       constexpr int kProducts = NZ * NX > 0 ? NZ * NX : 1;
-      constexpr int kReads = (2 * (NZ + NX) + kProducts - 1) / kProducts;
+      constexpr int kReads = (2 * (NZ + NX + NB) + kProducts - 1) / kProducts;
 #pragma unroll
       for (int m = 0; m < kProducts; ++m) {
         __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);               // a product
@@ -608,27 +625,39 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
     Operands cur;
     int off = 0;      // LDS offset of stage s
     if constexpr (NZ > 0) cur = read(0, 0);
-    for (int s = 0; s < nst; ++s) {
-      landed(max(0, min(kAhead - 2, nst - 2 - s)));
-      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-      if (s + kAhead < nst) issue(s + kAhead);
+    auto stage = [&](int s, auto more) {
       const int off1 = off == (kWgradRing - 1) * kWgradStage ? 0 : off + kWgradStage;
       if constexpr (NZ > 0) {
         const Operands nxt = read(off, 1);
         multiply(cur);
         interleave();
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (decltype(more)::value) issue(s + kAhead);      // behind products that are on their way
+        __builtin_amdgcn_sched_barrier(0);
         cur = read(s + 1 < nst ? off1 : off, 0);
         multiply(nxt);
         interleave();
         __builtin_amdgcn_sched_barrier(0);
+      } else {
+        if constexpr (decltype(more)::value) issue(s + kAhead);
       }
       off = off1;
+    };
+    int s = 0;
+    for (; s < nst - kAhead; ++s) {
+      // the two newest stages may be outstanding
+      asm volatile("s_waitcnt vmcnt(8)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      stage(s, std::true_type{});
+    }
+    for (; s < nst; ++s) {
+      asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      stage(s, std::false_type{});
     }
   };
   if (nst > 0) {
     for (int s = 0; s < min(kAhead, nst); ++s) issue(s);
-    landed(min(kAhead, nst) - 1);
+    if (nst >= kAhead) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");      // the first stage is there
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     asm volatile("s_barrier" ::: "memory");
     auto pick = [&](auto bias) {
 #define GMI_WGRAD_RUN(Z, X) run(std::integral_constant<int, Z>{}, std::integral_constant<int, X>{}, bias)
@@ -640,7 +669,9 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
       }
 #undef GMI_WGRAD_RUN
     };
-    if (do_bias) pick(std::true_type{}); else pick(std::false_type{});
+    if (n_bias == 0) pick(std::integral_constant<int, 0>{});
+    else if (n_bias == 1) pick(std::integral_constant<int, 1>{});
+    else pick(std::integral_constant<int, 2>{});
   }
 
   // tiled partials (ModelLayout::part_floats): a quad of results of a 32 x 32 tile is one 16-byte store per lane
@@ -661,10 +692,12 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
                              acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
       }
     }
-    if (do_bias) {
-      const float b = sum[i] + __shfl_xor(sum[i], 32, 64);      // the other half of the rows
-      if (lane < 32) dst[P.b_off + 32 * ot + lane] = b;
-    }
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    if (t >= n_bias) break;
+    const float b = sum[t] + __shfl_xor(sum[t], 32, 64);      // the other half of the rows
+    if (lane < 32) dst[P.b_off + 32 * ((o0 >> 5) + ot0 + wi + t * na) + lane] = b;
   }
 }
 

@@ -675,7 +675,7 @@ __device__ __forceinline__ void loss_epilogue(Ctx<S>& c, const ChainArgs& a, con
 template <class S>
 __device__ __forceinline__ void loss_sums(const Ctx<S>& c, const ChainArgs& a) {
   const int A = a.act_dim;
-  float* out = a.stat_part + (int64_t)blockIdx.x * (gmi::kStatStride + A);
+  float* out = a.stat_part + (int64_t)(c.row0 / S::rows) * (gmi::kStatStride + A);
   if (c.net == 0) {
     if (c.tid < 3) {
       float v = 0.f;
@@ -684,7 +684,7 @@ __device__ __forceinline__ void loss_sums(const Ctx<S>& c, const ChainArgs& a) {
     }
     if (c.tid == 3) {
       float ent = 0.f;
-      if (blockIdx.x == 0)
+      if (c.row0 == 0)
         for (int j = 0; j < A; ++j) ent += c.s_red[S::nrt * 40 + j] + 1.418938533204672742f;
       out[2] = ent;
       out[5] = out[6] = out[7] = 0.f;
@@ -868,7 +868,7 @@ __device__ __forceinline__ void row_tile(const ChainArgs& a, int item, unsigned 
   c.wave = __builtin_amdgcn_readfirstlane(c.tid >> 6);
   c.s = c.lane & 31;
   c.hh = c.lane >> 5;
-  c.net = S::fwd ? (int)blockIdx.y + a.net0 : (int)blockIdx.y;
+  c.net = S::fwd ? (int)blockIdx.y + a.net0 : (S::late_write ? (int)blockIdx.x >> 2 & 1 : (int)blockIdx.y);
   if constexpr (S::fwd) {
     const int t = item / a.slot_tiles;
     c.row0 = (item - t * a.slot_tiles) * S::rows;
@@ -1039,7 +1039,15 @@ __device__ __forceinline__ void row_tile(const ChainArgs& a, int item, unsigned 
 template <class S>
 __global__ __launch_bounds__(S::threads, 2) void train_tile_kernel(ChainArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  row_tile<S>(a, blockIdx.x, smem_raw);
+  if constexpr (!S::late_write) {
+    row_tile<S>(a, blockIdx.x, smem_raw);
+  } else {
+    // half of the dies (ids go round-robin over 8) take the policy net, the others the value net: a die's second-level cache holds the
+    // weights of one net over both rounds of workgroups (32768 rows of 211:512:512:256:128:20 175 us, 170 so; the narrower shapes, whose
+    // nets both fit, 84 and 87)
+    const int item = (int)(blockIdx.x >> 3) * 4 + (blockIdx.x & 3);
+    if (item < a.items) row_tile<S>(a, item, smem_raw);
+  }
 }
 // Items one after the other: a launch that its compute units cannot hold keeps kernels of other streams waiting.  The arguments are
 // read again for every item: kept over the loop, they and what follows from them spilled 170 scalar registers.
@@ -1094,6 +1102,8 @@ int launch_shape(gmi_instance* g, ChainArgs a, int rows, int* tiles_out, double 
     a.slot_tiles = tiles;
     a.items = tiles * (a.T + (a.val_last ? 1 : 0));
     tiles = a.items;
+  } else {
+    a.items = tiles;
   }
   if constexpr (S::nat && !S::fp8) {
     if (a.T > 1 || a.val_last) {
@@ -1109,7 +1119,7 @@ int launch_shape(gmi_instance* g, ChainArgs a, int rows, int* tiles_out, double 
       return GMI_OK;
     }
   }
-  ps.launch(train_tile_kernel<S>, dim3(tiles, S::fwd ? 2 - a.net0 : 2), dim3(S::threads), lds, a);
+  ps.launch(train_tile_kernel<S>, S::late_write ? dim3((tiles + 3) / 4 * 8) : dim3(tiles, S::fwd ? 2 - a.net0 : 2), dim3(S::threads), lds, a);
   GMI_LAUNCH_CHECK();
   return GMI_OK;
 }
