@@ -316,6 +316,7 @@ struct AdamTiles {
   int n;
   int start[gmi::kMaxWgradProblems + 1];
 };
+template <int U>
 __global__ __launch_bounds__(256) void adam_shadow_kernel(gmi::ShadowTable tab, AdamTiles tt, gmi::ChainEmit ce,
                                                           float* __restrict__ params, float* __restrict__ am,
                                                           float* __restrict__ av, PartSet ps, int64_t part_stride,
@@ -362,8 +363,7 @@ __global__ __launch_bounds__(256) void adam_shadow_kernel(gmi::ShadowTable tab, 
   for (int k = 1;; ++k) {
     const float* q = r.part + src;
     const float* qb = r.part + srcb;
-    auto add = [&](int s, auto n) {      // rows s, s + 4, ...: all loads before the first addition, fixed order
-      constexpr int U = decltype(n)::value;
+    for (int s = wave; s < n_split; s += 4 * U) {      // rows s, s + 4, ...: all loads before the first addition, fixed order
       float4 x[U];
       float y[U];
 #pragma unroll
@@ -378,10 +378,7 @@ __global__ __launch_bounds__(256) void adam_shadow_kernel(gmi::ShadowTable tab, 
           g.x += x[u].x; g.y += x[u].y; g.z += x[u].z; g.w += x[u].w;
           if (i0 == 0) gb += y[u];
         }
-    };
-    int s = wave;
-    for (; s + 16 < n_split; s += 32) add(s, std::integral_constant<int, 8>{});
-    if (s < n_split) add(s, std::integral_constant<int, 4>{});
+    }
     if (k >= ps.n) break;
     r = ps.r[k];
     n_split = layer_splits(ps, k, li);
@@ -624,9 +621,18 @@ int launch_adam(gmi_instance* g, gmi_model* const* ms, int n, const PartRows* pa
     for (int i = tab.n; i <= gmi::kMaxWgradProblems; ++i) tt.start[i] = INT32_MAX;
     gmi::ChainEmit ce;
     gmi::fill_chain_emit(m->L, &ce);
-    ps.launch(adam_shadow_kernel, dim3(total + 1), dim3(256), 0, tab, tt, ce, m->params, m->adam_m, m->adam_v, set,
-              m->L.part_floats, m->L.act_dim, hp->c_e, 1.0f / (float)rows, adam_scalars(hp, k), m->shadow,
-              stats_out, grad_out, do_update ? 1 : 0);
+    // loads in flight per thread: all of a layer's partial rows in one round trip
+    auto go = [&](auto kernel) {
+      ps.launch(kernel, dim3(total + 1), dim3(256), 0, tab, tt, ce, m->params, m->adam_m, m->adam_v, set, m->L.part_floats,
+                m->L.act_dim, hp->c_e, 1.0f / (float)rows, adam_scalars(hp, k), m->shadow, stats_out, grad_out, do_update ? 1 : 0);
+    };
+    int deep = 0;
+    for (int i = 0; i < n; ++i)
+      for (int l = 0; l < tab.n; ++l) deep = std::max<int>(deep, parts[i].split.n[l]);
+    if (deep <= 16) go(adam_shadow_kernel<4>);
+    else if (deep <= 32) go(adam_shadow_kernel<8>);
+    else if (deep <= 48) go(adam_shadow_kernel<12>);
+    else go(adam_shadow_kernel<24>);
     GMI_LAUNCH_CHECK();
     return GMI_OK;
   }
