@@ -37,6 +37,7 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
 
 constexpr int kNT = 512, kNW = 8;
+constexpr int kTouchLayers = 4;
 constexpr int kMaxLayers = GMI_MAX_HIDDEN + 1;
 constexpr size_t kLdsMax = 160 * 1024;
 constexpr int kDzStride = 32 + 8;           // head gradient rows
@@ -292,6 +293,17 @@ __global__ __launch_bounds__(kNT) void train_resident_kernel(ResArgs a) {
   request(g, wave);
   // sample of row tid of the present tile (rows past the batch take its last sample; their gradient is zero)
   int sample = tid < R ? a.idx[min((int)blockIdx.x * R + tid, a.rows - 1)] : 0;
+  // One word of each of the weights' 128-byte lines (the first kNT of a matrix), so that they are on their way to the die's cache while the
+  // rows are: Adam has just written them, and every layer's products waited for them from beyond it.
+  // (45:128:128:12, us per iteration 665 without, 658 with.)
+  uint32_t touched[kTouchLayers][2];
+#pragma unroll
+  for (int i = 0; i < kTouchLayers; ++i) {
+    const ResLayer& L = N.l[min(i, nl - 1)];
+    const int line = min(tid, (L.K * L.F >> 6) - 1);
+    touched[i][0] = reinterpret_cast<const uint32_t*>(L.wf)[32 * line];
+    touched[i][1] = reinterpret_cast<const uint32_t*>(i > 0 ? L.wtf : L.wf)[32 * line];
+  }
   for (int tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
     const int r0 = tile * R;
     if (tid < R) s_slot[tid] = (int64_t)(sample / a.n_envs) * a.ld_envs + (sample % a.n_envs);
@@ -353,6 +365,8 @@ __global__ __launch_bounds__(kNT) void train_resident_kernel(ResArgs a) {
       }
     }
     __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kTouchLayers; ++i) asm volatile("" ::"v"(touched[i][0]), "v"(touched[i][1]));
 
     for (int sg = 0; sg < 2 * nl - 1; ++sg) {
       const int nft = g.F >> 5, nks = g.K >> 4;
