@@ -195,6 +195,7 @@ int launch_train_chain(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_p
   a.x0_ready = (L.obs_dim % 4 == 0 && ((uintptr_t)b->d.obs & 15) == 0) ? 0 : 1;
   a.x16 = b->obs16;
   if (a.x0_ready == 1 && obs16_ready && b->obs16 && idx) a.x0_ready = 2;
+  a.stream = beyond_cache(L, rows) ? 1 : 0;
   a.rows = rows; a.act_dim = L.act_dim;
   a.clip = hp->clip; a.c_v = hp->c_v;
   a.stat_part = m->stat_part;

@@ -96,6 +96,7 @@ struct ChainArgs {
                                                    // floats, in order, that start at any 4-byte address
   const uint16_t* x16;                             // bf16 copy of all observations, [sample index][d[0]] (x0_ready == 2)
   int rows, act_dim;
+  int stream;                                      // host: TileShapeStream
   float clip, c_v;
   float* stat_part;                                // [tiles][kStatStride + act_dim]
   // inference (TileShapeFwd): workgroup row y works on net net0 + y; results of the heads

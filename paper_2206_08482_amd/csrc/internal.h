@@ -80,10 +80,11 @@ __device__ __forceinline__ float elu_f(float z) {
 }
 
 // 16 bytes per lane from base + s_off + lane_off, base and s_off wave-uniform: the address takes no vector instruction and no
-// vector registers beside lane_off.
+// vector registers beside lane_off.  AUX 2: streaming.
+template <int AUX = 0>
 __device__ __forceinline__ uint4 load_uniform(const void* base, int s_off, uint32_t lane_off) {
   const auto v = __builtin_amdgcn_raw_buffer_load_b128(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0xFFFFFFFFu, 0x00020000),
-                                                       lane_off, s_off, 0);
+                                                       lane_off, s_off, AUX);
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
@@ -96,10 +97,11 @@ __device__ __forceinline__ uint4 load_uniform(const void* base, int s_off, uint3
 // s_off goes into the vector offset, not into the instruction's scalar one: the compiler takes a store with a register there to have
 // read its data at once and lets the next instruction overwrite them, and the first word of the data was then sometimes that
 // instruction's (seen in a build of train_tile_kernel with a v_ashrrev right behind the store).  Without one it keeps them apart.
+template <int AUX = 17>
 __device__ __forceinline__ void store_through(void* base, uint32_t off, const uint4& v, int s_off = 0) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   const u32x4 x = {v.x, v.y, v.z, v.w};
-  __builtin_amdgcn_raw_buffer_store_b128(x, __builtin_amdgcn_make_buffer_rsrc(base, 0, 0xFFFFFFFFu, 0x00020000), off + s_off, 0, 17);
+  __builtin_amdgcn_raw_buffer_store_b128(x, __builtin_amdgcn_make_buffer_rsrc(base, 0, 0xFFFFFFFFu, 0x00020000), off + s_off, 0, AUX);
 }
 __device__ __forceinline__ void store_through(void* base, uint32_t off, float x, float y, float z, float w) {
   store_through(base, off, make_uint4(__float_as_uint(x), __float_as_uint(y), __float_as_uint(z), __float_as_uint(w)));
@@ -337,7 +339,7 @@ struct WgradBatch {
 };
 // n_split, chunk: fp32 (of all problems alike); bf16 takes the problems' own.
 int launch_wgrad(gmi_instance* g, int dtype, int rows, int n_split, int chunk, WgradBatch& batch,
-                 float* part, int64_t part_stride);
+                 float* part, int64_t part_stride, bool stream = false);
 
 }  // namespace gmi
 
@@ -466,7 +468,10 @@ namespace gmi {
 static inline int wgrad_tile_count(int pad) { return (pad + 255) / 256; }
 __host__ __device__ static inline int wgrad_tile(int pad) { const int n = (pad + 255) / 256; return ((pad >> 5) + n - 1) / n * 32; }
 static inline int wgrad_tiles(int out_pad, int in_pad) { return wgrad_tile_count(out_pad) * wgrad_tile_count(in_pad); }
-// Row splits per layer of a weight-gradient launch (model.hip).
+// Whether a minibatch's activations and gradients, stored by one kernel and read by the next, are more than the memory-side cache of
+// 256 MB holds: then they go by as streams (TileShapeStream, wgrad_bf16_kernel), else they are found there.
+bool beyond_cache(const ModelLayout& L, int rows);
+// Row splits per layer of a weight-gradient launch (mlp.hip).
 WgradSplits plan_wgrad(const int* out_pad, const int* in_pad, int n);
 constexpr int kLossBlocksMax = 2048; // workgroups of the loss kernel
 constexpr int kStatRowsMax = 8192;   // rows of per-workgroup loss statistics (one more row holds their sum)

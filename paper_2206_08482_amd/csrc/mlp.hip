@@ -377,6 +377,7 @@ constexpr int kWgradOperand = kWgradT * kWgradRows * 2; // bytes
 constexpr int kWgradStage = 2 * kWgradOperand;
 constexpr int kWgradRing = 5;
 constexpr int kWgradLds = kWgradRing * kWgradStage;
+constexpr int64_t kCacheBytes = (int64_t)240 << 20;      // beyond_cache: the rest of the 256 MB for weights, rows and partial gradients
 constexpr int kWgradGroups = 256, kSplitMin = 4, kSplitMax = 64, kWgradNarrow = 224;      // plan_wgrad
 __device__ const uint4 g_zero_piece = {0, 0, 0, 0};     // what rows past the end load
 
@@ -395,19 +396,22 @@ __device__ __forceinline__ void load_to_lds(const void* base, uint32_t off, uint
 __device__ __forceinline__ void load_to_lds(const void* src, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "m0", "memory");
 }
-// Four of the first kind, from base + off[k] to lds + 1024 k.
+// Four of the first kind, from base + off[k] to lds + 1024 k; STREAM: streaming loads.
+template <bool STREAM>
 __device__ __forceinline__ void load4_to_lds(const void* base, const uint32_t (&off)[4], uint32_t lds) {
-  asm volatile(
-      "s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %5\n\t"
-      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %5\n\t"
-      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %5\n\t"
-      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %5" ::"s"(lds), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]),
-      "s"(base) : "m0", "scc", "memory");
+#define GMI_LOAD4_TO_LDS(NT)                                                                                                       \
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %5" NT "\n\t"                                            \
+               "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %5" NT "\n\t"                                     \
+               "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %5" NT "\n\t"                                     \
+               "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %5" NT                                            \
+               ::"s"(lds), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base) : "m0", "scc", "memory")
+  if constexpr (STREAM) GMI_LOAD4_TO_LDS(" nt"); else GMI_LOAD4_TO_LDS("");
+#undef GMI_LOAD4_TO_LDS
 }
 #pragma clang diagnostic pop
 
-// LAYOUT: 0 both operands row-major, 1 both in the block layout of the row-tile trainer kernel.
-template <int LAYOUT>
+// LAYOUT: 0 both operands row-major, 1 both in the block layout of the row-tile trainer kernel; STREAM (blocks): beyond_cache.
+template <int LAYOUT, bool STREAM>
 __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, int rows, float* __restrict__ part, int64_t part_stride) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   // workgroup -> (entry, split and net, tile): the tiles of a split read the same rows, so they belong on one die (ids go round-robin
@@ -476,7 +480,7 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
     put = put == lds_w + (kWgradRing - 1) * kWgradStage ? lds_w : put + kWgradStage;
     if constexpr (LAYOUT == 1) {
       const char* base = opnd + ((((int64_t)(r0 >> 7) * nks_op + (f0 >> 4) + j0) * 4 + ((r0 >> 5) & 3)) << 10);
-      if (n_ld > 0) load4_to_lds(base, voff, dst);
+      if (n_ld > 0) load4_to_lds<STREAM>(base, voff, dst);
     } else if (r0 + kWgradRows <= row_end) {
       const char* base = opnd + (int64_t)(r0 + 2 * j0) * ld * 2;
 #pragma unroll
@@ -846,6 +850,19 @@ int launch_linear(gmi_instance* g, int dtype, int epi, int rows, const LinearBat
   }
 }
 
+bool beyond_cache(const ModelLayout& L, int rows) {
+  int64_t n = 0;
+  bool shared = false;
+  for (int net = 0; net < 2; ++net)
+    for (const LayerInfo& li : L.net[net]) {
+      n += li.in_pad + li.out_pad;
+      shared = shared || wgrad_tiles(li.out_pad, li.in_pad) >= 4;
+    }
+  // Matrices of four tiles and more, which read the same rows through the die's cache, lose more by the streams: us per iteration without /
+  // with them, 211:512:512:256:128:20, 24576 rows (302 MB) 2838 / 2890, 32768 (403 MB) 12684 / 12626, 65536 3062 / 3040.
+  return 2 * n * rows > (shared ? kCacheBytes / 2 * 3 : kCacheBytes);
+}
+
 // Splits of each layer's rows such that its workgroups read about as much as any other's: as many workgroups in all as keep the
 // launch in one round of one per compute unit.  A workgroup's time goes by the bytes of its rows, its tile's features of both operands
 // (a stage of few features is bound by the round trip instead: kWgradNarrow), and with the same splits for all layers the launch
@@ -880,7 +897,7 @@ WgradSplits plan_wgrad(const int* out_pad, const int* in_pad, int n) {
 }
 
 int launch_wgrad(gmi_instance* g, int dtype, int rows, int n_split, int chunk, WgradBatch& b, float* part,
-                 int64_t part_stride) {
+                 int64_t part_stride, bool stream) {
   if (b.n <= 0) return GMI_OK;
   ProfScope ps(g, kClsWgrad);
   {
@@ -923,13 +940,12 @@ int launch_wgrad(gmi_instance* g, int dtype, int rows, int n_split, int chunk, W
     else if (p.out_pad == q.out_pad && p.in_pad == q.in_pad && p.n_split == q.n_split && p.chunk == q.chunk) entry(i, i + half, 2);
     else { entry(i, i, 1); entry(i + half, i + half, 1); }
   }
-  static DeviceSet allowed[2];
-  const int layout = b.p[0].dz_blocks ? 1 : 0;
-  const void* kernel = layout ? (const void*)wgrad_bf16_kernel<1> : (const void*)wgrad_bf16_kernel<0>;
-  const int rc = allow_lds(kernel, kWgradLds, g->device, &allowed[layout]);
+  static DeviceSet allowed[3];
+  const int variant = b.p[0].dz_blocks ? (stream ? 2 : 1) : 0;
+  const auto kernel = variant == 2 ? wgrad_bf16_kernel<1, true> : variant == 1 ? wgrad_bf16_kernel<1, false> : wgrad_bf16_kernel<0, false>;
+  const int rc = allow_lds((const void*)kernel, kWgradLds, g->device, &allowed[variant]);
   if (rc != GMI_OK) return rc;
-  if (layout) ps.launch(wgrad_bf16_kernel<1>, dim3(total), dim3(512), kWgradLds, b, rows, part, part_stride);
-  else ps.launch(wgrad_bf16_kernel<0>, dim3(total), dim3(512), kWgradLds, b, rows, part, part_stride);
+  ps.launch(kernel, dim3(total), dim3(512), kWgradLds, b, rows, part, part_stride);
   GMI_LAUNCH_CHECK();
   return GMI_OK;
 }

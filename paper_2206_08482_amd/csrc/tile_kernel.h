@@ -55,6 +55,7 @@ struct TileShape {
   static constexpr bool fp8 = false;      // TileShapeFp8
   static constexpr bool lp_blocks = false;      // log-densities by blocks of four actions
   static constexpr bool keep = false;      // TileShapeKeep
+  static constexpr int store_aux = 17;      // write-through
   // Two waves of the workgroup on a SIMD: the first four take the matrix unit first and are done with the k loop while the others
   // are half way; a layer's results then wait in registers for the barrier behind which they may replace its input, so that the first
   // waves' epilogue runs under the others' products.  (32768 rows of 211:512:512:256:128:20 184 us, 176 so.  With waves of two
@@ -116,6 +117,15 @@ struct TileShapeKeep : TileShape<ROWS, DIMS...> {
   static constexpr size_t lds_bytes() { return B::lds_bytes() - B::x_bytes() + x_bytes(); }
 };
 constexpr size_t kKeepBytes = 80 * 1024;
+
+// The same with streaming stores (write-through either way), for minibatches whose activations no cache holds until they are read.  us per
+// iteration, with the weight gradients' streaming loads, without / with: 65536 rows of 108:400:200:100:21 1601 / 1464 (two epochs), 45056 1645
+// / 1581, 32768 3160 / 3222, 16384 1600 / 1758; 60:256:128:64:8 65536 953 / 885, 32768 619 / 664.  Not for the 512-wide shapes (24576 rows of
+// 211:512:512:256:128:20 2730 / 2813), whose weight gradients alone stream: 32768 12460 / 12300.
+template <class B>
+struct TileShapeStream : B {
+  static constexpr int store_aux = 19;
+};
 
 // The same shape for inference: the walk ends after the heads, nothing is stored for the weight gradients, and the
 // heads' results go out as policy means and values (the products and their order are the trainer's forward pass).
@@ -357,10 +367,15 @@ __device__ __forceinline__ void read_x(Ctx<S>& c) {
 __device__ __forceinline__ int64_t block_word(int tr, int nks, int ks, int rt) { return (((int64_t)tr * nks + ks) * 4 + rt) * 64; }
 
 // One block to memory for the weight-gradient kernel.
+template <class S>
 __device__ __forceinline__ void store_block(uint4* blk, uint32_t lane16, const uint4& v, int off = 0) {
-  gmi::store_through(blk, lane16, v, off);
+  gmi::store_through<S::store_aux>(blk, lane16, v, off);
 }
 
+// Streaming loads for them where the weights of the net fill the die's cache (211:512:512:256:128:20, us per iteration without / with: 12450 /
+// 12170; 108:400:200:100:21 3108 / 3160).
+template <class S>
+constexpr int kHAux = S::late_write ? 2 : 0;
 // Stored activations h[layer] of tile T = a * RT + b of this wave (input-gradient epilogue of segment SEG): the
 // lane's own slots of the blocks (2 ft, b) and (2 ft + 1, b), i.e. the values at the positions of its 16 results.
 template <class S, int SEG, int T>
@@ -377,8 +392,8 @@ __device__ __forceinline__ void fetch_h(Ctx<S>& c, const ChainArgs& a) {
       return;
     }
     const uint4* p = reinterpret_cast<const uint4*>(a.h[c.net][G::layer]) + block_word(c.tr, nks, 2 * ft, c.rt0 + first_rt<G>(c) + tb);
-    c.hq[T % (kHPre + 1)][0] = gmi::load_uniform(p, 0, c.lane16);
-    c.hq[T % (kHPre + 1)][1] = gmi::load_uniform(p, 4 * 1024, c.lane16);
+    c.hq[T % (kHPre + 1)][0] = gmi::load_uniform<kHAux<S>>(p, 0, c.lane16);
+    c.hq[T % (kHPre + 1)][1] = gmi::load_uniform<kHAux<S>>(p, 4 * 1024, c.lane16);
   }
 }
 
@@ -409,7 +424,7 @@ __device__ __forceinline__ void aux_op(Ctx<S>& c, const ChainArgs& a) {
     if constexpr (I == G::RT * G::NP) {
       if constexpr (KS % 2 == 0) c.sx = *x_block(c, G::in_area, KS, c.wave);      // the second half of the waves: k step KS + 1
     } else if constexpr (KS % 2 == 1) {
-      store_block(store_x_array<S, SEG>(c, a) + block_word(c.tr, G::NKS, c.wave / S::nrt, c.rt0 + c.wave % S::nrt), c.lane16, c.sx,
+      store_block<S>(store_x_array<S, SEG>(c, a) + block_word(c.tr, G::NKS, c.wave / S::nrt, c.rt0 + c.wave % S::nrt), c.lane16, c.sx,
                   (KS - 1) * 4096);      // arrays hold whole tiles
     }
   }
@@ -665,8 +680,8 @@ __device__ __forceinline__ void loss_epilogue(Ctx<S>& c, const ChainArgs& a, con
   c.X[(S::area(S::NL) + S::nrt + c.wave) * 64 + c.lane] = make_uint4(w[4], w[5], w[6], w[7]);
   {
     uint4* arr = reinterpret_cast<uint4*>(a.dz[c.net][S::NL - 1]);
-    store_block(arr + block_word(c.tr, 2, 0, c.rt0 + c.wave), c.lane16, make_uint4(w[0], w[1], w[2], w[3]));      // arrays hold whole tiles
-    store_block(arr + block_word(c.tr, 2, 1, c.rt0 + c.wave), c.lane16, make_uint4(w[4], w[5], w[6], w[7]));
+    store_block<S>(arr + block_word(c.tr, 2, 0, c.rt0 + c.wave), c.lane16, make_uint4(w[0], w[1], w[2], w[3]));      // arrays hold whole tiles
+    store_block<S>(arr + block_word(c.tr, 2, 1, c.rt0 + c.wave), c.lane16, make_uint4(w[4], w[5], w[6], w[7]));
   }
   }
 }
@@ -840,7 +855,7 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
                    block_word(c.tr, G::F / 16, c.wave / S::nrt, c.rt0 + c.wave % S::nrt);
 #pragma unroll 8
       for (int k2 = 0; k2 < G::F / 16; k2 += 2) {
-        store_block(arr, c.lane16, c.X[(G::out_area + k2 * S::nrt + c.wave) * 64 + c.lane], k2 * 4096);      // arrays hold whole tiles
+        store_block<S>(arr, c.lane16, c.X[(G::out_area + k2 * S::nrt + c.wave) * 64 + c.lane], k2 * 4096);      // arrays hold whole tiles
       }
     }
     run_segment<S, SEG + 1>(c, a);
@@ -1165,6 +1180,7 @@ GMI_TILE_FP8_PART_DECL(0); GMI_TILE_FP8_PART_DECL(1); GMI_TILE_FP8_PART_DECL(2);
     using S = std::conditional_t<K::lds_bytes() <= gmi_tile::kKeepBytes, K, gmi_tile::TileShape<64, __VA_ARGS__>>; \
     if (!gmi_tile::shape_matches<S>(L)) return GMI_ERR_UNSUPPORTED;                               \
     if (rows == 0) return GMI_OK;                                                                 \
+    if (a.stream) return gmi_tile::launch_shape<gmi_tile::TileShapeStream<S>>(g, a, rows, tiles_out, flops, bytes); \
     return gmi_tile::launch_shape<S>(g, a, rows, tiles_out, flops, bytes);                        \
   }
 #define GMI_TILE_WIDE_PART_DEFINE(k, ...)                                                         \
