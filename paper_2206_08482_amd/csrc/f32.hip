@@ -453,7 +453,8 @@ __global__ __launch_bounds__(kNT) void agent_f32_kernel(AgentF32Args a) {
 // ------------------------------------------------------------------------------------------------
 // Minibatch: grid (row-tile groups, nets).  A workgroup takes the row tiles blockIdx.x, + gridDim.x, ...; its weight
 // gradients go to row blockIdx.x of the partials (written for its first tile, accumulated in place for later ones) and
-// its statistics to row blockIdx.x of the statistics partials.
+// its statistics to row blockIdx.x of the statistics partials.  The last tile's gradients are written through: left in the die's cache they
+// have to be written back before the next kernel may start (us per iteration, 17:64:64:6 478 / 448, 37:128:64:12 862 / 807).
 struct TrainF32Args {
   F32Net net[2];
   const float* params;
@@ -508,7 +509,7 @@ __global__ __launch_bounds__(kNT) void train_f32_kernel(TrainF32Args a) {
 
   for (int tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
     const int r0 = tile * R;
-    const bool first = tile == (int)blockIdx.x;
+    const bool first = tile == (int)blockIdx.x, last = tile + (int)gridDim.x >= a.n_tiles;
     if (tid < R) s_slot[tid] = (int64_t)(sample / a.n_envs) * a.ld_envs + (sample % a.n_envs);
     __syncthreads();
     {   // the gather: everything is requested before the first result is stored
@@ -629,7 +630,10 @@ __global__ __launch_bounds__(kNT) void train_f32_kernel(TrainF32Args a) {
           }
 #pragma unroll
           for (int v = 0; v < 4; ++v)
-            if (o + v < L.out && i < L.in) dst[(int64_t)v * L.in] = acc[v];
+            if (o + v < L.out && i < L.in) {
+              if (last) gmi::store_through(dst + (int64_t)v * L.in, acc[v]);
+              else dst[(int64_t)v * L.in] = acc[v];
+            }
           if (it == 0) {
             b += __shfl_xor(b, 16, 64);
             b += __shfl_xor(b, 32, 64);

@@ -106,6 +106,8 @@ __device__ __forceinline__ void store_through(void* base, uint32_t off, const ui
 __device__ __forceinline__ void store_through(void* base, uint32_t off, float x, float y, float z, float w) {
   store_through(base, off, make_uint4(__float_as_uint(x), __float_as_uint(y), __float_as_uint(z), __float_as_uint(w)));
 }
+// One float per lane.
+__device__ __forceinline__ void store_through(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
 
 }  // namespace gmi
 

@@ -630,7 +630,7 @@ int launch_adam(gmi_instance* g, gmi_model* const* ms, int n, const PartRows* pa
     for (int i = tab.n; i <= gmi::kMaxWgradProblems; ++i) tt.start[i] = INT32_MAX;
     gmi::ChainEmit ce;
     gmi::fill_chain_emit(m->L, &ce);
-    // loads in flight per thread: all of a layer's partial rows in one round trip
+    // loads in flight per thread: all of a layer's partial rows in one round trip (up to 96 rows)
     auto go = [&](auto kernel) {
       ps.launch(kernel, dim3(total + 1), dim3(256), 0, tab, tt, ce, m->params, m->adam_m, m->adam_v, set, m->L.part_floats,
                 m->L.act_dim, hp->c_e, 1.0f / (float)rows, adam_scalars(hp, k), m->shadow, stats_out, grad_out, do_update ? 1 : 0);
@@ -641,7 +641,8 @@ int launch_adam(gmi_instance* g, gmi_model* const* ms, int n, const PartRows* pa
     if (deep <= 16) go(adam_shadow_kernel<4>);
     else if (deep <= 32) go(adam_shadow_kernel<8>);
     else if (deep <= 48) go(adam_shadow_kernel<12>);
-    else go(adam_shadow_kernel<24>);
+    else if (deep <= 96) go(adam_shadow_kernel<24>);
+    else go(adam_shadow_kernel<16>);      // two round trips
     GMI_LAUNCH_CHECK();
     return GMI_OK;
   }
