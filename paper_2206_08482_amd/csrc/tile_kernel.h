@@ -80,7 +80,7 @@ struct TileShape {
     for (int i = 0; i < s; ++i) n += cd_seg_blocks(dims(), i);
     return n;
   }
-  // first block of the activation area that holds layer l's input (TileShapeKeep: an area per layer; else they take turns)
+  // first block of the activation area that holds layer l's input (TileShapeKeep: an area per layer; TileShapeTurns: two areas; else one)
   static constexpr int area(int) { return 0; }
   // the loss epilogue's per-wave transposition buffers live in the activation area behind the head layer's input
   static constexpr size_t scr_offset() { return (size_t)dims().d[NL - 1] / 16 * nrt * 1024; }
@@ -156,6 +156,30 @@ struct TileShapeFp8 : TileShape<ROWS, DIMS...> {
     return TileShape<ROWS, DIMS...>::valid() && x_bytes() >= scr_offset() + (size_t)TileShape<ROWS, DIMS...>::nrt * kScrBytes;
   }
 };
+// A forward-only shape with two activation areas that the layers take in turn: a layer's results do not go where its input lies, so one
+// barrier per layer is enough.  The draws wait in the area that is not the heads' input.  For up to 256 wide layers, where a layer is as
+// short as its waits, and launches of at most one workgroup per compute unit (turns).  us per decision of 60:256:128:64:8, without / with: 1
+// row 7.24 / 6.95, 8192 rows 8.01 / 7.75, fp8 6.72 / 6.56 and 7.13 / 6.97; with more workgroups, which cover each other's waits, the larger
+// areas only cost (262144 rows 91.2 / 94.2; 65536 rows of 211:512:512:256:128:20 in fp8 92.4 / 97.5).
+template <class B>
+struct TileShapeTurns : B {
+  static constexpr bool keep = true;
+  static constexpr int turn(int parity) {      // blocks of the area of the even or odd layers' inputs
+    int n = B::NL % 2 == parity ? (B::nrt * kScrBytes + 1023) / 1024 : 0;
+    for (int l = parity; l < B::NL; l += 2) {
+      const int blocks = B::dims().d[l] / (B::fp8 ? 32 : 16) * B::nrt;
+      n = blocks > n ? blocks : n;
+    }
+    return n;
+  }
+  static constexpr int area(int l) { return l % 2 == 0 ? 0 : turn(0); }
+  static constexpr size_t scr_offset() { return (size_t)area(B::NL) * 1024; }
+  static constexpr size_t x_bytes() { return (size_t)(turn(0) + turn(1)) * 1024; }
+  static constexpr size_t lds_bytes() { return B::lds_bytes() - B::x_bytes() + x_bytes(); }
+};
+template <class B>
+using Turns = std::conditional_t<B::maxks() <= 16, TileShapeTurns<B>, B>;
+inline bool turns(const ChainArgs& a, int rows, int cus) { return a.T <= 1 && !a.val_last && 2 * ((rows + 63) / 64) <= cus; }
 // Segments the kernel runs for shape S.
 template <class S>
 constexpr int n_run() { return S::fwd ? S::NL : S::nseg(); }
@@ -494,9 +518,9 @@ __device__ __forceinline__ void write_tile(const Ctx<S>& c, const uint32_t (&w)[
                                // quads 0 and 1 of both, the first block's 16 bytes of its row, the upper one quads 2 and 3
     const auto u = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
     const auto v = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
-    c.X[((ft / 2 * 2 + c.hh) * S::nrt + rt) * 64 + c.s + 32 * (ft & 1)] = make_uint4(u[0], u[1], v[0], v[1]);
+    c.X[(G::out_area + (ft / 2 * 2 + c.hh) * S::nrt + rt) * 64 + c.s + 32 * (ft & 1)] = make_uint4(u[0], u[1], v[0], v[1]);
   } else if constexpr (S::nat) {      // quad q: features 8 (q % 2) + 4 hh .. of k step 2 ft + q / 2
-    char* x = reinterpret_cast<char*>(c.X + ((2 * ft) * S::nrt + rt) * 64 + c.s) + 8 * c.hh;
+    char* x = reinterpret_cast<char*>(c.X + (G::out_area + (2 * ft) * S::nrt + rt) * 64 + c.s) + 8 * c.hh;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       *reinterpret_cast<uint2*>(x + (q / 2) * S::nrt * 1024 + (q % 2) * 512) = make_uint2(w[2 * q], w[2 * q + 1]);
@@ -835,7 +859,7 @@ __device__ __forceinline__ void run_segment(Ctx<S>& c, const ChainArgs& a) {
     }
     issue_first_weights<S, SEG + 1>(c, a);
     prefetch_weights<S, SEG + 1>(c);
-    if constexpr (!S::keep && G::head) __syncthreads();      // every wave is done with the layer's input
+    if constexpr ((!S::keep || S::fwd) && G::head) __syncthreads();      // every wave is done with the layer's input, or has made its draws
     // this lane's loss inputs: cold loads, issued where a long stretch of arithmetic follows and no younger load is
     // waited for (the memory counter is in order)
     if constexpr (!S::fwd && SEG == (S::NL >= 3 ? S::NL - 3 : 0)) fetch_loss_inputs<S>(c, a);
@@ -1164,7 +1188,10 @@ GMI_TILE_FP8_PART_DECL(0); GMI_TILE_FP8_PART_DECL(1); GMI_TILE_FP8_PART_DECL(2);
     using S = gmi_tile::TileShapeFp8<64, __VA_ARGS__>;                                            \
     if (!gmi_tile::shape_matches<S>(L)) return GMI_ERR_UNSUPPORTED;                               \
     int tiles = 0;                                                                                \
-    return rows == 0 ? GMI_OK : gmi_tile::launch_shape<S>(g, a, rows, &tiles, 0.0, 0.0);          \
+    if (rows == 0) return GMI_OK;                                                                 \
+    if (gmi_tile::turns(a, rows, g->cu_count))                                                    \
+      return gmi_tile::launch_shape<gmi_tile::Turns<S>>(g, a, rows, &tiles, 0.0, 0.0);            \
+    return gmi_tile::launch_shape<S>(g, a, rows, &tiles, 0.0, 0.0);                               \
   }
 #define GMI_TILE_FWD_PART_DEFINE(k, SHAPE, ...)                                                   \
   GMI_TILE_FWD_PART_DECL(k) {                                                                     \
@@ -1172,6 +1199,8 @@ GMI_TILE_FP8_PART_DECL(0); GMI_TILE_FP8_PART_DECL(1); GMI_TILE_FP8_PART_DECL(2);
     if (!gmi_tile::shape_matches<S>(L)) return GMI_ERR_UNSUPPORTED;                               \
     *tiles_out = S::nat ? 1 : 0;                                                                  \
     if (rows == 0) return GMI_OK;                                                                 \
+    if (gmi_tile::turns(a, rows, g->cu_count))                                                    \
+      return gmi_tile::launch_shape<gmi_tile::Turns<S>>(g, a, rows, tiles_out, flops, bytes);     \
     return gmi_tile::launch_shape<S>(g, a, rows, tiles_out, flops, bytes);                        \
   }
 #define GMI_TILE_PART_DEFINE(k, ...)                                                              \

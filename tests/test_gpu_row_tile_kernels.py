@@ -309,6 +309,36 @@ def test_narrow_row_tile_decisions_are_those_of_the_agent_kernel(g, inst, dtype,
         assert np.isfinite(a).all() and np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("obs,act", [(60, 8), (24, 3), (23, 31)])
+def test_narrow_row_tile_decisions_with_one_and_with_two_activation_areas(g, inst, dtype, obs, act):
+    """A launch of at most one workgroup per compute unit takes its layers through two areas in turn, a larger one through one: the rows
+    that both decide are the same bit for bit."""
+    hidden, dev = [256, 128, 64], torch.device("cuda:0")
+    few = 32 * torch.cuda.get_device_properties(0).multi_processor_count
+    theta = torch.tensor(syn.make_model_params(obs, act, hidden, 5, policy_head_scale=0.5), device=dev)
+    x = torch.randn(few + 1, obs, generator=torch.Generator().manual_seed(3)).to(dev)
+    out = []
+    for n in (few, few + 1):
+        desc = g.model_desc(obs, act, hidden, g.dtype_code("bf16"), n)
+        r = [torch.full(s, float("nan"), device=dev) for s in ((n, act), (n,), (n,), (n, act))]
+        shadow = torch.zeros(g.gmi_model_shadow_bytes(desc), dtype=torch.uint8, device=dev)
+        torch.cuda.synchronize()
+        if dtype == "fp8":
+            model = g.gmi_fp8_bind(inst, desc)
+            g.gmi_fp8_refresh(inst, model, theta)
+            g.agent_act_fp8(inst, model, x, n, 42, 9, 100, *r)
+        else:
+            model = g.gmi_model_bind(inst, desc, theta, shadow)
+            g.gmi_model_refresh_shadow(inst, model)
+            g.agent_act(inst, model, x, n, 42, 9, 100, *r)
+        g.gmi_sync(inst)
+        (g.gmi_fp8_destroy if dtype == "fp8" else g.gmi_model_destroy)(model)
+        out.append([v.cpu().numpy() for v in r])
+    for a, b in zip(*out):
+        assert np.isfinite(b).all() and np.array_equal(a, b[:few])
+
+
 @pytest.mark.parametrize("obs,act,hidden,n", [
     (211, 20, [512, 512, 256, 128], 32769),   # 128 rows on 16 waves
     (60, 8, [256, 128, 64], 32801),           # two 128-row tiles per compute unit
