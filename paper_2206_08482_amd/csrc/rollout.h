@@ -343,6 +343,15 @@ __device__ __forceinline__ int fresh(int v) {
   return v;
 }
 
+// Groups of four k that a simulator wave reads before the actions are there: the two behind the state's part, and the ragged one
+// (0 where there is none).  A row has a group behind its whole ones only where O + A is ragged: past the last one that one is read
+// again, not used.
+struct SimGroups { int g0, g1, gt; };
+__host__ __device__ __forceinline__ SimGroups sim_groups_ahead(int O, int A) {
+  const int gs = O >> 2, ng = (O + A) >> 2, rem = (O + A) & 3, last = rem ? ng : ng - 1;
+  return {gs < last ? gs : last, gs + 1 < last ? gs + 1 : last, rem ? ng : 0};
+}
+
 // What a simulator wave has of an item before the actions are there: the state's part of the sums and the other operands.
 struct SimItem {
   SimLane sl;
@@ -367,7 +376,8 @@ __device__ __forceinline__ void sim_wave_steps(const RolloutEnv& a, const SplitA
 #pragma unroll 1
   for (int t = 0; t <= a.T; ++t, slot0 += a.ld_envs) {
     const int O = fresh(a.obs_dim), A = fresh(a.act_dim), OA = O + A, nbo = (O + 3) >> 2, nba = (A + 3) >> 2, npr = nba + nbo + 1;
-    const int gs = O >> 2, ng = OA >> 2, rem = OA & 3, gt = rem ? ng : 0, left = fresh(a.n - r0);
+    const int gs = O >> 2, ng = OA >> 2, rem = OA & 3, left = fresh(a.n - r0);
+    const SimGroups ahead = sim_groups_ahead(O, A);
     const float* s_in = s.in2 + (t & 1) * 16 * OS;
     const float4* s_noise = s.noise2 + (t & 1) * 16 * npr;
     const bool step = t < a.T;
@@ -385,9 +395,9 @@ __device__ __forceinline__ void sim_wave_steps(const RolloutEnv& a, const SplitA
     };
     auto operands = [&](SimItem& it) {      // what does not wait for the actions
       const float* mp = mr + it.sl.m_off;
-      it.m0 = *reinterpret_cast<const float4*>(mp + 4 * min(gs, ng));
-      it.m1 = *reinterpret_cast<const float4*>(mp + 4 * min(gs + 1, ng));
-      it.mt = *reinterpret_cast<const float4*>(mp + 4 * gt);
+      it.m0 = *reinterpret_cast<const float4*>(mp + 4 * ahead.g0);
+      it.m1 = *reinterpret_cast<const float4*>(mp + 4 * ahead.g1);
+      it.mt = *reinterpret_cast<const float4*>(mp + 4 * ahead.gt);
       it.zn = s_noise[it.sl.r * npr + nba + min(it.sl.blk, nbo - 1)];
       it.done = s.done[it.sl.r];
     };
@@ -418,8 +428,8 @@ __device__ __forceinline__ void sim_wave_steps(const RolloutEnv& a, const SplitA
       int dones = 0;
       auto finish = [&](SimItem& it) {
         const float* xp = s_in + it.sl.x_off;
-        const float4 x0 = *reinterpret_cast<const float4*>(xp + 4 * min(gs, ng)), x1 = *reinterpret_cast<const float4*>(xp + 4 * min(gs + 1, ng));
-        const float4 xt = *reinterpret_cast<const float4*>(xp + 4 * gt);
+        const float4 x0 = *reinterpret_cast<const float4*>(xp + 4 * ahead.g0), x1 = *reinterpret_cast<const float4*>(xp + 4 * ahead.g1);
+        const float4 xt = *reinterpret_cast<const float4*>(xp + 4 * ahead.gt);
         auto step4 = [&](const float4& mv, const float4& xv) {
           it.acc = __builtin_amdgcn_mfma_f32_4x4x1f32(mv.x, xv.x, it.acc, 0, 0, 0);
           it.acc = __builtin_amdgcn_mfma_f32_4x4x1f32(mv.y, xv.y, it.acc, 0, 0, 0);

@@ -9,6 +9,7 @@
 
 #include "../../include/gmidrl.h"
 #include "../../paper_2206_08482_amd/csrc/internal.h"
+#include "../../paper_2206_08482_amd/csrc/rollout.h"
 
 static int fails = 0;
 #define CHECK(c) do { if (!(c)) { std::printf("FAILED %s:%d: %s\n", __FILE__, __LINE__, #c); ++fails; } } while (0)
@@ -81,6 +82,21 @@ int main() {
     for (int i = 0; i < 8; ++i) ts.emplace_back([&done, i]() { for (int d = i; d < 64; d += 8) done.add(d); });
     for (std::thread& t : ts) t.join();
     for (int d = 0; d < 64; ++d) CHECK(done.has(d));
+  }
+  {
+    // a collection's simulator waves read inside every row of the matrix (the last one ends where the allocation does) and of the
+    // states, and every group of the product that they do not take in order is among the ones read ahead
+    int outside = 0, missed = 0;
+    for (int O = 1; O <= 700; ++O)
+      for (int A = 1; A <= 64; ++A) {
+        const SimGroups s = sim_groups_ahead(O, A);
+        const int last = (s.g0 > s.g1 ? s.g0 : s.g1) > s.gt ? (s.g0 > s.g1 ? s.g0 : s.g1) : s.gt;
+        outside += 4 * last + 4 > ((O + A + 3) & ~3) || 4 * last + 4 > gmi::env_row_stride(O, A) || 4 * last + 4 > split_stride(O, A);
+        const int gs = O / 4, ng = (O + A) / 4;
+        missed += (gs < ng && s.g0 != gs) || (gs + 1 < ng && s.g1 != gs + 1) || ((O + A) % 4 && s.gt != ng);
+      }
+    CHECK(outside == 0);
+    CHECK(missed == 0);
   }
   std::printf(fails ? "host checks: %d failed\n" : "host checks passed\n", fails);
   return fails ? 1 : 0;

@@ -674,6 +674,7 @@ def test_fp32_collection_at_the_edges_of_its_layout(g, obs, act, hidden, n):
     (3, 24, [64, 33, 16], 70, 3, 8),           # more blocks of actions than of states; two heads' tiles; one workgroup per tile
     (130, 9, [16, 16], 40, 3, None),           # nine state tiles: a simulator wave has three
     (256, 24, [16], 18, 2, None),              # the simulator's matrix in memory
+    (128, 4, [64], 21, 3, None),               # so too, its rows without padding, one product behind the state's: the last one
     (6, 2, [64, 64], 300, 5, 8),               # nineteen tiles on eight compute units; two products behind the state's
 ])
 def test_fp32_collection_with_the_roles_on_waves_of_their_own(g, obs, act, hidden, n, T, cus):
