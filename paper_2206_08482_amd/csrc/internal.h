@@ -473,6 +473,9 @@ static inline int wgrad_tiles(int out_pad, int in_pad) { return wgrad_tile_count
 // Whether a minibatch's activations and gradients, stored by one kernel and read by the next, are more than the memory-side cache of
 // 256 MB holds: then they go by as streams (TileShapeStream, wgrad_bf16_kernel), else they are found there.
 bool beyond_cache(const ModelLayout& L, int rows);
+// Sums over the rows that a wave of wgrad_bf16_kernel forms of each result: two where its tiles, at most four of 32 x 32, leave half of its
+// accumulators over.
+__host__ __device__ static inline int wgrad_sums(int out_pad, int in_pad) { return wgrad_tile(out_pad) > 128 && wgrad_tile(in_pad) > 128 ? 1 : 2; }
 // Row splits per layer of a weight-gradient launch (mlp.hip).
 WgradSplits plan_wgrad(const int* out_pad, const int* in_pad, int n);
 constexpr int kLossBlocksMax = 2048; // workgroups of the loss kernel

@@ -563,7 +563,7 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
   }
 
   floatx16 acc[4][2];
-  float sum[2] = {0.f, 0.f};
+  float sum[2][2] = {{0.f, 0.f}, {0.f, 0.f}};      // of a stage's two steps
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -600,17 +600,25 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
       for (int t = 0; t < NB; ++t) q.b[t] = operand(zb[t] + o, zb4[t] + o);
       return q;
     };
-    auto multiply = [&](const Operands& q) {
+    // Two sums over the rows, of the even and the odd steps, where the accumulators allow it (wgrad_sums): the layers of small tiles have
+    // fewer splits (plan_wgrad).
+    constexpr bool kTwo = NX < 2 || NZ <= 2;
+    auto second = [&](int i, int j) -> floatx16& { return NX < 2 ? acc[i][1] : acc[i + 2 & 3][j]; };
+    auto multiply = [&](const Operands& q, auto step) {
+      constexpr int K = decltype(step)::value;
 #pragma unroll
       for (int i = 0; i < NZ; ++i)
 #pragma unroll
-        for (int j = 0; j < NX; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q.z[i], q.x[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < NX; ++j) {
+          floatx16& a = kTwo && K ? second(i, j) : acc[i][j];
+          a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q.z[i], q.x[j], a, 0, 0, 0);
+        }
 #pragma unroll
       for (int t = 0; t < NB; ++t)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const bf2 v = {q.b[t][2 * e], q.b[t][2 * e + 1]};
-          sum[t] = __builtin_amdgcn_fdot2_f32_bf16(v, one, sum[t], false);
+          sum[t][K] = __builtin_amdgcn_fdot2_f32_bf16(v, one, sum[t][K], false);
         }
     };
     // the reads of the next step between the products of this one: a wave issues in order, and a product keeps the matrix
@@ -632,13 +640,13 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
       const int off1 = off == (kWgradRing - 1) * kWgradStage ? 0 : off + kWgradStage;
       if constexpr (NZ > 0) {
         const Operands nxt = read(off, 1);
-        multiply(cur);
+        multiply(cur, std::integral_constant<int, 0>{});
         interleave();
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (decltype(more)::value) issue(s + kAhead);      // behind products that are on their way
         __builtin_amdgcn_sched_barrier(0);
         cur = read(s + 1 < nst ? off1 : off, 0);
-        multiply(nxt);
+        multiply(nxt, std::integral_constant<int, 1>{});
         interleave();
         __builtin_amdgcn_sched_barrier(0);
       } else {
@@ -656,6 +664,11 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
       asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
       stage(s, std::false_type{});
     }
+    if constexpr (kTwo)
+#pragma unroll
+      for (int i = 0; i < NZ; ++i)
+#pragma unroll
+        for (int j = 0; j < NX; ++j) acc[i][j] += second(i, j);
   };
   if (nst > 0) {
     for (int s = 0; s < min(kAhead, nst); ++s) issue(s);
@@ -699,7 +712,7 @@ __global__ __launch_bounds__(512) void wgrad_bf16_kernel(gmi::WgradBatch batch, 
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     if (t >= n_bias) break;
-    const float b = sum[t] + __shfl_xor(sum[t], 32, 64);      // the other half of the rows
+    const float h = sum[t][0] + sum[t][1], b = h + __shfl_xor(h, 32, 64);      // the other half of the rows
     if (lane < 32) dst[P.b_off + 32 * ((o0 >> 5) + ot0 + wi + t * na) + lane] = b;
   }
 }
@@ -865,19 +878,23 @@ bool beyond_cache(const ModelLayout& L, int rows) {
 // Splits of each layer's rows such that its workgroups read about as much as any other's: as many workgroups in all as keep the
 // launch in one round of one per compute unit.  A workgroup's time goes by the bytes of its rows, its tile's features of both operands
 // (a stage of few features is bound by the round trip instead: kWgradNarrow), and with the same splits for all layers the launch
-// took as long as the widest tile's.
+// took as long as the widest tile's.  No layer forms fewer partial sums of its rows (splits times wgrad_sums) than the same splits for all would:
+// each addition rounds.  Error of the weights' gradients against 64-bit sums, root mean square over the tensors, 32768 rows as collected, with
+// the same splits / per layer, one sum each / as it is: 60:256:128:64:8 7.7e-8 / 7.6e-8 / 6.5e-8, 108:400:200:100:21 1.13e-7 / 1.15e-7 / 0.94e-7,
+// 211:512:512:256:128:20 1.57e-7 / 1.64e-7 / 1.41e-7 (its policy head 1.5 times as far off with one sum).
 WgradSplits plan_wgrad(const int* out_pad, const int* in_pad, int n) {
   WgradSplits r = {};
-  int tiles[kMaxWgradProblems], feats[kMaxWgradProblems], used = 0;
+  int tiles[kMaxWgradProblems], feats[kMaxWgradProblems], all = 0, used = 0;
   for (int i = 0; i < n; ++i) {
     tiles[i] = wgrad_tiles(out_pad[i], in_pad[i]);
     feats[i] = std::max(wgrad_tile(out_pad[i]) + wgrad_tile(in_pad[i]), kWgradNarrow);
-    used += tiles[i] * kSplitMin;
+    all += tiles[i];
   }
-  for (int i = 0; i < n; ++i) r.n[i] = kSplitMin;
-  if (used > kWgradGroups) {
-    for (int i = 0; i < n; ++i) r.n[i] = 2 * kSplitMin;
-    return r;
+  // the same for all, in fours
+  const int same = std::min(std::max(kWgradGroups / all / 4 * 4, 2 * kSplitMin), kSplitMax / 2);
+  for (int i = 0; i < n; ++i) {
+    r.n[i] = same / wgrad_sums(out_pad[i], in_pad[i]);
+    used += tiles[i] * r.n[i];
   }
   for (;;) {
     int most = 0;

@@ -98,6 +98,23 @@ int main() {
     CHECK(outside == 0);
     CHECK(missed == 0);
   }
+  {
+    // a weight gradient's rows: at least as many partial sums for every layer as the same number of splits for all would give, and
+    // no more workgroups than one per compute unit where that is possible
+    const int shapes[][6] = {{64, 256, 128, 64, 32, 0},    {128, 416, 224, 128, 32, 0},  {224, 512, 512, 256, 128, 32}, {224, 512, 512, 512, 256, 32},
+                             {256, 512, 512, 512, 512, 32}, {224, 512, 416, 416, 320, 32}, {64, 416, 320, 32, 0, 0},      {32, 320, 224, 64, 32, 0},
+                             {32, 32, 32, 0, 0, 0},        {160, 512, 512, 320, 320, 32}, {320, 1120, 1120, 64, 32, 0},  {256, 256, 192, 192, 32, 0}};
+    for (const auto& s : shapes) {
+      int out[12], in[12], n = 0, tiles = 0, groups = 0;
+      for (int net = 0; net < 2; ++net)
+        for (int l = 0; l < 5 && s[l + 1]; ++l) { out[n] = s[l + 1]; in[n++] = s[l]; }
+      const gmi::WgradSplits p = gmi::plan_wgrad(out, in, n);
+      for (int i = 0; i < n; ++i) { tiles += gmi::wgrad_tiles(out[i], in[i]); groups += gmi::wgrad_tiles(out[i], in[i]) * p.n[i]; }
+      const int even = 256 / tiles / 4 * 4, same = even < 8 ? 8 : even > 32 ? 32 : even;
+      for (int i = 0; i < n; ++i) CHECK(p.n[i] * gmi::wgrad_sums(out[i], in[i]) >= same);
+      CHECK(groups <= 256 || tiles > 32);
+    }
+  }
   std::printf(fails ? "host checks: %d failed\n" : "host checks passed\n", fails);
   return fails ? 1 : 0;
 }

@@ -24,7 +24,7 @@ def test_host_logic_under_address_and_undefined_behaviour_sanitizers(tmp_path):
     cmd = [_hipcc(), "--offload-arch=gfx950", "-O1", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
            "-packed-fp32-ops", "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
            "-Xarch_host", "-fno-sanitize-recover=undefined", "-Xarch_host", "-fno-omit-frame-pointer",
-           os.path.join(CSRC, "select.hip"), os.path.join(CSRC, "core.hip"), os.path.join(CSRC, "channels.hip"),
+           os.path.join(CSRC, "select.hip"), os.path.join(CSRC, "core.hip"), os.path.join(CSRC, "channels.hip"), os.path.join(CSRC, "mlp.hip"),
            os.path.join(ROOT, "tests", "host", "sanitize_host.cpp"), "-o", exe]
     build = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
     assert build.returncode == 0, build.stderr[-3000:]
