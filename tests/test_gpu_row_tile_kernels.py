@@ -79,6 +79,37 @@ def test_gradient_equals_the_per_layer_kernels(g, inst, obs, act, hidden, dtype,
     g.gmi_model_destroy(model)
 
 
+@pytest.mark.parametrize("obs,act,hidden,rows", [
+    (60, 8, (256, 128, 64), 63501),              # activations kept in LDS, 252 MB of them stored
+    (108, 21, (400, 200, 100), 37201),           # read back from memory, 252 MB
+    (211, 20, (512, 512, 256, 128), 30001),      # 369 MB: the weight gradients alone stream
+])
+def test_gradient_of_minibatches_that_no_cache_holds(g, inst, obs, act, hidden, rows):
+    """Beyond the memory-side cache activations and gradients are stored and read as streams.  The second of two minibatches, which finds the
+    first one's lines wherever they were left, against the per-layer kernels; the band as above (same roundings, other order of sums)."""
+    model, buf, keep = _setup(g, inst, obs, act, hidden, "bf16", 2, rows // 2 + 200, rows)
+    n, total = keep[0].numel(), 2 * (rows // 2 + 200)
+    hp = g.ppo_hparams(clip=0.2, c_v=0.5, c_e=0.01, minibatch=rows)
+    idx = [torch.tensor(np.random.default_rng(s).permutation(total)[:rows].astype(np.int32), device="cuda:0") for s in (1, 2)]
+    out = []
+    for fused in (1, 0):
+        grads, stats = [torch.zeros(n, device="cuda:0") for _ in idx], torch.zeros(5, device="cuda:0")
+        torch.cuda.synchronize()
+        g.gmi_set_fusion(inst, fused)
+        for i, gr in zip(idx, grads):
+            g.ppo_gradient(inst, model, buf, hp, i, rows, gr, stats)
+        g.gmi_sync(inst)
+        out.append(([v.cpu().numpy() for v in grads], stats.cpu().numpy()))
+    g.gmi_set_fusion(inst, 1)
+    (a, sa), (b, sb) = out
+    assert all(np.isfinite(v).all() for v in a) and not np.array_equal(a[0], a[1])
+    for x, y in zip(a, b):
+        assert rel_l2(x, y) <= 5e-3 and rel_max(x, y) <= 2e-2, (rel_l2(x, y), rel_max(x, y))
+    assert np.allclose(sa, sb, rtol=5e-3, atol=5e-3)
+    g.gmi_buffer_destroy(buf)
+    g.gmi_model_destroy(model)
+
+
 @pytest.mark.parametrize("obs,hidden", [(211, (512, 512, 256, 128)), (108, (400, 200, 100))])
 @pytest.mark.parametrize("act", [1, 2, 3, 4, 5, 7, 31, 32])
 @pytest.mark.parametrize("rows", [1, 3, 301])
