@@ -203,8 +203,9 @@ int launch_train_chain(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_p
   if (rows < 1 || rows > m->max_rows) return GMI_ERR_UNSUPPORTED;      // the activation arrays hold max_rows (in whole tiles)
   // algorithmic work at the logical (unpadded) widths: forward products of every layer, input-gradient products
   // of every layer but the first; bytes: the input rows and per-sample scalars read, every hidden activation
-  // written once and read once (ELU'), every layer's output gradient written once, the weights read once
+  // written once (and read once for ELU': reread), every layer's output gradient written once, the weights read once
   double flops = 0.0, bytes = 0.0;
+  a.reread = 0.0;
   for (int net = 0; net < 2; ++net) {
     for (int l = 0; l < L.n_layers; ++l) {
       const LayerInfo& li = L.net[net][l];
@@ -214,7 +215,7 @@ int launch_train_chain(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_p
       // fp32 observation rows read and the bf16 copy written (once), or the gathered bf16 rows read, or those read
       // from the copy of all observations and written in minibatch order
       if (l == 0) bytes += net == 0 ? (a.x0_ready == 1 ? 2.0 : (a.x0_ready == 2 ? 4.0 : 6.0)) * rows * li.in : 0.0;
-      else bytes += 2.0 * 2.0 * rows * li.in;                                // hidden activation: written, read back
+      else bytes += 2.0 * rows * li.in, a.reread += 2.0 * rows * li.in;      // hidden activation
     }
   }
   bytes += 4.0 * rows * (L.act_dim + 3);

@@ -115,6 +115,8 @@ struct ChainArgs {
   float* val_out;                                  // [rows] values
   uint16_t* x0b;                                   // the minibatch's observations as the first layer's operand blocks, written here for
                                                    // the weight-gradient kernel (by the policy net's workgroups)
+  double reread;                                   // host: bytes of hidden activations that the backward pass reads again from memory
+                                                   // unless they stay in LDS (TileShapeKeep)
 };
 
 }  // namespace gmi_chain

@@ -1136,7 +1136,7 @@ int launch_shape(gmi_instance* g, ChainArgs a, int rows, int* tiles_out, double 
   int rc = gmi::allow_lds((const void*)train_tile_kernel<S>, lds, g->device, &allowed);
   if (rc != GMI_OK) return rc;
   gmi::ProfScope ps(g, S::fwd ? gmi::kClsFusedAgent : gmi::kClsChainTrain);
-  ps.work(flops, bytes);
+  ps.work(flops, bytes + (S::fwd || S::keep ? 0.0 : a.reread));
   if constexpr (S::fwd) {
     a.slot_tiles = tiles;
     a.items = tiles * (a.T + (a.val_last ? 1 : 0));

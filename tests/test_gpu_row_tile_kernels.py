@@ -110,6 +110,25 @@ def test_gradient_of_minibatches_that_no_cache_holds(g, inst, obs, act, hidden, 
     g.gmi_model_destroy(model)
 
 
+@pytest.mark.parametrize("obs,act,hidden,reads_back", [(60, 8, (256, 128, 64), False), (108, 21, (400, 200, 100), True)])
+def test_stated_bytes_count_activations_read_back_where_they_are(g, inst, obs, act, hidden, reads_back):
+    rows = 512
+    model, buf, keep = _setup(g, inst, obs, act, hidden, "bf16", 2, rows // 2, rows)
+    cls = [g.gmi_profile_class_name(c) for c in range(g.gmi_profile_classes())].index("chain_train")
+    g.gmi_profile_enable(inst, 1 << cls)
+    _gradients(g, inst, model, buf, keep[0].numel(), 2, rows // 2, rows, 1)
+    launches, stated = g.gmi_profile_read(inst, cls)[1], g.gmi_profile_work(inst, cls)[1]
+    g.gmi_profile_enable(inst, 0)
+    want = rows * (6 * obs + 4 * (act + 3))      # observations read, their bf16 copy written; scalars of a sample
+    for out in (act, 1):
+        dims = (obs, *hidden, out)
+        for l, (i, o) in enumerate(zip(dims, dims[1:])):
+            want += 2 * i * o * (2 if l else 1) + 2 * rows * o + (2 * rows * i * (2 if reads_back else 1) if l else 0)
+    assert launches == 1 and stated == want
+    g.gmi_buffer_destroy(buf)
+    g.gmi_model_destroy(model)
+
+
 @pytest.mark.parametrize("obs,hidden", [(211, (512, 512, 256, 128)), (108, (400, 200, 100))])
 @pytest.mark.parametrize("act", [1, 2, 3, 4, 5, 7, 31, 32])
 @pytest.mark.parametrize("rows", [1, 3, 301])
