@@ -83,8 +83,10 @@ def test_gradient_equals_the_per_layer_kernels(g, inst, obs, act, hidden, dtype,
     (60, 8, (256, 128, 64), 63501),              # activations kept in LDS, 252 MB of them stored
     (108, 21, (400, 200, 100), 37201),           # read back from memory, 252 MB
     (211, 20, (512, 512, 256, 128), 30001),      # 369 MB: the weight gradients alone stream
+    (211, 20, (512, 512, 256, 128), 10177),      # (in the cache) 128 rows per workgroup, the first round five eighths full, a ragged tile
+    (211, 20, (512, 512, 512, 256), 32897),      # .., two full rounds and a third of two workgroups with one row
 ])
-def test_gradient_of_minibatches_that_no_cache_holds(g, inst, obs, act, hidden, rows):
+def test_gradient_of_large_minibatches(g, inst, obs, act, hidden, rows):
     """Beyond the memory-side cache activations and gradients are stored and read as streams.  The second of two minibatches, which finds the
     first one's lines wherever they were left, against the per-layer kernels; the band as above (same roundings, other order of sums)."""
     model, buf, keep = _setup(g, inst, obs, act, hidden, "bf16", 2, rows // 2 + 200, rows)
