@@ -377,7 +377,7 @@ constexpr int kWgradOperand = kWgradT * kWgradRows * 2; // bytes
 constexpr int kWgradStage = 2 * kWgradOperand;
 constexpr int kWgradRing = 5;
 constexpr int kWgradLds = kWgradRing * kWgradStage;
-constexpr int64_t kCacheBytes = (int64_t)240 << 20;      // beyond_cache: the rest of the 256 MB for weights, rows and partial gradients
+constexpr int64_t kCacheBytes = (int64_t)216 << 20;      // beyond_cache
 constexpr int kWgradGroups = 256, kSplitMin = 4, kSplitMax = 64, kWgradNarrow = 224;      // plan_wgrad
 __device__ const uint4 g_zero_piece = {0, 0, 0, 0};     // what rows past the end load
 
@@ -862,6 +862,10 @@ int launch_linear(gmi_instance* g, int dtype, int epi, int rows, const LinearBat
   }
 }
 
+// The rest of the cache holds weights, rows and partial gradients.  us per minibatch with its weight gradients and update, without / with the
+// streams: 60:256:128:64:8 49152 rows (195 MB) 96 / 98, 53248 109 / 108, 57344 (228 MB) 119 / 111, 65536 137 / 123; 108:400:200:100:21 30000
+// (204 MB) 126 / 137, 32768 (222 MB) 135 / 138, 34816 154 / 156, 36000 (244 MB) 160 / 155, 65536 282 / 258; 108:200:400:100:21 32768 136 / 142,
+// 40960 177 / 173.
 bool beyond_cache(const ModelLayout& L, int rows) {
   int64_t n = 0;
   bool shared = false;
@@ -870,14 +874,18 @@ bool beyond_cache(const ModelLayout& L, int rows) {
       n += li.in_pad + li.out_pad;
       shared = shared || wgrad_tiles(li.out_pad, li.in_pad) >= 4;
     }
-  // Matrices of four tiles and more, which read the same rows through the die's cache, lose more by the streams: us per iteration without /
-  // with them, 211:512:512:256:128:20, 24576 rows (302 MB) 2838 / 2890, 32768 (403 MB) 12684 / 12626, 65536 3062 / 3040.
+  // Matrices of four tiles and more read the same rows through the die's cache, and only the weight gradients of their shapes stream: up to
+  // half as much again no difference beyond the runs' own, above it a gain.  211:512:512:256:128:20 20480 rows (252 MB) 211 / 213, 24576 (302 MB)
+  // 232 / 228 and 233 / 236, 28672 (352 MB) 267 / 264, 32768 286 / 280, 36864 350 / 336, 40960 375 / 356, 65536 514 / 508;
+  // 211:512:512:512:256:20 20480 298 / 302, 24576 307 / 302, 32768 353 / 350, 40960 495 / 488, 65536 678 / 678.
   return 2 * n * rows > (shared ? kCacheBytes / 2 * 3 : kCacheBytes);
 }
 
 // Splits of each layer's rows such that its workgroups read about as much as any other's: as many workgroups in all as keep the
 // launch in one round of one per compute unit.  A workgroup's time goes by the bytes of its rows, its tile's features of both operands
-// (a stage of few features is bound by the round trip instead: kWgradNarrow), and with the same splits for all layers the launch
+// (a stage of few features is bound by the round trip instead, as if it had kWgradNarrow of them: us per minibatch with update for 32 / 192 /
+// 224 / 320, 60:256:128:64:8 4096 rows 31.5 / 31.6 / 30.4 / 30.9, 108:200:400:100:21 32768 rows 132 / 137 / 132 / 139, 108:400:200:100:21 134.8 /
+// 133.9 / 134.5 / 137.3; 512-wide shapes within 1 %), and with the same splits for all layers the launch
 // took as long as the widest tile's.  No layer forms fewer partial sums of its rows (splits times wgrad_sums) than the same splits for all would:
 // each addition rounds.  Error of the weights' gradients against 64-bit sums, root mean square over the tensors, 32768 rows as collected, with
 // the same splits / per layer, one sum each / as it is: 60:256:128:64:8 7.7e-8 / 7.6e-8 / 6.5e-8, 108:400:200:100:21 1.13e-7 / 1.15e-7 / 0.94e-7,

@@ -99,7 +99,10 @@ struct TileShape {
 // (from memory they were 59 of the 219 MB that 32768 rows of 60:256:128:64:8 moved), and a layer's results do not go where its input
 // lies, so one barrier per layer is enough.  Area l: layer l's input, then the gradient at it; area NL: the heads' gradient.  The
 // first layer's area has no gradient and serves the loss as its transposition buffers.  For shapes of which two workgroups fit a
-// compute unit that way (kKeepBytes): with one (108:400:200:100:21) nothing covers a wave's waits.
+// compute unit that way (kKeepBytes): with one (108:400:200:100:21) nothing covers a wave's waits.  Agents' kernels that run beside the trainer
+// find less LDS free, but lose nothing by it: lag-1 iterations of 60:256:128:64:8, us kept / read from memory, four agents of 4096
+// envs (16 steps, four epochs of 32768 rows) unmasked 2609 / 2776, on 32 compute units each 2519 / 2685, apart from the trainer 4769 / 5056; one
+// agent 646 / 686, 614 / 642 and 713 / 725.
 template <int ROWS, int... DIMS>
 struct TileShapeKeep : TileShape<ROWS, DIMS...> {
   using B = TileShape<ROWS, DIMS...>;
@@ -118,10 +121,9 @@ struct TileShapeKeep : TileShape<ROWS, DIMS...> {
 };
 constexpr size_t kKeepBytes = 80 * 1024;
 
-// The same with streaming stores (write-through either way), for minibatches whose activations no cache holds until they are read.  us per
-// iteration, with the weight gradients' streaming loads, without / with: 65536 rows of 108:400:200:100:21 1601 / 1464 (two epochs), 45056 1645
-// / 1581, 32768 3160 / 3222, 16384 1600 / 1758; 60:256:128:64:8 65536 953 / 885, 32768 619 / 664.  Not for the 512-wide shapes (24576 rows of
-// 211:512:512:256:128:20 2730 / 2813), whose weight gradients alone stream: 32768 12460 / 12300.
+// The same with streaming stores (write-through either way), for minibatches whose activations no cache holds until they are read
+// (beyond_cache, with figures).  Not for the 512-wide shapes (24576 rows of 211:512:512:256:128:20, us per iteration without / with 2730 / 2813),
+// whose weight gradients alone stream.
 template <class B>
 struct TileShapeStream : B {
   static constexpr int store_aux = 19;
