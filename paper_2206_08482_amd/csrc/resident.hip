@@ -638,27 +638,29 @@ namespace gmi {
 
 bool resident_supported(const ModelLayout& L) { return shape_ok(L); }
 // Where a row-tile kernel is compiled for the shape too.  Per minibatch with Adam, us, this kernel / that one:
-//   60:256:128:64:8: 32.2 / 28.4 at 1000 rows, 44.9 / 30.9 at 4096, 50.1 / 34.1 at 8192, 54.7 / 41.9 at 12288, 56.1 / 46.4 at 16384,
-//     where each of this kernel's workgroups has one tile; on 128 compute units 52.5 / 41.9 at 8192; on 120 33.9 / 32.2 at 1000,
-//     76.9 / 53.7 at 7680; on 96 34.8 / 32.0 at 1000, 45.3 / 42.4 at 3000, 52.5 / 47.9 at 6144; on 80 40.2 / 40.4 at 1304,
-//     41.4 / 46.2 at 2000, 46.8 / 52.3 at 3000, 78.6 / 60.2 at 5120; on 64 32.1 / 30.2 at 504, 34.8 / 34.1 at 752, 35.9 / 35.0 at 1000,
-//     40.7 / 41.1 at 1504, 41.7 / 46.9 at 2000, 48.2 / 52.0 at 4096; on 32 36.9 / 34.8 at 256, 37.9 / 39.0 at 384, 43.5 / 48.9 at
-//     1000, 49.6 / 70.4 at 2048; on 16 46.8 / 44.0 at 128, 46.8 / 48.2 at 256, 59.1 / 78.6 at 1024; on 8 64.6 / 61.8 at 64,
-//     65.7 / 66.1 at 128, 77.9 / 97.3 at 512;
-//   108:400:200:100:21: 47.7 / 43.0 at 1000, 50.8 / 46.8 at 4096, 63.5 / 54.6 at 8192; on 128 compute units 65.0 / 54.6 at 4096; on 64
-//     64.6 / 61.3 at 1024, 77.9 / 67.2 at 2048; on 8 179 / 168 at 256;
-//   211:512:512:256:128:20: 75.9 / 70.9 at 1000, 86.2 / 80.8 at 4096; on 64 compute units 129 / 124 at 1000; on 8 450 / 447 at 128;
-//   211:512:512:512:256:20: 93.3 / 89.7 at 1000, 104.7 / 102.2 at 4096; on 64 compute units 162 / 158 at 1024; on 8 628 / 626 at 128.
-// So this kernel serves such a shape only on fewer than 96 compute units, where it keeps the gradients in registers, from 12 rows per
-// compute unit on (the first of the sizes above at which it is no slower, within 3 %) and while every tile has a workgroup of its own
-// (one per net and two of the instance's compute units; 128-row tiles).  Between 64 and 96 compute units the tallest tiles lose and the
-// lower ones win (80, above); one line for both, where most sizes win.
+//   60:256:128:64:8: 31.4 / 27.5 at 1000 rows, 41.5 / 29.8 at 4096, 49.1 / 33.7 at 8192, 55.7 / 41.7 at 16384; on 128 compute units 52.0 / 42.2
+//     at 8192; on 120 33.2 / 29.9 at 1000; on 96 33.3 / 29.7 at 1000, 43.5 / 37.2 at 3000, 49.1 / 47.2 at 6144;
+//     on 88 41.1 / 39.7 at 1760, 66.7 / 47.5 at 2816, 78.1 / 60.5 at 5632; on 80 40.6 / 39.0 at 1304, 41.2 / 42.8 at 1600, 41.5 / 40.0 at 1800, 41.9 / 44.5 at 2000,
+//     66.4 / 48.6 at 2560, 47.4 / 48.0 at 3000, 47.3 / 51.2 at 3840, 78.2 / 59.8 at 4480; on 72 40.9 / 39.5 at 1440, 66.6 / 50.2 at 2304,
+//     47.4 / 50.4 at 3456, 78.2 / 59.8 at 4608; on 64 34.0 / 32.3 at 752, 35.4 / 33.4 at 1000, 40.3 / 38.9 at 1280, 40.3 / 40.0 at 1536,
+//     41.1 / 40.4 at 1792, 42.2 / 45.2 at 2000, 47.2 / 48.6 at 3000, 48.0 / 49.7 at 4096; on 48 41.6 / 44.9 at 960, 67.6 / 55.0 at 1152, 81.3 /
+//     76.7 at 3072; on 32 34.7 / 31.7 at 256, 35.3 / 36.0 at 512, 42.1 / 41.5 at 640, 42.2 / 42.4 at 768, 42.2 / 46.2 at 1000, 49.1 / 66.8 at
+//     2048; on 16 42.3 / 42.6 at 192, 42.3 / 43.3 at 256, 49.1 / 48.9 at 384, 48.8 / 53.1 at 512, 55.3 / 74.9 at 1024; on 8 56.3 / 55.7 at 96,
+//     62.4 / 62.6 at 192, 63.0 / 67.5 at 256, 69.7 / 89.3 at 512;
+//   108:400:200:100:21: 44.8 / 41.8 at 1000, 60.7 / 50.1 at 8192; on 64 compute units 62.1 / 59.1 at 1024, 79.6 / 68.0 at 2048; on 8 155 / 144
+//     at 256;
+//   211:512:512:256:128:20: 77.0 / 72.8 at 1000, 84.5 / 79.3 at 4096; on 64 compute units 119 / 114 at 1000; on 8 356 / 353 at 128;
+//   211:512:512:512:256:20: 94.8 / 90.0 at 1000, 105 / 102 at 4096; on 64 compute units 148 / 143 at 1000; on 8 493 / 490 at 128.
+// So this kernel serves such a shape only on fewer than 96 compute units, where it keeps the gradients in registers, from 24 rows per
+// compute unit on (12 on fewer than 64), and while every workgroup (two per row tile) has a compute unit at once.  Of those that the four shader engines of a
+// die do not share evenly (2816 rows on 88 compute units, 2560 on 80, 2304 on 72, 1152 on 48) not all get one: a second round.
 bool use_resident(const ModelLayout& L, int rows, int cus) {
   if (!shape_ok(L)) return false;
   if (!chain_compiled(L)) return true;
-  if (cus >= 96 || grad_sets(L) == 0 || rows < 12 * (int64_t)cus) return false;
+  if (cus >= 96 || grad_sets(L) == 0 || rows < (cus < 64 ? 12 : 24) * (int64_t)cus) return false;
   Plan p;
-  return rows <= 32 * (int64_t)pick_tiles(L, INT32_MAX, 1, &p) * trainer_groups(cus);
+  const int height = 32 * pick_tiles(L, rows, trainer_groups(cus), &p), groups = 2 * ((rows + height - 1) / height);
+  return groups <= (cus < 32 ? cus : cus / 32 * 32);
 }
 
 // Rows of gradient partials the kernel may fill with this model.

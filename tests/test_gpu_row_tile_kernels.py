@@ -201,6 +201,22 @@ def test_gradient_on_eight_compute_units_equals_the_per_layer_kernels(g, obs, ac
     g.gmi_destroy(masked)
 
 
+@pytest.mark.parametrize("cus,rows", [(8, 95), (8, 96), (8, 512), (8, 513), (80, 1919), (80, 2000), (80, 2560)])
+def test_gradient_at_the_line_between_the_trainer_kernels(g, cus, rows):
+    """60:256:128:64:8 on few compute units: both sides of the rule between the resident and the row-tile kernel."""
+    from paper_2206_08482_amd.instances import cu_masks
+    masked = g.gmi_create(cu_masks(256, [cus])[0])
+    N = (rows + 1) // 2
+    model, buf, keep = _setup(g, masked, 60, 8, (256, 128, 64), "bf16", 2, N, rows)
+    a, sa = _gradients(g, masked, model, buf, keep[0].numel(), 2, N, rows, 1)
+    b, sb = _gradients(g, masked, model, buf, keep[0].numel(), 2, N, rows, 0)
+    assert np.isfinite(a).all() and rel_l2(a, b) <= 5e-3 and rel_max(a, b) <= 2e-2      # the bf16 band above
+    assert np.allclose(sa, sb, rtol=5e-3, atol=5e-3)
+    g.gmi_buffer_destroy(buf)
+    g.gmi_model_destroy(model)
+    g.gmi_destroy(masked)
+
+
 @pytest.mark.parametrize("obs,act,hidden,n,shift", [
     (1, 1, [32], 1, 0),                       # one column, one action, one row
     (45, 12, [128, 128], 31, 0),              # rows of an odd length: 16-byte pieces span two rows
