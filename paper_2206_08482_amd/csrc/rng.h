@@ -35,6 +35,26 @@ __device__ __forceinline__ Words4 philox4x32_10(uint32_t c0, uint32_t c1, uint32
   return o;
 }
 
+// num / den, correctly rounded, y within an ulp of 1 / den: a Newton-Raphson step for the reciprocal, then two corrections of the quotient
+// by its exact residual (Markstein's division; a den of all ones, of j = 8388607, is the theorem's exception: there y has to be the nearest one,
+// which the unit gives).  No scaling: these operands -- 0 or at least 2^-24 over a number between 1.7 and 2.5 -- never need it.
+__host__ __device__ __forceinline__ float quotient_from(float y, float num, float den) {
+#pragma clang fp contract(off)
+  y = fmaf(fmaf(-den, y, 1.0f), y, y);
+  float t = num * y;
+  t = fmaf(fmaf(-den, t, num), y, t);
+  return fmaf(fmaf(-den, t, num), y, t);
+}
+// sqrt(x), correctly rounded, r0 within an ulp of it: the product of two neighbours lies beside the square of the number half way between
+// them by less than x's own spacing, so the sign of x - (neighbour) * r0, formed without rounding, says on which side of it the root is
+// (Tuckerman's test).  x is between 1e-7 and 34: no scaling.
+__host__ __device__ __forceinline__ float root_from(float r0, float x) {
+  const uint32_t bits = __builtin_bit_cast(uint32_t, r0);
+  const float down = __builtin_bit_cast(float, bits - 1u), up = __builtin_bit_cast(float, bits + 1u);
+  const float r = fmaf(-down, r0, x) <= 0.0f ? down : r0;
+  return fmaf(-up, r0, x) > 0.0f ? up : r;
+}
+
 // Two words -> two standard normals.  Every floating-point step is one correctly rounded
 // add / multiply / divide / sqrt in the order written: contraction into FMA is switched off so that
 // a CPU implementation of the same recipe reproduces the bits.
@@ -44,8 +64,9 @@ __device__ __forceinline__ Words4 philox4x32_10(uint32_t c0, uint32_t c1, uint32
 //   sin x / cos x by Taylor polynomials of degree 13 / 14, rotated by the quadrant.
 // Draws are bound by their instructions (env_step, the collections): without the scaling of the general divide and square root, with
 // the quadrant by sign bits and the generator's xors three at a time a block of four takes 226 vector instructions and 31 scalar ones
-// instead of 268 and 60; the results for all 2^23 radii and angles are the same.  Collections in which the draws are part of the chain, us: 8:32:32:2 (64 envs, 16 steps) 67 ->
-// 64, 108:400:200:100:21 (4096 envs, 32 steps) 388 -> 355.
+// instead of 268 and 60.  Quotient and root are correctly rounded for every radius, whichever estimates the units give within the ulp that
+// they are specified to (the host checks go through all of them).  Collections in which the draws are part of the chain, us: 8:32:32:2 (64 envs, 16
+// steps) 67 -> 64, 108:400:200:100:21 (4096 envs, 32 steps) 388 -> 355.
 __device__ __forceinline__ void normal_pair(uint32_t wa, uint32_t wb, float& z0, float& z1) {
 #pragma clang fp contract(off)
   const uint32_t j = ((wa >> 9) << 1) | 1u;
@@ -54,14 +75,8 @@ __device__ __forceinline__ void normal_pair(uint32_t wa, uint32_t wb, float& z0,
   int e = (int)(bits >> 23) - 127;
   float m = __uint_as_float((bits & 0x7FFFFFu) | 0x3F800000u);
   if (m > 0x1.6a09e6p+0f) { m = m * 0.5f; e += 1; }
-  // (m - 1) / (m + 1), correctly rounded: the steps of a general division without its scaling, which these operands -- 0 or at
-  // least 2^-24 over a number between 1.7 and 2.5 -- never need
   const float num = m - 1.0f, den = m + 1.0f;
-  float y = __builtin_amdgcn_rcpf(den);
-  y = fmaf(fmaf(-den, y, 1.0f), y, y);
-  float t = num * y;
-  t = fmaf(fmaf(-den, t, num), y, t);
-  t = fmaf(fmaf(-den, t, num), y, t);
+  const float t = quotient_from(__builtin_amdgcn_rcpf(den), num, den);
   const float t2 = t * t;
   float p = 0x1.745d18p-4f;
   p = p * t2 + 0x1.c71c72p-4f;
@@ -73,13 +88,8 @@ __device__ __forceinline__ void normal_pair(uint32_t wa, uint32_t wb, float& z0,
   const float lnm = q + q;
   const float k = (float)(e - 24);
   const float lnu = k * 0x1.62e4p-1f + (k * 0x1.7f7d1cp-20f + lnm);
-  // sqrt(-2 ln u1), correctly rounded: the unit's root is within one ulp, the exact sign of x - (one ulp beside it) * it decides.  x is
-  // between 1e-7 and 34: no scaling
   const float x2l = lnu * -2.0f;
-  const float r0 = __builtin_amdgcn_sqrtf(x2l);
-  const float down = __uint_as_float(__float_as_uint(r0) - 1u), up = __uint_as_float(__float_as_uint(r0) + 1u);
-  float r = fmaf(-down, r0, x2l) <= 0.0f ? down : r0;
-  r = fmaf(-up, r0, x2l) > 0.0f ? up : r;
+  const float r = root_from(__builtin_amdgcn_sqrtf(x2l), x2l);
 
   const uint32_t jf = (((wb >> 7) & 0x7FFFFFu) << 1) | 1u;
   const float f = (float)jf * 0x1p-24f;

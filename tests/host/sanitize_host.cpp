@@ -115,6 +115,26 @@ int main() {
       CHECK(groups <= 256 || tiles > 32);
     }
   }
+  {
+    // the quotient and the root of a draw: for every radius and every estimate within an ulp what IEEE division and square root give (at the
+    // theorem's exception with the reciprocal unit's own, see quotient_from)
+    const auto ulps = [](float v, int d) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, v) + (uint32_t)d); };
+    int64_t quotients = 0, roots = 0;
+    for (uint32_t j = 1; j < 1u << 24; j += 2) {
+      int e;
+      const float f = 2.0f * frexpf((float)j, &e), m = f > 0x1.6a09e6p+0f ? f * 0.5f : f, num = m - 1.0f, den = m + 1.0f;
+      const float t = num / den, y = (float)(1.0 / (double)den);
+      for (int d = -1; d <= 1; ++d)
+        if (j == 8388607 ? d == 0 : fabs((double)ulps(y, d) * den - 1.0) <= (double)(ulps(y, 1) - y) * den)
+          quotients += gmi::quotient_from(ulps(y, d), num, den) != t;
+    }
+    for (uint32_t bits = 0x3F800000u; bits < 0x40800000u; ++bits) {      // [1, 4): every mantissa under an even and an odd exponent
+      const float x = __builtin_bit_cast(float, bits), r = sqrtf(x);
+      for (int d = -1; d <= 1; ++d) roots += gmi::root_from(ulps(r, d), x) != r;
+    }
+    CHECK(quotients == 0);
+    CHECK(roots == 0);
+  }
   std::printf(fails ? "host checks: %d failed\n" : "host checks passed\n", fails);
   return fails ? 1 : 0;
 }

@@ -79,6 +79,17 @@ def test_noise_is_bit_exact(g, inst, n, dim, stream, step, off):
     assert np.array_equal(got.view(np.uint32), ref.view(np.uint32))
 
 
+def test_noise_of_the_radius_at_the_exception_of_the_division(g, inst):
+    """j = 8388607, den 2 - 2^-23: the one radius whose quotient depends on which neighbour of 1 / den the reciprocal unit gives."""
+    seed, stream, step, env = 42, 1, 7, 2862324
+    word = px.words_field(seed, stream, step, 1, 1, env)[2][0, 0]
+    assert 2 * (int(word) >> 9) + 1 == 8388607
+    out = zeros(1, 4)
+    g.gmi_noise_fill(inst, seed, stream, step, env, 1, 4, out)
+    g.gmi_sync(inst)
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), px.normal_field(seed, stream, step, 1, 4, env_offset=env).view(np.uint32))
+
+
 @pytest.mark.parametrize("n", [1, 2, 3, 64, 1000, 1024, 65536, 100003])
 def test_shuffle_is_bit_exact(g, inst, n):
     out = zeros(n, dtype=torch.int32)
