@@ -651,13 +651,14 @@ bool resident_supported(const ModelLayout& L) { return shape_ok(L); }
 //     at 256;
 //   211:512:512:256:128:20: 77.0 / 72.8 at 1000, 84.5 / 79.3 at 4096; on 64 compute units 119 / 114 at 1000; on 8 356 / 353 at 128;
 //   211:512:512:512:256:20: 94.8 / 90.0 at 1000, 105 / 102 at 4096; on 64 compute units 148 / 143 at 1000; on 8 493 / 490 at 128.
-// So this kernel serves such a shape only on fewer than 96 compute units, where it keeps the gradients in registers, from 24 rows per
-// compute unit on (12 on fewer than 64), and while every workgroup (two per row tile) has a compute unit at once.  Of those that the four shader engines of a
+// So this kernel serves such a shape only on fewer than 96 compute units, where it keeps the gradients in registers, from 12 rows per
+// compute unit on (one line for all: up to 24 rows it loses up to 6 % on 64 to 88 compute units and wins up to 7 % on fewer), and while
+// every workgroup (two per row tile) has a compute unit at once.  Of those that the four shader engines of a
 // die do not share evenly (2816 rows on 88 compute units, 2560 on 80, 2304 on 72, 1152 on 48) not all get one: a second round.
 bool use_resident(const ModelLayout& L, int rows, int cus) {
   if (!shape_ok(L)) return false;
   if (!chain_compiled(L)) return true;
-  if (cus >= 96 || grad_sets(L) == 0 || rows < (cus < 64 ? 12 : 24) * (int64_t)cus) return false;
+  if (cus >= 96 || grad_sets(L) == 0 || rows < 12 * (int64_t)cus) return false;
   Plan p;
   const int height = 32 * pick_tiles(L, rows, trainer_groups(cus), &p), groups = 2 * ((rows + height - 1) / height);
   return groups <= (cus < 32 ? cus : cus / 32 * 32);

@@ -83,7 +83,7 @@ def test_gradient_equals_the_per_layer_kernels(g, inst, obs, act, hidden, dtype,
     (60, 8, (256, 128, 64), 63501),              # activations kept in LDS, 252 MB of them stored
     (108, 21, (400, 200, 100), 37201),           # read back from memory, 252 MB
     (211, 20, (512, 512, 256, 128), 30001),      # 369 MB: the weight gradients alone stream
-    (211, 20, (512, 512, 256, 128), 10177),      # (in the cache) 128 rows per workgroup, the first round five eighths full, a ragged tile
+    (211, 20, (512, 512, 256, 128), 26753),      # 128 rows per workgroup, a second round five eighths full, a last tile of one row
     (211, 20, (512, 512, 512, 256), 32897),      # .., two full rounds and a third of two workgroups with one row
 ])
 def test_gradient_of_large_minibatches(g, inst, obs, act, hidden, rows):
@@ -201,7 +201,7 @@ def test_gradient_on_eight_compute_units_equals_the_per_layer_kernels(g, obs, ac
     g.gmi_destroy(masked)
 
 
-@pytest.mark.parametrize("cus,rows", [(8, 95), (8, 96), (8, 512), (8, 513), (80, 1919), (80, 2000), (80, 2560)])
+@pytest.mark.parametrize("cus,rows", [(8, 95), (8, 96), (8, 512), (8, 513), (80, 959), (80, 2000), (80, 2560)])
 def test_gradient_at_the_line_between_the_trainer_kernels(g, cus, rows):
     """60:256:128:64:8 on few compute units: both sides of the rule between the resident and the row-tile kernel."""
     from paper_2206_08482_amd.instances import cu_masks
