@@ -1118,18 +1118,18 @@ bool shape_matches(const ModelLayout& L) {
 }
 
 // The widest shapes: 128 samples per workgroup, which read the weights half as often, where the last round of such workgroups (one per
-// compute unit) is at least five eighths full, or where on most of the card two full rounds come before it; else 64, of which two
-// share a compute unit.  A minibatch with its weight gradients and update, us, 64 / 128 rows, of 211:512:512:256:128:20: 8192 rows 96 /
-// 106, 10240 120 / 115, 12288 127 / 125, 16384 155 / 147, 18432 201 / 225, 20000 199 / 207, 22528 231 / 242, 24576 224 / 225, 26624 267 /
+// compute unit) is at least five eighths full (the only one: three quarters), or where on most of the card two full rounds come before
+// it; else 64, of which two share a compute unit.  A minibatch with its weight gradients and update, us, 64 / 128 rows, of 211:512:512:256:128:20: 8192 rows 96 /
+// 106, 9216 122 / 126, 10240 120 / 115 and 127 / 130 (two boxes), 12288 127 / 125, 16384 155 / 147, 18432 201 / 225, 20000 199 / 207, 22528 231 / 242, 24576 224 / 225, 26624 267 /
 // 257, 28000 262 / 251, 32768 298 / 274, 34816 364 / 347, 40960 363 / 350, 49152 428 / 401, 65536 564 / 522; on 192 compute units
 // 18432 210 / 226, 20480 241 / 237, 27648 323 / 317, 30720 342 / 330; on 128 4096 95 / 110, 5120 117 / 114, 12288 175 / 195, 13312 201 / 198,
 // 18432 263 / 275, 20480 277 / 282, 32768 398 / 371; on 64 2048 122 / 137, 2560 145 / 143, 4096 153 / 151, 6144 193 / 211, 6656 219 / 214,
-// 8192 229 / 224, 10240 270 / 285, 16384 395 / 379.  Of 211:512:512:512:256:20: 8192 128 / 138, 10240 161 / 150, 16384 221 / 193, 18432 270 / 289,
-// 20000 277 / 266 (the one size of these at which the rule takes the side that is more than 3 % slower), 24576 311 / 302, 26624 361 / 322,
+// 8192 229 / 224, 10240 270 / 285, 16384 395 / 379.  Of 211:512:512:512:256:20: 8192 128 / 138, 10240 161 / 150 and 169 / 167, 16384 221 / 193, 18432 270 / 289,
+// 20000 277 / 266 (at this size and at 10240 the rule takes the side that is 4 and 1 to 7 % slower), 24576 311 / 302, 26624 361 / 322,
 // 34816 466 / 444, 65536 757 / 662; on 64 6144 256 / 273, 6656 290 / 274, 10240 365 / 376.
 inline bool wide_rows(int rows, int cus) {
   const int n = 2 * ((rows + 127) / 128), last = (n - 1) % cus + 1;      // workgroups, of the last round
-  return 8 * last >= 5 * cus || (n > 2 * cus && cus >= 192);
+  return n <= cus ? 4 * last >= 3 * cus : 8 * last >= 5 * cus || (n > 2 * cus && cus >= 192);
 }
 
 template <class S>
