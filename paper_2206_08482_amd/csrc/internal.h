@@ -249,6 +249,7 @@ struct gmi_model {
   float* grad_part;
   gmi::WgradSplits split;      // most row splits of each layer's weight gradient (bf16) ..
   int n_split_max;  // .. and of any (fp32: of all)
+  int n_split_even;            // the same splits for all layers (bf16)
   int part_rows;    // rows of grad_part (at least n_split_max)
   float* stat_part; // [n_split_max, 8]
 };
@@ -476,7 +477,8 @@ bool beyond_cache(const ModelLayout& L, int rows);
 // Sums over the rows that a wave of wgrad_bf16_kernel forms of each result: two where its tiles, at most four of 32 x 32, leave half of its
 // accumulators over.
 __host__ __device__ static inline int wgrad_sums(int out_pad, int in_pad) { return wgrad_tile(out_pad) > 128 && wgrad_tile(in_pad) > 128 ? 1 : 2; }
-// Row splits per layer of a weight-gradient launch (mlp.hip).
+// Row splits of a weight-gradient launch over so many tiles: the same for all layers, and per layer (mlp.hip).
+int even_splits(int n_tiles);
 WgradSplits plan_wgrad(const int* out_pad, const int* in_pad, int n);
 constexpr int kLossBlocksMax = 2048; // workgroups of the loss kernel
 constexpr int kStatRowsMax = 8192;   // rows of per-workgroup loss statistics (one more row holds their sum)

@@ -881,6 +881,8 @@ bool beyond_cache(const ModelLayout& L, int rows) {
   return 2 * n * rows > (shared ? kCacheBytes / 2 * 3 : kCacheBytes);
 }
 
+int even_splits(int n_tiles) { return std::min(std::max(kWgradGroups / n_tiles / 4 * 4, 2 * kSplitMin), kSplitMax / 2); }
+
 // Splits of each layer's rows such that its workgroups read about as much as any other's: as many workgroups in all as keep the
 // launch in one round of one per compute unit.  A workgroup's time goes by the bytes of its rows, its tile's features of both operands
 // (a stage of few features is bound by the round trip instead, as if it had kWgradNarrow of them: us per minibatch with update for 32 / 192 /
@@ -898,8 +900,7 @@ WgradSplits plan_wgrad(const int* out_pad, const int* in_pad, int n) {
     feats[i] = std::max(wgrad_tile(out_pad[i]) + wgrad_tile(in_pad[i]), kWgradNarrow);
     all += tiles[i];
   }
-  // the same for all, in fours
-  const int same = std::min(std::max(kWgradGroups / all / 4 * 4, 2 * kSplitMin), kSplitMax / 2);
+  const int same = even_splits(all);
   for (int i = 0; i < n; ++i) {
     r.n[i] = same / wgrad_sums(out_pad[i], in_pad[i]);
     used += tiles[i] * r.n[i];

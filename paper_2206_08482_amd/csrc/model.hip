@@ -394,10 +394,11 @@ extern "C" int gmi_model_bind(gmi_t g, const gmi_model_desc* d, float* params, v
         in_pad[n++] = L.net[net][l].in_pad;
       }
     m->split = gmi::plan_wgrad(out_pad, in_pad, n);
+    int n_tiles = 0;
+    for (int i = 0; i < n; ++i) n_tiles += gmi::wgrad_tiles(out_pad[i], in_pad[i]);
+    m->n_split_even = gmi::even_splits(n_tiles);
     if (L.dtype == GMI_DTYPE_F32) {
-      int n_tiles = 0;
-      for (int i = 0; i < n; ++i) n_tiles += gmi::wgrad_tiles(out_pad[i], in_pad[i]);
-      m->n_split_max = std::min(std::max(256 / n_tiles / 4 * 4, 8), 32);
+      m->n_split_max = m->n_split_even;
     } else {
       m->n_split_max = *std::max_element(m->split.n, m->split.n + n);
     }

@@ -548,7 +548,7 @@ struct PartRows {
 // Leaves gradient partials in m->grad_part / m->stat_part; their numbers of rows follow from the path, and with that from
 // the instance's switch and compute units.
 int minibatch_pass(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_hparams* hp, const int32_t* idx,
-                   int rows, int cus, bool want_grad, PartRows* parts, int* n_loss_blocks_out, bool obs16_ready = false) {
+                   int rows, int cus, bool want_grad, PartRows* parts, int* n_loss_blocks_out, bool obs16_ready = false, int replicas = 1) {
   const ModelLayout& L = m->L;
   const bool bf = L.dtype == GMI_DTYPE_BF16;
   int rc = GMI_ERR_UNSUPPORTED;
@@ -591,7 +591,10 @@ int minibatch_pass(gmi_instance* g, gmi_model* m, gmi_buffer* b, const gmi_ppo_h
       p.x = m->h[net][l]; p.ldx = li.in_pad;
       p.out = li.out; p.in = li.in; p.out_pad = li.out_pad; p.in_pad = li.in_pad;
       p.w_off = li.part_w; p.b_off = li.part_b;
-      const int most = std::min<int>(m->split.n[wb.n - 1], (rows + 63) / 64);      // at least 64 rows each
+      int most = std::min<int>(m->split.n[wb.n - 1], (rows + 63) / 64);      // at least 64 rows each
+      // one Adam launch reads the partials of all replicas, which takes longer than the splits save.  (Four of 60:256:128:64:8 with 8192 rows
+      // each, us of Adam with the splits per layer / no more than even ones: on 64 compute units each 27.0 / 20.0, unmasked 16.0 / 13.1.)
+      if (replicas > 1) most = std::min(most, m->n_split_even);
       p.chunk = ((rows + most - 1) / most + 31) / 32 * 32;
       p.n_split = (rows + p.chunk - 1) / p.chunk;
       parts->split.n[wb.n - 1] = (uint8_t)p.n_split;
@@ -766,7 +769,7 @@ extern "C" int ppo_update_group(const gmi_t* gs, const gmi_model_t* ms, const gm
       int nlb[kMaxGroup];
       for (int i = 0; i < n; ++i) {
         rc = minibatch_pass(gs[i], ms[i], bs[i], hp, bs[i]->perm + perm_off + (int64_t)j * hp->minibatch, hp->minibatch,
-                            gmi::trainer_cus(gs[i], n), true, &parts[i], &nlb[i], obs16[i]);
+                            gmi::trainer_cus(gs[i], n), true, &parts[i], &nlb[i], obs16[i], n);
         if (rc != GMI_OK) return rc;
         // replica i's partials are complete: let instance 0 see them
         if (i > 0) {
