@@ -390,11 +390,12 @@ typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
 // allocates, and says so of a clobber; it does write m0 for instructions of its own, and has to know of this write.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-#define GMI_LOAD_TO_LDS(ADDRESS, ...)                                                                                             \
-  do { asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, " ADDRESS ::"s"(lds), __VA_ARGS__ : "m0", "memory"); } while (0)
-__device__ __forceinline__ void load_to_lds(const void* base, uint32_t off, uint32_t lds) { GMI_LOAD_TO_LDS("%2", "v"(off), "s"(base)); }
-__device__ __forceinline__ void load_to_lds(const void* src, uint32_t lds) { GMI_LOAD_TO_LDS("off", "v"(src)); }
-#undef GMI_LOAD_TO_LDS
+__device__ __forceinline__ void load_to_lds(const void* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "m0", "memory");
+}
+__device__ __forceinline__ void load_to_lds(const void* src, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "m0", "memory");
+}
 // Four of the first kind, from base + off[k] to lds + 1024 k; STREAM: streaming loads.
 template <bool STREAM>
 __device__ __forceinline__ void load4_to_lds(const void* base, const uint32_t (&off)[4], uint32_t lds) {

@@ -49,12 +49,16 @@ def test_kernel_attributes_are_set_per_device():
 
 
 def test_inline_assembly_names_the_registers_it_writes():
-    """Instructions that take an LDS address from m0 are preceded by a write of m0: the compiler has to be told."""
+    """Instructions that take an LDS address from m0 are preceded by a write of m0 in the same statement, and the compiler is told of it."""
     csrc = os.path.join(ROOT, "paper_2206_08482_amd", "csrc")
-    found = 0
+    in_statements = everywhere = 0
     for f in sorted(os.listdir(csrc)):
-        for stmt in re.findall(r"asm volatile\((.*?)\);", open(os.path.join(csrc, f)).read(), re.S):
-            if re.search(r"\bs_\w+ m0\b", stmt):
-                found += 1
+        text = open(os.path.join(csrc, f)).read()
+        everywhere += text.count("global_load_lds")
+        for stmt in re.findall(r"asm volatile\((.*?)\);", text, re.S):
+            loads, writes = stmt.count("global_load_lds"), len(re.findall(r"\bs_\w+ m0\b", stmt))
+            in_statements += loads
+            assert writes == loads, (f, stmt)
+            if writes:
                 assert re.search(r':[^:]*"m0"[^:]*$', stmt), (f, stmt)
-    assert found == 2
+    assert in_statements == everywhere > 0
