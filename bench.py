@@ -32,8 +32,8 @@ PEAK_FP32_TFLOPS = 157.3       # vector fp32
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs summarised in profiles/hbm_traffic_C2_C4.md (counter values
 # scaled by what the same counters read for a copy kernel of known size).  Keyed by (workload, class).
 MEASURED_TRAFFIC = {
-    ("C2", "chain_train"): 152.06e6, ("C2", "wgrad"): 148.00e6, ("C2", "fused_rollout"): 23.20e6,
-    ("C4", "chain_train"): 670.79e6, ("C4", "wgrad"): 549.07e6, ("C4", "adam"): 97.72e6,
+    ("C2", "chain_train"): 152.03e6, ("C2", "wgrad"): 147.99e6, ("C2", "fused_rollout"): 23.20e6,
+    ("C4", "chain_train"): 670.77e6, ("C4", "wgrad"): 531.13e6, ("C4", "adam"): 97.70e6,
 }
 
 
